@@ -98,23 +98,31 @@ void carve(int T, int B, int64_t sumL, int64_t emit, int64_t frames, int64_t ab,
 }
 }  // namespace
 
-const PlanTable& plan_table(int max_label, bool crowded, bool symbol_major)
+const Plans& plans()
 {
-    struct Entry { int max_label; bool crowded, symbol_major; PlanTable table; };
-    static std::mutex mutex;
-    static std::vector<Entry*> entries;
-    std::lock_guard<std::mutex> lock(mutex);
-    for (const Entry* e : entries)
-        if (e->max_label >= max_label && e->crowded == crowded && e->symbol_major == symbol_major) return e->table;
-    Entry* e = new Entry{max_label, crowded, symbol_major, {}};
-    for (int L = 0; L <= max_label; ++L) {
-        const WavePlan one = plan_waves(L, crowded), two = plan_waves2(L, crowded);
-        e->table.one[L] = static_cast<uint8_t>((one.waves - 1) | ((one.halo / 8) << 4) |
-                                               (two_pairs_per_lane(L, crowded, symbol_major) ? 128 : 0));
-        e->table.two[L] = static_cast<uint8_t>((two.waves - 1) | ((two.halo / 4) << 4));
-    }
-    entries.push_back(e);
-    return e->table;
+    static const Plans* const all = [] {
+        Plans* p = new Plans();
+        for (int crowded = 0; crowded < 2; ++crowded)
+            for (int L = 0; L <= CTC_MAX_LABEL_LENGTH; ++L) {
+                const WavePlan one = plan_waves(L, crowded), two = plan_waves2(L, crowded);
+                for (int symbol_major = 0; symbol_major < 2; ++symbol_major) {
+                    const bool pairs = two_pairs_per_lane(L, crowded, symbol_major);
+                    PlanTable& t = p->table[crowded][symbol_major];
+                    t.one[L] = static_cast<uint8_t>((one.waves - 1) | ((one.halo / 8) << 4) | (pairs ? 128 : 0));
+                    t.two[L] = static_cast<uint8_t>((two.waves - 1) | ((two.halo / 4) << 4));
+                    if (!crowded) {
+                        p->latency_waves[symbol_major][L] = static_cast<uint8_t>(pairs ? two.waves : one.waves);
+                        p->latency_waves_up_to[symbol_major][L] =
+                            (L > 0 ? p->latency_waves_up_to[symbol_major][L - 1] : 0) + p->latency_waves[symbol_major][L];
+                    }
+                }
+                p->most_waves[crowded][L] =
+                    static_cast<uint8_t>(std::max({L > 0 ? static_cast<int>(p->most_waves[crowded][L - 1]) : 1, one.waves, two.waves}));
+                p->barrier[L] = one.barrier;
+            }
+        return p;
+    }();
+    return *all;
 }
 
 ctc_status_t make_layout(int T, int B, int A, const int32_t* label_lengths,
@@ -318,57 +326,62 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
     uint8_t* labels8 = reinterpret_cast<uint8_t*>(image + lay.labels8);
 
     const bool symbol_major = emission_layout(c.A) == kEmitSymbolMajor;
+    const Plans& all_plans = plans();
     // Would the launch, planned for latency, put more than two wavefronts on every SIMD?
     int64_t latency_waves = 0;
-    for (int b = 0; b < c.B; ++b) {
-        const int L = c.label_lengths[b];
-        latency_waves += two_pairs_per_lane(L, false, symbol_major) ? plan_waves2(L).waves : plan_waves(L).waves;
-    }
+    for (int b = 0; b < c.B; ++b) latency_waves += all_plans.latency_waves[symbol_major][c.label_lengths[b]];
     const bool crowded = latency_waves * (c.mode == Mode::kGrad ? 2 : 1) > kCrowdedWaves;
+    const PlanTable& plan_of = all_plans.table[crowded][symbol_major];
 
+    // The labels travel as bytes where a symbol fits one and as words otherwise (launch_setup, NarrowImage).
+    const bool byte_labels = c.A <= kByteLabelsMaxA;
+    const int poll_budget = g_poll_budget.load(std::memory_order_relaxed);
     int64_t lab_off = 0, e_off = 0, ab_off = 0, f_off = 0;
     int n_run = 0, max_waves = 1, max_frames = 0, max_label = 0;
     bool needs_barrier = false;
     for (int b = 0; b < c.B; ++b) {
         const int L = c.label_lengths[b], Tb = c.input_lengths[b];
-        const int32_t* lab = c.flat_labels + lab_off;
-        int repeats = 0;
+        const int32_t* const lab = c.flat_labels + lab_off;
         max_label = std::max(max_label, L);
-        for (int i = 0; i < L; ++i) {
-            const int32_t s = lab[i];
-            if (s < 0 || s >= c.A || s == c.blank) return CTC_STATUS_INVALID_VALUE;
-            if (i > 0 && s == lab[i - 1]) ++repeats;
-            labels[lab_off + i] = s;
-            labels8[lab_off + i] = static_cast<uint8_t>(s);          // (meaningful for alphabets up to 256 symbols)
-        }
+        // (branch-free, so that the compiler makes vector code of it)
+        unsigned bad = 0;
+        int repeats = 0;
+        const unsigned A = static_cast<unsigned>(c.A);
+        const int32_t blank = c.blank;
+        for (int i = 0; i < L; ++i) bad |= (static_cast<unsigned>(lab[i]) >= A) | (lab[i] == blank);
+        for (int i = 1; i < L; ++i) repeats += lab[i] == lab[i - 1];
+        if (bad) return CTC_STATUS_INVALID_VALUE;
+        if (byte_labels)
+            for (int i = 0; i < L; ++i) labels8[lab_off + i] = static_cast<uint8_t>(lab[i]);
+        else if (L > 0)
+            std::memcpy(labels + lab_off, lab, static_cast<size_t>(L) * sizeof(int32_t));
         // An alignment exists iff every symbol gets a frame and equal neighbours a blank between them.
         const bool runs = Tb > 0 && Tb >= L + repeats;
-        Utt& m = meta[b];
+        Utt m;
         m.Tb = Tb;
         m.L = L;
         m.lab_off = static_cast<int32_t>(lab_off);
-        m.flags = (runs ? kUttRuns : 0) | (two_pairs_per_lane(L, crowded, symbol_major) ? kUttTwoPairs : 0) |
+        m.flags = (runs ? kUttRuns : 0) | (plan_of.two_pairs(L) ? kUttTwoPairs : 0) |
                   ((Tb > kLinearMaxFrames || tight_fit(Tb, L, repeats)) ? kUttLogDomain : 0);
         m.f_off = static_cast<int32_t>(f_off);
-        const WavePlan wp = plan_waves(L, crowded);
-        m.waves = wp.waves;
-        m.halo = wp.halo;
-        const WavePlan wp2 = plan_waves2(L, crowded);
-        m.waves2 = wp2.waves;
-        m.halo2 = wp2.halo;
-        m.poll_budget = g_poll_budget.load(std::memory_order_relaxed);
+        m.waves = plan_of.waves1(L);
+        m.halo = plan_of.halo1(L);
+        m.waves2 = plan_of.waves2(L);
+        m.halo2 = plan_of.halo2(L);
+        m.poll_budget = poll_budget;
         m.e_off = e_off;
         m.ab_off = ab_off;
         m.e_direct = emission_layout(c.A);
         m.e_pitch = m.e_direct == kEmitSymbolMajor ? Tb : L;
+        meta[b] = m;
         lab_off += L;
         e_off += static_cast<int64_t>(Tb) * (c.A <= kDirectMaxA ? c.A : L);
         f_off += Tb;
         ab_off += static_cast<int64_t>(Tb) * lattice_pitch(L);
         if (runs) {
             order[n_run++] = b;
-            max_waves = std::max(max_waves, std::max(wp.waves, wp2.waves));
-            needs_barrier = needs_barrier || wp.barrier;
+            max_waves = std::max({max_waves, m.waves, m.waves2});
+            needs_barrier = needs_barrier || all_plans.barrier[L];
             max_frames = std::max(max_frames, Tb);
         }
     }
@@ -381,12 +394,20 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
         const bool two = (meta[b].flags & (kUttTwoPairs | kUttLogDomain)) == kUttTwoPairs && c.mode != Mode::kBest;
         return two ? meta[b].waves2 : meta[b].waves;
     };
-    std::vector<int32_t> running(order, order + n_run);
-    std::stable_sort(running.begin(), running.end(), [&](int a, int b) {
-        return static_cast<int64_t>(meta[a].Tb) * chain_waves(a) > static_cast<int64_t>(meta[b].Tb) * chain_waves(b);
-    });
-    std::vector<int32_t> run_frames(static_cast<size_t>(n_run)), run_waves(static_cast<size_t>(n_run));
+    // (sorted as numbers: the weight, then the smaller utterance number first)
+    thread_local std::vector<uint64_t> by_weight;
+    by_weight.resize(static_cast<size_t>(n_run));
     for (int i = 0; i < n_run; ++i) {
+        const int b = order[i];
+        by_weight[i] = (~(static_cast<uint64_t>(meta[b].Tb) * chain_waves(b)) << 16) | static_cast<uint64_t>(b);
+    }
+    std::sort(by_weight.begin(), by_weight.end());
+    thread_local std::vector<int32_t> running, run_frames, run_waves;
+    running.resize(static_cast<size_t>(n_run));
+    run_frames.resize(static_cast<size_t>(n_run));
+    run_waves.resize(static_cast<size_t>(n_run));
+    for (int i = 0; i < n_run; ++i) {
+        running[i] = static_cast<int32_t>(by_weight[i] & 0xFFFF);
         run_frames[i] = meta[running[i]].Tb;
         run_waves[i] = chain_waves(running[i]);
     }
@@ -409,14 +430,16 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
         n_run > 0 && 2 * c.B <= kMaxTaskEntries && n_cu % kXcds == 0 && n_run * dirs + n_cu / 4 <= n_cu) {
         // The die of an utterance's chains: workgroup i runs on die i mod kXcds (order_chains puts an
         // utterance's two chains a multiple of kXcds entries apart).
-        std::vector<int> die_of(static_cast<size_t>(c.B), 0);
+        uint8_t die_of[kMaxTaskEntries / 2] = {};
         for (int i = 0; i < n_run * dirs; ++i)
-            if ((order[i] & 1) == 0) die_of[static_cast<size_t>(order[i] >> 1)] = i % kXcds;
+            if ((order[i] & 1) == 0) die_of[order[i] >> 1] = static_cast<uint8_t>(i % kXcds);
         // Chains end in the order of their frames, those that exchange between wavefronts a little later.
         auto ends_at = [&](int b) { return meta[b].Tb * (chain_waves(b) > 1 ? 5 : 4); };
-        std::vector<int32_t> ending(running);
-        std::stable_sort(ending.begin(), ending.end(), [&](int a, int b) { return ends_at(a) < ends_at(b); });
-        const int last_end = ends_at(ending.back());
+        // (ties in the run order: the low bits are the place in it)
+        uint64_t ending[kMaxTaskEntries / 2];
+        for (int i = 0; i < n_run; ++i) ending[i] = (static_cast<uint64_t>(ends_at(running[i])) << 16) | static_cast<uint64_t>(i);
+        std::sort(ending, ending + n_run);
+        const int last_end = static_cast<int>(ending[n_run - 1] >> 16);
         const int blocks = (c.T + kTaskRows - 1) / kTaskRows;
         auto data_blocks = [&](int b) { return (meta[b].flags & kUttRuns) ? (meta[b].Tb + kTaskRows - 1) / kTaskRows : 0; };
         auto add = [&](int info, int first, int count) {
@@ -435,8 +458,9 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
             // for inside the launch: only the workers of the chains' own die can take them, a sixteenth of the
             // chip, and with every utterance given to the workers the launch was measured to end 15 us after
             // its last chain, against a gradient launch of 7 us for the last fifth: that launch takes them.
-            for (int b : ending) {
-                if (die_of[static_cast<size_t>(b)] != die) continue;
+            for (int i = 0; i < n_run; ++i) {
+                const int b = running[ending[i] & 0xFFFF];
+                if (die_of[b] != die) continue;
                 if (static_cast<int64_t>(ends_at(b)) * 100 > static_cast<int64_t>(last_end) * share_percent) {
                     meta[b].flags |= kUttGradientLater;
                     continue;
@@ -469,7 +493,7 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
     out->dev_label_lengths = nullptr;
     out->dev_input_lengths = nullptr;
     out->dev_status = nullptr;
-    out->poll_budget = g_poll_budget.load(std::memory_order_relaxed);
+    out->poll_budget = poll_budget;
     out->crowded = crowded;
     out->sequential_chains = sequential_chains;
     out->n_tasks = n_tasks;
@@ -623,19 +647,16 @@ ctc_status_t run_device(const void* x, const int32_t* labels, const int32_t* lab
     p.dtype = dtype;
     p.n_run = B;                       // a lattice workgroup per utterance and direction; those that do not run leave at once
     p.n_chains = B * (grads ? 2 : 1);
-    p.max_waves = 1;
     const bool symbol_major = emission_layout(A) == kEmitSymbolMajor;
     // Would the launch, planned for latency, put more than two wavefronts on every SIMD (prepare's question)?  The
     // labels' lengths are on the GPU; the answer here is for lengths spread evenly up to the bound.
-    int64_t waves_up_to_bound = 0;
-    for (int L = 0; L <= max_label; ++L)
-        waves_up_to_bound += two_pairs_per_lane(L, false, symbol_major) ? plan_waves2(L).waves : plan_waves(L).waves;
-    p.crowded = static_cast<int64_t>(B) * (grads ? 2 : 1) * waves_up_to_bound > static_cast<int64_t>(kCrowdedWaves) * (max_label + 1);
-    for (int L = 0; L <= max_label; ++L)
-        p.max_waves = std::max(p.max_waves, std::max(plan_waves(L, p.crowded).waves, plan_waves2(L, p.crowded).waves));
+    const Plans& all_plans = plans();
+    p.crowded = static_cast<int64_t>(B) * (grads ? 2 : 1) * all_plans.latency_waves_up_to[symbol_major][max_label] >
+                static_cast<int64_t>(kCrowdedWaves) * (max_label + 1);
+    p.max_waves = all_plans.most_waves[p.crowded][max_label];
     p.max_frames = T;
     p.max_label = max_label;
-    p.needs_barrier = plan_waves(max_label).barrier;
+    p.needs_barrier = all_plans.barrier[max_label];
     p.x = x;
     p.grads = grads;
     p.alignment = nullptr;

@@ -41,6 +41,7 @@ static_assert(sizeof(Utt) == 64, "Utt is copied word by word and read with scala
 // the gathered emissions would be, and the rows themselves, transposed, are the emission block
 // (emission_layout).
 constexpr int kDirectMaxA = 64;
+constexpr int kByteLabelsMaxA = 256;  // alphabets up to this size: the labels travel to the GPU as bytes
 constexpr int kDeviceFoldMaxB = 512;  // device-resident metadata: utterances up to which the narrow softmax launch builds the records
 constexpr int kNarrowMaxB = 128;      // utterances whose frame counts travel in the narrow softmax launch's arguments
 constexpr int kFlagFrames = 64;       // frames per word of Layout::row_flags = frames per workgroup of the narrow softmax launch
@@ -155,8 +156,17 @@ struct PlanTable {
     CTC_HOST_DEVICE int waves2(int L) const { return (two[L] & 15) + 1; }
     CTC_HOST_DEVICE int halo2(int L) const { return (two[L] >> 4) * 4; }
 };
-// For labels up to max_label (kept per distinct request: a training run asks for one or two).
-const PlanTable& plan_table(int max_label, bool crowded, bool symbol_major);
+// The plans of every supported label length, evaluated once per process: a call looks its utterances up
+// (evaluating plan_waves and plan_waves2 for each utterance of a 512-utterance minibatch was most of the
+// launcher's 130 us).
+struct Plans {
+    PlanTable table[2][2];                                      // [crowded][symbol_major]
+    uint8_t latency_waves[2][CTC_MAX_LABEL_LENGTH + 1];         // [symbol_major]: wavefronts of a linear-domain chain planned for latency
+    int latency_waves_up_to[2][CTC_MAX_LABEL_LENGTH + 1];       // ... summed over all lengths up to this one
+    uint8_t most_waves[2][CTC_MAX_LABEL_LENGTH + 1];            // [crowded]: most wavefronts of any plan for a label up to this length
+    bool barrier[CTC_MAX_LABEL_LENGTH + 1];                     // WavePlan::barrier
+};
+const Plans& plans();
 
 // How a launch's label emissions are laid out (Utt::e_direct).
 //   kEmitGathered:    [frame][label position], L floats per frame (alphabets above kDirectMaxA)

@@ -3240,7 +3240,7 @@ int launch_setup(const Launch& p, void* stream)
 {
     // (the workers' task list only if the lattice launch has workers; the byte labels after it are read in place)
     const int words = static_cast<int>((p.n_tasks > 0 ? p.lay.labels8 : p.lay.tasks) / 4);
-    const unsigned char* labels8 = p.A <= 256 ? static_cast<const unsigned char*>(p.host_image) + p.lay.labels8 : nullptr;
+    const unsigned char* labels8 = p.A <= kByteLabelsMaxA ? static_cast<const unsigned char*>(p.host_image) + p.lay.labels8 : nullptr;
     return checked_launch([&] {
         hipLaunchKernelGGL(ctc_upload_kernel, dim3((words + kRowThreads - 1) / kRowThreads), dim3(kRowThreads),
                            0, static_cast<hipStream_t>(stream), static_cast<const int*>(p.host_image),
@@ -3293,7 +3293,7 @@ int launch_softmax(const Launch& p, void* stream)
             NarrowArgs args;
             NarrowRows& rows_of = args.rows;
             NarrowDevice dv{};
-            if (p.dev_label_lengths) args.plans = plan_table(p.max_label, p.crowded, emission_layout(p.A) == kEmitSymbolMajor);
+            if (p.dev_label_lengths) args.plans = plans().table[p.crowded][emission_layout(p.A) == kEmitSymbolMajor];
             if (p.dev_label_lengths)
                 dv = NarrowDevice{p.labels, p.dev_label_lengths, p.dev_input_lengths, meta, reinterpret_cast<int*>(p.ws + p.lay.order),
                                   reinterpret_cast<int*>(p.ws + p.lay.status), p.max_label, p.poll_budget,

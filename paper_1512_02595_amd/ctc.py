@@ -1,8 +1,11 @@
-"""ctypes binding of libctc_mi355x.so: argument marshalling only.
+"""Binding of libctc_mi355x.so: argument marshalling only.
 
 The functions mirror include/ctc_mi355x.h.  Device buffers are passed as integer
 addresses (for instance torch.Tensor.data_ptr()), host arrays as numpy int32
-arrays.  There is no fallback: if the library has not been built, loading raises.
+arrays.  The three entry points of a training loop go through the native module
+`_binding` (a call through ctypes takes ten microseconds longer, half of a small
+minibatch's whole time); the rest, called rarely, through ctypes.  There is no
+fallback: if the library or the module has not been built, loading raises.
 """
 from __future__ import annotations
 
@@ -37,6 +40,7 @@ EXPORTS = ("ctc_workspace_size", "ctc_loss_and_grad", "ctc_profile_kernels",
            "ctc_debug_staging_allocations", "ctc_debug_set_overlap", "ctc_debug_replay_emission_fetches")
 
 _lib = None
+_native = None                # the module `_binding`, once load() has given it the library's addresses
 
 
 class CTCError(RuntimeError):
@@ -47,12 +51,13 @@ class CTCError(RuntimeError):
 
 def load() -> ctypes.CDLL:
     """Loads the HIP library (once).  Raises if it has not been built."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
         raise ImportError(f"{LIB_PATH} is missing: run `python -m paper_1512_02595_amd.build` "
                           "(there is no CPU fallback)")
+    from . import _binding                                       # (built by the same command)
     lib = ctypes.CDLL(LIB_PATH)
     i32p = ctypes.POINTER(ctypes.c_int32)
     vp, st, ci = ctypes.c_void_p, ctypes.c_int, ctypes.c_int
@@ -93,6 +98,9 @@ def load() -> ctypes.CDLL:
     lib.ctc_debug_set_sequential_chains.argtypes = [ci]
     lib.ctc_debug_staging_allocations.restype = ctypes.c_long
     lib.ctc_debug_staging_allocations.argtypes = []
+    _binding.bind(*(ctypes.cast(f, vp).value for f in (lib.ctc_loss_and_grad, lib.ctc_best_path,
+                                                       lib.ctc_loss_and_grad_device)))
+    _native = _binding
     _lib = lib
     return lib
 
@@ -133,22 +141,44 @@ def workspace_size(T, B, A, label_lengths, input_lengths, dtype=DTYPE_F32) -> in
     return n
 
 
+def _int32(a):
+    return None if a is None else np.ascontiguousarray(a, dtype=np.int32).reshape(-1)
+
+
+def _host_call(name, activations_ptr, flat_labels, label_lengths, input_lengths, *rest) -> int:
+    """One host-metadata call through the native module, which takes contiguous int32 arrays; others are converted."""
+    if _native is None:
+        load()
+    call = getattr(_native, name)
+    st = call(activations_ptr, flat_labels, label_lengths, input_lengths, *rest)
+    if st is None:
+        st = call(activations_ptr, _int32(flat_labels), _int32(label_lengths), _int32(input_lengths), *rest)
+    return st
+
+
+def _profile_call(entry, activations_ptr, flat_labels, label_lengths, input_lengths, T, B, A, blank,
+                  dtype, costs_ptr, out_ptr, workspace_ptr, workspace_bytes, stream, kernel_ms) -> int:
+    assert kernel_ms.dtype == np.float32 and kernel_ms.size >= NUM_KERNELS
+    _fl, flp = _i32(flat_labels, allow_none=True)
+    _ll, llp = _i32(label_lengths, allow_none=True)
+    _il, ilp = _i32(input_lengths, allow_none=True)
+    return int(getattr(load(), entry)(
+        ctypes.c_void_p(activations_ptr), flp, llp, ilp, int(T), int(B), int(A), int(blank),
+        int(dtype), ctypes.c_void_p(costs_ptr), ctypes.c_void_p(out_ptr),
+        ctypes.c_void_p(workspace_ptr), ctypes.c_size_t(workspace_bytes), ctypes.c_void_p(stream),
+        kernel_ms.ctypes.data_as(ctypes.POINTER(ctypes.c_float))))
+
+
 def loss_and_grad_status(activations_ptr, flat_labels, label_lengths, input_lengths, T, B, A, blank,
                          dtype, costs_ptr, grads_ptr, workspace_ptr, workspace_bytes, stream=0,
                          kernel_ms=None) -> int:
     """Raw call; returns the status.  With `kernel_ms` (float32 numpy array of NUM_KERNELS)
     the profiling entry point is used and the array is filled.  grads_ptr None (or 0): costs only."""
-    _fl, flp = _i32(flat_labels, allow_none=True)
-    _ll, llp = _i32(label_lengths, allow_none=True)
-    _il, ilp = _i32(input_lengths, allow_none=True)
-    args = [ctypes.c_void_p(activations_ptr), flp, llp, ilp, int(T), int(B), int(A), int(blank),
-            int(dtype), ctypes.c_void_p(costs_ptr), ctypes.c_void_p(grads_ptr),
-            ctypes.c_void_p(workspace_ptr), ctypes.c_size_t(workspace_bytes), ctypes.c_void_p(stream)]
-    lib = load()
     if kernel_ms is None:
-        return int(lib.ctc_loss_and_grad(*args))
-    assert kernel_ms.dtype == np.float32 and kernel_ms.size >= NUM_KERNELS
-    return int(lib.ctc_profile_kernels(*args, kernel_ms.ctypes.data_as(ctypes.POINTER(ctypes.c_float))))
+        return _host_call("loss_and_grad", activations_ptr, flat_labels, label_lengths, input_lengths, T, B, A, blank,
+                          dtype, costs_ptr, grads_ptr, workspace_ptr, workspace_bytes, stream)
+    return _profile_call("ctc_profile_kernels", activations_ptr, flat_labels, label_lengths, input_lengths, T, B, A,
+                         blank, dtype, costs_ptr, grads_ptr, workspace_ptr, workspace_bytes, stream, kernel_ms)
 
 
 def loss_and_grad(activations_ptr, flat_labels, label_lengths, input_lengths, T, B, A, blank,
@@ -166,17 +196,11 @@ def best_path_status(activations_ptr, flat_labels, label_lengths, input_lengths,
                      dtype, scores_ptr, alignment_ptr, workspace_ptr, workspace_bytes, stream=0,
                      kernel_ms=None) -> int:
     """Raw ctc_best_path (ctc_profile_best_path with `kernel_ms`); returns the status."""
-    _fl, flp = _i32(flat_labels, allow_none=True)
-    _ll, llp = _i32(label_lengths, allow_none=True)
-    _il, ilp = _i32(input_lengths, allow_none=True)
-    args = [ctypes.c_void_p(activations_ptr), flp, llp, ilp, int(T), int(B), int(A), int(blank),
-            int(dtype), ctypes.c_void_p(scores_ptr), ctypes.c_void_p(alignment_ptr),
-            ctypes.c_void_p(workspace_ptr), ctypes.c_size_t(workspace_bytes), ctypes.c_void_p(stream)]
-    lib = load()
     if kernel_ms is None:
-        return int(lib.ctc_best_path(*args))
-    assert kernel_ms.dtype == np.float32 and kernel_ms.size >= NUM_KERNELS
-    return int(lib.ctc_profile_best_path(*args, kernel_ms.ctypes.data_as(ctypes.POINTER(ctypes.c_float))))
+        return _host_call("best_path", activations_ptr, flat_labels, label_lengths, input_lengths, T, B, A, blank,
+                          dtype, scores_ptr, alignment_ptr, workspace_ptr, workspace_bytes, stream)
+    return _profile_call("ctc_profile_best_path", activations_ptr, flat_labels, label_lengths, input_lengths, T, B, A,
+                         blank, dtype, scores_ptr, alignment_ptr, workspace_ptr, workspace_bytes, stream, kernel_ms)
 
 
 def best_path(activations_ptr, flat_labels, label_lengths, input_lengths, T, B, A, blank,
@@ -217,11 +241,11 @@ def loss_and_grad_device_status(activations_ptr, labels_ptr, label_lengths_ptr, 
             int(dtype), ctypes.c_void_p(costs_ptr), ctypes.c_void_p(grads_ptr), ctypes.c_void_p(status_ptr),
             ctypes.c_void_p(workspace_ptr), ctypes.c_size_t(workspace_bytes), ctypes.c_void_p(stream),
             kernel_ms.ctypes.data_as(ctypes.POINTER(ctypes.c_float))))
-    return int(load().ctc_loss_and_grad_device(
-        ctypes.c_void_p(activations_ptr), ctypes.c_void_p(labels_ptr), ctypes.c_void_p(label_lengths_ptr),
-        ctypes.c_void_p(input_lengths_ptr), int(max_label_length), int(T), int(B), int(A), int(blank),
-        int(dtype), ctypes.c_void_p(costs_ptr), ctypes.c_void_p(grads_ptr), ctypes.c_void_p(status_ptr),
-        ctypes.c_void_p(workspace_ptr), ctypes.c_size_t(workspace_bytes), ctypes.c_void_p(stream)))
+    if _native is None:
+        load()
+    return _native.loss_and_grad_device(activations_ptr, labels_ptr, label_lengths_ptr, input_lengths_ptr, max_label_length,
+                                        T, B, A, blank, dtype, costs_ptr, grads_ptr, status_ptr, workspace_ptr,
+                                        workspace_bytes, stream)
 
 
 STATIC_WORKSPACE_BYTES = 64 << 20

@@ -25,10 +25,6 @@ namespace {
 
 thread_local int g_last_hip_error = 0;
 std::atomic<int> g_poll_budget{kDefaultPollBudget};
-// Gradient rows inside the lattice launch where it has idle compute units: 0 = never; otherwise the
-// percentage of the launch's expected duration up to which an utterance's chains must end for its rows
-// to be written by the launch's workers (the rest are written by the gradient launch that follows).
-std::atomic<int> g_overlap{kWorkerSharePercent};
 std::atomic<int> g_sequential_chains{0};
 
 constexpr size_t kAlign = 256;
@@ -69,7 +65,6 @@ void carve(int T, int B, int64_t sumL, int64_t emit, int64_t frames, int64_t ab,
     l.meta = off;   off += static_cast<size_t>(B) * sizeof(Utt);            // 64 B each: stays 8-byte aligned
     l.order = off;  off += static_cast<size_t>(B) * 2 * sizeof(int32_t);
     l.labels = off; off += static_cast<size_t>(sumL) * sizeof(int32_t);
-    l.tasks = off;  off += (static_cast<size_t>(B) * 6 + 1 + kXcds + 1) * sizeof(int32_t);
     l.labels8 = off; off += (static_cast<size_t>(sumL) + 3) / 4 * 4;
     l.upload_bytes = off;
     off = align_up(off);
@@ -77,14 +72,10 @@ void carve(int T, int B, int64_t sumL, int64_t emit, int64_t frames, int64_t ab,
     l.logp = off;   off = align_up(off + static_cast<size_t>(B) * sizeof(double));
     l.sink = off;   off = align_up(off + static_cast<size_t>(B) * 2 * kSinkWaves * kSinkBytes);
     l.chain_err = off; off = align_up(off + static_cast<size_t>(B) * sizeof(int32_t));
-    l.done = off;   off = align_up(off + static_cast<size_t>(B) * kDoneStride * sizeof(int32_t));
     l.domain = off; off = align_up(off + static_cast<size_t>(B) * 2 * sizeof(int32_t));
     l.row_flags = off;
     off = align_up(off + static_cast<size_t>(B) * ((T + kFlagFrames - 1) / kFlagFrames) * sizeof(int32_t));
     l.status = off; off = align_up(off + static_cast<size_t>(B) * sizeof(int32_t));
-    l.where = off;  off = align_up(off + static_cast<size_t>(B) * 2 * sizeof(int32_t));
-    l.leftover = off; off = align_up(off + static_cast<size_t>(B) * sizeof(int32_t));
-    l.lse = off;    off = align_up(off + static_cast<size_t>(B) * T * sizeof(float));
     l.emit_blank = off;
     off = align_up(off + (static_cast<size_t>(frames) + 2 * kBlankSlack) * sizeof(float));
     l.emit_blank64 = off;
@@ -138,11 +129,12 @@ ctc_status_t make_layout(int T, int B, int A, const int32_t* label_lengths,
         if (L < 0 || Tb < 0 || Tb > T) return CTC_STATUS_INVALID_VALUE;
         if (L > CTC_MAX_LABEL_LENGTH) too_long = true;
         sumL += L;
-        emit += Tb * (A <= kDirectMaxA ? A : L);
-        frames += Tb;
+        const int64_t padded = padded_frames(input_lengths[b]);
+        emit += padded * (A <= kDirectMaxA ? A : L);
+        frames += padded;
         // per-utterance byte offsets inside the kernels are 32-bit
-        if (Tb * lattice_pitch(L) * 8 > INT32_MAX) too_long = true;
-        ab += Tb * lattice_pitch(L);
+        if (padded * lattice_pitch(L) * 8 > INT32_MAX) too_long = true;
+        ab += padded * lattice_pitch(L);
     }
     if (too_long) return CTC_STATUS_UNSUPPORTED;
     if (sumL > INT32_MAX || frames > INT32_MAX) return CTC_STATUS_UNSUPPORTED;
@@ -158,7 +150,7 @@ ctc_status_t make_layout_bounds(int T, int B, int A, int max_label, ctc_dtype_t 
     if (!lay || T < 1 || B < 1 || A < 1 || max_label < 0) return CTC_STATUS_INVALID_VALUE;
     if (dtype != CTC_DTYPE_F32 && dtype != CTC_DTYPE_BF16) return CTC_STATUS_INVALID_VALUE;
     if (max_label > CTC_MAX_LABEL_LENGTH || B > kMaxDeviceMetaB) return CTC_STATUS_UNSUPPORTED;
-    const int64_t Tl = T, Bl = B, Ll = max_label;
+    const int64_t Tl = padded_frames(T), Bl = B, Ll = max_label;
     if (Tl * lattice_pitch(Ll) * 8 > INT32_MAX || Bl * Ll > INT32_MAX || Bl * Tl > INT32_MAX) return CTC_STATUS_UNSUPPORTED;
     carve(T, B, Bl * Ll, Bl * Tl * (A <= kDirectMaxA ? A : Ll), Bl * Tl, Bl * Tl * lattice_pitch(Ll), lay);
     return CTC_STATUS_SUCCESS;
@@ -325,7 +317,7 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
     int32_t* labels = reinterpret_cast<int32_t*>(image + lay.labels);
     uint8_t* labels8 = reinterpret_cast<uint8_t*>(image + lay.labels8);
 
-    const bool symbol_major = emission_layout(c.A) == kEmitSymbolMajor;
+    const bool symbol_major = emission_layout(c.A) == kEmitSymbols;
     const Plans& all_plans = plans();
     // Would the launch, planned for latency, put more than two wavefronts on every SIMD?
     int64_t latency_waves = 0;
@@ -372,12 +364,13 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
         m.e_off = e_off;
         m.ab_off = ab_off;
         m.e_direct = emission_layout(c.A);
-        m.e_pitch = m.e_direct == kEmitSymbolMajor ? Tb : L;
+        m.e_cols = m.e_direct == kEmitSymbols ? c.A : L;
         meta[b] = m;
+        const int64_t padded = padded_frames(Tb);
         lab_off += L;
-        e_off += static_cast<int64_t>(Tb) * (c.A <= kDirectMaxA ? c.A : L);
-        f_off += Tb;
-        ab_off += static_cast<int64_t>(Tb) * lattice_pitch(L);
+        e_off += padded * m.e_cols;
+        f_off += padded;
+        ab_off += padded * lattice_pitch(L);
         if (runs) {
             order[n_run++] = b;
             max_waves = std::max({max_waves, m.waves, m.waves2});
@@ -415,62 +408,7 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
     order_chains(running.data(), run_frames.data(), run_waves.data(), n_run, dirs, compute_units(), order);
     for (int i = n_run * dirs; i < 2 * c.B; ++i) order[i] = -1;
 
-    // Gradient rows inside the lattice launch (kTaskRows), where the launch leaves at least a quarter
-    // of the compute units without a chain.  (Narrow alphabets only: the workers run the gradient
-    // of ctc_gradient_narrow_kernel.)
-    const int n_cu = compute_units();
-    int32_t* const task_die = reinterpret_cast<int32_t*>(image + lay.tasks);     // [kXcds + 1]
-    int32_t* const task_prefix = task_die + kXcds + 1;                           // [2B + 1]
-    int32_t* const task_info = task_prefix + 2 * c.B + 1;                        // [2B]
-    int32_t* const task_first = task_info + 2 * c.B;                             // [2B]
-    int n_entries = 0, n_tasks = 0;
     const bool sequential_chains = c.mode == Mode::kGrad && g_sequential_chains.load(std::memory_order_relaxed) != 0;
-    const int share_percent = sequential_chains ? 0 : g_overlap.load(std::memory_order_relaxed);
-    if (share_percent > 0 && c.mode == Mode::kGrad && c.A <= kDirectMaxA && !needs_barrier &&
-        n_run > 0 && 2 * c.B <= kMaxTaskEntries && n_cu % kXcds == 0 && n_run * dirs + n_cu / 4 <= n_cu) {
-        // The die of an utterance's chains: workgroup i runs on die i mod kXcds (order_chains puts an
-        // utterance's two chains a multiple of kXcds entries apart).
-        uint8_t die_of[kMaxTaskEntries / 2] = {};
-        for (int i = 0; i < n_run * dirs; ++i)
-            if ((order[i] & 1) == 0) die_of[order[i] >> 1] = static_cast<uint8_t>(i % kXcds);
-        // Chains end in the order of their frames, those that exchange between wavefronts a little later.
-        auto ends_at = [&](int b) { return meta[b].Tb * (chain_waves(b) > 1 ? 5 : 4); };
-        // (ties in the run order: the low bits are the place in it)
-        uint64_t ending[kMaxTaskEntries / 2];
-        for (int i = 0; i < n_run; ++i) ending[i] = (static_cast<uint64_t>(ends_at(running[i])) << 16) | static_cast<uint64_t>(i);
-        std::sort(ending, ending + n_run);
-        const int last_end = static_cast<int>(ending[n_run - 1] >> 16);
-        const int blocks = (c.T + kTaskRows - 1) / kTaskRows;
-        auto data_blocks = [&](int b) { return (meta[b].flags & kUttRuns) ? (meta[b].Tb + kTaskRows - 1) / kTaskRows : 0; };
-        auto add = [&](int info, int first, int count) {
-            if (count <= 0) return;
-            task_prefix[n_entries] = n_tasks;
-            task_info[n_entries] = info;
-            task_first[n_entries] = first;
-            ++n_entries;
-            n_tasks += count;
-        };
-        for (int die = 0; die < kXcds; ++die) {
-            task_die[die] = n_entries;
-            // what needs no lattice first (shared out over the dies by utterance number) ...
-            for (int b = die; b < c.B; b += kXcds) add(b | (kTaskRowsLog2 << kTaskRowsShift), data_blocks(b), blocks - data_blocks(b));
-            // ... then the die's utterances as their chains end.  Those that end last are not worth waiting
-            // for inside the launch: only the workers of the chains' own die can take them, a sixteenth of the
-            // chip, and with every utterance given to the workers the launch was measured to end 15 us after
-            // its last chain, against a gradient launch of 7 us for the last fifth: that launch takes them.
-            for (int i = 0; i < n_run; ++i) {
-                const int b = running[ending[i] & 0xFFFF];
-                if (die_of[b] != die) continue;
-                if (static_cast<int64_t>(ends_at(b)) * 100 > static_cast<int64_t>(last_end) * share_percent) {
-                    meta[b].flags |= kUttGradientLater;
-                    continue;
-                }
-                add(b | kTaskWaits | (kTaskRowsLog2 << kTaskRowsShift), 0, data_blocks(b));
-            }
-        }
-        task_die[kXcds] = n_entries;
-        task_prefix[n_entries] = n_tasks;
-    }
 
     if (c.ws_bytes < lay.total) return CTC_STATUS_WORKSPACE_TOO_SMALL;
 
@@ -496,9 +434,7 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
     out->poll_budget = poll_budget;
     out->crowded = crowded;
     out->sequential_chains = sequential_chains;
-    out->n_tasks = n_tasks;
-    out->n_task_entries = n_entries;
-    out->n_cu = n_cu;
+    out->n_cu = compute_units();
     out->folded = c.A <= kDirectMaxA && c.B <= kNarrowMaxB && c.T < (1 << 29);
     out->lay = lay;
     return CTC_STATUS_SUCCESS;
@@ -590,8 +526,6 @@ ctc_status_t run(const Call& c, float* kernel_ms)
     }
 
     // Cost-only calls end with the lattice launch.
-    // (Where the lattice launch carries the gradient rows itself, Launch::n_tasks, the gradient launch only
-    // looks for utterances that the workers had to leave to it.)
     int (*const stages[CTC_NUM_KERNELS])(const Launch&, void*) = {
         launch_softmax, launch_lattice,
         c.mode == Mode::kGrad ? launch_gradient : (c.mode == Mode::kLoss ? nullptr : launch_backtrace)};
@@ -647,7 +581,7 @@ ctc_status_t run_device(const void* x, const int32_t* labels, const int32_t* lab
     p.dtype = dtype;
     p.n_run = B;                       // a lattice workgroup per utterance and direction; those that do not run leave at once
     p.n_chains = B * (grads ? 2 : 1);
-    const bool symbol_major = emission_layout(A) == kEmitSymbolMajor;
+    const bool symbol_major = emission_layout(A) == kEmitSymbols;
     // Would the launch, planned for latency, put more than two wavefronts on every SIMD (prepare's question)?  The
     // labels' lengths are on the GPU; the answer here is for lengths spread evenly up to the bound.
     const Plans& all_plans = plans();
@@ -670,22 +604,10 @@ ctc_status_t run_device(const void* x, const int32_t* labels, const int32_t* lab
     p.dev_input_lengths = input_lengths;
     p.dev_status = status;
     p.poll_budget = g_poll_budget.load(std::memory_order_relaxed);
-    p.n_tasks = 0;
-    p.n_task_entries = 0;
-    p.n_cu = 0;
+    p.n_cu = compute_units();
     // Narrow alphabets: the softmax launch builds the records itself (no planning launch before it); every
     // utterance's setup workgroup weighs all B utterances for the run order, which is worth it up to here.
     p.folded = A <= kDirectMaxA && B <= kDeviceFoldMaxB && max_label > 0;
-    // Gradient rows inside the lattice launch, under the conditions of prepare(); the task list is built on the GPU.
-    const int n_cu = compute_units(), share_percent = g_overlap.load(std::memory_order_relaxed);
-    p.n_cu = n_cu;
-    if (p.folded && grads && share_percent > 0 && !p.needs_barrier && 2 * B <= kMaxTaskEntries && n_cu % kXcds == 0 &&
-        p.n_chains + n_cu / 4 <= n_cu) {
-        p.device_tasks = true;
-        p.share_percent = share_percent;
-        p.n_tasks = B * ((T + kTaskRows - 1) / kTaskRows);
-        p.n_task_entries = 2 * B;
-    }
     p.lay = lay;
     // Per-launch device times for measurements (ctc_profile_kernels_device): events around the launches as in run().
     Events events;
@@ -890,7 +812,7 @@ long ctc_debug_replay_emission_fetches(int T, int B, int A, const int32_t* label
     const ctc_status_t st = bounds ? make_layout_bounds(T, B, A, max_label_length, CTC_DTYPE_F32, &lay)
                                    : make_layout(T, B, A, label_lengths, input_lengths, CTC_DTYPE_F32, &lay);
     if (st != CTC_STATUS_SUCCESS) return -1;
-    const bool symbol_major = emission_layout(A) == kEmitSymbolMajor;
+    const bool symbols = emission_layout(A) == kEmitSymbols;
     // the regions as carved: slack, blocks, slack
     const int64_t label_floats = lay.emit_floats + 2 * static_cast<int64_t>(kLabelSlack);
     const int64_t blank_floats = lay.frames + 2 * static_cast<int64_t>(kBlankSlack);
@@ -908,77 +830,49 @@ long ctc_debug_replay_emission_fetches(int T, int B, int A, const int32_t* label
         m.Tb = Tb;
         m.L = L;
         m.e_direct = emission_layout(A);
+        m.e_cols = symbols ? A : L;
         if (bounds) {
-            m.f_off = b * T;
-            m.e_off = static_cast<int64_t>(b) * T * (symbol_major ? A : max_label_length);
-            m.e_pitch = symbol_major ? T : L;
+            m.f_off = static_cast<int32_t>(b * padded_frames(T));
+            m.e_off = b * padded_frames(T) * (symbols ? A : max_label_length);
         } else {
             m.f_off = static_cast<int32_t>(f_off);
             m.e_off = e_off;
-            m.e_pitch = symbol_major ? Tb : L;
-            e_off += static_cast<int64_t>(Tb) * (symbol_major ? A : L);
-            f_off += Tb;
+            e_off += padded_frames(Tb) * m.e_cols;
+            f_off += padded_frames(Tb);
         }
         if (Tb < 1) continue;                       // its chains do not run
+        const int chunks = 2 * frame_blocks(Tb);
         for (int backward = 0; backward < 2; ++backward) {
-            const int f0 = backward ? Tb - 1 : 0, fdir = backward ? -1 : 1;
             // Lanes at the ends of every range a pointer depends on: first and last label position, first
             // and last symbol; a lane without a label state, for either constant.
             struct LaneKind { bool has_label; int symbol, li, constant; };
             const LaneKind kinds[] = {{L > 0, 0, 0, 0}, {L > 0, A - 1, L - 1, 0}, {L > 0, 0, L - 1, 0}, {L > 0, A - 1, 0, 0},
                                       {false, 0, 0, kZeroEmission}, {false, 0, 0, kLogZeroEmission}};
+            auto nothing = [](auto, int) {};
             for (const LaneKind& k : kinds) {
-                if (!k.has_label && k.constant == 0) continue;          // (L == 0: no label lanes)
-                int64_t p = label_emission_offset(m, k.has_label, symbol_major, k.symbol, k.li, f0, k.constant);
-                const int64_t step = label_emission_step(m, k.has_label, symbol_major, fdir);
-                touch(p, label_floats);                                  // step 0
-                auto fetch = [&](int) {
-                    if (symbol_major) {
-                        touch(p + fetch_window_first(backward != 0), label_floats);
-                        touch(p + fetch_window_first(backward != 0) + kChunk - 1, label_floats);
-                        p += step * kChunk;
-                    } else {
-                        for (int i = 0; i < kChunk; ++i) {
-                            p += step;
-                            touch(p, label_floats);
-                        }
-                    }
+                int64_t p = label_emission_offset(m, k.has_label, k.symbol, k.li, chain_chunk(0, chunks, backward != 0), k.constant);
+                const int64_t step = label_emission_step(m, k.has_label, backward != 0);
+                auto fetch = [&](auto, int) {
+                    touch(p, label_floats);
+                    touch(p + kChunk - 1, label_floats);
+                    p += step;
                 };
-                auto nothing = [](int, bool) {};
-                chain_schedule(Tb, fetch, fetch, nothing, nothing, [] {});
-                // the same pointer walk on the schedule with three register sets (run_chain_linear)
-                p = label_emission_offset(m, k.has_label, symbol_major, k.symbol, k.li, f0, k.constant);
-                chain_schedule3(Tb, fetch, fetch, fetch, nothing, nothing, nothing, [] {});
+                chain_schedule(chunks, fetch, nothing);
             }
-            for (int lane = 0; lane < kChunk; ++lane) {
-                const int64_t bp = blank_emission_offset(m, f0, fdir, lane);
-                touch(bp, blank_floats);                                  // step 0 (lane 0's is the one used)
-                auto fetch = [&](int s0) { touch(bp + static_cast<int64_t>(fdir) * s0, blank_floats); };
-                auto nothing = [](int, bool) {};
-                chain_schedule(Tb, fetch, fetch, nothing, nothing, [] {});
-            }
-            {
-                // the scalar windows of the linear-domain chains (the block of doubles has the same extent)
-                touch(blank64_window(m, f0, fdir, 0) + (fdir > 0 ? 0 : kChunk - 1), blank_floats);     // step 0
-                auto fetch = [&](int s0) {
-                    touch(blank64_window(m, f0, fdir, s0), blank_floats);
-                    touch(blank64_window(m, f0, fdir, s0) + kChunk - 1, blank_floats);
-                };
-                auto nothing = [](int, bool) {};
-                chain_schedule(Tb, fetch, fetch, nothing, nothing, [] {});
-                auto fetch3 = [&](int s0) { fetch(blank64_chunk_with(s0)); };
-                chain_schedule3(Tb, fetch3, fetch3, fetch3, nothing, nothing, nothing, [] {});
-            }
+            auto fetch = [&](auto, int i) {
+                if (i == 0) return;
+                const int64_t w = blank_emission_offset(m, chain_chunk(i - 1, chunks, backward != 0));
+                touch(w, blank_floats);                          // (the block of doubles has the same extent)
+                touch(w + kChunk - 1, blank_floats);
+            };
+            chain_schedule(chunks, fetch, nothing);
         }
     }
     if (margin_floats) *margin_floats = margin == INT64_MAX ? -1 : static_cast<long>(margin);
     return violations;
 }
 
-void ctc_debug_set_overlap(int percent)
-{
-    ctc::g_overlap.store(percent < 0 ? ctc::kWorkerSharePercent : std::min(percent, 100), std::memory_order_relaxed);
-}
+void ctc_debug_set_overlap(int) {}
 
 extern "C" void ctc_debug_set_sequential_chains(int on)
 {

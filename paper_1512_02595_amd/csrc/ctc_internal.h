@@ -5,41 +5,36 @@
 #include <cstddef>
 #include <algorithm>
 #include <cstdint>
+#include <type_traits>
 #include <vector>
 
 #include "ctc_mi355x.h"
 
-#ifndef CTC_STREAMING_MB
-#define CTC_STREAMING_MB 128
-#endif
-
 namespace ctc {
 
-// Per-utterance record, identical on host and device (48 bytes).
+// Per-utterance record, identical on host and device (64 bytes).
 struct Utt {
     int32_t Tb;        // frames of this utterance (input_lengths[b])
     int32_t L;         // label length
     int32_t lab_off;   // offset of its label string in the flat label array
     int32_t flags;     // bit 0: the lattice runs (Tb > 0 and an alignment exists);
                        // bit 1: lengths or labels failed the device-side checks (cost NaN)
-    int32_t f_off;     // frames of all earlier utterances: offset of its blank emissions [Tb]
+    int32_t f_off;     // padded frames (padded_frames) of all earlier utterances: offset of its blank emissions
     int32_t waves;     // wavefronts its lattice chains use when a lane owns one state pair (log-domain
                        // chains, and linear-domain chains of at most 64 pairs)
     int32_t halo;      // lanes per wavefront that recompute the wavefront below (0: none)
     int32_t poll_budget; // LDS polls a wavefront of its chains may spend waiting on a neighbour before it gives up
-    int64_t e_off;     // offset (floats) of its label emissions
-    int64_t ab_off;    // offset (8-byte words) of its alpha/beta blocks [Tb][lattice_pitch(L)]
-    int32_t e_pitch;   // row pitch (floats) of its emission block: L (a frame's gathered emissions, one
-                       // per label position) or the frames of a symbol's row (symbol-major block)
-    int32_t e_direct;  // layout of the emission block: kEmitGathered or kEmitSymbolMajor (emission_layout)
+    int64_t e_off;     // offset (floats) of its label emissions [chunk][e_cols][kChunk]
+    int64_t ab_off;    // offset (8-byte words) of its alpha/beta blocks [padded_frames(Tb)][lattice_pitch(L)]
+    int32_t e_cols;    // columns of its emission block: a column per symbol, or one per label position
+    int32_t e_direct;  // which of the two: kEmitGathered or kEmitSymbols (emission_layout)
     int32_t waves2;    // the same plan for linear-domain chains of more than 64 pairs, whose lanes own
     int32_t halo2;     // two neighbouring pairs each (plan_waves2)
 };
 static_assert(sizeof(Utt) == 64, "Utt is copied word by word and read with scalar loads: keep it 8-byte sized");
 
 // Alphabets up to this size skip the emission gather: a frame's normalised row is as small as
-// the gathered emissions would be, and the rows themselves, transposed, are the emission block
-// (emission_layout).
+// the gathered emissions would be, and the rows themselves are the emission block (emission_layout).
 constexpr int kDirectMaxA = 64;
 constexpr int kByteLabelsMaxA = 256;  // alphabets up to this size: the labels travel to the GPU as bytes
 constexpr int kDeviceFoldMaxB = 512;  // device-resident metadata: utterances up to which the narrow softmax launch builds the records
@@ -168,16 +163,23 @@ struct Plans {
 };
 const Plans& plans();
 
-// How a launch's label emissions are laid out (Utt::e_direct).
-//   kEmitGathered:    [frame][label position], L floats per frame (alphabets above kDirectMaxA)
-//   kEmitSymbolMajor: [symbol][frame]: the normalised rows themselves, transposed, so that a
-//                     symbol's frames lie side by side and a lane fetches the frames of a chunk
-//                     in two 16-byte loads instead of eight loads a row apart
-// Measured on gfx950 against the rows as they are ([frame][symbol]): English minibatch, lattice
-// launch 60.4 -> 58.4 us; long utterances (two wavefronts of a chain on one SIMD, instruction
-// issue the limit) 203 -> 168 us.
-constexpr int kEmitGathered = 0, kEmitSymbolMajor = 1;
-CTC_HOST_DEVICE inline int emission_layout(int A) { return A <= kDirectMaxA ? kEmitSymbolMajor : kEmitGathered; }
+// How a launch's label emissions are laid out: [chunk][column][frame of the chunk], kChunk frames of a column side
+// by side, so that a lane fetches what it needs of a chunk in two 16-byte loads.  The columns (Utt::e_direct) are
+//   kEmitGathered: the label's positions (alphabets above kDirectMaxA): neighbouring lanes read neighbouring columns;
+//   kEmitSymbols:  the symbols: the normalised rows themselves; a chunk of 29 symbols is 928 bytes, eight lines for the
+//                  64 lanes of a fetch to meet in.  (With a row per symbol over all frames every lane asked for a line
+//                  of its own, and the wavefronts of a compute unit queued for its L1.)
+// Blocks cover whole blocks of kBlockFrames frames.  Past an utterance's last frame they hold virtual frames in which
+// blank has probability 1 and every label 0: the start state of either recursion (its first blank has all the mass)
+// goes through them unchanged, and after its last frame the forward recursion merely gathers p in the last blank.
+// Chains thus consist of whole chunks on one grid in both directions.
+constexpr int kEmitGathered = 0, kEmitSymbols = 1;
+CTC_HOST_DEVICE inline int emission_layout(int A) { return A <= kDirectMaxA ? kEmitSymbols : kEmitGathered; }
+
+// Frames between two states that a chain stores for the gradient (checkpoints): see gradient_tile.
+constexpr int kBlockFrames = 2 * kChunkSteps;
+CTC_HOST_DEVICE inline int frame_blocks(int frames) { return (frames + kBlockFrames - 1) / kBlockFrames; }
+CTC_HOST_DEVICE inline int64_t padded_frames(int frames) { return static_cast<int64_t>(frame_blocks(frames)) * kBlockFrames; }
 
 // The sink of a lattice launch: for each of its up to 2 B chain workgroups, kSinkBytes for each of the
 // up to kSinkWaves wavefronts.
@@ -192,9 +194,6 @@ constexpr int kUttLogDomain = 4;
 // Linear-domain chains of this utterance give two neighbouring state pairs to every lane
 // (plan_waves2) instead of one (plan_waves): see two_pairs_per_lane.
 constexpr int kUttTwoPairs = 8;
-// Overlapped launches (kTaskRows): the utterance's gradient rows are written by the gradient launch,
-// not by the lattice launch's workers.
-constexpr int kUttGradientLater = 16;
 constexpr float kLinearMinLog2 = -100.0f;
 // Utterances of more frames than this run the log domain whatever their emissions: the lanes'
 // exponents, which fall by up to 100 per frame, must stay clear of kNoExponent and of int32's end.
@@ -276,61 +275,23 @@ inline void order_chains(const int32_t* utt, const int32_t* frames, const int32_
     }
 }
 
-// Lattice size (alpha and beta together) beyond which the gradient kernel reads it with loads
-// that leave no copy in the caches.  Measured on gfx950: 0.4 GB (512 utterances) 141 -> 104 us with
-// such loads, 53 MB (64 utterances) 14.9 -> 15.7 us.
-constexpr size_t kStreamingLatticeBytes = size_t(CTC_STREAMING_MB) << 20;
-
-// Gradient rows inside the lattice launch.  A launch with fewer chains than compute units leaves
-// the rest of the chip idle for as long as the longest chain runs, while the gradient of an
-// utterance could start the moment both of its chains have ended.  Such launches therefore carry
-// extra workgroups after the chains' ("workers") whose wavefronts share out a list of tasks: a task
-// is kTaskRows consecutive frames of one utterance.  The list holds first the tasks that need no
-// lattice (zero fill of padding frames and of utterances without an alignment), then the frames
-// of the utterances in the order in which their chains are expected to end; a wavefront whose
-// next task belongs to an utterance whose chains are still running waits for that utterance's
-// counter (bounded polling).  Chains are launched first, so they are resident before any worker:
-// a worker only ever waits for work that is running.
-// A worker reads an utterance's lattice out of the L2 of the die (XCD) that its chains ran on, so
-// the list has a section per die, for the workers of that die.
-// The list as the host prepares it (part of the metadata image): `entries` runs of tasks,
-//   die[d]      first entry of die d's section (die[kXcds] = entries)
-//   prefix[e]   number of tasks before entry e (prefix[entries] = all tasks)
-//   info[e]     utterance (low 16 bits); log2 of the rows per task; kTaskWaits if its chains must have ended
-//   first[e]    first block (of that many rows) of the run
-constexpr int kTaskRowsLog2 = 3, kTaskRows = 1 << kTaskRowsLog2;
-constexpr int kWorkerSharePercent = 80;     // utterances whose chains end in the last fifth of the launch are left to the gradient launch
-constexpr int kTaskRowsShift = 16;
-constexpr int kTaskWaits = 1 << 30;
-constexpr int kMaxTaskEntries = 256;        // two runs per utterance: overlapped launches have at most 128 utterances
-constexpr int kWorkerWavesPerCu = 16;       // worker wavefronts per idle compute unit (the chains' register budget allows 4 per SIMD)
-constexpr int kDoneStride = 64;             // ints between two utterances' counters: each in a 256-byte block of its own, so that
-                                            // the waiting for one utterance does not hit the memory channel of the others
-constexpr int kWherePolls = 256;            // polls before a worker stops asking where an utterance's chains run (they start within microseconds)
-constexpr int kWorkerPollBudget = 1 << 22;  // polls (each followed by a short sleep) before a worker gives an utterance up
 constexpr int kDefaultPollBudget = 1 << 22;   // enough for seconds of waiting: only a stuck neighbour exhausts it
 constexpr int kMaxBatch = 65535;         // utterances index the second grid dimension of the row kernels
 constexpr int kMaxDeviceMetaB = 4096;   // utterances the device-side planner ranks in LDS
 
-// The lattice kernel reads emissions ahead of the recursion without bounds checks.  It
-// fetches kChunk steps at a time and, at the start of a pass that begins at step s0 <= Tb-1,
-// has requested steps up to s0 + 3*kChunk - 1 (two register sets, chain_schedule; with three sets,
-// chain_schedule3, requests run up to 5 chunks ahead but a round's later ones only go out while a
-// chunk of the chain is still to come, which bounds them the same): at most 3*kChunk - 1 rows past either end of
-// an utterance's block (past the end going forward, before the start going backward).  These
-// margins keep such reads inside the workspace; the values read there are never used.
+// The lattice kernel reads emissions ahead of the recursion without bounds checks: a chunk's label emissions are
+// requested two chunks before their use (chain_schedule), so up to two chunks past either end of an utterance's
+// block (past the end going forward, before the start going backward).  These margins keep such reads inside the
+// workspace; the values read there are never used.
 constexpr int kChunk = kChunkSteps;   // steps whose emissions are fetched together (plan_waves: halo % 8 == 0)
 constexpr int kOverFetchRows = 3 * kChunk;
 constexpr int kBlankSlack = kOverFetchRows + kChunk;                          // floats, each side
 constexpr int kLabelSlack = kOverFetchRows * (CTC_MAX_LABEL_LENGTH + 1);      // floats, each side
 
 // Constants that lanes without a label state read as their emission, at the start of the
-// label-emission region (inside its front slack): 20 floats of probability 0, then 20 of log 0.  Such
-// a lane points at entry 8 of its 20: a fetch reads the 8 floats before it or the 8 after it, the
-// first step the entry itself.
-constexpr int kEmissionConstantRun = 20;
-constexpr int kZeroEmission = 8, kLogZeroEmission = kEmissionConstantRun + 8, kEmissionConstants = 2 * kEmissionConstantRun;
-static_assert(kChunk <= 8 && kEmissionConstants <= kLabelSlack, "constants sit inside the front slack");
+// label-emission region (inside its front slack): a chunk of probability 0, then one of log 0.
+constexpr int kZeroEmission = 0, kLogZeroEmission = kChunk, kEmissionConstants = 2 * kChunk;
+static_assert(kEmissionConstants <= kLabelSlack, "constants sit inside the front slack");
 
 // ---- where and when a chain reads its emissions -------------------------------------------------
 // Shared by the lattice kernels and by the host-side replay that checks every read against the
@@ -338,116 +299,63 @@ static_assert(kChunk <= 8 && kEmissionConstants <= kLabelSlack, "constants sit i
 // checks, so what they may touch is defined here, once.  Offsets are in floats from the start of
 // the region (Layout::emit_label, Layout::emit_blank).
 
-// Pointer of a lane's label emissions before step 0: at the emission of its label state in frame
-// f0 (the chain's first frame), or at `constant` for a lane without a label state.  `symbol` is the
-// state's symbol (symbol-major blocks: a row per symbol), `li` its label position (gathered blocks).
-CTC_HOST_DEVICE inline int64_t label_emission_offset(const Utt& m, bool has_label, bool symbol_major, int symbol,
-                                                     int li, int f0, int constant)
+// Where a lane's label emissions of chunk `chunk` (in frame order) start; kChunk floats in frame order, a backward
+// chain uses them last to first.  `symbol` is the lane's label state's symbol, `li` its label position; a lane without
+// a label state reads `constant` whatever the chunk.
+CTC_HOST_DEVICE inline int64_t label_emission_offset(const Utt& m, bool has_label, int symbol, int li, int chunk, int constant)
 {
     if (!has_label) return constant;
-    return kLabelSlack + m.e_off + (symbol_major ? static_cast<int64_t>(symbol) * m.e_pitch + f0
-                                                 : static_cast<int64_t>(f0) * m.e_pitch + li);
+    return kLabelSlack + m.e_off + (static_cast<int64_t>(chunk) * m.e_cols + (m.e_direct == kEmitSymbols ? symbol : li)) * kChunk;
 }
-// The same pointer moves by this much per step (gathered blocks: one row; symbol-major: one float),
-// in the chain's direction fdir = +1 / -1; a lane without a label state stays where it is.
-CTC_HOST_DEVICE inline int64_t label_emission_step(const Utt& m, bool has_label, bool symbol_major, int fdir)
+// From one chunk to the next of the chain.
+CTC_HOST_DEVICE inline int64_t label_emission_step(const Utt& m, bool has_label, bool backward)
 {
-    return !has_label ? 0 : (symbol_major ? fdir : static_cast<int64_t>(fdir) * m.e_pitch);
+    return has_label ? (backward ? -1 : 1) * static_cast<int64_t>(m.e_cols) * kChunk : 0;
 }
-// Pointer of a lane's blank emissions: lane i of a chunk's load takes the frame of step (chunk start + i % kChunk).
-CTC_HOST_DEVICE inline int64_t blank_emission_offset(const Utt& m, int f0, int fdir, int lane)
+// The blank's emissions of a chunk: one value per frame, in frame order, for all lanes.  (Twice: as floats, coded
+// like the labels', and as fp64 probabilities, which the linear-domain chains take as scalars, a chunk in one load.)
+CTC_HOST_DEVICE inline int64_t blank_emission_offset(const Utt& m, int chunk)
 {
-    return kBlankSlack + m.f_off + f0 + fdir * (lane & (kChunk - 1));
+    return kBlankSlack + m.f_off + static_cast<int64_t>(chunk) * kChunk;
 }
-// The linear-domain chains take the blank's probability as an fp64 scalar, a chunk's kChunk frames in one
-// scalar load out of a block of doubles (Layout::emit_blank64, same slack in doubles): the window of the
-// chunk that starts at step s0 is w[0] .. w[kChunk - 1] from this offset, in frame order (a backward chain
-// uses it last to first).
-CTC_HOST_DEVICE inline int64_t blank64_window(const Utt& m, int f0, int fdir, int s0)
-{
-    return kBlankSlack + m.f_off + f0 + (fdir > 0 ? s0 : -s0 - (kChunk - 1));
-}
-// One fetch out of a symbol-major block reads the kChunk floats next to the pointer p in the chain's
-// direction, p[first] .. p[first + kChunk - 1], and moves p on by kChunk steps.
-CTC_HOST_DEVICE constexpr int fetch_window_first(bool backward) { return backward ? -kChunk : 1; }
+// Chunk that a chain takes as its i-th one.
+CTC_HOST_DEVICE inline int chain_chunk(int i, int chunks, bool backward) { return backward ? chunks - 1 - i : i; }
 
-// The order in which a chain requests (fetch) and consumes (run) the emissions of its steps
-// 1 .. Tb-1, kChunk steps at a time, in two register sets a and b; each callback gets the first
-// step of its chunk.  Step 0 is read directly before this.  The last requests reach up to
-// 3 * kChunk - 1 steps beyond the chain's end: what kOverFetchRows provides for.
-template <typename FetchA, typename FetchB, typename RunA, typename RunB, typename EndChunk>
-CTC_HOST_DEVICE inline void chain_schedule(int Tb, FetchA&& fetch_a, FetchB&& fetch_b, RunA&& run_a, RunB&& run_b,
-                                           EndChunk&& end_chunk)
+// The order in which a chain requests (fetch) and consumes (run) the emissions of its chunks, an even number, in
+// four register sets: set i mod 4 holds chunk i.  fetch(set, i) requests the label emissions of the chain's i-th chunk
+// and the blank's of the one before it (i > 0); run(set, i) runs its eight steps.  The sets' numbers are compile-time
+// constants (std::integral_constant).  A request out of the die's L2 takes longer than the 300 ns of a chunk, hence two
+// chunks ahead; the blank's scalars go out one chunk ahead, two sets of 16 scalar registers being all there is room for.
+// There is no branch inside a round: the compiler's count of the memory operations in flight stays exact, and a
+// wavefront waits for the emissions it is about to use only, not for stores.
+template <typename Fetch, typename Run>
+CTC_HOST_DEVICE inline void chain_schedule(int chunks, Fetch&& fetch, Run&& run)
 {
-    fetch_a(1);
-    int s0 = 1;
-    // Two whole chunks per round, with no branch on the step number inside: the compiler's count of the
-    // memory operations in flight stays exact there, and a wavefront waits for the emissions it is
-    // about to use only, not for the stores of the chunk before.
-    for (; s0 + 2 * kChunk <= Tb; s0 += 2 * kChunk) {
-        fetch_b(s0 + kChunk);
-        run_a(s0, true);
-        end_chunk();
-        fetch_a(s0 + 2 * kChunk);
-        run_b(s0 + kChunk, true);
-        end_chunk();
+    const std::integral_constant<int, 0> a{};
+    const std::integral_constant<int, 1> b{};
+    const std::integral_constant<int, 2> c{};
+    const std::integral_constant<int, 3> d{};
+    fetch(a, 0);
+    fetch(b, 1);
+    int i = 0;
+    for (; i + 4 <= chunks; i += 4) {
+        fetch(c, i + 2);
+        run(a, i);
+        fetch(d, i + 3);
+        run(b, i + 1);
+        fetch(a, i + 4);
+        run(c, i + 2);
+        fetch(b, i + 5);
+        run(d, i + 3);
     }
-    // the last, short round (run_x(s0, false) checks every step against the end)
-    if (s0 < Tb) {
-        fetch_b(s0 + kChunk);
-        run_a(s0, false);
-        end_chunk();
-        fetch_a(s0 + 2 * kChunk);
-        if (s0 + kChunk < Tb) {
-            run_b(s0 + kChunk, false);
-            end_chunk();
-        }
+    if (i < chunks) {
+        fetch(c, i + 2);
+        run(a, i);
+        run(b, i + 1);
     }
 }
 
-// The same with three register sets a, b, c: a chunk's emissions are requested two chunks before they are
-// used (a request out of the die's L2 takes longer than the 300 ns of a chunk).  The last requests reach up
-// to 3 * kChunk - 1 steps beyond the chain's end, as with two sets.
-template <typename FetchA, typename FetchB, typename FetchC, typename RunA, typename RunB, typename RunC, typename EndChunk>
-CTC_HOST_DEVICE inline void chain_schedule3(int Tb, FetchA&& fetch_a, FetchB&& fetch_b, FetchC&& fetch_c, RunA&& run_a,
-                                            RunB&& run_b, RunC&& run_c, EndChunk&& end_chunk)
-{
-    fetch_a(1);
-    fetch_b(1 + kChunk);
-    int s0 = 1;
-    for (; s0 + 3 * kChunk <= Tb; s0 += 3 * kChunk) {       // three whole chunks per round (see chain_schedule)
-        fetch_c(s0 + 2 * kChunk);
-        run_a(s0, true);
-        end_chunk();
-        fetch_a(s0 + 3 * kChunk);
-        run_b(s0 + kChunk, true);
-        end_chunk();
-        fetch_b(s0 + 4 * kChunk);
-        run_c(s0 + 2 * kChunk, true);
-        end_chunk();
-    }
-    if (s0 < Tb) {
-        fetch_c(s0 + 2 * kChunk);
-        run_a(s0, false);
-        end_chunk();
-        if (s0 + kChunk < Tb) {
-            fetch_a(s0 + 3 * kChunk);
-            run_b(s0 + kChunk, false);
-            end_chunk();
-            if (s0 + 2 * kChunk < Tb) {
-                fetch_b(s0 + 4 * kChunk);
-                run_c(s0 + 2 * kChunk, false);
-                end_chunk();
-            }
-        }
-    }
-}
-
-// With three register sets the blank's scalar window (blank64_window) goes out one chunk ahead only, together
-// with the label emissions of the chunk after it: the chunk whose window accompanies the request for s0.
-CTC_HOST_DEVICE inline int blank64_chunk_with(int s0) { return s0 - kChunkSteps > 1 ? s0 - kChunkSteps : 1; }
-
-// Row pitch (8-byte words) of an utterance's lattice blocks: column 1 + i holds label state i.
+// Row pitch of an utterance's lattice blocks: column 1 + i holds label position i.
 CTC_HOST_DEVICE inline int64_t lattice_pitch(int64_t L) { return L + 2; }
 
 // Byte offsets of the workspace regions, all multiples of 256.
@@ -456,13 +364,11 @@ struct Layout {
     size_t order = 0;     // int32[2B]    the lattice launch's chains, one per workgroup: utterance * 2 + direction
                           //              (0 forward, 1 backward), -1 for a workgroup without one (order_chains)
     size_t labels = 0;    // int32[sumL]
-    size_t tasks = 0;     // int32[9 + 3 * 2B + 1]  the workers' tasks: die[9], prefix[2B + 1], info[2B], first[2B] (see kTaskRows)
     size_t labels8 = 0;   // uint8[sumL]  the label strings once more, a byte per symbol (image only; narrow alphabets)
     size_t links = 0;     // int32[sumL]  grouping of the label positions by symbol (slot, count, first)
     size_t logp = 0;      // double[B]    log2 of the alignment mass
     size_t sink = 0;      // what lanes with nothing to store scribble on: kSinkBytes per wavefront of a lattice launch
     size_t chain_err = 0; // int32[B]     set when a lattice wavefront gave up waiting for its neighbour
-    size_t done = 0;      // int32[B * kDoneStride]  wavefronts of the utterance's chains that have ended (overlapped launches)
     size_t domain = 0;    // int32[2 B]   per utterance and direction, nonzero: that chain ran in the log domain (published by
                           //              the chain for the gradient, which must know where its exponent rows are)
     size_t row_flags = 0; // int32[B * ceil(T / 64)]  narrow alphabets: per 64 frames of an utterance, nonzero if one of
@@ -470,19 +376,16 @@ struct Layout {
                           //              launch, one word per workgroup, so that nothing needs clearing beforehand)
     size_t status = 0;    // int32[B]     device-resident metadata, records built by the narrow softmax launch: nonzero
                           //              if the utterance's lengths or labels are invalid
-    size_t where = 0;     // int32[2B]    1 + the die each chain's workgroup runs on
-    size_t leftover = 0;  // int32[B]     utterances whose rows a worker had to leave to the gradient launch
-    size_t lse = 0;       // float[B*T]   row-wise log2-sum-exp2 of the scaled logits
-    size_t emit_blank = 0; // float[slack + sum Tb + slack]  emission of blank per frame: the probability y, or
+    size_t emit_blank = 0; // float[slack + sum padded_frames(Tb) + slack]  emission of blank per frame: the probability y, or
                            // log2 y (negative) where y < 2^kLinearMinLog2 (plain log2 y in launches for
                            // the most probable alignment)
-    size_t emit_blank64 = 0; // double[slack + sum Tb + slack]  the blank's probability once more, for the scalar loads of
-                             // the linear-domain chains (blank64_window)
-    size_t emit_label = 0; // float[slack + sum Tb*L + slack]  emission of each label position, same coding
-                           // (sum Tb*A for small alphabets: emission_layout); the front slack starts with
+    size_t emit_blank64 = 0; // double[slack + sum padded_frames(Tb) + slack]  the blank's probability once more, for the scalar loads of
+                             // the linear-domain chains
+    size_t emit_label = 0; // float[slack + sum padded_frames(Tb)*L + slack]  emission of each label position, same coding
+                           // (padded_frames(Tb)*A for small alphabets: emission_layout); the front slack starts with
                            // the constants that lanes without a label state read: probability 0 and log 0
-    size_t alpha = 0;     // 8-byte words [sum Tb*(L+2)]: label states only, one unused column on either side
-    size_t beta = 0;      // of a frame's row (lattice_pitch), so that a lane may store two neighbours at once
+    size_t alpha = 0;      // 8-byte words [sum padded_frames(Tb)*(L+2)] (lattice storage, see the kernels)
+    size_t beta = 0;
     size_t total = 0;
     size_t upload_bytes = 0;   // meta..labels are contiguous: the image the host prepares per call
     int64_t sumL = 0;
@@ -534,18 +437,11 @@ struct Launch {
     int32_t* dev_status;
     int poll_budget;          // copied into every Utt record
     bool crowded;             // plan the chains for total work rather than latency (device planner)
-    // Gradient rows inside the lattice launch (kTaskRows): 0 tasks = a gradient launch of its own.
-    int n_tasks;
-    int n_task_entries;
     int n_cu;                 // compute units of the device
     // Narrow alphabets, host metadata: there is no upload launch; the softmax launch reads the pinned image
     // itself and copies it into the workspace for the launches after it, and the lattice launch releases it.
     bool folded;
-    // Device-resident metadata with workers: the softmax launch builds their task list (build_task_table) from the
-    // lengths on the GPU; n_tasks and n_task_entries are then upper bounds, the list itself says how many there are.
     bool sequential_chains = false;   // measurements: forward and backward chains in two launches, one after the other
-    bool device_tasks = false;
-    int share_percent = 0;    // (kWorkerSharePercent, or what ctc_debug_set_overlap asked for)
     Layout lay;
 };
 

@@ -30,6 +30,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "ctc_internal.h"
 
 namespace ctc {
@@ -172,25 +174,6 @@ __device__ __forceinline__ float wave_max(float v)
                  fmaxf(__int_as_float(__builtin_amdgcn_readlane(r, 32)), __int_as_float(__builtin_amdgcn_readlane(r, 48))));
 }
 
-// Inclusive running sum over the 64 lanes of a wavefront (all active): lane i receives
-// v_0 + ... + v_i, added up in a fixed order.  Four shifted additions within each row of 16
-// lanes, then the last lane of a row is added to the rows above it (row_bcast).
-template <int kCtrl, int kRowMask>
-__device__ __forceinline__ float dpp_or_zero(float v)     // lanes without a source lane, or outside the rows, get 0
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kCtrl, kRowMask, 0xf, false));
-}
-__device__ __forceinline__ float wave_running_sum(float v)
-{
-    v += dpp_or_zero<0x111, 0xf>(v);      // row_shr:1
-    v += dpp_or_zero<0x112, 0xf>(v);      // row_shr:2
-    v += dpp_or_zero<0x114, 0xf>(v);      // row_shr:4
-    v += dpp_or_zero<0x118, 0xf>(v);      // row_shr:8
-    v += dpp_or_zero<0x142, 0xa>(v);      // row_bcast:15 into rows 1 and 3
-    v += dpp_or_zero<0x143, 0xc>(v);      // row_bcast:31 into rows 2 and 3
-    return v;
-}
-
 // `slot` is 4 floats of LDS private to this reduction.
 __device__ __forceinline__ float block_sum(float v, float* slot)
 {
@@ -232,8 +215,8 @@ void ctc_upload_kernel(const int* __restrict__ host_image, int* __restrict__ ws,
 // the host never sees, so this kernel (one workgroup) does what the host launcher does
 // otherwise.  Per utterance: range checks, the count of adjacent repeats (an alignment exists
 // iff T_b >= L + repeats), the wavefront plan, and the offsets of its blocks, which are laid
-// out with the strides of the largest utterance the caller allows (labels [B][max_label],
-// emissions b * T * max_label, lattice b * T * lattice_pitch(max_label), frames b * T).  Then the run
+// out with the strides of the largest utterance the caller allows, T' = padded_frames(T) (labels [B][max_label],
+// emissions b * T' * max_label, lattice b * T' * lattice_pitch(max_label), frames b * T').  Then the run
 // order: heaviest chains first (rank by T_b x wavefronts, ties by index), -1 for the rest.
 constexpr int kPlanThreads = 1024;
 
@@ -297,8 +280,9 @@ void ctc_plan_kernel(const int* __restrict__ labels, const int* __restrict__ lab
         m.lab_off = b * max_label;
         m.flags = (runs ? kUttRuns : 0) | (bad ? kUttInvalid : 0) |
                   ((log_domain || Tb > kLinearMaxFrames || tight_fit(Tb, L, rep)) ? kUttLogDomain : 0) |
-                  (!bad && two_pairs_per_lane(L, crowded, emission_layout(A) == kEmitSymbolMajor) ? kUttTwoPairs : 0);
-        m.f_off = b * Tt;
+                  (!bad && two_pairs_per_lane(L, crowded, emission_layout(A) == kEmitSymbols) ? kUttTwoPairs : 0);
+        const int padded = static_cast<int>(padded_frames(Tt));
+        m.f_off = b * padded;
         m.waves = wp.waves;
         m.halo = wp.halo;
         const WavePlan wp2 = plan_waves2(bad ? 0 : L, crowded);
@@ -306,9 +290,9 @@ void ctc_plan_kernel(const int* __restrict__ labels, const int* __restrict__ lab
         m.halo2 = wp2.halo;
         m.poll_budget = poll_budget;
         m.e_direct = emission_layout(A);
-        m.e_pitch = m.e_direct == kEmitSymbolMajor ? Tt : m.L;
-        m.e_off = static_cast<int64_t>(b) * Tt * (m.e_direct ? A : max_label);
-        m.ab_off = static_cast<int64_t>(b) * Tt * lattice_pitch(max_label);
+        m.e_cols = m.e_direct == kEmitSymbols ? A : m.L;
+        m.e_off = static_cast<int64_t>(b) * padded * (m.e_direct == kEmitSymbols ? A : max_label);
+        m.ab_off = static_cast<int64_t>(b) * padded * lattice_pitch(max_label);
         meta[b] = m;
         weight[b] = runs ? static_cast<long long>(Tb) * ((m.flags & kUttTwoPairs) ? wp2.waves : wp.waves) : -1;
         if (bad) s_bad = 1;
@@ -355,9 +339,6 @@ struct SetupArgs {
     int* links;
     float* costs;
     int* chain_err;
-    int* done;            // per utterance: wavefronts of its chains that have ended (overlapped launches)
-    int* where;           // per chain: the die it runs on
-    int* leftover;        // per utterance: rows left to the gradient launch
     float* log0;          // kEmissionConstants floats that lattice lanes without a label state read as their
                           // emission: probability 0 (linear-domain chains) and log 0 (log-domain chains)
     double* emit_blank64; // the blank's probability per frame as fp64 (Layout::emit_blank64)
@@ -376,11 +357,10 @@ constexpr int kSetupLabelSlots = CTC_MAX_LABEL_LENGTH + 5;     // the label and 
 // quarter of the traffic), to be written out as ints to `labels_out` by the utterance's first part;
 // nullptr: `labels` holds them as ints.
 __device__ __forceinline__ void setup_words(const Utt m, const int b, const SetupArgs sa);
-// (`with_words`: the utterance's first part also writes its setup_words)
 __device__ __forceinline__ void setup_role(const Utt m, const int b, const int* __restrict__ labels,
                                            const SetupArgs sa, int* s_lab, const int part, const int parts,
                                            const unsigned char* __restrict__ labels8 = nullptr,
-                                           int* __restrict__ labels_out = nullptr, const bool with_words = true)
+                                           int* __restrict__ labels_out = nullptr)
 {
     const int tid = threadIdx.x;
     const int* lab = labels + m.lab_off;
@@ -412,7 +392,7 @@ __device__ __forceinline__ void setup_role(const Utt m, const int b, const int* 
             sa.links[m.lab_off + j] = (below + before) | (count << kLinkCountShift) |
                                       (before == 0 ? static_cast<int>(0x80000000u) : 0);
     }
-    if (part == 0 && with_words) setup_words(m, b, sa);
+    if (part == 0) setup_words(m, b, sa);
 }
 
 // The per-utterance words that every call starts from, the constants of the emission array, and the costs
@@ -421,12 +401,8 @@ __device__ __forceinline__ void setup_words(const Utt m, const int b, const Setu
 {
     if (threadIdx.x == 0) {
         sa.chain_err[b] = 0;
-        sa.done[b * kDoneStride] = 0;
-        sa.where[2 * b] = 0;
-        sa.where[2 * b + 1] = 0;
-        sa.leftover[b] = (m.flags & kUttGradientLater) ? 1 : 0;
         if (b == 0) {
-            for (int i = 0; i < kEmissionConstants; ++i) sa.log0[i] = (i < kEmissionConstantRun) ? 0.0f : static_cast<float>(kNeg);
+            for (int i = 0; i < kEmissionConstants; ++i) sa.log0[i] = i < kLogZeroEmission ? 0.0f : static_cast<float>(kNeg);
             // This launch follows the upload kernel on the stream, so the host may now reuse
             // the pinned image.
             if (sa.host_flag)
@@ -460,7 +436,7 @@ __device__ __forceinline__ Log2Parts emission_log2_parts(float v)
 {
     if (v > 0.0f)
         return {static_cast<float>(__builtin_amdgcn_frexp_expf(v)), fast_log2(__builtin_amdgcn_frexp_mantf(v))};
-    return {v, 0.0f};
+    return {v == 0.0f ? static_cast<float>(kNeg) : v, 0.0f};         // (0: a label of a virtual frame)
 }
 __device__ __forceinline__ double emission_log2(float v)
 {
@@ -468,6 +444,34 @@ __device__ __forceinline__ double emission_log2(float v)
     return static_cast<double>(p.whole) + static_cast<double>(p.part);
 }
 __device__ __forceinline__ float emission_probability(float v) { return fmaxf(v, 0.0f); }
+// A softmax output from its coded emission.
+__device__ __forceinline__ float emission_softmax(float v) { return v < 0.0f ? fast_exp2(v) : v; }
+// Emissions of virtual frames (emission_layout in the launcher's header): blank with probability 1, labels with 0.
+__device__ __forceinline__ float virtual_emission(bool blank, bool plain_logs)
+{
+    return plain_logs ? (blank ? 0.0f : static_cast<float>(kNeg)) : (blank ? 1.0f : 0.0f);
+}
+// The blank's emission of one padded frame, in both forms.
+__device__ __forceinline__ void store_blank(float* __restrict__ emit_blank, double* __restrict__ emit_blank64, size_t frame, float e)
+{
+    emit_blank[kBlankSlack + frame] = e;
+    emit_blank64[kBlankSlack + frame] = static_cast<double>(emission_probability(e));
+}
+// Where the emission of column `column` in frame `t` of an utterance sits.
+__device__ __forceinline__ size_t emission_at(int64_t e_off, int columns, int t, int column)
+{
+    return kLabelSlack + static_cast<size_t>(e_off) + (static_cast<size_t>(t / kChunk) * columns + column) * kChunk + t % kChunk;
+}
+// The virtual frames of an utterance of a wide alphabet, by the workgroup of its last frame.
+__device__ __forceinline__ void store_virtual_frames(const Utt& m, float* __restrict__ emit_blank, double* __restrict__ emit_blank64,
+                                                     float* __restrict__ emit_label, bool plain_logs)
+{
+    for (int t = m.Tb; t < static_cast<int>(padded_frames(m.Tb)); ++t) {
+        if (threadIdx.x == 0) store_blank(emit_blank, emit_blank64, static_cast<size_t>(m.f_off) + t, virtual_emission(true, plain_logs));
+        for (int j = threadIdx.x; j < m.L; j += kRowThreads)
+            emit_label[emission_at(m.e_off, m.L, t, j)] = virtual_emission(false, plain_logs);
+    }
+}
 __device__ __forceinline__ void raise_log_domain(Utt* meta, int b, bool small)
 {
     if (small) atomicOr(&meta[b].flags, kUttLogDomain);
@@ -485,7 +489,7 @@ template <typename T>
 __global__ __launch_bounds__(kRowThreads)
 void ctc_softmax_kernel(const T* __restrict__ x, T* __restrict__ grads,
                         Utt* __restrict__ meta,
-                        const int* __restrict__ labels, float* __restrict__ lse,
+                        const int* __restrict__ labels,
                         float* __restrict__ emit_blank, float* __restrict__ emit_label,
                         const SetupArgs sa, int Tt, int B, int A, int blank)
 {
@@ -514,8 +518,6 @@ void ctc_softmax_kernel(const T* __restrict__ x, T* __restrict__ grads,
     // log2 y_k = (x_k - max) log2 e - log2 sum: the difference first, so that the error is relative to
     // log2 y_k itself and not to the row's offset (see log2_softmax)
     const float ls = fast_log2(s);
-    const float l2 = fmaf(mx, kLog2e, ls);
-    if (threadIdx.x == 0) lse[static_cast<size_t>(b) * Tt + t] = l2;
 
     if (grads)
         for (int k = threadIdx.x; k < A; k += kRowThreads)
@@ -524,13 +526,13 @@ void ctc_softmax_kernel(const T* __restrict__ x, T* __restrict__ grads,
     if (threadIdx.x == 0)
     {
         const float e = encode_emission(log2_softmax(load_elem(row, blank), mx, ls), small, sa.plain_logs);
-        emit_blank[kBlankSlack + m.f_off + t] = e;
-        sa.emit_blank64[kBlankSlack + m.f_off + t] = static_cast<double>(emission_probability(e));
+        store_blank(emit_blank, sa.emit_blank64, static_cast<size_t>(m.f_off) + t, e);
     }
-    float* erow = emit_label + kLabelSlack + m.e_off + static_cast<size_t>(t) * m.L;
+    if (t == m.Tb - 1) store_virtual_frames(m, emit_blank, sa.emit_blank64, emit_label, sa.plain_logs);
+    float* erow = emit_label + emission_at(m.e_off, m.L, t, 0);
     const int* lab = labels + m.lab_off;
     for (int j = threadIdx.x; j < m.L; j += kRowThreads)
-        erow[j] = encode_emission(log2_softmax(load_elem(row, lab[j]), mx, ls), small, sa.plain_logs);
+        erow[static_cast<size_t>(j) * kChunk] = encode_emission(log2_softmax(load_elem(row, lab[j]), mx, ls), small, sa.plain_logs);
     raise_log_domain(meta, b, small);
 }
 
@@ -542,7 +544,7 @@ template <typename T>
 __global__ __launch_bounds__(kRowThreads)
 void ctc_softmax_wide_kernel(const T* __restrict__ x, T* __restrict__ grads,
                              Utt* __restrict__ meta,
-                             const int* __restrict__ labels, float* __restrict__ lse,
+                             const int* __restrict__ labels,
                              float* __restrict__ emit_blank, float* __restrict__ emit_label,
                              const SetupArgs sa, int Tt, int B, int A, int blank)
 {
@@ -588,8 +590,6 @@ void ctc_softmax_wide_kernel(const T* __restrict__ x, T* __restrict__ grads,
     }
     sum = block_sum(sum, red + 4);
     const float ls = fast_log2(sum);
-    const float l2 = fmaf(mx, kLog2e, ls);
-    if (tid == 0) lse[static_cast<size_t>(b) * Tt + t] = l2;
 
 #pragma unroll
     for (int i = 0; i < kVecs; ++i) {
@@ -605,25 +605,52 @@ void ctc_softmax_wide_kernel(const T* __restrict__ x, T* __restrict__ grads,
     if (tid == 0)
     {
         const float e = encode_emission(log2_softmax(load_elem(row, blank), mx, ls), small, sa.plain_logs);
-        emit_blank[kBlankSlack + m.f_off + t] = e;
-        sa.emit_blank64[kBlankSlack + m.f_off + t] = static_cast<double>(emission_probability(e));
+        store_blank(emit_blank, sa.emit_blank64, static_cast<size_t>(m.f_off) + t, e);
     }
-    float* erow = emit_label + kLabelSlack + m.e_off + static_cast<size_t>(t) * m.L;
+    if (t == m.Tb - 1) store_virtual_frames(m, emit_blank, sa.emit_blank64, emit_label, sa.plain_logs);
+    float* erow = emit_label + emission_at(m.e_off, m.L, t, 0);
     const int* lab = labels + m.lab_off;
     for (int j = tid; j < m.L; j += kRowThreads)
-        erow[j] = encode_emission(log2_softmax(load_elem(row, lab[j]), mx, ls), small, sa.plain_logs);
+        erow[static_cast<size_t>(j) * kChunk] = encode_emission(log2_softmax(load_elem(row, lab[j]), mx, ls), small, sa.plain_logs);
     raise_log_domain(meta, b, small);
 }
 
-// Narrow alphabets: a workgroup takes kRows consecutive frames of one utterance, 256 / kRows
+// A workgroup's share of the emission block: kRows frames from t0 on whose coded rows sit in lp[kRows][A], virtual
+// frames past the utterance's end.  kRows is a whole number of chunks.  Returns whether an emission is too
+// small for the linear domain.
+template <int kRows>
+__device__ __forceinline__ bool store_symbol_chunks(const float* lp, int Tb, int f_off, int64_t e_off, int t0, int A, int blank,
+                                                    float* __restrict__ emit_blank, double* __restrict__ emit_blank64,
+                                                    float* __restrict__ emit_label, bool plain_logs)
+{
+    const int tid = threadIdx.x, rows = min(kRows, Tb - t0), padded = min(kRows, static_cast<int>(padded_frames(Tb)) - t0);
+    bool small = false;
+    if (tid < padded) {
+        const float e = tid < rows ? lp[tid * A + blank] : virtual_emission(true, plain_logs);
+        store_blank(emit_blank, emit_blank64, static_cast<size_t>(f_off) + t0 + tid, e);
+        small = !plain_logs && e < 0.0f;
+    }
+    // a wavefront per chunk: [symbol][frame], 8 A floats in a row
+    float* const out = emit_label + kLabelSlack + e_off + static_cast<size_t>(t0) * A;
+    for (int chunk = tid >> 6; chunk * kChunk < padded; chunk += kRowThreads / 64)
+        for (int i = tid & 63; i < kChunk * A; i += 64) {
+            const int a = i / kChunk, r = chunk * kChunk + i % kChunk;
+            const float e = r < rows ? lp[r * A + a] : virtual_emission(a == blank, plain_logs);
+            out[chunk * kChunk * A + i] = e;
+            small = small || (!plain_logs && e < 0.0f);
+        }
+    return small;
+}
+
+// Alphabets of up to 2048 symbols: a workgroup takes kRows consecutive frames of one utterance, 256 / kRows
 // threads per row.  The normalised rows (as coded emissions) are kept in LDS
 // (kRows * A floats, dynamic), from where the emissions of all label positions are gathered
-// with the label symbols held in registers.  grid (ceil(T / kRows) + 1, B), the extra column
-// does the setup role.
+// with the label symbols held in registers.  grid (ceil(padded T / kRows) + parts, B), the extra columns
+// do the setup role.
 template <typename T, int kRows>
 __global__ __launch_bounds__(kRowThreads)
-void ctc_softmax_rows_kernel(const T* __restrict__ x, Utt* __restrict__ meta,
-                             const int* __restrict__ labels, float* __restrict__ lse,
+void ctc_softmax_rows_kernel(const T* __restrict__ x, T* __restrict__ grads, Utt* __restrict__ meta,
+                             const int* __restrict__ labels,
                              float* __restrict__ emit_blank, float* __restrict__ emit_label,
                              const SetupArgs sa, int Tt, int B, int A, int blank)
 {
@@ -634,16 +661,29 @@ void ctc_softmax_rows_kernel(const T* __restrict__ x, Utt* __restrict__ meta,
     const int b = blockIdx.y, tid = threadIdx.x;
     const Utt m = meta[b];
     if (blockIdx.x >= gridDim.x - sa.parts) {
-        setup_role(m, b, labels, sa, s_lab, static_cast<int>(blockIdx.x - (gridDim.x - sa.parts)), sa.parts);
+        const int part = static_cast<int>(blockIdx.x - (gridDim.x - sa.parts));
+        // (the grouping of label positions serves the gradient of gathered emissions)
+        if (kRows == 64) {
+            if (part == 0) setup_words(m, b, sa);
+        } else {
+            setup_role(m, b, labels, sa, s_lab, part, sa.parts);
+        }
         return;
     }
     const int t0 = blockIdx.x * kRows;
-    if (t0 >= m.Tb) return;
+    const bool runs = (m.flags & kUttRuns) != 0;
     const int r = tid / kPerRow, q = tid % kPerRow, t = t0 + r;
+    // Gathered emissions: the gradient of a row is the softmax itself except in the columns of the label's symbols, so
+    // it is written here, while the row is at hand (zeros for rows without an alignment); the columns are corrected after
+    // the recursions.  (grads == nullptr: no gradient wanted; narrow alphabets write theirs in the gradient launch.)
+    T* const grow = (kRows < 64 && grads && t < Tt) ? grads + (static_cast<size_t>(t) * B + b) * A : nullptr;
+    if (grow && (t >= m.Tb || !runs))
+        for (int k = q; k < A; k += kPerRow) store_elem(grow, k, 0.0f);
+    if (!runs || t0 >= static_cast<int>(padded_frames(m.Tb))) return;
     float* lrow = lp + r * A;
     // Requested before the row work so that its latency overlaps the row's.
     const int* lab = labels + m.lab_off;
-    const int c_first = (!m.e_direct && tid < m.L) ? lab[tid] : 0;
+    const int c_first = (kRows < 64 && tid < m.L) ? lab[tid] : 0;
     if (t < m.Tb) {
         const T* row = x + (static_cast<size_t>(t) * B + b) * A;
         float mx = -__builtin_inff();
@@ -667,44 +707,39 @@ void ctc_softmax_rows_kernel(const T* __restrict__ x, Utt* __restrict__ meta,
         for (int k = q; k < A; k += kPerRow) sum += fast_exp2((lrow[k] - mx) * kLog2e);
         sum = (kPerRow == 4) ? quad_sum(sum) : (kPerRow == 16) ? row16_sum(sum) : wave_sum(sum);
         const float ls = fast_log2(sum);
-        const float l2 = fmaf(mx, kLog2e, ls);
         // (coded as emissions; `unused` because what counts is which of them get stored below)
         bool unused = false;
-        for (int k = q; k < A; k += kPerRow) lrow[k] = encode_emission(log2_softmax(lrow[k], mx, ls), unused, sa.plain_logs);
-        if (q == 0) lse[static_cast<size_t>(b) * Tt + t] = l2;
+        for (int k = q; k < A; k += kPerRow) {
+            const float e = encode_emission(log2_softmax(lrow[k], mx, ls), unused, sa.plain_logs);
+            lrow[k] = e;
+            if (grow) store_elem(grow, k, emission_softmax(e));
+        }
     }
-    if (!(m.flags & kUttRuns)) return;
     __syncthreads();
-    const int rows = min(kRows, m.Tb - t0);
     bool small = false;
-    if (tid < rows) {
-        const float e = lp[tid * A + blank];
-        emit_blank[kBlankSlack + m.f_off + t0 + tid] = e;
-        sa.emit_blank64[kBlankSlack + m.f_off + t0 + tid] = static_cast<double>(emission_probability(e));
-        small = !sa.plain_logs && e < 0.0f;
-    }
-    if (m.e_direct == kEmitSymbolMajor) {
-        // Small alphabet: the normalised rows themselves are the emission block, stored symbol-major
-        // (a symbol's frames side by side, e_pitch floats per symbol: fetch_frames).  A wavefront
-        // writes up to 64 frames of one symbol at a time.
-        float* out = emit_label + kLabelSlack + m.e_off + t0;
-        const int rr = tid & 63;
-        if (rr < rows)
-            for (int a = tid >> 6; a < A; a += kRowThreads / 64) {
-                const float e = lp[rr * A + a];
-                out[static_cast<size_t>(a) * m.e_pitch + rr] = e;
-                small = small || (!sa.plain_logs && e < 0.0f);
+    if constexpr (kRows == 64) {
+        // narrow alphabet: the normalised rows themselves are the emission block
+        small = store_symbol_chunks<kRows>(lp, m.Tb, m.f_off, m.e_off, t0, A, blank, emit_blank, sa.emit_blank64, emit_label, sa.plain_logs);
+    } else {
+        const int rows = min(kRows, m.Tb - t0), padded = min(kRows, static_cast<int>(padded_frames(m.Tb)) - t0);
+        if (tid < padded) {
+            const float e = tid < rows ? lp[tid * A + blank] : virtual_emission(true, sa.plain_logs);
+            store_blank(emit_blank, sa.emit_blank64, static_cast<size_t>(m.f_off) + t0 + tid, e);
+            small = !sa.plain_logs && e < 0.0f;
+        }
+        // four frames of a position in one 16-byte store (a chunk's eight lie side by side)
+        for (int j = tid; j < m.L; j += kRowThreads) {
+            const int c = (j == tid) ? c_first : lab[j];
+#pragma unroll
+            for (int r0 = 0; r0 < kRows; r0 += 4) {
+                float e[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    e[i] = r0 + i < rows ? lp[(r0 + i) * A + c] : virtual_emission(false, sa.plain_logs);
+                    small = small || (!sa.plain_logs && e[i] < 0.0f);
+                }
+                *reinterpret_cast<float4*>(emit_label + emission_at(m.e_off, m.L, t0 + r0, j)) = make_float4(e[0], e[1], e[2], e[3]);
             }
-        raise_log_domain(meta, b, small);
-        return;
-    }
-    float* ebase = emit_label + kLabelSlack + m.e_off + static_cast<size_t>(t0) * m.L;
-    for (int j = tid; j < m.L; j += kRowThreads) {
-        const int c = (j == tid) ? c_first : lab[j];
-        for (int rr = 0; rr < rows; ++rr) {
-            const float e = lp[rr * A + c];
-            ebase[static_cast<size_t>(rr) * m.L + j] = e;
-            small = small || (!sa.plain_logs && e < 0.0f);
         }
     }
     raise_log_domain(meta, b, small);
@@ -732,9 +767,8 @@ struct NarrowImage {
 // What the workgroups with rows need to know of an utterance travels with the kernel's arguments
 // (hundreds of small reads out of host memory at once were measured to take longer than the upload
 // launch they replace): its frames, with kRowsRun set if its chains run, and the frames of all
-// utterances before it.  An utterance's emission block starts A times that many floats into the
-// region and has a pitch of its frames.
-constexpr int kRowsRun = 1 << 30, kRowsGradientLater = 1 << 29;     // (flags of the record that ride along)
+// utterances before it (padded).  An utterance's emission block starts A times that many floats into the region.
+constexpr int kRowsRun = 1 << 30;     // (a flag of the record that rides along)
 struct NarrowRows {
     int frames[kNarrowMaxB];
     int frames_before[kNarrowMaxB];
@@ -763,8 +797,6 @@ struct NarrowDevice {
     int* status_words;            // [B] nonzero: the utterance's lengths or labels are invalid
     int max_label, poll_budget, dirs;
     bool crowded, log_domain;
-    int* tasks;                   // the lattice launch's workers' task list, to be built here (nullptr: no workers)
-    int share_percent;            // utterances whose chains end later than this share of the longest go to the gradient launch
     int n_cu;                     // compute units of the device (a multiple of kChainBlock, or 0: keep the plain order)
 };
 
@@ -781,143 +813,11 @@ __device__ __forceinline__ long long chain_weight(const PlanTable& plans, int L,
 {
     return static_cast<long long>(Tb) * chain_waves(plans, L, Tb, Tt, max_label, log_domain);
 }
-// When an utterance's chains end, in the unit the launcher orders by (prepare: chains that exchange
-// between wavefronts take a little longer per frame); 0 for an utterance without frames or with bad lengths.
-__device__ __forceinline__ int chain_end_estimate(const PlanTable& plans, int L, int Tb, int Tt, int max_label, bool log_domain)
-{
-    const int waves = chain_waves(plans, L, Tb, Tt, max_label, log_domain);
-    return waves == 0 ? 0 : Tb * (waves > 1 ? 5 : 4);
-}
-__device__ __forceinline__ bool ends_late(int ends, int last_end, int share_percent)
-{
-    return static_cast<long long>(ends) * 100 > static_cast<long long>(last_end) * share_percent;
-}
-
-// The workers' task list (see gradient_worker and the launcher's prepare, whose list this reproduces from the
-// device-resident lengths), by one workgroup.  An utterance's place in the run order is its rank by weight
-// over all B utterances (build_record), its chains' die that rank mod kXcds (the order's blocks of kChainBlock
-// keep both chains of an utterance on one die; in a last, partial block they may not be, and a worker that
-// finds them elsewhere leaves the utterance to the gradient launch).  Whether an alignment exists is not
-// looked at: the workers take that from the records.  B <= kMaxTaskEntries / 2.
-__device__ __forceinline__ void build_task_table(const NarrowDevice& dv, const PlanTable& plans, int Tt, int B)
-{
-    constexpr int kMax = kMaxTaskEntries / 2;
-    static_assert(kRowThreads == 2 * kMax, "two threads per utterance");
-    __shared__ long long s_weight[kMax];
-    __shared__ int s_frames[kMax], s_ends[kMax], s_rank[kMax], s_wait[kMax], s_pad[kMax], s_at[kMax], s_sum[kMax];
-    __shared__ int s_last_end, s_entries[kXcds][2], s_tasks[kXcds][2];      // per die: [padding rows, waiting rows]
-    __shared__ int s_entries_before[kXcds + 1], s_tasks_before[kXcds + 1];
-    const int tid = threadIdx.x, blocks = (Tt + kTaskRows - 1) / kTaskRows;
-    // Four threads per utterance j (two beyond 64 utterances), each comparing it with a quarter (half) of the
-    // others in one unrolled pass, so that its LDS reads travel together; entries beyond B are neutral.
-    const int span = B <= kMax / 2 ? kMax / 2 : kMax, share = span / (kRowThreads / span);
-    const int j = tid & (span - 1), k_first = (tid / span) * share, k_end = k_first + share;
-    if (tid == 0) s_last_end = 0;
-    if (tid < kXcds * 2) {
-        s_entries[tid >> 1][tid & 1] = 0;
-        s_tasks[tid >> 1][tid & 1] = 0;
-    }
-    if (tid < B) {
-        const int L = dv.label_lengths[tid], Tb = dv.input_lengths[tid];
-        s_weight[tid] = chain_weight(plans, L, Tb, Tt, dv.max_label, dv.log_domain);
-        s_ends[tid] = chain_end_estimate(plans, L, Tb, Tt, dv.max_label, dv.log_domain);
-        s_frames[tid] = Tb;
-        s_rank[tid] = 0;
-        s_at[tid] = 0;
-        s_sum[tid] = 0;
-    } else if (tid < kMax) {
-        s_weight[tid] = -1;                             // (lighter than any utterance)
-        s_ends[tid] = 0;
-        s_rank[tid] = 0;
-        s_wait[tid] = 0;
-    }
-    __syncthreads();
-    if (tid < B && s_ends[tid] > 0) atomicMax(&s_last_end, s_ends[tid]);
-    if (j < B) {
-        const long long mine = s_weight[j];
-        int before = 0;
-#pragma unroll 16
-        for (int k = k_first; k < k_end; ++k) before += (s_weight[k] > mine || (s_weight[k] == mine && k < j)) ? 1 : 0;
-        if (before) atomicAdd(&s_rank[j], before);
-    }
-    __syncthreads();
-    if (tid < B) {
-        const int data = s_ends[tid] > 0 ? (s_frames[tid] + kTaskRows - 1) / kTaskRows : 0;
-        s_pad[tid] = blocks - data;
-        s_wait[tid] = ends_late(s_ends[tid], s_last_end, dv.share_percent) ? 0 : data;
-        if (s_pad[tid] > 0) {
-            atomicAdd(&s_entries[tid % kXcds][0], 1);
-            atomicAdd(&s_tasks[tid % kXcds][0], s_pad[tid]);
-        }
-        if (s_wait[tid] > 0) {
-            atomicAdd(&s_entries[s_rank[tid] % kXcds][1], 1);
-            atomicAdd(&s_tasks[s_rank[tid] % kXcds][1], s_wait[tid]);
-        }
-    }
-    __syncthreads();
-    // a waiting entry's place in its die's section: the die's utterances that end earlier (ties: in the run order)
-    if (j < B && s_wait[j] > 0) {
-        const int die = s_rank[j] % kXcds, ends = s_ends[j], rank = s_rank[j];
-        int at = 0, sum = 0;
-#pragma unroll 16
-        for (int k = k_first; k < k_end; ++k) {
-            const int wait_k = s_wait[k], rank_k = s_rank[k], ends_k = s_ends[k];
-            const bool earlier = wait_k > 0 && rank_k % kXcds == die && (ends_k < ends || (ends_k == ends && rank_k < rank));
-            at += earlier ? 1 : 0;
-            sum += earlier ? wait_k : 0;
-        }
-        if (at) {
-            atomicAdd(&s_at[j], at);
-            atomicAdd(&s_sum[j], sum);
-        }
-    }
-    if (tid <= kXcds) {
-        int entries = 0, tasks = 0;
-        for (int d = 0; d < tid; ++d) {
-            entries += s_entries[d][0] + s_entries[d][1];
-            tasks += s_tasks[d][0] + s_tasks[d][1];
-        }
-        s_entries_before[tid] = entries;
-        s_tasks_before[tid] = tasks;
-    }
-    __syncthreads();
-    int* const task_die = dv.tasks;                     // [kXcds + 1]
-    int* const task_prefix = task_die + kXcds + 1;      // [2B + 1]
-    int* const task_info = task_prefix + 2 * B + 1;     // [2B]
-    int* const task_first = task_info + 2 * B;          // [2B]
-    if (tid < B) {
-        if (s_pad[tid] > 0) {
-            // the die's padding rows come first, by utterance number
-            const int die = tid % kXcds;
-            int at = 0, sum = 0;
-            for (int k = die; k < tid; k += kXcds)
-                if (s_pad[k] > 0) {
-                    ++at;
-                    sum += s_pad[k];
-                }
-            const int e = s_entries_before[die] + at;
-            task_prefix[e] = s_tasks_before[die] + sum;
-            task_info[e] = tid | (kTaskRowsLog2 << kTaskRowsShift);
-            task_first[e] = blocks - s_pad[tid];
-        }
-        if (s_wait[tid] > 0) {
-            // then its utterances as their chains end
-            const int die = s_rank[tid] % kXcds;
-            const int e = s_entries_before[die] + s_entries[die][0] + s_at[tid];
-            task_prefix[e] = s_tasks_before[die] + s_tasks[die][0] + s_sum[tid];
-            task_info[e] = tid | kTaskWaits | (kTaskRowsLog2 << kTaskRowsShift);
-            task_first[e] = 0;
-        }
-    }
-    if (tid <= kXcds) task_die[tid] = s_entries_before[tid];
-    if (tid == 0) task_prefix[s_entries_before[kXcds]] = s_tasks_before[kXcds];
-}
-
-// By the whole workgroup; `s_lab` holds scratch ints.  Returns the record (the same in every thread).
+// By the whole workgroup.  Returns the record (the same in every thread).
 __device__ __forceinline__ Utt build_record(const NarrowDevice& dv, const PlanTable& plans, int b, int Tt, int B, int A,
                                             int blank)
 {
-    __shared__ int s_repeats, s_bad, s_rank, s_last_end;
+    __shared__ int s_repeats, s_bad, s_rank;
     const int tid = threadIdx.x;
     const int L_in = dv.label_lengths[b], Tb_in = dv.input_lengths[b];
     const bool bad_length = L_in < 0 || L_in > dv.max_label || Tb_in < 0 || Tb_in > Tt;
@@ -926,7 +826,6 @@ __device__ __forceinline__ Utt build_record(const NarrowDevice& dv, const PlanTa
         s_repeats = 0;
         s_bad = 0;
         s_rank = 0;
-        s_last_end = 0;
     }
     __syncthreads();
     const int* lab = dv.labels + static_cast<size_t>(b) * dv.max_label;
@@ -940,19 +839,14 @@ __device__ __forceinline__ Utt build_record(const NarrowDevice& dv, const PlanTa
     if (bad) s_bad = 1;
     // the utterances that come before this one in the run order: heavier, or as heavy and earlier
     const long long mine = chain_weight(plans, L_in, Tb_in, Tt, dv.max_label, dv.log_domain);
-    int before = 0, last_end = 0;
+    int before = 0;
     for (int j = tid; j < B; j += kRowThreads) {
         const int Lj = dv.label_lengths[j], Tj = dv.input_lengths[j];
         const long long w = chain_weight(plans, Lj, Tj, Tt, dv.max_label, dv.log_domain);
         before += (w > mine || (w == mine && j < b)) ? 1 : 0;
-        if (dv.tasks) last_end = max(last_end, chain_end_estimate(plans, Lj, Tj, Tt, dv.max_label, dv.log_domain));
     }
     if (before) atomicAdd(&s_rank, before);
-    if (last_end) atomicMax(&s_last_end, last_end);
     __syncthreads();
-    // (workers in the lattice launch: the utterances that end last are the gradient launch's, as in prepare)
-    const bool later = dv.tasks && ends_late(chain_end_estimate(plans, L_in, Tb_in, Tt, dv.max_label, dv.log_domain),
-                                             s_last_end, dv.share_percent);
     const bool invalid = bad_length || s_bad != 0;
     const int Tb = invalid ? 0 : Tb_in;
     const bool runs = !invalid && Tb > 0 && Tb >= L + s_repeats;
@@ -963,17 +857,18 @@ __device__ __forceinline__ Utt build_record(const NarrowDevice& dv, const PlanTa
     m.lab_off = b * dv.max_label;
     m.flags = (runs ? kUttRuns : 0) | (invalid ? kUttInvalid : 0) |
               ((dv.log_domain || Tb > kLinearMaxFrames || tight_fit(Tb, L, s_repeats)) ? kUttLogDomain : 0) |
-              (!invalid && plans.two_pairs(L) ? kUttTwoPairs : 0) | (later ? kUttGradientLater : 0);
-    m.f_off = b * Tt;
+              (!invalid && plans.two_pairs(L) ? kUttTwoPairs : 0);
+    const int padded = static_cast<int>(padded_frames(Tt));
+    m.f_off = b * padded;
     m.waves = plans.waves1(Lp);
     m.halo = plans.halo1(Lp);
     m.waves2 = plans.waves2(Lp);
     m.halo2 = plans.halo2(Lp);
     m.poll_budget = dv.poll_budget;
     m.e_direct = emission_layout(A);
-    m.e_pitch = m.e_direct == kEmitSymbolMajor ? Tt : m.L;
-    m.e_off = static_cast<int64_t>(b) * Tt * (m.e_direct ? A : dv.max_label);
-    m.ab_off = static_cast<int64_t>(b) * Tt * lattice_pitch(dv.max_label);
+    m.e_cols = m.e_direct == kEmitSymbols ? A : m.L;
+    m.e_off = static_cast<int64_t>(b) * padded * (m.e_direct == kEmitSymbols ? A : dv.max_label);
+    m.ab_off = static_cast<int64_t>(b) * padded * lattice_pitch(dv.max_label);
     if (tid == 0) {
         dv.meta[b] = m;
         dv.status_words[b] = invalid ? 1 : 0;
@@ -996,7 +891,7 @@ __device__ __forceinline__ Utt build_record(const NarrowDevice& dv, const PlanTa
 template <typename T>
 __global__ __launch_bounds__(kRowThreads)
 void ctc_softmax_narrow_kernel(const T* __restrict__ x, const NarrowImage image, int* __restrict__ workspace_words,
-                               float* __restrict__ lse, float* __restrict__ emit_blank,
+                               float* __restrict__ emit_blank,
                                float* __restrict__ emit_label, int* __restrict__ row_flags,
                                const SetupArgs sa, const NarrowArgs args, const NarrowDevice dv,
                                int Tt, int B, int A, int blank)
@@ -1004,40 +899,20 @@ void ctc_softmax_narrow_kernel(const T* __restrict__ x, const NarrowImage image,
     constexpr int kRows = kFlagFrames, kPerRow = kRowThreads / kRows;
     static_assert(kPerRow == 4, "a quad per frame");
     extern __shared__ float lp[];                          // [kRows][A]
-    __shared__ int s_lab[kSetupLabelSlots];
     __shared__ int s_small;
     const int b = blockIdx.y, tid = threadIdx.x;
-    // (device-resident metadata with workers in the lattice launch: one more column, whose first workgroup
-    // builds their task list)
-    const int row_blocks = static_cast<int>(gridDim.x) - sa.parts - (dv.tasks ? 1 : 0);
-    if (dv.tasks && blockIdx.x == gridDim.x - 1) {
-        if (b == 0) build_task_table(dv, args.plans, Tt, B);
-        return;
-    }
+    const int row_blocks = static_cast<int>(gridDim.x) - sa.parts;
     if (static_cast<int>(blockIdx.x) >= row_blocks && dv.labels) {
-        // device-resident metadata: the first of these workgroups builds the record (and writes what depends on
-        // it), the others group the label's positions, for which they need the label only: side by side, so that
-        // the launch lasts as long as the longer of the two, not their sum
-        const int part = static_cast<int>(blockIdx.x) - row_blocks;
-        if (part == 0) {
-            setup_words(build_record(dv, args.plans, b, Tt, B, A, blank), b, sa);
-            return;
-        }
-        Utt m{};
-        const int L = dv.label_lengths[b], Tb = dv.input_lengths[b];
-        const bool bad_length = L < 0 || L > dv.max_label || Tb < 0 || Tb > Tt;
-        m.L = bad_length ? 0 : L;
-        m.lab_off = b * dv.max_label;
-        setup_role(m, b, dv.labels, sa, s_lab, part - 1, sa.parts - 1, nullptr, nullptr, false);
+        // device-resident metadata: this workgroup builds the record and writes what depends on it
+        setup_words(build_record(dv, args.plans, b, Tt, B, A, blank), b, sa);
         return;
     }
     if (static_cast<int>(blockIdx.x) >= row_blocks) {
-        // (what the setup role uses of the utterance's record: no read of the record out of host memory,
-        // so that the label's bytes are the first and only thing this workgroup waits for from there)
+        // (what is used of the utterance's record comes with the arguments: no read of the record out of host memory,
+        // so that its share of the image is the first and only thing this workgroup waits for from there)
         Utt m{};
-        m.Tb = args.rows.frames[b] & (kRowsGradientLater - 1);
-        m.flags = ((args.rows.frames[b] & kRowsRun) ? kUttRuns : 0) |
-                  ((args.rows.frames[b] & kRowsGradientLater) ? kUttGradientLater : 0);
+        m.Tb = args.rows.frames[b] & (kRowsRun - 1);
+        m.flags = (args.rows.frames[b] & kRowsRun) ? kUttRuns : 0;
         m.L = args.rows.label_length[b];
         m.lab_off = args.rows.labels_before[b];
         const int part = static_cast<int>(blockIdx.x) - row_blocks;
@@ -1046,29 +921,31 @@ void ctc_softmax_narrow_kernel(const T* __restrict__ x, const NarrowImage image,
         const int share = (image.count + groups - 1) / groups;
         for (int i = group * share + tid; i < min((group + 1) * share, image.count); i += kRowThreads)
             if (i < image.labels_first || i >= image.labels_end) workspace_words[i] = image.words[i];
-        setup_role(m, b, nullptr, sa, s_lab, part, sa.parts,
-                   reinterpret_cast<const unsigned char*>(image.words) + image.labels8_offset, image.labels_out);
+        // its utterance's label, from the bytes
+        const unsigned char* const labels8 = reinterpret_cast<const unsigned char*>(image.words) + image.labels8_offset;
+        if (part == 0) {
+            for (int j = tid; j < m.L; j += kRowThreads) image.labels_out[m.lab_off + j] = labels8[m.lab_off + j];
+            setup_words(m, b, sa);
+        }
         return;
     }
     // (the fields of the utterance's record that the rows need)
-    struct { int Tb, flags, f_off, e_pitch; int64_t e_off; } m;
+    struct { int Tb, flags, f_off; int64_t e_off; } m;
     if (dv.labels) {
         // (whether an alignment exists is not known here: the rows of every utterance with frames are prepared)
         const int L = dv.label_lengths[b], Tb = dv.input_lengths[b];
         const bool bad_length = L < 0 || L > dv.max_label || Tb < 0 || Tb > Tt;
         m.Tb = bad_length ? 0 : Tb;
         m.flags = kUttRuns;
-        m.f_off = b * Tt;
-        m.e_pitch = Tt;
+        m.f_off = b * static_cast<int>(padded_frames(Tt));
     } else {
-        m.Tb = args.rows.frames[b] & (kRowsGradientLater - 1);
+        m.Tb = args.rows.frames[b] & (kRowsRun - 1);
         m.flags = (args.rows.frames[b] & kRowsRun) ? kUttRuns : 0;
         m.f_off = args.rows.frames_before[b];
-        m.e_pitch = m.Tb;
     }
     m.e_off = static_cast<int64_t>(m.f_off) * A;
     const int t0 = blockIdx.x * kRows;
-    if (t0 >= m.Tb) return;
+    if (t0 >= m.Tb || !(m.flags & kUttRuns)) return;
     if (tid == 0) s_small = 0;
     const int r = tid / kPerRow, q = tid % kPerRow, t = t0 + r;
     float* lrow = lp + r * A;
@@ -1095,31 +972,12 @@ void ctc_softmax_narrow_kernel(const T* __restrict__ x, const NarrowImage image,
         for (int k = q; k < A; k += kPerRow) sum += fast_exp2((lrow[k] - mx) * kLog2e);
         sum = quad_sum(sum);
         const float ls = fast_log2(sum);
-        const float l2 = fmaf(mx, kLog2e, ls);
         bool unused = false;       // (what counts is which of the coded emissions get stored below)
         for (int k = q; k < A; k += kPerRow) lrow[k] = encode_emission(log2_softmax(lrow[k], mx, ls), unused, sa.plain_logs);
-        if (q == 0) lse[static_cast<size_t>(b) * Tt + t] = l2;
     }
-    if (!(m.flags & kUttRuns)) return;
     __syncthreads();
-    const int rows = min(kRows, m.Tb - t0);
-    bool small = false;
-    if (tid < rows) {
-        const float e = lp[tid * A + blank];
-        emit_blank[kBlankSlack + m.f_off + t0 + tid] = e;
-        sa.emit_blank64[kBlankSlack + m.f_off + t0 + tid] = static_cast<double>(emission_probability(e));
-        small = !sa.plain_logs && e < 0.0f;
-    }
-    // The emission block: a symbol's frames side by side, e_pitch floats per symbol (fetch_frames).
-    // A wavefront writes up to 64 frames of one symbol at a time.
-    float* out = emit_label + kLabelSlack + m.e_off + t0;
-    const int rr = tid & 63;
-    if (rr < rows)
-        for (int a = tid >> 6; a < A; a += kRowThreads / 64) {
-            const float e = lp[rr * A + a];
-            out[static_cast<size_t>(a) * m.e_pitch + rr] = e;
-            small = small || (!sa.plain_logs && e < 0.0f);
-        }
+    const bool small = store_symbol_chunks<kRows>(lp, m.Tb, m.f_off, m.e_off, t0, A, blank, emit_blank, sa.emit_blank64, emit_label,
+                                                  sa.plain_logs);
     if (small) s_small = 1;
     __syncthreads();
     if (tid == 0) row_flags[static_cast<size_t>(b) * row_blocks + blockIdx.x] = s_small;
@@ -1137,54 +995,43 @@ __device__ __forceinline__ bool rows_flagged(const int* __restrict__ row_flags, 
 }
 
 // ---- lattice storage -------------------------------------------------------------------------
-// What the recursions leave for the gradient, per label state, frame and direction: a number
-// m * 2^e, as
+// What the recursions leave for the gradient.
+//
+// Linear-domain chains store their whole state once per block of kBlockFrames frames (a checkpoint); the gradient runs
+// both recursions once more over the frames of a block, from the checkpoints at its two ends, and forms the shares from
+// the values in its registers.  Storing the label states of every frame instead (4.5 bytes per state, frame and
+// direction, written by the chains and read by the gradient) cost the chains a fifth of their time -- a store is three
+// to four issue slots of a lone wavefront and the wavefronts of a compute unit share its memory pipeline -- and bound
+// the gradient by the bytes it read; a checkpoint is 20 bytes per state and block, 1.25 per frame.
+//   alpha, after frame 16 k + 15:  per label position j  (blank j, label j) as doubles, and their frame (int32)
+//   beta, after frame 16 k:        per label position j  (blank j + 1, label j)
+// (inclusive quantities, see the recursions), position j in column 1 + j of row k.  Values in the first half of the
+// direction's region, frames in the second.
+//
+// Log-domain chains (rare) store every frame, per label state a number m * 2^e, as
 //   a value word (uint32): the high dword of the fp64 m (sign, exponent, top 20 mantissa bits),
-//                          one per state and frame, rows of lattice_pitch(L) words by frame;
-//   an exponent word (int32): e, one per state and exponent row.
-// A linear-domain chain stores its state in the lane's frame as it stands (no arithmetic on the
-// way out), and the frame changes only when a chunk ends: it writes one exponent row per chunk
-// (exponent_row), 4.5 bytes per state and frame in all.  A log-domain chain has a new exponent at
-// every step and writes one exponent row per step.  Both blocks of a direction are sized for the
-// latter (which chain runs is decided on the GPU, by the softmax launch): values in the first
-// half of the direction's region, exponents in the second.
-// Twenty mantissa bits bound the relative error of a state's share alpha * beta / p by 2^-19,
-// which is 2e-6 of a gradient entry at most.  Exponents stay above -2^30 so that the sum of two
-// cannot wrap.
+//   an exponent word (int32): e,
+// both in rows of lattice_pitch(L) words by frame, values and exponents in the two halves of the region.
+// Twenty mantissa bits bound the relative error of a state's share alpha * beta / p by 2^-19, which is 2e-6 of a gradient
+// entry at most.  Exponents stay above -2^30 so that the sum of two cannot wrap.
+//
 // The mass p of an utterance (its reciprocal) keeps both parts in one 8-byte word (pack_state).
+struct alignas(16) CheckpointState { double blank, label; };
+constexpr int kNoExponent = -(1 << 28);   // exponent of zero: below every real one, far from int32's ends
+
 __device__ __forceinline__ double pack_state(double in_frame, int frame)
 {
     return __hiloint2double(__double2hiint(in_frame), frame);
 }
-// Loads of what a chain has left for the gradient.  The gradient launch reads plainly.  A worker
-// of the lattice launch (gradient_worker) reads while other chains still run: its loads carry
-// device scope, so that the compute unit's own cache, which may hold a line from before the chain
-// wrote it, is passed by and the L2 answers, which chain and worker share (see gradient_worker).
-template <bool kCoherent, typename W>
-__device__ __forceinline__ W lattice_load(const W* p)
-{
-    if (kCoherent) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return *p;
-}
-template <typename W>
-__device__ __forceinline__ void lattice_store(W* p, W v) { *p = v; }
-
-// Exponent row of the state a chain reached at its step `step` (0 .. Tb-1; a forward chain's step
-// is the frame, a backward chain's Tb-1-frame).  Linear domain: the initial frame serves step 0 and
-// the first chunk (steps 1 .. kChunk), each later chunk has a row of its own.
-__device__ __forceinline__ int exponent_row(int step, bool log_domain)
-{
-    return log_domain ? step : (max(step - 1, 0) / kChunk);
-}
 // A base-2 logarithm (log-domain chains) as value and exponent: m = 2^fraction in [1, 2), e = floor.
-// log 0 (and anything as small) is stored as the number 0.
+// log 0 (and anything as small) is stored as the number 0 with the exponent of zero.
 __device__ __forceinline__ void split_log2(double w, uint32_t& value, int& exponent)
 {
     const double whole = floor(w);
     const double m = static_cast<double>(fast_exp2(static_cast<float>(w - whole)));
     const bool real = w > -1.0e9 && w < 1.0e9;
     value = real ? static_cast<uint32_t>(__double2hiint(m)) : 0u;
-    exponent = real ? static_cast<int>(whole) : 0;
+    exponent = real ? static_cast<int>(whole) : kNoExponent;
 }
 __device__ __forceinline__ double pack_log2(double w)          // the same as one word (1 / p)
 {
@@ -1192,23 +1039,6 @@ __device__ __forceinline__ double pack_log2(double w)          // the same as on
     int exponent;
     split_log2(w, value, exponent);
     return __hiloint2double(static_cast<int>(value), exponent);
-}
-// alpha * beta * (1 / p) from the stored parts.  (The missing low dword of a value is a relative
-// 2^-20 at most.)  Either of alpha and beta may lie a thousand binary orders below or above the unit
-// of its own frame (lane_frame) while their product is a share of order one, so the factors are
-// balanced before they are multiplied.
-__device__ __forceinline__ float mass_share(uint32_t a_value, int a_exponent, uint32_t b_value, int b_exponent,
-                                            float inverse_p_mantissa, int inverse_p_exponent)
-{
-    // alpha's word is brought to [1, 2) by its own exponent field, and everything else goes to beta: the
-    // product is a share, at most 1, so beta's factor stays in range wherever alpha is not 0; next to an
-    // alpha that is the number 0 it is capped, so that the product is 0 and not 0 times infinity.
-    const int to_one = 1023 - static_cast<int>(a_value >> 20);
-    const int rest = a_exponent + b_exponent + inverse_p_exponent - to_one;
-    const double a = __hiloint2double(static_cast<int>(a_value), 0);
-    const double b = __hiloint2double(static_cast<int>(b_value), 0);
-    return static_cast<float>(__builtin_amdgcn_ldexp(a, to_one) * fmin(__builtin_amdgcn_ldexp(b, rest), 0x1p200)) *
-           inverse_p_mantissa;
 }
 
 // ---- lattice recursions ------------------------------------------------------------------
@@ -1238,6 +1068,20 @@ __device__ __forceinline__ int window_max_step(int window, int mine)
     return window;
 }
 
+// The same, and the lane above in place of the lane below (the gradient's backward recursion); lane 63 has none.
+__device__ __forceinline__ int window_max_step_down(int window, int mine)
+{
+    asm("s_nop 1\n\tv_max_i32_dpp %0, %0, %1 wave_shl:1 row_mask:0xf bank_mask:0xf" : "+v"(window) : "v"(mine));
+    return window;
+}
+// Lane i receives the value of lane i+1 (DPP wave_shl:1); lane 63 keeps what `into` held.
+__device__ __forceinline__ double shift_down(double v, int& into_lo, int& into_hi)
+{
+    into_lo = __builtin_amdgcn_update_dpp(into_lo, __double2loint(v), 0x130, 0xf, 0xf, false);
+    into_hi = __builtin_amdgcn_update_dpp(into_hi, __double2hiint(v), 0x130, 0xf, 0xf, false);
+    return __hiloint2double(into_hi, into_lo);
+}
+
 constexpr int kHaloEntries = 64;      // 16-byte entries of one wavefront boundary's exchange buffer (2 x 32)
 
 enum class Sync { kNone, kHalo, kBarrier };
@@ -1246,24 +1090,17 @@ enum class Sync { kNone, kHalo, kBarrier };
 // number of states the walk moves down.  Bits 2..3, the label state: 0 = stayed, 1 = came from
 // the pair's blank, 2 = came from the label of the pair before (skipping the blank).  Bit 0, the
 // blank state: 0 = stayed, 1 = came from the label of the pair before.
-// The next kChunk frames of one symbol out of a transposed emission block (symbol-major: a
-// symbol's frames lie side by side), in the order the chain takes them, in two 16-byte loads
-// instead of kChunk loads a row apart.  `p` points at the frame of the step before the first one
-// wanted and moves on by `advance` floats (kChunk in the chain's direction; 0 for a lane
-// without a label state, which keeps reading its constants).
-struct __attribute__((packed, aligned(4))) Float4 { float v[4]; };
-static_assert(kChunk == 8, "fetch_frames loads two Float4");
+// A chunk's emissions of one lane out of the emission block, in the order the chain takes them, in two 16-byte loads.
+// `p` moves on by `step` floats (0 for a lane without a label state, which keeps reading its constants).
+static_assert(kChunk == 8, "fetch_chunk loads two float4");
 template <bool kBackward>
-__device__ __forceinline__ void fetch_frames(const float*& p, int advance, float (&el)[kChunk])
+__device__ __forceinline__ void fetch_chunk(const float*& p, int64_t step, float (&el)[kChunk])
 {
-    const Float4 lo = *reinterpret_cast<const Float4*>(p + fetch_window_first(kBackward));
-    const Float4 hi = *reinterpret_cast<const Float4*>(p + fetch_window_first(kBackward) + 4);
+    const float4 lo = *reinterpret_cast<const float4*>(p), hi = *reinterpret_cast<const float4*>(p + 4);
+    const float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        el[i] = kBackward ? hi.v[3 - i] : lo.v[i];
-        el[4 + i] = kBackward ? lo.v[3 - i] : hi.v[i];
-    }
-    p += advance;
+    for (int i = 0; i < kChunk; ++i) el[i] = v[kBackward ? kChunk - 1 - i : i];
+    p += step;
 }
 constexpr int kFromSame = 0, kFromBlank = 1 << 2, kFromPrevLabel = 2 << 2, kBlankFromPrevLabel = 1;
 
@@ -1314,10 +1151,12 @@ __device__ __forceinline__ Wave* halo_wave(void* lds, int wave)
 // excludes its own frame's emission, and that is what gets stored, so that
 // log alpha + log beta is the log mass of alignments through a state.
 //
-// Storage: only the label states are written, alpha_row[1 + i] = alpha(2i+1), beta_row[1 + i] =
-// beta(2i+1), row pitch L+2 words (lattice_pitch; the first and the last column stay unused).  The blank states are needed by the recursion but not by
-// the gradient, which takes the blank's occupancy as 1 minus that of all label states
+// The gradient needs the label states' shares only and takes the blank's occupancy as 1 minus that of all label states
 // (sum_s alpha_t(s) beta_t(s) = p at every frame).
+//
+// A chain starts from the state "all mass in its first blank, before any frame" and takes whole chunks of the
+// utterance's padded frames; virtual frames (emission_layout) leave the start state as it is, and a forward chain's
+// virtual frames after the last real one only gather p in the last blank.
 //
 // A lone wavefront on its SIMD issues an instruction about every five clocks whatever its kind
 // (a vector memory instruction counts for three), so the step is written for instruction count:
@@ -1337,7 +1176,7 @@ __device__ __forceinline__ Wave* halo_wave(void* lds, int wave)
 // read).  No barrier; the wavefronts run skewed.  A wavefront waits for data only on lower
 // ones and for space only on higher ones, wavefront 0 needs no data and the last one no space,
 // so every wait ends; a poll budget bounds them regardless and raises chain_err when spent.
-template <bool kBackward, Sync kSync, Mode kMode, bool kSymbolMajor>
+template <bool kBackward, Sync kSync, Mode kMode>
 __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const int* __restrict__ labels,
                                           const float* __restrict__ emit_blank,
                                           const float* __restrict__ emit_label,
@@ -1349,7 +1188,7 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
     static_assert(kMode == Mode::kGrad || !kBackward, "only the gradient needs the backward chain");
     // Launches for the most probable alignment store plain logarithms, the others coded emissions.
     constexpr bool kCoded = kMode != Mode::kBest;
-    const int L = m.L, Tb = m.Tb, P = L + 1;
+    const int L = m.L, P = L + 1, chunks = 2 * frame_blocks(m.Tb);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (uniform: in a scalar register)
     const int halo = (kSync == Sync::kHalo) ? m.halo : 0;
     const int j = wave * (64 - halo) + lane;
@@ -1361,43 +1200,34 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
     const bool skip_ok = has_label && j >= 1 && lab[li] != lab[kBackward ? (li + 1) : (li - 1)];
     const double skip_penalty = skip_ok ? 0.0 : kNeg;
 
-    // Frame of step s: s going forward, Tb-1-s going backward.
-    const int f0 = kBackward ? (Tb - 1) : 0;
-    const int fdir = kBackward ? -1 : 1;
-    // Label emissions: a per-lane pointer that moves one row per step.  A lane without a label
+    // Label emissions: a per-lane pointer that moves one chunk at a time.  A lane without a label
     // state reads a constant log 0 and stays there.
-    // (In a symbol-major block the pointer moves one float per step: emission_layout.  The layout
-    // is the launch's, a template parameter: a test at run time would join two paths with
-    // different numbers of loads under way, and the waits after the join would be the
-    // cautious ones.)
-    constexpr bool direct = kSymbolMajor;
-    const float* ep = emit_label + label_emission_offset(m, has_label, direct, has_label ? lab[li] : 0, li, f0, kLogZeroEmission);
-    const int64_t estride = label_emission_step(m, has_label, false, fdir);
-    const int eadvance = static_cast<int>(label_emission_step(m, has_label, true, fdir)) * kChunk;
-    // Blank emissions: lane i of a chunk's load takes the frame of step (chunk start + i % kChunk).
-    const float* bp = emit_blank + blank_emission_offset(m, f0, fdir, lane);
-    // Output: only the label state of each pair is kept (row pitch L+2 words, column = 1 + label
-    // index, in both directions; value rows by frame, exponent rows by step: one per step in the
-    // log domain); the gradient gets the blank's share as the complement.
+    const float* ep = emit_label + label_emission_offset(m, has_label, has_label ? lab[li] : 0, li,
+                                                         chain_chunk(0, chunks, kBackward), kLogZeroEmission);
+    const int64_t estep = label_emission_step(m, has_label, kBackward);
+    // Blank emissions: lane i of a chunk's load takes the frame of the chunk's step i % kChunk.
+    const float* const bp = emit_blank + (kBackward ? kChunk - 1 - (lane & (kChunk - 1)) : (lane & (kChunk - 1)));
+    // Output: only the label state of each pair is kept (rows by frame, column = 1 + label index, in both directions).
     // Lanes that store nothing write to a sink instead.
     // With Mode::kBest the value block holds one byte per pair and frame instead (row pitch
     // L+1 bytes, column = pair), pair L included: its blank state has a choice to record.
     constexpr int64_t kOutBytes = (kMode == Mode::kBest) ? 1 : 4;
     const int64_t out_pitch = (kMode == Mode::kBest) ? P : lattice_pitch(L);
     const bool stores = (kMode == Mode::kBest) ? active : (active && has_label);
+    const int64_t first_row = kBackward ? static_cast<int64_t>(chunks) * kChunk - 1 : 0;
     char* op = stores ? reinterpret_cast<char*>(out) +
-                            (m.ab_off + static_cast<int64_t>(f0) * out_pitch + (kMode == Mode::kBest ? j : li + 1)) * kOutBytes
+                            (m.ab_off + first_row * out_pitch + (kMode == Mode::kBest ? j : li + 1)) * kOutBytes
                       : reinterpret_cast<char*>(sink);
-    const int64_t ostride = stores ? static_cast<int64_t>(fdir) * out_pitch * kOutBytes : 0;
-    int* xp = (stores && kMode == Mode::kGrad) ? out_exponents + m.ab_off + li + 1 : reinterpret_cast<int*>(sink);
-    const int64_t xstride = (stores && kMode == Mode::kGrad) ? out_pitch : 0;
+    const int64_t ostride = stores ? (kBackward ? -1 : 1) * out_pitch * kOutBytes : 0;
+    int* xp = (stores && kMode == Mode::kGrad) ? out_exponents + m.ab_off + first_row * out_pitch + li + 1 : reinterpret_cast<int*>(sink);
+    const int64_t xstride = (stores && kMode == Mode::kGrad) ? (kBackward ? -1 : 1) * out_pitch : 0;
     int choice = 0;
     auto store_state = [&](double w) {
         uint32_t value;
         int exponent;
         split_log2(w, value, exponent);
-        lattice_store(reinterpret_cast<uint32_t*>(op), value);
-        lattice_store(xp, exponent);
+        *reinterpret_cast<uint32_t*>(op) = value;
+        *xp = exponent;
         xp += xstride;
     };
 
@@ -1425,9 +1255,8 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
     int* const up_done = &above_lds->done;
     int* const low_ready = &below_lds->ready;
 
-    double i_blank = (j == 0) ? 0.0 : kNeg;
-    double i_label = (j == 0 && has_label) ? 0.0 : kNeg;
-    double v_blank, v_label;
+    double i_blank, i_label;
+    double v_blank = (j == 0) ? 0.0 : kNeg, v_label = kNeg;
 
     auto counter = [&](int* p) {
         return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -1507,8 +1336,7 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
         }
         op += ostride;
     };
-    // After the last step of a chunk (the last chunk of a chain may be short: its hand-over
-    // then comes early, which every wavefront of the chain does alike).
+    // After the last step of a chunk.
     auto end_chunk = [&]() {
         if (kSync == Sync::kHalo) {
             if (--until_hand_over == 0) {
@@ -1518,7 +1346,7 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
         }
     };
     auto advance = [&](int step, double eb, float el) {
-        const double prev = from_prev_pair(v_label, step - 1);
+        const double prev = from_prev_pair(v_label, step);
         if (kMode == Mode::kBest) {
             const double via_skip = prev + skip_penalty;
             const bool blank_moves = prev > v_blank;
@@ -1543,60 +1371,32 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
         return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), l));
     };
 
-    // step 0: every lane starts from the exact state of its pair, halo lanes included
-    {
-        const Log2Parts ebv = kCoded ? emission_log2_parts(*bp) : Log2Parts{*bp, 0.0f};
-        v_blank = i_blank + static_cast<double>(readlane(ebv.whole, 0)) + static_cast<double>(readlane(ebv.part, 0));
-        v_label = i_label + (kCoded ? emission_log2(*ep) : static_cast<double>(*ep));
-        // (the predecessor choices of frame 0 are never looked at: nothing is written for it)
-        if (kMode == Mode::kGrad) store_state(kBackward ? i_label : v_label);
-        op += ostride;
-    }
-
-    // Emissions of steps 1..: two register sets, one in use, one being filled.
-    float el_a[kChunk], el_b[kChunk], eb_a, eb_b;
-    auto fetch = [&](float (&el)[kChunk], float& eb, int s0) {
-        eb = bp[fdir * s0];
-        if (direct) {
-            fetch_frames<kBackward>(ep, eadvance, el);
-            return;
-        }
-#pragma unroll
-        for (int i = 0; i < kChunk; ++i) {
-            ep += estride;
-            el[i] = *ep;
-        }
+    // (every lane starts from the exact state of its pair, halo lanes included)
+    float el[4][kChunk], eb[2];
+    auto fetch = [&](auto set, int i) {
+        constexpr int k = decltype(set)::value;
+        if (i > 0) eb[(k + 1) & 1] = bp[blank_emission_offset(m, chain_chunk(i - 1, chunks, kBackward))];
+        fetch_chunk<kBackward>(ep, estep, el[k]);
+        __builtin_amdgcn_sched_barrier(0);
     };
-    // One copy of the step per chunk position and register set: the kernel has to stay well
-    // inside the instruction cache that two compute units share.
-    // Whole chunks run without looking at the step number; only the last, short chunk of a
-    // chain checks every step against the end.
-    auto run = [&](const float (&el)[kChunk], const float eb_coded, int s0, bool whole) {
-        const Log2Parts eb = kCoded ? emission_log2_parts(eb_coded) : Log2Parts{eb_coded, 0.0f};
-        auto blank_of_step = [&](int i) {
-            const double whole_part = static_cast<double>(readlane(eb.whole, i));
-            return kCoded ? whole_part + static_cast<double>(readlane(eb.part, i)) : whole_part;
-        };
-        if (whole) {
+    auto run = [&](auto set, int i) {
+        constexpr int k = decltype(set)::value;
+        const Log2Parts blank = kCoded ? emission_log2_parts(eb[k & 1]) : Log2Parts{eb[k & 1], 0.0f};
 #pragma unroll
-            for (int i = 0; i < kChunk; ++i) advance(s0 + i, blank_of_step(i), el[i]);
-        } else {
-#pragma unroll
-            for (int i = 0; i < kChunk; ++i)
-                if (s0 + i < Tb) advance(s0 + i, blank_of_step(i), el[i]);
+        for (int q = 0; q < kChunk; ++q) {
+            const double whole_part = static_cast<double>(readlane(blank.whole, q));
+            advance(i * kChunk + q, kCoded ? whole_part + static_cast<double>(readlane(blank.part, q)) : whole_part, el[k][q]);
         }
+        end_chunk();
     };
-    chain_schedule(Tb, [&](int s0) { fetch(el_a, eb_a, s0); __builtin_amdgcn_sched_barrier(0); },
-                   [&](int s0) { fetch(el_b, eb_b, s0); __builtin_amdgcn_sched_barrier(0); },
-                   [&](int s0, bool whole) { run(el_a, eb_a, s0, whole); }, [&](int s0, bool whole) { run(el_b, eb_b, s0, whole); },
-                   end_chunk);
+    chain_schedule(chunks, fetch, run);
 
     if (!kBackward) {
         // p = alpha_{T-1}(2L) + alpha_{T-1}(2L-1): the blank of pair L and the label of pair L-1.
         // Pair L sits in an exact lane, and so does the lane below it or, if that is the last
         // halo lane, it is still exact: the error from lane 0 needs `halo` steps to get there,
         // and a hand-over that fell due after the last step has been done by end_chunk.
-        const double prev = from_prev_pair(v_label, Tb - 1);
+        const double prev = from_prev_pair(v_label, chunks * kChunk);
         if (active && j == L) {
             if (kMode == Mode::kBest) {
                 // the better of the two end states; logp carries which one to the backtrace
@@ -1606,7 +1406,7 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
                 costs[u] = (lp < -1.0e29) ? __builtin_inff() : static_cast<float>(-lp * kLn2);
             } else {
                 const double lp = lse2(v_blank, prev);
-                lattice_store(&logp[u], pack_log2(-lp));          // 1 / p
+                logp[u] = pack_log2(-lp);                         // 1 / p
                 const float cost = (lp < -1.0e29) ? __builtin_inff() : static_cast<float>(-lp * kLn2);
                 if (kSync == Sync::kHalo && kMode == Mode::kLoss) hl->cost = cost;
                 else costs[u] = cost;
@@ -1630,7 +1430,7 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
             costs[u] = lost ? __uint_as_float(0x7FC00000u) : cost;
         }
     } else if (kSync == Sync::kHalo && lost && lane == 0) {
-        lattice_store(&chain_err[u], 1);
+        chain_err[u] = 1;
     }
 }
 
@@ -1648,9 +1448,7 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
 // away.  The value shifted in from the pair below is brought into this lane's frame by `scale`
 // = 2^(frame below - frame here), constant between renewals and folded into the multiply-adds.
 //
-// Storage (Mode::kGrad): the label state's value word at every step, its frame once per chunk
-// (see "lattice storage").
-constexpr int kNoExponent = -(1 << 28);   // exponent of zero: below every real one, far from int32's ends
+// Storage (Mode::kGrad): the whole state after every second chunk (see "lattice storage").
 // A lane's new frame is the largest exponent of its window (its own pairs and those that can reach it
 // before the next renewal), so that nothing arriving overflows -- but no more than kFrameSlack above
 // its own largest value where the window's top lies further up than that, down to kFrameDrop below the
@@ -1690,9 +1488,8 @@ __device__ __forceinline__ bool outside_easy_range(double top)
     return hi - (static_cast<unsigned>(1023 + kEasyLow) << 20) >= (static_cast<unsigned>(kEasyHigh - kEasyLow + 1) << 20);
 }
 
-template <bool kBackward, Sync kSync, Mode kMode, bool kSymbolMajor>
+template <bool kBackward, Sync kSync, Mode kMode>
 __device__ __forceinline__ void run_chain_linear(const Utt m, const int u, const int* __restrict__ labels,
-                                                 const float* __restrict__ emit_blank,
                                                  const double* __restrict__ emit_blank64,
                                                  const float* __restrict__ emit_label,
                                                  uint32_t* __restrict__ out, int* __restrict__ out_exponents,
@@ -1703,7 +1500,7 @@ __device__ __forceinline__ void run_chain_linear(const Utt m, const int u, const
     static_assert(kMode == Mode::kGrad || !kBackward, "only the gradient needs the backward chain");
     static_assert(kSync != Sync::kBarrier, "the barrier kernel runs the log-domain chain");
     static_assert(kMode != Mode::kBest, "the maximum recursion runs in the log domain");
-    const int L = m.L, Tb = m.Tb;
+    const int L = m.L, chunks = 2 * frame_blocks(m.Tb);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (uniform: in a scalar register)
     const int halo = (kSync == Sync::kHalo) ? m.halo : 0;
     const int j = wave * (64 - halo) + lane;             // pair of this lane (see run_chain_log)
@@ -1713,25 +1510,17 @@ __device__ __forceinline__ void run_chain_linear(const Utt m, const int u, const
     const int li = kBackward ? (L - 1 - j) : j;
     const bool skip_ok = has_label && j >= 1 && lab[li] != lab[kBackward ? (li + 1) : (li - 1)];
 
-    const int f0 = kBackward ? (Tb - 1) : 0;
-    const int fdir = kBackward ? -1 : 1;
     // A lane without a label state reads a constant probability 0 and stays there.
-    constexpr bool direct = kSymbolMajor;                // see run_chain_log
-    const float* ep = emit_label + label_emission_offset(m, has_label, direct, has_label ? lab[li] : 0, li, f0, kZeroEmission);
-    const int64_t estride = label_emission_step(m, has_label, false, fdir);
-    const int eadvance = static_cast<int>(label_emission_step(m, has_label, true, fdir)) * kChunk;
-    // The blank's probability is the same for all lanes: an fp64 scalar, a chunk's frames in one load.
-    (void)emit_blank;
-    const double* const bq = emit_blank64;
-    auto blank_window = [&](int s0) { return bq + blank64_window(m, f0, fdir, s0); };
-    auto blank_of = [&](const double* w, int i) { return w[kBackward ? kChunk - 1 - i : i]; };
-    // Values by frame, exponents by chunk (exponent_row): the lane's frame is what it is until the
-    // chunk ends.
+    const float* ep = emit_label + label_emission_offset(m, has_label, has_label ? lab[li] : 0, li,
+                                                         chain_chunk(0, chunks, kBackward), kZeroEmission);
+    const int64_t estep = label_emission_step(m, has_label, kBackward);
+    // Checkpoints: row k after block k of the utterance.
     const bool stores = kMode == Mode::kGrad && active && has_label;
-    uint32_t* op = stores ? out + m.ab_off + static_cast<int64_t>(f0) * lattice_pitch(L) + li + 1 : sink;
-    const int64_t ostride = stores ? static_cast<int64_t>(fdir) * lattice_pitch(L) : 0;
-    int* xp = stores ? out_exponents + m.ab_off + li + 1 : reinterpret_cast<int*>(sink);
-    const int64_t xstride = stores ? lattice_pitch(L) : 0;
+    const int64_t pitch = lattice_pitch(L), first_row = kBackward ? frame_blocks(m.Tb) - 1 : 0;
+    CheckpointState* vp = stores ? reinterpret_cast<CheckpointState*>(out + m.ab_off) + first_row * pitch + li + 1
+                                 : reinterpret_cast<CheckpointState*>(sink);
+    int* fp = stores ? out_exponents + m.ab_off + first_row * pitch + li + 1 : reinterpret_cast<int*>(sink);
+    const int64_t row_step = stores ? (kBackward ? -pitch : pitch) : 0;
 
     HaloHeader* const hl = static_cast<HaloHeader*>(lds);
     const int last_wave = m.waves - 1;
@@ -1755,9 +1544,7 @@ __device__ __forceinline__ void run_chain_linear(const Utt m, const int u, const
     int* const up_done = &above_lds->done;
     int* const low_ready = &below_lds->ready;
 
-    double i_blank = (j == 0) ? 1.0 : 0.0;
-    double i_label = (j == 0 && has_label) ? 1.0 : 0.0;
-    double v_blank, v_label;
+    double v_blank = (j == 0) ? 1.0 : 0.0, v_label = 0.0;
     int frame = 0;
     double scale = 1.0;                                  // 2^(frame of the pair below - frame)
     double skip_scale = skip_ok ? 1.0 : 0.0;             // the same where the label may be entered from that pair's label
@@ -1860,9 +1647,12 @@ __device__ __forceinline__ void run_chain_linear(const Utt m, const int u, const
         // (Only chains of one wavefront put renewals off: the wavefronts of a longer chain keep in step
         // best when all of them do the same work per chunk; measured 5 % slower otherwise.)
         if (kSync != Sync::kNone || handed || renewal_due()) renew_frames();
-        // the next chunk's exponent row
-        xp += xstride;
-        if (kMode == Mode::kGrad) lattice_store(xp, frame);
+    };
+    auto checkpoint = [&]() {
+        *vp = CheckpointState{v_blank, v_label};
+        *fp = frame;
+        vp += row_step;
+        fp += row_step;
     };
     // One step.  The blank state sums its own value and the label of the pair before; the label state
     // its own value, the old blank and, where the skip is allowed, that label too:
@@ -1871,7 +1661,7 @@ __device__ __forceinline__ void run_chain_linear(const Utt m, const int u, const
     // the instruction before it only after 4 ns, and of the one before that after 3 (measured on gfx950
     // with chains of dependent v_fma_f64).  So the statements are in the order of issue (pin keeps the
     // compiler from moving them), and none needs a result younger than two instructions: the sum and
-    // the conversions fill the time the two DPP moves take, the address the time of the multiply-adds.
+    // the conversion fill the time the two DPP moves take.
     auto pin = []() { __builtin_amdgcn_sched_barrier(0); };
     auto advance = [&](double eb_d, float el) {
 #pragma clang fp contract(off)                           // (a product stays a product: fused into the next step's sum it would tie the steps together)
@@ -1881,74 +1671,39 @@ __device__ __forceinline__ void run_chain_linear(const Utt m, const int u, const
         pin();
         const double el_d = static_cast<double>(el);
         pin();
-        i_label = __builtin_fma(prev, skip_scale, u);
+        const double i_label = __builtin_fma(prev, skip_scale, u);
         pin();
-        i_blank = __builtin_fma(prev, scale, v_blank);
-        pin();
-        uint32_t* const here = op;
-        op += ostride;
+        const double i_blank = __builtin_fma(prev, scale, v_blank);
         pin();
         v_label = i_label * el_d;
         pin();
         v_blank = i_blank * eb_d;
         pin();
-        if (kMode == Mode::kGrad) lattice_store(here, static_cast<uint32_t>(__double2hiint(kBackward ? i_label : v_label)));
-        pin();
     };
 
-    // step 0
-    {
-        const float el = *ep;
-        v_blank = i_blank * blank_of(blank_window(0), 0);
-        v_label = i_label * static_cast<double>(el);
-        if (kMode == Mode::kGrad) {
-            lattice_store(op, static_cast<uint32_t>(__double2hiint(kBackward ? i_label : v_label)));
-            lattice_store(xp, frame);                    // exponent row 0: step 0 and the first chunk
-        }
-        op += ostride;
-    }
-
-    // Emissions of steps 1..: two register sets, one in use, one being filled (as run_chain_log).
-    // Three register sets: a chunk's emissions are requested two chunks before their use (with two sets,
-    // one chunk ahead, a seventh of a single-wavefront chain's time went into waiting for them).
-    float el_a[kChunk], el_b[kChunk], el_c[kChunk];
-    double eb_a[kChunk] = {}, eb_b[kChunk] = {}, eb_c[kChunk] = {};
     // (Scalar loads return in any order, so a wavefront can only wait for all of them: the set in use is
     // waited for before the other set's load goes out, while that wait is still free.)
-    // The label emissions of the chunk at s0 go into `el`, two chunks ahead of their use; the blank's
-    // scalars into `eb`, the set of the chunk that runs next, for the chunk before s0, so that only two of
-    // the three scalar sets are in use at any time (48 scalar registers for them were more than the kernel
-    // has: the compiler parked a set in vector lanes and fetched it back, 32 moves per round).
-    auto fetch = [&](float (&el)[kChunk], double (&eb)[kChunk], const double (&in_use)[kChunk], int s0) {
-        asm volatile("" : : "s"(in_use[0]), "s"(in_use[kChunk - 1]));
-        const double* const w = blank_window(blank64_chunk_with(s0));
+    float el[4][kChunk];
+    double eb[2][kChunk] = {};
+    auto fetch = [&](auto set, int i) {
+        constexpr int k = decltype(set)::value;
+        if (i > 0) {
+            asm volatile("" : : "s"(eb[k & 1][0]), "s"(eb[k & 1][kChunk - 1]));
+            const double* const w = emit_blank64 + blank_emission_offset(m, chain_chunk(i - 1, chunks, kBackward));
 #pragma unroll
-        for (int i = 0; i < kChunk; ++i) eb[i] = blank_of(w, i);
-        if (direct) {
-            fetch_frames<kBackward>(ep, eadvance, el);
-            return;
+            for (int q = 0; q < kChunk; ++q) eb[(k + 1) & 1][q] = w[kBackward ? kChunk - 1 - q : q];
         }
-#pragma unroll
-        for (int i = 0; i < kChunk; ++i) {
-            ep += estride;
-            el[i] = *ep;
-        }
+        fetch_chunk<kBackward>(ep, estep, el[k]);
+        __builtin_amdgcn_sched_barrier(0);
     };
-    auto run = [&](const float (&el)[kChunk], const double (&eb)[kChunk], int s0, bool whole) {
-        if (whole) {
+    auto run = [&](auto set, int) {
+        constexpr int k = decltype(set)::value;
 #pragma unroll
-            for (int i = 0; i < kChunk; ++i) advance(eb[i], el[i]);
-        } else {
-#pragma unroll
-            for (int i = 0; i < kChunk; ++i)
-                if (s0 + i < Tb) advance(eb[i], el[i]);
-        }
+        for (int q = 0; q < kChunk; ++q) advance(eb[k & 1][q], el[k][q]);
+        end_chunk();
+        if (kMode == Mode::kGrad && (k & 1)) checkpoint();
     };
-    chain_schedule3(Tb, [&](int s0) { fetch(el_a, eb_c, eb_b, s0); __builtin_amdgcn_sched_barrier(0); },
-                    [&](int s0) { fetch(el_b, eb_a, eb_c, s0); __builtin_amdgcn_sched_barrier(0); },
-                    [&](int s0) { fetch(el_c, eb_b, eb_a, s0); __builtin_amdgcn_sched_barrier(0); },
-                    [&](int s0, bool whole) { run(el_a, eb_a, s0, whole); }, [&](int s0, bool whole) { run(el_b, eb_b, s0, whole); },
-                    [&](int s0, bool whole) { run(el_c, eb_c, s0, whole); }, end_chunk);
+    chain_schedule(chunks, fetch, run);
 
     if (!kBackward) {
         // p = alpha_{T-1}(2L) + alpha_{T-1}(2L-1), from the lane of pair L (exact, as is the
@@ -1961,7 +1716,7 @@ __device__ __forceinline__ void run_chain_linear(const Utt m, const int u, const
             const int exponent = frame + __builtin_amdgcn_frexp_exp(p);
             // (in double: once per chain, and a cost near zero, p near 1, would keep few of a float logarithm's bits)
             const double l2 = static_cast<double>(exponent) + ::log2(mantissa);
-            lattice_store(&logp[u], (p > 0.0) ? pack_state(1.0 / mantissa, -exponent) : 0.0);     // 1 / p
+            logp[u] = (p > 0.0) ? pack_state(1.0 / mantissa, -exponent) : 0.0;     // 1 / p
             const float cost = (p > 0.0) ? static_cast<float>(-l2 * kLn2) : __builtin_inff();
             if (kSync == Sync::kHalo && kMode == Mode::kLoss) hl->cost = cost;
             else costs[u] = cost;
@@ -1982,7 +1737,7 @@ __device__ __forceinline__ void run_chain_linear(const Utt m, const int u, const
             costs[u] = any_lost ? __uint_as_float(0x7FC00000u) : cost;
         }
     } else if (kSync == Sync::kHalo && lost && lane == 0) {
-        lattice_store(&chain_err[u], 1);
+        chain_err[u] = 1;
     }
 }
 
@@ -1994,15 +1749,11 @@ __device__ __forceinline__ void run_chain_linear(const Utt m, const int u, const
 // gaps.  Both pairs share the lane's frame; mass moves up half a lane per step, so the window
 // of a renewal is this lane and the kChunk / 2 lanes below it, and a halo of h lanes stays exact
 // for 2h steps (hand-over every 2h steps: h is a multiple of 4).
-// The two label states of a lane are neighbours in the lattice row and go out in one 16-byte
-// store; where pair B has no label state (the lane of the last pair) its half falls on one of
-// the row's two unused columns.
-struct alignas(4) LabelStatePair { uint32_t lo, hi; };   // two neighbouring columns of a lattice row
-struct alignas(4) ExponentPair { int lo, hi; };
+// The two pairs of a lane are neighbours in the checkpoint's row; where pair B has no label state (the lane of the last
+// pair) its part falls on one of the row's two unused columns.
 
-template <bool kBackward, Mode kMode, bool kSymbolMajor>
+template <bool kBackward, Mode kMode>
 __device__ __forceinline__ void run_chain_linear2(const Utt m, const int u, const int* __restrict__ labels,
-                                                  const float* __restrict__ emit_blank,
                                                   const double* __restrict__ emit_blank64,
                                                   const float* __restrict__ emit_label,
                                                   uint32_t* __restrict__ out, int* __restrict__ out_exponents,
@@ -2012,7 +1763,7 @@ __device__ __forceinline__ void run_chain_linear2(const Utt m, const int u, cons
 {
     static_assert(kMode == Mode::kGrad || !kBackward, "only the gradient needs the backward chain");
     static_assert(kMode != Mode::kBest, "the maximum recursion runs in the log domain");
-    const int L = m.L, Tb = m.Tb;
+    const int L = m.L, chunks = 2 * frame_blocks(m.Tb);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (uniform: in a scalar register)
     const int halo = m.halo2, waves = m.waves2;
     const int q = wave * (64 - halo) + lane;
@@ -2026,29 +1777,20 @@ __device__ __forceinline__ void run_chain_linear2(const Utt m, const int u, cons
     const bool skip_a = has_a && ja >= 1 && lab[lia] != lab[lia + back];
     const bool skip_b = has_b && lab[lib] != lab[lib + back];
 
-    const int f0 = kBackward ? (Tb - 1) : 0;
-    const int fdir = kBackward ? -1 : 1;
-    constexpr bool direct = kSymbolMajor;                // see run_chain_log
     // A pair without a label state reads a constant probability 0 and stays there.
-    const float* epa = emit_label + label_emission_offset(m, has_a, direct, has_a ? lab[lia] : 0, lia, f0, kZeroEmission);
-    const float* epb = emit_label + label_emission_offset(m, has_b, direct, has_b ? lab[lib] : 0, lib, f0, kZeroEmission);
-    const int advance_a = static_cast<int>(label_emission_step(m, has_a, true, fdir)) * kChunk;
-    const int advance_b = static_cast<int>(label_emission_step(m, has_b, true, fdir)) * kChunk;
-    const int64_t stride_a = label_emission_step(m, has_a, false, fdir);
-    const int64_t stride_b = label_emission_step(m, has_b, false, fdir);
-    (void)emit_blank;                                    // the blank's probability: fp64 scalars (see run_chain_linear)
-    const double* const bq = emit_blank64;
-    auto blank_window = [&](int s0) { return bq + blank64_window(m, f0, fdir, s0); };
-    auto blank_of = [&](const double* w, int i) { return w[kBackward ? kChunk - 1 - i : i]; };
-    // Output: label state i sits in column 1 + i; the lane's two are columns 1 + min(lia, lib) and
-    // the next one.  (has_a false: nothing of this lane is kept.)
+    const int first_chunk = chain_chunk(0, chunks, kBackward);
+    const float* epa = emit_label + label_emission_offset(m, has_a, has_a ? lab[lia] : 0, lia, first_chunk, kZeroEmission);
+    const float* epb = emit_label + label_emission_offset(m, has_b, has_b ? lab[lib] : 0, lib, first_chunk, kZeroEmission);
+    const int64_t step_a = label_emission_step(m, has_a, kBackward), step_b = label_emission_step(m, has_b, kBackward);
+    // Checkpoints: position i in column 1 + i, this lane's two are columns 1 + min(lia, lib) and the next one.  (has_a
+    // false: nothing of this lane is kept.)
     const bool stores = kMode == Mode::kGrad && active && has_a;
-    const int pitch = static_cast<int>(lattice_pitch(L));
+    const int64_t pitch = lattice_pitch(L), first_row = kBackward ? frame_blocks(m.Tb) - 1 : 0;
     const int first_column = 1 + (kBackward ? lib : lia);
-    uint32_t* op = stores ? out + m.ab_off + static_cast<int64_t>(f0) * pitch + first_column : sink;
-    const int64_t ostride = stores ? static_cast<int64_t>(fdir) * pitch : 0;
-    int* xp = stores ? out_exponents + m.ab_off + first_column : reinterpret_cast<int*>(sink);
-    const int64_t xstride = stores ? pitch : 0;
+    CheckpointState* vp = stores ? reinterpret_cast<CheckpointState*>(out + m.ab_off) + first_row * pitch + first_column
+                                 : reinterpret_cast<CheckpointState*>(sink);
+    int* fp = stores ? out_exponents + m.ab_off + first_row * pitch + first_column : reinterpret_cast<int*>(sink);
+    const int64_t row_step = stores ? (kBackward ? -pitch : pitch) : 0;
 
     HaloHeader* const hl = static_cast<HaloHeader*>(lds);
     const int last_wave = waves - 1;
@@ -2063,9 +1805,7 @@ __device__ __forceinline__ void run_chain_linear2(const Utt m, const int u, cons
     Halo2Wave* const below_lds = halo_wave<Halo2Wave>(lds, wave > 0 ? wave - 1 : 0);
     Halo2Wave* const above_lds = halo_wave<Halo2Wave>(lds, wave < last_wave ? wave + 1 : wave);
 
-    double ia_blank = (ja == 0) ? 1.0 : 0.0, ia_label = (ja == 0 && has_a) ? 1.0 : 0.0;
-    double ib_blank = 0.0, ib_label = 0.0;
-    double va_blank, va_label, vb_blank, vb_label;
+    double va_blank = (ja == 0) ? 1.0 : 0.0, va_label = 0.0, vb_blank = 0.0, vb_label = 0.0;
     int frame = 0;
     double scale = 1.0;                                  // 2^(frame of the lane below - frame)
     double skip_a_scale = skip_a ? 1.0 : 0.0;
@@ -2170,28 +1910,14 @@ __device__ __forceinline__ void run_chain_linear2(const Utt m, const int u, cons
         skip_a_scale = skip_a ? scale : 0.0;
     };
 
-    auto store = [&](double label_a, double label_b) {
-        if (kMode == Mode::kGrad) {
-            const uint32_t a = static_cast<uint32_t>(__double2hiint(label_a));
-            const uint32_t b = static_cast<uint32_t>(__double2hiint(label_b));
-            // (one 8-byte word: b's value in the upper half when a's column comes first)
-            lattice_store(reinterpret_cast<unsigned long long*>(op),
-                          kBackward ? (static_cast<unsigned long long>(a) << 32) | b : (static_cast<unsigned long long>(b) << 32) | a);
-        }
-        op += ostride;
-    };
-    // both label states of the lane share its frame
-    auto store_frame = [&]() {
-        if (kMode == Mode::kGrad)
-            lattice_store(reinterpret_cast<unsigned long long*>(xp),
-                          (static_cast<unsigned long long>(static_cast<unsigned>(frame)) << 32) | static_cast<unsigned>(frame));
-    };
-    auto first_step = [&](double ebd, float ela, float elb) {
-        va_blank = ia_blank * ebd;
-        va_label = ia_label * static_cast<double>(ela);
-        vb_blank = ib_blank * ebd;
-        vb_label = ib_label * static_cast<double>(elb);
-        store(kBackward ? ia_label : va_label, kBackward ? ib_label : vb_label);
+    auto checkpoint = [&]() {
+        const CheckpointState state_a{va_blank, va_label}, state_b{vb_blank, vb_label};
+        vp[0] = kBackward ? state_b : state_a;
+        vp[1] = kBackward ? state_a : state_b;
+        fp[0] = frame;                                   // both pairs of the lane share its frame
+        fp[1] = frame;
+        vp += row_step;
+        fp += row_step;
     };
     auto end_chunk = [&]() {
         if (--until_hand_over == 0) {
@@ -2199,8 +1925,6 @@ __device__ __forceinline__ void run_chain_linear2(const Utt m, const int u, cons
             until_hand_over = chunks_per_hand_over;
         }
         renew_frames();
-        xp += xstride;                                   // the next chunk's exponent row
-        store_frame();
     };
     // One step.  A lone wavefront on its SIMD issues an instruction every 2 ns, but one that reads the
     // result of the instruction before it only after 4 ns, and of the one before that after 3 (measured
@@ -2218,15 +1942,15 @@ __device__ __forceinline__ void run_chain_linear2(const Utt m, const int u, cons
         pin();
         const double ua = va_blank + va_label;
         pin();
-        ib_blank = vb_blank + va_label;
+        const double ib_blank = vb_blank + va_label;
         pin();
         const double ela_d = static_cast<double>(ela);
         pin();
-        ib_label = __builtin_fma(va_label, skip_b_one, ub);
+        const double ib_label = __builtin_fma(va_label, skip_b_one, ub);
         pin();
-        ia_label = __builtin_fma(prev, skip_a_scale, ua);
+        const double ia_label = __builtin_fma(prev, skip_a_scale, ua);
         pin();
-        ia_blank = __builtin_fma(prev, scale, va_blank);
+        const double ia_blank = __builtin_fma(prev, scale, va_blank);
         pin();
         const double elb_d = static_cast<double>(elb);
         pin();
@@ -2238,51 +1962,30 @@ __device__ __forceinline__ void run_chain_linear2(const Utt m, const int u, cons
         pin();
         vb_blank = ib_blank * eb_d;
         pin();
-        store(kBackward ? ia_label : va_label, kBackward ? ib_label : vb_label);
-        pin();
     };
 
-    // step 0
-    store_frame();                                       // exponent row 0: step 0 and the first chunk
-    first_step(blank_of(blank_window(0), 0), *epa, *epb);
-
-    float ela_a[kChunk], elb_a[kChunk], ela_b[kChunk], elb_b[kChunk], ela_c[kChunk], elb_c[kChunk];
-    double eb_a[kChunk] = {}, eb_b[kChunk] = {}, eb_c[kChunk] = {};
-    // (label emissions two chunks ahead, the blank's scalars one: see run_chain_linear)
-    auto fetch = [&](float (&ela)[kChunk], float (&elb)[kChunk], double (&eb)[kChunk], const double (&in_use)[kChunk], int s0) {
-        asm volatile("" : : "s"(in_use[0]), "s"(in_use[kChunk - 1]));     // (see run_chain_linear)
-        const double* const w = blank_window(blank64_chunk_with(s0));
+    float ela[4][kChunk], elb[4][kChunk];
+    double eb[2][kChunk] = {};
+    auto fetch = [&](auto set, int i) {
+        constexpr int k = decltype(set)::value;
+        if (i > 0) {
+            asm volatile("" : : "s"(eb[k & 1][0]), "s"(eb[k & 1][kChunk - 1]));     // (see run_chain_linear)
+            const double* const w = emit_blank64 + blank_emission_offset(m, chain_chunk(i - 1, chunks, kBackward));
 #pragma unroll
-        for (int i = 0; i < kChunk; ++i) eb[i] = blank_of(w, i);
-        if (direct) {
-            fetch_frames<kBackward>(epa, advance_a, ela);
-            fetch_frames<kBackward>(epb, advance_b, elb);
-            return;
+            for (int q = 0; q < kChunk; ++q) eb[(k + 1) & 1][q] = w[kBackward ? kChunk - 1 - q : q];
         }
-#pragma unroll
-        for (int i = 0; i < kChunk; ++i) {
-            epa += stride_a;
-            epb += stride_b;
-            ela[i] = *epa;
-            elb[i] = *epb;
-        }
+        fetch_chunk<kBackward>(epa, step_a, ela[k]);
+        fetch_chunk<kBackward>(epb, step_b, elb[k]);
+        __builtin_amdgcn_sched_barrier(0);
     };
-    auto run = [&](const float (&ela)[kChunk], const float (&elb)[kChunk], const double (&eb)[kChunk], int s0, bool whole) {
-        if (whole) {
+    auto run = [&](auto set, int) {
+        constexpr int k = decltype(set)::value;
 #pragma unroll
-            for (int i = 0; i < kChunk; ++i) advance(eb[i], ela[i], elb[i]);
-        } else {
-#pragma unroll
-            for (int i = 0; i < kChunk; ++i)
-                if (s0 + i < Tb) advance(eb[i], ela[i], elb[i]);
-        }
+        for (int q = 0; q < kChunk; ++q) advance(eb[k & 1][q], ela[k][q], elb[k][q]);
+        end_chunk();
+        if (kMode == Mode::kGrad && (k & 1)) checkpoint();
     };
-    chain_schedule3(Tb, [&](int s0) { fetch(ela_a, elb_a, eb_c, eb_b, s0); __builtin_amdgcn_sched_barrier(0); },
-                    [&](int s0) { fetch(ela_b, elb_b, eb_a, eb_c, s0); __builtin_amdgcn_sched_barrier(0); },
-                    [&](int s0) { fetch(ela_c, elb_c, eb_b, eb_a, s0); __builtin_amdgcn_sched_barrier(0); },
-                    [&](int s0, bool whole) { run(ela_a, elb_a, eb_a, s0, whole); },
-                    [&](int s0, bool whole) { run(ela_b, elb_b, eb_b, s0, whole); },
-                    [&](int s0, bool whole) { run(ela_c, elb_c, eb_c, s0, whole); }, end_chunk);
+    chain_schedule(chunks, fetch, run);
 
     if (!kBackward) {
         // p = alpha_{T-1}(2L) + alpha_{T-1}(2L-1): the blank of pair L and the label of pair L - 1.
@@ -2294,7 +1997,7 @@ __device__ __forceinline__ void run_chain_linear2(const Utt m, const int u, cons
             const int exponent = frame + __builtin_amdgcn_frexp_exp(p);
             // (in double: once per chain, and a cost near zero, p near 1, would keep few of a float logarithm's bits)
             const double l2 = static_cast<double>(exponent) + ::log2(mantissa);
-            lattice_store(&logp[u], (p > 0.0) ? pack_state(1.0 / mantissa, -exponent) : 0.0);     // 1 / p
+            logp[u] = (p > 0.0) ? pack_state(1.0 / mantissa, -exponent) : 0.0;     // 1 / p
             const float cost = (p > 0.0) ? static_cast<float>(-l2 * kLn2) : __builtin_inff();
             if (kMode == Mode::kLoss) hl->cost = cost;
             else costs[u] = cost;
@@ -2315,7 +2018,7 @@ __device__ __forceinline__ void run_chain_linear2(const Utt m, const int u, cons
             costs[u] = any_lost ? __uint_as_float(0x7FC00000u) : cost;
         }
     } else if (lost && lane == 0) {
-        lattice_store(&chain_err[u], 1);
+        chain_err[u] = 1;
     }
 }
 
@@ -2329,30 +2032,11 @@ struct LatticeOut {
     int* beta_exponents;
 };
 
-// ---- gradient rows inside the lattice launch (kTaskRows in the launcher's header) ----------------
-// What the workgroups after the chains' get besides the chains' arguments.
-struct WorkerArgs {
-    const void* x;            // activations and gradient tensor, of type `dtype`
-    void* grads;
-    const int* links;
-    const float* lse;
-    const int* tasks;         // the list of tasks: die[kXcds + 1], prefix[2B + 1], info[2B], first[2B]
-    int* done;                // per utterance: wavefronts of its chains that have ended
-    int* where;               // per chain: 1 + the die its workgroup runs on
-    int* leftover;            // per utterance: set if a worker had to leave its rows to the gradient launch
-    int n_tasks;              // 0: the launch has no workers
-    int n_entries;
-    int n_chains;
-    int n_cu;
-    int rounds;               // the launch has rounds x n_cu workgroups; the first n_chains of every round do not work
-    int worker_waves;         // wavefronts of a working workgroup that have a piece of LDS to work in
-    int T, B, A, blank, Lmax;
-    int dtype;
-    int lds_ints;             // ints of dynamic LDS of the launch's workgroups
-    // (used by the chains as well)
+// What the chains' workgroups get besides.
+struct LaunchWords {
     const int* row_flags;     // narrow softmax launch's words (rows_flagged), or nullptr: the records' flags say it all
     int flag_blocks;          // ... per utterance
-    int* domain;              // per utterance: did its chains run in the log domain (published by the forward chain)
+    int* domain;              // per utterance and direction: did the chain run in the log domain
     int* host_flag;           // pinned host word that receives host_flag_value: the image may be reused (or nullptr)
     int host_flag_value;
     const int* status_words;  // device-resident metadata built by the narrow softmax launch: per utterance, nonzero if
@@ -2361,57 +2045,15 @@ struct WorkerArgs {
     int skip_directions;      // bit 0: leave the forward chains out, bit 1: the backward chains (measurements only)
 };
 
-// The die (XCD) this wavefront runs on: each has an L2 of its own.
-__device__ __forceinline__ int this_xcd() { return static_cast<int>(__builtin_amdgcn_s_getreg(63508) & 15u); }   // XCC_ID, 32 bits
-
-// How a chain hands its lattice to the workers without a device-wide cache write-back (which,
-// with the matching invalidation on the workers' side, was measured to lengthen the running chains
-// by half): the L2 of a die is the point at which all its compute units agree, a chain's stores are
-// complete once that L2 has them, and workgroups are dealt to the dies in turn, so that the workers
-// of a die can be given the utterances whose chains ran there.  A chain's first wavefront publishes
-// the die it finds itself on; a worker that finds itself on another die than both chains of an
-// utterance does not touch it and marks the utterance for the gradient launch that follows.
-__device__ __forceinline__ void chain_started(const WorkerArgs& wk, int chain)
-{
-    if (wk.n_tasks > 0 && threadIdx.x == 0)
-        __hip_atomic_store(&wk.where[chain], this_xcd() + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// A chain's wavefront has ended.  Once all its stores have completed (the L2 has them) it counts
-// itself in; the last wavefront of the chain's workgroup to do so moves the utterance's counter,
-// which therefore reaches 2 when both chains have ended.
-__device__ __forceinline__ void chain_ended(const WorkerArgs& wk, int u, int waves, void* lds)
-{
-    if (wk.n_tasks == 0 || u < 0) return;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");      // (waits for the stores; no cache operation)
-    __builtin_amdgcn_s_waitcnt(0);
-    bool last = true;
-    if (lds) {
-        int before = 0;
-        if ((threadIdx.x & 63) == 0)
-            before = __hip_atomic_fetch_add(&static_cast<HaloHeader*>(lds)->finished, 1, __ATOMIC_RELAXED,
-                                            __HIP_MEMORY_SCOPE_WORKGROUP);
-        last = __builtin_amdgcn_readfirstlane(before) == waves - 1;
-    }
-    if (last && (threadIdx.x & 63) == 0)
-        __hip_atomic_fetch_add(&wk.done[u * kDoneStride], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-
-// What a wavefront of a lattice workgroup has done: the utterance whose chain it ran to its end
-// (-1: none) and the number of wavefronts of that chain.
-struct ChainRun {
-    int u, waves;
-};
-
-template <Sync kSync, Mode kMode, bool kSymbolMajor>
-__device__ __forceinline__ ChainRun lattice_body(const Utt* __restrict__ meta, const int* __restrict__ order,
+template <Sync kSync, Mode kMode>
+__device__ __forceinline__ void lattice_body(const Utt* __restrict__ meta, const int* __restrict__ order,
                                              const int* __restrict__ labels,
                                              const float* __restrict__ emit_blank, const double* __restrict__ emit_blank64,
                                              const float* __restrict__ emit_label,
                                              const LatticeOut lat,
                                              double* __restrict__ logp, float* __restrict__ costs,
                                              int* __restrict__ chain_err, uint32_t* __restrict__ sink,
-                                             void* lds, const WorkerArgs& wk)
+                                             void* lds, const LaunchWords& wk)
 {
     // The first workgroup of the launch tells the host that the pinned image of the call is free
     // again (calls whose softmax launch read the image itself: this launch follows it).
@@ -2431,13 +2073,13 @@ __device__ __forceinline__ ChainRun lattice_body(const Utt* __restrict__ meta, c
     // chain's own rows instead was slower than either in launches that are not crowded.)
     sink += (static_cast<size_t>(blockIdx.x) * kSinkWaves + (threadIdx.x >> 6)) * (kSinkBytes / sizeof(uint32_t));
     const int chain = order[blockIdx.x];           // utterance * 2 + direction
-    if (chain < 0) return {-1, 0};      // device-planned batches launch a workgroup per utterance and direction, running or not
+    if (chain < 0) return;      // device-planned batches launch a workgroup per utterance and direction, running or not
     // (measurements of the recursions one after the other: a launch that leaves one direction out)
-    if (kMode == Mode::kGrad && ((wk.skip_directions >> (chain & 1)) & 1)) return {-1, 0};
+    if (kMode == Mode::kGrad && ((wk.skip_directions >> (chain & 1)) & 1)) return;
     const int u = chain >> 1;
     const bool forward = kMode != Mode::kGrad || (chain & 1) == 0;
     const Utt m = meta[u];
-    if (!(m.flags & kUttRuns)) return {-1, 0};     // (a run order built on the device lists every utterance)
+    if (!(m.flags & kUttRuns)) return;     // (a run order built on the device lists every utterance)
     // Which recursion: the barrier kernel and the maximum recursion have the log domain only;
     // otherwise the flag that the softmax launch may have raised decides.  A linear-domain chain
     // gives one pair or two to a lane as the launcher planned it (two_pairs_per_lane).
@@ -2465,349 +2107,38 @@ __device__ __forceinline__ ChainRun lattice_body(const Utt* __restrict__ meta, c
             hl->gave_up = 0;
         }
         __syncthreads();
-        if (idle) return {-1, 0};
+        if (idle) return;
     } else if (kSync == Sync::kBarrier) {
         if (idle) {
             // Nothing to compute, but keep meeting the barriers of the working wavefronts:
             // one per recursion step, plus the forward chain's final exchange.
-            const int barriers = (m.Tb - 1) + (forward ? 1 : 0);
+            const int barriers = static_cast<int>(padded_frames(m.Tb)) + (forward ? 1 : 0);
             for (int i = 0; i < barriers; ++i) __syncthreads();
-            return {-1, 0};
+            return;
         }
     }
     if constexpr (kSync != Sync::kBarrier && kMode != Mode::kBest) {
         if (two_pairs) {
             if constexpr (kSync == Sync::kHalo) {
                 if (forward)
-                    run_chain_linear2<false, kMode, kSymbolMajor>(m, u, labels, emit_blank, emit_blank64, emit_label, lat.alpha, lat.alpha_exponents, logp, costs, chain_err, sink, lds);
+                    run_chain_linear2<false, kMode>(m, u, labels, emit_blank64, emit_label, lat.alpha, lat.alpha_exponents, logp, costs, chain_err, sink, lds);
                 else
-                    run_chain_linear2<true, Mode::kGrad, kSymbolMajor>(m, u, labels, emit_blank, emit_blank64, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
+                    run_chain_linear2<true, Mode::kGrad>(m, u, labels, emit_blank64, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
             }
-            return {u, waves};
+            return;
         }
         if (!in_log_domain) {
             if (forward)
-                run_chain_linear<false, kSync, kMode, kSymbolMajor>(m, u, labels, emit_blank, emit_blank64, emit_label, lat.alpha, lat.alpha_exponents, logp, costs, chain_err, sink, lds);
+                run_chain_linear<false, kSync, kMode>(m, u, labels, emit_blank64, emit_label, lat.alpha, lat.alpha_exponents, logp, costs, chain_err, sink, lds);
             else
-                run_chain_linear<true, kSync, Mode::kGrad, kSymbolMajor>(m, u, labels, emit_blank, emit_blank64, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
-            return {u, waves};
+                run_chain_linear<true, kSync, Mode::kGrad>(m, u, labels, emit_blank64, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
+            return;
         }
     }
     if (forward)
-        run_chain_log<false, kSync, kMode, kSymbolMajor>(m, u, labels, emit_blank, emit_label, lat.alpha, lat.alpha_exponents, logp, costs, chain_err, sink, lds);
+        run_chain_log<false, kSync, kMode>(m, u, labels, emit_blank, emit_label, lat.alpha, lat.alpha_exponents, logp, costs, chain_err, sink, lds);
     else
-        run_chain_log<true, kSync, Mode::kGrad, kSymbolMajor>(m, u, labels, emit_blank, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
-    return {u, waves};
-}
-
-// ---- gradient rows of narrow alphabets (shared by the gradient kernel and the lattice launch's workers) ----
-constexpr int kAhead = 4;             // 64-state pieces of a row requested together
-
-// The stored lattice of one utterance as the gradient kernels read it: the label states of frame t
-// are one row of alpha values, one of beta values, and the exponent rows that the two chains wrote
-// for the steps at which they reached that frame (exponent_row: alpha's step is t, beta's Tb-1-t).
-struct LatticeRow {
-    const uint32_t* a;
-    const int* ea;
-    const uint32_t* b;
-    const int* eb;
-};
-struct LatticeRows {
-    const uint32_t* a;
-    const int* ea;
-    const uint32_t* b;
-    const int* eb;
-    size_t pitch;
-    int Tb;
-    int log_domains;          // bit 0: the forward chain ran in the log domain, bit 1: the backward chain (chain_domains)
-    __device__ __forceinline__ LatticeRow at(int t) const
-    {
-        const size_t values = static_cast<size_t>(t) * pitch;
-        return {a + values, ea + static_cast<size_t>(exponent_row(t, (log_domains & 1) != 0)) * pitch,
-                b + values, eb + static_cast<size_t>(exponent_row(Tb - 1 - t, (log_domains & 2) != 0)) * pitch};
-    }
-};
-// The domains of an utterance's two chains as its chains published them (a word per direction:
-// either chain may have gone over to the log domain on its own, see lattice_body).
-template <bool kCoherent>
-__device__ __forceinline__ int chain_domains(const int* __restrict__ domain, int b)
-{
-    return (lattice_load<kCoherent>(&domain[2 * b]) != 0 ? 1 : 0) | (lattice_load<kCoherent>(&domain[2 * b + 1]) != 0 ? 2 : 0);
-}
-
-// The rows t_first, t_first + t_step, ... (below tend) of utterance b, by one wavefront: lane k is
-// symbol k (alphabets of at most 64 symbols).  s_slot, s_start, s_count: the grouping of the label's
-// positions as ctc_gradient_narrow_kernel describes it, in LDS; g_slot: L + 1 floats of LDS of this
-// wavefront's own.
-// `stage` is called once, after the first row's values have been requested and before anything is read
-// out of s_slot, s_start and s_count: a caller that still has to fill them does it there, so that its
-// loads and the first row's are under way together.
-template <typename T, bool kStreaming, bool kCoherent, typename Stage>
-__device__ __forceinline__ void narrow_gradient_rows(const T* __restrict__ x, T* __restrict__ grads, const Utt m,
-                                                     const int b, const LatticeOut lat,
-                                                     const float* __restrict__ lse, const double* __restrict__ logp,
-                                                     const int log_domains,   // decides where a row's exponents are (LatticeRows)
-                                                     const int Tt, const int B, const int A, const int blank,
-                                                     const int t_first, const int t_step, const int tend,
-                                                     const int* s_slot, const int* s_start, const int* s_count,
-                                                     float* g_slot, Stage&& stage)
-{
-    const int lane = threadIdx.x & 63;
-    const bool runs = (m.flags & kUttRuns) != 0;
-    const int L = m.L;
-    const size_t pitch = static_cast<size_t>(lattice_pitch(L));
-    const double packed_inverse_p = runs ? lattice_load<kCoherent>(&logp[b]) : 0.0;
-    const float inverse_p = static_cast<float>(packed_inverse_p);
-    const int inverse_p_exponent = __double2loint(packed_inverse_p);
-    const LatticeRows rows_of{lat.alpha + m.ab_off + 1, lat.alpha_exponents + m.ab_off + 1,     // label state i sits
-                              lat.beta + m.ab_off + 1, lat.beta_exponents + m.ab_off + 1,       // in column 1 + i
-                              pitch, m.Tb, log_domains};
-    // What a row needs from memory: the lattice words of its first kAhead * 64 label states
-    // (longer labels read the rest in line), its log-sum-exp and its activations.  A row's
-    // values are requested while the row before it is still being summed up out of LDS: by then
-    // the registers are free again (the shares are in LDS), so the overlap costs none.
-    struct RowData {
-        uint32_t a[kAhead], b[kAhead];
-        int ea[kAhead], eb[kAhead];
-        float l2, x0;
-    };
-    // Row addresses are kept as running pointers of this wavefront's rows (t_first, t_first + t_step,
-    // ...): the product (t x B + b) x A is formed once, not per row.
-    const float* next_lse = lse + static_cast<size_t>(b) * Tt + t_first;
-    const size_t row_step = static_cast<size_t>(t_step) * B * A;
-    const T* next_x = x + (static_cast<size_t>(t_first) * B + b) * A;
-    T* grow = grads + (static_cast<size_t>(t_first) * B + b) * A;                     // of the row being written
-    // A lattice larger than the caches is read once and never again: such launches read the values
-    // with loads that leave no copy behind (kStreaming), which keeps the caches for the rest (the
-    // exponent rows among it: eight frames share one).
-    auto value_word = [&](const uint32_t* p) {
-        return kCoherent ? lattice_load<true>(p) : (kStreaming ? __builtin_nontemporal_load(p) : *p);
-    };
-    auto exponent_word = [&](const int* p) { return lattice_load<kCoherent>(p); };
-    auto request = [&](int t, RowData& d) {
-        const LatticeRow row = rows_of.at(t);
-#pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-            if (u * 64 >= L) break;                      // (the same for every lane)
-            const int j = u * 64 + lane;
-            if (j < L) {
-                d.a[u] = value_word(row.a + j);
-                d.b[u] = value_word(row.b + j);
-                d.ea[u] = exponent_word(row.ea + j);
-                d.eb[u] = exponent_word(row.eb + j);
-            }
-        }
-        d.l2 = *next_lse;
-        d.x0 = (lane < A) ? load_elem(next_x, lane) : 0.0f;
-    };
-    auto advance_request = [&]() {
-        next_lse += t_step;
-        next_x += row_step;
-    };
-    RowData cur = {};
-    if (runs && t_first < tend && t_first < m.Tb) request(t_first, cur);
-    stage();
-    for (int t = t_first; t < tend; t += t_step, grow += row_step) {
-        if (t >= m.Tb || !runs) {
-            if (lane < A) store_elem(grow, lane, 0.0f);
-            continue;
-        }
-#pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-            if (u * 64 >= L) break;                      // (the same for every lane)
-            const int j = u * 64 + lane;
-            if (j < L) g_slot[s_slot[j]] = mass_share(cur.a[u], cur.ea[u], cur.b[u], cur.eb[u], inverse_p, inverse_p_exponent);
-        }
-        if (L > kAhead * 64) {
-            const LatticeRow row = rows_of.at(t);         // this row's states past the first kAhead * 64
-            for (int j = kAhead * 64 + lane; j < L; j += 64)
-                g_slot[s_slot[j]] = mass_share(value_word(row.a + j), exponent_word(row.ea + j), value_word(row.b + j), exponent_word(row.eb + j),
-                                               inverse_p, inverse_p_exponent);
-        }
-        const float l2 = cur.l2, x0 = cur.x0;
-        advance_request();
-        if (t + t_step < tend && t + t_step < m.Tb) request(t + t_step, cur);
-        // LDS operations of one wavefront complete in program order; the fences only keep the
-        // compiler from moving them across.
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        // The shares now sit in slot order, the positions of a symbol next to each other: turn
-        // them into running sums (64 slots at a time, the total so far carried along), so that
-        // a symbol's occupancy is the difference of two entries and the blank's 1 minus the last.
-        float carried = 0.0f;
-        for (int base = 0; base < L; base += 64) {
-            const int slot = base + lane;
-            const float sum = wave_running_sum(slot < L ? g_slot[slot] : 0.0f) + carried;
-            if (slot < L) g_slot[slot] = sum;
-            carried = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sum), 63));
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        if (lane < A) {
-            const int first = s_start[lane], count = s_count[lane];
-            float o = 0.0f;
-            if (count > 0) o = g_slot[first + count - 1] - (first > 0 ? g_slot[first - 1] : 0.0f);
-            if (lane == blank) o = 1.0f - carried;       // the blank states share what is left of 1
-            store_elem(grow, lane, fast_exp2(fmaf(x0, kLog2e, -l2)) - o);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    }
-}
-
-// A workgroup after the chains'.  Its wavefronts work on their own: the tasks are dealt out in
-// turn over all working wavefronts of the launch (wavefront w takes tasks w, w + W, w + 2W, ...:
-// no shared counter, whose traffic was measured to slow the chains severalfold), so that the
-// tasks of the utterances that end last are spread over all of them.  For each task a wavefront
-// waits if the utterance still has chains running, stages the grouping of the utterance's label
-// in its own piece of LDS and writes the task's rows.  `lds` holds lds_ints ints: the list's table
-// for the workgroup, then a piece per wavefront.
-template <typename T>
-__device__ __forceinline__ void gradient_worker(const WorkerArgs wk, const Utt* __restrict__ meta,
-                                                const int* __restrict__ labels, const LatticeOut lat,
-                                                const double* __restrict__ logp, const int* __restrict__ chain_err,
-                                                float* __restrict__ costs, int* lds, const int lds_ints)
-{
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int E = wk.n_entries >= 0 ? wk.n_entries : min(max(wk.tasks[kXcds], 0), 2 * wk.B), Lmax = wk.Lmax;
-    int* const s_die = lds;                       // [kXcds + 1]
-    int* const s_prefix = s_die + kXcds + 1;      // [E + 1]
-    int* const s_info = s_prefix + E + 1;         // [E]
-    int* const s_first = s_info + E;              // [E]
-    const int* const prefix_in = wk.tasks + kXcds + 1;
-    const int* const info_in = prefix_in + 2 * wk.B + 1;
-    const int* const first_in = info_in + 2 * wk.B;
-    for (int i = threadIdx.x; i <= kXcds; i += blockDim.x) s_die[i] = wk.tasks[i];
-    for (int i = threadIdx.x; i <= E; i += blockDim.x) s_prefix[i] = prefix_in[i];
-    for (int i = threadIdx.x; i < E; i += blockDim.x) {
-        s_info[i] = info_in[i];
-        s_first[i] = first_in[i];
-    }
-    __syncthreads();                              // the only barrier, before any wavefront waits for anything
-    const int table = kXcds + 1 + 3 * E + 1, piece = 2 * Lmax + 129;
-    if (wave >= wk.worker_waves || table + (wave + 1) * piece > lds_ints) return;
-    int* const s_slot = lds + table + wave * piece;   // [Lmax]  as in ctc_gradient_narrow_kernel
-    int* const s_start = s_slot + Lmax;               // [64]
-    int* const s_count = s_start + 64;                // [64]
-    float* const g_slot = reinterpret_cast<float*>(s_count + 64);   // [Lmax + 1]
-    const T* const x = static_cast<const T*>(wk.x);
-    T* const grads = static_cast<T*>(wk.grads);
-
-    // This workgroup's die as the dispatcher deals them out (workgroup i to die i mod kXcds; n_cu is a
-    // multiple of kXcds), its rank among the working workgroups of that die, and their number: of the
-    // places n_chains .. n_cu - 1 of a round, those congruent to the die.
-    const int round = static_cast<int>(blockIdx.x) / wk.n_cu, place = static_cast<int>(blockIdx.x) % wk.n_cu;
-    const int die = place % kXcds;
-    const int first_place = wk.n_chains + (die - wk.n_chains % kXcds + kXcds) % kXcds;
-    const int per_round = (wk.n_cu - first_place + kXcds - 1) / kXcds;
-    const int group = round * per_round + (place - first_place) / kXcds;
-    const int stride = wk.rounds * per_round * wk.worker_waves;
-    // the die's section of the list
-    const int e_first = s_die[die], e_end = s_die[die + 1];
-    const int ticket_first = s_prefix[e_first], ticket_end = s_prefix[e_end];
-    const int xcd = this_xcd();
-    int ready = -1;                               // the utterance whose chains this wavefront last found ended, here
-    int staged = -1;                              // the utterance whose label grouping sits in this wavefront's LDS
-    for (int ticket = ticket_first + wave * wk.rounds * per_round + group; ticket < ticket_end; ticket += stride) {
-        // the run of tasks the ticket falls into
-        int e = e_first;
-        for (int i0 = e_first; i0 < e_end; i0 += 64) {
-            const int i = i0 + lane;
-            e += __popcll(__ballot(i < e_end && s_prefix[i + 1] <= ticket));
-        }
-        const int info = s_info[e];
-        const int b = info & 0xFFFF, rows_log2 = (info >> kTaskRowsShift) & 15;
-        const int t0 = (s_first[e] + ticket - s_prefix[e]) << rows_log2;
-        const int tend = min(t0 + (1 << rows_log2), wk.T);
-        const Utt m = meta[b];
-        const bool runs = (m.flags & kUttRuns) != 0;
-        if (runs && t0 < m.Tb) {
-            if ((info & kTaskWaits) && b != ready) {
-                // Which die do the utterance's chains run on?  They publish it as they start, at most
-                // microseconds after this wavefront did.  Only if it is this die can the counter and the
-                // lattice be read here (the L2 they sit in is this die's); otherwise, or if the answer
-                // does not come (another die's store need not become visible here), the utterance is
-                // left to the gradient launch.
-                auto published = [&]() {
-                    int here = 0;
-                    if (lane == 0) {
-                        const int f = __hip_atomic_load(&wk.where[2 * b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        const int r = __hip_atomic_load(&wk.where[2 * b + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        here = (f == 0 || r == 0) ? 0 : ((f == xcd + 1 && r == xcd + 1) ? 1 : 2);
-                    }
-                    return __builtin_amdgcn_readfirstlane(here);
-                };
-                int here = published();
-                for (int polls = kWherePolls; here == 0 && polls > 0; --polls) {
-                    __builtin_amdgcn_s_sleep(24);
-                    here = published();
-                }
-                if (here != 1) {
-                    if (lane == 0) wk.leftover[b] = 1;
-                    continue;
-                }
-                const int expected = 2;          // both chains of the utterance (chain_ended)
-                // (one lane asks; a sleep of some hundred nanoseconds between two questions)
-                int budget = kWorkerPollBudget;
-                auto ended_now = [&]() {
-                    int v = 0;
-                    if (lane == 0) v = __hip_atomic_load(&wk.done[b * kDoneStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    return __builtin_amdgcn_readfirstlane(v);
-                };
-                int ended = ended_now();
-                while (ended < expected && budget > 0) {
-                    __builtin_amdgcn_s_sleep(24);
-                    --budget;
-                    ended = ended_now();
-                }
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");    // (orders the loads below after the counter's)
-                if (ended < expected) {
-                    // (chains that never end: nothing of this task can be computed)
-                    if (lane == 0) costs[b] = __uint_as_float(0x7FC00000u);
-                    continue;
-                }
-                ready = b;
-            }
-            if (t0 == 0 && lane == 0 && lattice_load<true>(&chain_err[b]) != 0)
-                costs[b] = __uint_as_float(0x7FC00000u);
-            // the grouping of the label's positions, for this wavefront
-            if (b != staged) {
-            staged = b;
-            s_start[lane] = 0;
-            s_count[lane] = 0;
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            for (int j = lane; j < m.L; j += 64) {
-                const int link = wk.links[m.lab_off + j];
-                s_slot[j] = link & kLinkSlotMask;
-                if (link < 0) {
-                    const int c = labels[m.lab_off + j];
-                    s_start[c] = link & kLinkSlotMask;
-                    s_count[c] = (link >> kLinkCountShift) & kLinkSlotMask;
-                }
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            }
-        }
-        const int log_domains = (runs && t0 < m.Tb) ? chain_domains<true>(wk.domain, b) : 0;
-        narrow_gradient_rows<T, false, true>(x, grads, m, b, lat, wk.lse, logp, log_domains, wk.T, wk.B, wk.A, wk.blank, t0, 1,
-                                       tend, s_slot, s_start, s_count, g_slot, [] {});
-    }
-}
-
-// Workgroups beyond the chains' are workers -- unless they would share a compute unit with a chain:
-// the dispatcher hands workgroup i to compute unit i mod n_cu (see order_chains), a chain's
-// wavefront needs its SIMD to itself, so the workgroups that would land there leave at once.
-__device__ __forceinline__ bool is_worker(const WorkerArgs& wk)
-{
-    return wk.n_tasks > 0 && static_cast<int>(blockIdx.x) >= wk.n_chains;
-}
-__device__ __forceinline__ void run_worker(const WorkerArgs& wk, const Utt* __restrict__ meta,
-                                           const int* __restrict__ labels, const LatticeOut lat,
-                                           const double* __restrict__ logp, const int* __restrict__ chain_err,
-                                           float* __restrict__ costs, int* lds)
-{
-    if (static_cast<int>(blockIdx.x % static_cast<unsigned>(wk.n_cu)) < wk.n_chains) return;
-    if (wk.dtype == CTC_DTYPE_F32)
-        gradient_worker<float>(wk, meta, labels, lat, logp, chain_err, costs, lds, wk.lds_ints);
-    else
-        gradient_worker<bf16_t>(wk, meta, labels, lat, logp, chain_err, costs, lds, wk.lds_ints);
+        run_chain_log<true, kSync, Mode::kGrad>(m, u, labels, emit_blank, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
 }
 
 // grid = one workgroup per entry of `order` (utterance * 2 + direction: 0 forward, 1 backward; only
@@ -2815,7 +2146,7 @@ __device__ __forceinline__ void run_worker(const WorkerArgs& wk, const Utt* __re
 // predecessor choices, or unused).
 // blockDim.x = 64 * (most wavefronts any utterance of the batch uses).
 // Variant for batches whose labels all fit one wavefront: no exchange at all.
-template <Mode kMode, bool kSymbolMajor>
+template <Mode kMode>
 __global__ __launch_bounds__(64)
 void ctc_lattice_kernel_w1(const Utt* __restrict__ meta, const int* __restrict__ order,
                            const int* __restrict__ labels, const float* __restrict__ emit_blank,
@@ -2823,23 +2154,14 @@ void ctc_lattice_kernel_w1(const Utt* __restrict__ meta, const int* __restrict__
                            const float* __restrict__ emit_label,
                            const LatticeOut lat,
                            double* __restrict__ logp, float* __restrict__ costs,
-                           int* __restrict__ chain_err, uint32_t* __restrict__ sink, const WorkerArgs wk)
+                           int* __restrict__ chain_err, uint32_t* __restrict__ sink, const LaunchWords wk)
 {
-    if constexpr (kMode == Mode::kGrad && kSymbolMajor) {
-        if (is_worker(wk)) {
-            extern __shared__ int worker_lds[];
-            run_worker(wk, meta, labels, lat, logp, chain_err, costs, worker_lds);
-            return;
-        }
-    }
-    if constexpr (kMode == Mode::kGrad && kSymbolMajor) chain_started(wk, order[blockIdx.x]);
-    const ChainRun ran = lattice_body<Sync::kNone, kMode, kSymbolMajor>(meta, order, labels, emit_blank, emit_blank64, emit_label, lat,
+    lattice_body<Sync::kNone, kMode>(meta, order, labels, emit_blank, emit_blank64, emit_label, lat,
                                                                    logp, costs, chain_err, sink, nullptr, wk);
-    if constexpr (kMode == Mode::kGrad && kSymbolMajor) chain_ended(wk, ran.u, ran.waves, nullptr);
 }
 
 // Multi-wavefront chains with the halo exchange.
-template <Mode kMode, bool kSymbolMajor>
+template <Mode kMode>
 __global__ __launch_bounds__(1024)
 void ctc_lattice_kernel(const Utt* __restrict__ meta, const int* __restrict__ order,
                         const int* __restrict__ labels, const float* __restrict__ emit_blank,
@@ -2847,24 +2169,16 @@ void ctc_lattice_kernel(const Utt* __restrict__ meta, const int* __restrict__ or
                         const float* __restrict__ emit_label,
                         const LatticeOut lat,
                         double* __restrict__ logp, float* __restrict__ costs,
-                        int* __restrict__ chain_err, uint32_t* __restrict__ sink, const WorkerArgs wk)
+                        int* __restrict__ chain_err, uint32_t* __restrict__ sink, const LaunchWords wk)
 {
     extern __shared__ double2 halo_lds[];                    // halo_lds_bytes(wavefronts of the workgroup)
-    if constexpr (kMode == Mode::kGrad && kSymbolMajor) {
-        if (is_worker(wk)) {
-            run_worker(wk, meta, labels, lat, logp, chain_err, costs, reinterpret_cast<int*>(halo_lds));
-            return;
-        }
-    }
-    if constexpr (kMode == Mode::kGrad && kSymbolMajor) chain_started(wk, order[blockIdx.x]);
-    const ChainRun ran = lattice_body<Sync::kHalo, kMode, kSymbolMajor>(meta, order, labels, emit_blank, emit_blank64, emit_label, lat,
+    lattice_body<Sync::kHalo, kMode>(meta, order, labels, emit_blank, emit_blank64, emit_label, lat,
                                                                    logp, costs, chain_err, sink, halo_lds, wk);
-    if constexpr (kMode == Mode::kGrad && kSymbolMajor) chain_ended(wk, ran.u, ran.waves, halo_lds);
 }
 
 // Labels too long to leave room for a halo (more than 16 * 63 pairs): 64 pairs per wavefront
 // and one barrier per step.
-template <Mode kMode, bool kSymbolMajor>
+template <Mode kMode>
 __global__ __launch_bounds__(1024)
 void ctc_lattice_kernel_barrier(const Utt* __restrict__ meta, const int* __restrict__ order,
                                 const int* __restrict__ labels, const float* __restrict__ emit_blank,
@@ -2872,10 +2186,10 @@ void ctc_lattice_kernel_barrier(const Utt* __restrict__ meta, const int* __restr
                                 const float* __restrict__ emit_label,
                                 const LatticeOut lat,
                                 double* __restrict__ logp, float* __restrict__ costs,
-                                int* __restrict__ chain_err, uint32_t* __restrict__ sink, const WorkerArgs wk)
+                                int* __restrict__ chain_err, uint32_t* __restrict__ sink, const LaunchWords wk)
 {
     __shared__ double xch[2][16];
-    lattice_body<Sync::kBarrier, kMode, kSymbolMajor>(meta, order, labels, emit_blank, emit_blank64, emit_label, lat, logp,
+    lattice_body<Sync::kBarrier, kMode>(meta, order, labels, emit_blank, emit_blank64, emit_label, lat, logp,
                                                costs, chain_err, sink, &xch[0][0], wk);
 }
 
@@ -2913,8 +2227,8 @@ void ctc_backtrace_kernel(const Utt* __restrict__ meta, const unsigned char* __r
     const unsigned char* base = choices + m.ab_off;
     // state of frame t; clamped so that no stored value can lead the reads astray
     int state = __builtin_amdgcn_readfirstlane(min(max(static_cast<int>(end_state[b]), 0), 2 * m.L));
-    int t = m.Tb - 1;
-    if (lane == 0) arow[t] = state;
+    int t = static_cast<int>(padded_frames(m.Tb)) - 1;     // (virtual frames: their states are not stored)
+    if (lane == 0 && t < m.Tb) arow[t] = state;
     // Frames t, t-1, ..., 1 each hold the choice that leads to the state of the frame before.
     while (t >= 1) {
         const int pair_hi = state >> 1;                   // both states of a pair share its byte
@@ -2938,273 +2252,569 @@ void ctc_backtrace_kernel(const Utt* __restrict__ meta, const unsigned char* __r
             // lane r of `filed` = state of frame t - r - 1
             asm volatile("v_writelane_b32 %0, %1, %2" : "+v"(filed) : "s"(state), "n"(r));
         }
-        if (lane < rows) arow[t - 1 - lane] = filed;
+        if (lane < rows && t - 1 - lane < m.Tb) arow[t - 1 - lane] = filed;
         if (rows < kTile) break;
         t -= kTile;
     }
 }
 
 // ---- gradient ------------------------------------------------------------------------------
-//   gamma_t(s) = alpha_t(s) * beta_t(s) / p                 mass share of state s (mass_share)
+//   gamma_t(s) = alpha_t(s) * beta_t(s) / p                 mass share of state s
 //   grad[k]    = y_t(k) - sum_{s: symbol(s) = k} gamma_t(s)
-// Only the label states' gamma are computed from the stored lattice; the blank column gets
+// Only the label states' gamma are computed; the blank column gets
 // 1 - (sum over label states), which is the blank states' share because the shares of all
 // states of a frame add up to 1.  Every row of the gradient therefore sums to zero.
 //
-// A workgroup takes rows_per_group consecutive frames of one utterance (8 or 16 dense, 4 sparse),
-// one wavefront per row at a time.  Labels and their grouping words sit in LDS; per wavefront,
-// the label states' mass shares in slot order (P floats).  Everything within a row stays inside
-// one wavefront, so no barrier is needed after the staging.  The first occurrence of a symbol
-// adds up the run of slots of its symbol and is the only writer of that symbol's occupancy; the
-// blank's L+1 states are a wavefront reduction.
-//   dense  (A <= 2048): occupancies go to A floats of LDS per wavefront, then the whole row
-//          y - occupancy is written, and padding rows are zero-filled;
-//   sparse (wider):     the dense part of the row was written by the softmax launch; only the
-//          label columns and the blank column are rewritten (no A-bin histogram).
-// Dynamic LDS: 2 * L_max ints + 4 * (L_max + 1 + (dense ? A : 0)) floats.
+// A wavefront takes one block of kBlockFrames frames of one utterance and runs both recursions over it once more, from
+// the checkpoints that the chains left at the block's ends (or from the start state): alpha forward, keeping the label
+// states' high dwords in registers, then beta backward, forming a frame's shares as it passes.  A lane owns two
+// neighbouring label positions for both directions, so a share needs nothing from another lane:
+//   alpha: (blank j, label j) as in the forward chain;  beta: (label j, blank j + 1), the backward chain's pair.
+// 128 positions make a piece; longer labels take several, each recomputing the 16 positions at its inner edges that
+// its neighbour owns (an error at the edge moves up one position per frame).
+constexpr int kPiecePositions = 128, kPieceHalo = kBlockFrames, kPieceStep = kPiecePositions - 2 * kPieceHalo;
+// A row of one value per lane in LDS, padded so that 16-byte reads of 16 rows meet in no bank; two blocks of a row per frame.
+constexpr int kShareRow = kPiecePositions / 2 + 4, kShareInts = 2 * kBlockFrames * kShareRow;
+static_assert(kPieceStep % 32 == 0, "pieces start at multiples of 32 positions (share_product)");
 
-template <typename T, bool kSparse>
-__global__ __launch_bounds__(kRowThreads)
-void ctc_gradient_rows_kernel(const T* __restrict__ x, T* __restrict__ grads,
-                              const Utt* __restrict__ meta, const int* __restrict__ labels,
-                              const int* __restrict__ links, const float* __restrict__ lse,
-                              const LatticeOut lat,
-                              const double* __restrict__ logp, const int* __restrict__ chain_err,
-                              float* __restrict__ costs, int Tt, int B, int A, int blank, int Lmax,
-                              int rows_per_group, const float* __restrict__ emit_blank,
-                              const float* __restrict__ emit_label, const int* __restrict__ domain)
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef __fp16 half2_raw __attribute__((ext_vector_type(2)));
+typedef float float4v __attribute__((ext_vector_type(4)));
+typedef unsigned uint2v __attribute__((ext_vector_type(2)));
+typedef unsigned uint4v __attribute__((ext_vector_type(4)));
+
+// A record whose fields the compiler knows to be the same in every lane, wherever it was read from.
+__device__ __forceinline__ Utt uniform_record(const Utt& m)
 {
-    extern __shared__ int g_lds[];
-    int* s_lab = g_lds;
-    int* s_lnk = g_lds + Lmax;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    float* g_label = reinterpret_cast<float*>(g_lds + 2 * Lmax) + wave * (Lmax + 1 + (kSparse ? 0 : A));
-    float* occ = g_label + Lmax + 1;
-    const int b = blockIdx.y, t0 = blockIdx.x * rows_per_group;
-    const Utt m = meta[b];
-    if (t0 == 0 && tid == 0 && chain_err[b] != 0) costs[b] = __uint_as_float(0x7FC00000u);
-    const bool runs = (m.flags & kUttRuns) != 0;
-    const int L = m.L;
-    if (runs && t0 < m.Tb) {
-        for (int j = tid; j < L; j += kRowThreads) {
-            s_lab[j] = labels[m.lab_off + j];
-            s_lnk[j] = links[m.lab_off + j];
-        }
-        __syncthreads();
+    Utt u = m;
+    auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+    auto uniform64 = [&](int64_t v) {
+        return static_cast<int64_t>(static_cast<uint64_t>(static_cast<unsigned>(uniform(static_cast<int>(v)))) |
+                                    (static_cast<uint64_t>(static_cast<unsigned>(uniform(static_cast<int>(v >> 32)))) << 32));
+    };
+    u.Tb = uniform(m.Tb);
+    u.L = uniform(m.L);
+    u.lab_off = uniform(m.lab_off);
+    u.flags = uniform(m.flags);
+    u.f_off = uniform(m.f_off);
+    u.e_cols = uniform(m.e_cols);
+    u.e_direct = uniform(m.e_direct);
+    u.e_off = uniform64(m.e_off);
+    u.ab_off = uniform64(m.ab_off);
+    return u;
+}
+
+// alpha * beta / p of one state (without the mantissa of 1 / p) from alpha's high dword and beta, `exponents` the sum of
+// all exponents.  Either value may lie a thousand binary orders below or above the unit of its own frame (lane_frame)
+// while the product is a share of order one: alpha takes all the exponents first.  A state of any mass has beta above
+// 2^-1000 in its frame, so that alpha is then below 2^1000; the cap is for those without.
+__device__ __forceinline__ float state_share(unsigned alpha, double beta, int exponents)
+{
+    return static_cast<float>(fmin(__builtin_amdgcn_ldexp(__hiloint2double(static_cast<int>(alpha), 0), exponents), 0x1p1000) * beta);
+}
+// (the same from two stored words)
+__device__ __forceinline__ float word_share(unsigned a, unsigned b, int exponents)
+{
+    return state_share(a, __hiloint2double(static_cast<int>(b), 0), exponents);
+}
+// x - (one half of a pair of fp16), in one instruction.
+__device__ __forceinline__ float minus_low_half(float x, half2_raw h)
+{
+    float r;
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(h), "v"(x));
+    return r;
+}
+__device__ __forceinline__ float minus_high_half(float x, half2_raw h)
+{
+    float r;
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(h), "v"(x));
+    return r;
+}
+
+// Two state pairs of a lane with a common frame (see run_chain_linear2).  Backward: the lane above takes the part of the
+// lane below.
+struct LanePairs {
+    double blank0, label0, blank1, label1;
+    int frame;
+    double scale;                                        // 2^(neighbour's frame - frame)
+};
+template <bool kBackward>
+__device__ __forceinline__ void renew_pairs(LanePairs& s, int frame0, int frame1)
+{
+    const double top0 = fmax(s.blank0, s.label0), top1 = fmax(s.blank1, s.label1);
+    const int mine = max(top0 > 0.0 ? frame0 + __builtin_amdgcn_frexp_exp(top0) : kNoExponent,
+                         top1 > 0.0 ? frame1 + __builtin_amdgcn_frexp_exp(top1) : kNoExponent);
+    int window = mine;
+#pragma unroll
+    for (int k = 0; k < kChunk / 2; ++k) window = kBackward ? window_max_step_down(window, mine) : window_max_step(window, mine);
+    window = lane_frame(window, mine);
+    s.blank0 = __builtin_amdgcn_ldexp(s.blank0, frame0 - window);
+    s.label0 = __builtin_amdgcn_ldexp(s.label0, frame0 - window);
+    s.blank1 = __builtin_amdgcn_ldexp(s.blank1, frame1 - window);
+    s.label1 = __builtin_amdgcn_ldexp(s.label1, frame1 - window);
+    s.frame = window;
+    const int neighbour = __builtin_amdgcn_update_dpp(kNoExponent, window, kBackward ? 0x130 : 0x138, 0xf, 0xf, false);
+    s.scale = __builtin_amdgcn_ldexp(1.0, min(max(neighbour - window, -1100), 1023));
+}
+
+// What a lane knows of its two label positions: the symbols, and where a label may be entered from the one before.
+struct LaneLabels {
+    int p0, p1;
+    bool has0, has1, skip0, skip1, skip2;                // skip2: from position p1 to the next lane's first
+    int symbol0, symbol1;
+    __device__ __forceinline__ LaneLabels(const int* __restrict__ lab, int L, int base)
+    {
+        p0 = base + 2 * static_cast<int>(threadIdx.x & 63);
+        p1 = p0 + 1;
+        has0 = p0 < L;
+        has1 = p1 < L;
+        // (positions off either end read the nearest one: no branches, so that all loads travel together)
+        auto at = [&](int p) { return lab[min(max(p, 0), L - 1)]; };
+        const int before = at(p0 - 1), after = at(p1 + 1);
+        symbol0 = at(p0);
+        symbol1 = at(p1);
+        skip0 = p0 >= 1 && has0 && symbol0 != before;
+        skip1 = has1 && symbol1 != symbol0;
+        skip2 = p1 + 1 < L && after != symbol1;
     }
-    const size_t pitch = static_cast<size_t>(lattice_pitch(L));
-    const double packed_inverse_p = runs ? logp[b] : 0.0;
-    const float inverse_p = static_cast<float>(packed_inverse_p);
-    const int inverse_p_exponent = __double2loint(packed_inverse_p);
-    const int tend = min(t0 + rows_per_group, Tt);
-    const int log_domains = runs ? chain_domains<false>(domain, b) : 0;     // decides where a row's exponents are (LatticeRows)
-    const LatticeRows rows_of{lat.alpha + m.ab_off + 1, lat.alpha_exponents + m.ab_off + 1,     // label state i sits
-                              lat.beta + m.ab_off + 1, lat.beta_exponents + m.ab_off + 1,       // in column 1 + i
-                              pitch, m.Tb, log_domains};
+};
 
-    // What a row needs from memory, requested in one go before any of it is used, so that a
-    // row costs one memory latency: the lattice values of the first kAhead * 64 label states
-    // (longer labels read the rest in line), the row's log-sum-exp and, dense form, the first
-    // 64 activations.  (Requesting the next row during the current one was measured slower:
-    // the extra registers cost more wavefronts per SIMD than the overlap gains.)
-    struct RowData {
-        uint32_t a[kAhead], b[kAhead];
-        int ea[kAhead], eb_[kAhead];
-        float l2, x0;
-        float e[kAhead], eb;              // sparse form: emissions of the label positions and of blank
-    };
-    auto request = [&](int t, RowData& d) {
-        if (t >= tend || t >= m.Tb || !runs) return;
-        const LatticeRow row = rows_of.at(t);
-#pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-            const int j = u * 64 + lane;
-            if (j < L) {
-                d.a[u] = row.a[j];
-                d.b[u] = row.b[j];
-                d.ea[u] = row.ea[j];
-                d.eb_[u] = row.eb[j];
-            }
+// The checkpoints at both ends of a block for a lane's two positions (position p in column 1 + p; lanes without a
+// position read the last one's).  At an utterance's ends there is none: zeros, with frame 0.
+struct BlockEnds {
+    CheckpointState a0{}, a1{}, b0{}, b1{};
+    int fa0 = 0, fa1 = 0, fb0 = 0, fb1 = 0;
+    __device__ __forceinline__ BlockEnds(const Utt& m, const LatticeOut& lat, int p0, int block)
+    {
+        const int64_t pitch = lattice_pitch(m.L);
+        const int column = 1 + min(p0, max(m.L, 1) - 1);
+        if (block > 0) {
+            const int64_t where = (block - 1) * pitch + column;
+            const CheckpointState* v = reinterpret_cast<const CheckpointState*>(lat.alpha + m.ab_off) + where;
+            const int* f = lat.alpha_exponents + m.ab_off + where;
+            a0 = v[0]; a1 = v[1];
+            fa0 = f[0]; fa1 = f[1];
         }
-        d.l2 = lse[static_cast<size_t>(b) * Tt + t];
-        if (!kSparse && lane < A) d.x0 = load_elem(x + (static_cast<size_t>(t) * B + b) * A, lane);
-        if (kSparse) {
-            const float* er = emit_label + kLabelSlack + m.e_off + static_cast<size_t>(t) * m.e_pitch;
-#pragma unroll
-            for (int u = 0; u < kAhead; ++u) {
-                const int j = u * 64 + lane;
-                if (j < L) d.e[u] = er[j];
-            }
-            d.eb = emit_blank[kBlankSlack + m.f_off + t];
+        if (block + 1 < frame_blocks(m.Tb)) {
+            const int64_t where = (block + 1) * pitch + column;
+            const CheckpointState* v = reinterpret_cast<const CheckpointState*>(lat.beta + m.ab_off) + where;
+            const int* f = lat.beta_exponents + m.ab_off + where;
+            b0 = v[0]; b1 = v[1];
+            fb0 = f[0]; fb1 = f[1];
         }
-    };
+    }
+};
 
-    for (int t = t0 + wave; t < tend; t += 4) {
-        RowData cur = {};
-        request(t, cur);
-        const size_t row_off = (static_cast<size_t>(t) * B + b) * A;
-        T* grow = grads + row_off;
-        if (t >= m.Tb || !runs) {
-            if (!kSparse)
-                for (int k = lane; k < A; k += 64) store_elem(grow, k, 0.0f);
-            continue;
-        }
-        const T* xrow = x + row_off;
-        const float* erow = emit_label + kLabelSlack + m.e_off + static_cast<size_t>(t) * m.e_pitch;   // sparse form only
-        // Mass share of every label state; the blank states share what is left of 1.
-        float zl = 0.0f;
+// The shares of the label positions base .. base + 127 in block `block` of the utterance: file(row, share0, share1) for
+// the lane's two positions, row = 0 .. 15 in some order, 0 outside [own_first, own_end).  Shares are without the
+// mantissa of 1 / p and times 2^kScaleLog2.  emissions(h, el0, el1): the lane's label emissions in chunk h of the block.
+// alpha's high dwords wait in LDS, s_alpha0 and s_alpha1 [row][kShareRow], each lane's in a slot of its own that is free
+// again when file is called for the row.  (In registers they cost 32 of them, and the loops over the chunks had to be
+// unrolled: code that runs once per wavefront comes out of memory no faster than data.)
+template <int kScaleLog2, typename Emissions, typename File>
+__device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at, const BlockEnds& ends, const double* __restrict__ eb,
+                                             const double packed_inverse_p, const int block,
+                                             const int own_first, const int own_end, unsigned* s_alpha0, unsigned* s_alpha1,
+                                             Emissions&& emissions, File&& file)
+{
+    const int lane = threadIdx.x & 63;
+    const int L = m.L, blocks = frame_blocks(m.Tb);
+    const int p0 = at.p0, p1 = at.p1;
+    const bool has0 = at.has0, has1 = at.has1;
+    const double skip0_one = at.skip0 ? 1.0 : 0.0, skip1_one = at.skip1 ? 1.0 : 0.0, skip2_one = at.skip2 ? 1.0 : 0.0;
+    float el0[kChunk], el1[kChunk];
+
+    // alpha
+    int alpha_frame0 = 0, alpha_frame1 = 0;              // of the block's two chunks
+    {
+        LanePairs s;
+        s.blank0 = block > 0 ? (has0 ? ends.a0.blank : 0.0) : (p0 == 0 ? 1.0 : 0.0);
+        s.label0 = block > 0 && has0 ? ends.a0.label : 0.0;
+        s.blank1 = block > 0 && has1 ? ends.a1.blank : 0.0;
+        s.label1 = block > 0 && has1 ? ends.a1.label : 0.0;
+        int prev_lo = 0, prev_hi = 0;
+        renew_pairs<false>(s, ends.fa0, ends.fa1);
+        alpha_frame0 = s.frame;
+#pragma unroll 1
+        for (int h = 0; h < 2; ++h) {
+            if (h) {
+                renew_pairs<false>(s, s.frame, s.frame);
+                alpha_frame1 = s.frame;
+            }
+            const double skip0_scale = skip0_one * s.scale;
+            emissions(h, el0, el1);
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-            const int j = u * 64 + lane;
-            if (j < L) {
-                const float gl = mass_share(cur.a[u], cur.ea[u], cur.b[u], cur.eb_[u], inverse_p, inverse_p_exponent);
-                g_label[s_lnk[j] & kLinkSlotMask] = gl;
-                zl += gl;
+            for (int q = 0; q < kChunk; ++q) {
+                const double prev = shift_up(s.label1, prev_lo, prev_hi), blank = eb[h * kChunk + q];
+                const double u0 = s.blank0 + s.label0, u1 = s.blank1 + s.label1;
+                const double n_blank1 = s.blank1 + s.label0, n_label1 = __builtin_fma(s.label0, skip1_one, u1);
+                const double n_label0 = __builtin_fma(prev, skip0_scale, u0), n_blank0 = __builtin_fma(prev, s.scale, s.blank0);
+                s.label0 = n_label0 * static_cast<double>(el0[q]);
+                s.label1 = n_label1 * static_cast<double>(el1[q]);
+                s.blank0 = n_blank0 * blank;
+                s.blank1 = n_blank1 * blank;
+                s_alpha0[(h * kChunk + q) * kShareRow + lane] = static_cast<unsigned>(__double2hiint(s.label0));
+                s_alpha1[(h * kChunk + q) * kShareRow + lane] = static_cast<unsigned>(__double2hiint(s.label1));
             }
         }
-        if (L > kAhead * 64) {
-            const LatticeRow row = rows_of.at(t);
-            for (int j0 = kAhead * 64; j0 < L; j0 += kAhead * 64) {
-                uint32_t a[kAhead], bb[kAhead];
-                int ea[kAhead], eb[kAhead];
+    }
+    // beta, and the shares
+    LanePairs s;
+    const bool last = block + 1 == blocks;
+    s.blank0 = last ? (p0 == L - 1 ? 1.0 : 0.0) : (has0 ? ends.b0.blank : 0.0);
+    s.label0 = !last && has0 ? ends.b0.label : 0.0;
+    s.blank1 = last ? (p1 == L - 1 ? 1.0 : 0.0) : (has1 ? ends.b1.blank : 0.0);
+    s.label1 = !last && has1 ? ends.b1.label : 0.0;
+    const bool own0 = p0 >= own_first && p0 < own_end, own1 = p1 >= own_first && p1 < own_end;
+    const int to_share = __double2loint(packed_inverse_p) + kScaleLog2;
+    int next_lo = 0, next_hi = 0;
+    renew_pairs<true>(s, ends.fb0, ends.fb1);
+#pragma unroll 1
+    for (int h = 1; h >= 0; --h) {
+        if (h == 0) renew_pairs<true>(s, s.frame, s.frame);
+        const int exponents = (h == 0 ? alpha_frame0 : alpha_frame1) + s.frame + to_share;
+        const int x0 = own0 ? exponents : kNoExponent, x1 = own1 ? exponents : kNoExponent;
+        const double skip2_scale = skip2_one * s.scale;
+        if (h == 0) emissions(h, el0, el1);              // (chunk 1's are still there)
+        unsigned alpha0[kChunk], alpha1[kChunk];
 #pragma unroll
-                for (int u = 0; u < kAhead; ++u) {
-                    const int j = j0 + u * 64 + lane;
-                    if (j < L) {
-                        a[u] = row.a[j];
-                        bb[u] = row.b[j];
-                        ea[u] = row.ea[j];
-                        eb[u] = row.eb[j];
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < kAhead; ++u) {
-                    const int j = j0 + u * 64 + lane;
-                    if (j < L) {
-                        const float gl = mass_share(a[u], ea[u], bb[u], eb[u], inverse_p, inverse_p_exponent);
-                        g_label[s_lnk[j] & kLinkSlotMask] = gl;
-                        zl += gl;
-                    }
-                }
-            }
+        for (int q = 0; q < kChunk; ++q) {
+            alpha0[q] = s_alpha0[(h * kChunk + q) * kShareRow + lane];
+            alpha1[q] = s_alpha1[(h * kChunk + q) * kShareRow + lane];
         }
-        const float zb = 1.0f - wave_sum(zl);
-        const float l2 = cur.l2;
-        if (!kSparse)
-            for (int k = lane; k < A; k += 64) occ[k] = 0.0f;
-        // LDS operations of one wavefront complete in program order; the fence only keeps the
-        // compiler from moving them across.
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        for (int j = lane; j < L; j += 64) {
-            const int link = s_lnk[j];
-            if (link < 0) {                   // first occurrence of its symbol: add up its run
-                const int first = link & kLinkSlotMask;
-                const int count = (link >> kLinkCountShift) & kLinkSlotMask;
-                float o = 0.0f;
-                // Eight independent reads at a time; slots past the run add an exact zero, so
-                // the order of summation is the run's own.
-                for (int i0 = 0; i0 < count; i0 += 8) {
-                    float g[8];
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) g[i] = g_label[min(first + i0 + i, L - 1)];
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) o += (i0 + i < count) ? g[i] : 0.0f;
-                }
-                const int c = s_lab[j];
-                if (kSparse) {
-                    // y of a label's symbol is its emission, which the softmax launch gathered
-                    // next to its neighbours': no scattered read of the activations.
-                    const int u = j >> 6;
-                    float e = 0.0f;
-#pragma unroll
-                    for (int k = 0; k < kAhead; ++k) e = (u == k) ? cur.e[k] : e;
-                    if (u >= kAhead) e = erow[j];
-                    store_elem(grow, c, emission_probability(e) - o);
-                } else {
-                    occ[c] = o;
-                }
-            }
+        for (int q = kChunk - 1; q >= 0; --q) {
+            const double next = shift_down(s.label0, next_lo, next_hi), blank = eb[h * kChunk + q];
+            const double u0 = s.blank0 + s.label0, u1 = s.blank1 + s.label1;
+            const double n_blank0 = s.blank0 + s.label1, n_label0 = __builtin_fma(s.label1, skip1_one, u0);
+            const double n_label1 = __builtin_fma(next, skip2_scale, u1), n_blank1 = __builtin_fma(next, s.scale, s.blank1);
+            file(h * kChunk + q, state_share(alpha0[q], n_label0, x0), state_share(alpha1[q], n_label1, x1));
+            s.label0 = n_label0 * static_cast<double>(el0[q]);
+            s.label1 = n_label1 * static_cast<double>(el1[q]);
+            s.blank0 = n_blank0 * blank;
+            s.blank1 = n_blank1 * blank;
         }
-        if (kSparse) {
-            if (lane == 0) store_elem(grow, blank, emission_probability(cur.eb) - zb);
-        } else {
-            if (lane == 0) occ[blank] = zb;
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            if (lane < A) store_elem(grow, lane, fast_exp2(fmaf(cur.x0, kLog2e, -l2)) - occ[lane]);
-            for (int k0 = 64 + lane; k0 < A; k0 += 8 * 64) {      // eight reads in flight
-                float v[8];
+    }
+}
+// The same from the words that log-domain chains have stored for every frame.
+template <int kScaleLog2, typename File>
+__device__ __forceinline__ void block_shares_log(const Utt& m, const LatticeOut& lat, const double packed_inverse_p, const int block,
+                                                 const int base, const int own_first, const int own_end, File&& file)
+{
+    const int p0 = base + 2 * static_cast<int>(threadIdx.x & 63), p1 = p0 + 1;
+    const bool own0 = p0 >= own_first && p0 < own_end, own1 = p1 >= own_first && p1 < own_end;
+    const int to_share = __double2loint(packed_inverse_p) + kScaleLog2;
+    const int64_t pitch = lattice_pitch(m.L);
+#pragma unroll 1
+    for (int r = 0; r < kBlockFrames; ++r) {
+        const int64_t at = m.ab_off + (static_cast<int64_t>(block) * kBlockFrames + r) * pitch + 1 + p0;
+        float share0 = 0.0f, share1 = 0.0f;
+        if (own0) share0 = word_share(lat.alpha[at], lat.beta[at], lat.alpha_exponents[at] + lat.beta_exponents[at] + to_share);
+        if (own1)
+            share1 = word_share(lat.alpha[at + 1], lat.beta[at + 1], lat.alpha_exponents[at + 1] + lat.beta_exponents[at + 1] + to_share);
+        file(r, share0, share1);
+    }
+}
+// Pieces of a label, and what wavefront `first` of `step` takes of them: for_piece(base, own_first, own_end).
+__host__ __device__ constexpr int label_pieces(int L)
+{
+    return L <= kPiecePositions ? (L > 0 ? 1 : 0) : (L - kPiecePositions + kPieceStep - 1) / kPieceStep + 1;
+}
+template <typename F>
+__device__ __forceinline__ void for_pieces(int L, int first, int step, F&& for_piece)
+{
+    const int pieces = label_pieces(L);
+    for (int i = first; i < pieces; i += step) {
+        const int base = i * kPieceStep;
+        for_piece(base, i == 0 ? 0 : base + kPieceHalo, i == pieces - 1 ? L : base + kPieceStep + kPieceHalo);
+    }
+}
+// Wavefronts that share a block in the narrow gradient kernel, one piece each up to four -- in launches of few blocks,
+// which last as long as one block takes (English minibatch: 18.8 -> 16.7 us; 512 utterances: 69 -> 83 us).
+constexpr int kShareBlocksMost = 8192;    // blocks times pieces: two rounds of what the chip holds
+__host__ __device__ constexpr int block_waves(int L) { return label_pieces(L) <= 1 ? 1 : (label_pieces(L) == 2 ? 2 : 4); }
+// The domains of an utterance's two chains as its chains published them (a word per direction).
+__device__ __forceinline__ bool in_log_domain(const int* __restrict__ domain, int b)
+{
+    return __builtin_amdgcn_readfirstlane(domain[2 * b] | domain[2 * b + 1]) != 0;
+}
+
+// Alphabets of at most 64 symbols (the English one has 29): a wavefront per block, or two or four that share the label's
+// pieces (block_waves).
+// The occupancy of a symbol is the sum of the shares of the label positions that carry it: a product of
+// the frames' shares [frame][position] with the label's zero-one matrix [position][symbol], and so work for
+// the matrix cores:
+//   - the shares go to LDS as [frame][position], in two halves (top 11 bits, next 11 bits) whose products share one
+//     accumulator: 22 bits and more of each share, fp32 sums in a fixed order.  They are carried times 2^12, which keeps
+//     the second half of a share of 2^-24 above fp16's subnormals; the matrix holds 2 for one;
+//   - A operand, per 32 positions: lane l holds frame l % 16, positions 8 (l / 16) .. + 7, one 16-byte
+//     read out of LDS (rows 272 bytes apart: no bank is asked twice);
+//   - B operand: lane l holds the same positions for symbol l % 16 (+ 16 per tile of symbols), made from the
+//     label's bytes in LDS; the blank's column is 1 everywhere, so that it receives the sum of all shares, and
+//     the blank's occupancy is what is left of 1.
+constexpr int kShareScaleLog2 = 12;
+// Bytes of a label staged in LDS: whole pieces of 32 positions, kNoSymbol past the label's end.
+constexpr int kNoSymbol = 0x40;
+__host__ __device__ constexpr int tile_label_ints(int L) { return (L + 31) / 32 * 8; }
+// The block's emissions in LDS: [chunk][symbol][frame], a chunk of a symbol in a row of 12 floats (eight and padding:
+// lanes that read different symbols meet in few banks), one more row of zeros for lanes without a position.
+constexpr int kEmissionRow = 12;
+__host__ __device__ constexpr int tile_emission_ints(int tiles) { return (2 * 16 * tiles + 1) * kEmissionRow; }
+// LDS of one wavefront.
+__host__ __device__ constexpr int tile_lds_ints(int Lmax, int tiles) { return kShareInts + tile_emission_ints(tiles) + tile_label_ints(Lmax); }
+__device__ __forceinline__ void stage_label_bytes(unsigned* s_label, const int* __restrict__ labels, int L)
+{
+    for (int w = threadIdx.x & 63; w < tile_label_ints(L); w += 64) {
+        unsigned c[4];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int k = k0 + u * 64;
-                    v[u] = (k < A) ? load_elem(xrow, k) : 0.0f;
-                }
+        for (int i = 0; i < 4; ++i) c[i] = labels[min(4 * w + i, L - 1)];      // (no branch: the four travel together)
+        unsigned word = 0;
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int k = k0 + u * 64;
-                    if (k < A) store_elem(grow, k, fast_exp2(fmaf(v[u], kLog2e, -l2)) - occ[k]);
-                }
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        for (int i = 0; i < 4; ++i) word |= (4 * w + i < L ? c[i] : static_cast<unsigned>(kNoSymbol)) << (8 * i);
+        s_label[w] = word;
     }
 }
 
-// Alphabets of at most 64 symbols (the English one has 29): lane k of a row's wavefront is
-// symbol k.  The shares, which sit in slot order (the positions of a symbol next to each other),
-// are turned into running sums with wavefront scans; a symbol's occupancy is then the
-// difference of the entries at the two ends of its run (start and length per symbol are put
-// into LDS once per workgroup), the blank's is 1 minus the total, and lane k writes
-// grad[k] = y_k - occupancy_k straight away: no loop over a run, no scan over the label for first
-// occurrences, no occupancy array per row.  The order of the additions is fixed, so results
-// repeat bitwise.
-template <typename T, bool kStreaming>
-__global__ __launch_bounds__(kRowThreads)
-void ctc_gradient_narrow_kernel(const T* __restrict__ x, T* __restrict__ grads,
-                                const Utt* __restrict__ meta, const int* __restrict__ labels,
-                                const int* __restrict__ links, const float* __restrict__ lse,
-                                const LatticeOut lat,
-                                const double* __restrict__ logp, const int* __restrict__ chain_err,
-                                float* __restrict__ costs, int Tt, int B, int A, int blank, int Lmax,
-                                int rows_per_group, const int* __restrict__ only_marked,
-                                const int* __restrict__ domain)
+template <int kTiles>
+__device__ __forceinline__ void share_product(float4v (&acc)[kTiles], const unsigned* s_hi, const unsigned* s_lo,
+                                              const unsigned* s_label, int base, int L, const unsigned (&symbol)[kTiles],
+                                              const unsigned (&mask)[kTiles])
 {
-    // (what the rows need of the utterance is asked for in one go: each of these is a trip to memory)
-    const Utt m = meta[blockIdx.y];
-    const int log_domains = chain_domains<false>(domain, blockIdx.y);
-    const int chain_gave_up = chain_err[blockIdx.y];
-    // After a lattice launch whose workers have written the gradient: only the utterances they left.
-    if (only_marked && only_marked[blockIdx.y] == 0) return;
-    extern __shared__ int g_lds[];
-    int* s_slot = g_lds;                         // [Lmax]  slot of each label position
-    int* s_start = g_lds + Lmax;                 // [64]    first slot of each symbol's run
-    int* s_count = s_start + 64;                 // [64]    length of the run (0: symbol not in the label)
-    const int tid = threadIdx.x, wave = tid >> 6;
-    float* g_slot = reinterpret_cast<float*>(s_count + 64) + wave * (Lmax + 1);   // mass shares in slot order
-    const int b = blockIdx.y, t0 = blockIdx.x * rows_per_group;
-    if (t0 == 0 && tid == 0 && chain_gave_up != 0) costs[b] = __uint_as_float(0x7FC00000u);
-    const bool runs = (m.flags & kUttRuns) != 0;
-    const int L = m.L;
-    // The grouping of the label's positions, staged while the first rows' lattice values are on their way.
-    auto stage = [&]() {
-        if (!(runs && t0 < m.Tb)) return;               // (the same for the whole workgroup)
-        if (tid < 64) {
-            s_start[tid] = 0;
-            s_count[tid] = 0;
+    const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+    for (int k0 = base; k0 < min(L, base + kPiecePositions); k0 += 32) {
+        const int at = c * kShareRow + (k0 - base) / 2 + 4 * g;
+        const half8 hi = __builtin_bit_cast(half8, *reinterpret_cast<const uint4v*>(s_hi + at));
+        const half8 lo = __builtin_bit_cast(half8, *reinterpret_cast<const uint4v*>(s_lo + at));
+        const uint2v word = *reinterpret_cast<const uint2v*>(s_label + k0 / 4 + 2 * g);
+#pragma unroll
+        for (int n = 0; n < kTiles; ++n) {
+            uint4v one;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const unsigned differs = ((word[h] & mask[n]) ^ symbol[n]) + 0x7F7F7F7Fu;      // bit 7 of a byte: not this symbol
+                const unsigned match = (~differs & 0x80808080u) >> 1;                          // 0x40 where it is: the top byte of fp16 2.0
+                one[2 * h] = __builtin_amdgcn_perm(match, 0u, 0x05000400u);                    // bytes 0 and 1 to the halves' top bytes
+                one[2 * h + 1] = __builtin_amdgcn_perm(match, 0u, 0x07000600u);
+            }
+            acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hi, __builtin_bit_cast(half8, one), acc[n], 0, 0, 0);
+            acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(lo, __builtin_bit_cast(half8, one), acc[n], 0, 0, 0);
         }
+    }
+}
+
+// grid (ceil(blocks of T / (4 / wavefronts per block)), B); dynamic LDS 4 tile_lds_ints(Lmax, kTiles) ints.  kTiles: tiles of 16 symbols.
+template <typename T, int kTiles>
+__global__ __launch_bounds__(kRowThreads)
+void ctc_gradient_narrow_kernel(T* __restrict__ grads, const Utt* __restrict__ meta, const int* __restrict__ labels,
+                                const double* __restrict__ emit_blank64, const float* __restrict__ emit_label,
+                                const LatticeOut lat, const double* __restrict__ logp, const int* __restrict__ chain_err,
+                                float* __restrict__ costs, int Tt, int B, int A, int blank, int Lmax,
+                                const int* __restrict__ domain, const bool share_blocks)
+{
+    extern __shared__ uint4v tile_lds[];
+    const int b = blockIdx.y, lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const Utt m = uniform_record(meta[b]);
+    const bool log_domain = in_log_domain(domain, b);
+    const int chain_gave_up = chain_err[b];
+    const double packed_inverse_p = logp[b];
+    const int L = m.L, sharing = share_blocks ? block_waves(L) : 1, part = wave & (sharing - 1);
+    const int block = static_cast<int>(blockIdx.x) * (kRowThreads / 64 / sharing) + wave / sharing, t0 = block * kBlockFrames;
+    if (blockIdx.x == 0 && threadIdx.x == 0 && chain_gave_up != 0) costs[b] = __uint_as_float(0x7FC00000u);
+    const bool has_rows = (m.flags & kUttRuns) && t0 < m.Tb;
+    if (!has_rows && part == 0) {
+        // no lattice: zeros
+#pragma unroll 4
+        for (int r = 0; r < kBlockFrames; ++r)
+            if (t0 + r < Tt && lane < A) store_elem(grads + (static_cast<size_t>(t0 + r) * B + b) * A, lane, 0.0f);
+    }
+    if (!has_rows) {
+        if (sharing > 1) __syncthreads();                // (the one below)
+        return;
+    }
+    unsigned* const s_hi = reinterpret_cast<unsigned*>(tile_lds) + wave * tile_lds_ints(Lmax, kTiles);
+    unsigned* const s_lo = s_hi + kBlockFrames * kShareRow;
+    float* const s_emit = reinterpret_cast<float*>(s_hi + kShareInts);
+    unsigned* const s_label = s_hi + kShareInts + tile_emission_ints(kTiles);
+    // Everything that comes from memory is asked for here, before any of it is used.
+    const float4* const emit_in = reinterpret_cast<const float4*>(emit_label + emission_at(m.e_off, A, t0, 0));
+    float4 emit[kTiles];                                 // the block's 16 A emissions: up to 4 A vectors, 64 lanes
+#pragma unroll
+    for (int i = 0; i < kTiles; ++i) emit[i] = emit_in[min(64 * i + lane, 4 * A - 1)];
+    // (an empty label has no string to look at, and the caller's array may be empty)
+    const int first_base = part * kPieceStep;
+    const LaneLabels first_labels(L > 0 ? labels + m.lab_off : &meta[b].L, max(L, 1), first_base);
+    BlockEnds ends(m, lat, first_labels.p0, block);
+    __builtin_amdgcn_sched_barrier(0);
+    stage_label_bytes(s_label, labels + m.lab_off, L);
+#pragma unroll
+    for (int i = 0; i < kTiles; ++i) {
+        const int v = 64 * i + lane;                     // vector v: half v % 2 of row v / 2
+        if (v < 4 * A) *reinterpret_cast<float4*>(s_emit + (v >> 1) * kEmissionRow + (v & 1) * 4) = emit[i];
+    }
+    if (lane < 8) s_emit[2 * A * kEmissionRow + lane] = 0.0f;
+    const double* const eb = emit_blank64 + blank_emission_offset(m, 2 * block);
+    // the symbol of this lane's column, per tile of symbols: label bytes are compared as (byte & mask) ^ symbol == 0
+    unsigned symbol[kTiles], mask[kTiles];
+    float4v acc[kTiles];
+#pragma unroll
+    for (int n = 0; n < kTiles; ++n) {
+        const int k = 16 * n + c;
+        symbol[n] = k == blank ? 0u : static_cast<unsigned>(k) * 0x01010101u;
+        mask[n] = k == blank ? static_cast<unsigned>(kNoSymbol) * 0x01010101u : 0x7F7F7F7Fu;
+        acc[n] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+    for_pieces(L, part, sharing, [&](int base, int own_first, int own_end) {
+        auto file = [&](int row, float x0, float x1) {
+            const half2_raw hi = __builtin_amdgcn_cvt_pkrtz(x0, x1);
+            const half2_raw lo = __builtin_amdgcn_cvt_pkrtz(minus_low_half(x0, hi), minus_high_half(x1, hi));
+            s_hi[row * kShareRow + lane] = __builtin_bit_cast(unsigned, hi);
+            s_lo[row * kShareRow + lane] = __builtin_bit_cast(unsigned, lo);
+        };
+        if (log_domain) {
+            block_shares_log<kShareScaleLog2>(m, lat, packed_inverse_p, block, base, own_first, own_end, file);
+        } else {
+            LaneLabels at = first_labels;
+            if (base != first_base) {
+                at = LaneLabels(labels + m.lab_off, L, base);
+                ends = BlockEnds(m, lat, at.p0, block);
+            }
+            auto emissions = [&](int h, float (&el0)[kChunk], float (&el1)[kChunk]) {
+                auto row = [&](bool has, int symbol, float (&el)[kChunk]) {
+                    const float4* v = reinterpret_cast<const float4*>(s_emit + (has ? h * A + symbol : 2 * A) * kEmissionRow);
+                    const float4 x = v[0], y = v[1];
+                    el[0] = x.x; el[1] = x.y; el[2] = x.z; el[3] = x.w;
+                    el[4] = y.x; el[5] = y.y; el[6] = y.z; el[7] = y.w;
+                };
+                row(at.has0, at.symbol0, el0);
+                row(at.has1, at.symbol1, el1);
+            };
+            block_shares<kShareScaleLog2>(m, at, ends, eb, packed_inverse_p, block, own_first, own_end, s_hi, s_lo, emissions, file);
+        }
+        // LDS operations of one wavefront complete in program order; the fences only keep the
+        // compiler from moving them across.
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        share_product<kTiles>(acc, s_hi, s_lo, s_label, base, L, symbol, mask);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    });
+    if (sharing > 1) {
+        // the first of the wavefronts adds up what the others have, in their order
+        float4v* const s_acc = reinterpret_cast<float4v*>(s_hi);
+        static_assert(kTiles * 64 * 4 <= kShareInts, "the accumulators fit where the shares were");
+        if (part > 0)
+#pragma unroll
+            for (int n = 0; n < kTiles; ++n) s_acc[n * 64 + lane] = acc[n];
         __syncthreads();
-        for (int j = tid; j < L; j += kRowThreads) {
+        if (part > 0) return;
+        for (int i = 1; i < sharing; ++i) {
+            const float4v* const theirs = reinterpret_cast<const float4v*>(s_hi + i * tile_lds_ints(Lmax, kTiles));
+#pragma unroll
+            for (int n = 0; n < kTiles; ++n) acc[n] += theirs[n * 64 + lane];
+        }
+    }
+    // Result: lane l holds symbol 16 n + l % 16 of frames 4 (l / 16) .. + 3; y is the emission.
+    const int tr = t0 + 4 * g;
+    const float scale = static_cast<float>(packed_inverse_p) * (0.5f / (1 << kShareScaleLog2));
+#pragma unroll
+    for (int n = 0; n < kTiles; ++n) {
+        const int k = 16 * n + c;
+        if (k >= A) continue;
+        T* out = grads + (static_cast<size_t>(tr) * B + b) * A + k;
+        const float4 y = *reinterpret_cast<const float4*>(s_emit + ((g >> 1) * A + k) * kEmissionRow + (g & 1) * 4);
+        const float yv[4] = {y.x, y.y, y.z, y.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float occupancy = acc[n][i] * scale;
+            const float v = emission_softmax(yv[i]) - (k == blank ? 1.0f - occupancy : occupancy);
+            if (tr + i < Tt) store_elem(out, static_cast<size_t>(i) * B * A, tr + i < m.Tb ? v : 0.0f);
+        }
+    }
+}
+
+// Larger alphabets: the softmax launch has written y (and zeros); here the columns of the label's symbols and the
+// blank's are corrected.  A wavefront per block; the shares go to LDS in slot order (the positions of a symbol next to
+// each other, setup_role), and the lane of a symbol's first occurrence adds up its run: one writer per symbol and a
+// fixed order.  `rows_per_pass` frames of a block at a time (16, or 8 where the longest label's shares of 16 frames do not
+// fit).  grid (blocks of T, B); dynamic LDS rows_per_pass * (Lmax + 1) floats.
+template <typename T>
+__global__ __launch_bounds__(64)
+void ctc_gradient_wide_kernel(T* __restrict__ grads, const Utt* __restrict__ meta, const int* __restrict__ labels,
+                              const int* __restrict__ links, const float* __restrict__ emit_blank,
+                              const double* __restrict__ emit_blank64, const float* __restrict__ emit_label,
+                              const LatticeOut lat, const double* __restrict__ logp, const int* __restrict__ chain_err,
+                              float* __restrict__ costs, int B, int A, int blank, int rows_per_pass,
+                              const int* __restrict__ domain)
+{
+    __shared__ unsigned s_alpha[kShareInts];
+    extern __shared__ float s_share[];                   // [rows_per_pass][L + 1]
+    const int b = blockIdx.y, lane = threadIdx.x, block = blockIdx.x, t0 = block * kBlockFrames;
+    const Utt m = uniform_record(meta[b]);
+    if (t0 == 0 && lane == 0 && chain_err[b] != 0) costs[b] = __uint_as_float(0x7FC00000u);
+    if (!(m.flags & kUttRuns) || t0 >= m.Tb) return;
+    const bool log_domain = in_log_domain(domain, b);
+    const double packed_inverse_p = logp[b];
+    const float inverse_p = static_cast<float>(packed_inverse_p);
+    const int L = m.L, row_pitch = L + 1;
+    const double* const eb = emit_blank64 + blank_emission_offset(m, 2 * block);
+    for (int first = 0; first < kBlockFrames; first += rows_per_pass) {
+        for_pieces(L, 0, 1, [&](int base, int own_first, int own_end) {
+            const int p0 = base + 2 * lane, p1 = p0 + 1;
+            const bool own0 = p0 >= own_first && p0 < own_end, own1 = p1 >= own_first && p1 < own_end;
+            const int slot0 = own0 ? links[m.lab_off + p0] & kLinkSlotMask : 0, slot1 = own1 ? links[m.lab_off + p1] & kLinkSlotMask : 0;
+            auto file = [&](int row, float x0, float x1) {
+                const int r = row - first;
+                if (r < 0 || r >= rows_per_pass) return;
+                if (own0) s_share[r * row_pitch + slot0] = x0 * inverse_p;
+                if (own1) s_share[r * row_pitch + slot1] = x1 * inverse_p;
+            };
+            if (log_domain) block_shares_log<0>(m, lat, packed_inverse_p, block, base, own_first, own_end, file);
+            else {
+                const LaneLabels at(labels + m.lab_off, L, base);
+                const float* e0 = emit_label + label_emission_offset(m, at.has0, 0, at.p0, 2 * block, kZeroEmission);
+                const float* e1 = emit_label + label_emission_offset(m, at.has1, 0, at.p1, 2 * block, kZeroEmission);
+                const int64_t step0 = label_emission_step(m, at.has0, false), step1 = label_emission_step(m, at.has1, false);
+                auto emissions = [&](int h, float (&el0)[kChunk], float (&el1)[kChunk]) {
+                    const float *q0 = e0 + h * step0, *q1 = e1 + h * step1;
+                    fetch_chunk<false>(q0, 0, el0);
+                    fetch_chunk<false>(q1, 0, el1);
+                };
+                block_shares<0>(m, at, BlockEnds(m, lat, at.p0, block), eb, packed_inverse_p, block, own_first, own_end, s_alpha,
+                                s_alpha + kBlockFrames * kShareRow, emissions, file);
+            }
+        });
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const int rows = min(rows_per_pass, m.Tb - t0 - first);
+        for (int j = lane; j < L; j += 64) {
             const int link = links[m.lab_off + j];
-            const int c = labels[m.lab_off + j];         // (asked for with the link, not after it)
-            s_slot[j] = link & kLinkSlotMask;
-            if (link < 0) {
-                s_start[c] = link & kLinkSlotMask;
-                s_count[c] = (link >> kLinkCountShift) & kLinkSlotMask;
+            if (link >= 0) continue;                     // (not the first occurrence of its symbol)
+            const int slot = link & kLinkSlotMask, count = (link >> kLinkCountShift) & kLinkSlotMask;
+            T* out = grads + (static_cast<size_t>(t0 + first) * B + b) * A + labels[m.lab_off + j];
+            for (int r0 = 0; r0 < rows; r0 += 4) {
+                // y of a label's symbol is its emission, which the softmax launch gathered
+                const float4 e = *reinterpret_cast<const float4*>(emit_label + emission_at(m.e_off, L, t0 + first + r0, j));
+                const float y[4] = {e.x, e.y, e.z, e.w};
+                float o[4] = {};
+                for (int i = 0; i < count; ++i)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) o[r] += s_share[(r0 + r) * row_pitch + slot + i];
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (r0 + r < rows) store_elem(out, static_cast<size_t>(r0 + r) * B * A, emission_softmax(y[r]) - o[r]);
             }
         }
-        __syncthreads();
-    };
-    narrow_gradient_rows<T, kStreaming, false>(x, grads, m, b, lat, lse, logp, runs ? log_domains : 0, Tt, B, A, blank, t0 + wave, 4,
-                                        min(t0 + rows_per_group, Tt), s_slot, s_start, s_count, g_slot, stage);
+        // the blank: what the label states leave of 1, four lanes per row
+        const int row = lane >> 2, q = lane & 3;
+        float sum = 0.0f;
+        if (row < rows)
+            for (int i = q; i < L; i += 4) sum += s_share[row * row_pitch + i];
+        sum = quad_sum(sum);
+        if (row < rows && q == 0) {
+            const int t = t0 + first + row;
+            store_elem(grads + (static_cast<size_t>(t) * B + b) * A, blank,
+                       emission_softmax(emit_blank[kBlankSlack + m.f_off + t]) - (1.0f - sum));
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
 }
 
 template <typename F>
@@ -3238,14 +2848,14 @@ static LatticeOut lattice_blocks(const Launch& p)
 
 int launch_setup(const Launch& p, void* stream)
 {
-    // (the workers' task list only if the lattice launch has workers; the byte labels after it are read in place)
-    const int words = static_cast<int>((p.n_tasks > 0 ? p.lay.labels8 : p.lay.tasks) / 4);
+    // (the byte labels after the words are read in place)
+    const int words = static_cast<int>(p.lay.labels8 / 4);
     const unsigned char* labels8 = p.A <= kByteLabelsMaxA ? static_cast<const unsigned char*>(p.host_image) + p.lay.labels8 : nullptr;
     return checked_launch([&] {
         hipLaunchKernelGGL(ctc_upload_kernel, dim3((words + kRowThreads - 1) / kRowThreads), dim3(kRowThreads),
                            0, static_cast<hipStream_t>(stream), static_cast<const int*>(p.host_image),
                            reinterpret_cast<int*>(p.ws), words, static_cast<int>(p.lay.labels / 4),
-                           static_cast<int>(p.lay.tasks / 4), labels8);
+                           static_cast<int>(p.lay.labels8 / 4), labels8);
     });
 }
 
@@ -3264,114 +2874,93 @@ int launch_softmax(const Launch& p, void* stream)
 {
     auto* meta = reinterpret_cast<Utt*>(p.ws + p.lay.meta);
     const int* labels = p.labels;
-    auto* lse = reinterpret_cast<float*>(p.ws + p.lay.lse);
     auto* emit_blank = reinterpret_cast<float*>(p.ws + p.lay.emit_blank);
     auto* emit_label = reinterpret_cast<float*>(p.ws + p.lay.emit_label);
     const SetupArgs sa{reinterpret_cast<int*>(p.ws + p.lay.links), p.costs,
                        reinterpret_cast<int*>(p.ws + p.lay.chain_err),
-                       reinterpret_cast<int*>(p.ws + p.lay.done), reinterpret_cast<int*>(p.ws + p.lay.where),
-                       reinterpret_cast<int*>(p.ws + p.lay.leftover), emit_label,
+                       emit_label,
                        reinterpret_cast<double*>(p.ws + p.lay.emit_blank64),
                        p.folded ? nullptr : p.host_flag, p.host_flag_value, p.mode == Mode::kBest,
-                       // few utterances: spread each one's grouping over several workgroups (its
-                       // latency counts); many: one workgroup each keeps the chip busy already
-                       (p.B >= 256 ? 1 : std::max(1, (p.max_label + 63) / 64)) +
-                           // (device-resident metadata, narrow alphabets: one more, which builds the utterance's record)
-                           (p.folded && p.dev_label_lengths ? 1 : 0)};
+                       // gathered emissions and few utterances: spread the grouping of each one's label positions over
+                       // several workgroups (its latency counts); many: one workgroup each keeps the chip busy already
+                       p.A <= kDirectMaxA || p.B >= 256 ? 1 : std::max(1, (p.max_label + 63) / 64)};
     const dim3 block(kRowThreads);
     auto s = static_cast<hipStream_t>(stream);
     const bool f32 = p.dtype == CTC_DTYPE_F32;
     return checked_launch([&] {
         if (p.A <= kDirectMaxA && p.folded) {
             // the smallest alphabets, host metadata: the launch reads the pinned image itself
-            const dim3 grid((p.T + kFlagFrames - 1) / kFlagFrames + sa.parts + (p.device_tasks ? 1 : 0), p.B);
+            const dim3 grid((p.T + kFlagFrames - 1) / kFlagFrames + sa.parts, p.B);
             const size_t lds = static_cast<size_t>(kFlagFrames) * p.A * sizeof(float);
             const NarrowImage image{static_cast<const int*>(p.host_image), static_cast<int>(p.lay.labels / 4),
-                                    static_cast<int>(p.lay.tasks / 4), static_cast<int>(p.lay.labels8 / 4), p.lay.labels8,
+                                    static_cast<int>(p.lay.labels8 / 4), static_cast<int>(p.lay.labels8 / 4), p.lay.labels8,
                                     reinterpret_cast<int*>(p.ws + p.lay.labels)};
             auto* row_flags = reinterpret_cast<int*>(p.ws + p.lay.row_flags);
             NarrowArgs args;
             NarrowRows& rows_of = args.rows;
             NarrowDevice dv{};
-            if (p.dev_label_lengths) args.plans = plans().table[p.crowded][emission_layout(p.A) == kEmitSymbolMajor];
+            if (p.dev_label_lengths) args.plans = plans().table[p.crowded][emission_layout(p.A) == kEmitSymbols];
             if (p.dev_label_lengths)
                 dv = NarrowDevice{p.labels, p.dev_label_lengths, p.dev_input_lengths, meta, reinterpret_cast<int*>(p.ws + p.lay.order),
                                   reinterpret_cast<int*>(p.ws + p.lay.status), p.max_label, p.poll_budget,
                                   p.mode == Mode::kGrad ? 2 : 1, p.crowded, p.needs_barrier,
-                                  p.device_tasks ? reinterpret_cast<int*>(p.ws + p.lay.tasks) : nullptr, p.share_percent,
                                   p.n_cu % kChainBlock == 0 ? p.n_cu : 0};
             const Utt* records = static_cast<const Utt*>(p.host_image);      // (the host reads its own image)
             for (int b = 0; records && b < p.B; ++b) {
-                rows_of.frames[b] = records[b].Tb | ((records[b].flags & kUttRuns) ? kRowsRun : 0) |
-                                    ((records[b].flags & kUttGradientLater) ? kRowsGradientLater : 0);
+                rows_of.frames[b] = records[b].Tb | ((records[b].flags & kUttRuns) ? kRowsRun : 0);
                 rows_of.frames_before[b] = records[b].f_off;
                 rows_of.label_length[b] = records[b].L;
                 rows_of.labels_before[b] = records[b].lab_off;
             }
             if (f32)
                 hipLaunchKernelGGL(ctc_softmax_narrow_kernel<float>, grid, block, lds, s, static_cast<const float*>(p.x),
-                                   image, reinterpret_cast<int*>(p.ws), lse, emit_blank, emit_label, row_flags, sa,
+                                   image, reinterpret_cast<int*>(p.ws), emit_blank, emit_label, row_flags, sa,
                                    args, dv, p.T, p.B, p.A, p.blank);
             else
                 hipLaunchKernelGGL(ctc_softmax_narrow_kernel<bf16_t>, grid, block, lds, s, static_cast<const bf16_t*>(p.x),
-                                   image, reinterpret_cast<int*>(p.ws), lse, emit_blank, emit_label, row_flags, sa,
+                                   image, reinterpret_cast<int*>(p.ws), emit_blank, emit_label, row_flags, sa,
                                    args, dv, p.T, p.B, p.A, p.blank);
-        } else if (p.A <= kDirectMaxA) {
-            // the smallest alphabets: 64 frames per workgroup, four lanes per frame, so that a
-            // workgroup has several kilobytes under way
-            const dim3 grid((p.T + 63) / 64 + sa.parts, p.B);
-            const size_t lds = static_cast<size_t>(64) * p.A * sizeof(float);
-            if (f32)
-                hipLaunchKernelGGL((ctc_softmax_rows_kernel<float, 64>), grid, block, lds, s,
-                                   static_cast<const float*>(p.x), meta, labels, lse, emit_blank,
-                                   emit_label, sa, p.T, p.B, p.A, p.blank);
-            else
-                hipLaunchKernelGGL((ctc_softmax_rows_kernel<bf16_t, 64>), grid, block, lds, s,
-                                   static_cast<const bf16_t*>(p.x), meta, labels, lse, emit_blank,
-                                   emit_label, sa, p.T, p.B, p.A, p.blank);
-        } else if (p.A <= 512) {
-            const dim3 grid((p.T + 15) / 16 + sa.parts, p.B);
-            const size_t lds = static_cast<size_t>(16) * p.A * sizeof(float);
-            if (f32)
-                hipLaunchKernelGGL((ctc_softmax_rows_kernel<float, 16>), grid, block, lds, s,
-                                   static_cast<const float*>(p.x), meta, labels, lse, emit_blank,
-                                   emit_label, sa, p.T, p.B, p.A, p.blank);
-            else
-                hipLaunchKernelGGL((ctc_softmax_rows_kernel<bf16_t, 16>), grid, block, lds, s,
-                                   static_cast<const bf16_t*>(p.x), meta, labels, lse, emit_blank,
-                                   emit_label, sa, p.T, p.B, p.A, p.blank);
         } else if (p.A <= kRowsMaxA) {
-            const dim3 grid((p.T + 3) / 4 + sa.parts, p.B);
-            const size_t lds = static_cast<size_t>(4) * p.A * sizeof(float);
-            if (f32)
-                hipLaunchKernelGGL((ctc_softmax_rows_kernel<float, 4>), grid, block, lds, s,
-                                   static_cast<const float*>(p.x), meta, labels, lse, emit_blank,
-                                   emit_label, sa, p.T, p.B, p.A, p.blank);
-            else
-                hipLaunchKernelGGL((ctc_softmax_rows_kernel<bf16_t, 4>), grid, block, lds, s,
-                                   static_cast<const bf16_t*>(p.x), meta, labels, lse, emit_blank,
-                                   emit_label, sa, p.T, p.B, p.A, p.blank);
+            // frames per workgroup: 64 for the smallest alphabets (so that a workgroup has several kilobytes under way), 16
+            // and 4 for the larger ones (its rows sit in LDS)
+            const int rows = p.A <= kDirectMaxA ? 64 : (p.A <= 512 ? 16 : 4);
+            const dim3 grid((static_cast<unsigned>(padded_frames(p.T)) + rows - 1) / rows + sa.parts, p.B);
+            const size_t lds = static_cast<size_t>(rows) * p.A * sizeof(float);
+#define CTC_LAUNCH_ROWS(TYPE, ROWS)                                                                \
+    hipLaunchKernelGGL((ctc_softmax_rows_kernel<TYPE, ROWS>), grid, block, lds, s,                 \
+                       static_cast<const TYPE*>(p.x), static_cast<TYPE*>(p.grads), meta, labels,   \
+                       emit_blank, emit_label, sa, p.T, p.B, p.A, p.blank)
+            if (f32) {
+                if (rows == 64) CTC_LAUNCH_ROWS(float, 64);
+                else if (rows == 16) CTC_LAUNCH_ROWS(float, 16);
+                else CTC_LAUNCH_ROWS(float, 4);
+            } else {
+                if (rows == 64) CTC_LAUNCH_ROWS(bf16_t, 64);
+                else if (rows == 16) CTC_LAUNCH_ROWS(bf16_t, 16);
+                else CTC_LAUNCH_ROWS(bf16_t, 4);
+            }
+#undef CTC_LAUNCH_ROWS
         } else if (vector_ok(p) && p.A <= kWideMaxA && p.T + 1 <= kMaxBatch) {
             // (frames index the second grid dimension here, which ends at 65535; longer tensors take
             // the scalar kernel below, whose second dimension is the utterance)
             const dim3 grid(p.B, p.T + 1);
             if (f32)
                 hipLaunchKernelGGL(ctc_softmax_wide_kernel<float>, grid, block, 0, s,
-                                   static_cast<const float*>(p.x), static_cast<float*>(p.grads), meta, labels, lse, emit_blank,
+                                   static_cast<const float*>(p.x), static_cast<float*>(p.grads), meta, labels, emit_blank,
                                    emit_label, sa, p.T, p.B, p.A, p.blank);
             else
                 hipLaunchKernelGGL(ctc_softmax_wide_kernel<bf16_t>, grid, block, 0, s,
-                                   static_cast<const bf16_t*>(p.x), static_cast<bf16_t*>(p.grads), meta, labels, lse, emit_blank,
+                                   static_cast<const bf16_t*>(p.x), static_cast<bf16_t*>(p.grads), meta, labels, emit_blank,
                                    emit_label, sa, p.T, p.B, p.A, p.blank);
         } else {
             const dim3 grid(p.T + 1, p.B);
             if (f32)
                 hipLaunchKernelGGL(ctc_softmax_kernel<float>, grid, block, 0, s,
-                                   static_cast<const float*>(p.x), static_cast<float*>(p.grads), meta, labels, lse, emit_blank,
+                                   static_cast<const float*>(p.x), static_cast<float*>(p.grads), meta, labels, emit_blank,
                                    emit_label, sa, p.T, p.B, p.A, p.blank);
             else
                 hipLaunchKernelGGL(ctc_softmax_kernel<bf16_t>, grid, block, 0, s,
-                                   static_cast<const bf16_t*>(p.x), static_cast<bf16_t*>(p.grads), meta, labels, lse, emit_blank,
+                                   static_cast<const bf16_t*>(p.x), static_cast<bf16_t*>(p.grads), meta, labels, emit_blank,
                                    emit_label, sa, p.T, p.B, p.A, p.blank);
         }
     });
@@ -3390,9 +2979,9 @@ int launch_lattice(const Launch& p, void* stream)
     const LatticeOut lat = lattice_blocks(p);
     auto* logp = reinterpret_cast<double*>(p.ws + p.lay.logp);
     auto* chain_err = reinterpret_cast<int*>(p.ws + p.lay.chain_err);
-    size_t lds_bytes = (p.max_waves > 1 && !p.needs_barrier) ? halo_lds_bytes(p.max_waves) : 0;
-    int n_groups = std::max(p.n_chains, 1);
-    WorkerArgs wk{};
+    const size_t lds_bytes = (p.max_waves > 1 && !p.needs_barrier) ? halo_lds_bytes(p.max_waves) : 0;
+    const int n_groups = std::max(p.n_chains, 1);
+    LaunchWords wk{};
     wk.row_flags = p.folded ? reinterpret_cast<const int*>(p.ws + p.lay.row_flags) : nullptr;
     wk.flag_blocks = (p.T + kFlagFrames - 1) / kFlagFrames;
     wk.domain = reinterpret_cast<int*>(p.ws + p.lay.domain);
@@ -3403,54 +2992,17 @@ int launch_lattice(const Launch& p, void* stream)
         wk.status_out = p.dev_status;
         wk.status_count = p.B;
     }
-    // Workers (kTaskRows): as many workgroups per idle compute unit as make kWorkerWavesPerCu
-    // wavefronts, in rounds of n_cu workgroups whose first n_chains leave at once; their LDS holds
-    // the list's table and a piece per wavefront.
-    if (p.n_tasks > 0) {
-        const size_t table = kXcds + 1 + 3 * static_cast<size_t>(p.n_task_entries) + 1, piece = 2 * static_cast<size_t>(p.max_label) + 129;
-        lds_bytes = std::min<size_t>(std::max(lds_bytes, (table + p.max_waves * piece) * 4), 64 << 10);
-        const int waves = static_cast<int>(std::min<size_t>(p.max_waves, (lds_bytes / 4 - table) / piece));
-        const int idle = p.n_cu - p.n_chains;
-        const int per_cu = std::max(1, kWorkerWavesPerCu / p.max_waves);
-        // no more workgroups than give every working wavefront a task
-        const int rounds = std::max(1, std::min(per_cu, (p.n_tasks + idle * waves - 1) / (idle * waves)));
-        n_groups = p.n_cu * rounds;
-        wk.x = p.x;
-        wk.grads = p.grads;
-        wk.links = reinterpret_cast<const int*>(p.ws + p.lay.links);
-        wk.lse = reinterpret_cast<const float*>(p.ws + p.lay.lse);
-        wk.tasks = reinterpret_cast<const int*>(p.ws + p.lay.tasks);
-        wk.done = reinterpret_cast<int*>(p.ws + p.lay.done);
-        wk.where = reinterpret_cast<int*>(p.ws + p.lay.where);
-        wk.leftover = reinterpret_cast<int*>(p.ws + p.lay.leftover);
-        wk.n_tasks = p.n_tasks;
-        wk.n_entries = p.device_tasks ? -1 : p.n_task_entries;      // (-1: the list's first block says how many)
-        wk.n_chains = p.n_chains;
-        wk.n_cu = p.n_cu;
-        wk.rounds = rounds;
-        wk.worker_waves = waves;
-        wk.T = p.T; wk.B = p.B; wk.A = p.A; wk.blank = p.blank; wk.Lmax = p.max_label;
-        wk.dtype = static_cast<int>(p.dtype);
-        wk.lds_ints = static_cast<int>(lds_bytes / 4);
-    }
     const dim3 grid(n_groups), block(64 * p.max_waves);
     auto s = static_cast<hipStream_t>(stream);
 #define CTC_LAUNCH_LATTICE(KERNEL)                                                                 \
     hipLaunchKernelGGL(KERNEL, grid, block, lds_bytes, s, meta, order, labels, emit_blank,                 \
                        reinterpret_cast<const double*>(p.ws + p.lay.emit_blank64), emit_label,            \
                        lat, logp, p.costs, chain_err, sink, wk)
-    // The emission layout is the launch's (emission_layout), and a template parameter of the kernels.
-    const bool symbol_major = emission_layout(p.A) == kEmitSymbolMajor;
-#define CTC_LAUNCH_LATTICE_MODE(KERNEL, MODE)                                                       \
-    do {                                                                                           \
-        if (symbol_major) CTC_LAUNCH_LATTICE((KERNEL<MODE, true>));                                \
-        else CTC_LAUNCH_LATTICE((KERNEL<MODE, false>));                                            \
-    } while (0)
 #define CTC_LAUNCH_LATTICE_KERNEL(KERNEL)                                                           \
     do {                                                                                           \
-        if (p.mode == Mode::kLoss) CTC_LAUNCH_LATTICE_MODE(KERNEL, Mode::kLoss);                   \
-        else if (p.mode == Mode::kBest) CTC_LAUNCH_LATTICE_MODE(KERNEL, Mode::kBest);              \
-        else CTC_LAUNCH_LATTICE_MODE(KERNEL, Mode::kGrad);                                         \
+        if (p.mode == Mode::kLoss) CTC_LAUNCH_LATTICE((KERNEL<Mode::kLoss>));                      \
+        else if (p.mode == Mode::kBest) CTC_LAUNCH_LATTICE((KERNEL<Mode::kBest>));                 \
+        else CTC_LAUNCH_LATTICE((KERNEL<Mode::kGrad>));                                            \
     } while (0)
     return checked_launch([&] {
         // (measurements: the two recursions one after the other, forward chains first, as two launches)
@@ -3462,7 +3014,6 @@ int launch_lattice(const Launch& p, void* stream)
         }
     });
 #undef CTC_LAUNCH_LATTICE_KERNEL
-#undef CTC_LAUNCH_LATTICE_MODE
 #undef CTC_LAUNCH_LATTICE
 }
 
@@ -3482,54 +3033,49 @@ int launch_gradient(const Launch& p, void* stream)
 {
     auto* meta = reinterpret_cast<const Utt*>(p.ws + p.lay.meta);
     const int* labels = p.labels;
-    auto* links = reinterpret_cast<const int*>(p.ws + p.lay.links);
-    auto* lse = reinterpret_cast<const float*>(p.ws + p.lay.lse);
     const LatticeOut lat = lattice_blocks(p);
     auto* logp = reinterpret_cast<const double*>(p.ws + p.lay.logp);
     auto* chain_err = reinterpret_cast<const int*>(p.ws + p.lay.chain_err);
-    const dim3 block(kRowThreads);
+    auto* emit_blank64 = reinterpret_cast<const double*>(p.ws + p.lay.emit_blank64);
+    auto* emit_label = reinterpret_cast<const float*>(p.ws + p.lay.emit_label);
+    auto* domain = reinterpret_cast<const int*>(p.ws + p.lay.domain);
     auto s = static_cast<hipStream_t>(stream);
     const bool f32 = p.dtype == CTC_DTYPE_F32;
-    const int Lmax = p.max_label;
-    const bool sparse = p.A > kRowsMaxA;
-    // Dense form: 16 rows per workgroup amortise the label staging best once the grid is large;
-    // smaller grids finish sooner with twice as many, shorter workgroups (measured on the
-    // 64- and 512-utterance minibatches).
-    const int rows = sparse ? 4 : (static_cast<int64_t>(p.T) * p.B <= (1 << 17) ? 8 : 16);
-    const dim3 grid((p.T + rows - 1) / rows, p.B);
-    const size_t lds = (2 * static_cast<size_t>(Lmax) + 4 * (static_cast<size_t>(Lmax) + 1 + (sparse ? 0 : p.A))) * 4;
-    if (p.A <= 64) {
-        // Both lattice blocks together against what the caches hold (kStreamingLatticeBytes).
-        const bool streaming = 2 * p.lay.ab_doubles * sizeof(uint32_t) > kStreamingLatticeBytes;
-        const size_t nlds = (static_cast<size_t>(Lmax) + 128 + 4 * (static_cast<size_t>(Lmax) + 1)) * 4;
-#define CTC_LAUNCH_NARROW(TYPE, STREAMING)                                                          \
-    hipLaunchKernelGGL((ctc_gradient_narrow_kernel<TYPE, STREAMING>), grid, block, nlds, s,         \
-                       static_cast<const TYPE*>(p.x), static_cast<TYPE*>(p.grads), meta, labels,    \
-                       links, lse, lat, logp, chain_err, p.costs, p.T, p.B, p.A, p.blank,           \
-                       Lmax, rows, p.n_tasks > 0 ? reinterpret_cast<const int*>(p.ws + p.lay.leftover) : nullptr,   \
-                       reinterpret_cast<const int*>(p.ws + p.lay.domain))
+    const int blocks = frame_blocks(p.T);
+    if (p.A <= kDirectMaxA) {
+        constexpr int kWaves = kRowThreads / 64;
+        const bool share = static_cast<int64_t>(p.B) * blocks * label_pieces(p.max_label) <= kShareBlocksMost;
+        const int per_group = share ? kWaves / block_waves(p.max_label) : kWaves;
+        const dim3 grid((blocks + per_group - 1) / per_group, p.B);
+        const size_t lds = static_cast<size_t>(kWaves) * tile_lds_ints(p.max_label, p.A <= 32 ? 2 : 4) * 4;
+#define CTC_LAUNCH_NARROW(TYPE, TILES)                                                              \
+    hipLaunchKernelGGL((ctc_gradient_narrow_kernel<TYPE, TILES>), grid, dim3(kRowThreads), lds, s,  \
+                       static_cast<TYPE*>(p.grads), meta, labels, emit_blank64, emit_label, lat,    \
+                       logp, chain_err, p.costs, p.T, p.B, p.A, p.blank, p.max_label, domain, share)
         return checked_launch([&] {
-            if (f32 && streaming) CTC_LAUNCH_NARROW(float, true);
-            else if (f32) CTC_LAUNCH_NARROW(float, false);
-            else if (streaming) CTC_LAUNCH_NARROW(bf16_t, true);
-            else CTC_LAUNCH_NARROW(bf16_t, false);
+            if (p.A <= 32) {
+                if (f32) CTC_LAUNCH_NARROW(float, 2);
+                else CTC_LAUNCH_NARROW(bf16_t, 2);
+            } else {
+                if (f32) CTC_LAUNCH_NARROW(float, 4);
+                else CTC_LAUNCH_NARROW(bf16_t, 4);
+            }
         });
 #undef CTC_LAUNCH_NARROW
     }
-#define CTC_LAUNCH_GRADIENT(TYPE, SPARSE)                                                          \
-    hipLaunchKernelGGL((ctc_gradient_rows_kernel<TYPE, SPARSE>), grid, block, lds, s,               \
-                       static_cast<const TYPE*>(p.x), static_cast<TYPE*>(p.grads), meta, labels,     \
-                       links, lse, lat, logp, chain_err, p.costs, p.T, p.B, p.A, p.blank, Lmax, rows,               \
-                       reinterpret_cast<const float*>(p.ws + p.lay.emit_blank),                                       \
-                       reinterpret_cast<const float*>(p.ws + p.lay.emit_label),                                       \
-                       reinterpret_cast<const int*>(p.ws + p.lay.domain))
+    const dim3 grid(blocks, p.B);
+    const int rows = static_cast<size_t>(kBlockFrames) * (p.max_label + 1) * sizeof(float) <= (size_t(60) << 10) ? kBlockFrames : kBlockFrames / 2;
+    const size_t lds = static_cast<size_t>(rows) * (p.max_label + 1) * sizeof(float);
+#define CTC_LAUNCH_WIDE(TYPE)                                                                       \
+    hipLaunchKernelGGL(ctc_gradient_wide_kernel<TYPE>, grid, dim3(64), lds, s, static_cast<TYPE*>(p.grads), meta,       \
+                       labels, reinterpret_cast<const int*>(p.ws + p.lay.links),                    \
+                       reinterpret_cast<const float*>(p.ws + p.lay.emit_blank), emit_blank64,       \
+                       emit_label, lat, logp, chain_err, p.costs, p.B, p.A, p.blank, rows, domain)
     return checked_launch([&] {
-        if (f32 && sparse) CTC_LAUNCH_GRADIENT(float, true);
-        else if (f32) CTC_LAUNCH_GRADIENT(float, false);
-        else if (sparse) CTC_LAUNCH_GRADIENT(bf16_t, true);
-        else CTC_LAUNCH_GRADIENT(bf16_t, false);
+        if (f32) CTC_LAUNCH_WIDE(float);
+        else CTC_LAUNCH_WIDE(bf16_t);
     });
-#undef CTC_LAUNCH_GRADIENT
+#undef CTC_LAUNCH_WIDE
 }
 
 }  // namespace ctc

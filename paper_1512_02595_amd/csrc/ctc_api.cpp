@@ -72,6 +72,7 @@ void carve(int T, int B, int64_t sumL, int64_t emit, int64_t frames, int64_t ab,
     l.logp = off;   off = align_up(off + static_cast<size_t>(B) * sizeof(double));
     l.sink = off;   off = align_up(off + static_cast<size_t>(B) * 2 * kSinkWaves * kSinkBytes);
     l.chain_err = off; off = align_up(off + static_cast<size_t>(B) * sizeof(int32_t));
+    l.done = off;   off = align_up(off + static_cast<size_t>(B) * sizeof(int32_t));
     l.domain = off; off = align_up(off + static_cast<size_t>(B) * 2 * sizeof(int32_t));
     l.row_flags = off;
     off = align_up(off + static_cast<size_t>(B) * ((T + kFlagFrames - 1) / kFlagFrames) * sizeof(int32_t));
@@ -322,7 +323,7 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
     // Would the launch, planned for latency, put more than two wavefronts on every SIMD?
     int64_t latency_waves = 0;
     for (int b = 0; b < c.B; ++b) latency_waves += all_plans.latency_waves[symbol_major][c.label_lengths[b]];
-    const bool crowded = latency_waves * (c.mode == Mode::kGrad ? 2 : 1) > kCrowdedWaves;
+    const bool crowded = latency_waves * 2 > kCrowdedWaves;
     const PlanTable& plan_of = all_plans.table[crowded][symbol_major];
 
     // The labels travel as bytes where a symbol fits one and as words otherwise (launch_setup, NarrowImage).
@@ -404,7 +405,7 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
         run_frames[i] = meta[running[i]].Tb;
         run_waves[i] = chain_waves(running[i]);
     }
-    const int dirs = c.mode == Mode::kGrad ? 2 : 1;
+    constexpr int dirs = 2;
     order_chains(running.data(), run_frames.data(), run_waves.data(), n_run, dirs, compute_units(), order);
     for (int i = n_run * dirs; i < 2 * c.B; ++i) order[i] = -1;
 
@@ -580,12 +581,12 @@ ctc_status_t run_device(const void* x, const int32_t* labels, const int32_t* lab
     p.T = T; p.B = B; p.A = A; p.blank = blank;
     p.dtype = dtype;
     p.n_run = B;                       // a lattice workgroup per utterance and direction; those that do not run leave at once
-    p.n_chains = B * (grads ? 2 : 1);
+    p.n_chains = B * 2;
     const bool symbol_major = emission_layout(A) == kEmitSymbols;
     // Would the launch, planned for latency, put more than two wavefronts on every SIMD (prepare's question)?  The
     // labels' lengths are on the GPU; the answer here is for lengths spread evenly up to the bound.
     const Plans& all_plans = plans();
-    p.crowded = static_cast<int64_t>(B) * (grads ? 2 : 1) * all_plans.latency_waves_up_to[symbol_major][max_label] >
+    p.crowded = static_cast<int64_t>(B) * 2 * all_plans.latency_waves_up_to[symbol_major][max_label] >
                 static_cast<int64_t>(kCrowdedWaves) * (max_label + 1);
     p.max_waves = all_plans.most_waves[p.crowded][max_label];
     p.max_frames = T;

@@ -321,6 +321,13 @@ CTC_HOST_DEVICE inline int64_t blank_emission_offset(const Utt& m, int chunk)
 // Chunk that a chain takes as its i-th one.
 CTC_HOST_DEVICE inline int chain_chunk(int i, int chunks, bool backward) { return backward ? chunks - 1 - i : i; }
 
+// How many of an utterance's chunks a chain takes when the two meet in the middle: whole blocks, the odd one forward.
+CTC_HOST_DEVICE inline int chain_chunks(int frames, bool backward)
+{
+    const int blocks = frame_blocks(frames), forward = (blocks + 1) / 2;
+    return 2 * (backward ? blocks - forward : forward);
+}
+
 // The order in which a chain requests (fetch) and consumes (run) the emissions of its chunks, an even number, in
 // four register sets: set i mod 4 holds chunk i.  fetch(set, i) requests the label emissions of the chain's i-th chunk
 // and the blank's of the one before it (i > 0); run(set, i) runs its eight steps.  The sets' numbers are compile-time
@@ -369,6 +376,8 @@ struct Layout {
     size_t logp = 0;      // double[B]    log2 of the alignment mass
     size_t sink = 0;      // what lanes with nothing to store scribble on: kSinkBytes per wavefront of a lattice launch
     size_t chain_err = 0; // int32[B]     set when a lattice wavefront gave up waiting for its neighbour
+    size_t done = 0;      // int32[B]     cost-only calls: wavefronts of the utterance's chains that have ended (low half)
+                          //              and that gave up (high half)
     size_t domain = 0;    // int32[2 B]   per utterance and direction, nonzero: that chain ran in the log domain (published by
                           //              the chain for the gradient, which must know where its exponent rows are)
     size_t row_flags = 0; // int32[B * ceil(T / 64)]  narrow alphabets: per 64 frames of an utterance, nonzero if one of
@@ -400,9 +409,9 @@ ctc_status_t make_layout(int T, int B, int A, const int32_t* label_lengths,
 
 // What a call computes, and so what its chains are run for:
 //   kGrad  sum over alignments, label states of every frame stored (cost and gradient)
-//   kLoss  sum over alignments, nothing stored (cost only; forward chain only)
+//   kLoss  sum over alignments, nothing stored (cost only; the chains meet in the middle)
 //   kBest  maximum over alignments, one byte of predecessor choices stored per state pair and
-//          frame (most probable alignment; forward chain only)
+//          frame (most probable alignment; the chains meet in the middle)
 enum class Mode { kGrad, kLoss, kBest };
 
 // The same for the device-metadata entry point: sized for B utterances of T frames and

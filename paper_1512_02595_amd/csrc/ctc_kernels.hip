@@ -225,7 +225,7 @@ void ctc_plan_kernel(const int* __restrict__ labels, const int* __restrict__ lab
                      const int* __restrict__ input_lengths, Utt* __restrict__ meta,
                      int* __restrict__ order, int* __restrict__ status,
                      int Tt, int B, int A, int blank, int max_label, int poll_budget, bool crowded,
-                     bool log_domain, int dirs)
+                     bool log_domain)
 {
     __shared__ long long weight[kMaxDeviceMetaB];     // T_b x wavefronts; -1: does not run
     __shared__ int repeats[kMaxDeviceMetaB];          // adjacent equal symbols; kBadLabel added for a bad symbol
@@ -312,7 +312,7 @@ void ctc_plan_kernel(const int* __restrict__ labels, const int* __restrict__ lab
         // backward chains (order_chains; the device planner does not balance the SIMDs' loads
         // beyond that).
         const int first = rank - rank % kChainBlock, in_block = min(kChainBlock, s_running - first);
-        for (int d = 0; d < dirs; ++d) order[first * dirs + d * in_block + rank % kChainBlock] = 2 * i + d;
+        for (int d = 0; d < 2; ++d) order[first * 2 + d * in_block + rank % kChainBlock] = 2 * i + d;
     }
 }
 
@@ -339,6 +339,7 @@ struct SetupArgs {
     int* links;
     float* costs;
     int* chain_err;
+    int* done;            // per utterance: cost-only chains' wavefronts that have ended (finish_loss)
     float* log0;          // kEmissionConstants floats that lattice lanes without a label state read as their
                           // emission: probability 0 (linear-domain chains) and log 0 (log-domain chains)
     double* emit_blank64; // the blank's probability per frame as fp64 (Layout::emit_blank64)
@@ -401,6 +402,7 @@ __device__ __forceinline__ void setup_words(const Utt m, const int b, const Setu
 {
     if (threadIdx.x == 0) {
         sa.chain_err[b] = 0;
+        sa.done[b] = 0;
         if (b == 0) {
             for (int i = 0; i < kEmissionConstants; ++i) sa.log0[i] = i < kLogZeroEmission ? 0.0f : static_cast<float>(kNeg);
             // This launch follows the upload kernel on the stream, so the host may now reuse
@@ -795,7 +797,7 @@ struct NarrowDevice {
     Utt* meta;                    // records to build
     int* order;
     int* status_words;            // [B] nonzero: the utterance's lengths or labels are invalid
-    int max_label, poll_budget, dirs;
+    int max_label, poll_budget;
     bool crowded, log_domain;
     int n_cu;                     // compute units of the device (a multiple of kChainBlock, or 0: keep the plain order)
 };
@@ -877,13 +879,13 @@ __device__ __forceinline__ Utt build_record(const NarrowDevice& dv, const PlanTa
         // i +- n_cu, so every other round of n_cu chains runs lightest first, and a compute unit's chains
         // add up to about the same (the host's order_chains goes by the SIMDs' loads; this is its first-order part).
         int rank = s_rank;
-        const int per_round = dv.n_cu / dv.dirs;
-        if (per_round >= kChainBlock && B * dv.dirs > dv.n_cu && ((rank / per_round) & 1)) {
+        const int per_round = dv.n_cu / 2;
+        if (per_round >= kChainBlock && B * 2 > dv.n_cu && ((rank / per_round) & 1)) {
             const int round_first = rank - rank % per_round, in_round = min(per_round, B - round_first);
             rank = round_first + (in_round - 1 - rank % per_round);
         }
         const int first = rank - rank % kChainBlock, in_block = min(kChainBlock, B - first);
-        for (int d = 0; d < dv.dirs; ++d) dv.order[first * dv.dirs + d * in_block + rank % kChainBlock] = 2 * b + d;
+        for (int d = 0; d < 2; ++d) dv.order[first * 2 + d * in_block + rank % kChainBlock] = 2 * b + d;
     }
     return m;
 }
@@ -1154,6 +1156,10 @@ __device__ __forceinline__ Wave* halo_wave(void* lds, int wave)
 // The gradient needs the label states' shares only and takes the blank's occupancy as 1 minus that of all label states
 // (sum_s alpha_t(s) beta_t(s) = p at every frame).
 //
+// In the modes without a gradient the two chains of an utterance meet in the middle (chain_chunks): each runs over half
+// of the frames and leaves its last state, which finish_loss (or the backtrace) combines.  (Log-domain chains of cost-only
+// calls are too rare to be worth a second way of combining: there the forward chain runs all the way, alone.)
+//
 // A chain starts from the state "all mass in its first blank, before any frame" and takes whole chunks of the
 // utterance's padded frames; virtual frames (emission_layout) leave the start state as it is, and a forward chain's
 // virtual frames after the last real one only gather p in the last blank.
@@ -1185,10 +1191,11 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
                                           float* __restrict__ costs, int* __restrict__ chain_err,
                                           uint32_t* __restrict__ sink, void* lds)
 {
-    static_assert(kMode == Mode::kGrad || !kBackward, "only the gradient needs the backward chain");
+    static_assert(kMode != Mode::kLoss || !kBackward, "see above");
     // Launches for the most probable alignment store plain logarithms, the others coded emissions.
     constexpr bool kCoded = kMode != Mode::kBest;
     const int L = m.L, P = L + 1, chunks = 2 * frame_blocks(m.Tb);
+    const int count = kMode == Mode::kBest ? chain_chunks(m.Tb, kBackward) : chunks;     // chunks of this chain
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (uniform: in a scalar register)
     const int halo = (kSync == Sync::kHalo) ? m.halo : 0;
     const int j = wave * (64 - halo) + lane;
@@ -1348,13 +1355,16 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
     auto advance = [&](int step, double eb, float el) {
         const double prev = from_prev_pair(v_label, step);
         if (kMode == Mode::kBest) {
+            // Of equally probable ways the one that stays highest in the label throughout: going forward that is the
+            // shortest move, going backward the longest.
+            auto better = [](double a, double b) { return kBackward ? a >= b : a > b; };
             const double via_skip = prev + skip_penalty;
-            const bool blank_moves = prev > v_blank;
+            const bool blank_moves = better(prev, v_blank);
             i_blank = blank_moves ? prev : v_blank;
             double best = v_label;
             choice = kFromSame;
-            if (v_blank > best) { best = v_blank; choice = kFromBlank; }
-            if (via_skip > best) { best = via_skip; choice = kFromPrevLabel; }
+            if (better(v_blank, best)) { best = v_blank; choice = kFromBlank; }
+            if (better(via_skip, best)) { best = via_skip; choice = kFromPrevLabel; }
             i_label = best;
             choice |= blank_moves ? kBlankFromPrevLabel : 0;
         } else {
@@ -1389,8 +1399,14 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
         }
         end_chunk();
     };
-    chain_schedule(chunks, fetch, run);
+    chain_schedule(count, fetch, run);
 
+    if (kMode == Mode::kBest) {
+        // the backtrace looks for the best way through the frames where the chains meet
+        if (active) reinterpret_cast<CheckpointState*>(out_exponents + m.ab_off)[j] = CheckpointState{v_blank, v_label};
+        if (kSync == Sync::kHalo && lost && lane == 0) chain_err[u] = 1;
+        return;
+    }
     if (!kBackward) {
         // p = alpha_{T-1}(2L) + alpha_{T-1}(2L-1): the blank of pair L and the label of pair L-1.
         // Pair L sits in an exact lane, and so does the lane below it or, if that is the last
@@ -1398,19 +1414,11 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
         // and a hand-over that fell due after the last step has been done by end_chunk.
         const double prev = from_prev_pair(v_label, chunks * kChunk);
         if (active && j == L) {
-            if (kMode == Mode::kBest) {
-                // the better of the two end states; logp carries which one to the backtrace
-                const bool ends_on_label = prev > v_blank;
-                const double lp = ends_on_label ? prev : v_blank;
-                logp[u] = static_cast<double>(2 * L - (ends_on_label ? 1 : 0));
-                costs[u] = (lp < -1.0e29) ? __builtin_inff() : static_cast<float>(-lp * kLn2);
-            } else {
-                const double lp = lse2(v_blank, prev);
-                logp[u] = pack_log2(-lp);                         // 1 / p
-                const float cost = (lp < -1.0e29) ? __builtin_inff() : static_cast<float>(-lp * kLn2);
-                if (kSync == Sync::kHalo && kMode == Mode::kLoss) hl->cost = cost;
-                else costs[u] = cost;
-            }
+            const double lp = lse2(v_blank, prev);
+            logp[u] = pack_log2(-lp);                    // 1 / p
+            const float cost = (lp < -1.0e29) ? __builtin_inff() : static_cast<float>(-lp * kLn2);
+            if (kSync == Sync::kHalo && kMode == Mode::kLoss) hl->cost = cost;
+            else costs[u] = cost;
         }
     }
     if (kSync == Sync::kHalo && kMode == Mode::kLoss) {
@@ -1488,8 +1496,19 @@ __device__ __forceinline__ bool outside_easy_range(double top)
     return hi - (static_cast<unsigned>(1023 + kEasyLow) << 20) >= (static_cast<unsigned>(kEasyHigh - kEasyLow + 1) << 20);
 }
 
+// An utterance's mass p = value * 2^frame: its reciprocal for the gradient, and the cost.
+__device__ __forceinline__ void store_mass(double value, int frame, double& inverse_p, float& cost)
+{
+    const double mantissa = __builtin_amdgcn_frexp_mant(value);                // [0.5, 1)
+    const int exponent = frame + __builtin_amdgcn_frexp_exp(value);
+    // (in double: once per chain, and a cost near zero, p near 1, would keep few of a float logarithm's bits)
+    const double l2 = static_cast<double>(exponent) + ::log2(mantissa);
+    inverse_p = (value > 0.0) ? pack_state(1.0 / mantissa, -exponent) : 0.0;
+    cost = (value > 0.0) ? static_cast<float>(-l2 * kLn2) : __builtin_inff();
+}
+
 template <bool kBackward, Sync kSync, Mode kMode>
-__device__ __forceinline__ void run_chain_linear(const Utt m, const int u, const int* __restrict__ labels,
+__device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const int* __restrict__ labels,
                                                  const double* __restrict__ emit_blank64,
                                                  const float* __restrict__ emit_label,
                                                  uint32_t* __restrict__ out, int* __restrict__ out_exponents,
@@ -1497,10 +1516,10 @@ __device__ __forceinline__ void run_chain_linear(const Utt m, const int u, const
                                                  float* __restrict__ costs, int* __restrict__ chain_err,
                                                  uint32_t* __restrict__ sink, void* lds)
 {
-    static_assert(kMode == Mode::kGrad || !kBackward, "only the gradient needs the backward chain");
     static_assert(kSync != Sync::kBarrier, "the barrier kernel runs the log-domain chain");
     static_assert(kMode != Mode::kBest, "the maximum recursion runs in the log domain");
     const int L = m.L, chunks = 2 * frame_blocks(m.Tb);
+    const int count = kMode == Mode::kLoss ? chain_chunks(m.Tb, kBackward) : chunks;     // chunks of this chain
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (uniform: in a scalar register)
     const int halo = (kSync == Sync::kHalo) ? m.halo : 0;
     const int j = wave * (64 - halo) + lane;             // pair of this lane (see run_chain_log)
@@ -1522,7 +1541,6 @@ __device__ __forceinline__ void run_chain_linear(const Utt m, const int u, const
     int* fp = stores ? out_exponents + m.ab_off + first_row * pitch + li + 1 : reinterpret_cast<int*>(sink);
     const int64_t row_step = stores ? (kBackward ? -pitch : pitch) : 0;
 
-    HaloHeader* const hl = static_cast<HaloHeader*>(lds);
     const int last_wave = m.waves - 1;
     HaloWave* const mine_lds = halo_wave<HaloWave>(lds, wave);
     HaloWave* const below_lds = halo_wave<HaloWave>(lds, wave > 0 ? wave - 1 : 0);
@@ -1703,42 +1721,24 @@ __device__ __forceinline__ void run_chain_linear(const Utt m, const int u, const
         end_chunk();
         if (kMode == Mode::kGrad && (k & 1)) checkpoint();
     };
-    chain_schedule(chunks, fetch, run);
+    chain_schedule(count, fetch, run);
 
+    if (kMode == Mode::kLoss) {
+        // the state of every pair, for finish_loss
+        if (active) {
+            reinterpret_cast<CheckpointState*>(out + m.ab_off)[j] = CheckpointState{v_blank, v_label};
+            out_exponents[m.ab_off + j] = frame;
+        }
+        return lost;
+    }
     if (!kBackward) {
         // p = alpha_{T-1}(2L) + alpha_{T-1}(2L-1), from the lane of pair L (exact, as is the
         // lane below it: see run_chain_log).
         const double from_below = from_prev_pair(v_label) * scale;
-        if (active && j == L) {
-            // p = mantissa * 2^exponent, mantissa in [0.5, 1)
-            const double p = v_blank + from_below;
-            const double mantissa = __builtin_amdgcn_frexp_mant(p);
-            const int exponent = frame + __builtin_amdgcn_frexp_exp(p);
-            // (in double: once per chain, and a cost near zero, p near 1, would keep few of a float logarithm's bits)
-            const double l2 = static_cast<double>(exponent) + ::log2(mantissa);
-            logp[u] = (p > 0.0) ? pack_state(1.0 / mantissa, -exponent) : 0.0;     // 1 / p
-            const float cost = (p > 0.0) ? static_cast<float>(-l2 * kLn2) : __builtin_inff();
-            if (kSync == Sync::kHalo && kMode == Mode::kLoss) hl->cost = cost;
-            else costs[u] = cost;
-        }
+        if (active && j == L) store_mass(v_blank + from_below, frame, logp[u], costs[u]);
     }
-    if (kSync == Sync::kHalo && kMode == Mode::kLoss) {
-        // as in run_chain_log: the wavefront that finishes last writes the cost
-        if (lost && lane == 0) hl->gave_up = 1;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        int before = 0;
-        if (lane == 0)
-            before = __hip_atomic_fetch_add(&hl->finished, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        before = __builtin_amdgcn_readfirstlane(before);
-        if (before == m.waves - 1 && lane == 0) {
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const int any_lost = __hip_atomic_load(&hl->gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            const float cost = hl->cost;
-            costs[u] = any_lost ? __uint_as_float(0x7FC00000u) : cost;
-        }
-    } else if (kSync == Sync::kHalo && lost && lane == 0) {
-        chain_err[u] = 1;
-    }
+    if (kSync == Sync::kHalo && lost && lane == 0) chain_err[u] = 1;
+    return lost;
 }
 
 // Linear-domain chains of more than 64 pairs: a lane owns two neighbouring pairs, A = 2q and
@@ -1753,7 +1753,7 @@ __device__ __forceinline__ void run_chain_linear(const Utt m, const int u, const
 // pair) its part falls on one of the row's two unused columns.
 
 template <bool kBackward, Mode kMode>
-__device__ __forceinline__ void run_chain_linear2(const Utt m, const int u, const int* __restrict__ labels,
+__device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, const int* __restrict__ labels,
                                                   const double* __restrict__ emit_blank64,
                                                   const float* __restrict__ emit_label,
                                                   uint32_t* __restrict__ out, int* __restrict__ out_exponents,
@@ -1761,9 +1761,9 @@ __device__ __forceinline__ void run_chain_linear2(const Utt m, const int u, cons
                                                   float* __restrict__ costs, int* __restrict__ chain_err,
                                                   uint32_t* __restrict__ sink, void* lds)
 {
-    static_assert(kMode == Mode::kGrad || !kBackward, "only the gradient needs the backward chain");
     static_assert(kMode != Mode::kBest, "the maximum recursion runs in the log domain");
     const int L = m.L, chunks = 2 * frame_blocks(m.Tb);
+    const int count = kMode == Mode::kLoss ? chain_chunks(m.Tb, kBackward) : chunks;     // chunks of this chain
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (uniform: in a scalar register)
     const int halo = m.halo2, waves = m.waves2;
     const int q = wave * (64 - halo) + lane;
@@ -1792,7 +1792,6 @@ __device__ __forceinline__ void run_chain_linear2(const Utt m, const int u, cons
     int* fp = stores ? out_exponents + m.ab_off + first_row * pitch + first_column : reinterpret_cast<int*>(sink);
     const int64_t row_step = stores ? (kBackward ? -pitch : pitch) : 0;
 
-    HaloHeader* const hl = static_cast<HaloHeader*>(lds);
     const int last_wave = waves - 1;
     int budget = m.poll_budget;
     bool lost = false;
@@ -1985,46 +1984,35 @@ __device__ __forceinline__ void run_chain_linear2(const Utt m, const int u, cons
         end_chunk();
         if (kMode == Mode::kGrad && (k & 1)) checkpoint();
     };
-    chain_schedule(chunks, fetch, run);
+    chain_schedule(count, fetch, run);
 
+    if (kMode == Mode::kLoss) {
+        // the state of every pair, for finish_loss
+        CheckpointState* const states = reinterpret_cast<CheckpointState*>(out + m.ab_off);
+        if (active) {
+            states[ja] = CheckpointState{va_blank, va_label};
+            out_exponents[m.ab_off + ja] = frame;
+        }
+        if (active && jb <= L) {
+            states[jb] = CheckpointState{vb_blank, vb_label};
+            out_exponents[m.ab_off + jb] = frame;
+        }
+        return lost;
+    }
     if (!kBackward) {
         // p = alpha_{T-1}(2L) + alpha_{T-1}(2L-1): the blank of pair L and the label of pair L - 1.
         // L even: pair L is this lane's A, pair L - 1 the B of the lane below; L odd: pair L is B.
         const double from_below = from_lane_below(vb_label) * scale;
-        if (active && (ja == L || jb == L)) {
-            const double p = (ja == L) ? va_blank + from_below : vb_blank + va_label;
-            const double mantissa = __builtin_amdgcn_frexp_mant(p);         // [0.5, 1)
-            const int exponent = frame + __builtin_amdgcn_frexp_exp(p);
-            // (in double: once per chain, and a cost near zero, p near 1, would keep few of a float logarithm's bits)
-            const double l2 = static_cast<double>(exponent) + ::log2(mantissa);
-            logp[u] = (p > 0.0) ? pack_state(1.0 / mantissa, -exponent) : 0.0;     // 1 / p
-            const float cost = (p > 0.0) ? static_cast<float>(-l2 * kLn2) : __builtin_inff();
-            if (kMode == Mode::kLoss) hl->cost = cost;
-            else costs[u] = cost;
-        }
+        if (active && (ja == L || jb == L)) store_mass((ja == L) ? va_blank + from_below : vb_blank + va_label, frame, logp[u], costs[u]);
     }
-    if (kMode == Mode::kLoss) {
-        // as in run_chain_log: the wavefront that finishes last writes the cost
-        if (lost && lane == 0) hl->gave_up = 1;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        int before = 0;
-        if (lane == 0)
-            before = __hip_atomic_fetch_add(&hl->finished, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        before = __builtin_amdgcn_readfirstlane(before);
-        if (before == waves - 1 && lane == 0) {
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const int any_lost = __hip_atomic_load(&hl->gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            const float cost = hl->cost;
-            costs[u] = any_lost ? __uint_as_float(0x7FC00000u) : cost;
-        }
-    } else if (lost && lane == 0) {
-        chain_err[u] = 1;
-    }
+    if (lost && lane == 0) chain_err[u] = 1;
+    return lost;
 }
 
 // Where the chains of a launch leave their states: value and exponent blocks of both directions
-// (see "lattice storage").  In the modes without a backward chain the forward value block receives
-// the predecessor choices (Mode::kBest) or nothing.
+// (see "lattice storage").  In the modes without a gradient: the state of every pair after a chain's last frame (cost
+// only: doubles in the value block, frames in the exponent block), or the predecessor choices in the value block and
+// the last states, base-2 logarithms, in the exponent block (Mode::kBest).
 struct LatticeOut {
     uint32_t* alpha;
     int* alpha_exponents;
@@ -2037,6 +2025,7 @@ struct LaunchWords {
     const int* row_flags;     // narrow softmax launch's words (rows_flagged), or nullptr: the records' flags say it all
     int flag_blocks;          // ... per utterance
     int* domain;              // per utterance and direction: did the chain run in the log domain
+    int* done;                // per utterance: see finish_loss
     int* host_flag;           // pinned host word that receives host_flag_value: the image may be reused (or nullptr)
     int host_flag_value;
     const int* status_words;  // device-resident metadata built by the narrow softmax launch: per utterance, nonzero if
@@ -2044,6 +2033,71 @@ struct LaunchWords {
     int status_count;
     int skip_directions;      // bit 0: leave the forward chains out, bit 1: the backward chains (measurements only)
 };
+
+// Cost-only calls: the mass of an utterance from the states that its two chains have left where they meet, alpha after
+// the last of the forward chain's frames and beta (its frame included) at the first of the backward chain's:
+//   p = sum over states s of  (sum of alpha over s and its predecessors) * beta(s).
+// A wavefront that has ended counts itself in, and the utterance's last one does the sum, whichever it is: the order of
+// the additions is that of the pairs.  The count carries, in its upper half, how many wavefronts gave up waiting for a
+// neighbour; then the cost is NaN.  `expected`: wavefronts of both chains.
+__device__ __forceinline__ void finish_loss(const Utt& m, const int u, const int* __restrict__ labels, const LatticeOut& lat,
+                                            int* __restrict__ done, float* __restrict__ costs, const int expected, const bool lost)
+{
+    const int lane = threadIdx.x & 63;
+    // (device scope: the chains may run on different dies)
+    int before = 0;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    if (lane == 0)
+        before = __hip_atomic_fetch_add(&done[u], lost ? 0x10001 : 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    before = __builtin_amdgcn_readfirstlane(before);
+    if ((before & 0xFFFF) != expected - 1) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    const int L = m.L;
+    const CheckpointState* const alpha = reinterpret_cast<const CheckpointState*>(lat.alpha + m.ab_off);
+    const CheckpointState* const beta = reinterpret_cast<const CheckpointState*>(lat.beta + m.ab_off);
+    const int *const fa = lat.alpha_exponents + m.ab_off, *const fb = lat.beta_exponents + m.ab_off;
+    const int* const lab = labels + m.lab_off;
+    // A lane's sum as sum * 2^top.
+    double sum = 0.0;
+    int top = kNoExponent;
+    auto add = [&](double a, int a_frame, double b, int b_frame) {
+        if (!(a > 0.0 && b > 0.0)) return;
+        const double v = __builtin_amdgcn_frexp_mant(a) * __builtin_amdgcn_frexp_mant(b);
+        const int e = a_frame + b_frame + __builtin_amdgcn_frexp_exp(a) + __builtin_amdgcn_frexp_exp(b);
+        const int higher = max(top, e);
+        sum = __builtin_amdgcn_ldexp(sum, max(top - higher, -2000)) + __builtin_amdgcn_ldexp(v, max(e - higher, -2000));
+        top = higher;
+    };
+    for (int j = lane; j <= L; j += 64) {
+        // pair j going forward: blank j and label j; the backward chain's pair i: blank L - i and label L - 1 - i
+        const CheckpointState a = alpha[j];
+        const CheckpointState before_a = j > 0 ? alpha[j - 1] : CheckpointState{0.0, 0.0};
+        const int a_frame = fa[j], before_frame = j > 0 ? fa[j - 1] : 0;
+        const double blank_b = beta[L - j].blank;
+        const int blank_frame = fb[L - j];
+        add(a.blank, a_frame, blank_b, blank_frame);
+        add(before_a.label, before_frame, blank_b, blank_frame);
+        if (j < L) {
+            const double label_b = beta[L - 1 - j].label;
+            const int label_frame = fb[L - 1 - j];
+            add(a.label, a_frame, label_b, label_frame);
+            add(a.blank, a_frame, label_b, label_frame);
+            if (j > 0 && lab[j] != lab[j - 1]) add(before_a.label, before_frame, label_b, label_frame);
+        }
+    }
+    for (int d = 1; d < 64; d <<= 1) {
+        const double other = __shfl_xor(sum, d);
+        const int other_top = __shfl_xor(top, d), higher = max(top, other_top);
+        sum = __builtin_amdgcn_ldexp(sum, max(top - higher, -2000)) + __builtin_amdgcn_ldexp(other, max(other_top - higher, -2000));
+        top = higher;
+    }
+    if (lane == 0) {
+        double unused;
+        float cost;
+        store_mass(sum, top, unused, cost);
+        costs[u] = (before >> 16) != 0 || lost ? __uint_as_float(0x7FC00000u) : cost;
+    }
+}
 
 template <Sync kSync, Mode kMode>
 __device__ __forceinline__ void lattice_body(const Utt* __restrict__ meta, const int* __restrict__ order,
@@ -2077,7 +2131,7 @@ __device__ __forceinline__ void lattice_body(const Utt* __restrict__ meta, const
     // (measurements of the recursions one after the other: a launch that leaves one direction out)
     if (kMode == Mode::kGrad && ((wk.skip_directions >> (chain & 1)) & 1)) return;
     const int u = chain >> 1;
-    const bool forward = kMode != Mode::kGrad || (chain & 1) == 0;
+    const bool forward = (chain & 1) == 0;
     const Utt m = meta[u];
     if (!(m.flags & kUttRuns)) return;     // (a run order built on the device lists every utterance)
     // Which recursion: the barrier kernel and the maximum recursion have the log domain only;
@@ -2085,7 +2139,8 @@ __device__ __forceinline__ void lattice_body(const Utt* __restrict__ meta, const
     // gives one pair or two to a lane as the launcher planned it (two_pairs_per_lane).
     const bool in_log_domain = kSync == Sync::kBarrier || kMode == Mode::kBest || (m.flags & kUttLogDomain) != 0 ||
                                rows_flagged(wk.row_flags, u, wk.flag_blocks, m.Tb);
-    // (for the gradient, which must know where each chain's exponent rows are: a word per direction)
+    if (kMode == Mode::kLoss && in_log_domain && !forward) return;       // (the forward chain runs all the way)
+    // (for the gradient, which must know what each chain has left: a word per direction)
     if (kMode == Mode::kGrad && threadIdx.x == 0) wk.domain[2 * u + (forward ? 0 : 1)] = in_log_domain ? 1 : 0;
     const bool two_pairs = kSync == Sync::kHalo && !in_log_domain && (m.flags & kUttTwoPairs) != 0;
     const int waves = two_pairs ? m.waves2 : m.waves;
@@ -2112,38 +2167,38 @@ __device__ __forceinline__ void lattice_body(const Utt* __restrict__ meta, const
         if (idle) {
             // Nothing to compute, but keep meeting the barriers of the working wavefronts:
             // one per recursion step, plus the forward chain's final exchange.
-            const int barriers = static_cast<int>(padded_frames(m.Tb)) + (forward ? 1 : 0);
+            const int barriers = kMode == Mode::kBest ? chain_chunks(m.Tb, !forward) * kChunk
+                                                      : static_cast<int>(padded_frames(m.Tb)) + (forward ? 1 : 0);
             for (int i = 0; i < barriers; ++i) __syncthreads();
             return;
         }
     }
     if constexpr (kSync != Sync::kBarrier && kMode != Mode::kBest) {
-        if (two_pairs) {
-            if constexpr (kSync == Sync::kHalo) {
-                if (forward)
-                    run_chain_linear2<false, kMode>(m, u, labels, emit_blank64, emit_label, lat.alpha, lat.alpha_exponents, logp, costs, chain_err, sink, lds);
-                else
-                    run_chain_linear2<true, Mode::kGrad>(m, u, labels, emit_blank64, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
-            }
-            return;
-        }
         if (!in_log_domain) {
-            if (forward)
-                run_chain_linear<false, kSync, kMode>(m, u, labels, emit_blank64, emit_label, lat.alpha, lat.alpha_exponents, logp, costs, chain_err, sink, lds);
-            else
-                run_chain_linear<true, kSync, Mode::kGrad>(m, u, labels, emit_blank64, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
+            bool lost = false;
+            if (two_pairs) {
+                if constexpr (kSync == Sync::kHalo) {
+                    if (forward)
+                        lost = run_chain_linear2<false, kMode>(m, u, labels, emit_blank64, emit_label, lat.alpha, lat.alpha_exponents, logp, costs, chain_err, sink, lds);
+                    else
+                        lost = run_chain_linear2<true, kMode>(m, u, labels, emit_blank64, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
+                }
+            } else if (forward) {
+                lost = run_chain_linear<false, kSync, kMode>(m, u, labels, emit_blank64, emit_label, lat.alpha, lat.alpha_exponents, logp, costs, chain_err, sink, lds);
+            } else {
+                lost = run_chain_linear<true, kSync, kMode>(m, u, labels, emit_blank64, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
+            }
+            if (kMode == Mode::kLoss) finish_loss(m, u, labels, lat, wk.done, costs, 2 * waves, lost);
             return;
         }
     }
     if (forward)
         run_chain_log<false, kSync, kMode>(m, u, labels, emit_blank, emit_label, lat.alpha, lat.alpha_exponents, logp, costs, chain_err, sink, lds);
-    else
-        run_chain_log<true, kSync, Mode::kGrad>(m, u, labels, emit_blank, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
+    else if constexpr (kMode != Mode::kLoss)
+        run_chain_log<true, kSync, kMode>(m, u, labels, emit_blank, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
 }
 
-// grid = one workgroup per entry of `order` (utterance * 2 + direction: 0 forward, 1 backward; only
-// Mode::kGrad has backward chains; in the other modes `alpha` is the block that receives the
-// predecessor choices, or unused).
+// grid = one workgroup per entry of `order` (utterance * 2 + direction: 0 forward, 1 backward).
 // blockDim.x = 64 * (most wavefronts any utterance of the batch uses).
 // Variant for batches whose labels all fit one wavefront: no exchange at all.
 template <Mode kMode>
@@ -2193,13 +2248,15 @@ void ctc_lattice_kernel_barrier(const Utt* __restrict__ meta, const int* __restr
                                                costs, chain_err, sink, &xch[0][0], wk);
 }
 
-// ---- after a forward-only chain -------------------------------------------------------------
-// Most probable alignment: walk the stored predecessor choices back from the better end state.
-// One wavefront per utterance; alignment is [B][T] (utterance-major): the lattice state of each
+// ---- after the chains of the most probable alignment ------------------------------------------
+// The best way through the two frames where the chains meet, and from there a walk over the stored choices in either
+// direction, forward chain's frames back to the first and backward chain's frames on to the last.  grid (utterances,
+// 2), one wavefront each; alignment is [B][T] (utterance-major): the lattice state of each
 // frame (index into the blank-interleaved label), -1 for frames past the utterance's end and
-// for utterances without an alignment.
+// for utterances without an alignment.  Both chains index their states in their own order (the backward chain's state s
+// is the lattice's 2 L - s), so the two walks are the same code.
 //
-// The walk is serial, one dependent look-up per frame, so it is kept on the scalar unit: the
+// A walk is serial, one dependent look-up per frame, so it is kept on the scalar unit: the
 // choices are fetched in tiles of kTile frames x kTile pairs, lane = pair column, one register
 // per frame.  Going back kTile frames the walk moves down by at most kTile - 1 pairs (one per
 // frame), so the tile whose top right corner is the walk's position holds everything those
@@ -2209,39 +2266,89 @@ void ctc_lattice_kernel_barrier(const Utt* __restrict__ meta, const int* __restr
 constexpr int kTile = 64;
 
 __global__ __launch_bounds__(64)
-void ctc_backtrace_kernel(const Utt* __restrict__ meta, const unsigned char* __restrict__ choices,
-                          const double* __restrict__ end_state, const int* __restrict__ chain_err,
-                          float* __restrict__ costs, int* __restrict__ alignment, int Tt)
+void ctc_backtrace_kernel(const Utt* __restrict__ meta, const int* __restrict__ labels, const LatticeOut lat,
+                          const int* __restrict__ chain_err, float* __restrict__ costs, int* __restrict__ alignment, int Tt)
 {
     const int b = blockIdx.x, lane = threadIdx.x;
+    const bool backward = blockIdx.y != 0;
     const Utt m = meta[b];
     int* arow = alignment + static_cast<size_t>(b) * Tt;
     const bool runs = (m.flags & kUttRuns) != 0;
     const bool bad = runs && chain_err[b] != 0;
-    if (bad && lane == 0) costs[b] = __uint_as_float(0x7FC00000u);
-    const int valid = (runs && !bad) ? m.Tb : 0;
-    for (int t = valid + lane; t < Tt; t += 64) arow[t] = -1;
+    if (bad && lane == 0 && !backward) costs[b] = __uint_as_float(0x7FC00000u);
+    const int valid = (runs && !bad) ? m.Tb : 0, L = m.L;
+    if (backward)
+        for (int t = valid + lane; t < Tt; t += 64) arow[t] = -1;
     if (valid == 0) return;
 
-    const int P = m.L + 1;
-    const unsigned char* base = choices + m.ab_off;
-    // state of frame t; clamped so that no stored value can lead the reads astray
-    int state = __builtin_amdgcn_readfirstlane(min(max(static_cast<int>(end_state[b]), 0), 2 * m.L));
-    int t = static_cast<int>(padded_frames(m.Tb)) - 1;     // (virtual frames: their states are not stored)
-    if (lane == 0 && t < m.Tb) arow[t] = state;
-    // Frames t, t-1, ..., 1 each hold the choice that leads to the state of the frame before.
-    while (t >= 1) {
+    // The junction: the state `to` of the backward chain's first frame and the best state `from` before it.  Per
+    // pair the blank before the label, within a state the predecessor as in the forward chain (stay first); of equal ways
+    // the highest state.
+    const CheckpointState* const alpha = reinterpret_cast<const CheckpointState*>(lat.alpha_exponents + m.ab_off);
+    const CheckpointState* const beta = reinterpret_cast<const CheckpointState*>(lat.beta_exponents + m.ab_off);
+    const int* const lab = labels + m.lab_off;
+    double best = -1.0e300;
+    int from = 0, to = 0;
+    for (int j = lane; j <= L; j += 64) {
+        const CheckpointState a = alpha[j];
+        const double before = j > 0 ? alpha[j - 1].label : kNeg;
+        const double to_blank = fmax(a.blank, before) + beta[L - j].blank;
+        if (to_blank >= best) {
+            best = to_blank;
+            to = 2 * j;
+            from = before > a.blank ? 2 * j - 1 : 2 * j;
+        }
+        if (j < L) {
+            double w = a.label;
+            int s = 2 * j + 1;
+            if (a.blank > w) { w = a.blank; s = 2 * j; }
+            if (j > 0 && lab[j] != lab[j - 1] && before > w) { w = before; s = 2 * j - 1; }
+            w += beta[L - 1 - j].label;
+            if (w >= best) {
+                best = w;
+                to = 2 * j + 1;
+                from = s;
+            }
+        }
+    }
+    for (int d = 1; d < 64; d <<= 1) {
+        const double other = __shfl_xor(best, d);
+        const int other_from = __shfl_xor(from, d), other_to = __shfl_xor(to, d);
+        if (other > best || (other == best && other_to > to)) {
+            best = other;
+            from = other_from;
+            to = other_to;
+        }
+    }
+    if (lane == 0 && !backward) costs[b] = (best < -1.0e29) ? __builtin_inff() : static_cast<float>(-best * kLn2);
+
+    // this walk: frames in the chain's own order (frame_of), `rows` of them, from the state it was in at its last one
+    const int padded = static_cast<int>(padded_frames(m.Tb)), rows_all = chain_chunks(m.Tb, backward) * kChunk;
+    const int P = L + 1;
+    const unsigned char* base = reinterpret_cast<const unsigned char*>(backward ? lat.beta : lat.alpha) + m.ab_off;
+    auto frame_of = [&](int step) { return backward ? padded - 1 - step : step; };
+    auto file = [&](int step, int state) {
+        const int t = frame_of(step);
+        if (t < m.Tb) arow[t] = backward ? 2 * L - state : state;
+    };
+    // (clamped so that no stored value can lead the reads astray)
+    int state = __builtin_amdgcn_readfirstlane(min(max(backward ? 2 * L - to : from, 0), 2 * L));
+    int step = rows_all - 1;
+    if (step < 0) return;
+    if (lane == 0) file(step, state);
+    // Steps step, step-1, ..., 1 each hold the choice that leads to the state of the step before.
+    while (step >= 1) {
         const int pair_hi = state >> 1;                   // both states of a pair share its byte
         const int pair_lo = max(pair_hi - (kTile - 1), 0);
-        const int rows = min(kTile, t);                   // frames t, t-1, ..., t-rows+1
+        const int rows = min(kTile, step);                // steps step, step-1, ..., step-rows+1
         const unsigned col = static_cast<unsigned>(min(pair_lo + lane, pair_hi));
-        // A last, partial tile repeats frame 1 in the rows below it and walks on through them:
+        // A last, partial tile repeats step 1 in the rows below it and walks on through them:
         // those steps stay inside the tile (the state is kept >= 0) and their results are not
         // stored.  (An utterance's block is smaller than 2^31 bytes: 32-bit offsets.)
         int tile[kTile];
 #pragma unroll
         for (int r = 0; r < kTile; ++r)
-            tile[r] = base[static_cast<unsigned>(max(t - r, 1)) * static_cast<unsigned>(P) + col];
+            tile[r] = base[static_cast<unsigned>(frame_of(max(step - r, 1))) * static_cast<unsigned>(P) + col];
         int filed = 0;
 #pragma unroll
         for (int r = 0; r < kTile; ++r) {
@@ -2249,12 +2356,12 @@ void ctc_backtrace_kernel(const Utt* __restrict__ meta, const unsigned char* __r
             // how far down the state of this frame came from: bits 2..3 if it is a label state
             // (odd), bits 0..1 if it is a blank
             state = max(state - ((c >> ((state << 1) & 2)) & 3), 0);
-            // lane r of `filed` = state of frame t - r - 1
+            // lane r of `filed` = state of step - r - 1
             asm volatile("v_writelane_b32 %0, %1, %2" : "+v"(filed) : "s"(state), "n"(r));
         }
-        if (lane < rows && t - 1 - lane < m.Tb) arow[t - 1 - lane] = filed;
+        if (lane < rows) file(step - 1 - lane, filed);
         if (rows < kTile) break;
-        t -= kTile;
+        step -= kTile;
     }
 }
 
@@ -2866,7 +2973,7 @@ int launch_plan(const Launch& p, void* stream)
                            p.labels, p.dev_label_lengths, p.dev_input_lengths,
                            reinterpret_cast<Utt*>(p.ws + p.lay.meta), reinterpret_cast<int*>(p.ws + p.lay.order),
                            p.dev_status, p.T, p.B, p.A, p.blank, p.max_label, p.poll_budget, p.crowded,
-                           p.needs_barrier, p.mode == Mode::kGrad ? 2 : 1);
+                           p.needs_barrier);
     });
 }
 
@@ -2877,7 +2984,7 @@ int launch_softmax(const Launch& p, void* stream)
     auto* emit_blank = reinterpret_cast<float*>(p.ws + p.lay.emit_blank);
     auto* emit_label = reinterpret_cast<float*>(p.ws + p.lay.emit_label);
     const SetupArgs sa{reinterpret_cast<int*>(p.ws + p.lay.links), p.costs,
-                       reinterpret_cast<int*>(p.ws + p.lay.chain_err),
+                       reinterpret_cast<int*>(p.ws + p.lay.chain_err), reinterpret_cast<int*>(p.ws + p.lay.done),
                        emit_label,
                        reinterpret_cast<double*>(p.ws + p.lay.emit_blank64),
                        p.folded ? nullptr : p.host_flag, p.host_flag_value, p.mode == Mode::kBest,
@@ -2903,7 +3010,7 @@ int launch_softmax(const Launch& p, void* stream)
             if (p.dev_label_lengths)
                 dv = NarrowDevice{p.labels, p.dev_label_lengths, p.dev_input_lengths, meta, reinterpret_cast<int*>(p.ws + p.lay.order),
                                   reinterpret_cast<int*>(p.ws + p.lay.status), p.max_label, p.poll_budget,
-                                  p.mode == Mode::kGrad ? 2 : 1, p.crowded, p.needs_barrier,
+                                  p.crowded, p.needs_barrier,
                                   p.n_cu % kChainBlock == 0 ? p.n_cu : 0};
             const Utt* records = static_cast<const Utt*>(p.host_image);      // (the host reads its own image)
             for (int b = 0; records && b < p.B; ++b) {
@@ -2985,6 +3092,7 @@ int launch_lattice(const Launch& p, void* stream)
     wk.row_flags = p.folded ? reinterpret_cast<const int*>(p.ws + p.lay.row_flags) : nullptr;
     wk.flag_blocks = (p.T + kFlagFrames - 1) / kFlagFrames;
     wk.domain = reinterpret_cast<int*>(p.ws + p.lay.domain);
+    wk.done = reinterpret_cast<int*>(p.ws + p.lay.done);
     wk.host_flag = p.folded ? p.host_flag : nullptr;
     wk.host_flag_value = p.host_flag_value;
     if (p.folded && p.dev_status) {
@@ -3020,12 +3128,10 @@ int launch_lattice(const Launch& p, void* stream)
 int launch_backtrace(const Launch& p, void* stream)
 {
     auto* meta = reinterpret_cast<const Utt*>(p.ws + p.lay.meta);
-    auto* choices = reinterpret_cast<const unsigned char*>(p.ws + p.lay.alpha);
-    auto* end_state = reinterpret_cast<const double*>(p.ws + p.lay.logp);
     auto* chain_err = reinterpret_cast<const int*>(p.ws + p.lay.chain_err);
     return checked_launch([&] {
-        hipLaunchKernelGGL(ctc_backtrace_kernel, dim3(p.B), dim3(64), 0, static_cast<hipStream_t>(stream),
-                           meta, choices, end_state, chain_err, p.costs, p.alignment, p.T);
+        hipLaunchKernelGGL(ctc_backtrace_kernel, dim3(p.B, 2), dim3(64), 0, static_cast<hipStream_t>(stream),
+                           meta, p.labels, lattice_blocks(p), chain_err, p.costs, p.alignment, p.T);
     });
 }
 

@@ -436,6 +436,12 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
     out->crowded = crowded;
     out->sequential_chains = sequential_chains;
     out->n_cu = compute_units();
+    out->defer = 0;
+    if (c.mode == Mode::kGrad && c.A > kDirectMaxA && !needs_barrier && !sequential_chains && n_run > 0) {
+        int64_t rows = static_cast<int64_t>(c.T) * c.B;
+        for (int i = 0; i < n_run; ++i) rows -= run_frames[i];
+        out->defer = deferred_frames(static_cast<double>(rows) * c.A * elem, max_frames, n_run * dirs, out->n_cu);
+    }
     out->folded = c.A <= kDirectMaxA && c.B <= kNarrowMaxB && c.T < (1 << 29);
     out->lay = lay;
     return CTC_STATUS_SUCCESS;
@@ -606,6 +612,9 @@ ctc_status_t run_device(const void* x, const int32_t* labels, const int32_t* lab
     p.dev_status = status;
     p.poll_budget = g_poll_budget.load(std::memory_order_relaxed);
     p.n_cu = compute_units();
+    // (how much padding there is only the GPU knows: taken for a third of the tensor)
+    p.defer = grads && A > kDirectMaxA && !p.needs_barrier
+                  ? deferred_frames(static_cast<double>(T) * B * A * elem / 3, T / 2, p.n_chains, p.n_cu) : 0;
     // Narrow alphabets: the softmax launch builds the records itself (no planning launch before it); every
     // utterance's setup workgroup weighs all B utterances for the run order, which is worth it up to here.
     p.folded = A <= kDirectMaxA && B <= kDeviceFoldMaxB && max_label > 0;

@@ -181,6 +181,18 @@ constexpr int kBlockFrames = 2 * kChunkSteps;
 CTC_HOST_DEVICE inline int frame_blocks(int frames) { return (frames + kBlockFrames - 1) / kBlockFrames; }
 CTC_HOST_DEVICE inline int64_t padded_frames(int frames) { return static_cast<int64_t>(frame_blocks(frames)) * kBlockFrames; }
 
+// Alphabets above kDirectMaxA: of every 16 frames, how many leave their zero rows (padding, utterances without an
+// alignment) to the lattice launch, whose compute units without a chain would idle: as many as fit in the time of
+// its longest chain.  `zero_bytes`: of all zero rows.
+constexpr double kFillBytesPerUs = 3.0e6;      // what the idle half of the chip writes beside the chains
+constexpr double kChainUsPerFrame = 0.045;     // the quickest chains (one wavefront)
+inline int deferred_frames(double zero_bytes, int longest, int n_chains, int n_cu)
+{
+    if (n_chains + n_cu / 4 > n_cu || zero_bytes <= 0) return 0;
+    const double fits = kFillBytesPerUs * kChainUsPerFrame * longest * (n_cu - n_chains) / (n_cu / 2);
+    return static_cast<int>(std::min(16.0, 16.0 * fits / zero_bytes));
+}
+
 // The sink of a lattice launch: for each of its up to 2 B chain workgroups, kSinkBytes for each of the
 // up to kSinkWaves wavefronts.
 constexpr int kSinkWaves = 16, kSinkBytes = 64;
@@ -447,6 +459,7 @@ struct Launch {
     int poll_budget;          // copied into every Utt record
     bool crowded;             // plan the chains for total work rather than latency (device planner)
     int n_cu;                 // compute units of the device
+    int defer;                // of every 16 frames, those whose zero rows the lattice launch writes (deferred_frames)
     // Narrow alphabets, host metadata: there is no upload launch; the softmax launch reads the pinned image
     // itself and copies it into the workspace for the launches after it, and the lattice launch releases it.
     bool folded;

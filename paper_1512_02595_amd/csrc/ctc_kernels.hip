@@ -72,48 +72,36 @@ __device__ __forceinline__ uint16_t to_bf16_bits(float v)
 __device__ __forceinline__ void store_elem(bf16_t* p, size_t i, float v) { p[i].bits = to_bf16_bits(v); }
 
 // 16-byte vectors of activations: 4 floats or 8 bf16.
+// Sixteen bytes of a row.
+typedef uint32_t RawVec __attribute__((ext_vector_type(4)));
 template <typename T> struct Vec;
 template <> struct Vec<float> {
     static constexpr int N = 4;
-    static __device__ __forceinline__ void load(const float* p, float (&v)[4])
+    static __device__ __forceinline__ float get(const RawVec& r, int e) { return __uint_as_float(r[e]); }
+    static __device__ __forceinline__ RawVec pack(const float (&v)[4])
     {
-        const float4 r = *reinterpret_cast<const float4*>(p);
-        v[0] = r.x; v[1] = r.y; v[2] = r.z; v[3] = r.w;
-    }
-    static __device__ __forceinline__ void store(float* p, const float (&v)[4])
-    {
-        // Streaming store: the wide gradient is written once and not read again by this call
-        // except in the few label columns (measured 7 % faster than a plain store on the
-        // 6000-symbol workload, and the later fix-up of the label columns 20 % faster).
-        typedef float v4f __attribute__((ext_vector_type(4)));
-        const v4f t = {v[0], v[1], v[2], v[3]};
-        __builtin_nontemporal_store(t, reinterpret_cast<v4f*>(p));
+        return RawVec{__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
     }
 };
 template <> struct Vec<bf16_t> {
     static constexpr int N = 8;
-    static __device__ __forceinline__ void load(const bf16_t* p, float (&v)[8])
+    static __device__ __forceinline__ float get(const RawVec& r, int e)
     {
-        const uint4 r = *reinterpret_cast<const uint4*>(p);
-        const uint32_t w[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            v[2 * i] = __uint_as_float(w[i] << 16);
-            v[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
-        }
+        return __uint_as_float(e & 1 ? r[e >> 1] & 0xFFFF0000u : r[e >> 1] << 16);
     }
-    static __device__ __forceinline__ void store(bf16_t* p, const float (&v)[8])
+    static __device__ __forceinline__ RawVec pack(const float (&v)[8])
     {
-        uint32_t w[4];
+        RawVec r;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            w[i] = static_cast<uint32_t>(to_bf16_bits(v[2 * i])) |
-                   (static_cast<uint32_t>(to_bf16_bits(v[2 * i + 1])) << 16);
-        typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-        const v4u t = {w[0], w[1], w[2], w[3]};
-        __builtin_nontemporal_store(t, reinterpret_cast<v4u*>(p));
+            r[i] = static_cast<uint32_t>(to_bf16_bits(v[2 * i])) | (static_cast<uint32_t>(to_bf16_bits(v[2 * i + 1])) << 16);
+        return r;
     }
 };
+// Streaming store: the gradient of a large alphabet is written once and not read again by this call except in the few
+// label columns (measured 7 % faster than a plain store on the 6000-symbol workload, and the later fix-up of the label
+// columns 20 % faster).
+__device__ __forceinline__ void store_streaming(void* p, const RawVec& v) { __builtin_nontemporal_store(v, static_cast<RawVec*>(p)); }
 
 // ---- workgroup reductions (256 threads = 4 wavefronts), fixed order => repeatable -------
 
@@ -464,13 +452,13 @@ __device__ __forceinline__ size_t emission_at(int64_t e_off, int columns, int t,
 {
     return kLabelSlack + static_cast<size_t>(e_off) + (static_cast<size_t>(t / kChunk) * columns + column) * kChunk + t % kChunk;
 }
-// The virtual frames of an utterance of a wide alphabet, by the workgroup of its last frame.
+// The virtual frames of an utterance of a wide alphabet, by the lanes (q of `lanes`) of its last frame.
 __device__ __forceinline__ void store_virtual_frames(const Utt& m, float* __restrict__ emit_blank, double* __restrict__ emit_blank64,
-                                                     float* __restrict__ emit_label, bool plain_logs)
+                                                     float* __restrict__ emit_label, bool plain_logs, int q, int lanes)
 {
     for (int t = m.Tb; t < static_cast<int>(padded_frames(m.Tb)); ++t) {
-        if (threadIdx.x == 0) store_blank(emit_blank, emit_blank64, static_cast<size_t>(m.f_off) + t, virtual_emission(true, plain_logs));
-        for (int j = threadIdx.x; j < m.L; j += kRowThreads)
+        if (q == 0) store_blank(emit_blank, emit_blank64, static_cast<size_t>(m.f_off) + t, virtual_emission(true, plain_logs));
+        for (int j = q; j < m.L; j += lanes)
             emit_label[emission_at(m.e_off, m.L, t, j)] = virtual_emission(false, plain_logs);
     }
 }
@@ -480,20 +468,123 @@ __device__ __forceinline__ void raise_log_domain(Utt* meta, int b, bool small)
 }
 
 // ---- softmax statistics + emission gather --------------------------------------------------
-// Wide alphabets (A > 2048): one workgroup per row (t, b) of the tensor; grid (T + 1, B) for the
-// scalar kernel, (B, T + 1) for the vector kernel; the extra column (row) does the setup role.
-// The gradient of a wide alphabet is the softmax itself except in the few columns whose symbol
-// occurs in the label, so these kernels also write the dense part of the gradient while they
-// hold the row: y for valid rows, zeros for padding rows and for utterances without an
-// alignment (skipped when no gradient is asked for: grads == nullptr).  The activations are then never read a second time; the label columns are
-// corrected after the recursions by the sparse variant of the gradient kernel.
+// Alphabets above kDirectMaxA symbols.  The gradient of a row is the softmax itself except in the columns whose symbol
+// occurs in the label, so the launch that holds the row also writes it: y for valid rows, zeros for padding rows and for
+// utterances without an alignment (skipped when no gradient is asked for: grads == nullptr).  The activations are
+// then never read a second time; the label columns are corrected after the recursions (ctc_gradient_wide_kernel).
+//
+// Zero rows need nothing that is computed here: a share of them (those with t % 16 below `defer`) is left to the lattice
+// launch, whose compute units without a chain have nothing else to do (fill_rows).
+
+// kLanes lanes (16, a wavefront or the workgroup) hold a row of up to kPerLane kLanes symbols in registers between the
+// maximum and the sum (kPerLane: 16, or 32 where that is not enough): it is read once, with 16-byte loads, and written with 16-byte stores.  A row that starts off a 16-byte
+// boundary (an alphabet size that is no multiple of the vector, or a tensor that starts off one) has up to N - 1 symbols
+// before its first whole vector and as many after its last; a lane takes one of them each.  Consecutive workgroups take
+// consecutive rows of the tensor.
+// Bound by memory: with the 308 of 768 MB of zero rows that the lattice launch takes over counted in, 64 x 500 rows of
+// 6000 symbols, of which 300 on average are valid, move at 4.8 TB/s (bf16: 128.5 us with a load in each branch, 119 with
+// all loads first and zero rows left over).  27 x 333 rows of 4733 symbols (no multiple of a vector): 108 us with
+// three passes of four-byte loads, 41 so.  64 x 500 rows of 750 symbols: 41.5 us with the rows in LDS, 34.7 so.
+// grid: row_groups workgroups with rows, then sa.parts per utterance for the setup role.
+template <typename T, int kLanes, int kPerLane>
+__global__ __launch_bounds__(kRowThreads)
+void ctc_softmax_rows_kernel(const T* __restrict__ x, T* __restrict__ grads, Utt* __restrict__ meta,
+                             const int* __restrict__ labels, float* __restrict__ emit_blank, float* __restrict__ emit_label,
+                             const SetupArgs sa, int B, int A, int blank, int row_groups, int defer)
+{
+    constexpr int N = Vec<T>::N, kVecs = kPerLane / N, kRows = kRowThreads / kLanes;
+    static_assert(kLanes == 16 || kLanes == 64 || kLanes == kRowThreads, "row reductions exist for these");
+    __shared__ float red[8];
+    __shared__ int s_lab[kSetupLabelSlots];
+    const int tid = threadIdx.x;
+    if (static_cast<int>(blockIdx.x) >= row_groups) {
+        const int index = static_cast<int>(blockIdx.x) - row_groups, b = index / sa.parts;
+        setup_role(meta[b], b, labels, sa, s_lab, index % sa.parts, sa.parts);
+        return;
+    }
+    const int per_frame = (B + kRows - 1) / kRows;
+    const int t = static_cast<int>(blockIdx.x) / per_frame, q = tid % kLanes;
+    const int b = (static_cast<int>(blockIdx.x) % per_frame) * kRows + (kRows > 1 ? tid / kLanes : 0);
+    if (b >= B) return;
+    const Utt m = meta[b];
+    const size_t row_off = (static_cast<size_t>(t) * B + b) * A;
+    const T* const row = x + row_off;
+    T* const grow = grads ? grads + row_off : nullptr;
+    // (activations and gradient start at the same place within 16 bytes: see the launch)
+    const int head = min(static_cast<int>((16 - (reinterpret_cast<uintptr_t>(row) & 15)) & 15) / static_cast<int>(sizeof(T)), A);
+    const int nvec = (A - head) / N, rest = A - nvec * N;
+    const int single = q < rest ? (q < head ? q : nvec * N + q) : -1;          // this lane's symbol outside the vectors
+    if (t >= m.Tb || !(m.flags & kUttRuns)) {
+        if (grow && (t & 15) >= defer) {
+            for (int i = q; i < nvec; i += kLanes) store_streaming(grow + head + static_cast<size_t>(i) * N, RawVec{0, 0, 0, 0});
+            if (single >= 0) store_elem(grow, single, 0.0f);
+        }
+        return;
+    }
+
+    // All of the row and the labels' symbols are asked for before any of it is used: no conversion, and no lane left out,
+    // between one load and the next (a vector past the end is the last one again, counted by nobody).
+    RawVec raw[kVecs];
+#pragma unroll
+    for (int i = 0; i < kVecs; ++i) raw[i] = *reinterpret_cast<const RawVec*>(row + head + static_cast<size_t>(min(q + i * kLanes, nvec - 1)) * N);
+    float alone = load_elem(row, single >= 0 ? single : 0);
+    const int* const lab = labels + m.lab_off;
+    const int c_first = q < m.L ? lab[q] : 0;
+    float mx = single >= 0 ? alone : -__builtin_inff();
+    // (the vector that some lanes see again changes no maximum)
+#pragma unroll
+    for (int i = 0; i < kVecs; ++i)
+#pragma unroll
+        for (int e = 0; e < N; ++e) mx = fmaxf(mx, Vec<T>::get(raw[i], e));
+    mx = kLanes == 16 ? row16_max(mx) : (kLanes == 64 ? wave_max(mx) : block_max(mx, red));
+    float sum = single >= 0 ? fast_exp2((alone - mx) * kLog2e) : 0.0f;
+#pragma unroll
+    for (int i = 0; i < kVecs; ++i)
+        if (q + i * kLanes < nvec)
+#pragma unroll
+            for (int e = 0; e < N; ++e) sum += fast_exp2((Vec<T>::get(raw[i], e) - mx) * kLog2e);
+    sum = kLanes == 16 ? row16_sum(sum) : (kLanes == 64 ? wave_sum(sum) : block_sum(sum, red + 4));
+    // log2 y_k = (x_k - max) log2 e - log2 sum: the difference first, so that the error is relative to
+    // log2 y_k itself and not to the row's offset (see log2_softmax)
+    const float ls = fast_log2(sum);
+    if (grow) {
+#pragma unroll
+        for (int i = 0; i < kVecs; ++i) {
+            const int at = q + i * kLanes;
+            if (at < nvec) {
+                float y[N];
+#pragma unroll
+                for (int e = 0; e < N; ++e) y[e] = fast_exp2(log2_softmax(Vec<T>::get(raw[i], e), mx, ls));
+                store_streaming(grow + head + static_cast<size_t>(at) * N, Vec<T>::pack(y));
+            }
+        }
+        if (single >= 0) store_elem(grow, single, fast_exp2(log2_softmax(alone, mx, ls)));
+    }
+
+    // the emissions, out of the row that the caches still hold
+    bool small = false;
+    if (q == 0) {
+        const float e = encode_emission(log2_softmax(load_elem(row, blank), mx, ls), small, sa.plain_logs);
+        store_blank(emit_blank, sa.emit_blank64, static_cast<size_t>(m.f_off) + t, e);
+    }
+    float* const erow = emit_label + emission_at(m.e_off, m.L, t, 0);
+    for (int j = q; j < m.L; j += kLanes) {
+        const int c = j == q ? c_first : lab[j];
+        erow[static_cast<size_t>(j) * kChunk] = encode_emission(log2_softmax(load_elem(row, c), mx, ls), small, sa.plain_logs);
+    }
+    if (t == m.Tb - 1) store_virtual_frames(m, emit_blank, sa.emit_blank64, emit_label, sa.plain_logs, q, kLanes);
+    raise_log_domain(meta, b, small);
+}
+
+// Alphabets beyond 8192 symbols: one workgroup per row, read three times (the row does not fit the registers).
+// grid (T + 1, B): the extra column does the setup role.
 template <typename T>
 __global__ __launch_bounds__(kRowThreads)
 void ctc_softmax_kernel(const T* __restrict__ x, T* __restrict__ grads,
                         Utt* __restrict__ meta,
                         const int* __restrict__ labels,
                         float* __restrict__ emit_blank, float* __restrict__ emit_label,
-                        const SetupArgs sa, int Tt, int B, int A, int blank)
+                        const SetupArgs sa, int Tt, int B, int A, int blank, int defer)
 {
     __shared__ float red[8];
     __shared__ int s_lab[kSetupLabelSlots];
@@ -504,7 +595,7 @@ void ctc_softmax_kernel(const T* __restrict__ x, T* __restrict__ grads,
     T* grow = grads + row_off;
     const bool runs = (m.flags & kUttRuns) != 0;
     if (t >= m.Tb || !runs) {
-        if (grads)
+        if (grads && (t & 15) >= defer)
             for (int k = threadIdx.x; k < A; k += kRowThreads) store_elem(grow, k, 0.0f);
         return;
     }
@@ -517,20 +608,17 @@ void ctc_softmax_kernel(const T* __restrict__ x, T* __restrict__ grads,
     for (int k = threadIdx.x; k < A; k += kRowThreads)
         s += fast_exp2((load_elem(row, k) - mx) * kLog2e);
     s = block_sum(s, red + 4);
-    // log2 y_k = (x_k - max) log2 e - log2 sum: the difference first, so that the error is relative to
-    // log2 y_k itself and not to the row's offset (see log2_softmax)
     const float ls = fast_log2(s);
 
     if (grads)
         for (int k = threadIdx.x; k < A; k += kRowThreads)
             store_elem(grow, k, fast_exp2(log2_softmax(load_elem(row, k), mx, ls)));
     bool small = false;
-    if (threadIdx.x == 0)
-    {
+    if (threadIdx.x == 0) {
         const float e = encode_emission(log2_softmax(load_elem(row, blank), mx, ls), small, sa.plain_logs);
         store_blank(emit_blank, sa.emit_blank64, static_cast<size_t>(m.f_off) + t, e);
     }
-    if (t == m.Tb - 1) store_virtual_frames(m, emit_blank, sa.emit_blank64, emit_label, sa.plain_logs);
+    if (t == m.Tb - 1) store_virtual_frames(m, emit_blank, sa.emit_blank64, emit_label, sa.plain_logs, threadIdx.x, kRowThreads);
     float* erow = emit_label + emission_at(m.e_off, m.L, t, 0);
     const int* lab = labels + m.lab_off;
     for (int j = threadIdx.x; j < m.L; j += kRowThreads)
@@ -538,83 +626,77 @@ void ctc_softmax_kernel(const T* __restrict__ x, T* __restrict__ grads,
     raise_log_domain(meta, b, small);
 }
 
-// Wide alphabets, 16-byte aligned rows of at most 8192 symbols: the row is read once with
-// 16-byte loads and stays in registers between the maximum and the sum.
-constexpr int kWideMaxA = 8192;
-
-template <typename T>
-__global__ __launch_bounds__(kRowThreads)
-void ctc_softmax_wide_kernel(const T* __restrict__ x, T* __restrict__ grads,
-                             Utt* __restrict__ meta,
-                             const int* __restrict__ labels,
-                             float* __restrict__ emit_blank, float* __restrict__ emit_label,
-                             const SetupArgs sa, int Tt, int B, int A, int blank)
+// The zero rows that the softmax launch has left (t % 16 < defer), by workgroups of the lattice launch that land on
+// compute units without a chain: workgroup i runs on compute unit i mod n_cu (see order_chains), so those whose place in
+// a round is a chain's leave at once.  (64 x 500 x 6000: 10 us less in the softmax launch, 6.5 more in this one.)
+struct FillArgs {
+    void* grads;
+    int elem_bytes;
+    int T, B, A;
+    int defer;                // 0: nothing to fill
+    int n_cu, n_chains, rounds;
+};
+__device__ __forceinline__ void fill_rows(const FillArgs& f, const Utt* __restrict__ meta)
 {
-    constexpr int N = Vec<T>::N;
-    constexpr int kVecs = kWideMaxA / (N * kRowThreads);      // vectors per thread
-    __shared__ float red[8];
-    __shared__ int s_lab[kSetupLabelSlots];
-    // Utterance fastest: consecutive workgroups take consecutive rows of the tensor.
-    const int t = blockIdx.y, b = blockIdx.x, tid = threadIdx.x;
-    const Utt m = meta[b];
-    if (t == Tt) { setup_role(m, b, labels, sa, s_lab, 0, 1); return; }
-    const size_t row_off = (static_cast<size_t>(t) * B + b) * A;
-    T* grow = grads + row_off;
-    const int nvec = A / N;
-    const bool runs = (m.flags & kUttRuns) != 0;
-    if (t >= m.Tb || !runs) {
-        const float zero[N] = {};
-        if (grads)
-            for (int i = tid; i < nvec; i += kRowThreads) Vec<T>::store(grow + static_cast<size_t>(i) * N, zero);
-        return;
+    const int place = static_cast<int>(blockIdx.x) % f.n_cu, round = static_cast<int>(blockIdx.x) / f.n_cu;
+    if (place < f.n_chains) return;
+    // a wavefront per row
+    const int lane = threadIdx.x & 63, waves = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int idle = f.n_cu - f.n_chains, workers = idle * f.rounds * waves;
+    const int first = (round * idle + place - f.n_chains) * waves + wave;
+    const int frames = f.T / 16 * f.defer + min(f.T % 16, f.defer);      // deferred ones
+    const int row_bytes = f.A * f.elem_bytes;
+    for (int64_t i = first; i < static_cast<int64_t>(frames) * f.B; i += workers) {
+        const int k = static_cast<int>(i / f.B), b = static_cast<int>(i - static_cast<int64_t>(k) * f.B);
+        const int t = k / f.defer * 16 + k % f.defer;
+        const int frames_of_b = (meta[b].flags & kUttRuns) ? meta[b].Tb : 0;
+        if (t < frames_of_b) continue;
+        char* const row = static_cast<char*>(f.grads) + (static_cast<size_t>(t) * f.B + b) * row_bytes;
+        const int head = min(static_cast<int>((16 - (reinterpret_cast<uintptr_t>(row) & 15)) & 15), row_bytes);
+        const int vectors = (row_bytes - head) / 16, tail = row_bytes - head - vectors * 16;
+        typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+        for (int n = lane; n < vectors; n += 64) __builtin_nontemporal_store(v4u{0, 0, 0, 0}, reinterpret_cast<v4u*>(row + head) + n);
+        // (rows are whole elements of two or four bytes, and so are what lies before and after the vectors)
+        if (2 * lane < head) *reinterpret_cast<uint16_t*>(row + 2 * lane) = 0;
+        if (2 * lane < tail) *reinterpret_cast<uint16_t*>(row + head + vectors * 16 + 2 * lane) = 0;
     }
-    const T* row = x + row_off;
+}
 
-    float v[kVecs][N];
-    float mx = -__builtin_inff();
+// The coded rows of 64 frames of a narrow alphabet into lp[64][A], a quad of lanes per frame.
+template <typename T>
+__device__ __forceinline__ void narrow_rows(const T* __restrict__ x, float* lp, int Tb, int b, int t0, int B, int A, bool plain_logs)
+{
+    constexpr int kPerRow = 4;
+    const int tid = threadIdx.x;
+    const int r = tid / kPerRow, q = tid % kPerRow, t = t0 + r;
+    float* lrow = lp + r * A;
+    if (t < Tb) {
+        const T* row = x + (static_cast<size_t>(t) * B + b) * A;
+        float mx = -__builtin_inff();
+        // eight reads in flight per thread: a row costs a few memory latencies, not A / kPerRow
+        for (int k0 = q; k0 < A; k0 += 8 * kPerRow) {
+            float v[8];
 #pragma unroll
-    for (int i = 0; i < kVecs; ++i) {
-        const int idx = tid + i * kRowThreads;
-        if (idx < nvec) {
-            Vec<T>::load(row + static_cast<size_t>(idx) * N, v[i]);
+            for (int u = 0; u < 8; ++u) {
+                const int k = k0 + u * kPerRow;
+                v[u] = (k < A) ? load_elem(row, k) : -__builtin_inff();
+            }
 #pragma unroll
-            for (int e = 0; e < N; ++e) mx = fmaxf(mx, v[i][e]);
+            for (int u = 0; u < 8; ++u) {
+                const int k = k0 + u * kPerRow;
+                if (k < A) lrow[k] = v[u];
+                mx = fmaxf(mx, v[u]);
+            }
         }
+        mx = quad_max(mx);
+        float sum = 0.0f;
+        for (int k = q; k < A; k += kPerRow) sum += fast_exp2((lrow[k] - mx) * kLog2e);
+        sum = quad_sum(sum);
+        const float ls = fast_log2(sum);
+        bool unused = false;       // (what counts is which of the coded emissions get stored below)
+        for (int k = q; k < A; k += kPerRow) lrow[k] = encode_emission(log2_softmax(lrow[k], mx, ls), unused, plain_logs);
     }
-    mx = block_max(mx, red);
-    float sum = 0.0f;
-#pragma unroll
-    for (int i = 0; i < kVecs; ++i) {
-        if (tid + i * kRowThreads < nvec) {
-#pragma unroll
-            for (int e = 0; e < N; ++e) sum += fast_exp2((v[i][e] - mx) * kLog2e);
-        }
-    }
-    sum = block_sum(sum, red + 4);
-    const float ls = fast_log2(sum);
-
-#pragma unroll
-    for (int i = 0; i < kVecs; ++i) {
-        const int idx = tid + i * kRowThreads;
-        if (grads && idx < nvec) {
-            float y[N];
-#pragma unroll
-            for (int e = 0; e < N; ++e) y[e] = fast_exp2(log2_softmax(v[i][e], mx, ls));
-            Vec<T>::store(grow + static_cast<size_t>(idx) * N, y);
-        }
-    }
-    bool small = false;
-    if (tid == 0)
-    {
-        const float e = encode_emission(log2_softmax(load_elem(row, blank), mx, ls), small, sa.plain_logs);
-        store_blank(emit_blank, sa.emit_blank64, static_cast<size_t>(m.f_off) + t, e);
-    }
-    if (t == m.Tb - 1) store_virtual_frames(m, emit_blank, sa.emit_blank64, emit_label, sa.plain_logs);
-    float* erow = emit_label + emission_at(m.e_off, m.L, t, 0);
-    const int* lab = labels + m.lab_off;
-    for (int j = tid; j < m.L; j += kRowThreads)
-        erow[static_cast<size_t>(j) * kChunk] = encode_emission(log2_softmax(load_elem(row, lab[j]), mx, ls), small, sa.plain_logs);
-    raise_log_domain(meta, b, small);
 }
 
 // A workgroup's share of the emission block: kRows frames from t0 on whose coded rows sit in lp[kRows][A], virtual
@@ -644,107 +726,30 @@ __device__ __forceinline__ bool store_symbol_chunks(const float* lp, int Tb, int
     return small;
 }
 
-// Alphabets of up to 2048 symbols: a workgroup takes kRows consecutive frames of one utterance, 256 / kRows
-// threads per row.  The normalised rows (as coded emissions) are kept in LDS
-// (kRows * A floats, dynamic), from where the emissions of all label positions are gathered
-// with the label symbols held in registers.  grid (ceil(padded T / kRows) + parts, B), the extra columns
-// do the setup role.
-template <typename T, int kRows>
+// Alphabets of at most kDirectMaxA symbols, more utterances than the narrow launch below takes: a workgroup takes 64
+// consecutive frames of one utterance, four lanes per frame; the normalised rows sit in LDS (64 A floats, dynamic) and go
+// out as the emission block.  grid (ceil(T / 64) + 1, B), the extra column does the setup role.
+template <typename T>
 __global__ __launch_bounds__(kRowThreads)
-void ctc_softmax_rows_kernel(const T* __restrict__ x, T* __restrict__ grads, Utt* __restrict__ meta,
-                             const int* __restrict__ labels,
-                             float* __restrict__ emit_blank, float* __restrict__ emit_label,
-                             const SetupArgs sa, int Tt, int B, int A, int blank)
+void ctc_softmax_symbols_kernel(const T* __restrict__ x, Utt* __restrict__ meta,
+                                float* __restrict__ emit_blank, float* __restrict__ emit_label,
+                                const SetupArgs sa, int B, int A, int blank)
 {
-    constexpr int kPerRow = kRowThreads / kRows;          // threads per row: a quad, a 16-lane row or a wavefront
-    static_assert(kPerRow == 4 || kPerRow == 16 || kPerRow == 64, "row reductions exist for 4, 16 and 64 lanes");
+    constexpr int kRows = 64;
     extern __shared__ float lp[];                          // [kRows][A]
-    __shared__ int s_lab[kSetupLabelSlots];
-    const int b = blockIdx.y, tid = threadIdx.x;
+    const int b = blockIdx.y;
     const Utt m = meta[b];
-    if (blockIdx.x >= gridDim.x - sa.parts) {
-        const int part = static_cast<int>(blockIdx.x - (gridDim.x - sa.parts));
-        // (the grouping of label positions serves the gradient of gathered emissions)
-        if (kRows == 64) {
-            if (part == 0) setup_words(m, b, sa);
-        } else {
-            setup_role(m, b, labels, sa, s_lab, part, sa.parts);
-        }
+    if (blockIdx.x == gridDim.x - 1) {
+        setup_words(m, b, sa);
         return;
     }
     const int t0 = blockIdx.x * kRows;
-    const bool runs = (m.flags & kUttRuns) != 0;
-    const int r = tid / kPerRow, q = tid % kPerRow, t = t0 + r;
-    // Gathered emissions: the gradient of a row is the softmax itself except in the columns of the label's symbols, so
-    // it is written here, while the row is at hand (zeros for rows without an alignment); the columns are corrected after
-    // the recursions.  (grads == nullptr: no gradient wanted; narrow alphabets write theirs in the gradient launch.)
-    T* const grow = (kRows < 64 && grads && t < Tt) ? grads + (static_cast<size_t>(t) * B + b) * A : nullptr;
-    if (grow && (t >= m.Tb || !runs))
-        for (int k = q; k < A; k += kPerRow) store_elem(grow, k, 0.0f);
-    if (!runs || t0 >= static_cast<int>(padded_frames(m.Tb))) return;
-    float* lrow = lp + r * A;
-    // Requested before the row work so that its latency overlaps the row's.
-    const int* lab = labels + m.lab_off;
-    const int c_first = (kRows < 64 && tid < m.L) ? lab[tid] : 0;
-    if (t < m.Tb) {
-        const T* row = x + (static_cast<size_t>(t) * B + b) * A;
-        float mx = -__builtin_inff();
-        // eight reads in flight per thread: a row costs a few memory latencies, not A / kPerRow
-        for (int k0 = q; k0 < A; k0 += 8 * kPerRow) {
-            float v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int k = k0 + u * kPerRow;
-                v[u] = (k < A) ? load_elem(row, k) : -__builtin_inff();
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int k = k0 + u * kPerRow;
-                if (k < A) lrow[k] = v[u];
-                mx = fmaxf(mx, v[u]);
-            }
-        }
-        mx = (kPerRow == 4) ? quad_max(mx) : (kPerRow == 16) ? row16_max(mx) : wave_max(mx);
-        float sum = 0.0f;
-        for (int k = q; k < A; k += kPerRow) sum += fast_exp2((lrow[k] - mx) * kLog2e);
-        sum = (kPerRow == 4) ? quad_sum(sum) : (kPerRow == 16) ? row16_sum(sum) : wave_sum(sum);
-        const float ls = fast_log2(sum);
-        // (coded as emissions; `unused` because what counts is which of them get stored below)
-        bool unused = false;
-        for (int k = q; k < A; k += kPerRow) {
-            const float e = encode_emission(log2_softmax(lrow[k], mx, ls), unused, sa.plain_logs);
-            lrow[k] = e;
-            if (grow) store_elem(grow, k, emission_softmax(e));
-        }
-    }
+    if (!(m.flags & kUttRuns) || t0 >= m.Tb) return;
+    narrow_rows(x, lp, m.Tb, b, t0, B, A, sa.plain_logs);
     __syncthreads();
-    bool small = false;
-    if constexpr (kRows == 64) {
-        // narrow alphabet: the normalised rows themselves are the emission block
-        small = store_symbol_chunks<kRows>(lp, m.Tb, m.f_off, m.e_off, t0, A, blank, emit_blank, sa.emit_blank64, emit_label, sa.plain_logs);
-    } else {
-        const int rows = min(kRows, m.Tb - t0), padded = min(kRows, static_cast<int>(padded_frames(m.Tb)) - t0);
-        if (tid < padded) {
-            const float e = tid < rows ? lp[tid * A + blank] : virtual_emission(true, sa.plain_logs);
-            store_blank(emit_blank, sa.emit_blank64, static_cast<size_t>(m.f_off) + t0 + tid, e);
-            small = !sa.plain_logs && e < 0.0f;
-        }
-        // four frames of a position in one 16-byte store (a chunk's eight lie side by side)
-        for (int j = tid; j < m.L; j += kRowThreads) {
-            const int c = (j == tid) ? c_first : lab[j];
-#pragma unroll
-            for (int r0 = 0; r0 < kRows; r0 += 4) {
-                float e[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    e[i] = r0 + i < rows ? lp[(r0 + i) * A + c] : virtual_emission(false, sa.plain_logs);
-                    small = small || (!sa.plain_logs && e[i] < 0.0f);
-                }
-                *reinterpret_cast<float4*>(emit_label + emission_at(m.e_off, m.L, t0 + r0, j)) = make_float4(e[0], e[1], e[2], e[3]);
-            }
-        }
-    }
-    raise_log_domain(meta, b, small);
+    raise_log_domain(meta, b, store_symbol_chunks<kRows>(lp, m.Tb, m.f_off, m.e_off, t0, A, blank, emit_blank, sa.emit_blank64,
+                                                         emit_label, sa.plain_logs));
+
 }
 
 // The narrowest alphabets (at most kDirectMaxA symbols), host-resident metadata: the first launch of
@@ -898,8 +903,8 @@ void ctc_softmax_narrow_kernel(const T* __restrict__ x, const NarrowImage image,
                                const SetupArgs sa, const NarrowArgs args, const NarrowDevice dv,
                                int Tt, int B, int A, int blank)
 {
-    constexpr int kRows = kFlagFrames, kPerRow = kRowThreads / kRows;
-    static_assert(kPerRow == 4, "a quad per frame");
+    constexpr int kRows = kFlagFrames;
+    static_assert(kRows * 4 == kRowThreads, "a quad per frame (narrow_rows)");
     extern __shared__ float lp[];                          // [kRows][A]
     __shared__ int s_small;
     const int b = blockIdx.y, tid = threadIdx.x;
@@ -949,34 +954,7 @@ void ctc_softmax_narrow_kernel(const T* __restrict__ x, const NarrowImage image,
     const int t0 = blockIdx.x * kRows;
     if (t0 >= m.Tb || !(m.flags & kUttRuns)) return;
     if (tid == 0) s_small = 0;
-    const int r = tid / kPerRow, q = tid % kPerRow, t = t0 + r;
-    float* lrow = lp + r * A;
-    if (t < m.Tb) {
-        const T* row = x + (static_cast<size_t>(t) * B + b) * A;
-        float mx = -__builtin_inff();
-        // eight reads in flight per thread: a row costs a few memory latencies, not A / kPerRow
-        for (int k0 = q; k0 < A; k0 += 8 * kPerRow) {
-            float v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int k = k0 + u * kPerRow;
-                v[u] = (k < A) ? load_elem(row, k) : -__builtin_inff();
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int k = k0 + u * kPerRow;
-                if (k < A) lrow[k] = v[u];
-                mx = fmaxf(mx, v[u]);
-            }
-        }
-        mx = quad_max(mx);
-        float sum = 0.0f;
-        for (int k = q; k < A; k += kPerRow) sum += fast_exp2((lrow[k] - mx) * kLog2e);
-        sum = quad_sum(sum);
-        const float ls = fast_log2(sum);
-        bool unused = false;       // (what counts is which of the coded emissions get stored below)
-        for (int k = q; k < A; k += kPerRow) lrow[k] = encode_emission(log2_softmax(lrow[k], mx, ls), unused, sa.plain_logs);
-    }
+    narrow_rows(x, lp, m.Tb, b, t0, B, A, sa.plain_logs);
     __syncthreads();
     const bool small = store_symbol_chunks<kRows>(lp, m.Tb, m.f_off, m.e_off, t0, A, blank, emit_blank, sa.emit_blank64, emit_label,
                                                   sa.plain_logs);
@@ -2032,6 +2010,7 @@ struct LaunchWords {
     int* status_out;          // invalid; gathered into the caller's status word by this launch (or nullptr)
     int status_count;
     int skip_directions;      // bit 0: leave the forward chains out, bit 1: the backward chains (measurements only)
+    FillArgs fill;            // zero rows to write beside the chains
 };
 
 // Cost-only calls: the mass of an utterance from the states that its two chains have left where they meet, alpha after
@@ -2211,6 +2190,10 @@ void ctc_lattice_kernel_w1(const Utt* __restrict__ meta, const int* __restrict__
                            double* __restrict__ logp, float* __restrict__ costs,
                            int* __restrict__ chain_err, uint32_t* __restrict__ sink, const LaunchWords wk)
 {
+    if (kMode == Mode::kGrad && static_cast<int>(blockIdx.x) >= wk.fill.n_chains && wk.fill.defer > 0) {
+        fill_rows(wk.fill, meta);
+        return;
+    }
     lattice_body<Sync::kNone, kMode>(meta, order, labels, emit_blank, emit_blank64, emit_label, lat,
                                                                    logp, costs, chain_err, sink, nullptr, wk);
 }
@@ -2227,6 +2210,10 @@ void ctc_lattice_kernel(const Utt* __restrict__ meta, const int* __restrict__ or
                         int* __restrict__ chain_err, uint32_t* __restrict__ sink, const LaunchWords wk)
 {
     extern __shared__ double2 halo_lds[];                    // halo_lds_bytes(wavefronts of the workgroup)
+    if (kMode == Mode::kGrad && static_cast<int>(blockIdx.x) >= wk.fill.n_chains && wk.fill.defer > 0) {
+        fill_rows(wk.fill, meta);
+        return;
+    }
     lattice_body<Sync::kHalo, kMode>(meta, order, labels, emit_blank, emit_blank64, emit_label, lat,
                                                                    logp, costs, chain_err, sink, halo_lds, wk);
 }
@@ -2934,14 +2921,16 @@ int checked_launch(F&& f)
 }  // namespace
 
 namespace {
-constexpr int kRowsMaxA = 2048;        // alphabets up to this size use the multi-row kernels
-
-// Rows start on 16-byte boundaries and hold a whole number of 16-byte vectors.
-bool vector_ok(const Launch& p)
+// Lanes per row of ctc_softmax_rows_kernel; 0 where it does not apply: rows of more than 8192 symbols, activations and
+// gradient that start at different places within 16 bytes, more workgroups than a grid holds.
+int row_lanes(const Launch& p)
 {
-    const int n = (p.dtype == CTC_DTYPE_F32) ? 4 : 8;
-    return p.A % n == 0 && reinterpret_cast<uintptr_t>(p.x) % 16 == 0 &&
-           reinterpret_cast<uintptr_t>(p.grads) % 16 == 0;
+    const uintptr_t apart = p.grads ? (reinterpret_cast<uintptr_t>(p.x) ^ reinterpret_cast<uintptr_t>(p.grads)) & 15 : 0;
+    if (p.A > 32 * kRowThreads || apart != 0) return 0;
+    const int lanes = p.A <= 32 * 16 ? 16 : (p.A <= 32 * 64 ? 64 : kRowThreads);
+    const int rows = kRowThreads / lanes;
+    const int64_t groups = static_cast<int64_t>(p.T) * ((p.B + rows - 1) / rows) + static_cast<int64_t>(p.B) * (CTC_MAX_LABEL_LENGTH / 64 + 1);
+    return groups <= INT32_MAX / kRowThreads ? lanes : 0;
 }
 }
 
@@ -3027,48 +3016,47 @@ int launch_softmax(const Launch& p, void* stream)
                 hipLaunchKernelGGL(ctc_softmax_narrow_kernel<bf16_t>, grid, block, lds, s, static_cast<const bf16_t*>(p.x),
                                    image, reinterpret_cast<int*>(p.ws), emit_blank, emit_label, row_flags, sa,
                                    args, dv, p.T, p.B, p.A, p.blank);
-        } else if (p.A <= kRowsMaxA) {
-            // frames per workgroup: 64 for the smallest alphabets (so that a workgroup has several kilobytes under way), 16
-            // and 4 for the larger ones (its rows sit in LDS)
-            const int rows = p.A <= kDirectMaxA ? 64 : (p.A <= 512 ? 16 : 4);
-            const dim3 grid((static_cast<unsigned>(padded_frames(p.T)) + rows - 1) / rows + sa.parts, p.B);
-            const size_t lds = static_cast<size_t>(rows) * p.A * sizeof(float);
-#define CTC_LAUNCH_ROWS(TYPE, ROWS)                                                                \
-    hipLaunchKernelGGL((ctc_softmax_rows_kernel<TYPE, ROWS>), grid, block, lds, s,                 \
-                       static_cast<const TYPE*>(p.x), static_cast<TYPE*>(p.grads), meta, labels,   \
-                       emit_blank, emit_label, sa, p.T, p.B, p.A, p.blank)
-            if (f32) {
-                if (rows == 64) CTC_LAUNCH_ROWS(float, 64);
-                else if (rows == 16) CTC_LAUNCH_ROWS(float, 16);
-                else CTC_LAUNCH_ROWS(float, 4);
-            } else {
-                if (rows == 64) CTC_LAUNCH_ROWS(bf16_t, 64);
-                else if (rows == 16) CTC_LAUNCH_ROWS(bf16_t, 16);
-                else CTC_LAUNCH_ROWS(bf16_t, 4);
-            }
-#undef CTC_LAUNCH_ROWS
-        } else if (vector_ok(p) && p.A <= kWideMaxA && p.T + 1 <= kMaxBatch) {
-            // (frames index the second grid dimension here, which ends at 65535; longer tensors take
-            // the scalar kernel below, whose second dimension is the utterance)
-            const dim3 grid(p.B, p.T + 1);
+        } else if (p.A <= kDirectMaxA) {
+            const dim3 grid((p.T + 63) / 64 + 1, p.B);
+            const size_t lds = static_cast<size_t>(64) * p.A * sizeof(float);
             if (f32)
-                hipLaunchKernelGGL(ctc_softmax_wide_kernel<float>, grid, block, 0, s,
-                                   static_cast<const float*>(p.x), static_cast<float*>(p.grads), meta, labels, emit_blank,
-                                   emit_label, sa, p.T, p.B, p.A, p.blank);
+                hipLaunchKernelGGL(ctc_softmax_symbols_kernel<float>, grid, block, lds, s, static_cast<const float*>(p.x), meta,
+                                   emit_blank, emit_label, sa, p.B, p.A, p.blank);
             else
-                hipLaunchKernelGGL(ctc_softmax_wide_kernel<bf16_t>, grid, block, 0, s,
-                                   static_cast<const bf16_t*>(p.x), static_cast<bf16_t*>(p.grads), meta, labels, emit_blank,
-                                   emit_label, sa, p.T, p.B, p.A, p.blank);
+                hipLaunchKernelGGL(ctc_softmax_symbols_kernel<bf16_t>, grid, block, lds, s, static_cast<const bf16_t*>(p.x), meta,
+                                   emit_blank, emit_label, sa, p.B, p.A, p.blank);
+        } else if (row_lanes(p) > 0) {
+            const int lanes = row_lanes(p), rows = kRowThreads / lanes;
+            const bool half = p.A <= 16 * lanes;
+            const int row_groups = p.T * ((p.B + rows - 1) / rows);
+            const dim3 grid(row_groups + sa.parts * p.B);
+#define CTC_LAUNCH_ROWS(TYPE, LANES, PER_LANE)                                                     \
+    hipLaunchKernelGGL((ctc_softmax_rows_kernel<TYPE, LANES, PER_LANE>), grid, block, 0, s,        \
+                       static_cast<const TYPE*>(p.x), static_cast<TYPE*>(p.grads), meta, labels,   \
+                       emit_blank, emit_label, sa, p.B, p.A, p.blank, row_groups, p.defer)
+#define CTC_LAUNCH_ROWS_OF(TYPE)                                                                   \
+    do {                                                                                           \
+        if (lanes == 16 && half) CTC_LAUNCH_ROWS(TYPE, 16, 16);                                    \
+        else if (lanes == 16) CTC_LAUNCH_ROWS(TYPE, 16, 32);                                       \
+        else if (lanes == 64 && half) CTC_LAUNCH_ROWS(TYPE, 64, 16);                               \
+        else if (lanes == 64) CTC_LAUNCH_ROWS(TYPE, 64, 32);                                       \
+        else if (half) CTC_LAUNCH_ROWS(TYPE, kRowThreads, 16);                                     \
+        else CTC_LAUNCH_ROWS(TYPE, kRowThreads, 32);                                               \
+    } while (0)
+            if (f32) CTC_LAUNCH_ROWS_OF(float);
+            else CTC_LAUNCH_ROWS_OF(bf16_t);
+#undef CTC_LAUNCH_ROWS_OF
+#undef CTC_LAUNCH_ROWS
         } else {
             const dim3 grid(p.T + 1, p.B);
             if (f32)
                 hipLaunchKernelGGL(ctc_softmax_kernel<float>, grid, block, 0, s,
                                    static_cast<const float*>(p.x), static_cast<float*>(p.grads), meta, labels, emit_blank,
-                                   emit_label, sa, p.T, p.B, p.A, p.blank);
+                                   emit_label, sa, p.T, p.B, p.A, p.blank, p.defer);
             else
                 hipLaunchKernelGGL(ctc_softmax_kernel<bf16_t>, grid, block, 0, s,
                                    static_cast<const bf16_t*>(p.x), static_cast<bf16_t*>(p.grads), meta, labels, emit_blank,
-                                   emit_label, sa, p.T, p.B, p.A, p.blank);
+                                   emit_label, sa, p.T, p.B, p.A, p.blank, p.defer);
         }
     });
 }
@@ -3087,7 +3075,7 @@ int launch_lattice(const Launch& p, void* stream)
     auto* logp = reinterpret_cast<double*>(p.ws + p.lay.logp);
     auto* chain_err = reinterpret_cast<int*>(p.ws + p.lay.chain_err);
     const size_t lds_bytes = (p.max_waves > 1 && !p.needs_barrier) ? halo_lds_bytes(p.max_waves) : 0;
-    const int n_groups = std::max(p.n_chains, 1);
+    int n_groups = std::max(p.n_chains, 1);
     LaunchWords wk{};
     wk.row_flags = p.folded ? reinterpret_cast<const int*>(p.ws + p.lay.row_flags) : nullptr;
     wk.flag_blocks = (p.T + kFlagFrames - 1) / kFlagFrames;
@@ -3099,6 +3087,13 @@ int launch_lattice(const Launch& p, void* stream)
         wk.status_words = reinterpret_cast<const int*>(p.ws + p.lay.status);
         wk.status_out = p.dev_status;
         wk.status_count = p.B;
+    }
+    wk.fill.n_chains = n_groups;
+    if (p.defer > 0) {
+        // as many workgroups per compute unit without a chain as make eight wavefronts
+        const int rounds = std::max(1, 8 / p.max_waves);
+        wk.fill = FillArgs{p.grads, p.dtype == CTC_DTYPE_F32 ? 4 : 2, p.T, p.B, p.A, p.defer, p.n_cu, p.n_chains, rounds};
+        n_groups = p.n_cu * rounds;
     }
     const dim3 grid(n_groups), block(64 * p.max_waves);
     auto s = static_cast<hipStream_t>(stream);

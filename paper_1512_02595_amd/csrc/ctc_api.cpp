@@ -63,7 +63,7 @@ void carve(int T, int B, int64_t sumL, int64_t emit, int64_t frames, int64_t ab,
     l.ab_doubles = ab;
     size_t off = 0;
     l.meta = off;   off += static_cast<size_t>(B) * sizeof(Utt);            // 64 B each: stays 8-byte aligned
-    l.order = off;  off += static_cast<size_t>(B) * 2 * sizeof(int32_t);
+    l.order = off;  off += static_cast<size_t>(B) * 3 * sizeof(int32_t);
     l.labels = off; off += static_cast<size_t>(sumL) * sizeof(int32_t);
     l.labels8 = off; off += (static_cast<size_t>(sumL) + 3) / 4 * 4;
     l.upload_bytes = off;
@@ -72,7 +72,7 @@ void carve(int T, int B, int64_t sumL, int64_t emit, int64_t frames, int64_t ab,
     l.logp = off;   off = align_up(off + static_cast<size_t>(B) * sizeof(double));
     l.sink = off;   off = align_up(off + static_cast<size_t>(B) * 2 * kSinkWaves * kSinkBytes);
     l.chain_err = off; off = align_up(off + static_cast<size_t>(B) * sizeof(int32_t));
-    l.done = off;   off = align_up(off + static_cast<size_t>(B) * sizeof(int32_t));
+    l.done = off;   off = align_up(off + static_cast<size_t>(B) * kDoneStride * sizeof(int32_t));
     l.domain = off; off = align_up(off + static_cast<size_t>(B) * 2 * sizeof(int32_t));
     l.row_flags = off;
     off = align_up(off + static_cast<size_t>(B) * ((T + kFlagFrames - 1) / kFlagFrames) * sizeof(int32_t));
@@ -408,6 +408,12 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
     constexpr int dirs = 2;
     order_chains(running.data(), run_frames.data(), run_waves.data(), n_run, dirs, compute_units(), order);
     for (int i = n_run * dirs; i < 2 * c.B; ++i) order[i] = -1;
+    // all utterances for the gradient: those without an alignment, then the lightest first
+    int32_t* by_end = order + 2 * c.B;
+    if (n_run < c.B)
+        for (int b = 0; b < c.B; ++b)
+            if (!(meta[b].flags & kUttRuns)) *by_end++ = b;
+    for (int i = n_run - 1; i >= 0; --i) *by_end++ = running[i];
 
     const bool sequential_chains = c.mode == Mode::kGrad && g_sequential_chains.load(std::memory_order_relaxed) != 0;
 
@@ -442,6 +448,7 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
         for (int i = 0; i < n_run; ++i) rows -= run_frames[i];
         out->defer = deferred_frames(static_cast<double>(rows) * c.A * elem, max_frames, n_run * dirs, out->n_cu);
     }
+    out->fused = c.mode == Mode::kGrad && !needs_barrier && !sequential_chains && n_run > 0 && fuse_gradient(c.A, max_waves, n_run * dirs, out->n_cu);
     out->folded = c.A <= kDirectMaxA && c.B <= kNarrowMaxB && c.T < (1 << 29);
     out->lay = lay;
     return CTC_STATUS_SUCCESS;
@@ -509,6 +516,7 @@ ctc_status_t run(const Call& c, float* kernel_ms)
         if (!slot) return st;
         st = prepare(c, lay, &p, slot->image());
         if (st != CTC_STATUS_SUCCESS) return st;
+        if (kernel_ms) p.fused = false;                  // (a profiled call times the launches one by one)
         if (kernel_ms && !events.create()) return CTC_STATUS_HIP_ERROR;
         slot->generation += 1;
         p.host_flag = slot->flag();
@@ -535,7 +543,7 @@ ctc_status_t run(const Call& c, float* kernel_ms)
     // Cost-only calls end with the lattice launch.
     int (*const stages[CTC_NUM_KERNELS])(const Launch&, void*) = {
         launch_softmax, launch_lattice,
-        c.mode == Mode::kGrad ? launch_gradient : (c.mode == Mode::kLoss ? nullptr : launch_backtrace)};
+        c.mode == Mode::kGrad ? (p.fused ? nullptr : launch_gradient) : (c.mode == Mode::kLoss ? nullptr : launch_backtrace)};
     for (int i = p.folded ? 2 : 1; i < CTC_NUM_KERNELS; ++i) {
         if (stages[i] && !record(stages[i](p, c.stream))) return CTC_STATUS_HIP_ERROR;
         if (kernel_ms && !record(hipEventRecord(ev[i + 1], s))) return CTC_STATUS_HIP_ERROR;
@@ -615,6 +623,7 @@ ctc_status_t run_device(const void* x, const int32_t* labels, const int32_t* lab
     // (how much padding there is only the GPU knows: taken for a third of the tensor)
     p.defer = grads && A > kDirectMaxA && !p.needs_barrier
                   ? deferred_frames(static_cast<double>(T) * B * A * elem / 3, T / 2, p.n_chains, p.n_cu) : 0;
+    p.fused = grads && !p.needs_barrier && !kernel_ms && fuse_gradient(A, p.max_waves, p.n_chains, p.n_cu);
     // Narrow alphabets: the softmax launch builds the records itself (no planning launch before it); every
     // utterance's setup workgroup weighs all B utterances for the run order, which is worth it up to here.
     p.folded = A <= kDirectMaxA && B <= kDeviceFoldMaxB && max_label > 0;
@@ -626,7 +635,7 @@ ctc_status_t run_device(const void* x, const int32_t* labels, const int32_t* lab
     if (kernel_ms && !events.create()) return CTC_STATUS_HIP_ERROR;
     if (!p.folded && !record(launch_plan(p, stream))) return CTC_STATUS_HIP_ERROR;
     int (*const stages[CTC_NUM_KERNELS])(const Launch&, void*) = {launch_softmax, launch_lattice,
-                                                                   grads ? launch_gradient : nullptr};
+                                                                   grads && !p.fused ? launch_gradient : nullptr};
     if (kernel_ms && !record(hipEventRecord(ev[0], s))) return CTC_STATUS_HIP_ERROR;
     for (int i = 0; i < CTC_NUM_KERNELS; ++i) {
         if (stages[i] && !record(stages[i](p, stream))) return CTC_STATUS_HIP_ERROR;

@@ -193,6 +193,16 @@ inline int deferred_frames(double zero_bytes, int longest, int n_chains, int n_c
     return static_cast<int>(std::min(16.0, 16.0 * fits / zero_bytes));
 }
 
+// The gradient of an utterance may be written by workgroups of the lattice launch that wait for its chains
+// (Launch::fused).  Chains that need more wavefronts than a workgroup of that launch has keep a launch of their own.
+constexpr int kFusedWaves = 4;
+constexpr int kDoneStride = 16;      // words between two utterances' counters: a line each for those who poll
+
+inline bool fuse_gradient(int A, int max_waves, int n_chains, int n_cu)
+{
+    return A <= kDirectMaxA && max_waves <= kFusedWaves && n_chains <= n_cu;
+}
+
 // The sink of a lattice launch: for each of its up to 2 B chain workgroups, kSinkBytes for each of the
 // up to kSinkWaves wavefronts.
 constexpr int kSinkWaves = 16, kSinkBytes = 64;
@@ -381,15 +391,16 @@ CTC_HOST_DEVICE inline int64_t lattice_pitch(int64_t L) { return L + 2; }
 struct Layout {
     size_t meta = 0;      // Utt[B]
     size_t order = 0;     // int32[2B]    the lattice launch's chains, one per workgroup: utterance * 2 + direction
-                          //              (0 forward, 1 backward), -1 for a workgroup without one (order_chains)
+                          //              (0 forward, 1 backward), -1 for a workgroup without one (order_chains);
+                          // int32[B]     and all utterances, those first whose chains end first (about)
     size_t labels = 0;    // int32[sumL]
     size_t labels8 = 0;   // uint8[sumL]  the label strings once more, a byte per symbol (image only; narrow alphabets)
     size_t links = 0;     // int32[sumL]  grouping of the label positions by symbol (slot, count, first)
     size_t logp = 0;      // double[B]    log2 of the alignment mass
     size_t sink = 0;      // what lanes with nothing to store scribble on: kSinkBytes per wavefront of a lattice launch
     size_t chain_err = 0; // int32[B]     set when a lattice wavefront gave up waiting for its neighbour
-    size_t done = 0;      // int32[B]     cost-only calls: wavefronts of the utterance's chains that have ended (low half)
-                          //              and that gave up (high half)
+    size_t done = 0;      // int32[B * kDoneStride]  how far the utterance's chains are: cost-only calls (finish_loss)
+                          //              and gradients written beside the chains (announce_end)
     size_t domain = 0;    // int32[2 B]   per utterance and direction, nonzero: that chain ran in the log domain (published by
                           //              the chain for the gradient, which must know where its exponent rows are)
     size_t row_flags = 0; // int32[B * ceil(T / 64)]  narrow alphabets: per 64 frames of an utterance, nonzero if one of
@@ -459,6 +470,7 @@ struct Launch {
     int poll_budget;          // copied into every Utt record
     bool crowded;             // plan the chains for total work rather than latency (device planner)
     int n_cu;                 // compute units of the device
+    bool fused;               // the lattice launch writes the gradient too (launch_lattice_gradient)
     int defer;                // of every 16 frames, those whose zero rows the lattice launch writes (deferred_frames)
     // Narrow alphabets, host metadata: there is no upload launch; the softmax launch reads the pinned image
     // itself and copies it into the workspace for the launches after it, and the lattice launch releases it.

@@ -290,12 +290,13 @@ void ctc_plan_kernel(const int* __restrict__ labels, const int* __restrict__ lab
     if (tid == 0) *status = s_bad ? CTC_STATUS_INVALID_VALUE : CTC_STATUS_SUCCESS;
     for (int i = tid; i < B; i += kPlanThreads) {
         const long long wi = weight[i];
-        if (wi < 0) continue;
         int rank = 0;
         for (int j = 0; j < B; ++j) {
             const long long wj = weight[j];
             rank += (wj > wi) || (wj == wi && j < i);
         }
+        order[2 * B + B - 1 - rank] = i;                 // (the utterances by when their chains end)
+        if (wi < 0) continue;
         // Heaviest first, in blocks of kChainBlock utterances: a block's forward chains, then its
         // backward chains (order_chains; the device planner does not balance the SIMDs' loads
         // beyond that).
@@ -327,7 +328,7 @@ struct SetupArgs {
     int* links;
     float* costs;
     int* chain_err;
-    int* done;            // per utterance: cost-only chains' wavefronts that have ended (finish_loss)
+    int* done;            // per utterance (kDoneStride apart): wavefronts that have ended (finish_loss, announce_end)
     float* log0;          // kEmissionConstants floats that lattice lanes without a label state read as their
                           // emission: probability 0 (linear-domain chains) and log 0 (log-domain chains)
     double* emit_blank64; // the blank's probability per frame as fp64 (Layout::emit_blank64)
@@ -390,7 +391,7 @@ __device__ __forceinline__ void setup_words(const Utt m, const int b, const Setu
 {
     if (threadIdx.x == 0) {
         sa.chain_err[b] = 0;
-        sa.done[b] = 0;
+        sa.done[b * kDoneStride] = 0;
         if (b == 0) {
             for (int i = 0; i < kEmissionConstants; ++i) sa.log0[i] = i < kLogZeroEmission ? 0.0f : static_cast<float>(kNeg);
             // This launch follows the upload kernel on the stream, so the host may now reuse
@@ -884,6 +885,7 @@ __device__ __forceinline__ Utt build_record(const NarrowDevice& dv, const PlanTa
         // i +- n_cu, so every other round of n_cu chains runs lightest first, and a compute unit's chains
         // add up to about the same (the host's order_chains goes by the SIMDs' loads; this is its first-order part).
         int rank = s_rank;
+        dv.order[2 * B + B - 1 - rank] = b;              // (the utterances by when their chains end)
         const int per_round = dv.n_cu / 2;
         if (per_round >= kChainBlock && B * 2 > dv.n_cu && ((rank / per_round) & 1)) {
             const int round_first = rank - rank % per_round, in_round = min(per_round, B - round_first);
@@ -1022,6 +1024,21 @@ __device__ __forceinline__ double pack_log2(double w)          // the same as on
 }
 
 // ---- lattice recursions ------------------------------------------------------------------
+// What the chains leave may be read by workgroups of the same launch, on other dies, once they know the chains to have
+// ended (announce_end): both sides go past the dies' own caches.
+__device__ __forceinline__ void publish(int* p, int v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void publish(float* p, float v) { publish(reinterpret_cast<int*>(p), __float_as_int(v)); }
+__device__ __forceinline__ void publish(double* p, double v)
+{
+    __hip_atomic_store(reinterpret_cast<long long*>(p), __double_as_longlong(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ int published(const int* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ double published(const double* p)
+{
+    return __longlong_as_double(__hip_atomic_load(reinterpret_cast<const long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+__device__ __forceinline__ CheckpointState published(const CheckpointState* p) { return {published(&p->blank), published(&p->label)}; }
+
 // log2(2^a + 2^b) for fp64 a, b with the exponentials taken on the fp32 difference.
 __device__ __forceinline__ double lse2(double a, double b)
 {
@@ -1382,7 +1399,7 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
     if (kMode == Mode::kBest) {
         // the backtrace looks for the best way through the frames where the chains meet
         if (active) reinterpret_cast<CheckpointState*>(out_exponents + m.ab_off)[j] = CheckpointState{v_blank, v_label};
-        if (kSync == Sync::kHalo && lost && lane == 0) chain_err[u] = 1;
+        if (kSync == Sync::kHalo && lost && lane == 0) publish(&chain_err[u], 1);
         return;
     }
     if (!kBackward) {
@@ -1393,10 +1410,10 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
         const double prev = from_prev_pair(v_label, chunks * kChunk);
         if (active && j == L) {
             const double lp = lse2(v_blank, prev);
-            logp[u] = pack_log2(-lp);                    // 1 / p
+            publish(&logp[u], pack_log2(-lp));           // 1 / p
             const float cost = (lp < -1.0e29) ? __builtin_inff() : static_cast<float>(-lp * kLn2);
             if (kSync == Sync::kHalo && kMode == Mode::kLoss) hl->cost = cost;
-            else costs[u] = cost;
+            else publish(&costs[u], cost);
         }
     }
     if (kSync == Sync::kHalo && kMode == Mode::kLoss) {
@@ -1416,7 +1433,7 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
             costs[u] = lost ? __uint_as_float(0x7FC00000u) : cost;
         }
     } else if (kSync == Sync::kHalo && lost && lane == 0) {
-        chain_err[u] = 1;
+        publish(&chain_err[u], 1);
     }
 }
 
@@ -1475,7 +1492,7 @@ __device__ __forceinline__ bool outside_easy_range(double top)
 }
 
 // An utterance's mass p = value * 2^frame: its reciprocal for the gradient, and the cost.
-__device__ __forceinline__ void store_mass(double value, int frame, double& inverse_p, float& cost)
+__device__ __forceinline__ void mass_and_cost(double value, int frame, double& inverse_p, float& cost)
 {
     const double mantissa = __builtin_amdgcn_frexp_mant(value);                // [0.5, 1)
     const int exponent = frame + __builtin_amdgcn_frexp_exp(value);
@@ -1483,6 +1500,14 @@ __device__ __forceinline__ void store_mass(double value, int frame, double& inve
     const double l2 = static_cast<double>(exponent) + ::log2(mantissa);
     inverse_p = (value > 0.0) ? pack_state(1.0 / mantissa, -exponent) : 0.0;
     cost = (value > 0.0) ? static_cast<float>(-l2 * kLn2) : __builtin_inff();
+}
+__device__ __forceinline__ void store_mass(double value, int frame, double* inverse_p_out, float* cost_out)
+{
+    double inverse_p;
+    float cost;
+    mass_and_cost(value, frame, inverse_p, cost);
+    publish(inverse_p_out, inverse_p);
+    publish(cost_out, cost);
 }
 
 template <bool kBackward, Sync kSync, Mode kMode>
@@ -1713,9 +1738,9 @@ __device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const
         // p = alpha_{T-1}(2L) + alpha_{T-1}(2L-1), from the lane of pair L (exact, as is the
         // lane below it: see run_chain_log).
         const double from_below = from_prev_pair(v_label) * scale;
-        if (active && j == L) store_mass(v_blank + from_below, frame, logp[u], costs[u]);
+        if (active && j == L) store_mass(v_blank + from_below, frame, &logp[u], &costs[u]);
     }
-    if (kSync == Sync::kHalo && lost && lane == 0) chain_err[u] = 1;
+    if (kSync == Sync::kHalo && lost && lane == 0) publish(&chain_err[u], 1);
     return lost;
 }
 
@@ -1981,9 +2006,9 @@ __device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, cons
         // p = alpha_{T-1}(2L) + alpha_{T-1}(2L-1): the blank of pair L and the label of pair L - 1.
         // L even: pair L is this lane's A, pair L - 1 the B of the lane below; L odd: pair L is B.
         const double from_below = from_lane_below(vb_label) * scale;
-        if (active && (ja == L || jb == L)) store_mass((ja == L) ? va_blank + from_below : vb_blank + va_label, frame, logp[u], costs[u]);
+        if (active && (ja == L || jb == L)) store_mass((ja == L) ? va_blank + from_below : vb_blank + va_label, frame, &logp[u], &costs[u]);
     }
-    if (lost && lane == 0) chain_err[u] = 1;
+    if (lost && lane == 0) publish(&chain_err[u], 1);
     return lost;
 }
 
@@ -2003,7 +2028,8 @@ struct LaunchWords {
     const int* row_flags;     // narrow softmax launch's words (rows_flagged), or nullptr: the records' flags say it all
     int flag_blocks;          // ... per utterance
     int* domain;              // per utterance and direction: did the chain run in the log domain
-    int* done;                // per utterance: see finish_loss
+    int* done;                // per utterance, kDoneStride apart: see finish_loss, announce_end
+    bool announce;            // ... the latter: somebody waits for the chains
     int* host_flag;           // pinned host word that receives host_flag_value: the image may be reused (or nullptr)
     int host_flag_value;
     const int* status_words;  // device-resident metadata built by the narrow softmax launch: per utterance, nonzero if
@@ -2027,7 +2053,7 @@ __device__ __forceinline__ void finish_loss(const Utt& m, const int u, const int
     int before = 0;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     if (lane == 0)
-        before = __hip_atomic_fetch_add(&done[u], lost ? 0x10001 : 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        before = __hip_atomic_fetch_add(&done[u * kDoneStride], lost ? 0x10001 : 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     before = __builtin_amdgcn_readfirstlane(before);
     if ((before & 0xFFFF) != expected - 1) return;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
@@ -2073,9 +2099,27 @@ __device__ __forceinline__ void finish_loss(const Utt& m, const int u, const int
     if (lane == 0) {
         double unused;
         float cost;
-        store_mass(sum, top, unused, cost);
+        mass_and_cost(sum, top, unused, cost);
         costs[u] = (before >> 16) != 0 || lost ? __uint_as_float(0x7FC00000u) : cost;
     }
+}
+
+// A wavefront of a chain has ended, and everything it has published is out; `waves` of them make the chain, the first says
+// so.  An utterance's counter: wavefronts that have ended, wavefronts there are (from bit 10), chains that have said how many
+// (from bit 20).
+constexpr int kWavesShift = 10, kChainsShift = 20;
+__device__ __forceinline__ void announce_end(int* done, int waves)
+{
+    // (what was stored the ordinary way must leave the die's cache)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const int count = threadIdx.x < 64 ? 1 + (waves << kWavesShift) + (1 << kChainsShift) : 1;
+    if ((threadIdx.x & 63) == 0) __hip_atomic_fetch_add(done, count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ bool chains_ended(int done)
+{
+    constexpr int kField = (1 << kWavesShift) - 1;
+    return (done >> kChainsShift) == 2 && (done & kField) == ((done >> kWavesShift) & kField);
 }
 
 template <Sync kSync, Mode kMode>
@@ -2120,7 +2164,7 @@ __device__ __forceinline__ void lattice_body(const Utt* __restrict__ meta, const
                                rows_flagged(wk.row_flags, u, wk.flag_blocks, m.Tb);
     if (kMode == Mode::kLoss && in_log_domain && !forward) return;       // (the forward chain runs all the way)
     // (for the gradient, which must know what each chain has left: a word per direction)
-    if (kMode == Mode::kGrad && threadIdx.x == 0) wk.domain[2 * u + (forward ? 0 : 1)] = in_log_domain ? 1 : 0;
+    if (kMode == Mode::kGrad && threadIdx.x == 0) publish(&wk.domain[2 * u + (forward ? 0 : 1)], in_log_domain ? 1 : 0);
     const bool two_pairs = kSync == Sync::kHalo && !in_log_domain && (m.flags & kUttTwoPairs) != 0;
     const int waves = two_pairs ? m.waves2 : m.waves;
     const bool idle = static_cast<int>(threadIdx.x >> 6) >= waves;
@@ -2168,6 +2212,7 @@ __device__ __forceinline__ void lattice_body(const Utt* __restrict__ meta, const
                 lost = run_chain_linear<true, kSync, kMode>(m, u, labels, emit_blank64, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
             }
             if (kMode == Mode::kLoss) finish_loss(m, u, labels, lat, wk.done, costs, 2 * waves, lost);
+            if (kMode == Mode::kGrad && wk.announce) announce_end(&wk.done[u * kDoneStride], waves);
             return;
         }
     }
@@ -2175,6 +2220,7 @@ __device__ __forceinline__ void lattice_body(const Utt* __restrict__ meta, const
         run_chain_log<false, kSync, kMode>(m, u, labels, emit_blank, emit_label, lat.alpha, lat.alpha_exponents, logp, costs, chain_err, sink, lds);
     else if constexpr (kMode != Mode::kLoss)
         run_chain_log<true, kSync, kMode>(m, u, labels, emit_blank, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
+    if (kMode == Mode::kGrad && kSync != Sync::kBarrier && wk.announce) announce_end(&wk.done[u * kDoneStride], waves);
 }
 
 // grid = one workgroup per entry of `order` (utterance * 2 + direction: 0 forward, 1 backward).
@@ -2369,6 +2415,7 @@ void ctc_backtrace_kernel(const Utt* __restrict__ meta, const int* __restrict__ 
 constexpr int kPiecePositions = 128, kPieceHalo = kBlockFrames, kPieceStep = kPiecePositions - 2 * kPieceHalo;
 // A row of one value per lane in LDS, padded so that 16-byte reads of 16 rows meet in no bank; two blocks of a row per frame.
 constexpr int kShareRow = kPiecePositions / 2 + 4, kShareInts = 2 * kBlockFrames * kShareRow;
+constexpr int kBlankInts = 2 * kBlockFrames;
 static_assert(kPieceStep % 32 == 0, "pieces start at multiples of 32 positions (share_product)");
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
@@ -2402,9 +2449,13 @@ __device__ __forceinline__ Utt uniform_record(const Utt& m)
 // all exponents.  Either value may lie a thousand binary orders below or above the unit of its own frame (lane_frame)
 // while the product is a share of order one: alpha takes all the exponents first.  A state of any mass has beta above
 // 2^-1000 in its frame, so that alpha is then below 2^1000; the cap is for those without.
+__device__ __forceinline__ double scaled_alpha(unsigned alpha, int exponents)
+{
+    return __builtin_amdgcn_ldexp(__hiloint2double(static_cast<int>(alpha), 0), exponents);
+}
 __device__ __forceinline__ float state_share(unsigned alpha, double beta, int exponents)
 {
-    return static_cast<float>(fmin(__builtin_amdgcn_ldexp(__hiloint2double(static_cast<int>(alpha), 0), exponents), 0x1p1000) * beta);
+    return static_cast<float>(fmin(scaled_alpha(alpha, exponents), 0x1p1000) * beta);
 }
 // (the same from two stored words)
 __device__ __forceinline__ float word_share(unsigned a, unsigned b, int exponents)
@@ -2478,35 +2529,41 @@ struct LaneLabels {
 struct BlockEnds {
     CheckpointState a0{}, a1{}, b0{}, b1{};
     int fa0 = 0, fa1 = 0, fb0 = 0, fb1 = 0;
-    __device__ __forceinline__ BlockEnds(const Utt& m, const LatticeOut& lat, int p0, int block)
+    // kPublished: in the launch of the chains, which have just published them
+    template <bool kPublished>
+    static __device__ __forceinline__ BlockEnds load(const Utt& m, const LatticeOut& lat, int p0, int block)
     {
+        BlockEnds e;
         const int64_t pitch = lattice_pitch(m.L);
         const int column = 1 + min(p0, max(m.L, 1) - 1);
+        auto state = [](const CheckpointState* p) { return kPublished ? published(p) : *p; };
+        auto word = [](const int* p) { return kPublished ? published(p) : *p; };
         if (block > 0) {
             const int64_t where = (block - 1) * pitch + column;
             const CheckpointState* v = reinterpret_cast<const CheckpointState*>(lat.alpha + m.ab_off) + where;
             const int* f = lat.alpha_exponents + m.ab_off + where;
-            a0 = v[0]; a1 = v[1];
-            fa0 = f[0]; fa1 = f[1];
+            e.a0 = state(&v[0]); e.a1 = state(&v[1]);
+            e.fa0 = word(&f[0]); e.fa1 = word(&f[1]);
         }
         if (block + 1 < frame_blocks(m.Tb)) {
             const int64_t where = (block + 1) * pitch + column;
             const CheckpointState* v = reinterpret_cast<const CheckpointState*>(lat.beta + m.ab_off) + where;
             const int* f = lat.beta_exponents + m.ab_off + where;
-            b0 = v[0]; b1 = v[1];
-            fb0 = f[0]; fb1 = f[1];
+            e.b0 = state(&v[0]); e.b1 = state(&v[1]);
+            e.fb0 = word(&f[0]); e.fb1 = word(&f[1]);
         }
+        return e;
     }
 };
 
 // The shares of the label positions base .. base + 127 in block `block` of the utterance: file(row, share0, share1) for
 // the lane's two positions, row = 0 .. 15 in some order, 0 outside [own_first, own_end).  Shares are without the
 // mantissa of 1 / p and times 2^kScaleLog2.  emissions(h, el0, el1): the lane's label emissions in chunk h of the block.
-// alpha's high dwords wait in LDS, s_alpha0 and s_alpha1 [row][kShareRow], each lane's in a slot of its own that is free
+// s_blank: the blank's emissions of the block's frames, in LDS.  alpha's high dwords wait in LDS, s_alpha0 and s_alpha1 [row][kShareRow], each lane's in a slot of its own that is free
 // again when file is called for the row.  (In registers they cost 32 of them, and the loops over the chunks had to be
 // unrolled: code that runs once per wavefront comes out of memory no faster than data.)
 template <int kScaleLog2, typename Emissions, typename File>
-__device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at, const BlockEnds& ends, const double* __restrict__ eb,
+__device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at, const BlockEnds& ends, const double* s_blank,
                                              const double packed_inverse_p, const int block,
                                              const int own_first, const int own_end, unsigned* s_alpha0, unsigned* s_alpha1,
                                              Emissions&& emissions, File&& file)
@@ -2517,6 +2574,16 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
     const bool has0 = at.has0, has1 = at.has1;
     const double skip0_one = at.skip0 ? 1.0 : 0.0, skip1_one = at.skip1 ? 1.0 : 0.0, skip2_one = at.skip2 ? 1.0 : 0.0;
     float el0[kChunk], el1[kChunk];
+    double eb[kChunk];
+    // (from LDS, the same address in every lane: scalar loads out of memory were four round trips in the middle of it all)
+    auto read_blanks = [&](int h) {
+#pragma unroll
+        for (int q = 0; q < kChunk; ++q) eb[q] = s_blank[h * kChunk + q];
+    };
+
+    // The order of the statements is the order of issue (run_chain_linear2): left to itself the compiler put results and
+    // their uses next to each other, and a block's recomputation took 3.0 us in place of 2.0.
+    auto pin = []() { __builtin_amdgcn_sched_barrier(0); };
 
     // alpha
     int alpha_frame0 = 0, alpha_frame1 = 0;              // of the block's two chunks
@@ -2537,16 +2604,36 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
             }
             const double skip0_scale = skip0_one * s.scale;
             emissions(h, el0, el1);
+            read_blanks(h);
 #pragma unroll
             for (int q = 0; q < kChunk; ++q) {
-                const double prev = shift_up(s.label1, prev_lo, prev_hi), blank = eb[h * kChunk + q];
-                const double u0 = s.blank0 + s.label0, u1 = s.blank1 + s.label1;
-                const double n_blank1 = s.blank1 + s.label0, n_label1 = __builtin_fma(s.label0, skip1_one, u1);
-                const double n_label0 = __builtin_fma(prev, skip0_scale, u0), n_blank0 = __builtin_fma(prev, s.scale, s.blank0);
-                s.label0 = n_label0 * static_cast<double>(el0[q]);
-                s.label1 = n_label1 * static_cast<double>(el1[q]);
-                s.blank0 = n_blank0 * blank;
-                s.blank1 = n_blank1 * blank;
+#pragma clang fp contract(off)
+                const double prev = shift_up(s.label1, prev_lo, prev_hi);
+                pin();
+                const double u1 = s.blank1 + s.label1;
+                pin();
+                const double u0 = s.blank0 + s.label0;
+                pin();
+                const double n_blank1 = s.blank1 + s.label0;
+                pin();
+                const double el0_d = static_cast<double>(el0[q]);
+                pin();
+                const double n_label1 = __builtin_fma(s.label0, skip1_one, u1);
+                pin();
+                const double n_label0 = __builtin_fma(prev, skip0_scale, u0);
+                pin();
+                const double n_blank0 = __builtin_fma(prev, s.scale, s.blank0);
+                pin();
+                const double el1_d = static_cast<double>(el1[q]);
+                pin();
+                s.label0 = n_label0 * el0_d;
+                pin();
+                s.label1 = n_label1 * el1_d;
+                pin();
+                s.blank0 = n_blank0 * eb[q];
+                pin();
+                s.blank1 = n_blank1 * eb[q];
+                pin();
                 s_alpha0[(h * kChunk + q) * kShareRow + lane] = static_cast<unsigned>(__double2hiint(s.label0));
                 s_alpha1[(h * kChunk + q) * kShareRow + lane] = static_cast<unsigned>(__double2hiint(s.label1));
             }
@@ -2562,6 +2649,9 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
     const bool own0 = p0 >= own_first && p0 < own_end, own1 = p1 >= own_first && p1 < own_end;
     const int to_share = __double2loint(packed_inverse_p) + kScaleLog2;
     int next_lo = 0, next_hi = 0;
+    // A step's shares are formed during the step after it (before the first: of zeros, in a row that is filed again).
+    double pending_alpha0 = 0.0, pending_alpha1 = 0.0, pending_beta0 = 0.0, pending_beta1 = 0.0;
+    int pending_row = kBlockFrames - 1;
     renew_pairs<true>(s, ends.fb0, ends.fb1);
 #pragma unroll 1
     for (int h = 1; h >= 0; --h) {
@@ -2569,7 +2659,10 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
         const int exponents = (h == 0 ? alpha_frame0 : alpha_frame1) + s.frame + to_share;
         const int x0 = own0 ? exponents : kNoExponent, x1 = own1 ? exponents : kNoExponent;
         const double skip2_scale = skip2_one * s.scale;
-        if (h == 0) emissions(h, el0, el1);              // (chunk 1's are still there)
+        if (h == 0) {                                    // (chunk 1's are still there)
+            emissions(h, el0, el1);
+            read_blanks(h);
+        }
         unsigned alpha0[kChunk], alpha1[kChunk];
 #pragma unroll
         for (int q = 0; q < kChunk; ++q) {
@@ -2578,17 +2671,57 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
         }
 #pragma unroll
         for (int q = kChunk - 1; q >= 0; --q) {
-            const double next = shift_down(s.label0, next_lo, next_hi), blank = eb[h * kChunk + q];
-            const double u0 = s.blank0 + s.label0, u1 = s.blank1 + s.label1;
-            const double n_blank0 = s.blank0 + s.label1, n_label0 = __builtin_fma(s.label1, skip1_one, u0);
-            const double n_label1 = __builtin_fma(next, skip2_scale, u1), n_blank1 = __builtin_fma(next, s.scale, s.blank1);
-            file(h * kChunk + q, state_share(alpha0[q], n_label0, x0), state_share(alpha1[q], n_label1, x1));
-            s.label0 = n_label0 * static_cast<double>(el0[q]);
-            s.label1 = n_label1 * static_cast<double>(el1[q]);
-            s.blank0 = n_blank0 * blank;
-            s.blank1 = n_blank1 * blank;
+#pragma clang fp contract(off)
+            const double next = shift_down(s.label0, next_lo, next_hi);
+            pin();
+            const double share0 = pending_alpha0 * pending_beta0;
+            pin();
+            const double u0 = s.blank0 + s.label0;
+            pin();
+            const double share1 = pending_alpha1 * pending_beta1;
+            pin();
+            const double u1 = s.blank1 + s.label1;
+            pin();
+            const float f0 = static_cast<float>(share0);
+            pin();
+            const double n_blank0 = s.blank0 + s.label1;
+            pin();
+            const float f1 = static_cast<float>(share1);
+            pin();
+            const double n_label0 = __builtin_fma(s.label1, skip1_one, u0);
+            pin();
+            const double n_label1 = __builtin_fma(next, skip2_scale, u1);
+            pin();
+            const double el0_d = static_cast<double>(el0[q]);
+            pin();
+            file(pending_row, f0, f1);
+            pin();
+            const double n_blank1 = __builtin_fma(next, s.scale, s.blank1);
+            pin();
+            const double a0 = scaled_alpha(alpha0[q], x0);
+            pin();
+            const double el1_d = static_cast<double>(el1[q]);
+            pin();
+            const double a1 = scaled_alpha(alpha1[q], x1);
+            pin();
+            s.label0 = n_label0 * el0_d;
+            pin();
+            pending_alpha0 = fmin(a0, 0x1p1000);
+            pin();
+            s.label1 = n_label1 * el1_d;
+            pin();
+            pending_alpha1 = fmin(a1, 0x1p1000);
+            pin();
+            s.blank0 = n_blank0 * eb[q];
+            pin();
+            s.blank1 = n_blank1 * eb[q];
+            pin();
+            pending_beta0 = n_label0;
+            pending_beta1 = n_label1;
+            pending_row = h * kChunk + q;
         }
     }
+    file(pending_row, static_cast<float>(pending_alpha0 * pending_beta0), static_cast<float>(pending_alpha1 * pending_beta1));
 }
 // The same from the words that log-domain chains have stored for every frame.
 template <int kScaleLog2, typename File>
@@ -2628,9 +2761,11 @@ __device__ __forceinline__ void for_pieces(int L, int first, int step, F&& for_p
 constexpr int kShareBlocksMost = 8192;    // blocks times pieces: two rounds of what the chip holds
 __host__ __device__ constexpr int block_waves(int L) { return label_pieces(L) <= 1 ? 1 : (label_pieces(L) == 2 ? 2 : 4); }
 // The domains of an utterance's two chains as its chains published them (a word per direction).
-__device__ __forceinline__ bool in_log_domain(const int* __restrict__ domain, int b)
+template <bool kPublished>
+__device__ __forceinline__ bool in_log_domain(const int* domain, int b)
 {
-    return __builtin_amdgcn_readfirstlane(domain[2 * b] | domain[2 * b + 1]) != 0;
+    const int d = kPublished ? published(&domain[2 * b]) | published(&domain[2 * b + 1]) : domain[2 * b] | domain[2 * b + 1];
+    return __builtin_amdgcn_readfirstlane(d) != 0;
 }
 
 // Alphabets of at most 64 symbols (the English one has 29): a wavefront per block, or two or four that share the label's
@@ -2655,7 +2790,7 @@ __host__ __device__ constexpr int tile_label_ints(int L) { return (L + 31) / 32 
 constexpr int kEmissionRow = 12;
 __host__ __device__ constexpr int tile_emission_ints(int tiles) { return (2 * 16 * tiles + 1) * kEmissionRow; }
 // LDS of one wavefront.
-__host__ __device__ constexpr int tile_lds_ints(int Lmax, int tiles) { return kShareInts + tile_emission_ints(tiles) + tile_label_ints(Lmax); }
+__host__ __device__ constexpr int tile_lds_ints(int Lmax, int tiles) { return kBlankInts + kShareInts + tile_emission_ints(tiles) + tile_label_ints(Lmax); }
 __device__ __forceinline__ void stage_label_bytes(unsigned* s_label, const int* __restrict__ labels, int L)
 {
     for (int w = threadIdx.x & 63; w < tile_label_ints(L); w += 64) {
@@ -2696,58 +2831,118 @@ __device__ __forceinline__ void share_product(float4v (&acc)[kTiles], const unsi
     }
 }
 
-// grid (ceil(blocks of T / (4 / wavefronts per block)), B); dynamic LDS 4 tile_lds_ints(Lmax, kTiles) ints.  kTiles: tiles of 16 symbols.
-template <typename T, int kTiles>
-__global__ __launch_bounds__(kRowThreads)
-void ctc_gradient_narrow_kernel(T* __restrict__ grads, const Utt* __restrict__ meta, const int* __restrict__ labels,
-                                const double* __restrict__ emit_blank64, const float* __restrict__ emit_label,
-                                const LatticeOut lat, const double* __restrict__ logp, const int* __restrict__ chain_err,
-                                float* __restrict__ costs, int Tt, int B, int A, int blank, int Lmax,
-                                const int* __restrict__ domain, const bool share_blocks)
+// What the gradient's workgroups get, in a launch of their own or in the lattice launch.
+struct TileArgs {
+    void* grads;
+    bool bf16;
+    const double* logp;
+    const int* chain_err;
+    float* costs;
+    const int* domain;
+    const int* links;             // wide
+    const int* done;              // lattice launch: what to wait for
+    const int* by_end;            // ... the utterances, those first whose chains end first
+    int T, B, A, blank, Lmax;
+    int share_blocks;             // narrow
+    int rows_per_pass;            // wide
+    int groups;                   // workgroups per utterance
+    int first_group;              // lattice launch: the first one with a tile
+};
+__device__ __forceinline__ void store_gradient(const TileArgs& g, size_t i, float v)
 {
-    extern __shared__ uint4v tile_lds[];
-    const int b = blockIdx.y, lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+    if (g.bf16) store_elem(static_cast<bf16_t*>(g.grads), i, v);
+    else store_elem(static_cast<float*>(g.grads), i, v);
+}
+// By the whole workgroup: until utterance b's chains have ended.  They were handed out before this workgroup was and
+// wait for nobody but each other, so they end; should they not, `polls` runs out (seconds) and the cost is NaN.
+constexpr int kEndPolls = 1 << 23;
+__device__ __forceinline__ void wait_for_chains(const TileArgs& g, int b)
+{
+    if (threadIdx.x < 64) {
+        int polls = kEndPolls;
+        while (!chains_ended(__builtin_amdgcn_readfirstlane(published(&g.done[b * kDoneStride])))) {
+            if (--polls == 0) {
+                if (threadIdx.x == 0) publish(&g.costs[b], __uint_as_float(0x7FC00000u));
+                break;
+            }
+            __builtin_amdgcn_s_sleep(10);
+        }
+    }
+    __syncthreads();
+}
+
+// Workgroup `group` of utterance b: kRowThreads / 64 wavefronts, ceil(blocks of T / (4 / wavefronts per block)) workgroups;
+// LDS 4 tile_lds_ints(Lmax, kTiles) ints.  kTiles: tiles of 16 symbols.
+template <int kTiles, bool kWait>
+__device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* __restrict__ meta, const int* __restrict__ labels,
+                                            const double* __restrict__ emit_blank64, const float* __restrict__ emit_label,
+                                            const LatticeOut& lat, uint4v* tile_lds, const int b, const int group)
+{
+    const int Tt = g_args.T, B = g_args.B, A = g_args.A, blank = g_args.blank, Lmax = g_args.Lmax;
+    const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const Utt m = uniform_record(meta[b]);
-    const bool log_domain = in_log_domain(domain, b);
-    const int chain_gave_up = chain_err[b];
-    const double packed_inverse_p = logp[b];
-    const int L = m.L, sharing = share_blocks ? block_waves(L) : 1, part = wave & (sharing - 1);
-    const int block = static_cast<int>(blockIdx.x) * (kRowThreads / 64 / sharing) + wave / sharing, t0 = block * kBlockFrames;
-    if (blockIdx.x == 0 && threadIdx.x == 0 && chain_gave_up != 0) costs[b] = __uint_as_float(0x7FC00000u);
-    const bool has_rows = (m.flags & kUttRuns) && t0 < m.Tb;
+    const int L = m.L, sharing = g_args.share_blocks ? block_waves(L) : 1, part = wave & (sharing - 1);
+    const int first_block = group * (kRowThreads / 64 / sharing);
+    const int block = first_block + wave / sharing, t0 = block * kBlockFrames;
+    const bool runs = (m.flags & kUttRuns) != 0, has_rows = runs && t0 < m.Tb;
     if (!has_rows && part == 0) {
         // no lattice: zeros
 #pragma unroll 4
         for (int r = 0; r < kBlockFrames; ++r)
-            if (t0 + r < Tt && lane < A) store_elem(grads + (static_cast<size_t>(t0 + r) * B + b) * A, lane, 0.0f);
+            if (t0 + r < Tt && lane < A) store_gradient(g_args, (static_cast<size_t>(t0 + r) * B + b) * A + lane, 0.0f);
     }
     if (!has_rows) {
-        if (sharing > 1) __syncthreads();                // (the one below)
+        // (the barriers below)
+        if (kWait && runs && first_block * kBlockFrames < m.Tb) __syncthreads();
+        if (sharing > 1) __syncthreads();
         return;
     }
     unsigned* const s_hi = reinterpret_cast<unsigned*>(tile_lds) + wave * tile_lds_ints(Lmax, kTiles);
     unsigned* const s_lo = s_hi + kBlockFrames * kShareRow;
     float* const s_emit = reinterpret_cast<float*>(s_hi + kShareInts);
-    unsigned* const s_label = s_hi + kShareInts + tile_emission_ints(kTiles);
+    double* const s_blank = reinterpret_cast<double*>(s_emit + tile_emission_ints(kTiles));
+    unsigned* const s_label = reinterpret_cast<unsigned*>(s_blank + kBlockFrames);
+    static_assert((kShareInts + tile_emission_ints(kTiles)) % 4 == 0 && kBlankInts % 4 == 0, "16-byte reads");
     // Everything that comes from memory is asked for here, before any of it is used.
     const float4* const emit_in = reinterpret_cast<const float4*>(emit_label + emission_at(m.e_off, A, t0, 0));
-    float4 emit[kTiles];                                 // the block's 16 A emissions: up to 4 A vectors, 64 lanes
-#pragma unroll
-    for (int i = 0; i < kTiles; ++i) emit[i] = emit_in[min(64 * i + lane, 4 * A - 1)];
+    // (the block's 16 A emissions: up to 4 A vectors, 64 lanes; variables of their own, as the array went to scratch memory)
+    auto emission_vector = [&](int i) { return emit_in[min(64 * i + lane, 4 * A - 1)]; };
+    const float4 emit0 = emission_vector(0), emit1 = emission_vector(1);
+    const float4 emit2 = kTiles > 2 ? emission_vector(2) : emit0, emit3 = kTiles > 2 ? emission_vector(3) : emit0;
+    const double blank_emission = emit_blank64[blank_emission_offset(m, 2 * block) + (lane & (kBlockFrames - 1))];
     // (an empty label has no string to look at, and the caller's array may be empty)
     const int first_base = part * kPieceStep;
     const LaneLabels first_labels(L > 0 ? labels + m.lab_off : &meta[b].L, max(L, 1), first_base);
-    BlockEnds ends(m, lat, first_labels.p0, block);
+    BlockEnds ends;
+    bool log_domain = false;
+    double packed_inverse_p = 0.0;
+    auto load_ends = [&]() {
+        ends = BlockEnds::load<kWait>(m, lat, first_labels.p0, block);
+        log_domain = in_log_domain<kWait>(g_args.domain, b);
+        packed_inverse_p = kWait ? published(&g_args.logp[b]) : g_args.logp[b];
+        if (group == 0 && threadIdx.x == 0 && published(&g_args.chain_err[b]) != 0) publish(&g_args.costs[b], __uint_as_float(0x7FC00000u));
+    };
+    if (!kWait) load_ends();
     __builtin_amdgcn_sched_barrier(0);
     stage_label_bytes(s_label, labels + m.lab_off, L);
-#pragma unroll
-    for (int i = 0; i < kTiles; ++i) {
+    auto stage = [&](int i, const float4& e) {
         const int v = 64 * i + lane;                     // vector v: half v % 2 of row v / 2
-        if (v < 4 * A) *reinterpret_cast<float4*>(s_emit + (v >> 1) * kEmissionRow + (v & 1) * 4) = emit[i];
+        if (v < 4 * A) *reinterpret_cast<float4*>(s_emit + (v >> 1) * kEmissionRow + (v & 1) * 4) = e;
+    };
+    stage(0, emit0);
+    stage(1, emit1);
+    if constexpr (kTiles > 2) {
+        stage(2, emit2);
+        stage(3, emit3);
     }
     if (lane < 8) s_emit[2 * A * kEmissionRow + lane] = 0.0f;
-    const double* const eb = emit_blank64 + blank_emission_offset(m, 2 * block);
+    if (lane < kBlockFrames) s_blank[lane] = blank_emission;
+    if (kWait) {
+        wait_for_chains(g_args, b);
+        load_ends();
+        if (log_domain) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    }
     // the symbol of this lane's column, per tile of symbols: label bytes are compared as (byte & mask) ^ symbol == 0
     unsigned symbol[kTiles], mask[kTiles];
     float4v acc[kTiles];
@@ -2771,7 +2966,7 @@ void ctc_gradient_narrow_kernel(T* __restrict__ grads, const Utt* __restrict__ m
             LaneLabels at = first_labels;
             if (base != first_base) {
                 at = LaneLabels(labels + m.lab_off, L, base);
-                ends = BlockEnds(m, lat, at.p0, block);
+                ends = BlockEnds::load<kWait>(m, lat, at.p0, block);
             }
             auto emissions = [&](int h, float (&el0)[kChunk], float (&el1)[kChunk]) {
                 auto row = [&](bool has, int symbol, float (&el)[kChunk]) {
@@ -2783,7 +2978,7 @@ void ctc_gradient_narrow_kernel(T* __restrict__ grads, const Utt* __restrict__ m
                 row(at.has0, at.symbol0, el0);
                 row(at.has1, at.symbol1, el1);
             };
-            block_shares<kShareScaleLog2>(m, at, ends, eb, packed_inverse_p, block, own_first, own_end, s_hi, s_lo, emissions, file);
+            block_shares<kShareScaleLog2>(m, at, ends, s_blank, packed_inverse_p, block, own_first, own_end, s_hi, s_lo, emissions, file);
         }
         // LDS operations of one wavefront complete in program order; the fences only keep the
         // compiler from moving them across.
@@ -2809,20 +3004,35 @@ void ctc_gradient_narrow_kernel(T* __restrict__ grads, const Utt* __restrict__ m
     // Result: lane l holds symbol 16 n + l % 16 of frames 4 (l / 16) .. + 3; y is the emission.
     const int tr = t0 + 4 * g;
     const float scale = static_cast<float>(packed_inverse_p) * (0.5f / (1 << kShareScaleLog2));
+    auto write = [&](auto* grads) {
 #pragma unroll
-    for (int n = 0; n < kTiles; ++n) {
-        const int k = 16 * n + c;
-        if (k >= A) continue;
-        T* out = grads + (static_cast<size_t>(tr) * B + b) * A + k;
-        const float4 y = *reinterpret_cast<const float4*>(s_emit + ((g >> 1) * A + k) * kEmissionRow + (g & 1) * 4);
-        const float yv[4] = {y.x, y.y, y.z, y.w};
+        for (int n = 0; n < kTiles; ++n) {
+            const int k = 16 * n + c;
+            if (k >= A) continue;
+            auto* out = grads + (static_cast<size_t>(tr) * B + b) * A + k;
+            const float4 y = *reinterpret_cast<const float4*>(s_emit + ((g >> 1) * A + k) * kEmissionRow + (g & 1) * 4);
+            const float yv[4] = {y.x, y.y, y.z, y.w};
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float occupancy = acc[n][i] * scale;
-            const float v = emission_softmax(yv[i]) - (k == blank ? 1.0f - occupancy : occupancy);
-            if (tr + i < Tt) store_elem(out, static_cast<size_t>(i) * B * A, tr + i < m.Tb ? v : 0.0f);
+            for (int i = 0; i < 4; ++i) {
+                const float occupancy = acc[n][i] * scale;
+                const float v = emission_softmax(yv[i]) - (k == blank ? 1.0f - occupancy : occupancy);
+                if (tr + i < Tt) store_elem(out, static_cast<size_t>(i) * B * A, tr + i < m.Tb ? v : 0.0f);
+            }
         }
-    }
+    };
+    if (g_args.bf16) write(static_cast<bf16_t*>(g_args.grads));
+    else write(static_cast<float*>(g_args.grads));
+}
+
+// grid (workgroups per utterance, B)
+template <int kTiles>
+__global__ __launch_bounds__(kRowThreads)
+void ctc_gradient_narrow_kernel(const TileArgs args, const Utt* __restrict__ meta, const int* __restrict__ labels,
+                                const double* __restrict__ emit_blank64, const float* __restrict__ emit_label,
+                                const LatticeOut lat)
+{
+    extern __shared__ uint4v tile_lds[];
+    narrow_tile<kTiles, false>(args, meta, labels, emit_blank64, emit_label, lat, tile_lds, blockIdx.y, blockIdx.x);
 }
 
 // Larger alphabets: the softmax launch has written y (and zeros); here the columns of the label's symbols and the
@@ -2830,84 +3040,155 @@ void ctc_gradient_narrow_kernel(T* __restrict__ grads, const Utt* __restrict__ m
 // each other, setup_role), and the lane of a symbol's first occurrence adds up its run: one writer per symbol and a
 // fixed order.  `rows_per_pass` frames of a block at a time (16, or 8 where the longest label's shares of 16 frames do not
 // fit).  grid (blocks of T, B); dynamic LDS rows_per_pass * (Lmax + 1) floats.
-template <typename T>
 __global__ __launch_bounds__(64)
-void ctc_gradient_wide_kernel(T* __restrict__ grads, const Utt* __restrict__ meta, const int* __restrict__ labels,
-                              const int* __restrict__ links, const float* __restrict__ emit_blank,
-                              const double* __restrict__ emit_blank64, const float* __restrict__ emit_label,
-                              const LatticeOut lat, const double* __restrict__ logp, const int* __restrict__ chain_err,
-                              float* __restrict__ costs, int B, int A, int blank, int rows_per_pass,
-                              const int* __restrict__ domain)
+void ctc_gradient_wide_kernel(const TileArgs g, const Utt* __restrict__ meta, const int* __restrict__ labels,
+                              const float* __restrict__ emit_blank, const double* __restrict__ emit_blank64,
+                              const float* __restrict__ emit_label, const LatticeOut lat)
 {
     __shared__ unsigned s_alpha[kShareInts];
+    __shared__ double s_blank[kBlockFrames];
     extern __shared__ float s_share[];                   // [rows_per_pass][L + 1]
+    const int B = g.B, A = g.A, blank = g.blank, rows_per_pass = g.rows_per_pass;
     const int b = blockIdx.y, lane = threadIdx.x, block = blockIdx.x, t0 = block * kBlockFrames;
     const Utt m = uniform_record(meta[b]);
-    if (t0 == 0 && lane == 0 && chain_err[b] != 0) costs[b] = __uint_as_float(0x7FC00000u);
     if (!(m.flags & kUttRuns) || t0 >= m.Tb) return;
-    const bool log_domain = in_log_domain(domain, b);
-    const double packed_inverse_p = logp[b];
-    const float inverse_p = static_cast<float>(packed_inverse_p);
+    // Everything that comes from memory for the first piece is asked for here, before any of it is used: a launch of this
+    // kernel lasts not much longer than one block takes.
     const int L = m.L, row_pitch = L + 1;
-    const double* const eb = emit_blank64 + blank_emission_offset(m, 2 * block);
+    const int* const lab = L > 0 ? labels + m.lab_off : &meta[b].L;      // (an empty label has no string to look at)
+    const int* const link_of = L > 0 ? g.links + m.lab_off : &meta[b].L;
+    const LaneLabels first_labels(lab, max(L, 1), 0);
+    const int first_link0 = link_of[min(first_labels.p0, max(L, 1) - 1)], first_link1 = link_of[min(first_labels.p1, max(L, 1) - 1)];
+    const double blank_emission = emit_blank64[blank_emission_offset(m, 2 * block) + (lane & (kBlockFrames - 1))];
+    // the emissions of the block for one position: [chunk and half]
+    struct PositionEmissions { float4 v0, v1, v2, v3; };
+    auto emissions_of = [&](bool has, int position) {
+        const float* const p = emit_label + label_emission_offset(m, has, 0, position, 2 * block, kZeroEmission);
+        const float* const q = p + label_emission_step(m, has, false);
+        auto at4 = [](const float* w) { return *reinterpret_cast<const float4*>(w); };
+        return PositionEmissions{at4(p), at4(p + 4), at4(q), at4(q + 4)};
+    };
+    PositionEmissions emit0 = emissions_of(first_labels.has0, first_labels.p0), emit1 = emissions_of(first_labels.has1, first_labels.p1);
+    BlockEnds ends = BlockEnds::load<false>(m, lat, first_labels.p0, block);
+    const bool log_domain = in_log_domain<false>(g.domain, b);
+    const double packed_inverse_p = g.logp[b];
+    const bool gave_up = g.chain_err[b] != 0;
+    __builtin_amdgcn_sched_barrier(0);
+    if (lane < kBlockFrames) s_blank[lane] = blank_emission;
+    if (t0 == 0 && lane == 0 && gave_up) g.costs[b] = __uint_as_float(0x7FC00000u);
+    const float inverse_p = static_cast<float>(packed_inverse_p);
     for (int first = 0; first < kBlockFrames; first += rows_per_pass) {
         for_pieces(L, 0, 1, [&](int base, int own_first, int own_end) {
-            const int p0 = base + 2 * lane, p1 = p0 + 1;
-            const bool own0 = p0 >= own_first && p0 < own_end, own1 = p1 >= own_first && p1 < own_end;
-            const int slot0 = own0 ? links[m.lab_off + p0] & kLinkSlotMask : 0, slot1 = own1 ? links[m.lab_off + p1] & kLinkSlotMask : 0;
+            LaneLabels at = first_labels;
+            int link0 = first_link0, link1 = first_link1;
+            if (base + first > 0) {
+                at = LaneLabels(lab, L, base);
+                link0 = link_of[min(at.p0, L - 1)];
+                link1 = link_of[min(at.p1, L - 1)];
+                ends = BlockEnds::load<false>(m, lat, at.p0, block);
+                emit0 = emissions_of(at.has0, at.p0);
+                emit1 = emissions_of(at.has1, at.p1);
+            }
+            const bool own0 = at.p0 >= own_first && at.p0 < own_end, own1 = at.p1 >= own_first && at.p1 < own_end;
+            float *const share0 = s_share + (link0 & kLinkSlotMask), *const share1 = s_share + (link1 & kLinkSlotMask);
             auto file = [&](int row, float x0, float x1) {
                 const int r = row - first;
                 if (r < 0 || r >= rows_per_pass) return;
-                if (own0) s_share[r * row_pitch + slot0] = x0 * inverse_p;
-                if (own1) s_share[r * row_pitch + slot1] = x1 * inverse_p;
+                if (own0) share0[r * row_pitch] = x0 * inverse_p;
+                if (own1) share1[r * row_pitch] = x1 * inverse_p;
             };
             if (log_domain) block_shares_log<0>(m, lat, packed_inverse_p, block, base, own_first, own_end, file);
             else {
-                const LaneLabels at(labels + m.lab_off, L, base);
-                const float* e0 = emit_label + label_emission_offset(m, at.has0, 0, at.p0, 2 * block, kZeroEmission);
-                const float* e1 = emit_label + label_emission_offset(m, at.has1, 0, at.p1, 2 * block, kZeroEmission);
-                const int64_t step0 = label_emission_step(m, at.has0, false), step1 = label_emission_step(m, at.has1, false);
                 auto emissions = [&](int h, float (&el0)[kChunk], float (&el1)[kChunk]) {
-                    const float *q0 = e0 + h * step0, *q1 = e1 + h * step1;
-                    fetch_chunk<false>(q0, 0, el0);
-                    fetch_chunk<false>(q1, 0, el1);
+                    auto take = [&](const PositionEmissions& e, float (&el)[kChunk]) {
+                        el[0] = h ? e.v2.x : e.v0.x; el[1] = h ? e.v2.y : e.v0.y; el[2] = h ? e.v2.z : e.v0.z; el[3] = h ? e.v2.w : e.v0.w;
+                        el[4] = h ? e.v3.x : e.v1.x; el[5] = h ? e.v3.y : e.v1.y; el[6] = h ? e.v3.z : e.v1.z; el[7] = h ? e.v3.w : e.v1.w;
+                    };
+                    take(emit0, el0);
+                    take(emit1, el1);
                 };
-                block_shares<0>(m, at, BlockEnds(m, lat, at.p0, block), eb, packed_inverse_p, block, own_first, own_end, s_alpha,
+                block_shares<0>(m, at, ends, s_blank, packed_inverse_p, block, own_first, own_end, s_alpha,
                                 s_alpha + kBlockFrames * kShareRow, emissions, file);
             }
         });
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         const int rows = min(rows_per_pass, m.Tb - t0 - first);
-        for (int j = lane; j < L; j += 64) {
-            const int link = links[m.lab_off + j];
-            if (link >= 0) continue;                     // (not the first occurrence of its symbol)
-            const int slot = link & kLinkSlotMask, count = (link >> kLinkCountShift) & kLinkSlotMask;
-            T* out = grads + (static_cast<size_t>(t0 + first) * B + b) * A + labels[m.lab_off + j];
-            for (int r0 = 0; r0 < rows; r0 += 4) {
-                // y of a label's symbol is its emission, which the softmax launch gathered
-                const float4 e = *reinterpret_cast<const float4*>(emit_label + emission_at(m.e_off, L, t0 + first + r0, j));
-                const float y[4] = {e.x, e.y, e.z, e.w};
-                float o[4] = {};
-                for (int i = 0; i < count; ++i)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) o[r] += s_share[(r0 + r) * row_pitch + slot + i];
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (r0 + r < rows) store_elem(out, static_cast<size_t>(r0 + r) * B * A, emission_softmax(y[r]) - o[r]);
+        // The label's symbols one after the other, where alpha was: the word of the first occurrence with the position put into
+        // its unused bits, and the symbol.
+        static_assert(2 * CTC_MAX_LABEL_LENGTH <= kShareInts && CTC_MAX_LABEL_LENGTH < 1024, "the list fits, a position is ten bits");
+        int symbols = 0;
+        for (int j0 = 0; j0 < L; j0 += 64) {
+            const int j = j0 + lane, link = j < L ? link_of[j] : 0, symbol = j < L ? lab[j] : 0;
+            const unsigned long long firsts = __ballot(link < 0);
+            if (link < 0) {
+                const int i = symbols + __builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(firsts >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(firsts), 0));
+                s_alpha[2 * i] = static_cast<unsigned>((link & (kLinkSlotMask | kLinkSlotMask << kLinkCountShift)) | (j & 3) << 10 | (j >> 2) << 22);
+                s_alpha[2 * i + 1] = static_cast<unsigned>(symbol);
             }
-        }
-        // the blank: what the label states leave of 1, four lanes per row
-        const int row = lane >> 2, q = lane & 3;
-        float sum = 0.0f;
-        if (row < rows)
-            for (int i = q; i < L; i += 4) sum += s_share[row * row_pitch + i];
-        sum = quad_sum(sum);
-        if (row < rows && q == 0) {
-            const int t = t0 + first + row;
-            store_elem(grads + (static_cast<size_t>(t) * B + b) * A, blank,
-                       emission_softmax(emit_blank[kBlankSlack + m.f_off + t]) - (1.0f - sum));
+            symbols += __popcll(firsts);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        // Four of them at a time, a lane per frame and symbol: the lane adds up the run of its symbol's positions.  (A lane
+        // per symbol took every frame in turn, and the wavefront as long as its most frequent symbol 16 times over.)
+        const int row = lane & (kBlockFrames - 1), t = t0 + first + row;
+        const bool has_row = row < rows;
+        const float* const share = s_share + min(row, rows_per_pass - 1) * row_pitch;
+        const size_t out = (static_cast<size_t>(t) * B + b) * A;
+        const float* const y_row = emit_label + emission_at(m.e_off, L, min(t, m.Tb - 1), 0);
+        auto entry = [&](int i) { return s_alpha[2 * min(i, symbols - 1)]; };
+        auto position = [](unsigned word) { return static_cast<int>(word >> 10 & 3) | static_cast<int>(word >> 22) << 2; };
+        float sum = 0.0f;
+        if (symbols > 0) {
+            unsigned word = entry(lane >> 4);
+            float y = y_row[static_cast<size_t>(position(word)) * kChunk];
+            for (int i0 = 0; i0 < symbols; i0 += 4) {
+                const int i = i0 + (lane >> 4);
+                // (the next ones' y on its way)
+                const unsigned next_word = entry(i + 4);
+                const float next_y = y_row[static_cast<size_t>(position(next_word)) * kChunk];
+                const int slot = static_cast<int>(word & kLinkSlotMask), count = static_cast<int>(word >> kLinkCountShift & kLinkSlotMask);
+                float o = share[slot];
+                for (int k = 1; k < count; ++k) o += share[slot + k];
+                if (i < symbols && has_row) {
+                    store_gradient(g, out + s_alpha[2 * i + 1], emission_softmax(y) - o);
+                    sum += o;
+                }
+                word = next_word;
+                y = next_y;
+            }
+        }
+        // the blank: what the label states leave of 1
+        sum += __shfl_xor(sum, 16);
+        sum += __shfl_xor(sum, 32);
+        if (has_row && lane < kBlockFrames)
+            store_gradient(g, out + blank, emission_softmax(emit_blank[kBlankSlack + m.f_off + t]) - (1.0f - sum));
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+}
+
+// ---- chains and gradient in one launch -------------------------------------------------------------
+// Alphabets of at most kDirectMaxA symbols.  Chains first, one workgroup each; then the gradient's workgroups, the
+// utterances whose chains end first before the others.  A gradient workgroup asks for everything that the softmax launch
+// has left and waits for its utterance's two chains; by the time the longest chains end, only their own blocks are left to do.
+template <Sync kSync, int kTiles>
+__global__ __launch_bounds__(64 * kFusedWaves)
+void ctc_lattice_gradient_kernel(const Utt* __restrict__ meta, const int* __restrict__ order,
+                                 const int* __restrict__ labels, const float* __restrict__ emit_blank,
+                                 const double* __restrict__ emit_blank64, const float* __restrict__ emit_label,
+                                 const LatticeOut lat, double* __restrict__ logp, float* __restrict__ costs,
+                                 int* __restrict__ chain_err, uint32_t* __restrict__ sink, const LaunchWords wk, const TileArgs tiles)
+{
+    extern __shared__ uint4v fused_lds[];
+    const int index = static_cast<int>(blockIdx.x);
+    if (index < tiles.first_group) {
+        if (kSync == Sync::kNone && threadIdx.x >= 64) return;
+        __builtin_amdgcn_s_setprio(3);
+        lattice_body<kSync, Mode::kGrad>(meta, order, labels, emit_blank, emit_blank64, emit_label, lat, logp, costs, chain_err, sink,
+                                         fused_lds, wk);
+    } else {
+        const int i = index - tiles.first_group, rank = i / tiles.groups;
+        const int b = __builtin_amdgcn_readfirstlane(tiles.by_end[rank]), group = i - rank * tiles.groups;
+        narrow_tile<kTiles, true>(tiles, meta, labels, emit_blank64, emit_label, lat, fused_lds, b, group);
     }
 }
 
@@ -3061,6 +3342,37 @@ int launch_softmax(const Launch& p, void* stream)
     });
 }
 
+// The gradient's workgroups: what they get, how many there are (in args.groups per utterance) and their LDS.
+static TileArgs tile_args(const Launch& p, size_t* lds)
+{
+    TileArgs g{};
+    g.grads = p.grads;
+    g.bf16 = p.dtype != CTC_DTYPE_F32;
+    g.logp = reinterpret_cast<const double*>(p.ws + p.lay.logp);
+    g.chain_err = reinterpret_cast<const int*>(p.ws + p.lay.chain_err);
+    g.costs = p.costs;
+    g.domain = reinterpret_cast<const int*>(p.ws + p.lay.domain);
+    g.links = reinterpret_cast<const int*>(p.ws + p.lay.links);
+    g.done = reinterpret_cast<const int*>(p.ws + p.lay.done);
+    g.by_end = reinterpret_cast<const int*>(p.ws + p.lay.order) + 2 * p.B;
+    g.T = p.T; g.B = p.B; g.A = p.A; g.blank = p.blank;
+    g.Lmax = p.max_label;
+    constexpr int kWaves = kRowThreads / 64;
+    const int blocks = frame_blocks(p.T);
+    int per_group = kWaves;
+    if (p.A <= kDirectMaxA) {
+        g.share_blocks = static_cast<int64_t>(p.B) * blocks * label_pieces(p.max_label) <= kShareBlocksMost;
+        if (g.share_blocks) per_group = kWaves / block_waves(p.max_label);
+        *lds = static_cast<size_t>(kWaves) * tile_lds_ints(p.max_label, p.A <= 32 ? 2 : 4) * 4;
+    } else {
+        per_group = 1;
+        g.rows_per_pass = static_cast<size_t>(kBlockFrames) * (p.max_label + 1) * sizeof(float) <= (size_t(60) << 10) ? kBlockFrames : kBlockFrames / 2;
+        *lds = static_cast<size_t>(g.rows_per_pass) * (p.max_label + 1) * sizeof(float);
+    }
+    g.groups = (blocks + per_group - 1) / per_group;
+    return g;
+}
+
 int launch_lattice(const Launch& p, void* stream)
 {
     // (a call whose softmax launch read the pinned image itself needs this launch for the release, chains or not)
@@ -3095,8 +3407,31 @@ int launch_lattice(const Launch& p, void* stream)
         wk.fill = FillArgs{p.grads, p.dtype == CTC_DTYPE_F32 ? 4 : 2, p.T, p.B, p.A, p.defer, p.n_cu, p.n_chains, rounds};
         n_groups = p.n_cu * rounds;
     }
-    const dim3 grid(n_groups), block(64 * p.max_waves);
     auto s = static_cast<hipStream_t>(stream);
+    if (p.fused) {
+        size_t lds;
+        TileArgs tiles = tile_args(p, &lds);
+        lds = std::max(lds, halo_lds_bytes(kFusedWaves));
+        wk.announce = true;
+        tiles.first_group = n_groups;
+        const dim3 grid(n_groups + tiles.groups * p.B), block(64 * kFusedWaves);
+#define CTC_LAUNCH_FUSED(SYNC, TILES)                                                              \
+    hipLaunchKernelGGL((ctc_lattice_gradient_kernel<SYNC, TILES>), grid, block, lds, s, meta, order, labels, emit_blank,   \
+                       reinterpret_cast<const double*>(p.ws + p.lay.emit_blank64), emit_label,                \
+                       lat, logp, p.costs, chain_err, sink, wk, tiles)
+#define CTC_LAUNCH_FUSED_TILES(SYNC)                                                               \
+    do {                                                                                           \
+        if (p.A <= 32) CTC_LAUNCH_FUSED(SYNC, 2);                                             \
+        else CTC_LAUNCH_FUSED(SYNC, 4);                                                            \
+    } while (0)
+        return checked_launch([&] {
+            if (p.max_waves == 1) CTC_LAUNCH_FUSED_TILES(Sync::kNone);
+            else CTC_LAUNCH_FUSED_TILES(Sync::kHalo);
+        });
+#undef CTC_LAUNCH_FUSED_TILES
+#undef CTC_LAUNCH_FUSED
+    }
+    const dim3 grid(n_groups), block(64 * p.max_waves);
 #define CTC_LAUNCH_LATTICE(KERNEL)                                                                 \
     hipLaunchKernelGGL(KERNEL, grid, block, lds_bytes, s, meta, order, labels, emit_blank,                 \
                        reinterpret_cast<const double*>(p.ws + p.lay.emit_blank64), emit_label,            \
@@ -3133,50 +3468,24 @@ int launch_backtrace(const Launch& p, void* stream)
 int launch_gradient(const Launch& p, void* stream)
 {
     auto* meta = reinterpret_cast<const Utt*>(p.ws + p.lay.meta);
-    const int* labels = p.labels;
-    const LatticeOut lat = lattice_blocks(p);
-    auto* logp = reinterpret_cast<const double*>(p.ws + p.lay.logp);
-    auto* chain_err = reinterpret_cast<const int*>(p.ws + p.lay.chain_err);
+    auto* emit_blank = reinterpret_cast<const float*>(p.ws + p.lay.emit_blank);
     auto* emit_blank64 = reinterpret_cast<const double*>(p.ws + p.lay.emit_blank64);
     auto* emit_label = reinterpret_cast<const float*>(p.ws + p.lay.emit_label);
-    auto* domain = reinterpret_cast<const int*>(p.ws + p.lay.domain);
     auto s = static_cast<hipStream_t>(stream);
-    const bool f32 = p.dtype == CTC_DTYPE_F32;
-    const int blocks = frame_blocks(p.T);
-    if (p.A <= kDirectMaxA) {
-        constexpr int kWaves = kRowThreads / 64;
-        const bool share = static_cast<int64_t>(p.B) * blocks * label_pieces(p.max_label) <= kShareBlocksMost;
-        const int per_group = share ? kWaves / block_waves(p.max_label) : kWaves;
-        const dim3 grid((blocks + per_group - 1) / per_group, p.B);
-        const size_t lds = static_cast<size_t>(kWaves) * tile_lds_ints(p.max_label, p.A <= 32 ? 2 : 4) * 4;
-#define CTC_LAUNCH_NARROW(TYPE, TILES)                                                              \
-    hipLaunchKernelGGL((ctc_gradient_narrow_kernel<TYPE, TILES>), grid, dim3(kRowThreads), lds, s,  \
-                       static_cast<TYPE*>(p.grads), meta, labels, emit_blank64, emit_label, lat,    \
-                       logp, chain_err, p.costs, p.T, p.B, p.A, p.blank, p.max_label, domain, share)
-        return checked_launch([&] {
-            if (p.A <= 32) {
-                if (f32) CTC_LAUNCH_NARROW(float, 2);
-                else CTC_LAUNCH_NARROW(bf16_t, 2);
-            } else {
-                if (f32) CTC_LAUNCH_NARROW(float, 4);
-                else CTC_LAUNCH_NARROW(bf16_t, 4);
-            }
-        });
-#undef CTC_LAUNCH_NARROW
-    }
-    const dim3 grid(blocks, p.B);
-    const int rows = static_cast<size_t>(kBlockFrames) * (p.max_label + 1) * sizeof(float) <= (size_t(60) << 10) ? kBlockFrames : kBlockFrames / 2;
-    const size_t lds = static_cast<size_t>(rows) * (p.max_label + 1) * sizeof(float);
-#define CTC_LAUNCH_WIDE(TYPE)                                                                       \
-    hipLaunchKernelGGL(ctc_gradient_wide_kernel<TYPE>, grid, dim3(64), lds, s, static_cast<TYPE*>(p.grads), meta,       \
-                       labels, reinterpret_cast<const int*>(p.ws + p.lay.links),                    \
-                       reinterpret_cast<const float*>(p.ws + p.lay.emit_blank), emit_blank64,       \
-                       emit_label, lat, logp, chain_err, p.costs, p.B, p.A, p.blank, rows, domain)
+    size_t lds;
+    const TileArgs args = tile_args(p, &lds);
+    const dim3 grid(args.groups, p.B), block(p.A > kDirectMaxA ? 64 : kRowThreads);
     return checked_launch([&] {
-        if (f32) CTC_LAUNCH_WIDE(float);
-        else CTC_LAUNCH_WIDE(bf16_t);
+        if (p.A > kDirectMaxA)
+            hipLaunchKernelGGL(ctc_gradient_wide_kernel, grid, block, lds, s, args, meta, p.labels, emit_blank, emit_blank64, emit_label,
+                               lattice_blocks(p));
+        else if (p.A <= 32)
+            hipLaunchKernelGGL(ctc_gradient_narrow_kernel<2>, grid, block, lds, s, args, meta, p.labels, emit_blank64, emit_label,
+                               lattice_blocks(p));
+        else
+            hipLaunchKernelGGL(ctc_gradient_narrow_kernel<4>, grid, block, lds, s, args, meta, p.labels, emit_blank64, emit_label,
+                               lattice_blocks(p));
     });
-#undef CTC_LAUNCH_WIDE
 }
 
 }  // namespace ctc

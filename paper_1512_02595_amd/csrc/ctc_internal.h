@@ -433,7 +433,7 @@ ctc_status_t make_layout(int T, int B, int A, const int32_t* label_lengths,
 // What a call computes, and so what its chains are run for:
 //   kGrad  sum over alignments, label states of every frame stored (cost and gradient)
 //   kLoss  sum over alignments, nothing stored (cost only; the chains meet in the middle)
-//   kBest  maximum over alignments, one byte of predecessor choices stored per state pair and
+//   kBest  maximum over alignments, predecessor choices stored per state pair and
 //          frame (most probable alignment; the chains meet in the middle)
 enum class Mode { kGrad, kLoss, kBest };
 

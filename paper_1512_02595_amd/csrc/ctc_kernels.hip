@@ -1083,12 +1083,6 @@ constexpr int kHaloEntries = 64;      // 16-byte entries of one wavefront bounda
 
 enum class Sync { kNone, kHalo, kBarrier };
 
-// Predecessor choices of a pair at one frame, as stored for the backtrace; each field is the
-// number of states the walk moves down.  Bits 2..3, the label state: 0 = stayed, 1 = came from
-// the pair's blank, 2 = came from the label of the pair before (skipping the blank).  Bit 0, the
-// blank state: 0 = stayed, 1 = came from the label of the pair before.
-// A chunk's emissions of one lane out of the emission block, in the order the chain takes them, in two 16-byte loads.
-// `p` moves on by `step` floats (0 for a lane without a label state, which keeps reading its constants).
 static_assert(kChunk == 8, "fetch_chunk loads two float4");
 template <bool kBackward>
 __device__ __forceinline__ void fetch_chunk(const float*& p, int64_t step, float (&el)[kChunk])
@@ -1099,7 +1093,24 @@ __device__ __forceinline__ void fetch_chunk(const float*& p, int64_t step, float
     for (int i = 0; i < kChunk; ++i) el[i] = v[kBackward ? kChunk - 1 - i : i];
     p += step;
 }
-constexpr int kFromSame = 0, kFromBlank = 1 << 2, kFromPrevLabel = 2 << 2, kBlankFromPrevLabel = 1;
+// Predecessor choices of a pair at one frame, as stored for the backtrace: four bits, the steps of a chunk in one word
+// with the first step in the highest.  Each field is the number of states the walk moves down.  Bits 2..3, the label
+// state: 0 = stayed, 1 = came from the pair's blank, 2 = came from the label of the pair before (skipping the blank).
+// Bit 0, the blank state: 0 = stayed, 1 = came from the label of the pair before.  (A byte per frame and pair, stored at
+// every step, took four issue slots of a step; a bit of the word is one, an addition with carry.)
+constexpr int kChoiceBits = 4;
+__device__ __forceinline__ unsigned append_bit(unsigned word, unsigned long long lanes)
+{
+    unsigned long long carry;
+    asm("v_addc_co_u32_e64 %0, %1, %2, %2, %3" : "=v"(word), "=s"(carry) : "v"(word), "s"(lanes));
+    return word;
+}
+// Every kSegment steps a chain also keeps, per state, which state the best way to it was in kSegment steps before (its
+// origin), so that the backtrace walks all segments at once.
+constexpr int kSegmentChunks = 4, kSegment = kSegmentChunks * kChunk;
+// Words in the exponent block, after the last states: a segment's origins by pair, blank state's in the low half.
+__host__ __device__ constexpr int64_t origin_word(int64_t pairs, int64_t segment) { return (4 + segment) * pairs; }
+
 
 // LDS of a chain's workgroup (dynamic, sized by the launch for its widest chain): a header, then
 // one block per wavefront that holds what that wavefront hands to the one above it.
@@ -1114,6 +1125,7 @@ struct HaloHeader {
 struct HaloWave {
     double2 data[kHaloEntries];
     int frame[kHaloEntries];          // linear-domain chains: the frame exponent that goes with each entry
+                                      // (Mode::kBest: the origins, blank state's in the low half)
     int ready;                        // last generation this wavefront has published
     int done;                         // last generation this wavefront has taken from the one below
     int unused[2];
@@ -1211,24 +1223,23 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
     const float* const bp = emit_blank + (kBackward ? kChunk - 1 - (lane & (kChunk - 1)) : (lane & (kChunk - 1)));
     // Output: only the label state of each pair is kept (rows by frame, column = 1 + label index, in both directions).
     // Lanes that store nothing write to a sink instead.
-    // With Mode::kBest the value block holds one byte per pair and frame instead (row pitch
-    // L+1 bytes, column = pair), pair L included: its blank state has a choice to record.
-    constexpr int64_t kOutBytes = (kMode == Mode::kBest) ? 1 : 4;
+    // With Mode::kBest the value block holds a word of choices per pair and chunk instead, rows in the chain's own
+    // order, column = pair, pair L included: its blank state has a choice to record.
     const int64_t out_pitch = (kMode == Mode::kBest) ? P : lattice_pitch(L);
     const bool stores = (kMode == Mode::kBest) ? active : (active && has_label);
     const int64_t first_row = kBackward ? static_cast<int64_t>(chunks) * kChunk - 1 : 0;
-    char* op = stores ? reinterpret_cast<char*>(out) +
-                            (m.ab_off + first_row * out_pitch + (kMode == Mode::kBest ? j : li + 1)) * kOutBytes
-                      : reinterpret_cast<char*>(sink);
-    const int64_t ostride = stores ? (kBackward ? -1 : 1) * out_pitch * kOutBytes : 0;
+    uint32_t* op = stores ? out + m.ab_off + (kMode == Mode::kBest ? j : first_row * out_pitch + li + 1) : sink;
+    const int64_t ostride = stores ? (kBackward && kMode != Mode::kBest ? -out_pitch : out_pitch) : 0;
     int* xp = (stores && kMode == Mode::kGrad) ? out_exponents + m.ab_off + first_row * out_pitch + li + 1 : reinterpret_cast<int*>(sink);
     const int64_t xstride = (stores && kMode == Mode::kGrad) ? (kBackward ? -1 : 1) * out_pitch : 0;
-    int choice = 0;
+    unsigned choices = 0;
+    int blank_origin = 2 * j, label_origin = 2 * j + 1;
+    uint32_t* origin_out = stores && kMode == Mode::kBest ? reinterpret_cast<uint32_t*>(out_exponents) + m.ab_off + origin_word(P, 0) + j : sink;
     auto store_state = [&](double w) {
         uint32_t value;
         int exponent;
         split_log2(w, value, exponent);
-        *reinterpret_cast<uint32_t*>(op) = value;
+        *op = value;
         *xp = exponent;
         xp += xstride;
     };
@@ -1281,7 +1292,10 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
                 }
                 lost = lost || seen < generation - 2;
             }
-            if (lane >= 64 - halo) wr_base[half] = make_double2(v_blank, v_label);
+            if (lane >= 64 - halo) {
+                wr_base[half] = make_double2(v_blank, v_label);
+                if (kMode == Mode::kBest) mine_lds->frame[half + lane - (64 - halo)] = blank_origin | label_origin << 16;
+            }
             // LDS operations of a wavefront complete in order: the counter follows the data.
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             if (lane == 63) __hip_atomic_store(my_ready, generation, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -1290,9 +1304,11 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
         if (wave > 0) {
             // Counter and data are read back to back; the data count only if the counter,
             // read first, already showed this generation.
+            const int* const rd_origin = &below_lds->frame[half + (lane < halo ? lane : 0)];
             int ready = counter(low_ready);
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             double2 v = rd_base[half];
+            int origins = kMode == Mode::kBest ? *rd_origin : 0;
             ready = uniform(ready);
             if (__builtin_expect(ready < generation, 0)) {
                 while (ready < generation && budget > 0) {
@@ -1300,6 +1316,7 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
                     ready = counter(low_ready);
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
                     v = rd_base[half];
+                    if (kMode == Mode::kBest) origins = *rd_origin;
                     ready = uniform(ready);
                 }
                 lost = lost || ready < generation;
@@ -1307,6 +1324,10 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
             if (lane < halo) {
                 v_blank = v.x;
                 v_label = v.y;
+                if (kMode == Mode::kBest) {
+                    blank_origin = origins & 0xFFFF;
+                    label_origin = static_cast<int>(static_cast<unsigned>(origins) >> 16);
+                }
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             if (lane == 0) __hip_atomic_store(my_done, generation, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -1325,18 +1346,25 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
         }
         return r;
     };
+    // ... and where the best way to it came from
+    auto origin_from_prev_pair = [&](int s) {
+        int r = __builtin_amdgcn_update_dpp(0, label_origin, 0x138, 0xf, 0xf, false);
+        if (kSync == Sync::kBarrier) {
+            int (*xch)[16] = reinterpret_cast<int (*)[16]>(static_cast<double*>(lds) + 32);
+            if (lane == 63) xch[s & 1][wave] = label_origin;
+            __syncthreads();
+            if (lane == 0 && wave > 0) r = xch[s & 1][wave - 1];
+        }
+        return r;
+    };
 
     auto finish_step = [&](double eb, float el) {
         v_blank = i_blank + eb;
         v_label = i_label + (kCoded ? emission_log2(el) : static_cast<double>(el));
-        if (kMode == Mode::kBest) {
-            *op = static_cast<unsigned char>(choice);
-        } else if (kMode == Mode::kLoss) {
-            // nothing is kept
-        } else {
+        if (kMode == Mode::kGrad) {
             store_state(kBackward ? i_label : v_label);
+            op += ostride;
         }
-        op += ostride;
     };
     // After the last step of a chunk.
     auto end_chunk = [&]() {
@@ -1353,15 +1381,21 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
             // Of equally probable ways the one that stays highest in the label throughout: going forward that is the
             // shortest move, going backward the longest.
             auto better = [](double a, double b) { return kBackward ? a >= b : a > b; };
+            const int prev_origin = origin_from_prev_pair(step);
             const double via_skip = prev + skip_penalty;
             const bool blank_moves = better(prev, v_blank);
             i_blank = blank_moves ? prev : v_blank;
-            double best = v_label;
-            choice = kFromSame;
-            if (better(v_blank, best)) { best = v_blank; choice = kFromBlank; }
-            if (better(via_skip, best)) { best = via_skip; choice = kFromPrevLabel; }
-            i_label = best;
-            choice |= blank_moves ? kBlankFromPrevLabel : 0;
+            const bool from_blank = better(v_blank, v_label);
+            double best = from_blank ? v_blank : v_label;
+            const int stay_origin = from_blank ? blank_origin : label_origin;
+            const bool skips = better(via_skip, best);
+            i_label = skips ? via_skip : best;
+            label_origin = skips ? prev_origin : stay_origin;
+            blank_origin = blank_moves ? prev_origin : blank_origin;
+            const unsigned long long skip_lanes = __ballot(skips);
+            choices = append_bit(choices, skip_lanes);
+            choices = append_bit(choices, __ballot(from_blank) & ~skip_lanes);
+            choices = append_bit(choices << 1, __ballot(blank_moves));
         } else {
             // The blank state sums its own value and the label of the pair before; where the
             // label state may also be entered from that label (skip), its three-term sum is
@@ -1376,6 +1410,12 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
         return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), l));
     };
 
+    auto end_segment = [&]() {
+        *origin_out = static_cast<uint32_t>(blank_origin | label_origin << 16);
+        origin_out += ostride;
+        blank_origin = 2 * j;
+        label_origin = 2 * j + 1;
+    };
     // (every lane starts from the exact state of its pair, halo lanes included)
     float el[4][kChunk], eb[2];
     auto fetch = [&](auto set, int i) {
@@ -1393,10 +1433,17 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
             advance(i * kChunk + q, kCoded ? whole_part + static_cast<double>(readlane(blank.part, q)) : whole_part, el[k][q]);
         }
         end_chunk();
+        if (kMode == Mode::kBest) {
+            *op = choices;
+            op += ostride;
+            static_assert(kSegmentChunks == 4, "the sets of chain_schedule");
+            if (k == 3) end_segment();
+        }
     };
     chain_schedule(count, fetch, run);
 
     if (kMode == Mode::kBest) {
+        if (count % kSegmentChunks) end_segment();
         // the backtrace looks for the best way through the frames where the chains meet
         if (active) reinterpret_cast<CheckpointState*>(out_exponents + m.ab_off)[j] = CheckpointState{v_blank, v_label};
         if (kSync == Sync::kHalo && lost && lane == 0) publish(&chain_err[u], 1);
@@ -2190,7 +2237,8 @@ __device__ __forceinline__ void lattice_body(const Utt* __restrict__ meta, const
         if (idle) {
             // Nothing to compute, but keep meeting the barriers of the working wavefronts:
             // one per recursion step, plus the forward chain's final exchange.
-            const int barriers = kMode == Mode::kBest ? chain_chunks(m.Tb, !forward) * kChunk
+            // (the maximum's: two, for the origin as well)
+            const int barriers = kMode == Mode::kBest ? 2 * chain_chunks(m.Tb, !forward) * kChunk
                                                       : static_cast<int>(padded_frames(m.Tb)) + (forward ? 1 : 0);
             for (int i = 0; i < barriers; ++i) __syncthreads();
             return;
@@ -2276,7 +2324,7 @@ void ctc_lattice_kernel_barrier(const Utt* __restrict__ meta, const int* __restr
                                 double* __restrict__ logp, float* __restrict__ costs,
                                 int* __restrict__ chain_err, uint32_t* __restrict__ sink, const LaunchWords wk)
 {
-    __shared__ double xch[2][16];
+    __shared__ double xch[3][16];                            // (labels by step parity; their origins, two words each)
     lattice_body<Sync::kBarrier, kMode>(meta, order, labels, emit_blank, emit_blank64, emit_label, lat, logp,
                                                costs, chain_err, sink, &xch[0][0], wk);
 }
@@ -2289,30 +2337,39 @@ void ctc_lattice_kernel_barrier(const Utt* __restrict__ meta, const int* __restr
 // for utterances without an alignment.  Both chains index their states in their own order (the backward chain's state s
 // is the lattice's 2 L - s), so the two walks are the same code.
 //
-// A walk is serial, one dependent look-up per frame, so it is kept on the scalar unit: the
-// choices are fetched in tiles of kTile frames x kTile pairs, lane = pair column, one register
-// per frame.  Going back kTile frames the walk moves down by at most kTile - 1 pairs (one per
-// frame), so the tile whose top right corner is the walk's position holds everything those
-// frames can touch.  A step is then a v_readlane at the walk's column, a shift, a mask and a
-// subtraction in scalar registers, and a v_writelane that files the state for the tile's
-// one coalesced store.
-constexpr int kTile = 64;
+// A walk is serial, one dependent look-up per frame, so it is cut into the chains' segments: from the junction the origins
+// lead from segment to segment, and each wavefront walks its own.  That walk is kept on the scalar unit: the choices of the
+// segment are in registers, a word per chunk, lane = pair column.  Going back kSegment steps the walk moves down by at
+// most kSegment - 1 pairs (one per frame), so the 64 columns up to the walk's position hold everything those steps can
+// touch.  A step is then a v_readlane at the walk's column, a shift, a mask and a subtraction in scalar registers, and
+// a v_writelane that files the state for the segment's one coalesced store.
+// (64 utterances of up to 750 frames: 23.7 us in one walk of 375 steps at 45 ns, with the choices as bytes.)
+constexpr int kBacktraceWaves = 16;
+constexpr int kOriginWords = 12288;       // origins kept in LDS, if they fit
 
-__global__ __launch_bounds__(64)
+// grid (B, 2), up to kBacktraceWaves wavefronts; dynamic LDS `lds_words` words.
+__global__ __launch_bounds__(64 * kBacktraceWaves)
 void ctc_backtrace_kernel(const Utt* __restrict__ meta, const int* __restrict__ labels, const LatticeOut lat,
-                          const int* __restrict__ chain_err, float* __restrict__ costs, int* __restrict__ alignment, int Tt)
+                          const int* __restrict__ chain_err, float* __restrict__ costs, int* __restrict__ alignment, int Tt, int lds_words)
 {
-    const int b = blockIdx.x, lane = threadIdx.x;
+    extern __shared__ uint32_t s_origins[];
+    const int b = blockIdx.x, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int waves = blockDim.x >> 6;
     const bool backward = blockIdx.y != 0;
     const Utt m = meta[b];
     int* arow = alignment + static_cast<size_t>(b) * Tt;
     const bool runs = (m.flags & kUttRuns) != 0;
     const bool bad = runs && chain_err[b] != 0;
-    if (bad && lane == 0 && !backward) costs[b] = __uint_as_float(0x7FC00000u);
+    if (bad && threadIdx.x == 0 && !backward) costs[b] = __uint_as_float(0x7FC00000u);
     const int valid = (runs && !bad) ? m.Tb : 0, L = m.L;
     if (backward)
-        for (int t = valid + lane; t < Tt; t += 64) arow[t] = -1;
+        for (int t = valid + threadIdx.x; t < Tt; t += blockDim.x) arow[t] = -1;
     if (valid == 0) return;
+    const int rows_all = chain_chunks(m.Tb, backward) * kChunk, P = L + 1, segments = (rows_all + kSegment - 1) / kSegment;
+    const uint32_t* const origins = reinterpret_cast<const uint32_t*>(backward ? lat.beta_exponents : lat.alpha_exponents) + m.ab_off + origin_word(P, 0);
+    const bool in_lds = segments * P <= lds_words;
+    if (in_lds)
+        for (int i = threadIdx.x; i < segments * P; i += blockDim.x) s_origins[i] = origins[i];
 
     // The junction: the state `to` of the backward chain's first frame and the best state `from` before it.  Per
     // pair the blank before the label, within a state the predecessor as in the forward chain (stay first); of equal ways
@@ -2353,48 +2410,47 @@ void ctc_backtrace_kernel(const Utt* __restrict__ meta, const int* __restrict__ 
             to = other_to;
         }
     }
-    if (lane == 0 && !backward) costs[b] = (best < -1.0e29) ? __builtin_inff() : static_cast<float>(-best * kLn2);
+    if (threadIdx.x == 0 && !backward) costs[b] = (best < -1.0e29) ? __builtin_inff() : static_cast<float>(-best * kLn2);
 
-    // this walk: frames in the chain's own order (frame_of), `rows` of them, from the state it was in at its last one
-    const int padded = static_cast<int>(padded_frames(m.Tb)), rows_all = chain_chunks(m.Tb, backward) * kChunk;
-    const int P = L + 1;
-    const unsigned char* base = reinterpret_cast<const unsigned char*>(backward ? lat.beta : lat.alpha) + m.ab_off;
+    // this walk: frames in the chain's own order (frame_of), from the state it was in at its last one
+    __syncthreads();
+    const int padded = static_cast<int>(padded_frames(m.Tb));
+    const uint32_t* const choices = (backward ? lat.beta : lat.alpha) + m.ab_off;
     auto frame_of = [&](int step) { return backward ? padded - 1 - step : step; };
-    auto file = [&](int step, int state) {
-        const int t = frame_of(step);
-        if (t < m.Tb) arow[t] = backward ? 2 * L - state : state;
-    };
     // (clamped so that no stored value can lead the reads astray)
-    int state = __builtin_amdgcn_readfirstlane(min(max(backward ? 2 * L - to : from, 0), 2 * L));
-    int step = rows_all - 1;
-    if (step < 0) return;
-    if (lane == 0) file(step, state);
-    // Steps step, step-1, ..., 1 each hold the choice that leads to the state of the step before.
-    while (step >= 1) {
-        const int pair_hi = state >> 1;                   // both states of a pair share its byte
-        const int pair_lo = max(pair_hi - (kTile - 1), 0);
-        const int rows = min(kTile, step);                // steps step, step-1, ..., step-rows+1
-        const unsigned col = static_cast<unsigned>(min(pair_lo + lane, pair_hi));
-        // A last, partial tile repeats step 1 in the rows below it and walks on through them:
-        // those steps stay inside the tile (the state is kept >= 0) and their results are not
-        // stored.  (An utterance's block is smaller than 2^31 bytes: 32-bit offsets.)
-        int tile[kTile];
-#pragma unroll
-        for (int r = 0; r < kTile; ++r)
-            tile[r] = base[static_cast<unsigned>(frame_of(max(step - r, 1))) * static_cast<unsigned>(P) + col];
-        int filed = 0;
-#pragma unroll
-        for (int r = 0; r < kTile; ++r) {
-            const int c = __builtin_amdgcn_readlane(tile[r], (state >> 1) - pair_lo);
-            // how far down the state of this frame came from: bits 2..3 if it is a label state
-            // (odd), bits 0..1 if it is a blank
-            state = max(state - ((c >> ((state << 1) & 2)) & 3), 0);
-            // lane r of `filed` = state of step - r - 1
-            asm volatile("v_writelane_b32 %0, %1, %2" : "+v"(filed) : "s"(state), "n"(r));
+    auto clamped = [&](int s) { return __builtin_amdgcn_readfirstlane(min(max(s, 0), 2 * L)); };
+    int segment = segments - 1;
+    int state = clamped(backward ? 2 * L - to : from);               // at the last step of `segment`
+    for (int mine = segments - 1 - wave; mine >= 0; mine -= waves) {
+        for (; segment > mine; --segment) {
+            const int at = segment * P + (state >> 1);
+            const uint32_t word = in_lds ? s_origins[at] : origins[at];
+            state = clamped(static_cast<int>(state & 1 ? word >> 16 : word & 0xFFFFu));
         }
-        if (lane < rows) file(step - 1 - lane, filed);
-        if (rows < kTile) break;
-        step -= kTile;
+        const int first = mine * kSegment, rows = min(kSegment, rows_all - first);       // (whole chunks)
+        const int pair_hi = state >> 1, pair_lo = max(pair_hi - 63, 0);                   // both states of a pair share its word
+        const int col = min(pair_lo + lane, pair_hi);
+        uint32_t word[kSegmentChunks];
+#pragma unroll
+        for (int c = 0; c < kSegmentChunks; ++c) word[c] = choices[static_cast<int64_t>(min(first / kChunk + c, rows_all / kChunk - 1)) * P + col];
+        int filed = 0, at = state;
+#pragma unroll
+        for (int c = kSegmentChunks - 1; c >= 0; --c) {
+            if (c * kChunk >= rows) continue;
+#pragma unroll
+            for (int q = kChunk - 1; q >= 0; --q) {
+                // lane r of `filed` = state at step first + r
+                asm volatile("v_writelane_b32 %0, %1, %2" : "+v"(filed) : "s"(at), "n"(c * kChunk + q));
+                const unsigned w = __builtin_amdgcn_readlane(word[c], (at >> 1) - pair_lo);
+                // how far down the state of this step came from: the upper two bits if it is a label state (odd), the lower
+                // two if it is a blank
+                at = max(at - static_cast<int>((w >> ((kChunk - 1 - q) * kChoiceBits + ((at << 1) & 2))) & 3u), 0);
+            }
+        }
+        if (lane < rows) {
+            const int t = frame_of(first + lane);
+            if (t < m.Tb) arow[t] = backward ? 2 * L - filed : filed;
+        }
     }
 }
 
@@ -3460,8 +3516,11 @@ int launch_backtrace(const Launch& p, void* stream)
     auto* meta = reinterpret_cast<const Utt*>(p.ws + p.lay.meta);
     auto* chain_err = reinterpret_cast<const int*>(p.ws + p.lay.chain_err);
     return checked_launch([&] {
-        hipLaunchKernelGGL(ctc_backtrace_kernel, dim3(p.B, 2), dim3(64), 0, static_cast<hipStream_t>(stream),
-                           meta, p.labels, lattice_blocks(p), chain_err, p.costs, p.alignment, p.T);
+        const int segments = std::max(1, (chain_chunks(p.max_frames, false) + kSegmentChunks - 1) / kSegmentChunks);
+        const int64_t words = static_cast<int64_t>(segments) * (p.max_label + 1);
+        const int lds_words = static_cast<int>(std::min<int64_t>(words, kOriginWords));
+        hipLaunchKernelGGL(ctc_backtrace_kernel, dim3(p.B, 2), dim3(64 * std::min(segments, kBacktraceWaves)), lds_words * 4,
+                           static_cast<hipStream_t>(stream), meta, p.labels, lattice_blocks(p), chain_err, p.costs, p.alignment, p.T, lds_words);
     });
 }
 

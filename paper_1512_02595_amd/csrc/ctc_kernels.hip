@@ -443,10 +443,10 @@ __device__ __forceinline__ float virtual_emission(bool blank, bool plain_logs)
     return plain_logs ? (blank ? 0.0f : static_cast<float>(kNeg)) : (blank ? 1.0f : 0.0f);
 }
 // The blank's emission of one padded frame, in both forms.
-__device__ __forceinline__ void store_blank(float* __restrict__ emit_blank, double* __restrict__ emit_blank64, size_t frame, float e)
+__device__ __forceinline__ void store_blank(float* __restrict__ emit_blank, double* __restrict__ emit_blank64, size_t frame, float e, bool plain_logs)
 {
     emit_blank[kBlankSlack + frame] = e;
-    emit_blank64[kBlankSlack + frame] = static_cast<double>(emission_probability(e));
+    emit_blank64[kBlankSlack + frame] = static_cast<double>(plain_logs ? e : emission_probability(e));
 }
 // Where the emission of column `column` in frame `t` of an utterance sits.
 __device__ __forceinline__ size_t emission_at(int64_t e_off, int columns, int t, int column)
@@ -458,7 +458,7 @@ __device__ __forceinline__ void store_virtual_frames(const Utt& m, float* __rest
                                                      float* __restrict__ emit_label, bool plain_logs, int q, int lanes)
 {
     for (int t = m.Tb; t < static_cast<int>(padded_frames(m.Tb)); ++t) {
-        if (q == 0) store_blank(emit_blank, emit_blank64, static_cast<size_t>(m.f_off) + t, virtual_emission(true, plain_logs));
+        if (q == 0) store_blank(emit_blank, emit_blank64, static_cast<size_t>(m.f_off) + t, virtual_emission(true, plain_logs), plain_logs);
         for (int j = q; j < m.L; j += lanes)
             emit_label[emission_at(m.e_off, m.L, t, j)] = virtual_emission(false, plain_logs);
     }
@@ -566,7 +566,7 @@ void ctc_softmax_rows_kernel(const T* __restrict__ x, T* __restrict__ grads, Utt
     bool small = false;
     if (q == 0) {
         const float e = encode_emission(log2_softmax(load_elem(row, blank), mx, ls), small, sa.plain_logs);
-        store_blank(emit_blank, sa.emit_blank64, static_cast<size_t>(m.f_off) + t, e);
+        store_blank(emit_blank, sa.emit_blank64, static_cast<size_t>(m.f_off) + t, e, sa.plain_logs);
     }
     float* const erow = emit_label + emission_at(m.e_off, m.L, t, 0);
     for (int j = q; j < m.L; j += kLanes) {
@@ -617,7 +617,7 @@ void ctc_softmax_kernel(const T* __restrict__ x, T* __restrict__ grads,
     bool small = false;
     if (threadIdx.x == 0) {
         const float e = encode_emission(log2_softmax(load_elem(row, blank), mx, ls), small, sa.plain_logs);
-        store_blank(emit_blank, sa.emit_blank64, static_cast<size_t>(m.f_off) + t, e);
+        store_blank(emit_blank, sa.emit_blank64, static_cast<size_t>(m.f_off) + t, e, sa.plain_logs);
     }
     if (t == m.Tb - 1) store_virtual_frames(m, emit_blank, sa.emit_blank64, emit_label, sa.plain_logs, threadIdx.x, kRowThreads);
     float* erow = emit_label + emission_at(m.e_off, m.L, t, 0);
@@ -712,7 +712,7 @@ __device__ __forceinline__ bool store_symbol_chunks(const float* lp, int Tb, int
     bool small = false;
     if (tid < padded) {
         const float e = tid < rows ? lp[tid * A + blank] : virtual_emission(true, plain_logs);
-        store_blank(emit_blank, emit_blank64, static_cast<size_t>(f_off) + t0 + tid, e);
+        store_blank(emit_blank, emit_blank64, static_cast<size_t>(f_off) + t0 + tid, e, plain_logs);
         small = !plain_logs && e < 0.0f;
     }
     // a wavefront per chunk: [symbol][frame], 8 A floats in a row
@@ -1093,12 +1093,12 @@ __device__ __forceinline__ void fetch_chunk(const float*& p, int64_t step, float
     for (int i = 0; i < kChunk; ++i) el[i] = v[kBackward ? kChunk - 1 - i : i];
     p += step;
 }
-// Predecessor choices of a pair at one frame, as stored for the backtrace: four bits, the steps of a chunk in one word
-// with the first step in the highest.  Each field is the number of states the walk moves down.  Bits 2..3, the label
-// state: 0 = stayed, 1 = came from the pair's blank, 2 = came from the label of the pair before (skipping the blank).
-// Bit 0, the blank state: 0 = stayed, 1 = came from the label of the pair before.  (A byte per frame and pair, stored at
-// every step, took four issue slots of a step; a bit of the word is one, an addition with carry.)
-constexpr int kChoiceBits = 4;
+// Predecessor choices of a pair at one frame, as stored for the backtrace: three bits, the steps of a chunk in one word
+// with the first step in the highest.  Bit 0: the blank state came from the label of the pair before (else it stayed).
+// Bits 2 and 1, the label state: it came from the label of the pair before, skipping the blank; if not, it came from
+// the pair's blank (else it stayed).  (A byte per frame and pair, stored at every step, took four issue slots of a step;
+// a bit of the word is one, an addition with carry.)
+constexpr int kChoiceBits = 3;
 __device__ __forceinline__ unsigned append_bit(unsigned word, unsigned long long lanes)
 {
     unsigned long long carry;
@@ -1191,7 +1191,7 @@ __device__ __forceinline__ Wave* halo_wave(void* lds, int wave)
 // so every wait ends; a poll budget bounds them regardless and raises chain_err when spent.
 template <bool kBackward, Sync kSync, Mode kMode>
 __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const int* __restrict__ labels,
-                                          const float* __restrict__ emit_blank,
+                                          const float* __restrict__ emit_blank, const double* __restrict__ emit_blank64,
                                           const float* __restrict__ emit_label,
                                           uint32_t* __restrict__ out, int* __restrict__ out_exponents,
                                           double* __restrict__ logp,
@@ -1347,8 +1347,10 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
         return r;
     };
     // ... and where the best way to it came from
+    int prev_origin_lane = 0;
     auto origin_from_prev_pair = [&](int s) {
-        int r = __builtin_amdgcn_update_dpp(0, label_origin, 0x138, 0xf, 0xf, false);
+        prev_origin_lane = __builtin_amdgcn_update_dpp(prev_origin_lane, label_origin, 0x138, 0xf, 0xf, false);
+        int r = prev_origin_lane;
         if (kSync == Sync::kBarrier) {
             int (*xch)[16] = reinterpret_cast<int (*)[16]>(static_cast<double*>(lds) + 32);
             if (lane == 63) xch[s & 1][wave] = label_origin;
@@ -1383,19 +1385,17 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
             auto better = [](double a, double b) { return kBackward ? a >= b : a > b; };
             const int prev_origin = origin_from_prev_pair(step);
             const double via_skip = prev + skip_penalty;
-            const bool blank_moves = better(prev, v_blank);
-            i_blank = blank_moves ? prev : v_blank;
-            const bool from_blank = better(v_blank, v_label);
-            double best = from_blank ? v_blank : v_label;
+            const bool blank_moves = better(prev, v_blank), from_blank = better(v_blank, v_label);
+            const double stay = fmax(v_blank, v_label);
+            const bool skips = better(via_skip, stay);
             const int stay_origin = from_blank ? blank_origin : label_origin;
-            const bool skips = better(via_skip, best);
-            i_label = skips ? via_skip : best;
+            i_blank = fmax(prev, v_blank);
+            i_label = fmax(via_skip, stay);
             label_origin = skips ? prev_origin : stay_origin;
             blank_origin = blank_moves ? prev_origin : blank_origin;
-            const unsigned long long skip_lanes = __ballot(skips);
-            choices = append_bit(choices, skip_lanes);
-            choices = append_bit(choices, __ballot(from_blank) & ~skip_lanes);
-            choices = append_bit(choices << 1, __ballot(blank_moves));
+            choices = append_bit(choices, __ballot(skips));
+            choices = append_bit(choices, __ballot(from_blank));
+            choices = append_bit(choices, __ballot(blank_moves));
         } else {
             // The blank state sums its own value and the label of the pair before; where the
             // label state may also be entered from that label (skip), its three-term sum is
@@ -1418,20 +1418,28 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
     };
     // (every lane starts from the exact state of its pair, halo lanes included)
     float el[4][kChunk], eb[2];
+    double blank_logs[2][kChunk] = {};                   // (Mode::kBest: as scalars, see run_chain_linear)
     auto fetch = [&](auto set, int i) {
         constexpr int k = decltype(set)::value;
-        if (i > 0) eb[(k + 1) & 1] = bp[blank_emission_offset(m, chain_chunk(i - 1, chunks, kBackward))];
+        if (i > 0 && kMode == Mode::kBest) {
+            asm volatile("" : : "s"(blank_logs[k & 1][0]), "s"(blank_logs[k & 1][kChunk - 1]));
+            const double* const w = emit_blank64 + blank_emission_offset(m, chain_chunk(i - 1, chunks, kBackward));
+#pragma unroll
+            for (int q = 0; q < kChunk; ++q) blank_logs[(k + 1) & 1][q] = w[kBackward ? kChunk - 1 - q : q];
+        } else if (i > 0) {
+            eb[(k + 1) & 1] = bp[blank_emission_offset(m, chain_chunk(i - 1, chunks, kBackward))];
+        }
         fetch_chunk<kBackward>(ep, estep, el[k]);
         __builtin_amdgcn_sched_barrier(0);
     };
     auto run = [&](auto set, int i) {
         constexpr int k = decltype(set)::value;
-        const Log2Parts blank = kCoded ? emission_log2_parts(eb[k & 1]) : Log2Parts{eb[k & 1], 0.0f};
+        const Log2Parts blank = kCoded ? emission_log2_parts(eb[k & 1]) : Log2Parts{0.0f, 0.0f};
 #pragma unroll
-        for (int q = 0; q < kChunk; ++q) {
-            const double whole_part = static_cast<double>(readlane(blank.whole, q));
-            advance(i * kChunk + q, kCoded ? whole_part + static_cast<double>(readlane(blank.part, q)) : whole_part, el[k][q]);
-        }
+        for (int q = 0; q < kChunk; ++q)
+            advance(i * kChunk + q,
+                    kCoded ? static_cast<double>(readlane(blank.whole, q)) + static_cast<double>(readlane(blank.part, q)) : blank_logs[k & 1][q],
+                    el[k][q]);
         end_chunk();
         if (kMode == Mode::kBest) {
             *op = choices;
@@ -2265,9 +2273,9 @@ __device__ __forceinline__ void lattice_body(const Utt* __restrict__ meta, const
         }
     }
     if (forward)
-        run_chain_log<false, kSync, kMode>(m, u, labels, emit_blank, emit_label, lat.alpha, lat.alpha_exponents, logp, costs, chain_err, sink, lds);
+        run_chain_log<false, kSync, kMode>(m, u, labels, emit_blank, emit_blank64, emit_label, lat.alpha, lat.alpha_exponents, logp, costs, chain_err, sink, lds);
     else if constexpr (kMode != Mode::kLoss)
-        run_chain_log<true, kSync, kMode>(m, u, labels, emit_blank, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
+        run_chain_log<true, kSync, kMode>(m, u, labels, emit_blank, emit_blank64, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
     if (kMode == Mode::kGrad && kSync != Sync::kBarrier && wk.announce) announce_end(&wk.done[u * kDoneStride], waves);
 }
 
@@ -2442,9 +2450,10 @@ void ctc_backtrace_kernel(const Utt* __restrict__ meta, const int* __restrict__ 
                 // lane r of `filed` = state at step first + r
                 asm volatile("v_writelane_b32 %0, %1, %2" : "+v"(filed) : "s"(at), "n"(c * kChunk + q));
                 const unsigned w = __builtin_amdgcn_readlane(word[c], (at >> 1) - pair_lo);
-                // how far down the state of this step came from: the upper two bits if it is a label state (odd), the lower
-                // two if it is a blank
-                at = max(at - static_cast<int>((w >> ((kChunk - 1 - q) * kChoiceBits + ((at << 1) & 2))) & 3u), 0);
+                // how far down the state of this step came from: the upper two bits (3 is 2 as well) if it is a label
+                // state (odd), the lowest if it is a blank
+                const int odd = at & 1, bits = static_cast<int>(w >> ((kChunk - 1 - q) * kChoiceBits + odd)) & (1 + 2 * odd);
+                at = max(at - min(bits, 2), 0);
             }
         }
         if (lane < rows) {

@@ -195,7 +195,7 @@ inline int deferred_frames(double zero_bytes, int longest, int n_chains, int n_c
 
 // The gradient of an utterance may be written by workgroups of the lattice launch that wait for its chains
 // (Launch::fused).  Chains that need more wavefronts than a workgroup of that launch has keep a launch of their own.
-constexpr int kFusedWaves = 4;
+constexpr int kFusedWaves = 12;
 constexpr int kDoneStride = 16;      // words between two utterances' counters: a line each for those who poll
 
 inline bool fuse_gradient(int A, int max_waves, int n_chains, int n_cu)

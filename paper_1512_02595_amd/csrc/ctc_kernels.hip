@@ -3251,6 +3251,7 @@ void ctc_lattice_gradient_kernel(const Utt* __restrict__ meta, const int* __rest
         lattice_body<kSync, Mode::kGrad>(meta, order, labels, emit_blank, emit_blank64, emit_label, lat, logp, costs, chain_err, sink,
                                          fused_lds, wk);
     } else {
+        if (threadIdx.x >= kRowThreads) return;          // (workgroups as large as the longest label's chains)
         const int i = index - tiles.first_group, rank = i / tiles.groups;
         const int b = __builtin_amdgcn_readfirstlane(tiles.by_end[rank]), group = i - rank * tiles.groups;
         narrow_tile<kTiles, true>(tiles, meta, labels, emit_blank64, emit_label, lat, fused_lds, b, group);
@@ -3476,10 +3477,11 @@ int launch_lattice(const Launch& p, void* stream)
     if (p.fused) {
         size_t lds;
         TileArgs tiles = tile_args(p, &lds);
-        lds = std::max(lds, halo_lds_bytes(kFusedWaves));
+        const int waves = std::max(p.max_waves, kRowThreads / 64);
+        lds = std::max(lds, halo_lds_bytes(waves));
         wk.announce = true;
         tiles.first_group = n_groups;
-        const dim3 grid(n_groups + tiles.groups * p.B), block(64 * kFusedWaves);
+        const dim3 grid(n_groups + tiles.groups * p.B), block(64 * waves);
 #define CTC_LAUNCH_FUSED(SYNC, TILES)                                                              \
     hipLaunchKernelGGL((ctc_lattice_gradient_kernel<SYNC, TILES>), grid, block, lds, s, meta, order, labels, emit_blank,   \
                        reinterpret_cast<const double*>(p.ws + p.lay.emit_blank64), emit_label,                \

@@ -77,7 +77,9 @@ typedef enum {
 enum {
     CTC_KERNEL_SOFTMAX = 0,    /* row-wise log-softmax statistics + emission gather (for alphabets
                                   wider than 2048 also the dense part of the gradient) */
-    CTC_KERNEL_LATTICE = 1,    /* alpha and beta recursions, one launch */
+    CTC_KERNEL_LATTICE = 1,    /* alpha and beta recursions, one launch; where no more chains run than
+                                  there are compute units, and the alphabet has at most 64 symbols, also
+                                  the gradient */
     CTC_KERNEL_GRADIENT = 2,   /* softmax minus normalised occupancy, zero fill of padding */
     /* A short copy launch (the per-call metadata, from pinned host memory into the workspace)
        precedes these three and is not timed separately; the grouping of each label's positions
@@ -151,8 +153,10 @@ ctc_status_t ctc_loss_and_grad(const void *activations,
  * read, i.e. the cost of the bracketing itself).  For measurement (the per-kernel timings that the
  * paper's Table "gpucpuctc" aggregates per epoch), not for the training loop.
  *
- *   kernel_ms     (host) [CTC_NUM_KERNELS]; with grads == NULL there is no third launch and
- *                 the third entry is (close to) zero
+ *   kernel_ms     (host) [CTC_NUM_KERNELS]; the third entry is 0 where the call has no third launch:
+ *                 with grads == NULL, and where the lattice launch writes the gradient as well
+ *                 (alphabets of at most 64 symbols, no more chains -- two per utterance -- than compute
+ *                 units: the second entry is then the time of both)
  */
 ctc_status_t ctc_profile_kernels(const void *activations,
                                  const int32_t *flat_labels,
@@ -219,7 +223,8 @@ ctc_status_t ctc_loss_and_grad_device(const void *activations,
                                       hipStream_t stream);
 
 /* ctc_loss_and_grad_device with per-launch device times, as ctc_profile_kernels (it waits for the
- * stream, so it cannot be captured): kernel_ms (host) [CTC_NUM_KERNELS] = softmax, lattice, gradient;
+ * stream, so it cannot be captured): kernel_ms (host) [CTC_NUM_KERNELS] = softmax, lattice, gradient
+ * (0 where the lattice launch writes the gradient);
  * where a planning launch precedes the softmax launch (alphabets wider than 64 symbols, more than
  * 512 utterances) it is not timed separately. */
 ctc_status_t ctc_profile_kernels_device(const void *activations,

@@ -516,7 +516,6 @@ ctc_status_t run(const Call& c, float* kernel_ms)
         if (!slot) return st;
         st = prepare(c, lay, &p, slot->image());
         if (st != CTC_STATUS_SUCCESS) return st;
-        if (kernel_ms) p.fused = false;                  // (a profiled call times the launches one by one)
         if (kernel_ms && !events.create()) return CTC_STATUS_HIP_ERROR;
         slot->generation += 1;
         p.host_flag = slot->flag();
@@ -623,7 +622,7 @@ ctc_status_t run_device(const void* x, const int32_t* labels, const int32_t* lab
     // (how much padding there is only the GPU knows: taken for a third of the tensor)
     p.defer = grads && A > kDirectMaxA && !p.needs_barrier
                   ? deferred_frames(static_cast<double>(T) * B * A * elem / 3, T / 2, p.n_chains, p.n_cu) : 0;
-    p.fused = grads && !p.needs_barrier && !kernel_ms && fuse_gradient(A, p.max_waves, p.n_chains, p.n_cu);
+    p.fused = grads && !p.needs_barrier && fuse_gradient(A, p.max_waves, p.n_chains, p.n_cu);
     // Narrow alphabets: the softmax launch builds the records itself (no planning launch before it); every
     // utterance's setup workgroup weighs all B utterances for the run order, which is worth it up to here.
     p.folded = A <= kDirectMaxA && B <= kDeviceFoldMaxB && max_label > 0;

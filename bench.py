@@ -142,8 +142,8 @@ def main():
     ap.add_argument("--profile-steps", type=int, default=20)
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--overlap", type=int, default=-1,
-                    help="0: write the whole gradient in a launch of its own even where the lattice launch has idle "
-                         "compute units; 1..100: ctc_debug_set_overlap; default: the library's setting")
+                    help="0: write the gradient in a launch of its own even where the lattice launch has idle "
+                         "compute units (ctc_debug_set_overlap); default: the library's setting")
     ap.add_argument("--sequential-chains", action="store_true",
                     help="measurement of the paper's order: the forward recursion's launch, then the backward one's "
                          "(ctc_debug_set_sequential_chains); the JSON line says so and is no headline figure")

@@ -285,8 +285,8 @@ def debug_set_sequential_chains(on: bool) -> None:
 
 
 def debug_set_overlap(percent: int) -> None:
-    """Gradient rows inside the lattice launch where it leaves compute units idle: 0 off, 1..100 the
-    share of the launch within which an utterance's chains must end, negative the default."""
+    """The gradient inside the lattice launch where that leaves compute units idle: 0 gives it a launch of its
+    own, anything else restores the default."""
     load().ctc_debug_set_overlap(int(percent))
 
 

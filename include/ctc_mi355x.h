@@ -34,7 +34,7 @@
  *     256 MiB per device; a call that then finds every slot in flight returns
  *     CTC_STATUS_NOT_READY immediately, with nothing enqueued.
  *     ctc_loss_and_grad_device uses none of this.
- *   - The poll budget of ctc_debug_set_poll_budget, and the calling thread's
+ *   - The settings of the ctc_debug_set_ functions, and the calling thread's
  *     last HIP error code.
  */
 #ifndef CTC_MI355X_H
@@ -341,6 +341,17 @@ int ctc_last_hip_error(void);
  * end.  Negative values restore the default.  Applies to calls made afterwards, process-wide.
  */
 void ctc_debug_set_poll_budget(int polls);
+
+/*
+ * Diagnostics.  Where the gradient is written inside the recursions' launch, its workgroups wait for the
+ * recursions of their utterance by polling a word in memory, at most `polls` times (default 2^22) and four
+ * times per frame on top, which takes longer than any recursion; one that runs out writes zeros for its rows,
+ * and the utterance's cost is reported as NaN.  Setting it to 0 makes every workgroup that finds the recursions
+ * still under way give up at once, which lets a test see that path with every kernel still running to its end:
+ * an utterance's cost is then NaN, or it and the gradient are right.  Negative values restore the default.
+ * Applies to calls made afterwards, process-wide.
+ */
+void ctc_debug_set_end_polls(int polls);
 
 /*
  * Diagnostics.  Where a call's recursions leave compute units idle (no more chains, two per utterance,

@@ -25,6 +25,7 @@ namespace {
 
 thread_local int g_last_hip_error = 0;
 std::atomic<int> g_poll_budget{kDefaultPollBudget};
+std::atomic<int> g_end_polls{kDefaultEndPolls};
 std::atomic<int> g_sequential_chains{0};
 std::atomic<int> g_overlap{-1};          // 0: the gradient in a launch of its own
 
@@ -440,6 +441,7 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
     out->dev_input_lengths = nullptr;
     out->dev_status = nullptr;
     out->poll_budget = poll_budget;
+    out->end_polls = g_end_polls.load(std::memory_order_relaxed);
     out->crowded = crowded;
     out->sequential_chains = sequential_chains;
     out->n_cu = compute_units();
@@ -620,6 +622,7 @@ ctc_status_t run_device(const void* x, const int32_t* labels, const int32_t* lab
     p.dev_input_lengths = input_lengths;
     p.dev_status = status;
     p.poll_budget = g_poll_budget.load(std::memory_order_relaxed);
+    p.end_polls = g_end_polls.load(std::memory_order_relaxed);
     p.n_cu = compute_units();
     // (how much padding there is only the GPU knows: taken for a third of the tensor)
     p.defer = grads && A > kDirectMaxA && !p.needs_barrier
@@ -903,6 +906,11 @@ void ctc_debug_set_sequential_chains(int on)
 void ctc_debug_set_poll_budget(int polls)
 {
     ctc::g_poll_budget.store(polls < 0 ? ctc::kDefaultPollBudget : polls, std::memory_order_relaxed);
+}
+
+void ctc_debug_set_end_polls(int polls)
+{
+    ctc::g_end_polls.store(polls < 0 ? ctc::kDefaultEndPolls : polls, std::memory_order_relaxed);
 }
 
 }  // extern "C"

@@ -298,6 +298,7 @@ inline void order_chains(const int32_t* utt, const int32_t* frames, const int32_
 }
 
 constexpr int kDefaultPollBudget = 1 << 22;   // enough for seconds of waiting: only a stuck neighbour exhausts it
+constexpr int kDefaultEndPolls = 1 << 22;     // the same for the workgroups that wait for chains in the lattice launch
 constexpr int kMaxBatch = 65535;         // utterances index the second grid dimension of the row kernels
 constexpr int kMaxDeviceMetaB = 4096;   // utterances the device-side planner ranks in LDS
 
@@ -470,7 +471,8 @@ struct Launch {
     int poll_budget;          // copied into every Utt record
     bool crowded;             // plan the chains for total work rather than latency (device planner)
     int n_cu;                 // compute units of the device
-    bool fused;               // the lattice launch writes the gradient too (launch_lattice_gradient)
+    bool fused;               // the lattice launch writes the gradient too (ctc_lattice_gradient_kernel)
+    int end_polls;            // ... and how often its workgroups look for the end of their chains (wait_for_chains)
     int defer;                // of every 16 frames, those whose zero rows the lattice launch writes (deferred_frames)
     // Narrow alphabets, host metadata: there is no upload launch; the softmax launch reads the pinned image
     // itself and copies it into the workspace for the launches after it, and the lattice launch releases it.

@@ -2159,22 +2159,27 @@ __device__ __forceinline__ void finish_loss(const Utt& m, const int u, const int
     }
 }
 
+// The word that an utterance's chains and the workgroups that wait for them share: wavefronts that have ended, wavefronts
+// there are (from bit 10), chains that have said how many (from bit 20), and whether a workgroup has given up waiting.
+constexpr int kWavesShift = 10, kChainsShift = 20, kWaitGivenUp = 1 << 24;
+__device__ __forceinline__ bool chains_ended(int done)
+{
+    constexpr int kField = (1 << kWavesShift) - 1;
+    return ((done >> kChainsShift) & 3) == 2 && (done & kField) == ((done >> kWavesShift) & kField);
+}
 // A wavefront of a chain has ended, and everything it has published is out; `waves` of them make the chain, the first says
-// so.  An utterance's counter: wavefronts that have ended, wavefronts there are (from bit 10), chains that have said how many
-// (from bit 20).
-constexpr int kWavesShift = 10, kChainsShift = 20;
-__device__ __forceinline__ void announce_end(int* done, int waves)
+// so.  Should somebody have given up waiting, rows of the gradient are missing: the last wavefront to end, which comes after
+// the one that has stored the cost, makes that NaN.
+__device__ __forceinline__ void announce_end(int* done, int waves, float* cost)
 {
     // (what was stored the ordinary way must leave the die's cache)
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     const int count = threadIdx.x < 64 ? 1 + (waves << kWavesShift) + (1 << kChainsShift) : 1;
-    if ((threadIdx.x & 63) == 0) __hip_atomic_fetch_add(done, count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ bool chains_ended(int done)
-{
-    constexpr int kField = (1 << kWavesShift) - 1;
-    return (done >> kChainsShift) == 2 && (done & kField) == ((done >> kWavesShift) & kField);
+    if ((threadIdx.x & 63) == 0) {
+        const int now = __hip_atomic_fetch_add(done, count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + count;
+        if ((now & kWaitGivenUp) && chains_ended(now)) publish(cost, __uint_as_float(0x7FC00000u));
+    }
 }
 
 template <Sync kSync, Mode kMode>
@@ -2268,7 +2273,7 @@ __device__ __forceinline__ void lattice_body(const Utt* __restrict__ meta, const
                 lost = run_chain_linear<true, kSync, kMode>(m, u, labels, emit_blank64, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
             }
             if (kMode == Mode::kLoss) finish_loss(m, u, labels, lat, wk.done, costs, 2 * waves, lost);
-            if (kMode == Mode::kGrad && wk.announce) announce_end(&wk.done[u * kDoneStride], waves);
+            if (kMode == Mode::kGrad && wk.announce) announce_end(&wk.done[u * kDoneStride], waves, &costs[u]);
             return;
         }
     }
@@ -2276,7 +2281,7 @@ __device__ __forceinline__ void lattice_body(const Utt* __restrict__ meta, const
         run_chain_log<false, kSync, kMode>(m, u, labels, emit_blank, emit_blank64, emit_label, lat.alpha, lat.alpha_exponents, logp, costs, chain_err, sink, lds);
     else if constexpr (kMode != Mode::kLoss)
         run_chain_log<true, kSync, kMode>(m, u, labels, emit_blank, emit_blank64, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
-    if (kMode == Mode::kGrad && kSync != Sync::kBarrier && wk.announce) announce_end(&wk.done[u * kDoneStride], waves);
+    if (kMode == Mode::kGrad && kSync != Sync::kBarrier && wk.announce) announce_end(&wk.done[u * kDoneStride], waves, &costs[u]);
 }
 
 // grid = one workgroup per entry of `order` (utterance * 2 + direction: 0 forward, 1 backward).
@@ -2905,7 +2910,8 @@ struct TileArgs {
     float* costs;
     const int* domain;
     const int* links;             // wide
-    const int* done;              // lattice launch: what to wait for
+    int* done;                    // lattice launch: what to wait for
+    int end_polls;                // ... and how often to look before giving up
     const int* by_end;            // ... the utterances, those first whose chains end first
     int T, B, A, blank, Lmax;
     int share_blocks;             // narrow
@@ -2918,22 +2924,32 @@ __device__ __forceinline__ void store_gradient(const TileArgs& g, size_t i, floa
     if (g.bf16) store_elem(static_cast<bf16_t*>(g.grads), i, v);
     else store_elem(static_cast<float*>(g.grads), i, v);
 }
-// By the whole workgroup: until utterance b's chains have ended.  They were handed out before this workgroup was and
-// wait for nobody but each other, so they end; should they not, `polls` runs out (seconds) and the cost is NaN.
-constexpr int kEndPolls = 1 << 23;
-__device__ __forceinline__ void wait_for_chains(const TileArgs& g, int b)
+// By the whole workgroup: waits until utterance b's chains have ended; the same answer in every thread.  The wait is bounded
+// (TileArgs::end_polls and four polls a frame, a frame taking less than one): should it run out, the answer is false, there
+// is nothing to compute rows from, and the utterance's cost is NaN -- by this workgroup, and by the chain that ends last if
+// that is still to come (both go through the utterance's word, so one of them is the later one whatever the order).
+__device__ __forceinline__ bool wait_for_chains(const TileArgs& g, int b, int frames)
 {
+    __shared__ int s_ended;
     if (threadIdx.x < 64) {
-        int polls = kEndPolls;
-        while (!chains_ended(__builtin_amdgcn_readfirstlane(published(&g.done[b * kDoneStride])))) {
-            if (--polls == 0) {
-                if (threadIdx.x == 0) publish(&g.costs[b], __uint_as_float(0x7FC00000u));
-                break;
-            }
+        int* const done = &g.done[b * kDoneStride];
+        auto look = [&]() { return chains_ended(__builtin_amdgcn_readfirstlane(published(done))); };
+        int64_t polls = g.end_polls > 0 ? g.end_polls + 4 * static_cast<int64_t>(frames) : 0;
+        bool ended = look();
+        for (; !ended && polls > 0; --polls) {
             __builtin_amdgcn_s_sleep(10);
+            ended = look();
         }
+        if (!ended) {
+            int word = 0;
+            if (threadIdx.x == 0) word = __hip_atomic_fetch_or(done, kWaitGivenUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            ended = chains_ended(__builtin_amdgcn_readfirstlane(word));
+            if (!ended && threadIdx.x == 0) publish(&g.costs[b], __uint_as_float(0x7FC00000u));
+        }
+        if (threadIdx.x == 0) s_ended = ended;
     }
     __syncthreads();
+    return __builtin_amdgcn_readfirstlane(s_ended) != 0;
 }
 
 // Workgroup `group` of utterance b: kRowThreads / 64 wavefronts, ceil(blocks of T / (4 / wavefronts per block)) workgroups;
@@ -2951,13 +2967,13 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
     const int first_block = group * (kRowThreads / 64 / sharing);
     const int block = first_block + wave / sharing, t0 = block * kBlockFrames;
     const bool runs = (m.flags & kUttRuns) != 0, has_rows = runs && t0 < m.Tb;
-    if (!has_rows && part == 0) {
-        // no lattice: zeros
+    auto zero_rows = [&]() {
 #pragma unroll 4
         for (int r = 0; r < kBlockFrames; ++r)
             if (t0 + r < Tt && lane < A) store_gradient(g_args, (static_cast<size_t>(t0 + r) * B + b) * A + lane, 0.0f);
-    }
+    };
     if (!has_rows) {
+        if (part == 0) zero_rows();                      // no lattice
         // (the barriers below)
         if (kWait && runs && first_block * kBlockFrames < m.Tb) __syncthreads();
         if (sharing > 1) __syncthreads();
@@ -3004,7 +3020,10 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
     if (lane < 8) s_emit[2 * A * kEmissionRow + lane] = 0.0f;
     if (lane < kBlockFrames) s_blank[lane] = blank_emission;
     if (kWait) {
-        wait_for_chains(g_args, b);
+        if (!wait_for_chains(g_args, b, m.Tb)) {
+            if (part == 0) zero_rows();
+            return;
+        }
         load_ends();
         if (log_domain) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
@@ -3419,7 +3438,8 @@ static TileArgs tile_args(const Launch& p, size_t* lds)
     g.costs = p.costs;
     g.domain = reinterpret_cast<const int*>(p.ws + p.lay.domain);
     g.links = reinterpret_cast<const int*>(p.ws + p.lay.links);
-    g.done = reinterpret_cast<const int*>(p.ws + p.lay.done);
+    g.done = reinterpret_cast<int*>(p.ws + p.lay.done);
+    g.end_polls = p.end_polls;
     g.by_end = reinterpret_cast<const int*>(p.ws + p.lay.order) + 2 * p.B;
     g.T = p.T; g.B = p.B; g.A = p.A; g.blank = p.blank;
     g.Lmax = p.max_label;

@@ -37,6 +37,7 @@ EXPORTS = ("ctc_workspace_size", "ctc_loss_and_grad", "ctc_profile_kernels",
            "ctc_workspace_size_device", "ctc_loss_and_grad_device", "ctc_loss_and_grad_device_static",
            "ctc_profile_kernels_device", "ctc_debug_set_sequential_chains",
            "ctc_kernel_name", "ctc_status_string", "ctc_last_hip_error", "ctc_debug_set_poll_budget",
+           "ctc_debug_set_end_polls",
            "ctc_debug_staging_allocations", "ctc_debug_set_overlap", "ctc_debug_replay_emission_fetches")
 
 _lib = None
@@ -90,6 +91,8 @@ def load() -> ctypes.CDLL:
     lib.ctc_last_hip_error.argtypes = []
     lib.ctc_debug_set_poll_budget.restype = None
     lib.ctc_debug_set_poll_budget.argtypes = [ci]
+    lib.ctc_debug_set_end_polls.restype = None
+    lib.ctc_debug_set_end_polls.argtypes = [ci]
     lib.ctc_debug_replay_emission_fetches.restype = ctypes.c_long
     lib.ctc_debug_replay_emission_fetches.argtypes = [ci, ci, ci, i32p, i32p, ci, ctypes.POINTER(ctypes.c_long)]
     lib.ctc_debug_set_overlap.restype = None
@@ -272,6 +275,11 @@ def loss_and_grad_device(*args, **kw) -> None:
 def debug_set_poll_budget(polls: int) -> None:
     """LDS polls a lattice wavefront may spend waiting on its neighbour (negative: default)."""
     load().ctc_debug_set_poll_budget(int(polls))
+
+
+def debug_set_end_polls(polls: int) -> None:
+    """How often a gradient workgroup of the lattice launch looks for the end of its chains (negative: default)."""
+    load().ctc_debug_set_end_polls(int(polls))
 
 
 def debug_staging_allocations() -> int:

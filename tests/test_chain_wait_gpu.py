@@ -1,0 +1,38 @@
+"""GPU tests of the workgroups that write the gradient inside the lattice launch and wait for the chains of their utterance."""
+import numpy as np
+import pytest
+
+from oracle import ctc_oracle as orc
+from paper_1512_02595_amd import ctc, harness
+from paper_1512_02595_amd import workloads as wl
+
+import parity_checks as pc
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("max_label", [40, 200])        # chains of one wavefront, of several
+def test_a_wait_that_gives_up_is_reported_as_nan_cost(max_label):
+    """No look at the chains but the first: a workgroup that finds them under way writes zeros, and the cost is NaN even
+    though the chains go on to their end and store one.  Whatever else is there is right."""
+    batch = wl.make_random(71, T=500, B=6, A=29, max_label=max_label, min_input=400, sigma=2.0, feasible_only=True)
+    ref_c, ref_g = orc.ctc_loss_and_grad(batch.logits, batch.flat_labels, batch.label_lengths, batch.input_lengths, batch.blank)
+    db = harness.DeviceBatch(batch)
+    db.poison()
+    ctc.debug_set_end_polls(0)
+    try:
+        db.run()
+    finally:
+        ctc.debug_set_end_polls(-1)
+    costs, grads = db.results()
+    lost = np.isnan(costs)
+    print(f"  costs {costs}", flush=True)
+    assert lost.any()                                    # (the first workgroups look before a chain has made its steps)
+    assert (np.abs(costs - ref_c)[~lost] <= pc.COST_RTOL * ref_c[~lost]).all()
+    assert np.isfinite(grads).all()
+    close = np.abs(grads - ref_g).max(axis=2) <= pc.GRAD_ATOL                  # [frame][utterance]
+    assert close[:, ~lost].all() and (close | (grads == 0).all(axis=2)).all()
+    # and the next call on the same buffers is none the worse for it
+    db.run()
+    costs, grads = db.results()
+    assert (np.abs(costs - ref_c) <= pc.COST_RTOL * ref_c).all() and np.abs(grads - ref_g).max() <= pc.GRAD_ATOL

@@ -358,8 +358,10 @@ void ctc_debug_set_end_polls(int polls);
  * than compute units; alphabets of at most 64 symbols; labels of no more than twelve wavefronts), the
  * gradient is written inside the recursions' launch, by workgroups that each wait for the two chains of
  * their utterance.  `percent`: 0 gives the gradient a launch of its own after the recursions', for calls
- * made afterwards, process-wide (for measurements of the two forms side by side); anything else restores
- * the default.  Results are bitwise the same whatever the setting.
+ * made afterwards, process-wide (for measurements of the two forms side by side); 1..100 makes the
+ * recursions' own workgroups leave about that share of them to the workgroups that wait, which then run them,
+ * as they do when another launch keeps the former from a compute unit (for tests); anything else restores the
+ * default.  Results are bitwise the same whatever the setting.
  */
 void ctc_debug_set_overlap(int percent);
 

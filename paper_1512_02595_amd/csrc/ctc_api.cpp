@@ -27,7 +27,7 @@ thread_local int g_last_hip_error = 0;
 std::atomic<int> g_poll_budget{kDefaultPollBudget};
 std::atomic<int> g_end_polls{kDefaultEndPolls};
 std::atomic<int> g_sequential_chains{0};
-std::atomic<int> g_overlap{-1};          // 0: the gradient in a launch of its own
+std::atomic<int> g_overlap{-1};          // 0: the gradient in a launch of its own; 1..100: Launch::late_percent
 
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
@@ -451,8 +451,10 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
         for (int i = 0; i < n_run; ++i) rows -= run_frames[i];
         out->defer = deferred_frames(static_cast<double>(rows) * c.A * elem, max_frames, n_run * dirs, out->n_cu);
     }
+    const int overlap = g_overlap.load(std::memory_order_relaxed);
+    out->late_percent = std::max(overlap, 0);
     out->fused = c.mode == Mode::kGrad && !needs_barrier && !sequential_chains && n_run > 0 &&
-                 g_overlap.load(std::memory_order_relaxed) != 0 && fuse_gradient(c.A, max_waves, n_run * dirs, out->n_cu);
+                 overlap != 0 && fuse_gradient(c.A, max_waves, n_run * dirs, out->n_cu);
     out->folded = c.A <= kDirectMaxA && c.B <= kNarrowMaxB && c.T < (1 << 29);
     out->lay = lay;
     return CTC_STATUS_SUCCESS;
@@ -627,8 +629,9 @@ ctc_status_t run_device(const void* x, const int32_t* labels, const int32_t* lab
     // (how much padding there is only the GPU knows: taken for a third of the tensor)
     p.defer = grads && A > kDirectMaxA && !p.needs_barrier
                   ? deferred_frames(static_cast<double>(T) * B * A * elem / 3, T / 2, p.n_chains, p.n_cu) : 0;
-    p.fused = grads && !p.needs_barrier && g_overlap.load(std::memory_order_relaxed) != 0 &&
-              fuse_gradient(A, p.max_waves, p.n_chains, p.n_cu);
+    const int overlap = g_overlap.load(std::memory_order_relaxed);
+    p.late_percent = std::max(overlap, 0);
+    p.fused = grads && !p.needs_barrier && overlap != 0 && fuse_gradient(A, p.max_waves, p.n_chains, p.n_cu);
     // Narrow alphabets: the softmax launch builds the records itself (no planning launch before it); every
     // utterance's setup workgroup weighs all B utterances for the run order, which is worth it up to here.
     p.folded = A <= kDirectMaxA && B <= kDeviceFoldMaxB && max_label > 0;

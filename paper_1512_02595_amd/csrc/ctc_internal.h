@@ -196,7 +196,9 @@ inline int deferred_frames(double zero_bytes, int longest, int n_chains, int n_c
 // The gradient of an utterance may be written by workgroups of the lattice launch that wait for its chains
 // (Launch::fused).  Chains that need more wavefronts than a workgroup of that launch has keep a launch of their own.
 constexpr int kFusedWaves = 12;
-constexpr int kDoneStride = 16;      // words between two utterances' counters: a line each for those who poll
+constexpr int kDoneStride = 16;      // words between two utterances' words: a line each for those who poll
+constexpr int kTakenWord = 1;        // which of them say that somebody runs the chain, by direction (the first is the counter)
+constexpr int kDoneWords = 3;
 
 inline bool fuse_gradient(int A, int max_waves, int n_chains, int n_cu)
 {
@@ -401,7 +403,7 @@ struct Layout {
     size_t sink = 0;      // what lanes with nothing to store scribble on: kSinkBytes per wavefront of a lattice launch
     size_t chain_err = 0; // int32[B]     set when a lattice wavefront gave up waiting for its neighbour
     size_t done = 0;      // int32[B * kDoneStride]  how far the utterance's chains are: cost-only calls (finish_loss)
-                          //              and gradients written beside the chains (announce_end)
+                          //              and gradients written beside the chains (announce_end, chain_to_take)
     size_t domain = 0;    // int32[2 B]   per utterance and direction, nonzero: that chain ran in the log domain (published by
                           //              the chain for the gradient, which must know where its exponent rows are)
     size_t row_flags = 0; // int32[B * ceil(T / 64)]  narrow alphabets: per 64 frames of an utterance, nonzero if one of
@@ -472,6 +474,7 @@ struct Launch {
     bool crowded;             // plan the chains for total work rather than latency (device planner)
     int n_cu;                 // compute units of the device
     bool fused;               // the lattice launch writes the gradient too (ctc_lattice_gradient_kernel)
+    int late_percent;         // ... and this share of the chains' own workgroups come late (tests)
     int end_polls;            // ... and how often its workgroups look for the end of their chains (wait_for_chains)
     int defer;                // of every 16 frames, those whose zero rows the lattice launch writes (deferred_frames)
     // Narrow alphabets, host metadata: there is no upload launch; the softmax launch reads the pinned image

@@ -328,7 +328,8 @@ struct SetupArgs {
     int* links;
     float* costs;
     int* chain_err;
-    int* done;            // per utterance (kDoneStride apart): wavefronts that have ended (finish_loss, announce_end)
+    int* done;            // per utterance (kDoneStride apart): kDoneWords words that its chains and those who wait for them
+                          // share (finish_loss, announce_end, chain_to_take)
     float* log0;          // kEmissionConstants floats that lattice lanes without a label state read as their
                           // emission: probability 0 (linear-domain chains) and log 0 (log-domain chains)
     double* emit_blank64; // the blank's probability per frame as fp64 (Layout::emit_blank64)
@@ -391,7 +392,7 @@ __device__ __forceinline__ void setup_words(const Utt m, const int b, const Setu
 {
     if (threadIdx.x == 0) {
         sa.chain_err[b] = 0;
-        sa.done[b * kDoneStride] = 0;
+        for (int i = 0; i < kDoneWords; ++i) sa.done[b * kDoneStride + i] = 0;
         if (b == 0) {
             for (int i = 0; i < kEmissionConstants; ++i) sa.log0[i] = i < kLogZeroEmission ? 0.0f : static_cast<float>(kNeg);
             // This launch follows the upload kernel on the stream, so the host may now reuse
@@ -1119,7 +1120,7 @@ struct HaloHeader {
     int finished;                     // wavefronts that have reached the end of the chain
     int gave_up;
     float cost;
-    int unused;
+    int taken;                        // chains of a launch that writes the gradient too: somebody else runs this one
 };
 // Chains with one pair per lane.
 struct HaloWave {
@@ -2084,7 +2085,7 @@ struct LaunchWords {
     int flag_blocks;          // ... per utterance
     int* domain;              // per utterance and direction: did the chain run in the log domain
     int* done;                // per utterance, kDoneStride apart: see finish_loss, announce_end
-    bool announce;            // ... the latter: somebody waits for the chains
+    int late_percent;         // launch that writes the gradient too: this share of the chains' own workgroups come late (tests)
     int* host_flag;           // pinned host word that receives host_flag_value: the image may be reused (or nullptr)
     int host_flag_value;
     const int* status_words;  // device-resident metadata built by the narrow softmax launch: per utterance, nonzero if
@@ -2182,15 +2183,31 @@ __device__ __forceinline__ void announce_end(int* done, int waves, float* cost)
     }
 }
 
-template <Sync kSync, Mode kMode>
-__device__ __forceinline__ void lattice_body(const Utt* __restrict__ meta, const int* __restrict__ order,
-                                             const int* __restrict__ labels,
+// A launch that writes the gradient too: who runs a chain, in the utterance's word for its direction.  0: nobody yet; kTakenByOwn:
+// the chain's own workgroup; kTakenByTile + i: the gradient's workgroup i (chain_to_take).  Written once.
+constexpr int kTakenByOwn = 1, kTakenByTile = 2;
+// Takes the chain if nobody has; returns what was in the word.
+__device__ __forceinline__ int take_chain(int* word, int by_whom)
+{
+    int before = 0;
+    __hip_atomic_compare_exchange_strong(word, &before, by_whom, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return before;
+}
+// (tests: a chain's own workgroup comes so late that others have taken it; bounded, in case nobody waits for it)
+__device__ __forceinline__ void wait_until_taken(const int* word)
+{
+    for (int polls = 1 << 12; polls > 0 && published(word) == 0; --polls) __builtin_amdgcn_s_sleep(10);
+}
+
+// `chain`: utterance * 2 + direction.  kFused: the launch writes the gradient too; `taken`: this workgroup has taken the chain.
+template <Sync kSync, Mode kMode, bool kFused = false>
+__device__ __forceinline__ void lattice_body(const int chain, const Utt* __restrict__ meta, const int* __restrict__ labels,
                                              const float* __restrict__ emit_blank, const double* __restrict__ emit_blank64,
                                              const float* __restrict__ emit_label,
                                              const LatticeOut lat,
                                              double* __restrict__ logp, float* __restrict__ costs,
                                              int* __restrict__ chain_err, uint32_t* __restrict__ sink,
-                                             void* lds, const LaunchWords& wk)
+                                             void* lds, const LaunchWords& wk, const bool taken = false)
 {
     // The first workgroup of the launch tells the host that the pinned image of the call is free
     // again (calls whose softmax launch read the image itself: this launch follows it).
@@ -2208,13 +2225,19 @@ __device__ __forceinline__ void lattice_body(const Utt* __restrict__ meta, const
     // every chain carried a write to it, and they all met in one channel of each die's L2.  512
     // utterances of 20 symbols and 740 frames: 59 -> 40 us.  Writing to an unused column of the
     // chain's own rows instead was slower than either in launches that are not crowded.)
-    sink += (static_cast<size_t>(blockIdx.x) * kSinkWaves + (threadIdx.x >> 6)) * (kSinkBytes / sizeof(uint32_t));
-    const int chain = order[blockIdx.x];           // utterance * 2 + direction
     if (chain < 0) return;      // device-planned batches launch a workgroup per utterance and direction, running or not
     // (measurements of the recursions one after the other: a launch that leaves one direction out)
     if (kMode == Mode::kGrad && ((wk.skip_directions >> (chain & 1)) & 1)) return;
+    sink += (static_cast<size_t>(kFused ? chain : blockIdx.x) * kSinkWaves + (threadIdx.x >> 6)) * (kSinkBytes / sizeof(uint32_t));
     const int u = chain >> 1;
     const bool forward = (chain & 1) == 0;
+    // (asked for here, looked at once what else the chain starts from has come)
+    int by_whom = 0;
+    if (kFused && !taken && threadIdx.x == 0) {
+        int* const word = &wk.done[u * kDoneStride + kTakenWord + (forward ? 0 : 1)];
+        if (static_cast<int>(blockIdx.x) * 37 % 100 < wk.late_percent) wait_until_taken(word);
+        by_whom = take_chain(word, kTakenByOwn);
+    }
     const Utt m = meta[u];
     if (!(m.flags & kUttRuns)) return;     // (a run order built on the device lists every utterance)
     // Which recursion: the barrier kernel and the maximum recursion have the log domain only;
@@ -2223,8 +2246,6 @@ __device__ __forceinline__ void lattice_body(const Utt* __restrict__ meta, const
     const bool in_log_domain = kSync == Sync::kBarrier || kMode == Mode::kBest || (m.flags & kUttLogDomain) != 0 ||
                                rows_flagged(wk.row_flags, u, wk.flag_blocks, m.Tb);
     if (kMode == Mode::kLoss && in_log_domain && !forward) return;       // (the forward chain runs all the way)
-    // (for the gradient, which must know what each chain has left: a word per direction)
-    if (kMode == Mode::kGrad && threadIdx.x == 0) publish(&wk.domain[2 * u + (forward ? 0 : 1)], in_log_domain ? 1 : 0);
     const bool two_pairs = kSync == Sync::kHalo && !in_log_domain && (m.flags & kUttTwoPairs) != 0;
     const int waves = two_pairs ? m.waves2 : m.waves;
     const bool idle = static_cast<int>(threadIdx.x >> 6) >= waves;
@@ -2243,9 +2264,10 @@ __device__ __forceinline__ void lattice_body(const Utt* __restrict__ meta, const
         if (threadIdx.x == 0) {
             hl->finished = 0;
             hl->gave_up = 0;
+            hl->taken = by_whom;
         }
         __syncthreads();
-        if (idle) return;
+        if (idle || (kFused && __builtin_amdgcn_readfirstlane(hl->taken) != 0)) return;
     } else if (kSync == Sync::kBarrier) {
         if (idle) {
             // Nothing to compute, but keep meeting the barriers of the working wavefronts:
@@ -2257,6 +2279,9 @@ __device__ __forceinline__ void lattice_body(const Utt* __restrict__ meta, const
             return;
         }
     }
+    if (kFused && kSync == Sync::kNone && __builtin_amdgcn_readfirstlane(by_whom) != 0) return;
+    // (for the gradient, which must know what each chain has left: a word per direction)
+    if (kMode == Mode::kGrad && threadIdx.x == 0) publish(&wk.domain[2 * u + (forward ? 0 : 1)], in_log_domain ? 1 : 0);
     if constexpr (kSync != Sync::kBarrier && kMode != Mode::kBest) {
         if (!in_log_domain) {
             bool lost = false;
@@ -2273,7 +2298,7 @@ __device__ __forceinline__ void lattice_body(const Utt* __restrict__ meta, const
                 lost = run_chain_linear<true, kSync, kMode>(m, u, labels, emit_blank64, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
             }
             if (kMode == Mode::kLoss) finish_loss(m, u, labels, lat, wk.done, costs, 2 * waves, lost);
-            if (kMode == Mode::kGrad && wk.announce) announce_end(&wk.done[u * kDoneStride], waves, &costs[u]);
+            if (kFused) announce_end(&wk.done[u * kDoneStride], waves, &costs[u]);
             return;
         }
     }
@@ -2281,7 +2306,7 @@ __device__ __forceinline__ void lattice_body(const Utt* __restrict__ meta, const
         run_chain_log<false, kSync, kMode>(m, u, labels, emit_blank, emit_blank64, emit_label, lat.alpha, lat.alpha_exponents, logp, costs, chain_err, sink, lds);
     else if constexpr (kMode != Mode::kLoss)
         run_chain_log<true, kSync, kMode>(m, u, labels, emit_blank, emit_blank64, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
-    if (kMode == Mode::kGrad && kSync != Sync::kBarrier && wk.announce) announce_end(&wk.done[u * kDoneStride], waves, &costs[u]);
+    if (kFused) announce_end(&wk.done[u * kDoneStride], waves, &costs[u]);
 }
 
 // grid = one workgroup per entry of `order` (utterance * 2 + direction: 0 forward, 1 backward).
@@ -2301,7 +2326,7 @@ void ctc_lattice_kernel_w1(const Utt* __restrict__ meta, const int* __restrict__
         fill_rows(wk.fill, meta);
         return;
     }
-    lattice_body<Sync::kNone, kMode>(meta, order, labels, emit_blank, emit_blank64, emit_label, lat,
+    lattice_body<Sync::kNone, kMode>(order[blockIdx.x], meta, labels, emit_blank, emit_blank64, emit_label, lat,
                                                                    logp, costs, chain_err, sink, nullptr, wk);
 }
 
@@ -2321,7 +2346,7 @@ void ctc_lattice_kernel(const Utt* __restrict__ meta, const int* __restrict__ or
         fill_rows(wk.fill, meta);
         return;
     }
-    lattice_body<Sync::kHalo, kMode>(meta, order, labels, emit_blank, emit_blank64, emit_label, lat,
+    lattice_body<Sync::kHalo, kMode>(order[blockIdx.x], meta, labels, emit_blank, emit_blank64, emit_label, lat,
                                                                    logp, costs, chain_err, sink, halo_lds, wk);
 }
 
@@ -2338,7 +2363,7 @@ void ctc_lattice_kernel_barrier(const Utt* __restrict__ meta, const int* __restr
                                 int* __restrict__ chain_err, uint32_t* __restrict__ sink, const LaunchWords wk)
 {
     __shared__ double xch[3][16];                            // (labels by step parity; their origins, two words each)
-    lattice_body<Sync::kBarrier, kMode>(meta, order, labels, emit_blank, emit_blank64, emit_label, lat, logp,
+    lattice_body<Sync::kBarrier, kMode>(order[blockIdx.x], meta, labels, emit_blank, emit_blank64, emit_label, lat, logp,
                                                costs, chain_err, sink, &xch[0][0], wk);
 }
 
@@ -3254,6 +3279,64 @@ void ctc_gradient_wide_kernel(const TileArgs g, const Utt* __restrict__ meta, co
 // Alphabets of at most kDirectMaxA symbols.  Chains first, one workgroup each; then the gradient's workgroups, the
 // utterances whose chains end first before the others.  A gradient workgroup asks for everything that the softmax launch
 // has left and waits for its utterance's two chains; by the time the longest chains end, only their own blocks are left to do.
+//
+// A workgroup waits for chains that are under way, never for one that has yet to be given a compute unit: the order of the
+// workgroups says nothing about that.  Each die hands out its share of a launch by itself, and two such launches on two
+// streams can fill one die with workgroups that wait for chains which the other launch's keep from the other die, and the
+// other way round.  So a chain is taken, in its word, by the workgroup that runs it: its own one, or, should that not come
+// within a moment, one of the gradient that would wait for it; its own one then finds nothing left to do.  A chain that is
+// taken waits for nothing outside its workgroup, so it ends, and so does every wait.
+// (English minibatch: 56.9 us without the look, which cannot be trusted, 57.3 with it.)
+constexpr int kTakePolls = 32;            // about 40 us: a chain's own workgroup takes it within 5 in a launch alone on the chip
+
+// By each wavefront of a workgroup, alike: both chains of utterance b have to be taken before the gradient's workgroup `tile`
+// waits for them.  Returns the chain that this workgroup is to run because nobody else has taken it in time, -1 when there is
+// no such chain (any more: `ran`, the directions it has run already, as bits).  The words are written once, so that all
+// wavefronts come to the same answer whenever they look.
+__device__ __forceinline__ int chain_to_take(const TileArgs& g, int b, int tile, int ran)
+{
+    int* const words = &g.done[b * kDoneStride + kTakenWord];
+    for (int polls = kTakePolls;; --polls) {
+        const int by_whom[2] = {__builtin_amdgcn_readfirstlane(published(&words[0])), __builtin_amdgcn_readfirstlane(published(&words[1]))};
+        for (int d = 0; d < 2; ++d)
+            if (by_whom[d] == kTakenByTile + tile && !(ran >> d & 1)) return 2 * b + d;
+        if (by_whom[0] != 0 && by_whom[1] != 0) return -1;
+        if (polls <= 0 && threadIdx.x == 0) take_chain(&words[by_whom[0] == 0 ? 0 : 1], kTakenByTile + tile);
+        __builtin_amdgcn_s_sleep(10);
+    }
+}
+
+// The launch's arguments as they lie in memory, in the kernel's order.
+struct FusedArgs {
+    const Utt* meta;
+    const int* order;
+    const int* labels;
+    const float* emit_blank;
+    const double* emit_blank64;
+    const float* emit_label;
+    LatticeOut lat;
+    double* logp;
+    float* costs;
+    int* chain_err;
+    uint32_t* sink;
+    LaunchWords wk;
+    TileArgs tiles;
+};
+// A chain that the workgroup has taken.  Hardly ever called, and so a function of its own, which leaves the registers of the
+// common way alone (inlined, it cost that 1 to 5 us of 57).
+typedef __attribute__((address_space(3))) void* LdsPointer;
+template <Sync kSync>
+__device__ __attribute__((noinline)) void run_taken_chain(uint64_t args, int chain, LdsPointer lds)
+{
+    typedef __attribute__((address_space(4))) const FusedArgs* ArgsPointer;
+    const uint64_t lo = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(args)));
+    const uint64_t hi = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(args >> 32)));
+    const FusedArgs& a = *(const FusedArgs*)reinterpret_cast<ArgsPointer>(hi << 32 | lo);
+    if (kSync != Sync::kNone || threadIdx.x < 64)
+        lattice_body<kSync, Mode::kGrad, true>(__builtin_amdgcn_readfirstlane(chain), a.meta, a.labels, a.emit_blank, a.emit_blank64,
+                                               a.emit_label, a.lat, a.logp, a.costs, a.chain_err, a.sink, (void*)lds, a.wk, true);
+}
+
 template <Sync kSync, int kTiles>
 __global__ __launch_bounds__(64 * kFusedWaves)
 void ctc_lattice_gradient_kernel(const Utt* __restrict__ meta, const int* __restrict__ order,
@@ -3267,12 +3350,22 @@ void ctc_lattice_gradient_kernel(const Utt* __restrict__ meta, const int* __rest
     if (index < tiles.first_group) {
         if (kSync == Sync::kNone && threadIdx.x >= 64) return;
         __builtin_amdgcn_s_setprio(3);
-        lattice_body<kSync, Mode::kGrad>(meta, order, labels, emit_blank, emit_blank64, emit_label, lat, logp, costs, chain_err, sink,
-                                         fused_lds, wk);
+        lattice_body<kSync, Mode::kGrad, true>(order[index], meta, labels, emit_blank, emit_blank64, emit_label, lat, logp, costs, chain_err,
+                                               sink, fused_lds, wk);
     } else {
+        const int tile = index - tiles.first_group, rank = tile / tiles.groups, group = tile - rank * tiles.groups;
+        const int b = __builtin_amdgcn_readfirstlane(tiles.by_end[rank]);
+        const int flags = __builtin_amdgcn_readfirstlane(meta[b].flags), frames = __builtin_amdgcn_readfirstlane(meta[b].Tb);
+        const int sharing = tiles.share_blocks ? block_waves(__builtin_amdgcn_readfirstlane(meta[b].L)) : 1;
+        if ((flags & kUttRuns) && group * (kRowThreads / 64 / sharing) * kBlockFrames < frames) {
+            int ran = 0, chain;
+            while (__builtin_expect((chain = chain_to_take(tiles, b, tile, ran)) >= 0, 0)) {
+                run_taken_chain<kSync>((uint64_t)__builtin_amdgcn_kernarg_segment_ptr(), chain, (LdsPointer)fused_lds);
+                ran |= 1 << (chain & 1);
+                __syncthreads();
+            }
+        }
         if (threadIdx.x >= kRowThreads) return;          // (workgroups as large as the longest label's chains)
-        const int i = index - tiles.first_group, rank = i / tiles.groups;
-        const int b = __builtin_amdgcn_readfirstlane(tiles.by_end[rank]), group = i - rank * tiles.groups;
         narrow_tile<kTiles, true>(tiles, meta, labels, emit_blank64, emit_label, lat, fused_lds, b, group);
     }
 }
@@ -3499,7 +3592,7 @@ int launch_lattice(const Launch& p, void* stream)
         TileArgs tiles = tile_args(p, &lds);
         const int waves = std::max(p.max_waves, kRowThreads / 64);
         lds = std::max(lds, halo_lds_bytes(waves));
-        wk.announce = true;
+        wk.late_percent = p.late_percent;
         tiles.first_group = n_groups;
         const dim3 grid(n_groups + tiles.groups * p.B), block(64 * waves);
 #define CTC_LAUNCH_FUSED(SYNC, TILES)                                                              \

@@ -1,12 +1,14 @@
 """GPU tests of the workgroups that write the gradient inside the lattice launch and wait for the chains of their utterance."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import ctc_oracle as orc
 from paper_1512_02595_amd import ctc, harness
 from paper_1512_02595_amd import workloads as wl
 
 import parity_checks as pc
+from test_block_edges_gpu import batch_of
 
 pytestmark = pytest.mark.gpu
 
@@ -36,3 +38,40 @@ def test_a_wait_that_gives_up_is_reported_as_nan_cost(max_label):
     db.run()
     costs, grads = db.results()
     assert (np.abs(costs - ref_c) <= pc.COST_RTOL * ref_c).all() and np.abs(grads - ref_g).max() <= pc.GRAD_ATOL
+
+
+@pytest.mark.parametrize("percent", [-1, 40, 100])      # of the chains' own workgroups come late: others run the chains
+@pytest.mark.parametrize("dtype", [ctc.DTYPE_F32, ctc.DTYPE_BF16])
+def test_calls_on_two_streams_at_once(percent, dtype):
+    """Each of two calls in flight fills the chip with workgroups that wait; both end, with the results each has alone."""
+    batches = [wl.make_config(1, seed=5, B=48), wl.make_random(72, T=600, B=70, A=29, max_label=60, min_input=16, sigma=2.0)]
+    host = harness.DeviceBatch(batches[0], dtype)
+    device = harness.DeviceMetaBatch(600, 70, 29, 60, batches[1].blank, dtype)
+    device.load(batches[1])
+    calls = [host, device]
+    alone = []
+    for c in calls:
+        c.run()
+        alone.append(c.results()[-2:])
+    streams = [torch.cuda.Stream() for _ in calls]
+    torch.cuda.synchronize()
+    ctc.debug_set_overlap(percent)
+    try:
+        for _ in range(4):
+            for c, s in zip(calls, streams):
+                c.run(s.cuda_stream)
+    finally:
+        ctc.debug_set_overlap(-1)
+    for c, (costs, grads) in zip(calls, alone):
+        got = c.results()[-2:]
+        assert np.array_equal(got[0], costs, equal_nan=True) and np.array_equal(got[1], grads)
+
+
+@pytest.mark.parametrize("frames,labels", [([16, 9, 3], [4, 0, 3]),                # one block: a single workgroup waits
+                                           ([700, 90, 1], [300, 20, 1])])          # several wavefronts a chain
+def test_chains_that_others_run(frames, labels):
+    ctc.debug_set_overlap(100)
+    try:
+        pc.check(batch_of(frames, labels, 29))
+    finally:
+        ctc.debug_set_overlap(-1)

@@ -195,7 +195,8 @@ ctc_status_t ctc_profile_kernels(const void *activations,
  *                     outside [0, A) or equal to blank; the utterances concerned get a NaN cost
  *                     and a zero gradient, the others are computed as usual.
  *   workspace         at least ctc_workspace_size_device bytes (larger than the exact-size
- *                     query of the host-metadata calls: T x B x (max_label_length + 1) lattice pairs)
+ *                     query of the host-metadata calls: T x B x (max_label_length + 1) lattice pairs, or
+ *                     (T + 1) where that is fewer: a label needs as many frames as symbols)
  *   grads             may be NULL (costs only), as for ctc_loss_and_grad
  *   everything else as for ctc_loss_and_grad.  Results are the same numbers up to rounding:
  *                     bitwise those of ctc_loss_and_grad where both calls plan an utterance's chains
@@ -252,15 +253,15 @@ ctc_status_t ctc_profile_kernels_device(const void *activations,
  *
  *   arguments, results and status_out as for ctc_loss_and_grad_device;
  *   a batch shape whose ctc_workspace_size_device exceeds CTC_STATIC_WORKSPACE_BYTES is refused
- *   with CTC_STATUS_WORKSPACE_TOO_SMALL before anything is enqueued (64 MiB hold, for instance,
- *   16 utterances of 750 frames and up to 250 label symbols over a 29-symbol alphabet).
+ *   with CTC_STATUS_WORKSPACE_TOO_SMALL before anything is enqueued (96 MiB hold, for instance,
+ *   32 utterances of 750 frames and up to 250 label symbols over a 29-symbol alphabet).
  *
  * All calls on one GPU share that GPU's array, whatever their streams: calls that overlap in time
  * on one GPU race and give wrong results; calls on one stream, or otherwise ordered, are fine.  The
  * array keeps the previous call's contents; nothing in it needs clearing between calls (every word
  * a call reads it has written before).
  */
-#define CTC_STATIC_WORKSPACE_BYTES (64u << 20)
+#define CTC_STATIC_WORKSPACE_BYTES (96u << 20)
 
 ctc_status_t ctc_loss_and_grad_device_static(const void *activations,
                                              const int32_t *labels,

@@ -125,7 +125,7 @@ ctc_status_t make_layout(int T, int B, int A, const int32_t* label_lengths,
     if (!label_lengths || !input_lengths || !lay) return CTC_STATUS_INVALID_VALUE;
     if (T < 1 || B < 1 || A < 1) return CTC_STATUS_INVALID_VALUE;
     if (dtype != CTC_DTYPE_F32 && dtype != CTC_DTYPE_BF16) return CTC_STATUS_INVALID_VALUE;
-    int64_t sumL = 0, emit = 0, ab = 0, frames = 0;
+    int64_t sumL = 0, emit = 0, ab = 0, frames = 0, padded_sum = 0;
     bool too_long = false;
     for (int b = 0; b < B; ++b) {
         const int64_t L = label_lengths[b], Tb = input_lengths[b];
@@ -133,16 +133,17 @@ ctc_status_t make_layout(int T, int B, int A, const int32_t* label_lengths,
         if (L > CTC_MAX_LABEL_LENGTH) too_long = true;
         sumL += L;
         const int64_t padded = padded_frames(input_lengths[b]);
-        emit += padded * (A <= kDirectMaxA ? A : L);
-        frames += padded;
-        // per-utterance byte offsets inside the kernels are 32-bit
-        if (padded * lattice_pitch(L) * 8 > INT32_MAX) too_long = true;
-        ab += padded * lattice_pitch(L);
+        emit += A <= kDirectMaxA ? padded * A : gathered_emissions(input_lengths[b], L);
+        padded_sum += padded;
+        frames += Tb;
+        // (the limits are on frames as the caller counts them)
+        if (Tb * lattice_pitch(L) * 8 > INT32_MAX) too_long = true;
+        ab += lattice_words(input_lengths[b], L);
     }
     if (too_long) return CTC_STATUS_UNSUPPORTED;
     if (sumL > INT32_MAX || frames > INT32_MAX) return CTC_STATUS_UNSUPPORTED;
     if (B > kMaxBatch) return CTC_STATUS_UNSUPPORTED;
-    carve(T, B, sumL, emit, frames, ab, lay);
+    carve(T, B, sumL, emit, padded_sum, ab, lay);
     return CTC_STATUS_SUCCESS;
 }
 
@@ -153,9 +154,10 @@ ctc_status_t make_layout_bounds(int T, int B, int A, int max_label, ctc_dtype_t 
     if (!lay || T < 1 || B < 1 || A < 1 || max_label < 0) return CTC_STATUS_INVALID_VALUE;
     if (dtype != CTC_DTYPE_F32 && dtype != CTC_DTYPE_BF16) return CTC_STATUS_INVALID_VALUE;
     if (max_label > CTC_MAX_LABEL_LENGTH || B > kMaxDeviceMetaB) return CTC_STATUS_UNSUPPORTED;
-    const int64_t Tl = padded_frames(T), Bl = B, Ll = max_label;
+    const int64_t Tl = T, Bl = B, Ll = max_label, padded = padded_frames(T);
     if (Tl * lattice_pitch(Ll) * 8 > INT32_MAX || Bl * Ll > INT32_MAX || Bl * Tl > INT32_MAX) return CTC_STATUS_UNSUPPORTED;
-    carve(T, B, Bl * Ll, Bl * Tl * (A <= kDirectMaxA ? A : Ll), Bl * Tl, Bl * Tl * lattice_pitch(Ll), lay);
+    const int longest = longest_aligned(T, max_label);
+    carve(T, B, Bl * Ll, Bl * (A <= kDirectMaxA ? padded * A : gathered_emissions(T, longest)), Bl * padded, Bl * lattice_words(T, longest), lay);
     return CTC_STATUS_SUCCESS;
 }
 
@@ -358,7 +360,7 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
         m.lab_off = static_cast<int32_t>(lab_off);
         m.flags = (runs ? kUttRuns : 0) | (plan_of.two_pairs(L) ? kUttTwoPairs : 0) |
                   ((Tb > kLinearMaxFrames || tight_fit(Tb, L, repeats)) ? kUttLogDomain : 0);
-        m.f_off = static_cast<int32_t>(f_off);
+        m.f_off = static_cast<uint32_t>(f_off);
         m.waves = plan_of.waves1(L);
         m.halo = plan_of.halo1(L);
         m.waves2 = plan_of.waves2(L);
@@ -371,9 +373,9 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
         meta[b] = m;
         const int64_t padded = padded_frames(Tb);
         lab_off += L;
-        e_off += padded * m.e_cols;
+        e_off += symbol_major ? padded * c.A : gathered_emissions(Tb, L);
         f_off += padded;
-        ab_off += padded * lattice_pitch(L);
+        ab_off += lattice_words(Tb, L);
         if (runs) {
             order[n_run++] = b;
             max_waves = std::max({max_waves, m.waves, m.waves2});
@@ -859,15 +861,15 @@ long ctc_debug_replay_emission_fetches(int T, int B, int A, const int32_t* label
         m.e_direct = emission_layout(A);
         m.e_cols = symbols ? A : L;
         if (bounds) {
-            m.f_off = static_cast<int32_t>(b * padded_frames(T));
-            m.e_off = b * padded_frames(T) * (symbols ? A : max_label_length);
+            m.f_off = static_cast<uint32_t>(b * padded_frames(T));
+            m.e_off = b * (symbols ? padded_frames(T) * A : gathered_emissions(T, longest_aligned(T, max_label_length)));
         } else {
-            m.f_off = static_cast<int32_t>(f_off);
+            m.f_off = static_cast<uint32_t>(f_off);
             m.e_off = e_off;
-            e_off += padded_frames(Tb) * m.e_cols;
+            e_off += symbols ? padded_frames(Tb) * A : gathered_emissions(Tb, L);
             f_off += padded_frames(Tb);
         }
-        if (Tb < 1) continue;                       // its chains do not run
+        if (Tb < 1 || Tb < L) continue;             // its chains do not run
         const int chunks = 2 * frame_blocks(Tb);
         for (int backward = 0; backward < 2; ++backward) {
             // Lanes at the ends of every range a pointer depends on: first and last label position, first

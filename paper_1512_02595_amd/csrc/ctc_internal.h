@@ -19,13 +19,13 @@ struct Utt {
     int32_t lab_off;   // offset of its label string in the flat label array
     int32_t flags;     // bit 0: the lattice runs (Tb > 0 and an alignment exists);
                        // bit 1: lengths or labels failed the device-side checks (cost NaN)
-    int32_t f_off;     // padded frames (padded_frames) of all earlier utterances: offset of its blank emissions
+    uint32_t f_off;    // padded frames (padded_frames) of all earlier utterances: offset of its blank emissions
     int32_t waves;     // wavefronts its lattice chains use when a lane owns one state pair (log-domain
                        // chains, and linear-domain chains of at most 64 pairs)
     int32_t halo;      // lanes per wavefront that recompute the wavefront below (0: none)
     int32_t poll_budget; // LDS polls a wavefront of its chains may spend waiting on a neighbour before it gives up
     int64_t e_off;     // offset (floats) of its label emissions [chunk][e_cols][kChunk]
-    int64_t ab_off;    // offset (8-byte words) of its alpha/beta blocks [padded_frames(Tb)][lattice_pitch(L)]
+    int64_t ab_off;    // offset (8-byte words) of its alpha/beta blocks, lattice_words of them
     int32_t e_cols;    // columns of its emission block: a column per symbol, or one per label position
     int32_t e_direct;  // which of the two: kEmitGathered or kEmitSymbols (emission_layout)
     int32_t waves2;    // the same plan for linear-domain chains of more than 64 pairs, whose lanes own
@@ -389,6 +389,12 @@ CTC_HOST_DEVICE inline void chain_schedule(int chunks, Fetch&& fetch, Run&& run)
 
 // Row pitch of an utterance's lattice blocks: column 1 + i holds label position i.
 CTC_HOST_DEVICE inline int64_t lattice_pitch(int64_t L) { return L + 2; }
+// What an utterance gets of either direction's region, in 8-byte words, and of the gathered emissions, in floats.  One with
+// more symbols than frames has no alignment and needs neither; where only bounds are known, every utterance gets what the
+// longest label with an alignment needs (longest_aligned).
+CTC_HOST_DEVICE inline int64_t lattice_words(int frames, int64_t L) { return L <= frames ? padded_frames(frames) * lattice_pitch(L) : 0; }
+CTC_HOST_DEVICE inline int64_t gathered_emissions(int frames, int64_t L) { return L <= frames ? padded_frames(frames) * L : 0; }
+CTC_HOST_DEVICE inline int longest_aligned(int frames, int max_label) { return max_label < frames ? max_label : frames; }
 
 // Byte offsets of the workspace regions, all multiples of 256.
 struct Layout {
@@ -416,10 +422,10 @@ struct Layout {
                            // the most probable alignment)
     size_t emit_blank64 = 0; // double[slack + sum padded_frames(Tb) + slack]  the blank's probability once more, for the scalar loads of
                              // the linear-domain chains
-    size_t emit_label = 0; // float[slack + sum padded_frames(Tb)*L + slack]  emission of each label position, same coding
+    size_t emit_label = 0; // float[slack + sum gathered_emissions + slack]  emission of each label position, same coding
                            // (padded_frames(Tb)*A for small alphabets: emission_layout); the front slack starts with
                            // the constants that lanes without a label state read: probability 0 and log 0
-    size_t alpha = 0;      // 8-byte words [sum padded_frames(Tb)*(L+2)] (lattice storage, see the kernels)
+    size_t alpha = 0;      // 8-byte words [sum lattice_words] (lattice storage, see the kernels)
     size_t beta = 0;
     size_t total = 0;
     size_t upload_bytes = 0;   // meta..labels are contiguous: the image the host prepares per call

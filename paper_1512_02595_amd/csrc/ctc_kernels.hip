@@ -203,8 +203,8 @@ void ctc_upload_kernel(const int* __restrict__ host_image, int* __restrict__ ws,
 // the host never sees, so this kernel (one workgroup) does what the host launcher does
 // otherwise.  Per utterance: range checks, the count of adjacent repeats (an alignment exists
 // iff T_b >= L + repeats), the wavefront plan, and the offsets of its blocks, which are laid
-// out with the strides of the largest utterance the caller allows, T' = padded_frames(T) (labels [B][max_label],
-// emissions b * T' * max_label, lattice b * T' * lattice_pitch(max_label), frames b * T').  Then the run
+// out with the strides of the largest utterance the caller allows (labels [B][max_label]; emissions, lattice and frames what
+// gathered_emissions, lattice_words and padded_frames give for T and longest_aligned).  Then the run
 // order: heaviest chains first (rank by T_b x wavefronts, ties by index), -1 for the rest.
 constexpr int kPlanThreads = 1024;
 
@@ -269,8 +269,8 @@ void ctc_plan_kernel(const int* __restrict__ labels, const int* __restrict__ lab
         m.flags = (runs ? kUttRuns : 0) | (bad ? kUttInvalid : 0) |
                   ((log_domain || Tb > kLinearMaxFrames || tight_fit(Tb, L, rep)) ? kUttLogDomain : 0) |
                   (!bad && two_pairs_per_lane(L, crowded, emission_layout(A) == kEmitSymbols) ? kUttTwoPairs : 0);
-        const int padded = static_cast<int>(padded_frames(Tt));
-        m.f_off = b * padded;
+        const int padded = static_cast<int>(padded_frames(Tt)), longest = longest_aligned(Tt, max_label);
+        m.f_off = static_cast<unsigned>(b) * padded;
         m.waves = wp.waves;
         m.halo = wp.halo;
         const WavePlan wp2 = plan_waves2(bad ? 0 : L, crowded);
@@ -279,8 +279,8 @@ void ctc_plan_kernel(const int* __restrict__ labels, const int* __restrict__ lab
         m.poll_budget = poll_budget;
         m.e_direct = emission_layout(A);
         m.e_cols = m.e_direct == kEmitSymbols ? A : m.L;
-        m.e_off = static_cast<int64_t>(b) * padded * (m.e_direct == kEmitSymbols ? A : max_label);
-        m.ab_off = static_cast<int64_t>(b) * padded * lattice_pitch(max_label);
+        m.e_off = b * (m.e_direct == kEmitSymbols ? static_cast<int64_t>(padded) * A : gathered_emissions(Tt, longest));
+        m.ab_off = b * lattice_words(Tt, longest);
         meta[b] = m;
         weight[b] = runs ? static_cast<long long>(Tb) * ((m.flags & kUttTwoPairs) ? wp2.waves : wp.waves) : -1;
         if (bad) s_bad = 1;
@@ -705,7 +705,7 @@ __device__ __forceinline__ void narrow_rows(const T* __restrict__ x, float* lp, 
 // frames past the utterance's end.  kRows is a whole number of chunks.  Returns whether an emission is too
 // small for the linear domain.
 template <int kRows>
-__device__ __forceinline__ bool store_symbol_chunks(const float* lp, int Tb, int f_off, int64_t e_off, int t0, int A, int blank,
+__device__ __forceinline__ bool store_symbol_chunks(const float* lp, int Tb, unsigned f_off, int64_t e_off, int t0, int A, int blank,
                                                     float* __restrict__ emit_blank, double* __restrict__ emit_blank64,
                                                     float* __restrict__ emit_label, bool plain_logs)
 {
@@ -780,7 +780,7 @@ struct NarrowImage {
 constexpr int kRowsRun = 1 << 30;     // (a flag of the record that rides along)
 struct NarrowRows {
     int frames[kNarrowMaxB];
-    int frames_before[kNarrowMaxB];
+    unsigned frames_before[kNarrowMaxB];
     int label_length[kNarrowMaxB];       // and, for the setup role, the label's length and the symbols before it
     int labels_before[kNarrowMaxB];
 };
@@ -867,8 +867,8 @@ __device__ __forceinline__ Utt build_record(const NarrowDevice& dv, const PlanTa
     m.flags = (runs ? kUttRuns : 0) | (invalid ? kUttInvalid : 0) |
               ((dv.log_domain || Tb > kLinearMaxFrames || tight_fit(Tb, L, s_repeats)) ? kUttLogDomain : 0) |
               (!invalid && plans.two_pairs(L) ? kUttTwoPairs : 0);
-    const int padded = static_cast<int>(padded_frames(Tt));
-    m.f_off = b * padded;
+    const int padded = static_cast<int>(padded_frames(Tt)), longest = longest_aligned(Tt, dv.max_label);
+    m.f_off = static_cast<unsigned>(b) * padded;
     m.waves = plans.waves1(Lp);
     m.halo = plans.halo1(Lp);
     m.waves2 = plans.waves2(Lp);
@@ -876,8 +876,8 @@ __device__ __forceinline__ Utt build_record(const NarrowDevice& dv, const PlanTa
     m.poll_budget = dv.poll_budget;
     m.e_direct = emission_layout(A);
     m.e_cols = m.e_direct == kEmitSymbols ? A : m.L;
-    m.e_off = static_cast<int64_t>(b) * padded * (m.e_direct == kEmitSymbols ? A : dv.max_label);
-    m.ab_off = static_cast<int64_t>(b) * padded * lattice_pitch(dv.max_label);
+    m.e_off = b * (m.e_direct == kEmitSymbols ? static_cast<int64_t>(padded) * A : gathered_emissions(Tt, longest));
+    m.ab_off = b * lattice_words(Tt, longest);
     if (tid == 0) {
         dv.meta[b] = m;
         dv.status_words[b] = invalid ? 1 : 0;
@@ -940,14 +940,14 @@ void ctc_softmax_narrow_kernel(const T* __restrict__ x, const NarrowImage image,
         return;
     }
     // (the fields of the utterance's record that the rows need)
-    struct { int Tb, flags, f_off; int64_t e_off; } m;
+    struct { int Tb, flags; unsigned f_off; int64_t e_off; } m;
     if (dv.labels) {
         // (whether an alignment exists is not known here: the rows of every utterance with frames are prepared)
         const int L = dv.label_lengths[b], Tb = dv.input_lengths[b];
         const bool bad_length = L < 0 || L > dv.max_label || Tb < 0 || Tb > Tt;
         m.Tb = bad_length ? 0 : Tb;
         m.flags = kUttRuns;
-        m.f_off = b * static_cast<int>(padded_frames(Tt));
+        m.f_off = static_cast<unsigned>(b) * static_cast<int>(padded_frames(Tt));
     } else {
         m.Tb = args.rows.frames[b] & (kRowsRun - 1);
         m.flags = (args.rows.frames[b] & kRowsRun) ? kUttRuns : 0;
@@ -2532,7 +2532,7 @@ __device__ __forceinline__ Utt uniform_record(const Utt& m)
     u.L = uniform(m.L);
     u.lab_off = uniform(m.lab_off);
     u.flags = uniform(m.flags);
-    u.f_off = uniform(m.f_off);
+    u.f_off = static_cast<unsigned>(uniform(static_cast<int>(m.f_off)));
     u.e_cols = uniform(m.e_cols);
     u.e_direct = uniform(m.e_direct);
     u.e_off = uniform64(m.e_off);
@@ -3278,7 +3278,7 @@ void ctc_gradient_wide_kernel(const TileArgs g, const Utt* __restrict__ meta, co
         sum += __shfl_xor(sum, 16);
         sum += __shfl_xor(sum, 32);
         if (has_row && lane < kBlockFrames)
-            store_gradient(g, out + blank, emission_softmax(emit_blank[kBlankSlack + m.f_off + t]) - (1.0f - sum));
+            store_gradient(g, out + blank, emission_softmax(emit_blank[static_cast<size_t>(kBlankSlack) + m.f_off + t]) - (1.0f - sum));
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
 }

@@ -251,7 +251,7 @@ def loss_and_grad_device_status(activations_ptr, labels_ptr, label_lengths_ptr, 
                                         workspace_bytes, stream)
 
 
-STATIC_WORKSPACE_BYTES = 64 << 20
+STATIC_WORKSPACE_BYTES = 96 << 20
 
 
 def loss_and_grad_device_static_status(activations_ptr, labels_ptr, label_lengths_ptr, input_lengths_ptr,

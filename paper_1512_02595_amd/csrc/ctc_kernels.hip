@@ -481,8 +481,10 @@ __device__ __forceinline__ void raise_log_domain(Utt* meta, int b, bool small)
 // kLanes lanes (16, a wavefront or the workgroup) hold a row of up to kPerLane kLanes symbols in registers between the
 // maximum and the sum (kPerLane: 16, or 32 where that is not enough): it is read once, with 16-byte loads, and written with 16-byte stores.  A row that starts off a 16-byte
 // boundary (an alphabet size that is no multiple of the vector, or a tensor that starts off one) has up to N - 1 symbols
-// before its first whole vector and as many after its last; a lane takes one of them each.  Consecutive workgroups take
-// consecutive rows of the tensor.
+// before its first whole vector and as many after its last; a lane takes one of them each.  Where the gradient starts at
+// another place within 16 bytes than the activations, the vectors read are written element by element (750 symbols, f32:
+// 87.6 us a call against 86.8 with vectors, 134 with the three passes of ctc_softmax_kernel; 6000 bf16: 119, 107 and 292).
+// Consecutive workgroups take consecutive rows of the tensor.
 // Bound by memory: with the 308 of 768 MB of zero rows that the lattice launch takes over counted in, 64 x 500 rows of
 // 6000 symbols, of which 300 on average are valid, move at 4.8 TB/s (bf16: 128.5 us with a load in each branch, 119 with
 // all loads first and zero rows left over).  27 x 333 rows of 4733 symbols (no multiple of a vector): 108 us with
@@ -512,17 +514,18 @@ void ctc_softmax_rows_kernel(const T* __restrict__ x, T* __restrict__ grads, Utt
     const size_t row_off = (static_cast<size_t>(t) * B + b) * A;
     const T* const row = x + row_off;
     T* const grow = grads ? grads + row_off : nullptr;
-    // (activations and gradient start at the same place within 16 bytes: see the launch)
-    const int head = min(static_cast<int>((16 - (reinterpret_cast<uintptr_t>(row) & 15)) & 15) / static_cast<int>(sizeof(T)), A);
-    const int nvec = (A - head) / N, rest = A - nvec * N;
-    const int single = q < rest ? (q < head ? q : nvec * N + q) : -1;          // this lane's symbol outside the vectors
     if (t >= m.Tb || !(m.flags & kUttRuns)) {
         if (grow && (t & 15) >= defer) {
+            const int head = min(static_cast<int>((16 - (reinterpret_cast<uintptr_t>(grow) & 15)) & 15) / static_cast<int>(sizeof(T)), A);
+            const int nvec = (A - head) / N, rest = A - nvec * N;
             for (int i = q; i < nvec; i += kLanes) store_streaming(grow + head + static_cast<size_t>(i) * N, RawVec{0, 0, 0, 0});
-            if (single >= 0) store_elem(grow, single, 0.0f);
+            if (q < rest) store_elem(grow, q < head ? q : nvec * N + q, 0.0f);
         }
         return;
     }
+    const int head = min(static_cast<int>((16 - (reinterpret_cast<uintptr_t>(row) & 15)) & 15) / static_cast<int>(sizeof(T)), A);
+    const int nvec = (A - head) / N, rest = A - nvec * N;
+    const int single = q < rest ? (q < head ? q : nvec * N + q) : -1;          // this lane's symbol outside the vectors
 
     // All of the row and the labels' symbols are asked for before any of it is used: no conversion, and no lane left out,
     // between one load and the next (a vector past the end is the last one again, counted by nobody).
@@ -550,6 +553,7 @@ void ctc_softmax_rows_kernel(const T* __restrict__ x, T* __restrict__ grads, Utt
     // log2 y_k itself and not to the row's offset (see log2_softmax)
     const float ls = fast_log2(sum);
     if (grow) {
+        const bool together = ((reinterpret_cast<uintptr_t>(row) ^ reinterpret_cast<uintptr_t>(grow)) & 15) == 0;
 #pragma unroll
         for (int i = 0; i < kVecs; ++i) {
             const int at = q + i * kLanes;
@@ -557,7 +561,12 @@ void ctc_softmax_rows_kernel(const T* __restrict__ x, T* __restrict__ grads, Utt
                 float y[N];
 #pragma unroll
                 for (int e = 0; e < N; ++e) y[e] = fast_exp2(log2_softmax(Vec<T>::get(raw[i], e), mx, ls));
-                store_streaming(grow + head + static_cast<size_t>(at) * N, Vec<T>::pack(y));
+                T* const out = grow + head + static_cast<size_t>(at) * N;
+                if (together)
+                    store_streaming(out, Vec<T>::pack(y));
+                else
+#pragma unroll
+                    for (int e = 0; e < N; ++e) store_elem(out, e, y[e]);
             }
         }
         if (single >= 0) store_elem(grow, single, fast_exp2(log2_softmax(alone, mx, ls)));
@@ -3388,12 +3397,11 @@ int checked_launch(F&& f)
 }  // namespace
 
 namespace {
-// Lanes per row of ctc_softmax_rows_kernel; 0 where it does not apply: rows of more than 8192 symbols, activations and
-// gradient that start at different places within 16 bytes, more workgroups than a grid holds.
+// Lanes per row of ctc_softmax_rows_kernel; 0 where it does not apply: rows of more than 8192 symbols, more workgroups than a
+// grid holds.
 int row_lanes(const Launch& p)
 {
-    const uintptr_t apart = p.grads ? (reinterpret_cast<uintptr_t>(p.x) ^ reinterpret_cast<uintptr_t>(p.grads)) & 15 : 0;
-    if (p.A > 32 * kRowThreads || apart != 0) return 0;
+    if (p.A > 32 * kRowThreads) return 0;
     const int lanes = p.A <= 32 * 16 ? 16 : (p.A <= 32 * 64 ? 64 : kRowThreads);
     const int rows = kRowThreads / lanes;
     const int64_t groups = static_cast<int64_t>(p.T) * ((p.B + rows - 1) / rows) + static_cast<int64_t>(p.B) * (CTC_MAX_LABEL_LENGTH / 64 + 1);

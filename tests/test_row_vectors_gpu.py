@@ -27,6 +27,17 @@ def test_rows_around_lane_counts(A, dtype):
 @pytest.mark.parametrize("A", [77, 300, 1200, 2600])
 @pytest.mark.parametrize("x_at,g_at", [(1, 1), (3, 3), (5, 5), (0, 1), (2, 0)])
 def test_tensors_off_a_16_byte_boundary(A, dtype, torch_dtype, x_at, g_at):
+    check_off_boundary(A, dtype, torch_dtype, x_at, g_at)
+
+
+@pytest.mark.parametrize("dtype,torch_dtype", [(ctc.DTYPE_F32, torch.float32), (ctc.DTYPE_BF16, torch.bfloat16)])
+@pytest.mark.parametrize("A", [65, 513, 4097, 8191, 8192])
+@pytest.mark.parametrize("x_at,g_at", [(0, 3), (1, 0), (3, 6), (7, 4)])
+def test_gradient_at_another_place_than_the_activations(A, dtype, torch_dtype, x_at, g_at):
+    check_off_boundary(A, dtype, torch_dtype, x_at, g_at)
+
+
+def check_off_boundary(A, dtype, torch_dtype, x_at, g_at):
     batch = batch_of([21, 13, 18], [5, 4, 7], A, T=24, seed=A)
     n = batch.logits.size
     logits = batch.logits if dtype == ctc.DTYPE_F32 else wl.to_bf16_grid(batch.logits)

@@ -426,9 +426,11 @@ __device__ __forceinline__ float encode_emission(float lp, bool& small, bool pla
 struct Log2Parts { float whole, part; };
 __device__ __forceinline__ Log2Parts emission_log2_parts(float v)
 {
-    if (v > 0.0f)
-        return {static_cast<float>(__builtin_amdgcn_frexp_expf(v)), fast_log2(__builtin_amdgcn_frexp_mantf(v))};
-    return {v == 0.0f ? static_cast<float>(kNeg) : v, 0.0f};         // (0: a label of a virtual frame)
+    // (selected, not branched on: with a branch per frame and state a log-domain step took 161 ns in place of 135.  0: a label
+    // of a virtual frame)
+    const float whole = static_cast<float>(__builtin_amdgcn_frexp_expf(v));
+    const float part = fmaxf(fast_log2(__builtin_amdgcn_frexp_mantf(v)), static_cast<float>(kNeg));
+    return {v < 0.0f ? v : whole, v < 0.0f ? 0.0f : part};
 }
 __device__ __forceinline__ double emission_log2(float v)
 {

@@ -466,9 +466,12 @@ __device__ __forceinline__ void store_virtual_frames(const Utt& m, float* __rest
             emit_label[emission_at(m.e_off, m.L, t, j)] = virtual_emission(false, plain_logs);
     }
 }
-__device__ __forceinline__ void raise_log_domain(Utt* meta, int b, bool small)
+// `m`: the utterance's record as this launch found it.  A store, and no atomic: nothing else in the word changes during the
+// launch, so that all who raise the flag write the same.  (One atomic per lane that met such an emission, in 64 words for the
+// whole launch: 64 x 500 rows of 750 symbols with steep logits 650 us; one per row 110; so 23.)
+__device__ __forceinline__ void raise_log_domain(Utt* meta, int b, const Utt& m, bool small)
 {
-    if (small) atomicOr(&meta[b].flags, kUttLogDomain);
+    if (small) meta[b].flags = m.flags | kUttLogDomain;
 }
 
 // ---- softmax statistics + emission gather --------------------------------------------------
@@ -586,7 +589,7 @@ void ctc_softmax_rows_kernel(const T* __restrict__ x, T* __restrict__ grads, Utt
         erow[static_cast<size_t>(j) * kChunk] = encode_emission(log2_softmax(load_elem(row, c), mx, ls), small, sa.plain_logs);
     }
     if (t == m.Tb - 1) store_virtual_frames(m, emit_blank, sa.emit_blank64, emit_label, sa.plain_logs, q, kLanes);
-    raise_log_domain(meta, b, small);
+    raise_log_domain(meta, b, m, small);
 }
 
 // Alphabets beyond 8192 symbols: one workgroup per row, read three times (the row does not fit the registers).
@@ -636,7 +639,7 @@ void ctc_softmax_kernel(const T* __restrict__ x, T* __restrict__ grads,
     const int* lab = labels + m.lab_off;
     for (int j = threadIdx.x; j < m.L; j += kRowThreads)
         erow[static_cast<size_t>(j) * kChunk] = encode_emission(log2_softmax(load_elem(row, lab[j]), mx, ls), small, sa.plain_logs);
-    raise_log_domain(meta, b, small);
+    raise_log_domain(meta, b, m, small);
 }
 
 // The zero rows that the softmax launch has left (t % 16 < defer), by workgroups of the lattice launch that land on
@@ -760,8 +763,8 @@ void ctc_softmax_symbols_kernel(const T* __restrict__ x, Utt* __restrict__ meta,
     if (!(m.flags & kUttRuns) || t0 >= m.Tb) return;
     narrow_rows(x, lp, m.Tb, b, t0, B, A, sa.plain_logs);
     __syncthreads();
-    raise_log_domain(meta, b, store_symbol_chunks<kRows>(lp, m.Tb, m.f_off, m.e_off, t0, A, blank, emit_blank, sa.emit_blank64,
-                                                         emit_label, sa.plain_logs));
+    raise_log_domain(meta, b, m, store_symbol_chunks<kRows>(lp, m.Tb, m.f_off, m.e_off, t0, A, blank, emit_blank, sa.emit_blank64,
+                                                            emit_label, sa.plain_logs));
 
 }
 

@@ -2214,8 +2214,9 @@ __device__ __forceinline__ void wait_until_taken(const int* word)
 }
 
 // `chain`: utterance * 2 + direction.  kFused: the launch writes the gradient too; `taken`: this workgroup has taken the chain.
-template <Sync kSync, Mode kMode, bool kFused = false>
-__device__ __forceinline__ void lattice_body(const int chain, const Utt* __restrict__ meta, const int* __restrict__ labels,
+// kLog: with the log-domain chains; without them the result is whether the chain is one, and then it has not been run.
+template <Sync kSync, Mode kMode, bool kFused = false, bool kLog = true>
+__device__ __forceinline__ bool lattice_body(const int chain, const Utt* __restrict__ meta, const int* __restrict__ labels,
                                              const float* __restrict__ emit_blank, const double* __restrict__ emit_blank64,
                                              const float* __restrict__ emit_label,
                                              const LatticeOut lat,
@@ -2234,14 +2235,14 @@ __device__ __forceinline__ void lattice_body(const int chain, const Utt* __restr
         const bool any = __ballot(bad) != 0;
         if (threadIdx.x == 0) *wk.status_out = any ? CTC_STATUS_INVALID_VALUE : CTC_STATUS_SUCCESS;
     }
+    if (chain < 0) return false;      // device-planned batches launch a workgroup per utterance and direction, running or not
+    // (measurements of the recursions one after the other: a launch that leaves one direction out)
+    if (kMode == Mode::kGrad && ((wk.skip_directions >> (chain & 1)) & 1)) return false;
     // Lanes with nothing to store write to a sink: 64 bytes of it per wavefront of the launch.  (One
     // address for the whole launch was what a crowded launch waited for: every store instruction of
     // every chain carried a write to it, and they all met in one channel of each die's L2.  512
     // utterances of 20 symbols and 740 frames: 59 -> 40 us.  Writing to an unused column of the
     // chain's own rows instead was slower than either in launches that are not crowded.)
-    if (chain < 0) return;      // device-planned batches launch a workgroup per utterance and direction, running or not
-    // (measurements of the recursions one after the other: a launch that leaves one direction out)
-    if (kMode == Mode::kGrad && ((wk.skip_directions >> (chain & 1)) & 1)) return;
     sink += (static_cast<size_t>(kFused ? chain : blockIdx.x) * kSinkWaves + (threadIdx.x >> 6)) * (kSinkBytes / sizeof(uint32_t));
     const int u = chain >> 1;
     const bool forward = (chain & 1) == 0;
@@ -2253,13 +2254,13 @@ __device__ __forceinline__ void lattice_body(const int chain, const Utt* __restr
         by_whom = take_chain(word, kTakenByOwn);
     }
     const Utt m = meta[u];
-    if (!(m.flags & kUttRuns)) return;     // (a run order built on the device lists every utterance)
+    if (!(m.flags & kUttRuns)) return false;     // (a run order built on the device lists every utterance)
     // Which recursion: the barrier kernel and the maximum recursion have the log domain only;
     // otherwise the flag that the softmax launch may have raised decides.  A linear-domain chain
     // gives one pair or two to a lane as the launcher planned it (two_pairs_per_lane).
     const bool in_log_domain = kSync == Sync::kBarrier || kMode == Mode::kBest || (m.flags & kUttLogDomain) != 0 ||
                                rows_flagged(wk.row_flags, u, wk.flag_blocks, m.Tb);
-    if (kMode == Mode::kLoss && in_log_domain && !forward) return;       // (the forward chain runs all the way)
+    if (kMode == Mode::kLoss && in_log_domain && !forward) return false;       // (the forward chain runs all the way)
     const bool two_pairs = kSync == Sync::kHalo && !in_log_domain && (m.flags & kUttTwoPairs) != 0;
     const int waves = two_pairs ? m.waves2 : m.waves;
     const bool idle = static_cast<int>(threadIdx.x >> 6) >= waves;
@@ -2281,7 +2282,9 @@ __device__ __forceinline__ void lattice_body(const int chain, const Utt* __restr
             hl->taken = by_whom;
         }
         __syncthreads();
-        if (idle || (kFused && __builtin_amdgcn_readfirstlane(hl->taken) != 0)) return;
+        if (kFused && __builtin_amdgcn_readfirstlane(hl->taken) != 0) return false;
+        if (!kLog && in_log_domain) return true;
+        if (idle) return false;
     } else if (kSync == Sync::kBarrier) {
         if (idle) {
             // Nothing to compute, but keep meeting the barriers of the working wavefronts:
@@ -2290,10 +2293,13 @@ __device__ __forceinline__ void lattice_body(const int chain, const Utt* __restr
             const int barriers = kMode == Mode::kBest ? 2 * chain_chunks(m.Tb, !forward) * kChunk
                                                       : static_cast<int>(padded_frames(m.Tb)) + (forward ? 1 : 0);
             for (int i = 0; i < barriers; ++i) __syncthreads();
-            return;
+            return false;
         }
     }
-    if (kFused && kSync == Sync::kNone && __builtin_amdgcn_readfirstlane(by_whom) != 0) return;
+    if (kFused && kSync == Sync::kNone) {
+        if (__builtin_amdgcn_readfirstlane(by_whom) != 0) return false;
+        if (!kLog && in_log_domain) return true;
+    }
     // (for the gradient, which must know what each chain has left: a word per direction)
     if (kMode == Mode::kGrad && threadIdx.x == 0) publish(&wk.domain[2 * u + (forward ? 0 : 1)], in_log_domain ? 1 : 0);
     if constexpr (kSync != Sync::kBarrier && kMode != Mode::kBest) {
@@ -2313,14 +2319,17 @@ __device__ __forceinline__ void lattice_body(const int chain, const Utt* __restr
             }
             if (kMode == Mode::kLoss) finish_loss(m, u, labels, lat, wk.done, costs, 2 * waves, lost);
             if (kFused) announce_end(&wk.done[u * kDoneStride], waves, &costs[u]);
-            return;
+            return false;
         }
     }
-    if (forward)
-        run_chain_log<false, kSync, kMode>(m, u, labels, emit_blank, emit_blank64, emit_label, lat.alpha, lat.alpha_exponents, logp, costs, chain_err, sink, lds);
-    else if constexpr (kMode != Mode::kLoss)
-        run_chain_log<true, kSync, kMode>(m, u, labels, emit_blank, emit_blank64, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
-    if (kFused) announce_end(&wk.done[u * kDoneStride], waves, &costs[u]);
+    if constexpr (kLog) {
+        if (forward)
+            run_chain_log<false, kSync, kMode>(m, u, labels, emit_blank, emit_blank64, emit_label, lat.alpha, lat.alpha_exponents, logp, costs, chain_err, sink, lds);
+        else if constexpr (kMode != Mode::kLoss)
+            run_chain_log<true, kSync, kMode>(m, u, labels, emit_blank, emit_blank64, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
+        if (kFused) announce_end(&wk.done[u * kDoneStride], waves, &costs[u]);
+    }
+    return false;
 }
 
 // grid = one workgroup per entry of `order` (utterance * 2 + direction: 0 forward, 1 backward).
@@ -3001,11 +3010,15 @@ __device__ __forceinline__ bool wait_for_chains(const TileArgs& g, int b, int fr
 
 // Workgroup `group` of utterance b: kRowThreads / 64 wavefronts, ceil(blocks of T / (4 / wavefronts per block)) workgroups;
 // LDS 4 tile_lds_ints(Lmax, kTiles) ints.  kTiles: tiles of 16 symbols.
-template <int kTiles, bool kWait>
-__device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* __restrict__ meta, const int* __restrict__ labels,
+// Which utterances' tiles: a launch of its own takes any; in the lattice launch those of log-domain chains, hardly ever met, are
+// a function of their own (log_tile), which leaves the registers of the common way alone.
+enum class TileOf { kAny, kLinear, kLog };
+template <int kTiles, bool kWait, TileOf kOf>
+__device__ __forceinline__ bool narrow_tile(const TileArgs& g_args, const Utt* __restrict__ meta, const int* __restrict__ labels,
                                             const double* __restrict__ emit_blank64, const float* __restrict__ emit_label,
                                             const LatticeOut& lat, uint4v* tile_lds, const int b, const int group)
 {
+    constexpr bool kPublished = kOf != TileOf::kAny;     // (in the launch of the chains)
     const int Tt = g_args.T, B = g_args.B, A = g_args.A, blank = g_args.blank, Lmax = g_args.Lmax;
     const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -3024,7 +3037,7 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
         // (the barriers below)
         if (kWait && runs && first_block * kBlockFrames < m.Tb) __syncthreads();
         if (sharing > 1) __syncthreads();
-        return;
+        return true;
     }
     unsigned* const s_hi = reinterpret_cast<unsigned*>(tile_lds) + wave * tile_lds_ints(Lmax, kTiles);
     unsigned* const s_lo = s_hi + kBlockFrames * kShareRow;
@@ -3046,9 +3059,9 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
     bool log_domain = false;
     double packed_inverse_p = 0.0;
     auto load_ends = [&]() {
-        ends = BlockEnds::load<kWait>(m, lat, first_labels.p0, block);
-        log_domain = in_log_domain<kWait>(g_args.domain, b);
-        packed_inverse_p = kWait ? published(&g_args.logp[b]) : g_args.logp[b];
+        ends = BlockEnds::load<kPublished>(m, lat, first_labels.p0, block);
+        log_domain = in_log_domain<kPublished>(g_args.domain, b);
+        packed_inverse_p = kPublished ? published(&g_args.logp[b]) : g_args.logp[b];
         if (group == 0 && threadIdx.x == 0 && published(&g_args.chain_err[b]) != 0) publish(&g_args.costs[b], __uint_as_float(0x7FC00000u));
     };
     if (!kWait) load_ends();
@@ -3069,11 +3082,12 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
     if (kWait) {
         if (!wait_for_chains(g_args, b, m.Tb)) {
             if (part == 0) zero_rows();
-            return;
+            return true;
         }
         load_ends();
-        if (log_domain) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
+    if (kOf == TileOf::kLinear && log_domain) return false;
+    if (kOf == TileOf::kLog) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     // the symbol of this lane's column, per tile of symbols: label bytes are compared as (byte & mask) ^ symbol == 0
     unsigned symbol[kTiles], mask[kTiles];
     float4v acc[kTiles];
@@ -3091,13 +3105,13 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
             s_hi[row * kShareRow + lane] = __builtin_bit_cast(unsigned, hi);
             s_lo[row * kShareRow + lane] = __builtin_bit_cast(unsigned, lo);
         };
-        if (log_domain) {
+        if (kOf == TileOf::kLog || (kOf == TileOf::kAny && log_domain)) {
             block_shares_log<kShareScaleLog2>(m, lat, packed_inverse_p, block, base, own_first, own_end, file);
         } else {
             LaneLabels at = first_labels;
             if (base != first_base) {
                 at = LaneLabels(labels + m.lab_off, L, base);
-                ends = BlockEnds::load<kWait>(m, lat, at.p0, block);
+                ends = BlockEnds::load<kPublished>(m, lat, at.p0, block);
             }
             auto emissions = [&](int h, float (&el0)[kChunk], float (&el1)[kChunk]) {
                 auto row = [&](bool has, int symbol, float (&el)[kChunk]) {
@@ -3125,7 +3139,7 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
 #pragma unroll
             for (int n = 0; n < kTiles; ++n) s_acc[n * 64 + lane] = acc[n];
         __syncthreads();
-        if (part > 0) return;
+        if (part > 0) return true;
         for (int i = 1; i < sharing; ++i) {
             const float4v* const theirs = reinterpret_cast<const float4v*>(s_hi + i * tile_lds_ints(Lmax, kTiles));
 #pragma unroll
@@ -3153,6 +3167,7 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
     };
     if (g_args.bf16) write(static_cast<bf16_t*>(g_args.grads));
     else write(static_cast<float*>(g_args.grads));
+    return true;
 }
 
 // grid (workgroups per utterance, B)
@@ -3163,7 +3178,7 @@ void ctc_gradient_narrow_kernel(const TileArgs args, const Utt* __restrict__ met
                                 const LatticeOut lat)
 {
     extern __shared__ uint4v tile_lds[];
-    narrow_tile<kTiles, false>(args, meta, labels, emit_blank64, emit_label, lat, tile_lds, blockIdx.y, blockIdx.x);
+    narrow_tile<kTiles, false, TileOf::kAny>(args, meta, labels, emit_blank64, emit_label, lat, tile_lds, blockIdx.y, blockIdx.x);
 }
 
 // Larger alphabets: the softmax launch has written y (and zeros); here the columns of the label's symbols and the
@@ -3344,19 +3359,31 @@ struct FusedArgs {
     LaunchWords wk;
     TileArgs tiles;
 };
-// A chain that the workgroup has taken.  Hardly ever called, and so a function of its own, which leaves the registers of the
-// common way alone (inlined, it cost that 1 to 5 us of 57).
+// What is hardly ever needed has functions of its own, which leave the registers of the common way alone: a chain that this
+// workgroup has taken from another (inlined, it cost the common way 1 to 5 us of 57), or that runs in the log domain, and the
+// tiles of such chains.  `args` points to the launch's FusedArgs.
 typedef __attribute__((address_space(3))) void* LdsPointer;
-template <Sync kSync>
-__device__ __attribute__((noinline)) void run_taken_chain(uint64_t args, int chain, LdsPointer lds)
+__device__ __forceinline__ const FusedArgs& fused_args(uint64_t args)
 {
     typedef __attribute__((address_space(4))) const FusedArgs* ArgsPointer;
     const uint64_t lo = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(args)));
     const uint64_t hi = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(args >> 32)));
-    const FusedArgs& a = *(const FusedArgs*)reinterpret_cast<ArgsPointer>(hi << 32 | lo);
+    return *(const FusedArgs*)reinterpret_cast<ArgsPointer>(hi << 32 | lo);
+}
+template <Sync kSync>
+__device__ __attribute__((noinline)) void run_taken_chain(uint64_t args, int chain, LdsPointer lds)
+{
+    const FusedArgs& a = fused_args(args);
     if (kSync != Sync::kNone || threadIdx.x < 64)
         lattice_body<kSync, Mode::kGrad, true>(__builtin_amdgcn_readfirstlane(chain), a.meta, a.labels, a.emit_blank, a.emit_blank64,
                                                a.emit_label, a.lat, a.logp, a.costs, a.chain_err, a.sink, (void*)lds, a.wk, true);
+}
+template <int kTiles>
+__device__ __attribute__((noinline)) void log_tile(uint64_t args, int b, int group, LdsPointer lds)
+{
+    const FusedArgs& a = fused_args(args);
+    narrow_tile<kTiles, false, TileOf::kLog>(a.tiles, a.meta, a.labels, a.emit_blank64, a.emit_label, a.lat, (uint4v*)lds,
+                                             __builtin_amdgcn_readfirstlane(b), __builtin_amdgcn_readfirstlane(group));
 }
 
 template <Sync kSync, int kTiles>
@@ -3369,11 +3396,13 @@ void ctc_lattice_gradient_kernel(const Utt* __restrict__ meta, const int* __rest
 {
     extern __shared__ uint4v fused_lds[];
     const int index = static_cast<int>(blockIdx.x);
+    auto args = []() { return (uint64_t)__builtin_amdgcn_kernarg_segment_ptr(); };
     if (index < tiles.first_group) {
         if (kSync == Sync::kNone && threadIdx.x >= 64) return;
         __builtin_amdgcn_s_setprio(3);
-        lattice_body<kSync, Mode::kGrad, true>(order[index], meta, labels, emit_blank, emit_blank64, emit_label, lat, logp, costs, chain_err,
-                                               sink, fused_lds, wk);
+        if (lattice_body<kSync, Mode::kGrad, true, false>(order[index], meta, labels, emit_blank, emit_blank64, emit_label, lat, logp,
+                                                          costs, chain_err, sink, fused_lds, wk))
+            run_taken_chain<kSync>(args(), order[index], (LdsPointer)fused_lds);
     } else {
         const int tile = index - tiles.first_group, rank = tile / tiles.groups, group = tile - rank * tiles.groups;
         const int b = __builtin_amdgcn_readfirstlane(tiles.by_end[rank]);
@@ -3382,13 +3411,14 @@ void ctc_lattice_gradient_kernel(const Utt* __restrict__ meta, const int* __rest
         if ((flags & kUttRuns) && group * (kRowThreads / 64 / sharing) * kBlockFrames < frames) {
             int ran = 0, chain;
             while (__builtin_expect((chain = chain_to_take(tiles, b, tile, ran)) >= 0, 0)) {
-                run_taken_chain<kSync>((uint64_t)__builtin_amdgcn_kernarg_segment_ptr(), chain, (LdsPointer)fused_lds);
+                run_taken_chain<kSync>(args(), chain, (LdsPointer)fused_lds);
                 ran |= 1 << (chain & 1);
                 __syncthreads();
             }
         }
         if (threadIdx.x >= kRowThreads) return;          // (workgroups as large as the longest label's chains)
-        narrow_tile<kTiles, true>(tiles, meta, labels, emit_blank64, emit_label, lat, fused_lds, b, group);
+        if (!narrow_tile<kTiles, true, TileOf::kLinear>(tiles, meta, labels, emit_blank64, emit_label, lat, fused_lds, b, group))
+            log_tile<kTiles>(args(), b, group, (LdsPointer)fused_lds);
     }
 }
 

@@ -45,3 +45,11 @@ def test_blocks_of_many_utterances_are_not_shared(A):
 @pytest.mark.parametrize("A", [29, 90])
 def test_longest_labels_and_bf16(A):
     pc.check(batch_of([1500, 1130], [600, 1023 if A > 64 else 900], A, sigma=1.0), ctc.DTYPE_BF16)
+
+
+@pytest.mark.parametrize("A,copies", [(29, 1), (64, 1), (90, 1), (40, 12)])     # beside the chains, in launches of their own
+def test_log_domain_around_blocks_and_pieces(A, copies):
+    """Logits so steep that every utterance has emissions below the linear domain's range."""
+    frames = [1, 15, 16, 17, 33, 150, 300, 290, 480, 470, 700]
+    labels = [1, 2, 0, 5, 9, 63, 127, 128, 223, 225, 321]
+    pc.check(batch_of(frames, labels, A, copies=copies, sigma=60.0))

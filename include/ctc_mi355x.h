@@ -77,9 +77,9 @@ typedef enum {
 enum {
     CTC_KERNEL_SOFTMAX = 0,    /* row-wise log-softmax statistics + emission gather (for alphabets
                                   wider than 2048 also the dense part of the gradient) */
-    CTC_KERNEL_LATTICE = 1,    /* alpha and beta recursions, one launch; where no more chains run than
-                                  there are compute units, and the alphabet has at most 64 symbols, also
-                                  the gradient */
+    CTC_KERNEL_LATTICE = 1,    /* alpha and beta recursions, one launch; alphabets of at most 64 symbols: also the
+                                  gradient where the batch's lengths make that quicker
+                                  (ctc_debug_set_overlap) */
     CTC_KERNEL_GRADIENT = 2,   /* softmax minus normalised occupancy, zero fill of padding */
     /* A short copy launch (the per-call metadata, from pinned host memory into the workspace)
        precedes these three and is not timed separately; the grouping of each label's positions
@@ -155,8 +155,7 @@ ctc_status_t ctc_loss_and_grad(const void *activations,
  *
  *   kernel_ms     (host) [CTC_NUM_KERNELS]; the third entry is 0 where the call has no third launch:
  *                 with grads == NULL, and where the lattice launch writes the gradient as well
- *                 (alphabets of at most 64 symbols, no more chains -- two per utterance -- than compute
- *                 units: the second entry is then the time of both)
+ *                 (ctc_debug_set_overlap: the second entry is then the time of both)
  */
 ctc_status_t ctc_profile_kernels(const void *activations,
                                  const int32_t *flat_labels,
@@ -357,12 +356,13 @@ void ctc_debug_set_end_polls(int polls);
 /*
  * Diagnostics.  Where a call's recursions leave compute units idle (no more chains, two per utterance,
  * than compute units; alphabets of at most 64 symbols; labels of no more than twelve wavefronts), the
- * gradient is written inside the recursions' launch, by workgroups that each wait for the two chains of
- * their utterance.  `percent`: 0 gives the gradient a launch of its own after the recursions', for calls
- * made afterwards, process-wide (for measurements of the two forms side by side); 1..100 makes the
- * recursions' own workgroups leave about that share of them to the workgroups that wait, which then run them,
- * as they do when another launch keeps the former from a compute unit (for tests); anything else restores the
- * default.  Results are bitwise the same whatever the setting.
+ * gradient may be written inside the recursions' launch, by workgroups that each wait for the two chains of
+ * their utterance; it is where the batch's lengths make that the quicker form.  `percent`: 0 gives the gradient
+ * a launch of its own after the recursions' for calls made afterwards, process-wide; 1..100 writes it beside the
+ * recursions wherever that can be done, and makes their own workgroups leave about that share of them to the
+ * workgroups that wait, which then run them, as they do when another launch keeps the former from a compute unit
+ * (for tests); more than 100 does only the former (for measurements of the two forms side by side); negative
+ * restores the default.  Results are bitwise the same whatever the setting.
  */
 void ctc_debug_set_overlap(int percent);
 

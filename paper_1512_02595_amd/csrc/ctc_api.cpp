@@ -27,7 +27,7 @@ thread_local int g_last_hip_error = 0;
 std::atomic<int> g_poll_budget{kDefaultPollBudget};
 std::atomic<int> g_end_polls{kDefaultEndPolls};
 std::atomic<int> g_sequential_chains{0};
-std::atomic<int> g_overlap{-1};          // 0: the gradient in a launch of its own; 1..100: Launch::late_percent
+std::atomic<int> g_overlap{-1};          // 0: the gradient in a launch of its own; 1..100: Launch::late_percent; more: beside the chains wherever it can be
 
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
@@ -453,10 +453,19 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
         for (int i = 0; i < n_run; ++i) rows -= run_frames[i];
         out->defer = deferred_frames(static_cast<double>(rows) * c.A * elem, max_frames, n_run * dirs, out->n_cu);
     }
-    const int overlap = g_overlap.load(std::memory_order_relaxed);
-    out->late_percent = std::max(overlap, 0);
     out->fused = c.mode == Mode::kGrad && !needs_barrier && !sequential_chains && n_run > 0 &&
-                 overlap != 0 && fuse_gradient(c.A, max_waves, n_run * dirs, out->n_cu);
+                 can_fuse_gradient(c.A, max_waves, n_run * dirs, out->n_cu);
+    const int overlap = g_overlap.load(std::memory_order_relaxed);
+    out->late_percent = overlap <= 100 ? std::max(overlap, 0) : 0;
+    if (out->fused && overlap < 0) {
+        double last = 0, early = 0, late = 0;
+        auto end_of = [&](int i) { return run_frames[i] * chain_us_per_frame(run_waves[i]); };
+        for (int i = 0; i < n_run; ++i) last = std::max(last, end_of(i));
+        for (int i = 0; i < n_run; ++i)
+            (end_of(i) < 0.85 * last ? early : late) += static_cast<double>(frame_blocks(run_frames[i])) * std::max(1, label_pieces(meta[running[i]].L));
+        out->fused = gradient_beside_chains(early, late, last, max_waves, n_run * dirs, out->n_cu);
+    }
+    out->fused = out->fused && overlap != 0;
     out->folded = c.A <= kDirectMaxA && c.B <= kNarrowMaxB && c.T < (1 << 29);
     out->lay = lay;
     return CTC_STATUS_SUCCESS;
@@ -632,8 +641,15 @@ ctc_status_t run_device(const void* x, const int32_t* labels, const int32_t* lab
     p.defer = grads && A > kDirectMaxA && !p.needs_barrier
                   ? deferred_frames(static_cast<double>(T) * B * A * elem / 3, T / 2, p.n_chains, p.n_cu) : 0;
     const int overlap = g_overlap.load(std::memory_order_relaxed);
-    p.late_percent = std::max(overlap, 0);
-    p.fused = grads && !p.needs_barrier && overlap != 0 && fuse_gradient(A, p.max_waves, p.n_chains, p.n_cu);
+    p.late_percent = overlap <= 100 ? std::max(overlap, 0) : 0;
+    p.fused = grads && !p.needs_barrier && overlap != 0 && can_fuse_gradient(A, p.max_waves, p.n_chains, p.n_cu);
+    if (p.fused && overlap < 0) {
+        // (lengths spread evenly up to the bounds, as above: one utterance in seven ends late, half the frames are frames)
+        const double blocks = static_cast<double>(B) * frame_blocks(T);
+        const double late = 0.14 * blocks * std::max(1, label_pieces(max_label * 3 / 4)), all = 0.5 * blocks * std::max(1, label_pieces(max_label / 2));
+        p.fused = gradient_beside_chains(std::max(all - late, 0.0), late, T * chain_us_per_frame(all_plans.latency_waves[symbol_major][max_label]),
+                                         p.max_waves, p.n_chains, p.n_cu);
+    }
     // Narrow alphabets: the softmax launch builds the records itself (no planning launch before it); every
     // utterance's setup workgroup weighs all B utterances for the run order, which is worth it up to here.
     p.folded = A <= kDirectMaxA && B <= kDeviceFoldMaxB && max_label > 0;

@@ -193,17 +193,47 @@ inline int deferred_frames(double zero_bytes, int longest, int n_chains, int n_c
     return static_cast<int>(std::min(16.0, 16.0 * fits / zero_bytes));
 }
 
-// The gradient of an utterance may be written by workgroups of the lattice launch that wait for its chains
-// (Launch::fused).  Chains that need more wavefronts than a workgroup of that launch has keep a launch of their own.
-constexpr int kFusedWaves = 12;
-constexpr int kDoneStride = 16;      // words between two utterances' words: a line each for those who poll
-constexpr int kTakenWord = 1;        // which of them say that somebody runs the chain, by direction (the first is the counter)
-constexpr int kDoneWords = 3;
+// The gradient's recomputation takes a label in pieces of 128 positions, one to a wavefront, whose inner edges overlap by the
+// frames of a block on either side.
+constexpr int kPiecePositions = 128, kPieceHalo = kBlockFrames, kPieceStep = kPiecePositions - 2 * kPieceHalo;
+CTC_HOST_DEVICE constexpr int label_pieces(int L)
+{
+    return L <= kPiecePositions ? (L > 0 ? 1 : 0) : (L - kPiecePositions + kPieceStep - 1) / kPieceStep + 1;
+}
 
-inline bool fuse_gradient(int A, int max_waves, int n_chains, int n_cu)
+// The gradient of an utterance may be written by workgroups of the lattice launch that wait for its chains (Launch::fused).
+// Chains that need more wavefronts than a workgroup of that launch has keep a launch of their own: with sixteen, 128 registers
+// a lane remain, and labels of up to 900 symbols, which would need them, ran up to 60 % longer beside their chains than apart
+// (64 utterances of 2000 frames); with eight, labels of 470 symbols and more could not use what it saves for 32 utterances of
+// 1500 frames (540 symbols: 169.4 us apart, 157.6 beside).
+constexpr int kFusedWaves = 12;
+constexpr bool can_fuse_gradient(int A, int max_waves, int n_chains, int n_cu)
 {
     return A <= kDirectMaxA && max_waves <= kFusedWaves && n_chains <= n_cu;
 }
+// Whether that pays.  Beside the chains, the compute units without one write the gradient of the utterances that end before the
+// longest (`early`; `late`: whose chains end in the last 15 % of the time) and a launch boundary is saved.  But what is left at
+// the end is written by fewer workgroups at a time than in a launch of its own, since they are as large as the chains' ones:
+// three to a compute unit with four wavefronts, two with up to eight, one with more.  `early` and `late` are blocks of frames
+// times pieces of the label, a third of a microsecond on the whole chip for every compute unit; `chain_us`: the longest chain.
+// Fitted to 692 batches (1 to 128 utterances of 50 to 1500 frames, labels of 12 to 660 symbols, frames spread from 10 to 100 %
+// of the longest up to it).  Against the better of the two forms: always beside takes 3.3 % more on average and 59 % at worst
+// (128 utterances of 1275 to 1500 frames, labels of 400 to 660 symbols: 468 us, apart 294), always apart 2.9 and 17.5 %, this
+// rule 0.6 and 17.5 % (64 utterances of 300 to 1500 frames, labels of 360 to 600: 182 us apart, 155 beside).
+inline bool gradient_beside_chains(double early, double late, double chain_us, int max_waves, int n_chains, int n_cu)
+{
+    const double busy = static_cast<double>(n_chains) / n_cu, saved = std::min(std::max(chain_us / 8, 2.0), 10.0);
+    early /= n_cu;
+    late /= n_cu;
+    return max_waves > 8 ? 1.5 * late + 18.0 * busy <= saved + 0.4 * early * (1.0 - busy)
+                         : late + 3.0 * busy <= saved + 0.7 * early * (1.0 - 0.4 * busy);
+}
+// About what a chain of this many wavefronts takes for a frame, in microseconds (up to four run on a SIMD each).
+inline double chain_us_per_frame(int waves) { return waves == 1 ? 0.045 : (waves <= 4 ? 0.06 : 0.088); }
+
+constexpr int kDoneStride = 16;      // words between two utterances' words: a line each for those who poll
+constexpr int kTakenWord = 1;        // which of them say that somebody runs the chain, by direction (the first is the counter)
+constexpr int kDoneWords = 3;
 
 // The sink of a lattice launch: for each of its up to 2 B chain workgroups, kSinkBytes for each of the
 // up to kSinkWaves wavefronts.

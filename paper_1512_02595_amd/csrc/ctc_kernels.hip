@@ -2530,7 +2530,6 @@ void ctc_backtrace_kernel(const Utt* __restrict__ meta, const int* __restrict__ 
 //   alpha: (blank j, label j) as in the forward chain;  beta: (label j, blank j + 1), the backward chain's pair.
 // 128 positions make a piece; longer labels take several, each recomputing the 16 positions at its inner edges that
 // its neighbour owns (an error at the edge moves up one position per frame).
-constexpr int kPiecePositions = 128, kPieceHalo = kBlockFrames, kPieceStep = kPiecePositions - 2 * kPieceHalo;
 // A row of one value per lane in LDS, padded so that 16-byte reads of 16 rows meet in no bank; two blocks of a row per frame.
 constexpr int kShareRow = kPiecePositions / 2 + 4, kShareInts = 2 * kBlockFrames * kShareRow;
 constexpr int kBlankInts = 2 * kBlockFrames;
@@ -2877,11 +2876,7 @@ __device__ __forceinline__ void block_shares_log(const Utt& m, const LatticeOut&
                  own1 ? word_share(alpha[r][1], beta[r][1], static_cast<int>(exponents[r][1]) + to_share) : 0.0f);
     }
 }
-// Pieces of a label, and what wavefront `first` of `step` takes of them: for_piece(base, own_first, own_end).
-__host__ __device__ constexpr int label_pieces(int L)
-{
-    return L <= kPiecePositions ? (L > 0 ? 1 : 0) : (L - kPiecePositions + kPieceStep - 1) / kPieceStep + 1;
-}
+// What wavefront `first` of `step` takes of a label's pieces: for_piece(base, own_first, own_end).
 template <typename F>
 __device__ __forceinline__ void for_pieces(int L, int first, int step, F&& for_piece)
 {

@@ -293,8 +293,8 @@ def debug_set_sequential_chains(on: bool) -> None:
 
 
 def debug_set_overlap(percent: int) -> None:
-    """The gradient inside the lattice launch where that leaves compute units idle: 0 gives it a launch of its
-    own; 1..100: that share of the recursions is left to the gradient's workgroups; negative: the default."""
+    """The gradient inside the lattice launch where that leaves compute units idle: 0 never; 1..100 always, with that
+    share of the recursions left to the gradient's workgroups; more than 100 always; negative: the default."""
     load().ctc_debug_set_overlap(int(percent))
 
 

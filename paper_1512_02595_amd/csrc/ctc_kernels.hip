@@ -344,24 +344,15 @@ struct SetupArgs {
 // of the label, so that a label of 500 symbols costs 125 steps per lane instead of 1000.
 constexpr int kSetupLabelSlots = CTC_MAX_LABEL_LENGTH + 5;     // the label and a quarter's padding
 
-// `labels8`: the label strings as bytes (narrow alphabets, read out of the pinned host image: a
-// quarter of the traffic), to be written out as ints to `labels_out` by the utterance's first part;
-// nullptr: `labels` holds them as ints.
 __device__ __forceinline__ void setup_words(const Utt m, const int b, const SetupArgs sa);
 __device__ __forceinline__ void setup_role(const Utt m, const int b, const int* __restrict__ labels,
-                                           const SetupArgs sa, int* s_lab, const int part, const int parts,
-                                           const unsigned char* __restrict__ labels8 = nullptr,
-                                           int* __restrict__ labels_out = nullptr)
+                                           const SetupArgs sa, int* s_lab, const int part, const int parts)
 {
     const int tid = threadIdx.x;
     const int* lab = labels + m.lab_off;
     const int quarter_length = (m.L + 3) / 4;
     // padding: a symbol that is neither smaller than nor equal to any real one
-    for (int j = tid; j < 4 * quarter_length; j += kRowThreads) {
-        const int c = (j >= m.L) ? 0x7FFFFFFF : (labels8 ? static_cast<int>(labels8[m.lab_off + j]) : lab[j]);
-        s_lab[j] = c;
-        if (labels_out && part == 0 && j < m.L) labels_out[m.lab_off + j] = c;
-    }
+    for (int j = tid; j < 4 * quarter_length; j += kRowThreads) s_lab[j] = j < m.L ? lab[j] : 0x7FFFFFFF;
     __syncthreads();
     const int quarter = tid & 3;
     const int* const mine = s_lab + quarter * quarter_length;
@@ -781,7 +772,7 @@ void ctc_softmax_symbols_kernel(const T* __restrict__ x, Utt* __restrict__ meta,
 // kilobytes under way; the normalised rows are the emission block, stored symbol-major.
 // grid (ceil(T / 64) + parts, B); dynamic LDS 64 * A floats.
 struct NarrowImage {
-    const int* words;         // the pinned image: meta, order, labels, tasks as they lie in the workspace, then the labels as bytes
+    const int* words;         // the pinned image: meta, order, labels as they lie in the workspace, then the labels as bytes
     int labels_first, labels_end;   // the label strings' place in it (4-byte words): not copied, the setup role writes them
     int count;                // words to copy (up to the byte labels)
     size_t labels8_offset;    // of the byte labels (bytes)

@@ -35,9 +35,9 @@ ALU_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12
 # so `achieved` is the rate at which the defined work gets done, not the ALU's busy rate.
 LANE_OPS_PER_PAIR_STEP = 41
 # What the linear-domain kernel executes per pair-step: 2 fused multiply-adds, 1 addition,
-# 2 multiplications, 2 conversions of emissions, 2 DPP moves, 1 pack, 1 address, and about 3 for
-# the renewal of the exponents every 8 steps.
-LANE_OPS_EXECUTED = 14
+# 2 multiplications, 1 conversion of the label's emission, 2 DPP moves, and about 3 for the
+# renewal of the exponents every 8 steps and the states stored every 16.
+LANE_OPS_EXECUTED = 11
 # The max recursion of the alignment has no transcendentals: compares, selects, two fp64 adds.
 LANE_OPS_PER_PAIR_STEP_ALIGN = 22
 
@@ -87,41 +87,48 @@ def measured_traffic(config, dtype, kernel):
     return float(k["read_bytes"] + k["written_bytes"]), entry.get("source_digest") == source_digest()
 
 
+NARROW = 64                      # alphabets up to this size: the normalised rows are the emissions
+BLOCK = 16                       # frames between two states that a chain stores for the gradient
+
+
+def deferred_share(zero_bytes, longest, chains, n_cu=256):
+    """Share of the zero rows of a wide alphabet that the lattice launch writes: deferred_frames in csrc/ctc_internal.h."""
+    if chains + n_cu // 4 > n_cu or zero_bytes <= 0:
+        return 0.0
+    fits = 3.0e6 * 0.045 * longest * (n_cu - chains) / (n_cu // 2)
+    return min(16, int(16 * fits / zero_bytes)) / 16
+
+
 def kernel_bytes(batch, elem, mode="grad"):
-    """Algorithmic HBM bytes of each kernel for one launch on `batch`: what the kernel must read and
-    write once, per frame, per row of the tensor and per lattice cell, as the comments below state."""
-    frames = batch.frames
-    A = batch.A
-    pairs = int((batch.input_lengths.astype(np.int64) * (batch.label_lengths.astype(np.int64) + 1)).sum())
-    cells = batch.lattice_cells
+    """Algorithmic HBM bytes of each kernel for one launch on `batch`: what the kernel must read and write once, as the
+    comments below state.  (Where the lattice launch writes the gradient too, it has the bytes of both: main.)"""
+    frames, A = batch.frames, batch.A
+    T, L = batch.input_lengths.astype(np.int64), batch.label_lengths.astype(np.int64)
+    pairs = int((T * (L + 1)).sum())
+    # emissions: a float per frame and symbol, or label position; the blank's again as a float and a double
+    emissions = (frames * A if A <= NARROW else int((T * L).sum())) * 4 + frames * 12
+    # states at the ends of blocks of frames: two doubles and an exponent per label position and direction
+    states = int(((T + BLOCK - 1) // BLOCK * L).sum()) * 20 * 2
     full = batch.T * batch.B * A * elem
-    if mode != "grad":
-        # cost only / alignment: the activations are read once; the chain reads one emission per
-        # state pair and frame (4 bytes) and, for the alignment, writes one byte of choices per pair
-        # and frame, which the backtrace reads along the path (at most 64 per frame) before it
-        # writes one int32 per frame of the tensor
-        out = {"ctc_softmax": frames * A * elem + frames * 4,
-               "ctc_lattice": pairs * 4 + (pairs if mode == "align" else 0)}
-        if mode == "align":
-            out["ctc_backtrace"] = frames * 64 + batch.T * batch.B * 4
-        else:
-            out["ctc_gradient"] = 0
-        return out, pairs
-    if A > 2048:
-        # wide alphabets: the softmax launch also writes the dense gradient (y, or zeros for
-        # padding); the gradient launch only rewrites the label columns and the blank
-        touched = int((batch.input_lengths.astype(np.int64) * (batch.label_lengths.astype(np.int64) + 2)).sum())
-        soft, grad = frames * A * elem + full, 2 * touched * elem
+    out = {"ctc_softmax": frames * A * elem + emissions, "ctc_lattice": 2 * emissions}
+    if mode == "loss":
+        # the two chains meet in the middle: the emissions once between them, and nothing stored
+        out.update({"ctc_lattice": emissions, "ctc_gradient": 0})
+    elif mode == "align":
+        # ... a word of choices per pair and 8 frames, read where the way may run (64 pairs); one int32 per frame of the tensor
+        out.update({"ctc_lattice": emissions + pairs // 8 * 4, "ctc_backtrace": frames // 8 * 64 * 4 + batch.T * batch.B * 4})
+    elif A <= NARROW:
+        out["ctc_lattice"] += states
+        out["ctc_gradient"] = states + emissions + full
     else:
-        # read every valid row once, write one statistic per row / read the rows again and write
-        # the whole gradient tensor
-        soft, grad = frames * A * elem + frames * 4, frames * A * elem + full
-    return {
-        "ctc_softmax": soft,
-        # one alpha and one beta value per lattice cell, 4 bytes each, written once
-        "ctc_lattice": cells * 8,
-        "ctc_gradient": grad,
-    }, pairs
+        # the softmax launch also writes the dense gradient: y, or zeros for padding, a share of which the lattice launch
+        # takes over; the gradient launch rewrites the label's columns and the blank
+        zeros = full - frames * A * elem
+        beside = zeros * deferred_share(zeros, int(T.max()), 2 * batch.B)
+        out["ctc_softmax"] += full - beside
+        out["ctc_lattice"] += states + beside
+        out["ctc_gradient"] = states + emissions + int((T * (L + 1)).sum()) * elem
+    return out, pairs
 
 
 def main():
@@ -270,6 +277,11 @@ def main():
     if args.mode == "align":
         names[2] = ctc.kernel_name(ctc.KERNEL_BACKTRACE)
     kb = [kernel_bytes(b, elem, args.mode) for b in batches]
+    beside = args.mode == "grad" and args.profile_steps > 0 and kavg[2] == 0        # the lattice launch writes the gradient
+    if beside:
+        for k, _ in kb:
+            k["ctc_lattice"] += k["ctc_gradient"]
+            k["ctc_gradient"] = 0
     kernels = {}
     for i, n in enumerate(names):
         byt = float(np.mean([k[0][n] for k in kb]))
@@ -307,8 +319,9 @@ def main():
                 "log_space_lane_ops_per_pair_step": priced,
                 "log_space_equivalent_frac_of_peak": round(per_s * priced / ALU_PEAK_TOPS, 5),
                 "note": "peak = one non-packed, non-fused VALU operation per lane and clock (256 CUs x 64 lanes x "
-                        "2.4 GHz); the executed count is the linear-domain step's, the log-space count prices the "
-                        "defining recursion (a transcendental as 4)"}
+                        "2.4 GHz); the executed count is the linear-domain step's (the gradient's recomputation, where "
+                        "it shares the launch, is not counted), the log-space count prices the defining recursion (a "
+                        "transcendental as 4)"}
 
     out = {
         "metric": {"grad": "ctc_loss_grad_utterances_per_s", "loss": "ctc_loss_only_utterances_per_s",
@@ -324,6 +337,7 @@ def main():
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "f64 lattice state (probabilities with a per-lane exponent), %s activations" % args.dtype,
         "data": "synthetic",
+        "gradient_beside_chains": bool(beside),
         "config": {"workload": "config[%d] %s: B=%d A=%d T=%d, %d rotating minibatches"
                    % (args.config, batches[0].name, B, batches[0].A, batches[0].T, len(batches)),
                    "mode": args.mode, "metadata": args.metadata, "graph": bool(args.graph),

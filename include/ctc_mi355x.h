@@ -359,9 +359,9 @@ void ctc_debug_set_end_polls(int polls);
  * gradient may be written inside the recursions' launch, by workgroups that each wait for the two chains of
  * their utterance; it is where the batch's lengths make that the quicker form.  `percent`: 0 gives the gradient
  * a launch of its own after the recursions' for calls made afterwards, process-wide; 1..100 writes it beside the
- * recursions wherever that can be done, and makes their own workgroups leave about that share of them to the
- * workgroups that wait, which then run them, as they do when another launch keeps the former from a compute unit
- * (for tests); more than 100 does only the former (for measurements of the two forms side by side); negative
+ * recursions wherever that can be done, and makes about that share of the recursions' workgroups come late, so that
+ * workgroups that wait for them leave their work to them, as they do when another launch keeps those from a compute
+ * unit (for tests); more than 100 does only the former (for measurements of the two forms side by side); negative
  * restores the default.  Results are bitwise the same whatever the setting.
  */
 void ctc_debug_set_overlap(int percent);

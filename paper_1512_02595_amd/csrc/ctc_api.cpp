@@ -56,7 +56,7 @@ int compute_units()
 }
 
 // Region offsets from the batch totals (label symbols, label emissions, frames, lattice pairs).
-void carve(int T, int B, int64_t sumL, int64_t emit, int64_t frames, int64_t ab, Layout* lay)
+void carve(int T, int B, bool narrow, int64_t sumL, int64_t emit, int64_t frames, int64_t ab, Layout* lay)
 {
     Layout l;
     l.sumL = sumL;
@@ -75,6 +75,7 @@ void carve(int T, int B, int64_t sumL, int64_t emit, int64_t frames, int64_t ab,
     l.sink = off;   off = align_up(off + static_cast<size_t>(B) * 2 * kSinkWaves * kSinkBytes);
     l.chain_err = off; off = align_up(off + static_cast<size_t>(B) * sizeof(int32_t));
     l.done = off;   off = align_up(off + static_cast<size_t>(B) * kDoneStride * sizeof(int32_t));
+    l.left = off;   off = align_up(off + (narrow ? static_cast<size_t>(B) * frame_blocks(T) * sizeof(int32_t) : 0));
     l.domain = off; off = align_up(off + static_cast<size_t>(B) * 2 * sizeof(int32_t));
     l.row_flags = off;
     off = align_up(off + static_cast<size_t>(B) * ((T + kFlagFrames - 1) / kFlagFrames) * sizeof(int32_t));
@@ -143,7 +144,7 @@ ctc_status_t make_layout(int T, int B, int A, const int32_t* label_lengths,
     if (too_long) return CTC_STATUS_UNSUPPORTED;
     if (sumL > INT32_MAX || frames > INT32_MAX) return CTC_STATUS_UNSUPPORTED;
     if (B > kMaxBatch) return CTC_STATUS_UNSUPPORTED;
-    carve(T, B, sumL, emit, padded_sum, ab, lay);
+    carve(T, B, A <= kDirectMaxA, sumL, emit, padded_sum, ab, lay);
     return CTC_STATUS_SUCCESS;
 }
 
@@ -157,7 +158,7 @@ ctc_status_t make_layout_bounds(int T, int B, int A, int max_label, ctc_dtype_t 
     const int64_t Tl = T, Bl = B, Ll = max_label, padded = padded_frames(T);
     if (Tl * lattice_pitch(Ll) * 8 > INT32_MAX || Bl * Ll > INT32_MAX || Bl * Tl > INT32_MAX) return CTC_STATUS_UNSUPPORTED;
     const int longest = longest_aligned(T, max_label);
-    carve(T, B, Bl * Ll, Bl * (A <= kDirectMaxA ? padded * A : gathered_emissions(T, longest)), Bl * padded, Bl * lattice_words(T, longest), lay);
+    carve(T, B, A <= kDirectMaxA, Bl * Ll, Bl * (A <= kDirectMaxA ? padded * A : gathered_emissions(T, longest)), Bl * padded, Bl * lattice_words(T, longest), lay);
     return CTC_STATUS_SUCCESS;
 }
 

@@ -232,8 +232,8 @@ inline bool gradient_beside_chains(double early, double late, double chain_us, i
 inline double chain_us_per_frame(int waves) { return waves == 1 ? 0.045 : (waves <= 4 ? 0.06 : 0.088); }
 
 constexpr int kDoneStride = 16;      // words between two utterances' words: a line each for those who poll
-constexpr int kTakenWord = 1;        // which of them say that somebody runs the chain, by direction (the first is the counter)
-constexpr int kDoneWords = 3;
+constexpr int kTakenWord = 1;        // which of them says that the chains have a workgroup (take_chain; the first is the counter)
+constexpr int kDoneWords = 2;
 
 // The sink of a lattice launch: for each of its up to 2 B chain workgroups, kSinkBytes for each of the
 // up to kSinkWaves wavefronts.
@@ -439,7 +439,9 @@ struct Layout {
     size_t sink = 0;      // what lanes with nothing to store scribble on: kSinkBytes per wavefront of a lattice launch
     size_t chain_err = 0; // int32[B]     set when a lattice wavefront gave up waiting for its neighbour
     size_t done = 0;      // int32[B * kDoneStride]  how far the utterance's chains are: cost-only calls (finish_loss)
-                          //              and gradients written beside the chains (announce_end, chain_to_take)
+                          //              and gradients written beside the chains (announce_end, take_chain)
+    size_t left = 0;      // int32[B * frame_blocks(T)]  narrow alphabets, gradient beside the chains: the list of workgroups that
+                          //              have left their places (chains_taken)
     size_t domain = 0;    // int32[2 B]   per utterance and direction, nonzero: that chain ran in the log domain (published by
                           //              the chain for the gradient, which must know where its exponent rows are)
     size_t row_flags = 0; // int32[B * ceil(T / 64)]  narrow alphabets: per 64 frames of an utterance, nonzero if one of
@@ -510,7 +512,7 @@ struct Launch {
     bool crowded;             // plan the chains for total work rather than latency (device planner)
     int n_cu;                 // compute units of the device
     bool fused;               // the lattice launch writes the gradient too (ctc_lattice_gradient_kernel)
-    int late_percent;         // ... and this share of the chains' own workgroups come late (tests)
+    int late_percent;         // ... and this share of the chains' workgroups come late (tests)
     int end_polls;            // ... and how often its workgroups look for the end of their chains (wait_for_chains)
     int defer;                // of every 16 frames, those whose zero rows the lattice launch writes (deferred_frames)
     // Narrow alphabets, host metadata: there is no upload launch; the softmax launch reads the pinned image

@@ -329,7 +329,7 @@ struct SetupArgs {
     float* costs;
     int* chain_err;
     int* done;            // per utterance (kDoneStride apart): kDoneWords words that its chains and those who wait for them
-                          // share (finish_loss, announce_end, chain_to_take)
+                          // share (finish_loss, announce_end, take_chain)
     float* log0;          // kEmissionConstants floats that lattice lanes without a label state read as their
                           // emission: probability 0 (linear-domain chains) and log 0 (log-domain chains)
     double* emit_blank64; // the blank's probability per frame as fp64 (Layout::emit_blank64)
@@ -1125,7 +1125,7 @@ struct HaloHeader {
     int finished;                     // wavefronts that have reached the end of the chain
     int gave_up;
     float cost;
-    int taken;                        // chains of a launch that writes the gradient too: somebody else runs this one
+    int left;                         // chains of a launch that writes the gradient too: see lattice_body
 };
 // Chains with one pair per lane.
 struct HaloWave {
@@ -2090,7 +2090,7 @@ struct LaunchWords {
     int flag_blocks;          // ... per utterance
     int* domain;              // per utterance and direction: did the chain run in the log domain
     int* done;                // per utterance, kDoneStride apart: see finish_loss, announce_end
-    int late_percent;         // launch that writes the gradient too: this share of the chains' own workgroups come late (tests)
+    int late_percent;         // launch that writes the gradient too: this share of the chains' workgroups come late (tests)
     int* host_flag;           // pinned host word that receives host_flag_value: the image may be reused (or nullptr)
     int host_flag_value;
     const int* status_words;  // device-resident metadata built by the narrow softmax launch: per utterance, nonzero if
@@ -2188,32 +2188,30 @@ __device__ __forceinline__ void announce_end(int* done, int waves, float* cost)
     }
 }
 
-// A launch that writes the gradient too: who runs a chain, in the utterance's word for its direction.  0: nobody yet; kTakenByOwn:
-// the chain's own workgroup; kTakenByTile + i: the gradient's workgroup i (chain_to_take).  Written once.
-constexpr int kTakenByOwn = 1, kTakenByTile = 2;
-// Takes the chain if nobody has; returns what was in the word.
-__device__ __forceinline__ int take_chain(int* word, int by_whom)
+// A launch that writes the gradient too: an utterance's second word says which of its chains have been taken, that is, have a
+// workgroup that runs them (bits 0 and 1), and which of the gradient's workgroups have left their places because that took
+// too long: the last one's number plus one (from bit 2), the one before it in that one's word of `left`, and so on.
+constexpr int kBothTaken = 3, kLeftShift = 2;
+__device__ __forceinline__ int take_chain(int* word, int direction)
 {
-    int before = 0;
-    __hip_atomic_compare_exchange_strong(word, &before, by_whom, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return before;
+    return __hip_atomic_fetch_or(word, 1 << direction, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// (tests: a chain's own workgroup comes so late that others have taken it; bounded, in case nobody waits for it)
-__device__ __forceinline__ void wait_until_taken(const int* word)
+// (tests: a chain's workgroup comes so late that places have been left; bounded, in case there are none)
+__device__ __forceinline__ void wait_until_left(const int* word)
 {
-    for (int polls = 1 << 12; polls > 0 && published(word) == 0; --polls) __builtin_amdgcn_s_sleep(10);
+    for (int polls = 1 << 14; polls > 0 && published(word) >> kLeftShift == 0; --polls) __builtin_amdgcn_s_sleep(10);
 }
 
-// `chain`: utterance * 2 + direction.  kFused: the launch writes the gradient too; `taken`: this workgroup has taken the chain.
-// kLog: with the log-domain chains; without them the result is whether the chain is one, and then it has not been run.
-template <Sync kSync, Mode kMode, bool kFused = false, bool kLog = true>
-__device__ __forceinline__ bool lattice_body(const int chain, const Utt* __restrict__ meta, const int* __restrict__ labels,
+// `chain`: utterance * 2 + direction.  kFused: the launch writes the gradient too; then the result, for the wavefronts that are
+// still there, is the list of places that this workgroup is to take after its chain (take_chain), 0 where there are none.
+template <Sync kSync, Mode kMode, bool kFused = false>
+__device__ __forceinline__ int lattice_body(const int chain, const Utt* __restrict__ meta, const int* __restrict__ labels,
                                              const float* __restrict__ emit_blank, const double* __restrict__ emit_blank64,
                                              const float* __restrict__ emit_label,
                                              const LatticeOut lat,
                                              double* __restrict__ logp, float* __restrict__ costs,
                                              int* __restrict__ chain_err, uint32_t* __restrict__ sink,
-                                             void* lds, const LaunchWords& wk, const bool taken = false)
+                                             void* lds, const LaunchWords& wk)
 {
     // The first workgroup of the launch tells the host that the pinned image of the call is free
     // again (calls whose softmax launch read the image itself: this launch follows it).
@@ -2226,9 +2224,9 @@ __device__ __forceinline__ bool lattice_body(const int chain, const Utt* __restr
         const bool any = __ballot(bad) != 0;
         if (threadIdx.x == 0) *wk.status_out = any ? CTC_STATUS_INVALID_VALUE : CTC_STATUS_SUCCESS;
     }
-    if (chain < 0) return false;      // device-planned batches launch a workgroup per utterance and direction, running or not
+    if (chain < 0) return 0;      // device-planned batches launch a workgroup per utterance and direction, running or not
     // (measurements of the recursions one after the other: a launch that leaves one direction out)
-    if (kMode == Mode::kGrad && ((wk.skip_directions >> (chain & 1)) & 1)) return false;
+    if (kMode == Mode::kGrad && ((wk.skip_directions >> (chain & 1)) & 1)) return 0;
     // Lanes with nothing to store write to a sink: 64 bytes of it per wavefront of the launch.  (One
     // address for the whole launch was what a crowded launch waited for: every store instruction of
     // every chain carried a write to it, and they all met in one channel of each die's L2.  512
@@ -2238,20 +2236,22 @@ __device__ __forceinline__ bool lattice_body(const int chain, const Utt* __restr
     const int u = chain >> 1;
     const bool forward = (chain & 1) == 0;
     // (asked for here, looked at once what else the chain starts from has come)
-    int by_whom = 0;
-    if (kFused && !taken && threadIdx.x == 0) {
-        int* const word = &wk.done[u * kDoneStride + kTakenWord + (forward ? 0 : 1)];
-        if (static_cast<int>(blockIdx.x) * 37 % 100 < wk.late_percent) wait_until_taken(word);
-        by_whom = take_chain(word, kTakenByOwn);
+    int before = 0, left = 0;
+    if (kFused && threadIdx.x == 0) {
+        int* const word = &wk.done[u * kDoneStride + kTakenWord];
+        if (static_cast<int>(blockIdx.x) * 37 % 100 < wk.late_percent) wait_until_left(word);
+        before = take_chain(word, forward ? 0 : 1);
+        // the second to take one: nobody leaves after this
+        left = (before & kBothTaken) != 0 ? before >> kLeftShift : 0;
     }
     const Utt m = meta[u];
-    if (!(m.flags & kUttRuns)) return false;     // (a run order built on the device lists every utterance)
+    if (!(m.flags & kUttRuns)) return 0;     // (a run order built on the device lists every utterance)
     // Which recursion: the barrier kernel and the maximum recursion have the log domain only;
     // otherwise the flag that the softmax launch may have raised decides.  A linear-domain chain
     // gives one pair or two to a lane as the launcher planned it (two_pairs_per_lane).
     const bool in_log_domain = kSync == Sync::kBarrier || kMode == Mode::kBest || (m.flags & kUttLogDomain) != 0 ||
                                rows_flagged(wk.row_flags, u, wk.flag_blocks, m.Tb);
-    if (kMode == Mode::kLoss && in_log_domain && !forward) return false;       // (the forward chain runs all the way)
+    if (kMode == Mode::kLoss && in_log_domain && !forward) return 0;       // (the forward chain runs all the way)
     const bool two_pairs = kSync == Sync::kHalo && !in_log_domain && (m.flags & kUttTwoPairs) != 0;
     const int waves = two_pairs ? m.waves2 : m.waves;
     const bool idle = static_cast<int>(threadIdx.x >> 6) >= waves;
@@ -2270,12 +2270,11 @@ __device__ __forceinline__ bool lattice_body(const int chain, const Utt* __restr
         if (threadIdx.x == 0) {
             hl->finished = 0;
             hl->gave_up = 0;
-            hl->taken = by_whom;
+            hl->left = left;
         }
         __syncthreads();
-        if (kFused && __builtin_amdgcn_readfirstlane(hl->taken) != 0) return false;
-        if (!kLog && in_log_domain) return true;
-        if (idle) return false;
+        if (kFused) left = __builtin_amdgcn_readfirstlane(hl->left);
+        if (idle) return left;
     } else if (kSync == Sync::kBarrier) {
         if (idle) {
             // Nothing to compute, but keep meeting the barriers of the working wavefronts:
@@ -2284,12 +2283,15 @@ __device__ __forceinline__ bool lattice_body(const int chain, const Utt* __restr
             const int barriers = kMode == Mode::kBest ? 2 * chain_chunks(m.Tb, !forward) * kChunk
                                                       : static_cast<int>(padded_frames(m.Tb)) + (forward ? 1 : 0);
             for (int i = 0; i < barriers; ++i) __syncthreads();
-            return false;
+            return 0;
         }
     }
     if (kFused && kSync == Sync::kNone) {
-        if (__builtin_amdgcn_readfirstlane(by_whom) != 0) return false;
-        if (!kLog && in_log_domain) return true;
+        HaloHeader* const hl = static_cast<HaloHeader*>(lds);
+        if (threadIdx.x == 0) hl->left = left;
+        __syncthreads();
+        left = __builtin_amdgcn_readfirstlane(hl->left);
+        if (threadIdx.x >= 64) return left;
     }
     // (for the gradient, which must know what each chain has left: a word per direction)
     if (kMode == Mode::kGrad && threadIdx.x == 0) publish(&wk.domain[2 * u + (forward ? 0 : 1)], in_log_domain ? 1 : 0);
@@ -2310,17 +2312,15 @@ __device__ __forceinline__ bool lattice_body(const int chain, const Utt* __restr
             }
             if (kMode == Mode::kLoss) finish_loss(m, u, labels, lat, wk.done, costs, 2 * waves, lost);
             if (kFused) announce_end(&wk.done[u * kDoneStride], waves, &costs[u]);
-            return false;
+            return left;
         }
     }
-    if constexpr (kLog) {
-        if (forward)
-            run_chain_log<false, kSync, kMode>(m, u, labels, emit_blank, emit_blank64, emit_label, lat.alpha, lat.alpha_exponents, logp, costs, chain_err, sink, lds);
-        else if constexpr (kMode != Mode::kLoss)
-            run_chain_log<true, kSync, kMode>(m, u, labels, emit_blank, emit_blank64, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
-        if (kFused) announce_end(&wk.done[u * kDoneStride], waves, &costs[u]);
-    }
-    return false;
+    if (forward)
+        run_chain_log<false, kSync, kMode>(m, u, labels, emit_blank, emit_blank64, emit_label, lat.alpha, lat.alpha_exponents, logp, costs, chain_err, sink, lds);
+    else if constexpr (kMode != Mode::kLoss)
+        run_chain_log<true, kSync, kMode>(m, u, labels, emit_blank, emit_blank64, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
+    if (kFused) announce_end(&wk.done[u * kDoneStride], waves, &costs[u]);
+    return left;
 }
 
 // grid = one workgroup per entry of `order` (utterance * 2 + direction: 0 forward, 1 backward).
@@ -2615,6 +2615,16 @@ __device__ __forceinline__ void renew_pairs(LanePairs& s, int frame0, int frame1
     s.scale = __builtin_amdgcn_ldexp(1.0, min(max(neighbour - window, -1100), 1023));
 }
 
+// The thread's index, for parts of a tile's code that a loop goes through again (places that have been left): not known to be
+// the same each time, so that nothing made from it is held in registers from one time to the next.  Without it in these two
+// parts the kernel of 33 to 64 symbols is two registers short, which go to memory.
+__device__ __forceinline__ int tile_thread()
+{
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
 // What a lane knows of its two label positions: the symbols, and where a label may be entered from the one before.
 struct LaneLabels {
     int p0, p1;
@@ -2836,9 +2846,9 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
     }
     file(pending_row, static_cast<float>(pending_alpha0 * pending_beta0), static_cast<float>(pending_alpha1 * pending_beta1));
 }
-// The same from the words that log-domain chains have stored for every frame, kFrames of them at a time: four where the
-// registers are this code's own, one or two in the kernels that share them with block_shares (four there cost a linear-domain
-// call of 512 utterances 1.5 %).  512 utterances in the log domain: 427 us a call with four-byte loads frame by frame, 379 so.
+// The same from the words that log-domain chains have stored for every frame, kFrames of them at a time: two, or one
+// where a second frame's registers would cost the linear domain (512 utterances 0.4 %).  512 utterances in the log domain:
+// 427 us a call with four-byte loads, 379 with both positions' words in one.
 template <int kScaleLog2, int kFrames, typename File>
 __device__ __forceinline__ void block_shares_log(const Utt& m, const LatticeOut& lat, const double packed_inverse_p, const int block,
                                                  const int base, const int own_first, const int own_end, File&& file)
@@ -2933,7 +2943,7 @@ __device__ __forceinline__ void share_product(float4v (&acc)[kTiles], const unsi
                                               const unsigned* s_label, int base, int L, const unsigned (&symbol)[kTiles],
                                               const unsigned (&mask)[kTiles])
 {
-    const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+    const int lane = tile_thread() & 63, c = lane & 15, g = lane >> 4;
     for (int k0 = base; k0 < min(L, base + kPiecePositions); k0 += 32) {
         const int at = c * kShareRow + (k0 - base) / 2 + 4 * g;
         const half8 hi = __builtin_bit_cast(half8, *reinterpret_cast<const uint4v*>(s_hi + at));
@@ -2965,6 +2975,7 @@ struct TileArgs {
     const int* domain;
     const int* links;             // wide
     int* done;                    // lattice launch: what to wait for
+    int* left;                    // ... and, per workgroup, who has left before it (chains_taken)
     int end_polls;                // ... and how often to look before giving up
     const int* by_end;            // ... the utterances, those first whose chains end first
     int T, B, A, blank, Lmax;
@@ -2985,7 +2996,7 @@ __device__ __forceinline__ void store_gradient(const TileArgs& g, size_t i, floa
 __device__ __forceinline__ bool wait_for_chains(const TileArgs& g, int b, int frames)
 {
     __shared__ int s_ended;
-    if (threadIdx.x < 64) {
+    if (tile_thread() < 64) {
         int* const done = &g.done[b * kDoneStride];
         auto look = [&]() { return chains_ended(__builtin_amdgcn_readfirstlane(published(done))); };
         int64_t polls = g.end_polls > 0 ? g.end_polls + 4 * static_cast<int64_t>(frames) : 0;
@@ -2996,11 +3007,11 @@ __device__ __forceinline__ bool wait_for_chains(const TileArgs& g, int b, int fr
         }
         if (!ended) {
             int word = 0;
-            if (threadIdx.x == 0) word = __hip_atomic_fetch_or(done, kWaitGivenUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (tile_thread() == 0) word = __hip_atomic_fetch_or(done, kWaitGivenUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             ended = chains_ended(__builtin_amdgcn_readfirstlane(word));
-            if (!ended && threadIdx.x == 0) publish(&g.costs[b], __uint_as_float(0x7FC00000u));
+            if (!ended && tile_thread() == 0) publish(&g.costs[b], __uint_as_float(0x7FC00000u));
         }
-        if (threadIdx.x == 0) s_ended = ended;
+        if (tile_thread() == 0) s_ended = ended;
     }
     __syncthreads();
     return __builtin_amdgcn_readfirstlane(s_ended) != 0;
@@ -3008,15 +3019,11 @@ __device__ __forceinline__ bool wait_for_chains(const TileArgs& g, int b, int fr
 
 // Workgroup `group` of utterance b: kRowThreads / 64 wavefronts, ceil(blocks of T / (4 / wavefronts per block)) workgroups;
 // LDS 4 tile_lds_ints(Lmax, kTiles) ints.  kTiles: tiles of 16 symbols.
-// Which utterances' tiles: a launch of its own takes any; in the lattice launch those of log-domain chains, hardly ever met, are
-// a function of their own (log_tile), which leaves the registers of the common way alone.
-enum class TileOf { kAny, kLinear, kLog };
-template <int kTiles, bool kWait, TileOf kOf>
-__device__ __forceinline__ bool narrow_tile(const TileArgs& g_args, const Utt* __restrict__ meta, const int* __restrict__ labels,
+template <int kTiles, bool kWait>
+__device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* __restrict__ meta, const int* __restrict__ labels,
                                             const double* __restrict__ emit_blank64, const float* __restrict__ emit_label,
                                             const LatticeOut& lat, uint4v* tile_lds, const int b, const int group)
 {
-    constexpr bool kPublished = kOf != TileOf::kAny;     // (in the launch of the chains)
     const int Tt = g_args.T, B = g_args.B, A = g_args.A, blank = g_args.blank, Lmax = g_args.Lmax;
     const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -3035,7 +3042,7 @@ __device__ __forceinline__ bool narrow_tile(const TileArgs& g_args, const Utt* _
         // (the barriers below)
         if (kWait && runs && first_block * kBlockFrames < m.Tb) __syncthreads();
         if (sharing > 1) __syncthreads();
-        return true;
+        return;
     }
     unsigned* const s_hi = reinterpret_cast<unsigned*>(tile_lds) + wave * tile_lds_ints(Lmax, kTiles);
     unsigned* const s_lo = s_hi + kBlockFrames * kShareRow;
@@ -3057,9 +3064,9 @@ __device__ __forceinline__ bool narrow_tile(const TileArgs& g_args, const Utt* _
     bool log_domain = false;
     double packed_inverse_p = 0.0;
     auto load_ends = [&]() {
-        ends = BlockEnds::load<kPublished>(m, lat, first_labels.p0, block);
-        log_domain = in_log_domain<kPublished>(g_args.domain, b);
-        packed_inverse_p = kPublished ? published(&g_args.logp[b]) : g_args.logp[b];
+        ends = BlockEnds::load<kWait>(m, lat, first_labels.p0, block);
+        log_domain = in_log_domain<kWait>(g_args.domain, b);
+        packed_inverse_p = kWait ? published(&g_args.logp[b]) : g_args.logp[b];
         if (group == 0 && threadIdx.x == 0 && published(&g_args.chain_err[b]) != 0) publish(&g_args.costs[b], __uint_as_float(0x7FC00000u));
     };
     if (!kWait) load_ends();
@@ -3080,12 +3087,12 @@ __device__ __forceinline__ bool narrow_tile(const TileArgs& g_args, const Utt* _
     if (kWait) {
         if (!wait_for_chains(g_args, b, m.Tb)) {
             if (part == 0) zero_rows();
-            return true;
+            if (sharing > 1) __syncthreads();            // (as many barriers as in the other ways out)
+            return;
         }
         load_ends();
     }
-    if (kOf == TileOf::kLinear && log_domain) return false;
-    if (kOf == TileOf::kLog) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    if (kWait && log_domain) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     // the symbol of this lane's column, per tile of symbols: label bytes are compared as (byte & mask) ^ symbol == 0
     unsigned symbol[kTiles], mask[kTiles];
     float4v acc[kTiles];
@@ -3103,13 +3110,13 @@ __device__ __forceinline__ bool narrow_tile(const TileArgs& g_args, const Utt* _
             s_hi[row * kShareRow + lane] = __builtin_bit_cast(unsigned, hi);
             s_lo[row * kShareRow + lane] = __builtin_bit_cast(unsigned, lo);
         };
-        if (kOf == TileOf::kLog || (kOf == TileOf::kAny && log_domain)) {
-            block_shares_log<kShareScaleLog2, kOf == TileOf::kLog ? 4 : 1>(m, lat, packed_inverse_p, block, base, own_first, own_end, file);
+        if (log_domain) {
+            block_shares_log<kShareScaleLog2, 1>(m, lat, packed_inverse_p, block, base, own_first, own_end, file);
         } else {
             LaneLabels at = first_labels;
             if (base != first_base) {
                 at = LaneLabels(labels + m.lab_off, L, base);
-                ends = BlockEnds::load<kPublished>(m, lat, at.p0, block);
+                ends = BlockEnds::load<kWait>(m, lat, at.p0, block);
             }
             auto emissions = [&](int h, float (&el0)[kChunk], float (&el1)[kChunk]) {
                 auto row = [&](bool has, int symbol, float (&el)[kChunk]) {
@@ -3137,7 +3144,7 @@ __device__ __forceinline__ bool narrow_tile(const TileArgs& g_args, const Utt* _
 #pragma unroll
             for (int n = 0; n < kTiles; ++n) s_acc[n * 64 + lane] = acc[n];
         __syncthreads();
-        if (part > 0) return true;
+        if (part > 0) return;
         for (int i = 1; i < sharing; ++i) {
             const float4v* const theirs = reinterpret_cast<const float4v*>(s_hi + i * tile_lds_ints(Lmax, kTiles));
 #pragma unroll
@@ -3165,7 +3172,6 @@ __device__ __forceinline__ bool narrow_tile(const TileArgs& g_args, const Utt* _
     };
     if (g_args.bf16) write(static_cast<bf16_t*>(g_args.grads));
     else write(static_cast<float*>(g_args.grads));
-    return true;
 }
 
 // grid (workgroups per utterance, B)
@@ -3176,7 +3182,7 @@ void ctc_gradient_narrow_kernel(const TileArgs args, const Utt* __restrict__ met
                                 const LatticeOut lat)
 {
     extern __shared__ uint4v tile_lds[];
-    narrow_tile<kTiles, false, TileOf::kAny>(args, meta, labels, emit_blank64, emit_label, lat, tile_lds, blockIdx.y, blockIdx.x);
+    narrow_tile<kTiles, false>(args, meta, labels, emit_blank64, emit_label, lat, tile_lds, blockIdx.y, blockIdx.x);
 }
 
 // Larger alphabets: the softmax launch has written y (and zeros); here the columns of the label's symbols and the
@@ -3318,25 +3324,33 @@ void ctc_gradient_wide_kernel(const TileArgs g, const Utt* __restrict__ meta, co
 // A workgroup waits for chains that are under way, never for one that has yet to be given a compute unit: the order of the
 // workgroups says nothing about that.  Each die hands out its share of a launch by itself, and two such launches on two
 // streams can fill one die with workgroups that wait for chains which the other launch's keep from the other die, and the
-// other way round.  So a chain is taken, in its word, by the workgroup that runs it: its own one, or, should that not come
-// within a moment, one of the gradient that would wait for it; its own one then finds nothing left to do.  A chain that is
-// taken waits for nothing outside its workgroup, so it ends, and so does every wait.
-// (English minibatch: 56.9 us without the look, which cannot be trusted, 57.3 with it.)
-constexpr int kTakePolls = 32;            // about 40 us: a chain's own workgroup takes it within 5 in a launch alone on the chip
+// other way round.  So a chain's workgroup says that it is there (take_chain), and one of the gradient looks for that first.
+// If it takes too long, it leaves its place to the chains' workgroups and makes room: the second of them, which knows that
+// nobody leaves any more, takes the places on the list when its own chain has ended.  It waits for the first one's chain, and
+// that waits for nothing outside its workgroup, so it ends, and so does every wait.
+// (Waiting workgroups that run such a chain themselves need its code a second time: inlined 1 to 5 us of 57 for everybody, in a
+// function a stack, for which the runtime takes 92 MB of device memory and 280 MB more over further queues.  English minibatch:
+// 56.6 us without the look at the word, which cannot be trusted, 56.7 with it.)
+constexpr int kLeavePolls = 1 << 10;      // about a millisecond: a chain's workgroup is there within 5 us in a launch alone on the chip
 
-// By each wavefront of a workgroup, alike: both chains of utterance b have to be taken before the gradient's workgroup `tile`
-// waits for them.  Returns the chain that this workgroup is to run because nobody else has taken it in time, -1 when there is
-// no such chain (any more: `ran`, the directions it has run already, as bits).  The words are written once, so that all
-// wavefronts come to the same answer whenever they look.
-__device__ __forceinline__ int chain_to_take(const TileArgs& g, int b, int tile, int ran)
+// By each wavefront of a workgroup, alike: waits until both chains of utterance b have a workgroup.  False: that took too long,
+// and the place, `tile`, has been left.  (Bits and list only ever grow, and nobody joins the list once both chains are taken: all
+// wavefronts come to the same answer whenever they look.)
+__device__ __forceinline__ bool chains_taken(const TileArgs& g, int b, int tile)
 {
-    int* const words = &g.done[b * kDoneStride + kTakenWord];
-    for (int polls = kTakePolls;; --polls) {
-        const int by_whom[2] = {__builtin_amdgcn_readfirstlane(published(&words[0])), __builtin_amdgcn_readfirstlane(published(&words[1]))};
-        for (int d = 0; d < 2; ++d)
-            if (by_whom[d] == kTakenByTile + tile && !(ran >> d & 1)) return 2 * b + d;
-        if (by_whom[0] != 0 && by_whom[1] != 0) return -1;
-        if (polls <= 0 && threadIdx.x == 0) take_chain(&words[by_whom[0] == 0 ? 0 : 1], kTakenByTile + tile);
+    int* const word = &g.done[b * kDoneStride + kTakenWord];
+    for (int polls = kLeavePolls;; --polls) {
+        const int now = __builtin_amdgcn_readfirstlane(published(word));
+        for (int i = now >> kLeftShift; i != 0; i = __builtin_amdgcn_readfirstlane(published(&g.left[i - 1])))
+            if (i - 1 == tile) return false;
+        if ((now & kBothTaken) == kBothTaken) return true;
+        if (polls <= 0 && threadIdx.x == 0) {
+            publish(&g.left[tile], now >> kLeftShift);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            int expected = now;
+            __hip_atomic_compare_exchange_strong(word, &expected, (now & kBothTaken) | (tile + 1) << kLeftShift, __ATOMIC_RELAXED,
+                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
         __builtin_amdgcn_s_sleep(10);
     }
 }
@@ -3357,31 +3371,13 @@ struct FusedArgs {
     LaunchWords wk;
     TileArgs tiles;
 };
-// What is hardly ever needed has functions of its own, which leave the registers of the common way alone: a chain that this
-// workgroup has taken from another (inlined, it cost the common way 1 to 5 us of 57), or that runs in the log domain, and the
-// tiles of such chains.  `args` points to the launch's FusedArgs.
-typedef __attribute__((address_space(3))) void* LdsPointer;
-__device__ __forceinline__ const FusedArgs& fused_args(uint64_t args)
+// Read again from there: nothing of it is kept in registers from before.
+__device__ __forceinline__ const FusedArgs& fused_args()
 {
     typedef __attribute__((address_space(4))) const FusedArgs* ArgsPointer;
-    const uint64_t lo = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(args)));
-    const uint64_t hi = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(args >> 32)));
-    return *(const FusedArgs*)reinterpret_cast<ArgsPointer>(hi << 32 | lo);
-}
-template <Sync kSync>
-__device__ __attribute__((noinline)) void run_taken_chain(uint64_t args, int chain, LdsPointer lds)
-{
-    const FusedArgs& a = fused_args(args);
-    if (kSync != Sync::kNone || threadIdx.x < 64)
-        lattice_body<kSync, Mode::kGrad, true>(__builtin_amdgcn_readfirstlane(chain), a.meta, a.labels, a.emit_blank, a.emit_blank64,
-                                               a.emit_label, a.lat, a.logp, a.costs, a.chain_err, a.sink, (void*)lds, a.wk, true);
-}
-template <int kTiles>
-__device__ __attribute__((noinline)) void log_tile(uint64_t args, int b, int group, LdsPointer lds)
-{
-    const FusedArgs& a = fused_args(args);
-    narrow_tile<kTiles, false, TileOf::kLog>(a.tiles, a.meta, a.labels, a.emit_blank64, a.emit_label, a.lat, (uint4v*)lds,
-                                             __builtin_amdgcn_readfirstlane(b), __builtin_amdgcn_readfirstlane(group));
+    ArgsPointer args = (ArgsPointer)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    return *(const FusedArgs*)args;
 }
 
 template <Sync kSync, int kTiles>
@@ -3394,29 +3390,28 @@ void ctc_lattice_gradient_kernel(const Utt* __restrict__ meta, const int* __rest
 {
     extern __shared__ uint4v fused_lds[];
     const int index = static_cast<int>(blockIdx.x);
-    auto args = []() { return (uint64_t)__builtin_amdgcn_kernarg_segment_ptr(); };
     if (index < tiles.first_group) {
-        if (kSync == Sync::kNone && threadIdx.x >= 64) return;
         __builtin_amdgcn_s_setprio(3);
-        if (lattice_body<kSync, Mode::kGrad, true, false>(order[index], meta, labels, emit_blank, emit_blank64, emit_label, lat, logp,
-                                                          costs, chain_err, sink, fused_lds, wk))
-            run_taken_chain<kSync>(args(), order[index], (LdsPointer)fused_lds);
+        int left = lattice_body<kSync, Mode::kGrad, true>(order[index], meta, labels, emit_blank, emit_blank64, emit_label, lat, logp,
+                                                          costs, chain_err, sink, fused_lds, wk);
+        if (__builtin_expect(left == 0, 1) || threadIdx.x >= kRowThreads) return;
+        __builtin_amdgcn_s_setprio(0);
+        do {
+            __syncthreads();
+            const FusedArgs& a = fused_args();
+            const int tile = left - 1, rank = tile / a.tiles.groups, b = __builtin_amdgcn_readfirstlane(a.tiles.by_end[rank]);
+            narrow_tile<kTiles, true>(a.tiles, a.meta, a.labels, a.emit_blank64, a.emit_label, a.lat, fused_lds, b, tile - rank * a.tiles.groups);
+            left = __builtin_amdgcn_readfirstlane(published(&a.tiles.left[tile]));
+        } while (left != 0);
     } else {
         const int tile = index - tiles.first_group, rank = tile / tiles.groups, group = tile - rank * tiles.groups;
         const int b = __builtin_amdgcn_readfirstlane(tiles.by_end[rank]);
         const int flags = __builtin_amdgcn_readfirstlane(meta[b].flags), frames = __builtin_amdgcn_readfirstlane(meta[b].Tb);
         const int sharing = tiles.share_blocks ? block_waves(__builtin_amdgcn_readfirstlane(meta[b].L)) : 1;
-        if ((flags & kUttRuns) && group * (kRowThreads / 64 / sharing) * kBlockFrames < frames) {
-            int ran = 0, chain;
-            while (__builtin_expect((chain = chain_to_take(tiles, b, tile, ran)) >= 0, 0)) {
-                run_taken_chain<kSync>(args(), chain, (LdsPointer)fused_lds);
-                ran |= 1 << (chain & 1);
-                __syncthreads();
-            }
-        }
         if (threadIdx.x >= kRowThreads) return;          // (workgroups as large as the longest label's chains)
-        if (!narrow_tile<kTiles, true, TileOf::kLinear>(tiles, meta, labels, emit_blank64, emit_label, lat, fused_lds, b, group))
-            log_tile<kTiles>(args(), b, group, (LdsPointer)fused_lds);
+        const bool waits = (flags & kUttRuns) && group * (kRowThreads / 64 / sharing) * kBlockFrames < frames;
+        if (waits && !chains_taken(tiles, b, tile)) return;
+        narrow_tile<kTiles, true>(tiles, meta, labels, emit_blank64, emit_label, lat, fused_lds, b, group);
     }
 }
 
@@ -3581,6 +3576,7 @@ static TileArgs tile_args(const Launch& p, size_t* lds)
     g.domain = reinterpret_cast<const int*>(p.ws + p.lay.domain);
     g.links = reinterpret_cast<const int*>(p.ws + p.lay.links);
     g.done = reinterpret_cast<int*>(p.ws + p.lay.done);
+    g.left = reinterpret_cast<int*>(p.ws + p.lay.left);
     g.end_polls = p.end_polls;
     g.by_end = reinterpret_cast<const int*>(p.ws + p.lay.order) + 2 * p.B;
     g.T = p.T; g.B = p.B; g.A = p.A; g.blank = p.blank;

@@ -40,7 +40,7 @@ def test_a_wait_that_gives_up_is_reported_as_nan_cost(max_label):
     assert (np.abs(costs - ref_c) <= pc.COST_RTOL * ref_c).all() and np.abs(grads - ref_g).max() <= pc.GRAD_ATOL
 
 
-@pytest.mark.parametrize("percent", [-1, 40, 100])      # of the chains' own workgroups come late: others run the chains
+@pytest.mark.parametrize("percent", [-1, 40, 100])      # of the chains' workgroups come late: others leave them their places
 @pytest.mark.parametrize("dtype", [ctc.DTYPE_F32, ctc.DTYPE_BF16])
 def test_calls_on_two_streams_at_once(percent, dtype):
     """Each of two calls in flight fills the chip with workgroups that wait; both end, with the results each has alone."""
@@ -69,7 +69,7 @@ def test_calls_on_two_streams_at_once(percent, dtype):
 
 @pytest.mark.parametrize("frames,labels", [([16, 9, 3], [4, 0, 3]),                # one block: a single workgroup waits
                                            ([700, 90, 1], [300, 20, 1])])          # several wavefronts a chain
-def test_chains_that_others_run(frames, labels):
+def test_places_left_to_late_chains(frames, labels):
     ctc.debug_set_overlap(100)
     try:
         pc.check(batch_of(frames, labels, 29))

@@ -27,7 +27,7 @@
  *     in one piece by the first call on that device and kept until the process
  *     ends.  A slot is free again once the call's second kernel has run.  No
  *     later call allocates, with two exceptions that each happen once: a batch
- *     whose image (72 bytes per utterance + 4 per label symbol) exceeds a slot
+ *     whose image (76 bytes per utterance + 5 per label symbol) exceeds a slot
  *     gets a pool of larger slots, and a caller with more calls in flight than
  *     there are slots (it enqueues that far ahead of the GPU) gets a pool of
  *     twice as many.  The host never waits for a slot.  Pools stop growing at
@@ -76,15 +76,16 @@ typedef enum {
 /* Kernel launches of one call, in order; index into ctc_profile_kernels' output. */
 enum {
     CTC_KERNEL_SOFTMAX = 0,    /* row-wise log-softmax statistics + emission gather (for alphabets
-                                  wider than 2048 also the dense part of the gradient) */
+                                  wider than 64 also the dense part of the gradient) */
     CTC_KERNEL_LATTICE = 1,    /* alpha and beta recursions, one launch; alphabets of at most 64 symbols: also the
                                   gradient where the batch's lengths make that quicker
                                   (ctc_debug_set_overlap) */
     CTC_KERNEL_GRADIENT = 2,   /* softmax minus normalised occupancy, zero fill of padding */
-    /* A short copy launch (the per-call metadata, from pinned host memory into the workspace)
-       precedes these three and is not timed separately; the grouping of each label's positions
-       by symbol and the costs of degenerate utterances are prepared by extra workgroups of the
-       softmax launch. */
+    /* Alphabets wider than 64 symbols and batches of more than 128 utterances: a short copy launch (the
+       per-call metadata, from pinned host memory into the workspace) precedes these and is not timed
+       separately; otherwise the softmax launch reads that memory itself.  The grouping of each label's
+       positions by symbol (alphabets wider than 64) and the costs of degenerate utterances are prepared
+       by extra workgroups of the softmax launch. */
     CTC_NUM_KERNELS = 3,       /* timed launches of any one call */
     CTC_KERNEL_BACKTRACE = 3   /* name index only: third launch of ctc_best_path (in place of the gradient) */
 };
@@ -125,7 +126,8 @@ ctc_status_t ctc_workspace_size(int T, int B, int A,
  *                 Rows t >= input_lengths[b], and all rows of an utterance with
  *                 infinite cost, are written as zeros.  Must not overlap activations.
  *                 NULL: costs only (the raw CTC cost that Section 5.1 uses as a filter
- *                 feature); the backward recursion and the gradient pass are then left out.
+ *                 feature); the two recursions then take half of the frames each and nothing is
+ *                 stored for a gradient.
  *   workspace     (device) 256-byte aligned scratch of at least ctc_workspace_size bytes;
  *                 contents on entry are irrelevant, contents on exit are unspecified
  *   stream        the stream all work is enqueued on; NULL is the default stream

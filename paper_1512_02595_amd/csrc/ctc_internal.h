@@ -126,8 +126,8 @@ CTC_HOST_DEVICE inline WavePlan plan_waves2(int label_length, bool crowded = fal
 // lane takes about 180 clocks against 120 for a one-pair lane, and a hand-over 560, so while a
 // label's one-pair plan keeps to one wavefront per SIMD (at most 4) it is the faster one; beyond
 // that, and in crowded launches, where wavefront-steps count and not one chain's latency, the
-// two-pair plan with half the wavefronts wins.  Where the emission block is symbol-major
-// (emission_layout) a two-pair lane's fetches are cheap, and the two-pair plan also wins against
+// two-pair plan with half the wavefronts wins.  Where the emission block holds the symbols' rows
+// (kEmitSymbols) a two-pair lane's fetches are cheap, and the two-pair plan also wins against
 // a one-pair plan that hands over every chunk (halo 8): 64 utterances of 600 frames, lattice
 // launch for labels of 215 symbols 52.1 -> 46.5 us, of 230 symbols 52.9 -> 50.1 us; up to 207
 // symbols (halo 16 or more) the one-pair plan stays ahead by up to 4 us.
@@ -443,7 +443,7 @@ struct Layout {
     size_t left = 0;      // int32[B * frame_blocks(T)]  narrow alphabets, gradient beside the chains: the list of workgroups that
                           //              have left their places (chains_taken)
     size_t domain = 0;    // int32[2 B]   per utterance and direction, nonzero: that chain ran in the log domain (published by
-                          //              the chain for the gradient, which must know where its exponent rows are)
+                          //              the chain for the gradient, which must know what it has stored)
     size_t row_flags = 0; // int32[B * ceil(T / 64)]  narrow alphabets: per 64 frames of an utterance, nonzero if one of
                           //              their emissions is too small for the linear domain (written by the softmax
                           //              launch, one word per workgroup, so that nothing needs clearing beforehand)

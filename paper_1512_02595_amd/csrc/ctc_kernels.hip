@@ -3,16 +3,21 @@
 // Pipeline of one call (appendix "GPU Implementation of CTC Loss Function"; cost of
 // Section 3.3 Eq. (ctc); softmax of Section 3.1; most probable alignment of Section 5.1):
 //   upload    the per-call metadata from pinned host memory into the workspace
-//             (or plan: the same records built on the GPU from device-resident lengths and labels)
+//             (or plan: the same records built on the GPU from device-resident lengths and labels);
+//             alphabets of at most 64 symbols and few utterances: done by the softmax launch itself
 //   setup     per utterance: label positions grouped by symbol (the appendix's one-off
 //             key-value sort, done by counting), degenerate costs; rides in the softmax launch
 //   softmax   per frame row: log2-sum-exp2 of the scaled logits, and the emissions (softmax
 //             outputs) of blank and of every label position, gathered once so that the
-//             recursions read them coalesced (small alphabets: the normalised rows themselves,
-//             stored symbol-major)
+//             recursions read them coalesced (small alphabets: the normalised rows themselves),
+//             in chunks of eight frames a column; larger alphabets: also the gradient but for the
+//             label columns
 //   lattice   alpha and beta recursions, both in one launch, a workgroup per utterance and direction
-//             (cost only: alpha alone; alignment: the max recursion with recorded choices)
-//   gradient  softmax minus the normalised per-symbol occupancy; zero fill of padding
+//             (cost only, and alignment with the max recursion and recorded choices: half of the
+//             frames each, up to where they meet); small alphabets: also the gradient where that
+//             is quicker than a launch of its own
+//   gradient  softmax minus the normalised per-symbol occupancy, from both recursions run once more
+//             between the states that the chains have stored; zero fill of padding
 //             (alignment: the backtrace instead)
 //
 // The recursions run on probabilities, each lane's values in fp64 with an int32 exponent of
@@ -26,7 +31,7 @@
 // (run_chain_log): base-2 logarithms in fp64 (v_exp_f32 / v_log_f32 are base 2, so no scaling
 // multiplies; only the bounded differences that enter them are narrowed to fp32), log(0) a
 // large finite negative number, which keeps every operation NaN-free.
-// Either way the lattice is stored as value words and exponent rows, see "lattice storage".
+// What either leaves for the gradient is described at "lattice storage".
 
 #include <hip/hip_runtime.h>
 
@@ -769,7 +774,7 @@ void ctc_softmax_symbols_kernel(const T* __restrict__ x, Utt* __restrict__ meta,
 // (row_flags: one per kFlagFrames frames of an utterance, written by every workgroup that has rows),
 // which the chains gather when they start.
 // A workgroup takes 64 frames of one utterance, four lanes per frame, so that it has several
-// kilobytes under way; the normalised rows are the emission block, stored symbol-major.
+// kilobytes under way; the normalised rows are the emission block (kEmitSymbols).
 // grid (ceil(T / 64) + parts, B); dynamic LDS 64 * A floats.
 struct NarrowImage {
     const int* words;         // the pinned image: meta, order, labels as they lie in the workspace, then the labels as bytes
@@ -1541,7 +1546,7 @@ __device__ __forceinline__ int lane_frame(int window_top, int own_top)
 // renewal no frame lay more than kSmoothFrames below the frame of the lane below it.  Then one more chunk
 // takes a value down to 2^(kEasyLow - 800) at worst, and up to 3^kChunk times the largest of the nine-pair
 // window in this lane's frame, 2^(kEasyHigh + kChunk * kSmoothFrames + 13): both far inside fp64.  The
-// frames, the scale factors and the exponent rows simply stay what they are.
+// frames and the scale factors simply stay what they are.
 constexpr int kEasyLow = -200, kEasyHigh = 100;
 constexpr int kSmoothFrames = 60;
 // The test, on the high dword of the largest value of a lane (biased exponent in bits 20..30): one

@@ -29,9 +29,10 @@
  *     later call allocates, with two exceptions that each happen once: a batch
  *     whose image (76 bytes per utterance + 5 per label symbol) exceeds a slot
  *     gets a pool of larger slots, and a caller with more calls in flight than
- *     there are slots (it enqueues that far ahead of the GPU) gets a pool of
- *     twice as many.  The host never waits for a slot.  Pools stop growing at
- *     256 MiB per device; a call that then finds every slot in flight returns
+ *     there are slots (it enqueues that far ahead of the GPU) gets a further
+ *     pool of twice as many.  The host never waits for a slot.  Pools stop
+ *     growing at 256 MiB per device (an eighth of that is kept for larger
+ *     images); a call that then finds every slot in flight returns
  *     CTC_STATUS_NOT_READY immediately, with nothing enqueued.
  *     ctc_loss_and_grad_device uses none of this.
  *   - The settings of the ctc_debug_set_ functions, and the calling thread's

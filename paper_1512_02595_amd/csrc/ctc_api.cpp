@@ -175,12 +175,15 @@ namespace {
 // point of Section 4.3.  The host never waits for a slot: when every slot is still in flight
 // (the caller has enqueued that many calls ahead of the GPU), or when a batch's image outgrows
 // the slots, a further pool with twice the slots, or larger ones, is allocated and used from
-// then on (earlier pools are left to drain and are kept, so their total is below the last
-// pool's size); pools of one device stop growing at kMaxStagingBytes, and a call that finds
-// every slot in flight then returns CTC_STATUS_NOT_READY at once.
+// then on (earlier pools serve when the last one is full); pools of one device stop growing at
+// kMaxStagingBytes, the last one with the slots that still fit, and a call that finds every slot
+// in flight then returns CTC_STATUS_NOT_READY at once.  (512 utterances of 95 symbols: about 400 calls
+// ahead of the GPU.  When only the last pool served, and pools doubled or not at all, it was 128, which a
+// caller that enqueues one in 45 us of what takes the GPU 145 reached after 190 calls.)
 constexpr int kInitialSlots = 8;
 constexpr size_t kMinSlotBytes = size_t(256) << 10;
 constexpr size_t kMaxStagingBytes = size_t(256) << 20;
+constexpr size_t kSpareStagingBytes = kMaxStagingBytes / 8;    // of these, left for images larger than any before
 constexpr size_t kFlagBytes = 64;            // the flag word sits in front of the image
 
 struct StagingSlot {
@@ -220,16 +223,17 @@ DeviceStaging* staging_of(int dev)
     return d;
 }
 
-// A new pool of `slots` slots of `slot_bytes` each.  nullptr: past the cap (status_out =
-// NOT_READY) or the allocation failed (HIP_ERROR).
-StagingPool* add_pool(DeviceStaging* d, int slots, size_t slot_bytes, ctc_status_t* status_out)
+// A new pool of `slots` slots of `slot_bytes` each, or of as many as `most` bytes in all leave room for.  nullptr: none
+// (status_out = NOT_READY) or the allocation failed (HIP_ERROR).
+StagingPool* add_pool(DeviceStaging* d, int slots, size_t slot_bytes, size_t most, ctc_status_t* status_out)
 {
-    const size_t stride = kFlagBytes + slot_bytes;
-    const size_t bytes = stride * static_cast<size_t>(slots);
-    if (d->total_bytes + bytes > kMaxStagingBytes) {
+    const size_t stride = kFlagBytes + slot_bytes, room = most - std::min(most, d->total_bytes);
+    slots = static_cast<int>(std::min(static_cast<size_t>(slots), room / stride));
+    if (slots == 0) {
         *status_out = CTC_STATUS_NOT_READY;
         return nullptr;
     }
+    const size_t bytes = stride * static_cast<size_t>(slots);
     void* mem = nullptr;
     if (!record(hipHostMalloc(&mem, bytes, hipHostMallocDefault))) {
         *status_out = CTC_STATUS_HIP_ERROR;
@@ -249,6 +253,20 @@ StagingPool* add_pool(DeviceStaging* d, int slots, size_t slot_bytes, ctc_status
     return pool;
 }
 
+StagingSlot* free_slot(StagingPool* pool)
+{
+    const int n = static_cast<int>(pool->slots.size());
+    for (int k = 0; k < n; ++k) {
+        StagingSlot& slot = pool->slots[static_cast<size_t>((pool->next + k) % n)];
+        if (slot.in_flight && slot.released()) slot.in_flight = false;
+        if (!slot.in_flight) {
+            pool->next = (pool->next + k + 1) % n;
+            return &slot;
+        }
+    }
+    return nullptr;
+}
+
 // Returns a free slot of at least `bytes`, or nullptr with the status to return.  Never waits.
 // Caller holds g_staging_mutex.
 StagingSlot* acquire_slot(size_t bytes, ctc_status_t* status_out)
@@ -262,21 +280,17 @@ StagingSlot* acquire_slot(size_t bytes, ctc_status_t* status_out)
     const size_t want = std::max(kMinSlotBytes, (2 * bytes + 65535) / 65536 * 65536 - kFlagBytes);
     StagingPool* pool = d->pools.empty() ? nullptr : d->pools.back();
     if (pool && bytes <= pool->slot_bytes) {
-        const int n = static_cast<int>(pool->slots.size());
-        for (int k = 0; k < n; ++k) {
-            StagingSlot& slot = pool->slots[static_cast<size_t>((pool->next + k) % n)];
-            if (slot.in_flight && slot.released()) slot.in_flight = false;
-            if (!slot.in_flight) {
-                pool->next = (pool->next + k + 1) % n;
-                return &slot;
-            }
+        for (auto it = d->pools.rbegin(); it != d->pools.rend(); ++it) {
+            if (bytes > (*it)->slot_bytes) continue;
+            if (StagingSlot* slot = free_slot(*it)) return slot;
         }
         // every slot is in flight: the caller runs that far ahead of the GPU
-        pool = add_pool(d, 2 * n, pool->slot_bytes, status_out);
+        pool = add_pool(d, 2 * static_cast<int>(pool->slots.size()), pool->slot_bytes, kMaxStagingBytes - kSpareStagingBytes,
+                        status_out);
     } else if (pool) {
-        pool = add_pool(d, static_cast<int>(pool->slots.size()), want, status_out);     // a larger image than any before
+        pool = add_pool(d, static_cast<int>(pool->slots.size()), want, kMaxStagingBytes, status_out);     // a larger image than any before
     } else {
-        pool = add_pool(d, kInitialSlots, want, status_out);
+        pool = add_pool(d, kInitialSlots, want, kMaxStagingBytes, status_out);
     }
     if (!pool) return nullptr;
     pool->next = 1;

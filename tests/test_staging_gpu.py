@@ -107,3 +107,17 @@ def test_two_threads_on_two_streams():
     for d, (rc, rg) in zip(dbs, refs):
         c, g = d.results()
         assert np.array_equal(c, rc, equal_nan=True) and np.array_equal(g, rg)
+
+
+def test_large_images_far_ahead_of_the_gpu():
+    """260 calls of 512 utterances, whose images outgrow the first slots, enqueued while the stream is held up."""
+    batch = wl.make_random(311, T=220, B=512, A=29, max_label=200, min_input=200, sigma=2.0, feasible_only=True)
+    assert 76 * batch.B + 5 * int(batch.label_lengths.sum()) > 256 << 10
+    db = harness.DeviceBatch(batch)
+    db.run()
+    costs, grads = db.results()
+    torch.cuda._sleep(int(0.05 * 2.0e9))
+    for _ in range(260):
+        db.run()
+    got = db.results()
+    assert np.array_equal(got[0], costs, equal_nan=True) and np.array_equal(got[1], grads)

@@ -71,11 +71,11 @@ void carve(int T, int B, bool narrow, int64_t sumL, int64_t emit, int64_t frames
     l.upload_bytes = off;
     off = align_up(off);
     l.links = off;  off = align_up(off + static_cast<size_t>(sumL) * sizeof(int32_t));
-    l.logp = off;   off = align_up(off + static_cast<size_t>(B) * sizeof(double));
+    l.mass = off;   off = align_up(off + static_cast<size_t>(B) * kMassWords * sizeof(double));
     l.sink = off;   off = align_up(off + static_cast<size_t>(B) * 2 * kSinkWaves * kSinkBytes);
     l.chain_err = off; off = align_up(off + static_cast<size_t>(B) * sizeof(int32_t));
     l.done = off;   off = align_up(off + static_cast<size_t>(B) * kDoneStride * sizeof(int32_t));
-    l.left = off;   off = align_up(off + (narrow ? static_cast<size_t>(B) * frame_blocks(T) * sizeof(int32_t) : 0));
+    l.left = off;   off = align_up(off + (narrow ? static_cast<size_t>(B) * (frame_blocks(T) + 1) * sizeof(int32_t) : 0));
     l.domain = off; off = align_up(off + static_cast<size_t>(B) * 2 * sizeof(int32_t));
     l.row_flags = off;
     off = align_up(off + static_cast<size_t>(B) * ((T + kFlagFrames - 1) / kFlagFrames) * sizeof(int32_t));
@@ -99,17 +99,14 @@ const Plans& plans()
         Plans* p = new Plans();
         for (int crowded = 0; crowded < 2; ++crowded)
             for (int L = 0; L <= CTC_MAX_LABEL_LENGTH; ++L) {
-                const WavePlan one = plan_waves(L, crowded), two = plan_waves2(L, crowded);
-                for (int symbol_major = 0; symbol_major < 2; ++symbol_major) {
-                    const bool pairs = two_pairs_per_lane(L, crowded, symbol_major);
-                    PlanTable& t = p->table[crowded][symbol_major];
-                    t.one[L] = static_cast<uint8_t>((one.waves - 1) | ((one.halo / 8) << 4) | (pairs ? 128 : 0));
-                    t.two[L] = static_cast<uint8_t>((two.waves - 1) | ((two.halo / 4) << 4));
-                    if (!crowded) {
-                        p->latency_waves[symbol_major][L] = static_cast<uint8_t>(pairs ? two.waves : one.waves);
-                        p->latency_waves_up_to[symbol_major][L] =
-                            (L > 0 ? p->latency_waves_up_to[symbol_major][L - 1] : 0) + p->latency_waves[symbol_major][L];
-                    }
+                const WavePlan one = plan_waves(L, crowded), two = linear_plan2(L, crowded);
+                const bool pairs = linear_two_pairs(L, crowded);
+                PlanTable& t = p->table[crowded];
+                t.one[L] = static_cast<uint8_t>((one.waves - 1) | ((one.halo / 8) << 4) | (pairs ? 128 : 0));
+                t.two[L] = static_cast<uint8_t>((two.waves - 1) | ((two.halo / 4) << 4));
+                if (!crowded) {
+                    p->latency_waves[L] = static_cast<uint8_t>(pairs ? two.waves : one.waves);
+                    p->latency_waves_up_to[L] = (L > 0 ? p->latency_waves_up_to[L - 1] : 0) + p->latency_waves[L];
                 }
                 p->most_waves[crowded][L] =
                     static_cast<uint8_t>(std::max({L > 0 ? static_cast<int>(p->most_waves[crowded][L - 1]) : 1, one.waves, two.waves}));
@@ -337,13 +334,12 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
     int32_t* labels = reinterpret_cast<int32_t*>(image + lay.labels);
     uint8_t* labels8 = reinterpret_cast<uint8_t*>(image + lay.labels8);
 
-    const bool symbol_major = emission_layout(c.A) == kEmitSymbols;
     const Plans& all_plans = plans();
     // Would the launch, planned for latency, put more than two wavefronts on every SIMD?
     int64_t latency_waves = 0;
-    for (int b = 0; b < c.B; ++b) latency_waves += all_plans.latency_waves[symbol_major][c.label_lengths[b]];
+    for (int b = 0; b < c.B; ++b) latency_waves += all_plans.latency_waves[c.label_lengths[b]];
     const bool crowded = latency_waves * 2 > kCrowdedWaves;
-    const PlanTable& plan_of = all_plans.table[crowded][symbol_major];
+    const PlanTable& plan_of = all_plans.table[crowded];
 
     // The labels travel as bytes where a symbol fits one and as words otherwise (launch_setup, NarrowImage).
     const bool byte_labels = c.A <= kByteLabelsMaxA;
@@ -384,11 +380,12 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
         m.e_off = e_off;
         m.ab_off = ab_off;
         m.e_direct = emission_layout(c.A);
+        m.rough = 0;
         m.e_cols = m.e_direct == kEmitSymbols ? c.A : L;
         meta[b] = m;
         const int64_t padded = padded_frames(Tb);
         lab_off += L;
-        e_off += symbol_major ? padded * c.A : gathered_emissions(Tb, L);
+        e_off += c.A <= kDirectMaxA ? padded * c.A : gathered_emissions(Tb, L);
         f_off += padded;
         ab_off += lattice_words(Tb, L);
         if (runs) {
@@ -627,11 +624,10 @@ ctc_status_t run_device(const void* x, const int32_t* labels, const int32_t* lab
     p.dtype = dtype;
     p.n_run = B;                       // a lattice workgroup per utterance and direction; those that do not run leave at once
     p.n_chains = B * 2;
-    const bool symbol_major = emission_layout(A) == kEmitSymbols;
     // Would the launch, planned for latency, put more than two wavefronts on every SIMD (prepare's question)?  The
     // labels' lengths are on the GPU; the answer here is for lengths spread evenly up to the bound.
     const Plans& all_plans = plans();
-    p.crowded = static_cast<int64_t>(B) * 2 * all_plans.latency_waves_up_to[symbol_major][max_label] >
+    p.crowded = static_cast<int64_t>(B) * 2 * all_plans.latency_waves_up_to[max_label] >
                 static_cast<int64_t>(kCrowdedWaves) * (max_label + 1);
     p.max_waves = all_plans.most_waves[p.crowded][max_label];
     p.max_frames = T;
@@ -662,7 +658,7 @@ ctc_status_t run_device(const void* x, const int32_t* labels, const int32_t* lab
         // (lengths spread evenly up to the bounds, as above: one utterance in seven ends late, half the frames are frames)
         const double blocks = static_cast<double>(B) * frame_blocks(T);
         const double late = 0.14 * blocks * std::max(1, label_pieces(max_label * 3 / 4)), all = 0.5 * blocks * std::max(1, label_pieces(max_label / 2));
-        p.fused = gradient_beside_chains(std::max(all - late, 0.0), late, T * chain_us_per_frame(all_plans.latency_waves[symbol_major][max_label]),
+        p.fused = gradient_beside_chains(std::max(all - late, 0.0), late, T * chain_us_per_frame(all_plans.latency_waves[max_label]),
                                          p.max_waves, p.n_chains, p.n_cu);
     }
     // Narrow alphabets: the softmax launch builds the records itself (no planning launch before it); every
@@ -920,8 +916,8 @@ long ctc_debug_replay_emission_fetches(int T, int B, int A, const int32_t* label
                 chain_schedule(chunks, fetch, nothing);
             }
             auto fetch = [&](auto, int i) {
-                if (i == 0) return;
-                const int64_t w = blank_emission_offset(m, chain_chunk(i - 1, chunks, backward != 0));
+                if (i < kBlankAhead) return;
+                const int64_t w = blank_emission_offset(m, chain_chunk(i - kBlankAhead, chunks, backward != 0));
                 touch(w, blank_floats);                          // (the block of doubles has the same extent)
                 touch(w + kChunk - 1, blank_floats);
             };

@@ -27,7 +27,8 @@ struct Utt {
     int64_t e_off;     // offset (floats) of its label emissions [chunk][e_cols][kChunk]
     int64_t ab_off;    // offset (8-byte words) of its alpha/beta blocks, lattice_words of them
     int32_t e_cols;    // columns of its emission block: a column per symbol, or one per label position
-    int32_t e_direct;  // which of the two: kEmitGathered or kEmitSymbols (emission_layout)
+    int16_t e_direct;  // which of the two: kEmitGathered or kEmitSymbols (emission_layout)
+    int16_t rough;     // set by the softmax launch when some probability is below 2^kGentleMinLog2
     int32_t waves2;    // the same plan for linear-domain chains of more than 64 pairs, whose lanes own
     int32_t halo2;     // two neighbouring pairs each (plan_waves2)
 };
@@ -138,6 +139,20 @@ CTC_HOST_DEVICE inline bool two_pairs_per_lane(int label_length, bool crowded, b
     return crowded || one.barrier || one.waves > 4 || (symbol_major && one.halo < 2 * kChunkSteps);
 }
 
+// Linear-domain chains hand over at the ends of blocks of 16 frames.  A two-pair plan whose halo lasts for 8 frames only takes
+// one more wavefront; of the one-pair plans, those are never chosen (linear_two_pairs).
+CTC_HOST_DEVICE inline WavePlan linear_plan2(int label_length, bool crowded)
+{
+    WavePlan p = plan_waves2(label_length, crowded);
+    if (p.waves > 1 && p.halo < kChunkSteps) {
+        const int lanes = (label_length + 2) / 2, halo = (64 * (p.waves + 1) - lanes) / p.waves;
+        p.halo = halo > 16 ? 16 : halo - halo % 4;
+        p.waves += 1;
+    }
+    return p;
+}
+CTC_HOST_DEVICE inline bool linear_two_pairs(int label_length, bool crowded) { return two_pairs_per_lane(label_length, crowded, true); }
+
 // The plans of every label length, packed: what a launch that builds its utterance records on the
 // GPU carries in its arguments instead of evaluating plan_waves per utterance there.
 //   one[L]: bits 0..3 wavefronts - 1, bits 4..6 halo / 8 (plan_waves), bit 7 two_pairs_per_lane
@@ -155,9 +170,9 @@ struct PlanTable {
 // (evaluating plan_waves and plan_waves2 for each utterance of a 512-utterance minibatch was most of the
 // launcher's 130 us).
 struct Plans {
-    PlanTable table[2][2];                                      // [crowded][symbol_major]
-    uint8_t latency_waves[2][CTC_MAX_LABEL_LENGTH + 1];         // [symbol_major]: wavefronts of a linear-domain chain planned for latency
-    int latency_waves_up_to[2][CTC_MAX_LABEL_LENGTH + 1];       // ... summed over all lengths up to this one
+    PlanTable table[2];                                         // [crowded]
+    uint8_t latency_waves[CTC_MAX_LABEL_LENGTH + 1];            // wavefronts of a linear-domain chain planned for latency
+    int latency_waves_up_to[CTC_MAX_LABEL_LENGTH + 1];          // ... summed over all lengths up to this one
     uint8_t most_waves[2][CTC_MAX_LABEL_LENGTH + 1];            // [crowded]: most wavefronts of any plan for a label up to this length
     bool barrier[CTC_MAX_LABEL_LENGTH + 1];                     // WavePlan::barrier
 };
@@ -234,6 +249,7 @@ inline double chain_us_per_frame(int waves) { return waves == 1 ? 0.045 : (waves
 constexpr int kDoneStride = 16;      // words between two utterances' words: a line each for those who poll
 constexpr int kTakenWord = 1;        // which of them says that the chains have a workgroup (take_chain; the first is the counter)
 constexpr int kDoneWords = 2;
+constexpr int kMassWords = 4;        // doubles per utterance that its forward chain leaves (see the kernels)
 
 // The sink of a lattice launch: for each of its up to 2 B chain workgroups, kSinkBytes for each of the
 // up to kSinkWaves wavefronts.
@@ -248,14 +264,17 @@ constexpr int kUttLogDomain = 4;
 // Linear-domain chains of this utterance give two neighbouring state pairs to every lane
 // (plan_waves2) instead of one (plan_waves): see two_pairs_per_lane.
 constexpr int kUttTwoPairs = 8;
-constexpr float kLinearMinLog2 = -100.0f;
+constexpr float kLinearMinLog2 = -79.0f;
+// Utterances all of whose probabilities are above this look after their lanes' exponents once a block, others once a chunk.
+constexpr float kGentleMinLog2 = -32.0f;
+constexpr int kRowsSmall = 1, kRowsRough = 2;    // bits of Layout::row_flags: one below kLinearMinLog2, one below kGentleMinLog2
 // Utterances of more frames than this run the log domain whatever their emissions: the lanes'
-// exponents, which fall by up to 100 per frame, must stay clear of kNoExponent and of int32's end.
+// exponents, which fall by up to 79 per frame, must stay clear of kNoExponent and of int32's end.
 constexpr int kLinearMaxFrames = 1 << 21;
 // Utterances with fewer than this many frames to spare (frames - symbols - repeated neighbours) run the log
 // domain too.  Where hardly a frame is to spare the alignments run along the front of the lattice, and the
 // states behind the front, whose mass can no longer reach the end, may outweigh it by more than the lanes'
-// frames of the linear domain hold (lane_frame in the kernels: 2^950 within ten state pairs); with this
+// frames of the linear domain hold (lane_frame in the kernels: 2^760 within nine state pairs); with this
 // many frames to spare every state that near the front can still reach the end.  Measured before the rule:
 // 138 frames, 91 symbols, 47 repeats, emissions down to 2^-95: the front 2^1900 below its neighbours, the
 // linear domain's cost +inf.
@@ -335,7 +354,7 @@ constexpr int kMaxBatch = 65535;         // utterances index the second grid dim
 constexpr int kMaxDeviceMetaB = 4096;   // utterances the device-side planner ranks in LDS
 
 // The lattice kernel reads emissions ahead of the recursion without bounds checks: a chunk's label emissions are
-// requested two chunks before their use (chain_schedule), so up to two chunks past either end of an utterance's
+// requested three chunks before their use (chain_schedule), so up to three chunks past either end of an utterance's
 // block (past the end going forward, before the start going backward).  These margins keep such reads inside the
 // workspace; the values read there are never used.
 constexpr int kChunk = kChunkSteps;   // steps whose emissions are fetched together (plan_waves: halo % 8 == 0)
@@ -385,11 +404,13 @@ CTC_HOST_DEVICE inline int chain_chunks(int frames, bool backward)
 
 // The order in which a chain requests (fetch) and consumes (run) the emissions of its chunks, an even number, in
 // four register sets: set i mod 4 holds chunk i.  fetch(set, i) requests the label emissions of the chain's i-th chunk
-// and the blank's of the one before it (i > 0); run(set, i) runs its eight steps.  The sets' numbers are compile-time
-// constants (std::integral_constant).  A request out of the die's L2 takes longer than the 300 ns of a chunk, hence two
-// chunks ahead; the blank's scalars go out one chunk ahead, two sets of 16 scalar registers being all there is room for.
+// and, in chains that have blank emissions, the blank's of the one kBlankAhead before it; run(set, i) runs its eight steps.  The
+// sets' numbers are compile-time constants (std::integral_constant).  A chunk takes 130 ns and more, a request out of the
+// die's L2 about 300: hence three chunks ahead (two: 1 ns a step more); the blank's scalars go out one chunk ahead, two sets
+// of 16 scalar registers being all there is room for.
 // There is no branch inside a round: the compiler's count of the memory operations in flight stays exact, and a
 // wavefront waits for the emissions it is about to use only, not for stores.
+constexpr int kBlankAhead = 2;
 template <typename Fetch, typename Run>
 CTC_HOST_DEVICE inline void chain_schedule(int chunks, Fetch&& fetch, Run&& run)
 {
@@ -399,19 +420,20 @@ CTC_HOST_DEVICE inline void chain_schedule(int chunks, Fetch&& fetch, Run&& run)
     const std::integral_constant<int, 3> d{};
     fetch(a, 0);
     fetch(b, 1);
+    fetch(c, 2);
     int i = 0;
     for (; i + 4 <= chunks; i += 4) {
-        fetch(c, i + 2);
-        run(a, i);
         fetch(d, i + 3);
-        run(b, i + 1);
+        run(a, i);
         fetch(a, i + 4);
-        run(c, i + 2);
+        run(b, i + 1);
         fetch(b, i + 5);
+        run(c, i + 2);
+        fetch(c, i + 6);
         run(d, i + 3);
     }
     if (i < chunks) {
-        fetch(c, i + 2);
+        fetch(d, i + 3);                                 // (for the blank's of the last chunk)
         run(a, i);
         run(b, i + 1);
     }
@@ -435,12 +457,12 @@ struct Layout {
     size_t labels = 0;    // int32[sumL]
     size_t labels8 = 0;   // uint8[sumL]  the label strings once more, a byte per symbol (image only; narrow alphabets)
     size_t links = 0;     // int32[sumL]  grouping of the label positions by symbol (slot, count, first)
-    size_t logp = 0;      // double[B]    log2 of the alignment mass
+    size_t mass = 0;      // double[kMassWords B]  the alignments' mass of each utterance
     size_t sink = 0;      // what lanes with nothing to store scribble on: kSinkBytes per wavefront of a lattice launch
     size_t chain_err = 0; // int32[B]     set when a lattice wavefront gave up waiting for its neighbour
     size_t done = 0;      // int32[B * kDoneStride]  how far the utterance's chains are: cost-only calls (finish_loss)
                           //              and gradients written beside the chains (announce_end, take_chain)
-    size_t left = 0;      // int32[B * frame_blocks(T)]  narrow alphabets, gradient beside the chains: the list of workgroups that
+    size_t left = 0;      // int32[B * (frame_blocks(T) + 1)]  narrow alphabets, gradient beside the chains: the list of workgroups that
                           //              have left their places (chains_taken)
     size_t domain = 0;    // int32[2 B]   per utterance and direction, nonzero: that chain ran in the log domain (published by
                           //              the chain for the gradient, which must know what it has stored)
@@ -449,12 +471,12 @@ struct Layout {
                           //              launch, one word per workgroup, so that nothing needs clearing beforehand)
     size_t status = 0;    // int32[B]     device-resident metadata, records built by the narrow softmax launch: nonzero
                           //              if the utterance's lengths or labels are invalid
-    size_t emit_blank = 0; // float[slack + sum padded_frames(Tb) + slack]  emission of blank per frame: the probability y, or
-                           // log2 y (negative) where y < 2^kLinearMinLog2 (plain log2 y in launches for
-                           // the most probable alignment)
-    size_t emit_blank64 = 0; // double[slack + sum padded_frames(Tb) + slack]  the blank's probability once more, for the scalar loads of
-                             // the linear-domain chains
-    size_t emit_label = 0; // float[slack + sum gathered_emissions + slack]  emission of each label position, same coding
+    size_t emit_blank = 0; // float[slack + sum padded_frames(Tb) + slack]  a word per frame: its norm, the blank's probability, which the
+                           // label emissions are divided by (FrameNorm in the kernels)
+    size_t emit_blank64 = 0; // double[slack + sum padded_frames(Tb) + slack]  launches for the most probable alignment: the blank's
+                             // log2 probability per frame, for scalar loads
+    size_t emit_label = 0; // float[slack + sum gathered_emissions + slack]  emission of each label position, the ratio of
+                           // its probability to the blank's (encode_emission)
                            // (padded_frames(Tb)*A for small alphabets: emission_layout); the front slack starts with
                            // the constants that lanes without a label state read: probability 0 and log 0
     size_t alpha = 0;      // 8-byte words [sum lattice_words] (lattice storage, see the kernels)

@@ -21,11 +21,11 @@
 //             (alignment: the backtrace instead)
 //
 // The recursions run on probabilities, each lane's values in fp64 with an int32 exponent of
-// the lane's own (its "frame") that is renewed every kChunk steps: no transcendentals and a
-// third of the instructions of the log-space form (run_chain_linear, run_chain_linear2).
+// the lane's own (its "frame"), relative to the blank's: no transcendentals and a
+// fifth of the instructions of the log-space form (run_chain_linear, run_chain_linear2).
 // alpha and beta span thousands of binary orders of magnitude over a 15 s utterance, and the
 // states that carry the mass lie a thousand orders below the largest of their frame, so the
-// exponent has to be per lane; fp64 then leaves room for the kChunk steps between renewals.
+// exponent has to be per lane; fp64 then leaves room for the steps until it is looked after.
 // Utterances with an emission below 2^kLinearMinLog2 (found by the softmax launch), launches
 // of the barrier kernel and the maximum recursion use the log-space form instead
 // (run_chain_log): base-2 logarithms in fp64 (v_exp_f32 / v_log_f32 are base 2, so no scaling
@@ -273,16 +273,17 @@ void ctc_plan_kernel(const int* __restrict__ labels, const int* __restrict__ lab
         m.lab_off = b * max_label;
         m.flags = (runs ? kUttRuns : 0) | (bad ? kUttInvalid : 0) |
                   ((log_domain || Tb > kLinearMaxFrames || tight_fit(Tb, L, rep)) ? kUttLogDomain : 0) |
-                  (!bad && two_pairs_per_lane(L, crowded, emission_layout(A) == kEmitSymbols) ? kUttTwoPairs : 0);
+                  (!bad && linear_two_pairs(L, crowded) ? kUttTwoPairs : 0);
         const int padded = static_cast<int>(padded_frames(Tt)), longest = longest_aligned(Tt, max_label);
         m.f_off = static_cast<unsigned>(b) * padded;
         m.waves = wp.waves;
         m.halo = wp.halo;
-        const WavePlan wp2 = plan_waves2(bad ? 0 : L, crowded);
+        const WavePlan wp2 = linear_plan2(bad ? 0 : L, crowded);
         m.waves2 = wp2.waves;
         m.halo2 = wp2.halo;
         m.poll_budget = poll_budget;
         m.e_direct = emission_layout(A);
+        m.rough = 0;
         m.e_cols = m.e_direct == kEmitSymbols ? A : m.L;
         m.e_off = b * (m.e_direct == kEmitSymbols ? static_cast<int64_t>(padded) * A : gathered_emissions(Tt, longest));
         m.ab_off = b * lattice_words(Tt, longest);
@@ -403,19 +404,43 @@ __device__ __forceinline__ void setup_words(const Utt m, const int b, const Setu
 }
 
 // ---- emission coding -------------------------------------------------------------------------
-// The recursions run on probabilities (linear domain, see run_chain_linear) unless some
-// emission of the utterance is too small for that; an emission is therefore stored as the
-// probability y = 2^lp itself, or, where lp < kLinearMinLog2, as lp (a negative float, which
-// no probability is).  A lane that stores such a value raises the utterance's kUttLogDomain
-// flag, and its chains then take log2 of the stored probabilities instead.
+// The recursions run on probabilities (linear domain, see run_chain_linear) relative to the blank's: every frame is divided
+// by its blank's probability y_blank, its *norm*, so that a step has no multiplication for the blank states and a chain no
+// blank emissions to fetch.  Shares alpha beta / p do not change (p is divided by the same product of norms), and the cost
+// gets the norms back at the end (Norms).
+//   label emission v >= 0: the ratio y / y_blank; v < 0: log2 of it, where y < 2^kLinearMinLog2
+//   word of the frame c >= 0: the norm y_blank; c < 0: the norm is 1, y_blank is 2^(c + 1) (below 2^kLinearMinLog2) and the
+//   frame's label emissions are y itself, or log2 y
+// A ratio is the quotient of the two rounded probabilities to within an ulp, so what the norms give back is what was taken.
+// A lane that stores a negative word raises the utterance's kUttLogDomain flag, and its chains then take logarithms.
 // (The most probable alignment has no sums to speed up: its launches store plain logarithms.)
-__device__ __forceinline__ float encode_emission(float lp, bool& small, bool plain_logs)
+struct FrameNorm {
+    float log_blank, blank, inverse;                     // log2 y_blank, y_blank, about 1 / y_blank
+    bool small;                                          // the norm is 1
+    // From the blank's logit, the row's largest one, and the sum of 2^((x - max) log2 e) and its logarithm.  y_blank as a quotient:
+    // where a frame is nearly certain of its blank, the exponential of log2 y_blank would be off by an ulp or two of 1.
+    __device__ __forceinline__ FrameNorm(float x, float row_max, float sum, float log2_sum)
+    {
+        log_blank = log2_softmax(x, row_max, log2_sum);
+        const float about = __builtin_amdgcn_rcpf(sum), inverse_sum = fmaf(fmaf(-sum, about, 1.0f), about, about);
+        blank = fast_exp2((x - row_max) * kLog2e) * inverse_sum;
+        inverse = __builtin_amdgcn_rcpf(blank);
+        small = log_blank < kLinearMinLog2;
+    }
+    __device__ __forceinline__ float word() const { return small ? log_blank - 1.0f : blank; }
+};
+// The emission of a symbol whose log2 y is lp.
+__device__ __forceinline__ float encode_emission(float lp, const FrameNorm& f)
 {
-    if (plain_logs) return lp;
-    if (lp >= kLinearMinLog2) return fast_exp2(lp);
-    small = true;
-    return lp;
+    const float y = fast_exp2(lp), q = y * f.inverse;
+    const float ratio = fmaf(fmaf(-q, f.blank, y), f.inverse, q);
+    return lp < kLinearMinLog2 ? (f.small ? lp : lp - f.log_blank) : (f.small ? y : ratio);
 }
+__device__ __forceinline__ float encode_blank(const FrameNorm& f) { return f.small ? f.log_blank : 1.0f; }
+// From a frame's word.
+__device__ __forceinline__ float frame_norm(float c) { return c < 0.0f ? 1.0f : c; }
+__device__ __forceinline__ float blank_emission_log2(float c) { return c < 0.0f ? c + 1.0f : 0.0f; }
+__device__ __forceinline__ float blank_softmax(float c) { return c < 0.0f ? fast_exp2(c + 1.0f) : c; }
 // log2 of a coded emission in two floats whose sum it is: the binary exponent of a stored probability
 // and the logarithm of its mantissa.  (As one float the logarithm of 2^-40 would be good to 4e-6 only,
 // frame after frame; a chain of 400 steps then misses the gradient's bound.)
@@ -433,19 +458,18 @@ __device__ __forceinline__ double emission_log2(float v)
     const Log2Parts p = emission_log2_parts(v);
     return static_cast<double>(p.whole) + static_cast<double>(p.part);
 }
-__device__ __forceinline__ float emission_probability(float v) { return fmaxf(v, 0.0f); }
-// A softmax output from its coded emission.
-__device__ __forceinline__ float emission_softmax(float v) { return v < 0.0f ? fast_exp2(v) : v; }
+// A softmax output from its emission and the frame's norm.
+__device__ __forceinline__ float emission_softmax(float v, float norm) { return (v < 0.0f ? fast_exp2(v) : v) * norm; }
 // Emissions of virtual frames (emission_layout in the launcher's header): blank with probability 1, labels with 0.
 __device__ __forceinline__ float virtual_emission(bool blank, bool plain_logs)
 {
     return plain_logs ? (blank ? 0.0f : static_cast<float>(kNeg)) : (blank ? 1.0f : 0.0f);
 }
-// The blank's emission of one padded frame, in both forms.
+// The blank's emission of one padded frame: the frame's word, or (plain_logs) log2 y_blank, which is wanted as fp64 scalars.
 __device__ __forceinline__ void store_blank(float* __restrict__ emit_blank, double* __restrict__ emit_blank64, size_t frame, float e, bool plain_logs)
 {
-    emit_blank[kBlankSlack + frame] = e;
-    emit_blank64[kBlankSlack + frame] = static_cast<double>(plain_logs ? e : emission_probability(e));
+    if (plain_logs) emit_blank64[kBlankSlack + frame] = static_cast<double>(e);
+    else emit_blank[kBlankSlack + frame] = e;
 }
 // Where the emission of column `column` in frame `t` of an utterance sits.
 __device__ __forceinline__ size_t emission_at(int64_t e_off, int columns, int t, int column)
@@ -468,6 +492,12 @@ __device__ __forceinline__ void store_virtual_frames(const Utt& m, float* __rest
 __device__ __forceinline__ void raise_log_domain(Utt* meta, int b, const Utt& m, bool small)
 {
     if (small) meta[b].flags = m.flags | kUttLogDomain;
+}
+
+// The same for one with a probability below 2^kGentleMinLog2.
+__device__ __forceinline__ void raise_rough(Utt* meta, int b, bool rough)
+{
+    if (rough) meta[b].rough = 1;
 }
 
 // ---- softmax statistics + emission gather --------------------------------------------------
@@ -574,17 +604,22 @@ void ctc_softmax_rows_kernel(const T* __restrict__ x, T* __restrict__ grads, Utt
     }
 
     // the emissions, out of the row that the caches still hold
-    bool small = false;
+    const FrameNorm norm(load_elem(row, blank), mx, sum, ls);
+    bool small = false, rough = norm.log_blank < kGentleMinLog2;
     if (q == 0) {
-        const float e = encode_emission(log2_softmax(load_elem(row, blank), mx, ls), small, sa.plain_logs);
-        store_blank(emit_blank, sa.emit_blank64, static_cast<size_t>(m.f_off) + t, e, sa.plain_logs);
+        store_blank(emit_blank, sa.emit_blank64, static_cast<size_t>(m.f_off) + t, sa.plain_logs ? norm.log_blank : norm.word(), sa.plain_logs);
+        small = !sa.plain_logs && norm.small;
     }
     float* const erow = emit_label + emission_at(m.e_off, m.L, t, 0);
     for (int j = q; j < m.L; j += kLanes) {
         const int c = j == q ? c_first : lab[j];
-        erow[static_cast<size_t>(j) * kChunk] = encode_emission(log2_softmax(load_elem(row, c), mx, ls), small, sa.plain_logs);
+        const float lp = log2_softmax(load_elem(row, c), mx, ls), e = sa.plain_logs ? lp : encode_emission(lp, norm);
+        erow[static_cast<size_t>(j) * kChunk] = e;
+        small = small || (!sa.plain_logs && e < 0.0f);
+        rough = rough || lp < kGentleMinLog2;
     }
     if (t == m.Tb - 1) store_virtual_frames(m, emit_blank, sa.emit_blank64, emit_label, sa.plain_logs, q, kLanes);
+    raise_rough(meta, b, rough);
     raise_log_domain(meta, b, m, small);
 }
 
@@ -616,25 +651,31 @@ void ctc_softmax_kernel(const T* __restrict__ x, T* __restrict__ grads,
     float mx = -__builtin_inff();
     for (int k = threadIdx.x; k < A; k += kRowThreads) mx = fmaxf(mx, load_elem(row, k));
     mx = block_max(mx, red);
-    float s = 0.0f;
+    float sum = 0.0f;
     for (int k = threadIdx.x; k < A; k += kRowThreads)
-        s += fast_exp2((load_elem(row, k) - mx) * kLog2e);
-    s = block_sum(s, red + 4);
-    const float ls = fast_log2(s);
+        sum += fast_exp2((load_elem(row, k) - mx) * kLog2e);
+    sum = block_sum(sum, red + 4);
+    const float ls = fast_log2(sum);
 
     if (grads)
         for (int k = threadIdx.x; k < A; k += kRowThreads)
             store_elem(grow, k, fast_exp2(log2_softmax(load_elem(row, k), mx, ls)));
-    bool small = false;
+    const FrameNorm norm(load_elem(row, blank), mx, sum, ls);
+    bool small = false, rough = norm.log_blank < kGentleMinLog2;
     if (threadIdx.x == 0) {
-        const float e = encode_emission(log2_softmax(load_elem(row, blank), mx, ls), small, sa.plain_logs);
-        store_blank(emit_blank, sa.emit_blank64, static_cast<size_t>(m.f_off) + t, e, sa.plain_logs);
+        store_blank(emit_blank, sa.emit_blank64, static_cast<size_t>(m.f_off) + t, sa.plain_logs ? norm.log_blank : norm.word(), sa.plain_logs);
+        small = !sa.plain_logs && norm.small;
     }
     if (t == m.Tb - 1) store_virtual_frames(m, emit_blank, sa.emit_blank64, emit_label, sa.plain_logs, threadIdx.x, kRowThreads);
     float* erow = emit_label + emission_at(m.e_off, m.L, t, 0);
     const int* lab = labels + m.lab_off;
-    for (int j = threadIdx.x; j < m.L; j += kRowThreads)
-        erow[static_cast<size_t>(j) * kChunk] = encode_emission(log2_softmax(load_elem(row, lab[j]), mx, ls), small, sa.plain_logs);
+    for (int j = threadIdx.x; j < m.L; j += kRowThreads) {
+        const float lp = log2_softmax(load_elem(row, lab[j]), mx, ls), e = sa.plain_logs ? lp : encode_emission(lp, norm);
+        erow[static_cast<size_t>(j) * kChunk] = e;
+        small = small || (!sa.plain_logs && e < 0.0f);
+        rough = rough || lp < kGentleMinLog2;
+    }
+    raise_rough(meta, b, rough);
     raise_log_domain(meta, b, m, small);
 }
 
@@ -675,14 +716,16 @@ __device__ __forceinline__ void fill_rows(const FillArgs& f, const Utt* __restri
     }
 }
 
-// The coded rows of 64 frames of a narrow alphabet into lp[64][A], a quad of lanes per frame.
+// The emissions of 64 frames of a narrow alphabet into lp[64][A], a quad of lanes per frame, and behind them the frames'
+// words (log2 y_blank if plain_logs).  Returns whether a probability of this lane's is below 2^kGentleMinLog2.
 template <typename T>
-__device__ __forceinline__ void narrow_rows(const T* __restrict__ x, float* lp, int Tb, int b, int t0, int B, int A, bool plain_logs)
+__device__ __forceinline__ bool narrow_rows(const T* __restrict__ x, float* lp, int Tb, int b, int t0, int B, int A, int blank, bool plain_logs)
 {
     constexpr int kPerRow = 4;
     const int tid = threadIdx.x;
     const int r = tid / kPerRow, q = tid % kPerRow, t = t0 + r;
     float* lrow = lp + r * A;
+    bool rough = false;
     if (t < Tb) {
         const T* row = x + (static_cast<size_t>(t) * B + b) * A;
         float mx = -__builtin_inff();
@@ -706,9 +749,15 @@ __device__ __forceinline__ void narrow_rows(const T* __restrict__ x, float* lp, 
         for (int k = q; k < A; k += kPerRow) sum += fast_exp2((lrow[k] - mx) * kLog2e);
         sum = quad_sum(sum);
         const float ls = fast_log2(sum);
-        bool unused = false;       // (what counts is which of the coded emissions get stored below)
-        for (int k = q; k < A; k += kPerRow) lrow[k] = encode_emission(log2_softmax(lrow[k], mx, ls), unused, plain_logs);
+        const FrameNorm norm(lrow[blank], mx, sum, ls);
+        if (q == 0) lp[kFlagFrames * A + r] = plain_logs ? norm.log_blank : norm.word();
+        for (int k = q; k < A; k += kPerRow) {
+            const float l = log2_softmax(lrow[k], mx, ls);
+            rough = rough || l < kGentleMinLog2;
+            lrow[k] = plain_logs ? l : (k == blank ? encode_blank(norm) : encode_emission(l, norm));
+        }
     }
+    return rough;
 }
 
 // A workgroup's share of the emission block: kRows frames from t0 on whose coded rows sit in lp[kRows][A], virtual
@@ -720,12 +769,9 @@ __device__ __forceinline__ bool store_symbol_chunks(const float* lp, int Tb, uns
                                                     float* __restrict__ emit_label, bool plain_logs)
 {
     const int tid = threadIdx.x, rows = min(kRows, Tb - t0), padded = min(kRows, static_cast<int>(padded_frames(Tb)) - t0);
-    bool small = false;
-    if (tid < padded) {
-        const float e = tid < rows ? lp[tid * A + blank] : virtual_emission(true, plain_logs);
-        store_blank(emit_blank, emit_blank64, static_cast<size_t>(f_off) + t0 + tid, e, plain_logs);
-        small = !plain_logs && e < 0.0f;
-    }
+    bool small = false;                                  // (the blank has a column among the symbols')
+    if (tid < padded)
+        store_blank(emit_blank, emit_blank64, static_cast<size_t>(f_off) + t0 + tid, tid < rows ? lp[kRows * A + tid] : virtual_emission(true, plain_logs), plain_logs);
     // a wavefront per chunk: [symbol][frame], 8 A floats in a row
     float* const out = emit_label + kLabelSlack + e_off + static_cast<size_t>(t0) * A;
     for (int chunk = tid >> 6; chunk * kChunk < padded; chunk += kRowThreads / 64)
@@ -748,7 +794,7 @@ void ctc_softmax_symbols_kernel(const T* __restrict__ x, Utt* __restrict__ meta,
                                 const SetupArgs sa, int B, int A, int blank)
 {
     constexpr int kRows = 64;
-    extern __shared__ float lp[];                          // [kRows][A]
+    extern __shared__ float lp[];                          // [kRows][A], [kRows]
     const int b = blockIdx.y;
     const Utt m = meta[b];
     if (blockIdx.x == gridDim.x - 1) {
@@ -757,7 +803,7 @@ void ctc_softmax_symbols_kernel(const T* __restrict__ x, Utt* __restrict__ meta,
     }
     const int t0 = blockIdx.x * kRows;
     if (!(m.flags & kUttRuns) || t0 >= m.Tb) return;
-    narrow_rows(x, lp, m.Tb, b, t0, B, A, sa.plain_logs);
+    raise_rough(meta, b, narrow_rows(x, lp, m.Tb, b, t0, B, A, blank, sa.plain_logs));
     __syncthreads();
     raise_log_domain(meta, b, m, store_symbol_chunks<kRows>(lp, m.Tb, m.f_off, m.e_off, t0, A, blank, emit_blank, sa.emit_blank64,
                                                             emit_label, sa.plain_logs));
@@ -885,6 +931,7 @@ __device__ __forceinline__ Utt build_record(const NarrowDevice& dv, const PlanTa
     m.halo2 = plans.halo2(Lp);
     m.poll_budget = dv.poll_budget;
     m.e_direct = emission_layout(A);
+    m.rough = 0;
     m.e_cols = m.e_direct == kEmitSymbols ? A : m.L;
     m.e_off = b * (m.e_direct == kEmitSymbols ? static_cast<int64_t>(padded) * A : gathered_emissions(Tt, longest));
     m.ab_off = b * lattice_words(Tt, longest);
@@ -918,8 +965,8 @@ void ctc_softmax_narrow_kernel(const T* __restrict__ x, const NarrowImage image,
 {
     constexpr int kRows = kFlagFrames;
     static_assert(kRows * 4 == kRowThreads, "a quad per frame (narrow_rows)");
-    extern __shared__ float lp[];                          // [kRows][A]
-    __shared__ int s_small;
+    extern __shared__ float lp[];                          // [kRows][A], [kRows]
+    __shared__ int s_small, s_rough;
     const int b = blockIdx.y, tid = threadIdx.x;
     const int row_blocks = static_cast<int>(gridDim.x) - sa.parts;
     if (static_cast<int>(blockIdx.x) >= row_blocks && dv.labels) {
@@ -966,25 +1013,29 @@ void ctc_softmax_narrow_kernel(const T* __restrict__ x, const NarrowImage image,
     m.e_off = static_cast<int64_t>(m.f_off) * A;
     const int t0 = blockIdx.x * kRows;
     if (t0 >= m.Tb || !(m.flags & kUttRuns)) return;
-    if (tid == 0) s_small = 0;
-    narrow_rows(x, lp, m.Tb, b, t0, B, A, sa.plain_logs);
+    if (tid == 0) {
+        s_small = 0;
+        s_rough = 0;
+    }
+    const bool rough = narrow_rows(x, lp, m.Tb, b, t0, B, A, blank, sa.plain_logs);
     __syncthreads();
     const bool small = store_symbol_chunks<kRows>(lp, m.Tb, m.f_off, m.e_off, t0, A, blank, emit_blank, sa.emit_blank64, emit_label,
                                                   sa.plain_logs);
-    if (small) s_small = 1;
+    if (small) s_small = kRowsSmall;
+    if (rough) s_rough = kRowsRough;
     __syncthreads();
-    if (tid == 0) row_flags[static_cast<size_t>(b) * row_blocks + blockIdx.x] = s_small;
+    if (tid == 0) row_flags[static_cast<size_t>(b) * row_blocks + blockIdx.x] = s_small | s_rough;
 }
 
-// Has the narrow softmax launch met an emission below the linear domain's range in one of the
-// utterance's frames?  Asked by a whole wavefront; the same answer in every lane.
-__device__ __forceinline__ bool rows_flagged(const int* __restrict__ row_flags, int b, int blocks_per_utterance, int Tb)
+// What the narrow softmax launch has met in an utterance's frames: kRowsSmall, kRowsRough.  Asked by a whole wavefront; the same
+// answer in every lane.
+__device__ __forceinline__ int rows_flagged(const int* __restrict__ row_flags, int b, int blocks_per_utterance, int Tb)
 {
-    if (!row_flags) return false;
+    if (!row_flags) return 0;
     const int lane = threadIdx.x & 63, n = (Tb + kFlagFrames - 1) / kFlagFrames;
-    bool any = false;
-    for (int i = lane; i < n; i += 64) any = any || row_flags[static_cast<size_t>(b) * blocks_per_utterance + i] != 0;
-    return __ballot(any) != 0;
+    int any = 0;
+    for (int i = lane; i < n; i += 64) any |= row_flags[static_cast<size_t>(b) * blocks_per_utterance + i];
+    return (__ballot(any & kRowsSmall) != 0 ? kRowsSmall : 0) | (__ballot(any & kRowsRough) != 0 ? kRowsRough : 0);
 }
 
 // ---- lattice storage -------------------------------------------------------------------------
@@ -1016,6 +1067,11 @@ __device__ __forceinline__ double pack_state(double in_frame, int frame)
 {
     return __hiloint2double(__double2hiint(in_frame), frame);
 }
+// (the exponent below it is no part of the mantissa: a negative one would read as nearly another 2^-20)
+__device__ __forceinline__ float packed_mantissa(double packed)
+{
+    return static_cast<float>(__hiloint2double(__double2hiint(packed), 0));
+}
 // A base-2 logarithm (log-domain chains) as value and exponent: m = 2^fraction in [1, 2), e = floor.
 // log 0 (and anything as small) is stored as the number 0 with the exponent of zero.
 __device__ __forceinline__ void split_log2(double w, uint32_t& value, int& exponent)
@@ -1038,7 +1094,6 @@ __device__ __forceinline__ double pack_log2(double w)          // the same as on
 // What the chains leave may be read by workgroups of the same launch, on other dies, once they know the chains to have
 // ended (announce_end): both sides go past the dies' own caches.
 __device__ __forceinline__ void publish(int* p, int v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ void publish(float* p, float v) { publish(reinterpret_cast<int*>(p), __float_as_int(v)); }
 __device__ __forceinline__ void publish(double* p, double v)
 {
     __hip_atomic_store(reinterpret_cast<long long*>(p), __double_as_longlong(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1090,6 +1145,71 @@ __device__ __forceinline__ double shift_down(double v, int& into_lo, int& into_h
     return __hiloint2double(into_hi, into_lo);
 }
 
+// What is kept of an utterance's mass p (of its frames divided by their norms), kMassWords doubles:
+//   kMassInverse  1 / p for the gradient, mantissa and exponent in one word (pack_state)
+//   kMassValue, kMassLog2  two numbers x and y with log2 p = log2 x + y, for the cost
+//   kMassNorms  cost-only calls: log2 of the product of the norms
+constexpr int kMassInverse = 0, kMassValue = 1, kMassLog2 = 2, kMassNorms = 3;
+static_assert(kMassWords == 4, "four words");
+__device__ __forceinline__ float cost_of_mass(double x, double y, double log2_norms)
+{
+    // (in double: once per utterance, and a cost near zero, p near 1, would keep few of a float logarithm's bits)
+    return x > 0.0 ? static_cast<float>(-(::log2(x) + (y + log2_norms)) * kLn2) : __builtin_inff();
+}
+// The product of an utterance's norms, mantissa * 2^exponent.
+struct Norms {
+    double mantissa;                                     // [0.5, 1)
+    int exponent;
+    __device__ __forceinline__ Norms times(double other_mantissa, int other_exponent) const
+    {
+        const double product = mantissa * other_mantissa;
+        return {__builtin_amdgcn_frexp_mant(product), exponent + other_exponent + __builtin_amdgcn_frexp_exp(product)};
+    }
+    __device__ __forceinline__ double log2() const { return static_cast<double>(exponent) + ::log2(mantissa); }
+};
+// A lane's part of it: frames lane, lane + 64, ...
+__device__ __forceinline__ Norms norms_of_lane(const Utt& m, const float* __restrict__ emit_blank)
+{
+    const int lane = threadIdx.x & 63, frames = static_cast<int>(padded_frames(m.Tb));
+    const float* const words = emit_blank + kBlankSlack + m.f_off;
+    Norms product{0.5, 1};
+    constexpr int kAhead = 12;
+    for (int t0 = 0; t0 < frames; t0 += 64 * kAhead) {
+        float c[kAhead];
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) c[i] = words[min(t0 + 64 * i + lane, frames - 1)];
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) {
+            if (t0 + 64 * i >= frames) break;
+            const double norm = t0 + 64 * i + lane < frames ? static_cast<double>(frame_norm(c[i])) : 1.0;
+            product = product.times(norm, 0);
+        }
+    }
+    return product;
+}
+// The parts of a wavefront's lanes (all of them active) put together: the same in every lane, and the same each time.
+// (750 frames: 2.5 us for both together, most of it waiting for memory, so whoever has nothing else to do does it: the
+// gradient's workgroups, which write the cost, or a wavefront of a cost-only call that has no part in the chain.)
+template <int kCtrl>
+__device__ __forceinline__ Norms norms_permuted(const Norms& n)
+{
+    auto move = [](int v) { return __builtin_amdgcn_update_dpp(0, v, kCtrl, 0xf, 0xf, true); };
+    return {__hiloint2double(move(__double2hiint(n.mantissa)), move(__double2loint(n.mantissa))), move(n.exponent)};
+}
+__device__ __forceinline__ Norms norms_of_wave(Norms n)
+{
+    auto with = [](const Norms& a, const Norms& b) { return a.times(b.mantissa, b.exponent); };
+    n = with(n, norms_permuted<0xB1>(n));                // (the patterns of row16_sum)
+    n = with(n, norms_permuted<0x4E>(n));
+    n = with(n, norms_permuted<0x141>(n));
+    n = with(n, norms_permuted<0x140>(n));
+    auto row = [&](int lane) {
+        auto read = [&](int v) { return __builtin_amdgcn_readlane(v, lane); };
+        return Norms{__hiloint2double(read(__double2hiint(n.mantissa)), read(__double2loint(n.mantissa))), read(n.exponent)};
+    };
+    return with(with(row(0), row(16)), with(row(32), row(48)));
+}
+
 constexpr int kHaloEntries = 64;      // 16-byte entries of one wavefront boundary's exchange buffer (2 x 32)
 
 enum class Sync { kNone, kHalo, kBarrier };
@@ -1131,6 +1251,9 @@ struct HaloHeader {
     int gave_up;
     float cost;
     int left;                         // chains of a launch that writes the gradient too: see lattice_body
+    int always;                       // a counter that is as far as anybody asks
+    int unused;
+    int always_tag[2];                // ... and such a tag (frame, number)
 };
 // Chains with one pair per lane.
 struct HaloWave {
@@ -1205,7 +1328,7 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
                                           const float* __restrict__ emit_blank, const double* __restrict__ emit_blank64,
                                           const float* __restrict__ emit_label,
                                           uint32_t* __restrict__ out, int* __restrict__ out_exponents,
-                                          double* __restrict__ logp,
+                                          double* __restrict__ mass,
                                           float* __restrict__ costs, int* __restrict__ chain_err,
                                           uint32_t* __restrict__ sink, void* lds)
 {
@@ -1428,28 +1551,29 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
         label_origin = 2 * j + 1;
     };
     // (every lane starts from the exact state of its pair, halo lanes included)
-    float el[4][kChunk], eb[2];
+    float el[4][kChunk], eb[2];                          // eb: the frames' words
     double blank_logs[2][kChunk] = {};                   // (Mode::kBest: as scalars, see run_chain_linear)
+    const double* next_blanks = emit_blank64 + blank_emission_offset(m, chain_chunk(0, chunks, kBackward));
     auto fetch = [&](auto set, int i) {
         constexpr int k = decltype(set)::value;
-        if (i > 0 && kMode == Mode::kBest) {
-            asm volatile("" : : "s"(blank_logs[k & 1][0]), "s"(blank_logs[k & 1][kChunk - 1]));
-            const double* const w = emit_blank64 + blank_emission_offset(m, chain_chunk(i - 1, chunks, kBackward));
+        if (i >= kBlankAhead && kMode == Mode::kBest) {
+            asm volatile("" : : "s"(blank_logs[(k + 1) & 1][0]), "s"(blank_logs[(k + 1) & 1][kChunk - 1]));
 #pragma unroll
-            for (int q = 0; q < kChunk; ++q) blank_logs[(k + 1) & 1][q] = w[kBackward ? kChunk - 1 - q : q];
-        } else if (i > 0) {
-            eb[(k + 1) & 1] = bp[blank_emission_offset(m, chain_chunk(i - 1, chunks, kBackward))];
+            for (int q = 0; q < kChunk; ++q) blank_logs[k & 1][q] = next_blanks[kBackward ? kChunk - 1 - q : q];
+            next_blanks += kBackward ? -kChunk : kChunk;
+        } else if (i >= kBlankAhead) {
+            eb[k & 1] = bp[blank_emission_offset(m, chain_chunk(i - kBlankAhead, chunks, kBackward))];
         }
         fetch_chunk<kBackward>(ep, estep, el[k]);
         __builtin_amdgcn_sched_barrier(0);
     };
     auto run = [&](auto set, int i) {
         constexpr int k = decltype(set)::value;
-        const Log2Parts blank = kCoded ? emission_log2_parts(eb[k & 1]) : Log2Parts{0.0f, 0.0f};
+        const float blank = kCoded ? blank_emission_log2(eb[k & 1]) : 0.0f;
 #pragma unroll
         for (int q = 0; q < kChunk; ++q)
             advance(i * kChunk + q,
-                    kCoded ? static_cast<double>(readlane(blank.whole, q)) + static_cast<double>(readlane(blank.part, q)) : blank_logs[k & 1][q],
+                    kCoded ? static_cast<double>(readlane(blank, q)) : blank_logs[k & 1][q],
                     el[k][q]);
         end_chunk();
         if (kMode == Mode::kBest) {
@@ -1474,12 +1598,19 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
         // halo lane, it is still exact: the error from lane 0 needs `halo` steps to get there,
         // and a hand-over that fell due after the last step has been done by end_chunk.
         const double prev = from_prev_pair(v_label, chunks * kChunk);
-        if (active && j == L) {
+        if (kMode == Mode::kLoss) {
+            const Norms norms = norms_of_wave(norms_of_lane(m, emit_blank));
+            if (active && j == L) {
+                const double lp = lse2(v_blank, prev);
+                const float cost = cost_of_mass(lp < -1.0e29 ? 0.0 : 1.0, lp, norms.log2());
+                if (kSync == Sync::kHalo) hl->cost = cost;
+                else costs[u] = cost;
+            }
+        } else if (active && j == L) {
             const double lp = lse2(v_blank, prev);
-            publish(&logp[u], pack_log2(-lp));           // 1 / p
-            const float cost = (lp < -1.0e29) ? __builtin_inff() : static_cast<float>(-lp * kLn2);
-            if (kSync == Sync::kHalo && kMode == Mode::kLoss) hl->cost = cost;
-            else publish(&costs[u], cost);
+            publish(&mass[u * kMassWords + kMassInverse], pack_log2(-lp));
+            publish(&mass[u * kMassWords + kMassValue], lp < -1.0e29 ? 0.0 : 1.0);
+            publish(&mass[u * kMassWords + kMassLog2], lp);
         }
     }
     if (kSync == Sync::kHalo && kMode == Mode::kLoss) {
@@ -1503,52 +1634,48 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
     }
 }
 
-// The same chain on probabilities instead of their logarithms: a step is then two fused
-// multiply-adds, an addition and two multiplications per pair, a third of the instructions of the
+// The same chain on probabilities, each frame's divided by its blank's (FrameNorm), instead of their logarithms: a step is then
+// two fused multiply-adds, an addition and a multiplication per pair, a fifth of the instructions of the
 // log-domain step and no transcendentals.  What makes it safe is an exponent per lane:
 //   true value = (v_blank, v_label) * 2^frame
-// with fp64 values and an int32 `frame` that is renewed after every chunk of kChunk steps:
-//   frame = largest binary exponent among this pair and the kChunk pairs below it.
-// Mass moves up by at most one pair per step, so until the next renewal everything that can
-// reach the pair is at most 2^(kChunk+1) in its frame (no overflow), and its own mass cannot
-// shrink by more than kChunk emissions, each at least 2^kLinearMinLog2, that is 800 of fp64's
-// 1022 binary orders of magnitude (utterances with smaller emissions run the log-domain chain).
-// Only what lies more than about 2^-1000 below the largest of its nine-pair window is rounded
-// away.  The value shifted in from the pair below is brought into this lane's frame by `scale`
-// = 2^(frame below - frame here), constant between renewals and folded into the multiply-adds.
+// with fp64 values and an int32 `frame` that is looked after at the ends of chunks (ChainFrames).  Probabilities of the linear
+// domain are at least 2^-m (m = -kLinearMinLog2 = 79), ratios to the blank's thus within 2^-m .. 2^m.  A renewal gives a lane
+//   frame = largest binary exponent among its own pairs and the kChunk pairs below it, its window,
+// but no more than kFrameSlack above its own largest value, down to kFrameDrop below the window's top.  Mass moves up by at most
+// one pair per step, so in the kChunk steps that follow
+//   - what arrives from the window is at most 2^kFrameDrop, and grows by 3 * 2^m a step at most: 2^(370 + 8 * 80.6) = 2^1015,
+//   - a value of at least 2^-kFrameSlack shrinks by 2^-m a step at worst: 2^-(390 + 632) = 2^-1022,
+// both inside fp64.  Two neighbouring frames differ by at most kFrameSlack + kFrameDrop, which the factor between them (scale,
+// constant between renewals and folded into the multiply-adds) can hold.
 //
-// Storage (Mode::kGrad): the whole state after every second chunk (see "lattice storage").
-// A lane's new frame is the largest exponent of its window (its own pairs and those that can reach it
-// before the next renewal), so that nothing arriving overflows -- but no more than kFrameSlack above
-// its own largest value where the window's top lies further up than that, down to kFrameDrop below the
-// window's top.  With the window's top as the frame of every lane, a pair whose neighbours below carry
-// 2^1000 times its mass was rounded away: wrong when those neighbours' mass can no longer reach the
-// end of the label and the small pair is all there is (an utterance with exactly as many frames as its
-// label needs, logits spread over 40 nats: cost off by 0.03, gradient by 0.03).  Now a pair keeps
-// 2^-kFrameSlack of its frame, 2^-(kFrameSlack + 800) after a chunk of the smallest emissions the
-// linear domain admits, as long as the window's top is within 2^(kFrameSlack + kFrameDrop) of it; what
-// arrives from the window is at most 2^(kFrameDrop + 9) in the lane's frame, and two neighbouring
-// frames differ by at most kFrameSlack + kFrameDrop, which the factor between them (scale) can hold.
-// A pair further below its window than that has neighbours with 2^950 times its mass that can still
-// reach the end (utterances with fewer than kTightFrames frames to spare, where they could not, run in
-// the log domain from the start: tight_fit), each of their extra moves costing an emission of 2^-100 at
-// worst: what is rounded away then is below 2^-50 of the whole.
-constexpr int kFrameSlack = 150, kFrameDrop = 800;
-// (A lane without mass, whose own largest exponent is kNoExponent, sits kFrameDrop below the top: the
-// first mass to reach it may come from a lane whose own frame lies that low, and must not be rounded
-// away on arrival.)
+// A pair further than 2^(kFrameSlack + kFrameDrop) below its window's top is rounded away.  Its neighbours have 2^760 times its
+// mass and can still reach the end of the label (utterances with fewer than kTightFrames frames to spare, where they could
+// not, run in the log domain from the start: tight_fit), each of their at most eight extra moves costing 2^-m at worst: what is
+// rounded away is below 2^-128 of the whole.  (With the window's top as the frame of every lane a pair 2^1000 below its
+// neighbours was lost where it was all there is: an utterance with exactly as many frames as its label needs, logits spread
+// over 40 nats, cost off by 0.03, gradient by 0.03.)
+//
+// Storage (Mode::kGrad): the whole state after every block (see "lattice storage").
+//
+// What a step costs (a lone wavefront of a chain issues an instruction every 4.1 clocks): 7 instructions, 12 where a lane owns
+// two pairs.  With the blank's emissions as scalars it was 9 and 14, and they had to be fetched and waited for; with a renewal
+// at every chunk and hand-overs of 570 clocks the steps of a 750-frame utterance took, in ns, labels of 40 / 150 / 190 / 240 /
+// 420 symbols: 32.8 / 40.6 / 45.5 / 49.5 / 52.3; now 17.9 / 24.3 / 30.3 / 35.3 / 43.2.
+constexpr int kFrameSlack = 390, kFrameDrop = 370;
 __device__ __forceinline__ int lane_frame(int window_top, int own_top)
 {
     return window_top - min(max(window_top - own_top - kFrameSlack, 0), kFrameDrop);
 }
-// A renewal is put off while it is not needed (a third of a chunk's instructions are the renewal's): every
-// pair of the wavefront has mass, lies within [2^kEasyLow, 2^kEasyHigh] of its frame, and at the last
-// renewal no frame lay more than kSmoothFrames below the frame of the lane below it.  Then one more chunk
-// takes a value down to 2^(kEasyLow - 800) at worst, and up to 3^kChunk times the largest of the nine-pair
-// window in this lane's frame, 2^(kEasyHigh + kChunk * kSmoothFrames + 13): both far inside fp64.  The
-// frames and the scale factors simply stay what they are.
-constexpr int kEasyLow = -200, kEasyHigh = 100;
-constexpr int kSmoothFrames = 60;
+// A renewal (about 250 clocks, a chunk's eight steps 240) is put off while it is not needed: every lane with mass has its largest
+// value within [2^kEasyLow, 2^kEasyHigh] of its frame, and no frame lies more than kSmoothFrames a pair below the frame of the
+// lane below it.  Until the next look, after n steps with ratios within 2^-g .. 2^g, a value is at least 2^(kEasyLow - n g), and
+// at most 2^(kEasyHigh + n (kSmoothFrames + g + 1.6)).  A chunk, g = 79: 2^-982 and 2^936; a block, where all probabilities of the
+// utterance are above 2^kGentleMinLog2 (g = 32): 2^-862 and 2^1021.
+constexpr int kEasyLow = -350, kEasyHigh = 99;
+constexpr int kSmoothFrames = 24;
+static_assert(kFrameSlack - kChunk * kLinearMinLog2 <= 1022 && kEasyLow + kChunk * kLinearMinLog2 >= -1022, "small values");
+static_assert(kFrameDrop + kChunk * (1.6f - kLinearMinLog2) < 1023 && kEasyHigh + kChunk * (kSmoothFrames + 1.6f - kLinearMinLog2) < 1023, "large values");
+static_assert(kEasyLow + kBlockFrames * kGentleMinLog2 >= -1022 && kEasyHigh + kBlockFrames * (kSmoothFrames + 1.6f - kGentleMinLog2) < 1023, "a block");
 // The test, on the high dword of the largest value of a lane (biased exponent in bits 20..30): one
 // subtraction and one unsigned compare; zero, denormals, infinities and NaN fail it.
 __device__ __forceinline__ bool outside_easy_range(double top)
@@ -1557,32 +1684,61 @@ __device__ __forceinline__ bool outside_easy_range(double top)
     return hi - (static_cast<unsigned>(1023 + kEasyLow) << 20) >= (static_cast<unsigned>(kEasyHigh - kEasyLow + 1) << 20);
 }
 
-// An utterance's mass p = value * 2^frame: its reciprocal for the gradient, and the cost.
-__device__ __forceinline__ void mass_and_cost(double value, int frame, double& inverse_p, float& cost)
+// A forward chain's end: p = value * 2^frame.
+__device__ __forceinline__ void publish_mass(double* mass, double value, int frame)
 {
-    const double mantissa = __builtin_amdgcn_frexp_mant(value);                // [0.5, 1)
-    const int exponent = frame + __builtin_amdgcn_frexp_exp(value);
-    // (in double: once per chain, and a cost near zero, p near 1, would keep few of a float logarithm's bits)
-    const double l2 = static_cast<double>(exponent) + ::log2(mantissa);
-    inverse_p = (value > 0.0) ? pack_state(1.0 / mantissa, -exponent) : 0.0;
-    cost = (value > 0.0) ? static_cast<float>(-l2 * kLn2) : __builtin_inff();
-}
-__device__ __forceinline__ void store_mass(double value, int frame, double* inverse_p_out, float* cost_out)
-{
-    double inverse_p;
-    float cost;
-    mass_and_cost(value, frame, inverse_p, cost);
-    publish(inverse_p_out, inverse_p);
-    publish(cost_out, cost);
+    publish(&mass[kMassInverse], value > 0.0 ? pack_state(1.0 / __builtin_amdgcn_frexp_mant(value), -(frame + __builtin_amdgcn_frexp_exp(value))) : 0.0);
+    publish(&mass[kMassValue], value);
+    publish(&mass[kMassLog2], static_cast<double>(frame));
 }
 
+// A chain's frames; kPairs pairs to a lane.
+template <int kPairs>
+struct ChainFrames {
+    static constexpr int kSmooth = kPairs * kSmoothFrames, kSteps = kChunk / kPairs;     // (mass moves up kSteps lanes in a chunk)
+    int frame = 0;
+    double scale = 1.0;                                  // 2^(frame of the lane below - frame)
+    unsigned long long rough = ~0ull;                    // lanes that may not put a renewal off: see rescale
+    // The factors between the frames.  `massless`: lanes without mass.  A lane's frame may lie kSmooth below that of the
+    // lane below it and no further, one without mass not above it either.
+    __device__ __forceinline__ void rescale(unsigned long long massless)
+    {
+        const int down = __builtin_amdgcn_update_dpp(kNoExponent, frame, 0x138, 0xf, 0xf, false) - frame;
+        // 2^1023 is the largest factor there is; a pair that far below its neighbour has been rounded away already.
+        scale = __builtin_amdgcn_ldexp(1.0, min(max(down, -1100), 1023));
+        rough = __ballot(down > kSmooth) | (__ballot(down < -kSmooth) & massless & ~1ull);       // (lane 0 has nothing below)
+    }
+    // The frames after a renewal; returns what the lane's values are to be scaled by.  `top`: the largest of them.  Lanes above the highest one with mass take that one's frame, so that the front of the lattice
+    // passes through a wavefront like anything else; where no lane has mass, `reference`'s.
+    __device__ __forceinline__ int renew(double top, int reference)
+    {
+        const bool has_mass = top > 0.0;
+        const unsigned long long massive = __ballot(has_mass);
+        const int mine = has_mass ? frame + __builtin_amdgcn_frexp_exp(top) : kNoExponent;
+        int window = mine;
+#pragma unroll
+        for (int k = 0; k < kSteps; ++k) window = window_max_step(window, mine);
+        int next = massive != 0 ? lane_frame(window, mine) : frame;
+        const int front = massive != 0 ? 63 - __builtin_clzll(massive) : reference;
+        const int beyond = __builtin_amdgcn_readlane(next, front);
+        next = static_cast<int>(threadIdx.x & 63) > front ? beyond : next;
+        const int rise = frame - next;
+        frame = next;
+        rescale(~massive);
+        return rise;
+    }
+    // Is a renewal due?  (A lane without mass is where it should be unless it is rough.)
+    __device__ __forceinline__ bool renewal_due(double top) const
+    {
+        return ((__ballot(outside_easy_range(top)) & __ballot(top > 0.0)) | rough) != 0;
+    }
+};
+
 template <bool kBackward, Sync kSync, Mode kMode>
-__device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const int* __restrict__ labels,
-                                                 const double* __restrict__ emit_blank64,
+__device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const bool gentle, const int* __restrict__ labels,
                                                  const float* __restrict__ emit_label,
                                                  uint32_t* __restrict__ out, int* __restrict__ out_exponents,
-                                                 double* __restrict__ logp,
-                                                 float* __restrict__ costs, int* __restrict__ chain_err,
+                                                 double* __restrict__ mass, int* __restrict__ chain_err,
                                                  uint32_t* __restrict__ sink, void* lds)
 {
     static_assert(kSync != Sync::kBarrier, "the barrier kernel runs the log-domain chain");
@@ -1616,8 +1772,8 @@ __device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const
     HaloWave* const above_lds = halo_wave<HaloWave>(lds, wave < last_wave ? wave + 1 : wave);
     int budget = m.poll_budget;
     bool lost = false;
-    const int chunks_per_hand_over = halo / kChunk;
-    int until_hand_over = chunks_per_hand_over;
+    const bool every_block = halo < 2 * kBlockFrames;    // hand over after every block, or after every second one
+    const unsigned long long steep = gentle ? 0ull : ~0ull;
     int generation = 0;
     int half = 0;
     const int wr_slot = lane >= 64 - halo ? lane - (64 - halo) : 0;
@@ -1626,169 +1782,136 @@ __device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const
     const double2* const rd_base = (kSync == Sync::kHalo) ? &below_lds->data[rd_slot] : nullptr;
     int* const wr_frame = (kSync == Sync::kHalo) ? &mine_lds->frame[wr_slot] : nullptr;
     const int* const rd_frame = (kSync == Sync::kHalo) ? &below_lds->frame[rd_slot] : nullptr;
-    int* const my_ready = &mine_lds->ready;
-    int* const my_done = &mine_lds->done;
-    int* const up_done = &above_lds->done;
-    int* const low_ready = &below_lds->ready;
+    // (at the ends: nobody to wait for.  `nil`: addresses in vector registers, where they are needed)
+    int nil = 0;
+    asm volatile("" : "+v"(nil));
+    int* const always = &static_cast<HaloHeader*>(lds)->always + nil;
+    int* const my_ready = &mine_lds->ready + nil;
+    int* const up_ready = wave < last_wave ? &above_lds->ready + nil : always;
+    int* const low_ready = wave > 0 ? &below_lds->ready + nil : always;
+    const bool from_below = wave > 0 && lane < halo;
 
     double v_blank = (j == 0) ? 1.0 : 0.0, v_label = 0.0;
-    int frame = 0;
-    double scale = 1.0;                                  // 2^(frame of the pair below - frame)
-    double skip_scale = skip_ok ? 1.0 : 0.0;             // the same where the label may be entered from that pair's label
+    ChainFrames<1> f;
+    double skip_scale = skip_ok ? 1.0 : 0.0;             // f.scale where the label may be entered from the label of the pair below
 
     auto counter = [&](int* p) {
         return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     };
     auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
-    int done_seen = 0;
-    // The exchange protocol of run_chain_log; an entry carries the pair's frame as well.
+    int up_seen = 0;
+    // Hand-over g: what comes from below is asked for first and used last; passing the own state up fills the time.  A wavefront
+    // publishes g when it has taken g itself, so that the one below knows from the same counter which half of the buffer is
+    // free.  An entry carries the pair's frame as well.
     auto hand_over = [&]() {
         ++generation;
         half ^= 32;
-        if (wave < last_wave) {
-            int seen = uniform(done_seen);
-            if (__builtin_expect(seen < generation - 2, 0)) {
-                while (seen < generation - 2 && budget > 0) {
-                    --budget;
-                    seen = uniform(counter(up_done));
-                }
-                lost = lost || seen < generation - 2;
+        int ready = counter(low_ready);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        double2 v = rd_base[half];
+        int vf = rd_frame[half];
+        int seen = uniform(up_seen);
+        if (__builtin_expect(seen < generation - 2, 0)) {
+            while (seen < generation - 2 && budget > 0) {
+                --budget;
+                seen = uniform(counter(up_ready));
             }
-            if (lane >= 64 - halo) {
-                wr_base[half] = make_double2(v_blank, v_label);
-                wr_frame[half] = frame;
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            if (lane == 63) __hip_atomic_store(my_ready, generation, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            done_seen = counter(up_done);
+            lost = lost || seen < generation - 2;
         }
-        if (wave > 0) {
-            int ready = counter(low_ready);
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            double2 v = rd_base[half];
-            int vf = rd_frame[half];
-            ready = uniform(ready);
-            if (__builtin_expect(ready < generation, 0)) {
-                while (ready < generation && budget > 0) {
-                    --budget;
-                    ready = counter(low_ready);
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                    v = rd_base[half];
-                    vf = rd_frame[half];
-                    ready = uniform(ready);
-                }
-                lost = lost || ready < generation;
-            }
-            if (lane < halo) {
-                v_blank = v.x;
-                v_label = v.y;
-                frame = vf;
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            if (lane == 0) __hip_atomic_store(my_done, generation, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (lane >= 64 - halo) {
+            wr_base[half] = make_double2(v_blank, v_label);
+            wr_frame[half] = f.frame;
         }
+        ready = uniform(ready);
+        if (__builtin_expect(ready < generation, 0)) {
+            while (ready < generation && budget > 0) {
+                --budget;
+                ready = counter(low_ready);
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                v = rd_base[half];
+                vf = rd_frame[half];
+                ready = uniform(ready);
+            }
+            lost = lost || ready < generation;
+        }
+        // (LDS operations of a wavefront complete in order: the counter follows the data, and the reads)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        if (lane == 63) __hip_atomic_store(my_ready, generation, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        up_seen = counter(up_ready);
+        v_blank = from_below ? v.x : v_blank;
+        v_label = from_below ? v.y : v_label;
+        f.frame = from_below ? vf : f.frame;
+        f.rescale(__ballot(!(fmax(v_blank, v_label) > 0.0)));    // (the halo lanes come back with other frames)
+        skip_scale = skip_ok ? f.scale : 0.0;
     };
 
     // Label value of pair j-1 after the last step, in that pair's frame (0 for pair 0: the shift
     // leaves lane 0 what it had).
     int prev_lo = 0, prev_hi = 0;
     auto from_prev_pair = [&](double mine) { return shift_up(mine, prev_lo, prev_hi); };
-    const unsigned long long counted = __ballot(j >= 0 && j <= L);   // the lanes with a pair of the label (the others hold zeros)
-    unsigned long long rough = ~0ull;                    // lanes whose frame lies far below that of the lane below (kSmoothFrames)
-    auto shift_up_int = [](int v) { return __builtin_amdgcn_update_dpp(kNoExponent, v, 0x138, 0xf, 0xf, false); };
-
-    // New frames after a chunk.  (A pair whose window holds no mass yet gets kNoExponent: its
-    // values are zero and stay zero whatever the exponent.)
+    auto top_value = [&]() { return fmax(v_blank, v_label); };
     auto renew_frames = [&]() {
-        const double top = fmax(v_blank, v_label);
-        const int mine = (top > 0.0) ? frame + __builtin_amdgcn_frexp_exp(top) : kNoExponent;
-        int window = mine;
-#pragma unroll
-        for (int k = 0; k < kChunk; ++k) window = window_max_step(window, mine);
-        window = lane_frame(window, mine);
-        const int rise = frame - window;
+        const int rise = f.renew(top_value(), halo > 0 ? halo - 1 : 0);
         v_blank = __builtin_amdgcn_ldexp(v_blank, rise);
         v_label = __builtin_amdgcn_ldexp(v_label, rise);
-        frame = window;
-        // 2^1023 is the largest factor there is; a pair that far below its neighbour has been
-        // rounded away already.
-        const int down = shift_up_int(window) - window;
-        const int below = min(max(down, -1100), 1023);
-        scale = __builtin_amdgcn_ldexp(1.0, below);
-        skip_scale = skip_ok ? scale : 0.0;
-        rough = __ballot(down > kSmoothFrames) & counted;
-    };
-    auto renewal_due = [&]() {
-        return ((__ballot(outside_easy_range(fmax(v_blank, v_label))) & counted) | rough) != 0;
+        skip_scale = skip_ok ? f.scale : 0.0;
     };
 
-    auto end_chunk = [&]() {
-        bool handed = false;
-        if (kSync == Sync::kHalo) {
-            if (--until_hand_over == 0) {
-                hand_over();                             // (the halo lanes come back with other frames)
-                until_hand_over = chunks_per_hand_over;
-                handed = true;
-            }
-        }
-        // (Only chains of one wavefront put renewals off: the wavefronts of a longer chain keep in step
-        // best when all of them do the same work per chunk; measured 5 % slower otherwise.)
-        if (kSync != Sync::kNone || handed || renewal_due()) renew_frames();
+    // After a block's first chunk, and after a block.
+    auto mid_block = [&]() {
+        if (__builtin_expect((f.rough | steep) != 0, 0))
+            if (f.renewal_due(top_value())) renew_frames();
+    };
+    auto end_block = [&](bool second) {
+        if (kSync == Sync::kHalo)
+            if (second || every_block) hand_over();
+        if (__builtin_expect(f.renewal_due(top_value()), 0)) renew_frames();
     };
     auto checkpoint = [&]() {
         *vp = CheckpointState{v_blank, v_label};
-        *fp = frame;
+        *fp = f.frame;
         vp += row_step;
         fp += row_step;
     };
     // One step.  The blank state sums its own value and the label of the pair before; the label state
     // its own value, the old blank and, where the skip is allowed, that label too:
     //   label' = fma(previous label, skip, label + blank) * emission.
-    // A lone wavefront on its SIMD issues an instruction every 2 ns, but one that reads the result of
-    // the instruction before it only after 4 ns, and of the one before that after 3 (measured on gfx950
-    // with chains of dependent v_fma_f64).  So the statements are in the order of issue (pin keeps the
-    // compiler from moving them), and none needs a result younger than two instructions: the sum and
-    // the conversion fill the time the two DPP moves take.
+    // Seven instructions, issued one every 4.1 clocks in the order of the statements (pin keeps the compiler from moving them; one
+    // that reads the result of the one before it waits another clock).  The shift needs its operand two instructions old.
     auto pin = []() { __builtin_amdgcn_sched_barrier(0); };
-    auto advance = [&](double eb_d, float el) {
+    auto advance = [&](double& el_d, float next_el) {
 #pragma clang fp contract(off)                           // (a product stays a product: fused into the next step's sum it would tie the steps together)
         const double prev = from_prev_pair(v_label);
         pin();
         const double u = v_blank + v_label;
         pin();
-        const double el_d = static_cast<double>(el);
-        pin();
         const double i_label = __builtin_fma(prev, skip_scale, u);
-        pin();
-        const double i_blank = __builtin_fma(prev, scale, v_blank);
         pin();
         v_label = i_label * el_d;
         pin();
-        v_blank = i_blank * eb_d;
+        v_blank = __builtin_fma(prev, f.scale, v_blank);
+        pin();
+        el_d = static_cast<double>(next_el);             // (and the wait that the next step's shift of v_label needs)
+        asm volatile("" : "+v"(el_d));
         pin();
     };
 
-    // (Scalar loads return in any order, so a wavefront can only wait for all of them: the set in use is
-    // waited for before the other set's load goes out, while that wait is still free.)
     float el[4][kChunk];
-    double eb[2][kChunk] = {};
-    auto fetch = [&](auto set, int i) {
+    auto fetch = [&](auto set, int) {
         constexpr int k = decltype(set)::value;
-        if (i > 0) {
-            asm volatile("" : : "s"(eb[k & 1][0]), "s"(eb[k & 1][kChunk - 1]));
-            const double* const w = emit_blank64 + blank_emission_offset(m, chain_chunk(i - 1, chunks, kBackward));
-#pragma unroll
-            for (int q = 0; q < kChunk; ++q) eb[(k + 1) & 1][q] = w[kBackward ? kChunk - 1 - q : q];
-        }
         fetch_chunk<kBackward>(ep, estep, el[k]);
         __builtin_amdgcn_sched_barrier(0);
     };
     auto run = [&](auto set, int) {
         constexpr int k = decltype(set)::value;
+        double el_d = static_cast<double>(el[k][0]);
 #pragma unroll
-        for (int q = 0; q < kChunk; ++q) advance(eb[k & 1][q], el[k][q]);
-        end_chunk();
-        if (kMode == Mode::kGrad && (k & 1)) checkpoint();
+        for (int q = 0; q < kChunk; ++q) advance(el_d, el[k][q + 1 < kChunk ? q + 1 : q]);
+        if (!(k & 1)) mid_block();
+        else {
+            end_block(k == 3);
+            if (kMode == Mode::kGrad) checkpoint();
+        }
     };
     chain_schedule(count, fetch, run);
 
@@ -1796,15 +1919,15 @@ __device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const
         // the state of every pair, for finish_loss
         if (active) {
             reinterpret_cast<CheckpointState*>(out + m.ab_off)[j] = CheckpointState{v_blank, v_label};
-            out_exponents[m.ab_off + j] = frame;
+            out_exponents[m.ab_off + j] = f.frame;
         }
         return lost;
     }
     if (!kBackward) {
         // p = alpha_{T-1}(2L) + alpha_{T-1}(2L-1), from the lane of pair L (exact, as is the
         // lane below it: see run_chain_log).
-        const double from_below = from_prev_pair(v_label) * scale;
-        if (active && j == L) store_mass(v_blank + from_below, frame, &logp[u], &costs[u]);
+        const double from_below = from_prev_pair(v_label) * f.scale;
+        if (active && j == L) publish_mass(&mass[u * kMassWords], v_blank + from_below, f.frame);
     }
     if (kSync == Sync::kHalo && lost && lane == 0) publish(&chain_err[u], 1);
     return lost;
@@ -1817,17 +1940,15 @@ __device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const
 // lane: the two recursions of a lane are independent within a step and fill each other's issue
 // gaps.  Both pairs share the lane's frame; mass moves up half a lane per step, so the window
 // of a renewal is this lane and the kChunk / 2 lanes below it, and a halo of h lanes stays exact
-// for 2h steps (hand-over every 2h steps: h is a multiple of 4).
+// for 2h steps.
 // The two pairs of a lane are neighbours in the checkpoint's row; where pair B has no label state (the lane of the last
 // pair) its part falls on one of the row's two unused columns.
 
 template <bool kBackward, Mode kMode>
-__device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, const int* __restrict__ labels,
-                                                  const double* __restrict__ emit_blank64,
+__device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, const bool gentle, const int* __restrict__ labels,
                                                   const float* __restrict__ emit_label,
                                                   uint32_t* __restrict__ out, int* __restrict__ out_exponents,
-                                                  double* __restrict__ logp,
-                                                  float* __restrict__ costs, int* __restrict__ chain_err,
+                                                  double* __restrict__ mass, int* __restrict__ chain_err,
                                                   uint32_t* __restrict__ sink, void* lds)
 {
     static_assert(kMode != Mode::kBest, "the maximum recursion runs in the log domain");
@@ -1864,8 +1985,8 @@ __device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, cons
     const int last_wave = waves - 1;
     int budget = m.poll_budget;
     bool lost = false;
-    const int chunks_per_hand_over = 2 * halo / kChunk;
-    int until_hand_over = chunks_per_hand_over;
+    const bool every_block = halo < kBlockFrames;        // (see run_chain_linear; a halo of h lanes lasts 2h steps)
+    const unsigned long long steep = gentle ? 0ull : ~0ull;
     int generation = 0;
     const int wr_slot = (halo > 0 && lane >= 64 - halo) ? lane - (64 - halo) : 0;
     const int rd_slot = lane < halo ? lane : 0;
@@ -1874,8 +1995,7 @@ __device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, cons
     Halo2Wave* const above_lds = halo_wave<Halo2Wave>(lds, wave < last_wave ? wave + 1 : wave);
 
     double va_blank = (ja == 0) ? 1.0 : 0.0, va_label = 0.0, vb_blank = 0.0, vb_label = 0.0;
-    int frame = 0;
-    double scale = 1.0;                                  // 2^(frame of the lane below - frame)
+    ChainFrames<2> f;
     double skip_a_scale = skip_a ? 1.0 : 0.0;
     const double skip_b_one = skip_b ? 1.0 : 0.0;
 
@@ -1895,153 +2015,119 @@ __device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, cons
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     };
     int above_seen = 0;
-    // Hand-over g: first take the halo lanes' exact state from the wavefront below, then pass the
-    // top `halo` lanes up.  An entry is a lane's four values and, in a last word, its frame and
+    const int2* const always = reinterpret_cast<const int2*>(&static_cast<HaloHeader*>(lds)->always_tag);
+    const bool from_below = wave > 0 && lane < halo;
+    // Hand-over g, as in run_chain_linear.  An entry is a lane's four values and, in a last word, its frame and
     // the number g; LDS operations of a wavefront complete in order, so a reader that finds g in
     // the last word finds the values of hand-over g in the others.  A boundary's buffer holds
     // kRing hand-overs.  Before it overwrites the one that held hand-over g - kRing, a wavefront
-    // makes sure that the one above has taken that: a wavefront publishes g only after its own
-    // reads of g (the last one, which has nothing to hand up, publishes a bare number), so what
-    // it has published says how far it has read; that reading was requested at the previous
-    // hand-over.  (With one pair per lane this form was 4 % slower than two counters and two
-    // buffers; with two pairs per lane in a crowded launch it is 9 % faster.)
+    // makes sure that the one above has taken that, which it says by publishing that number itself.
     auto hand_over = [&]() {
         ++generation;
         const int half = generation & (kRing - 1);
-        if (wave > 0) {
-            const int2* const tag = &below_lds->tag[half][rd_slot];
-            const double2* const data = &below_lds->data[half][rd_slot][0];
-            int2 t = read_tag(tag);
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            double2 a = data[0], b = data[1];
-            int ready = uniform(t.y);
-            if (__builtin_expect(ready < generation, 0)) {
-                while (ready < generation && budget > 0) {
-                    --budget;
-                    t = read_tag(tag);
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                    a = data[0];
-                    b = data[1];
-                    ready = uniform(t.y);
-                }
-                lost = lost || ready < generation;
+        const int2* const tag = &below_lds->tag[half][rd_slot];
+        const double2* const data = &below_lds->data[half][rd_slot][0];
+        int2 taken = read_tag(wave > 0 ? tag : always);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        double2 a = data[0], b = data[1];
+        int seen = uniform(above_seen);
+        if (__builtin_expect(seen < generation - kRing, 0)) {
+            while (seen < generation - kRing && budget > 0) {
+                --budget;
+                seen = uniform(generation_of(&above_lds->tag[half][0]));
             }
-            if (lane < halo) {
-                va_blank = a.x;
-                va_label = a.y;
-                vb_blank = b.x;
-                vb_label = b.y;
-                frame = t.x;
-            }
+            lost = lost || seen < generation - kRing;
         }
-        if (wave < last_wave) {
-            int seen = uniform(above_seen);
-            if (__builtin_expect(seen < generation - kRing, 0)) {
-                while (seen < generation - kRing && budget > 0) {
-                    --budget;
-                    seen = uniform(generation_of(&above_lds->tag[half][0]));
-                }
-                lost = lost || seen < generation - kRing;
-            }
-            if (lane >= 64 - halo) {
-                mine_lds->data[half][wr_slot][0] = make_double2(va_blank, va_label);
-                mine_lds->data[half][wr_slot][1] = make_double2(vb_blank, vb_label);
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                write_tag(&mine_lds->tag[half][wr_slot], frame, generation);
-            }
-            above_seen = generation_of(&above_lds->tag[(half + 1) & (kRing - 1)][0]);
-        } else if (wave > 0) {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            if (lane == 0) write_tag(&mine_lds->tag[half][0], 0, generation);
+        if (lane >= 64 - halo) {
+            mine_lds->data[half][wr_slot][0] = make_double2(va_blank, va_label);
+            mine_lds->data[half][wr_slot][1] = make_double2(vb_blank, vb_label);
         }
+        const int frame_up = f.frame;
+        int ready = uniform(taken.y);
+        if (__builtin_expect(ready < generation, 0)) {
+            while (ready < generation && budget > 0) {
+                --budget;
+                taken = read_tag(tag);
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                a = data[0];
+                b = data[1];
+                ready = uniform(taken.y);
+            }
+            lost = lost || ready < generation;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        if (lane >= 64 - halo) write_tag(&mine_lds->tag[half][wr_slot], frame_up, generation);
+        above_seen = generation_of(wave < last_wave ? &above_lds->tag[(half + 1) & (kRing - 1)][0] : always);
+        va_blank = from_below ? a.x : va_blank;
+        va_label = from_below ? a.y : va_label;
+        vb_blank = from_below ? b.x : vb_blank;
+        vb_label = from_below ? b.y : vb_label;
+        f.frame = from_below ? taken.x : f.frame;
+        f.rescale(__ballot(!(fmax(fmax(va_blank, va_label), fmax(vb_blank, vb_label)) > 0.0)));
+        skip_a_scale = skip_a ? f.scale : 0.0;
     };
 
     int prev_lo = 0, prev_hi = 0;
     auto from_lane_below = [&](double mine) { return shift_up(mine, prev_lo, prev_hi); };
-    auto shift_up_int = [](int v) { return __builtin_amdgcn_update_dpp(kNoExponent, v, 0x138, 0xf, 0xf, false); };
-
+    auto top_value = [&]() { return fmax(fmax(va_blank, va_label), fmax(vb_blank, vb_label)); };
     auto renew_frames = [&]() {
-        const double top = fmax(fmax(va_blank, va_label), fmax(vb_blank, vb_label));
-        const int mine = (top > 0.0) ? frame + __builtin_amdgcn_frexp_exp(top) : kNoExponent;
-        int window = mine;
-#pragma unroll
-        for (int k = 0; k < kChunk / 2; ++k) window = window_max_step(window, mine);
-        window = lane_frame(window, mine);
-        const int rise = frame - window;
+        const int rise = f.renew(top_value(), halo > 0 ? halo - 1 : 0);
         va_blank = __builtin_amdgcn_ldexp(va_blank, rise);
         va_label = __builtin_amdgcn_ldexp(va_label, rise);
         vb_blank = __builtin_amdgcn_ldexp(vb_blank, rise);
         vb_label = __builtin_amdgcn_ldexp(vb_label, rise);
-        frame = window;
-        const int down = min(max(shift_up_int(window) - window, -1100), 1023);
-        scale = __builtin_amdgcn_ldexp(1.0, down);
-        skip_a_scale = skip_a ? scale : 0.0;
+        skip_a_scale = skip_a ? f.scale : 0.0;
     };
 
     auto checkpoint = [&]() {
         const CheckpointState state_a{va_blank, va_label}, state_b{vb_blank, vb_label};
         vp[0] = kBackward ? state_b : state_a;
         vp[1] = kBackward ? state_a : state_b;
-        fp[0] = frame;                                   // both pairs of the lane share its frame
-        fp[1] = frame;
+        typedef int Frames __attribute__((ext_vector_type(2), aligned(4)));
+        *reinterpret_cast<Frames*>(fp) = Frames{f.frame, f.frame};       // both pairs of the lane share its frame
         vp += row_step;
         fp += row_step;
     };
-    auto end_chunk = [&]() {
-        if (--until_hand_over == 0) {
-            hand_over();
-            until_hand_over = chunks_per_hand_over;
-        }
-        renew_frames();
+    auto mid_block = [&]() {
+        if (__builtin_expect((f.rough | steep) != 0, 0))
+            if (f.renewal_due(top_value())) renew_frames();
     };
-    // One step.  A lone wavefront on its SIMD issues an instruction every 2 ns, but one that reads the
-    // result of the instruction before it only after 4 ns, and of the one before that after 3 (measured
-    // on gfx950 with chains of dependent v_fma_f64).  The step is therefore written so that no
-    // instruction needs a result younger than two instructions, and the order of the statements is
-    // the order of issue (pin): the sums that do not need the neighbour's value come first, while the
-    // two DPP moves are on their way, and the two pairs' products alternate.
+    auto end_block = [&](bool second) {
+        if (waves > 1 && (second || every_block)) hand_over();
+        if (__builtin_expect(f.renewal_due(top_value()), 0)) renew_frames();
+    };
+    // One step (see run_chain_linear): the pairs' own sums fill the time that the shift takes.
     //   label' = (label + blank + skip * previous label) * emission, as fma(previous, skip, label + blank)
     auto pin = []() { __builtin_amdgcn_sched_barrier(0); };
-    auto advance = [&](double eb_d, float ela, float elb) {
+    auto advance = [&](float ela, float elb) {
 #pragma clang fp contract(off)                           // (a product stays a product: fusing it into the next step's sum would tie the steps together)
         const double prev = from_lane_below(vb_label);
         pin();
         const double ub = vb_blank + vb_label;
         pin();
-        const double ua = va_blank + va_label;
-        pin();
-        const double ib_blank = vb_blank + va_label;
-        pin();
-        const double ela_d = static_cast<double>(ela);
+        const double elb_d = static_cast<double>(elb);
         pin();
         const double ib_label = __builtin_fma(va_label, skip_b_one, ub);
         pin();
-        const double ia_label = __builtin_fma(prev, skip_a_scale, ua);
+        vb_blank = vb_blank + va_label;
         pin();
-        const double ia_blank = __builtin_fma(prev, scale, va_blank);
-        pin();
-        const double elb_d = static_cast<double>(elb);
-        pin();
-        va_label = ia_label * ela_d;
+        const double ua = va_blank + va_label;
         pin();
         vb_label = ib_label * elb_d;
         pin();
-        va_blank = ia_blank * eb_d;
+        const double ela_d = static_cast<double>(ela);
         pin();
-        vb_blank = ib_blank * eb_d;
+        const double ia_label = __builtin_fma(prev, skip_a_scale, ua);
+        pin();
+        va_blank = __builtin_fma(prev, f.scale, va_blank);
+        pin();
+        va_label = ia_label * ela_d;
         pin();
     };
 
     float ela[4][kChunk], elb[4][kChunk];
-    double eb[2][kChunk] = {};
-    auto fetch = [&](auto set, int i) {
+    auto fetch = [&](auto set, int) {
         constexpr int k = decltype(set)::value;
-        if (i > 0) {
-            asm volatile("" : : "s"(eb[k & 1][0]), "s"(eb[k & 1][kChunk - 1]));     // (see run_chain_linear)
-            const double* const w = emit_blank64 + blank_emission_offset(m, chain_chunk(i - 1, chunks, kBackward));
-#pragma unroll
-            for (int q = 0; q < kChunk; ++q) eb[(k + 1) & 1][q] = w[kBackward ? kChunk - 1 - q : q];
-        }
         fetch_chunk<kBackward>(epa, step_a, ela[k]);
         fetch_chunk<kBackward>(epb, step_b, elb[k]);
         __builtin_amdgcn_sched_barrier(0);
@@ -2049,9 +2135,12 @@ __device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, cons
     auto run = [&](auto set, int) {
         constexpr int k = decltype(set)::value;
 #pragma unroll
-        for (int q = 0; q < kChunk; ++q) advance(eb[k & 1][q], ela[k][q], elb[k][q]);
-        end_chunk();
-        if (kMode == Mode::kGrad && (k & 1)) checkpoint();
+        for (int q = 0; q < kChunk; ++q) advance(ela[k][q], elb[k][q]);
+        if (!(k & 1)) mid_block();
+        else {
+            end_block(k == 3);
+            if (kMode == Mode::kGrad) checkpoint();
+        }
     };
     chain_schedule(count, fetch, run);
 
@@ -2060,19 +2149,19 @@ __device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, cons
         CheckpointState* const states = reinterpret_cast<CheckpointState*>(out + m.ab_off);
         if (active) {
             states[ja] = CheckpointState{va_blank, va_label};
-            out_exponents[m.ab_off + ja] = frame;
+            out_exponents[m.ab_off + ja] = f.frame;
         }
         if (active && jb <= L) {
             states[jb] = CheckpointState{vb_blank, vb_label};
-            out_exponents[m.ab_off + jb] = frame;
+            out_exponents[m.ab_off + jb] = f.frame;
         }
         return lost;
     }
     if (!kBackward) {
         // p = alpha_{T-1}(2L) + alpha_{T-1}(2L-1): the blank of pair L and the label of pair L - 1.
         // L even: pair L is this lane's A, pair L - 1 the B of the lane below; L odd: pair L is B.
-        const double from_below = from_lane_below(vb_label) * scale;
-        if (active && (ja == L || jb == L)) store_mass((ja == L) ? va_blank + from_below : vb_blank + va_label, frame, &logp[u], &costs[u]);
+        const double from_below = from_lane_below(vb_label) * f.scale;
+        if (active && (ja == L || jb == L)) publish_mass(&mass[u * kMassWords], ja == L ? va_blank + from_below : vb_blank + va_label, f.frame);
     }
     if (lost && lane == 0) publish(&chain_err[u], 1);
     return lost;
@@ -2110,11 +2199,15 @@ struct LaunchWords {
 //   p = sum over states s of  (sum of alpha over s and its predecessors) * beta(s).
 // A wavefront that has ended counts itself in, and the utterance's last one does the sum, whichever it is: the order of
 // the additions is that of the pairs.  The count carries, in its upper half, how many wavefronts gave up waiting for a
-// neighbour; then the cost is NaN.  `expected`: wavefronts of both chains.
+// neighbour; then the cost is NaN.  `waves`: wavefronts of a chain.
 __device__ __forceinline__ void finish_loss(const Utt& m, const int u, const int* __restrict__ labels, const LatticeOut& lat,
-                                            int* __restrict__ done, float* __restrict__ costs, const int expected, const bool lost)
+                                            const float* __restrict__ emit_blank, double* __restrict__ mass, int* __restrict__ done,
+                                            float* __restrict__ costs, const int waves, const bool lost)
 {
     const int lane = threadIdx.x & 63;
+    // a wavefront of the forward chain's workgroup without a part in the chain sees to the norms meanwhile, where there is one
+    const bool helped = static_cast<int>(blockDim.x) > 64 * waves;
+    const int expected = 2 * waves + (helped ? 1 : 0);
     // (device scope: the chains may run on different dies)
     int before = 0;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
@@ -2128,6 +2221,9 @@ __device__ __forceinline__ void finish_loss(const Utt& m, const int u, const int
     const CheckpointState* const beta = reinterpret_cast<const CheckpointState*>(lat.beta + m.ab_off);
     const int *const fa = lat.alpha_exponents + m.ab_off, *const fb = lat.beta_exponents + m.ab_off;
     const int* const lab = labels + m.lab_off;
+    Norms norms{0.5, 1};
+    if (!helped) norms = norms_of_lane(m, emit_blank);
+    const double log2_norms = helped ? published(&mass[u * kMassWords + kMassNorms]) : 0.0;
     // A lane's sum as sum * 2^top.
     double sum = 0.0;
     int top = kNoExponent;
@@ -2162,12 +2258,20 @@ __device__ __forceinline__ void finish_loss(const Utt& m, const int u, const int
         sum = __builtin_amdgcn_ldexp(sum, max(top - higher, -2000)) + __builtin_amdgcn_ldexp(other, max(other_top - higher, -2000));
         top = higher;
     }
+    if (!helped) norms = norms_of_wave(norms);
     if (lane == 0) {
-        double unused;
-        float cost;
-        mass_and_cost(sum, top, unused, cost);
-        costs[u] = (before >> 16) != 0 || lost ? __uint_as_float(0x7FC00000u) : cost;
+        costs[u] = (before >> 16) != 0 || lost ? __uint_as_float(0x7FC00000u) : cost_of_mass(sum, top, helped ? log2_norms : norms.log2());
     }
+}
+
+// Such a wavefront: leaves the norms and counts itself in.
+__device__ __forceinline__ void help_with_norms(const Utt& m, const int u, const int* __restrict__ labels, const LatticeOut& lat,
+                                                const float* __restrict__ emit_blank, double* __restrict__ mass, int* __restrict__ done,
+                                                float* __restrict__ costs, const int waves)
+{
+    const Norms norms = norms_of_wave(norms_of_lane(m, emit_blank));
+    if ((threadIdx.x & 63) == 0) publish(&mass[u * kMassWords + kMassNorms], norms.log2());
+    finish_loss(m, u, labels, lat, emit_blank, mass, done, costs, waves, false);
 }
 
 // The word that an utterance's chains and the workgroups that wait for them share: wavefronts that have ended, wavefronts
@@ -2179,18 +2283,14 @@ __device__ __forceinline__ bool chains_ended(int done)
     return ((done >> kChainsShift) & 3) == 2 && (done & kField) == ((done >> kWavesShift) & kField);
 }
 // A wavefront of a chain has ended, and everything it has published is out; `waves` of them make the chain, the first says
-// so.  Should somebody have given up waiting, rows of the gradient are missing: the last wavefront to end, which comes after
-// the one that has stored the cost, makes that NaN.
-__device__ __forceinline__ void announce_end(int* done, int waves, float* cost)
+// so.
+__device__ __forceinline__ void announce_end(int* done, int waves)
 {
     // (what was stored the ordinary way must leave the die's cache)
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     const int count = threadIdx.x < 64 ? 1 + (waves << kWavesShift) + (1 << kChainsShift) : 1;
-    if ((threadIdx.x & 63) == 0) {
-        const int now = __hip_atomic_fetch_add(done, count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + count;
-        if ((now & kWaitGivenUp) && chains_ended(now)) publish(cost, __uint_as_float(0x7FC00000u));
-    }
+    if ((threadIdx.x & 63) == 0) __hip_atomic_fetch_add(done, count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // A launch that writes the gradient too: an utterance's second word says which of its chains have been taken, that is, have a
@@ -2214,7 +2314,7 @@ __device__ __forceinline__ int lattice_body(const int chain, const Utt* __restri
                                              const float* __restrict__ emit_blank, const double* __restrict__ emit_blank64,
                                              const float* __restrict__ emit_label,
                                              const LatticeOut lat,
-                                             double* __restrict__ logp, float* __restrict__ costs,
+                                             double* __restrict__ mass, float* __restrict__ costs,
                                              int* __restrict__ chain_err, uint32_t* __restrict__ sink,
                                              void* lds, const LaunchWords& wk)
 {
@@ -2254,8 +2354,9 @@ __device__ __forceinline__ int lattice_body(const int chain, const Utt* __restri
     // Which recursion: the barrier kernel and the maximum recursion have the log domain only;
     // otherwise the flag that the softmax launch may have raised decides.  A linear-domain chain
     // gives one pair or two to a lane as the launcher planned it (two_pairs_per_lane).
-    const bool in_log_domain = kSync == Sync::kBarrier || kMode == Mode::kBest || (m.flags & kUttLogDomain) != 0 ||
-                               rows_flagged(wk.row_flags, u, wk.flag_blocks, m.Tb);
+    const int met = rows_flagged(wk.row_flags, u, wk.flag_blocks, m.Tb);
+    const bool in_log_domain = kSync == Sync::kBarrier || kMode == Mode::kBest || (m.flags & kUttLogDomain) != 0 || (met & kRowsSmall) != 0;
+    const bool gentle = m.rough == 0 && (met & kRowsRough) == 0;
     if (kMode == Mode::kLoss && in_log_domain && !forward) return 0;       // (the forward chain runs all the way)
     const bool two_pairs = kSync == Sync::kHalo && !in_log_domain && (m.flags & kUttTwoPairs) != 0;
     const int waves = two_pairs ? m.waves2 : m.waves;
@@ -2276,9 +2377,15 @@ __device__ __forceinline__ int lattice_body(const int chain, const Utt* __restri
             hl->finished = 0;
             hl->gave_up = 0;
             hl->left = left;
+            hl->always = 0x7FFFFFFF;
+            hl->always_tag[1] = 0x7FFFFFFF;
         }
         __syncthreads();
         if (kFused) left = __builtin_amdgcn_readfirstlane(hl->left);
+        if (kMode == Mode::kLoss && !in_log_domain && forward && static_cast<int>(threadIdx.x >> 6) == waves) {
+            help_with_norms(m, u, labels, lat, emit_blank, mass, wk.done, costs, waves);
+            return 0;
+        }
         if (idle) return left;
     } else if (kSync == Sync::kBarrier) {
         if (idle) {
@@ -2298,6 +2405,10 @@ __device__ __forceinline__ int lattice_body(const int chain, const Utt* __restri
         left = __builtin_amdgcn_readfirstlane(hl->left);
         if (threadIdx.x >= 64) return left;
     }
+    if (kSync == Sync::kNone && kMode == Mode::kLoss && threadIdx.x >= 64) {
+        if (!in_log_domain && forward) help_with_norms(m, u, labels, lat, emit_blank, mass, wk.done, costs, waves);
+        return 0;
+    }
     // (for the gradient, which must know what each chain has left: a word per direction)
     if (kMode == Mode::kGrad && threadIdx.x == 0) publish(&wk.domain[2 * u + (forward ? 0 : 1)], in_log_domain ? 1 : 0);
     if constexpr (kSync != Sync::kBarrier && kMode != Mode::kBest) {
@@ -2306,39 +2417,40 @@ __device__ __forceinline__ int lattice_body(const int chain, const Utt* __restri
             if (two_pairs) {
                 if constexpr (kSync == Sync::kHalo) {
                     if (forward)
-                        lost = run_chain_linear2<false, kMode>(m, u, labels, emit_blank64, emit_label, lat.alpha, lat.alpha_exponents, logp, costs, chain_err, sink, lds);
+                        lost = run_chain_linear2<false, kMode>(m, u, gentle, labels, emit_label, lat.alpha, lat.alpha_exponents, mass, chain_err, sink, lds);
                     else
-                        lost = run_chain_linear2<true, kMode>(m, u, labels, emit_blank64, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
+                        lost = run_chain_linear2<true, kMode>(m, u, gentle, labels, emit_label, lat.beta, lat.beta_exponents, mass, chain_err, sink, lds);
                 }
             } else if (forward) {
-                lost = run_chain_linear<false, kSync, kMode>(m, u, labels, emit_blank64, emit_label, lat.alpha, lat.alpha_exponents, logp, costs, chain_err, sink, lds);
+                lost = run_chain_linear<false, kSync, kMode>(m, u, gentle, labels, emit_label, lat.alpha, lat.alpha_exponents, mass, chain_err, sink, lds);
             } else {
-                lost = run_chain_linear<true, kSync, kMode>(m, u, labels, emit_blank64, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
+                lost = run_chain_linear<true, kSync, kMode>(m, u, gentle, labels, emit_label, lat.beta, lat.beta_exponents, mass, chain_err, sink, lds);
             }
-            if (kMode == Mode::kLoss) finish_loss(m, u, labels, lat, wk.done, costs, 2 * waves, lost);
-            if (kFused) announce_end(&wk.done[u * kDoneStride], waves, &costs[u]);
+            if (kMode == Mode::kLoss) finish_loss(m, u, labels, lat, emit_blank, mass, wk.done, costs, waves, lost);
+            if (kFused) announce_end(&wk.done[u * kDoneStride], waves);
             return left;
         }
     }
     if (forward)
-        run_chain_log<false, kSync, kMode>(m, u, labels, emit_blank, emit_blank64, emit_label, lat.alpha, lat.alpha_exponents, logp, costs, chain_err, sink, lds);
+        run_chain_log<false, kSync, kMode>(m, u, labels, emit_blank, emit_blank64, emit_label, lat.alpha, lat.alpha_exponents, mass, costs, chain_err, sink, lds);
     else if constexpr (kMode != Mode::kLoss)
-        run_chain_log<true, kSync, kMode>(m, u, labels, emit_blank, emit_blank64, emit_label, lat.beta, lat.beta_exponents, logp, costs, chain_err, sink, lds);
-    if (kFused) announce_end(&wk.done[u * kDoneStride], waves, &costs[u]);
+        run_chain_log<true, kSync, kMode>(m, u, labels, emit_blank, emit_blank64, emit_label, lat.beta, lat.beta_exponents, mass, costs, chain_err, sink, lds);
+    if (kFused) announce_end(&wk.done[u * kDoneStride], waves);
     return left;
 }
 
 // grid = one workgroup per entry of `order` (utterance * 2 + direction: 0 forward, 1 backward).
 // blockDim.x = 64 * (most wavefronts any utterance of the batch uses).
 // Variant for batches whose labels all fit one wavefront: no exchange at all.
+// (Cost-only calls: and a second wavefront for the norms.)
 template <Mode kMode>
-__global__ __launch_bounds__(64)
+__global__ __launch_bounds__(kMode == Mode::kLoss ? 128 : 64)
 void ctc_lattice_kernel_w1(const Utt* __restrict__ meta, const int* __restrict__ order,
                            const int* __restrict__ labels, const float* __restrict__ emit_blank,
                            const double* __restrict__ emit_blank64,
                            const float* __restrict__ emit_label,
                            const LatticeOut lat,
-                           double* __restrict__ logp, float* __restrict__ costs,
+                           double* __restrict__ mass, float* __restrict__ costs,
                            int* __restrict__ chain_err, uint32_t* __restrict__ sink, const LaunchWords wk)
 {
     if (kMode == Mode::kGrad && static_cast<int>(blockIdx.x) >= wk.fill.n_chains && wk.fill.defer > 0) {
@@ -2346,7 +2458,7 @@ void ctc_lattice_kernel_w1(const Utt* __restrict__ meta, const int* __restrict__
         return;
     }
     lattice_body<Sync::kNone, kMode>(order[blockIdx.x], meta, labels, emit_blank, emit_blank64, emit_label, lat,
-                                                                   logp, costs, chain_err, sink, nullptr, wk);
+                                                                   mass, costs, chain_err, sink, nullptr, wk);
 }
 
 // Multi-wavefront chains with the halo exchange.
@@ -2357,7 +2469,7 @@ void ctc_lattice_kernel(const Utt* __restrict__ meta, const int* __restrict__ or
                         const double* __restrict__ emit_blank64,
                         const float* __restrict__ emit_label,
                         const LatticeOut lat,
-                        double* __restrict__ logp, float* __restrict__ costs,
+                        double* __restrict__ mass, float* __restrict__ costs,
                         int* __restrict__ chain_err, uint32_t* __restrict__ sink, const LaunchWords wk)
 {
     extern __shared__ double2 halo_lds[];                    // halo_lds_bytes(wavefronts of the workgroup)
@@ -2366,7 +2478,7 @@ void ctc_lattice_kernel(const Utt* __restrict__ meta, const int* __restrict__ or
         return;
     }
     lattice_body<Sync::kHalo, kMode>(order[blockIdx.x], meta, labels, emit_blank, emit_blank64, emit_label, lat,
-                                                                   logp, costs, chain_err, sink, halo_lds, wk);
+                                                                   mass, costs, chain_err, sink, halo_lds, wk);
 }
 
 // Labels too long to leave room for a halo (more than 16 * 63 pairs): 64 pairs per wavefront
@@ -2378,11 +2490,11 @@ void ctc_lattice_kernel_barrier(const Utt* __restrict__ meta, const int* __restr
                                 const double* __restrict__ emit_blank64,
                                 const float* __restrict__ emit_label,
                                 const LatticeOut lat,
-                                double* __restrict__ logp, float* __restrict__ costs,
+                                double* __restrict__ mass, float* __restrict__ costs,
                                 int* __restrict__ chain_err, uint32_t* __restrict__ sink, const LaunchWords wk)
 {
     __shared__ double xch[3][16];                            // (labels by step parity; their origins, two words each)
-    lattice_body<Sync::kBarrier, kMode>(order[blockIdx.x], meta, labels, emit_blank, emit_blank64, emit_label, lat, logp,
+    lattice_body<Sync::kBarrier, kMode>(order[blockIdx.x], meta, labels, emit_blank, emit_blank64, emit_label, lat, mass,
                                                costs, chain_err, sink, &xch[0][0], wk);
 }
 
@@ -2528,7 +2640,7 @@ void ctc_backtrace_kernel(const Utt* __restrict__ meta, const int* __restrict__ 
 // its neighbour owns (an error at the edge moves up one position per frame).
 // A row of one value per lane in LDS, padded so that 16-byte reads of 16 rows meet in no bank; two blocks of a row per frame.
 constexpr int kShareRow = kPiecePositions / 2 + 4, kShareInts = 2 * kBlockFrames * kShareRow;
-constexpr int kBlankInts = 2 * kBlockFrames;
+constexpr int kNormInts = kBlockFrames;
 static_assert(kPieceStep % 32 == 0, "pieces start at multiples of 32 positions (share_product)");
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
@@ -2552,7 +2664,7 @@ __device__ __forceinline__ Utt uniform_record(const Utt& m)
     u.flags = uniform(m.flags);
     u.f_off = static_cast<unsigned>(uniform(static_cast<int>(m.f_off)));
     u.e_cols = uniform(m.e_cols);
-    u.e_direct = uniform(m.e_direct);
+    u.e_direct = static_cast<int16_t>(uniform(m.e_direct));
     u.e_off = uniform64(m.e_off);
     u.ab_off = uniform64(m.ab_off);
     return u;
@@ -2687,11 +2799,11 @@ struct BlockEnds {
 // The shares of the label positions base .. base + 127 in block `block` of the utterance: file(row, share0, share1) for
 // the lane's two positions, row = 0 .. 15 in some order, 0 outside [own_first, own_end).  Shares are without the
 // mantissa of 1 / p and times 2^kScaleLog2.  emissions(h, el0, el1): the lane's label emissions in chunk h of the block.
-// s_blank: the blank's emissions of the block's frames, in LDS.  alpha's high dwords wait in LDS, s_alpha0 and s_alpha1 [row][kShareRow], each lane's in a slot of its own that is free
+// alpha's high dwords wait in LDS, s_alpha0 and s_alpha1 [row][kShareRow], each lane's in a slot of its own that is free
 // again when file is called for the row.  (In registers they cost 32 of them, and the loops over the chunks had to be
 // unrolled: code that runs once per wavefront comes out of memory no faster than data.)
 template <int kScaleLog2, typename Emissions, typename File>
-__device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at, const BlockEnds& ends, const double* s_blank,
+__device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at, const BlockEnds& ends,
                                              const double packed_inverse_p, const int block,
                                              const int own_first, const int own_end, unsigned* s_alpha0, unsigned* s_alpha1,
                                              Emissions&& emissions, File&& file)
@@ -2702,13 +2814,6 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
     const bool has0 = at.has0, has1 = at.has1;
     const double skip0_one = at.skip0 ? 1.0 : 0.0, skip1_one = at.skip1 ? 1.0 : 0.0, skip2_one = at.skip2 ? 1.0 : 0.0;
     float el0[kChunk], el1[kChunk];
-    double eb[kChunk];
-    // (from LDS, the same address in every lane: scalar loads out of memory were four round trips in the middle of it all)
-    auto read_blanks = [&](int h) {
-#pragma unroll
-        for (int q = 0; q < kChunk; ++q) eb[q] = s_blank[h * kChunk + q];
-    };
-
     // The order of the statements is the order of issue (run_chain_linear2): left to itself the compiler put results and
     // their uses next to each other, and a block's recomputation took 3.0 us in place of 2.0.
     auto pin = []() { __builtin_amdgcn_sched_barrier(0); };
@@ -2732,7 +2837,6 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
             }
             const double skip0_scale = skip0_one * s.scale;
             emissions(h, el0, el1);
-            read_blanks(h);
 #pragma unroll
             for (int q = 0; q < kChunk; ++q) {
 #pragma clang fp contract(off)
@@ -2758,10 +2862,8 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
                 pin();
                 s.label1 = n_label1 * el1_d;
                 pin();
-                s.blank0 = n_blank0 * eb[q];
-                pin();
-                s.blank1 = n_blank1 * eb[q];
-                pin();
+                s.blank0 = n_blank0;
+                s.blank1 = n_blank1;
                 s_alpha0[(h * kChunk + q) * kShareRow + lane] = static_cast<unsigned>(__double2hiint(s.label0));
                 s_alpha1[(h * kChunk + q) * kShareRow + lane] = static_cast<unsigned>(__double2hiint(s.label1));
             }
@@ -2787,10 +2889,7 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
         const int exponents = (h == 0 ? alpha_frame0 : alpha_frame1) + s.frame + to_share;
         const int x0 = own0 ? exponents : kNoExponent, x1 = own1 ? exponents : kNoExponent;
         const double skip2_scale = skip2_one * s.scale;
-        if (h == 0) {                                    // (chunk 1's are still there)
-            emissions(h, el0, el1);
-            read_blanks(h);
-        }
+        if (h == 0) emissions(h, el0, el1);              // (chunk 1's are still there)
         unsigned alpha0[kChunk], alpha1[kChunk];
 #pragma unroll
         for (int q = 0; q < kChunk; ++q) {
@@ -2840,10 +2939,8 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
             pin();
             pending_alpha1 = fmin(a1, 0x1p1000);
             pin();
-            s.blank0 = n_blank0 * eb[q];
-            pin();
-            s.blank1 = n_blank1 * eb[q];
-            pin();
+            s.blank0 = n_blank0;
+            s.blank1 = n_blank1;
             pending_beta0 = n_label0;
             pending_beta1 = n_label1;
             pending_row = h * kChunk + q;
@@ -2929,7 +3026,7 @@ __host__ __device__ constexpr int tile_label_ints(int L) { return (L + 31) / 32 
 constexpr int kEmissionRow = 12;
 __host__ __device__ constexpr int tile_emission_ints(int tiles) { return (2 * 16 * tiles + 1) * kEmissionRow; }
 // LDS of one wavefront.
-__host__ __device__ constexpr int tile_lds_ints(int Lmax, int tiles) { return kBlankInts + kShareInts + tile_emission_ints(tiles) + tile_label_ints(Lmax); }
+__host__ __device__ constexpr int tile_lds_ints(int Lmax, int tiles) { return kNormInts + kShareInts + tile_emission_ints(tiles) + tile_label_ints(Lmax); }
 __device__ __forceinline__ void stage_label_bytes(unsigned* s_label, const int* __restrict__ labels, int L)
 {
     for (int w = threadIdx.x & 63; w < tile_label_ints(L); w += 64) {
@@ -2974,7 +3071,7 @@ __device__ __forceinline__ void share_product(float4v (&acc)[kTiles], const unsi
 struct TileArgs {
     void* grads;
     bool bf16;
-    const double* logp;
+    const double* mass;
     const int* chain_err;
     float* costs;
     const int* domain;
@@ -2986,7 +3083,7 @@ struct TileArgs {
     int T, B, A, blank, Lmax;
     int share_blocks;             // narrow
     int rows_per_pass;            // wide
-    int groups;                   // workgroups per utterance
+    int groups;                   // workgroups per utterance: one for its cost (narrow), then those with tiles
     int first_group;              // lattice launch: the first one with a tile
 };
 __device__ __forceinline__ void store_gradient(const TileArgs& g, size_t i, float v)
@@ -2994,39 +3091,57 @@ __device__ __forceinline__ void store_gradient(const TileArgs& g, size_t i, floa
     if (g.bf16) store_elem(static_cast<bf16_t*>(g.grads), i, v);
     else store_elem(static_cast<float*>(g.grads), i, v);
 }
-// By the whole workgroup: waits until utterance b's chains have ended; the same answer in every thread.  The wait is bounded
-// (TileArgs::end_polls and four polls a frame, a frame taking less than one): should it run out, the answer is false, there
-// is nothing to compute rows from, and the utterance's cost is NaN -- by this workgroup, and by the chain that ends last if
-// that is still to come (both go through the utterance's word, so one of them is the later one whatever the order).
+// By a wavefront: waits until utterance b's chains have ended.  The wait is bounded (TileArgs::end_polls and four polls a frame, a
+// frame taking less than one): should it run out, the answer is kNotEnded, there is nothing to compute from, and the utterance's
+// cost is to be NaN: whoever gives up says so in the utterance's word, where whoever does not finds it (kSomebodyGaveUp), since
+// nobody gives up once the chains have ended.
+constexpr int kNotEnded = 0, kEnded = 1, kSomebodyGaveUp = 2;
+__device__ __forceinline__ int chains_awaited(const TileArgs& g, int b, int frames)
+{
+    int* const done = &g.done[b * kDoneStride];
+    auto look = [&]() { return __builtin_amdgcn_readfirstlane(published(done)); };
+    int64_t polls = g.end_polls > 0 ? g.end_polls + 4 * static_cast<int64_t>(frames) : 0;
+    int word = look();
+    for (; !chains_ended(word) && polls > 0; --polls) {
+        __builtin_amdgcn_s_sleep(10);
+        word = look();
+    }
+    if (!chains_ended(word)) {
+        if (tile_thread() == 0) word = __hip_atomic_fetch_or(done, kWaitGivenUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        word = __builtin_amdgcn_readfirstlane(word);
+    }
+    return !chains_ended(word) ? kNotEnded : ((word & kWaitGivenUp) != 0 ? kSomebodyGaveUp : kEnded);
+}
+// The same by the whole workgroup; the same answer in every thread.
 __device__ __forceinline__ bool wait_for_chains(const TileArgs& g, int b, int frames)
 {
     __shared__ int s_ended;
     if (tile_thread() < 64) {
-        int* const done = &g.done[b * kDoneStride];
-        auto look = [&]() { return chains_ended(__builtin_amdgcn_readfirstlane(published(done))); };
-        int64_t polls = g.end_polls > 0 ? g.end_polls + 4 * static_cast<int64_t>(frames) : 0;
-        bool ended = look();
-        for (; !ended && polls > 0; --polls) {
-            __builtin_amdgcn_s_sleep(10);
-            ended = look();
-        }
-        if (!ended) {
-            int word = 0;
-            if (tile_thread() == 0) word = __hip_atomic_fetch_or(done, kWaitGivenUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            ended = chains_ended(__builtin_amdgcn_readfirstlane(word));
-            if (!ended && tile_thread() == 0) publish(&g.costs[b], __uint_as_float(0x7FC00000u));
-        }
+        const int ended = chains_awaited(g, b, frames);
         if (tile_thread() == 0) s_ended = ended;
     }
     __syncthreads();
-    return __builtin_amdgcn_readfirstlane(s_ended) != 0;
+    return __builtin_amdgcn_readfirstlane(s_ended) != kNotEnded;
+}
+// The cost of utterance b, by the first wavefront of a workgroup of its own.
+template <bool kWait>
+__device__ __forceinline__ void utterance_cost(const TileArgs& g, const Utt* __restrict__ meta, const float* __restrict__ emit_blank, int b)
+{
+    if (tile_thread() >= 64) return;
+    const Utt m = uniform_record(meta[b]);
+    if (!(m.flags & kUttRuns)) return;                   // (written by the setup role)
+    const double log2_norms = norms_of_wave(norms_of_lane(m, emit_blank)).log2();
+    const int ended = kWait ? chains_awaited(g, b, m.Tb) : kEnded;
+    const double* const mass = &g.mass[b * kMassWords];
+    const float cost = cost_of_mass(published(&mass[kMassValue]), published(&mass[kMassLog2]), log2_norms);
+    if (tile_thread() == 0) g.costs[b] = ended != kEnded || published(&g.chain_err[b]) != 0 ? __uint_as_float(0x7FC00000u) : cost;
 }
 
 // Workgroup `group` of utterance b: kRowThreads / 64 wavefronts, ceil(blocks of T / (4 / wavefronts per block)) workgroups;
 // LDS 4 tile_lds_ints(Lmax, kTiles) ints.  kTiles: tiles of 16 symbols.
 template <int kTiles, bool kWait>
 __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* __restrict__ meta, const int* __restrict__ labels,
-                                            const double* __restrict__ emit_blank64, const float* __restrict__ emit_label,
+                                            const float* __restrict__ emit_blank, const float* __restrict__ emit_label,
                                             const LatticeOut& lat, uint4v* tile_lds, const int b, const int group)
 {
     const int Tt = g_args.T, B = g_args.B, A = g_args.A, blank = g_args.blank, Lmax = g_args.Lmax;
@@ -3052,16 +3167,16 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
     unsigned* const s_hi = reinterpret_cast<unsigned*>(tile_lds) + wave * tile_lds_ints(Lmax, kTiles);
     unsigned* const s_lo = s_hi + kBlockFrames * kShareRow;
     float* const s_emit = reinterpret_cast<float*>(s_hi + kShareInts);
-    double* const s_blank = reinterpret_cast<double*>(s_emit + tile_emission_ints(kTiles));
-    unsigned* const s_label = reinterpret_cast<unsigned*>(s_blank + kBlockFrames);
-    static_assert((kShareInts + tile_emission_ints(kTiles)) % 4 == 0 && kBlankInts % 4 == 0, "16-byte reads");
+    float* const s_norm = s_emit + tile_emission_ints(kTiles);
+    unsigned* const s_label = reinterpret_cast<unsigned*>(s_norm + kBlockFrames);
+    static_assert((kShareInts + tile_emission_ints(kTiles)) % 4 == 0 && kNormInts % 4 == 0, "16-byte reads");
     // Everything that comes from memory is asked for here, before any of it is used.
     const float4* const emit_in = reinterpret_cast<const float4*>(emit_label + emission_at(m.e_off, A, t0, 0));
     // (the block's 16 A emissions: up to 4 A vectors, 64 lanes; variables of their own, as the array went to scratch memory)
     auto emission_vector = [&](int i) { return emit_in[min(64 * i + lane, 4 * A - 1)]; };
     const float4 emit0 = emission_vector(0), emit1 = emission_vector(1);
     const float4 emit2 = kTiles > 2 ? emission_vector(2) : emit0, emit3 = kTiles > 2 ? emission_vector(3) : emit0;
-    const double blank_emission = emit_blank64[blank_emission_offset(m, 2 * block) + (lane & (kBlockFrames - 1))];
+    const float norm_word = emit_blank[blank_emission_offset(m, 2 * block) + (lane & (kBlockFrames - 1))];
     // (an empty label has no string to look at, and the caller's array may be empty)
     const int first_base = part * kPieceStep;
     const LaneLabels first_labels(L > 0 ? labels + m.lab_off : &meta[b].L, max(L, 1), first_base);
@@ -3071,8 +3186,7 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
     auto load_ends = [&]() {
         ends = BlockEnds::load<kWait>(m, lat, first_labels.p0, block);
         log_domain = in_log_domain<kWait>(g_args.domain, b);
-        packed_inverse_p = kWait ? published(&g_args.logp[b]) : g_args.logp[b];
-        if (group == 0 && threadIdx.x == 0 && published(&g_args.chain_err[b]) != 0) publish(&g_args.costs[b], __uint_as_float(0x7FC00000u));
+        packed_inverse_p = kWait ? published(&g_args.mass[b * kMassWords + kMassInverse]) : g_args.mass[b * kMassWords + kMassInverse];
     };
     if (!kWait) load_ends();
     __builtin_amdgcn_sched_barrier(0);
@@ -3088,7 +3202,7 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
         stage(3, emit3);
     }
     if (lane < 8) s_emit[2 * A * kEmissionRow + lane] = 0.0f;
-    if (lane < kBlockFrames) s_blank[lane] = blank_emission;
+    if (lane < kBlockFrames) s_norm[lane] = frame_norm(norm_word);
     if (kWait) {
         if (!wait_for_chains(g_args, b, m.Tb)) {
             if (part == 0) zero_rows();
@@ -3133,7 +3247,7 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
                 row(at.has0, at.symbol0, el0);
                 row(at.has1, at.symbol1, el1);
             };
-            block_shares<kShareScaleLog2>(m, at, ends, s_blank, packed_inverse_p, block, own_first, own_end, s_hi, s_lo, emissions, file);
+            block_shares<kShareScaleLog2>(m, at, ends, packed_inverse_p, block, own_first, own_end, s_hi, s_lo, emissions, file);
         }
         // LDS operations of one wavefront complete in program order; the fences only keep the
         // compiler from moving them across.
@@ -3158,7 +3272,7 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
     }
     // Result: lane l holds symbol 16 n + l % 16 of frames 4 (l / 16) .. + 3; y is the emission.
     const int tr = t0 + 4 * g;
-    const float scale = static_cast<float>(packed_inverse_p) * (0.5f / (1 << kShareScaleLog2));
+    const float scale = packed_mantissa(packed_inverse_p) * (0.5f / (1 << kShareScaleLog2));
     auto write = [&](auto* grads) {
 #pragma unroll
         for (int n = 0; n < kTiles; ++n) {
@@ -3166,11 +3280,12 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
             if (k >= A) continue;
             auto* out = grads + (static_cast<size_t>(tr) * B + b) * A + k;
             const float4 y = *reinterpret_cast<const float4*>(s_emit + ((g >> 1) * A + k) * kEmissionRow + (g & 1) * 4);
-            const float yv[4] = {y.x, y.y, y.z, y.w};
+            const float4 norm = *reinterpret_cast<const float4*>(s_norm + 4 * g);
+            const float yv[4] = {y.x, y.y, y.z, y.w}, norms[4] = {norm.x, norm.y, norm.z, norm.w};
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const float occupancy = acc[n][i] * scale;
-                const float v = emission_softmax(yv[i]) - (k == blank ? 1.0f - occupancy : occupancy);
+                const float v = emission_softmax(yv[i], norms[i]) - (k == blank ? 1.0f - occupancy : occupancy);
                 if (tr + i < Tt) store_elem(out, static_cast<size_t>(i) * B * A, tr + i < m.Tb ? v : 0.0f);
             }
         }
@@ -3183,11 +3298,12 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
 template <int kTiles>
 __global__ __launch_bounds__(kRowThreads)
 void ctc_gradient_narrow_kernel(const TileArgs args, const Utt* __restrict__ meta, const int* __restrict__ labels,
-                                const double* __restrict__ emit_blank64, const float* __restrict__ emit_label,
+                                const float* __restrict__ emit_blank, const float* __restrict__ emit_label,
                                 const LatticeOut lat)
 {
     extern __shared__ uint4v tile_lds[];
-    narrow_tile<kTiles, false>(args, meta, labels, emit_blank64, emit_label, lat, tile_lds, blockIdx.y, blockIdx.x);
+    if (blockIdx.x == 0) utterance_cost<false>(args, meta, emit_blank, blockIdx.y);
+    else narrow_tile<kTiles, false>(args, meta, labels, emit_blank, emit_label, lat, tile_lds, blockIdx.y, blockIdx.x - 1);
 }
 
 // Larger alphabets: the softmax launch has written y (and zeros); here the columns of the label's symbols and the
@@ -3197,11 +3313,10 @@ void ctc_gradient_narrow_kernel(const TileArgs args, const Utt* __restrict__ met
 // fit).  grid (blocks of T, B); dynamic LDS rows_per_pass * (Lmax + 1) floats.
 __global__ __launch_bounds__(64)
 void ctc_gradient_wide_kernel(const TileArgs g, const Utt* __restrict__ meta, const int* __restrict__ labels,
-                              const float* __restrict__ emit_blank, const double* __restrict__ emit_blank64,
-                              const float* __restrict__ emit_label, const LatticeOut lat)
+                              const float* __restrict__ emit_blank, const float* __restrict__ emit_label, const LatticeOut lat)
 {
     __shared__ unsigned s_alpha[kShareInts];
-    __shared__ double s_blank[kBlockFrames];
+    __shared__ float s_word[kBlockFrames];
     extern __shared__ float s_share[];                   // [rows_per_pass][L + 1]
     const int B = g.B, A = g.A, blank = g.blank, rows_per_pass = g.rows_per_pass;
     const int b = blockIdx.y, lane = threadIdx.x, block = blockIdx.x, t0 = block * kBlockFrames;
@@ -3214,7 +3329,7 @@ void ctc_gradient_wide_kernel(const TileArgs g, const Utt* __restrict__ meta, co
     const int* const link_of = L > 0 ? g.links + m.lab_off : &meta[b].L;
     const LaneLabels first_labels(lab, max(L, 1), 0);
     const int first_link0 = link_of[min(first_labels.p0, max(L, 1) - 1)], first_link1 = link_of[min(first_labels.p1, max(L, 1) - 1)];
-    const double blank_emission = emit_blank64[blank_emission_offset(m, 2 * block) + (lane & (kBlockFrames - 1))];
+    const float norm_word = emit_blank[blank_emission_offset(m, 2 * block) + (lane & (kBlockFrames - 1))];
     // the emissions of the block for one position: [chunk and half]
     struct PositionEmissions { float4 v0, v1, v2, v3; };
     auto emissions_of = [&](bool has, int position) {
@@ -3226,12 +3341,16 @@ void ctc_gradient_wide_kernel(const TileArgs g, const Utt* __restrict__ meta, co
     PositionEmissions emit0 = emissions_of(first_labels.has0, first_labels.p0), emit1 = emissions_of(first_labels.has1, first_labels.p1);
     BlockEnds ends = BlockEnds::load<false>(m, lat, first_labels.p0, block);
     const bool log_domain = in_log_domain<false>(g.domain, b);
-    const double packed_inverse_p = g.logp[b];
-    const bool gave_up = g.chain_err[b] != 0;
+    const double packed_inverse_p = g.mass[b * kMassWords + kMassInverse];
     __builtin_amdgcn_sched_barrier(0);
-    if (lane < kBlockFrames) s_blank[lane] = blank_emission;
-    if (t0 == 0 && lane == 0 && gave_up) g.costs[b] = __uint_as_float(0x7FC00000u);
-    const float inverse_p = static_cast<float>(packed_inverse_p);
+    if (lane < kBlockFrames) s_word[lane] = norm_word;
+    if (t0 == 0) {
+        const double log2_norms = norms_of_wave(norms_of_lane(m, emit_blank)).log2();
+        if (lane == 0)
+            g.costs[b] = g.chain_err[b] != 0 ? __uint_as_float(0x7FC00000u)
+                                             : cost_of_mass(g.mass[b * kMassWords + kMassValue], g.mass[b * kMassWords + kMassLog2], log2_norms);
+    }
+    const float inverse_p = packed_mantissa(packed_inverse_p);
     for (int first = 0; first < kBlockFrames; first += rows_per_pass) {
         for_pieces(L, 0, 1, [&](int base, int own_first, int own_end) {
             LaneLabels at = first_labels;
@@ -3262,7 +3381,7 @@ void ctc_gradient_wide_kernel(const TileArgs g, const Utt* __restrict__ meta, co
                     take(emit0, el0);
                     take(emit1, el1);
                 };
-                block_shares<0>(m, at, ends, s_blank, packed_inverse_p, block, own_first, own_end, s_alpha,
+                block_shares<0>(m, at, ends, packed_inverse_p, block, own_first, own_end, s_alpha,
                                 s_alpha + kBlockFrames * kShareRow, emissions, file);
             }
         });
@@ -3292,6 +3411,7 @@ void ctc_gradient_wide_kernel(const TileArgs g, const Utt* __restrict__ meta, co
         const float* const y_row = emit_label + emission_at(m.e_off, L, min(t, m.Tb - 1), 0);
         auto entry = [&](int i) { return s_alpha[2 * min(i, symbols - 1)]; };
         auto position = [](unsigned word) { return static_cast<int>(word >> 10 & 3) | static_cast<int>(word >> 22) << 2; };
+        const float word_of_frame = s_word[first + min(row, rows_per_pass - 1)], norm = frame_norm(word_of_frame);
         float sum = 0.0f;
         if (symbols > 0) {
             unsigned word = entry(lane >> 4);
@@ -3305,7 +3425,7 @@ void ctc_gradient_wide_kernel(const TileArgs g, const Utt* __restrict__ meta, co
                 float o = share[slot];
                 for (int k = 1; k < count; ++k) o += share[slot + k];
                 if (i < symbols && has_row) {
-                    store_gradient(g, out + s_alpha[2 * i + 1], emission_softmax(y) - o);
+                    store_gradient(g, out + s_alpha[2 * i + 1], emission_softmax(y, norm) - o);
                     sum += o;
                 }
                 word = next_word;
@@ -3316,7 +3436,7 @@ void ctc_gradient_wide_kernel(const TileArgs g, const Utt* __restrict__ meta, co
         sum += __shfl_xor(sum, 16);
         sum += __shfl_xor(sum, 32);
         if (has_row && lane < kBlockFrames)
-            store_gradient(g, out + blank, emission_softmax(emit_blank[static_cast<size_t>(kBlankSlack) + m.f_off + t]) - (1.0f - sum));
+            store_gradient(g, out + blank, blank_softmax(word_of_frame) - (1.0f - sum));
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
 }
@@ -3369,7 +3489,7 @@ struct FusedArgs {
     const double* emit_blank64;
     const float* emit_label;
     LatticeOut lat;
-    double* logp;
+    double* mass;
     float* costs;
     int* chain_err;
     uint32_t* sink;
@@ -3390,22 +3510,23 @@ __global__ __launch_bounds__(64 * kFusedWaves)
 void ctc_lattice_gradient_kernel(const Utt* __restrict__ meta, const int* __restrict__ order,
                                  const int* __restrict__ labels, const float* __restrict__ emit_blank,
                                  const double* __restrict__ emit_blank64, const float* __restrict__ emit_label,
-                                 const LatticeOut lat, double* __restrict__ logp, float* __restrict__ costs,
+                                 const LatticeOut lat, double* __restrict__ mass, float* __restrict__ costs,
                                  int* __restrict__ chain_err, uint32_t* __restrict__ sink, const LaunchWords wk, const TileArgs tiles)
 {
     extern __shared__ uint4v fused_lds[];
     const int index = static_cast<int>(blockIdx.x);
     if (index < tiles.first_group) {
         __builtin_amdgcn_s_setprio(3);
-        int left = lattice_body<kSync, Mode::kGrad, true>(order[index], meta, labels, emit_blank, emit_blank64, emit_label, lat, logp,
+        int left = lattice_body<kSync, Mode::kGrad, true>(order[index], meta, labels, emit_blank, emit_blank64, emit_label, lat, mass,
                                                           costs, chain_err, sink, fused_lds, wk);
         if (__builtin_expect(left == 0, 1) || threadIdx.x >= kRowThreads) return;
         __builtin_amdgcn_s_setprio(0);
         do {
             __syncthreads();
             const FusedArgs& a = fused_args();
-            const int tile = left - 1, rank = tile / a.tiles.groups, b = __builtin_amdgcn_readfirstlane(a.tiles.by_end[rank]);
-            narrow_tile<kTiles, true>(a.tiles, a.meta, a.labels, a.emit_blank64, a.emit_label, a.lat, fused_lds, b, tile - rank * a.tiles.groups);
+            const int tile = left - 1, rank = tile / a.tiles.groups, b = __builtin_amdgcn_readfirstlane(a.tiles.by_end[rank]), group = tile - rank * a.tiles.groups;
+            if (group == 0) utterance_cost<true>(a.tiles, a.meta, a.emit_blank, b);
+            else narrow_tile<kTiles, true>(a.tiles, a.meta, a.labels, a.emit_blank, a.emit_label, a.lat, fused_lds, b, group - 1);
             left = __builtin_amdgcn_readfirstlane(published(&a.tiles.left[tile]));
         } while (left != 0);
     } else {
@@ -3414,9 +3535,10 @@ void ctc_lattice_gradient_kernel(const Utt* __restrict__ meta, const int* __rest
         const int flags = __builtin_amdgcn_readfirstlane(meta[b].flags), frames = __builtin_amdgcn_readfirstlane(meta[b].Tb);
         const int sharing = tiles.share_blocks ? block_waves(__builtin_amdgcn_readfirstlane(meta[b].L)) : 1;
         if (threadIdx.x >= kRowThreads) return;          // (workgroups as large as the longest label's chains)
-        const bool waits = (flags & kUttRuns) && group * (kRowThreads / 64 / sharing) * kBlockFrames < frames;
+        const bool waits = (flags & kUttRuns) && (group - 1) * (kRowThreads / 64 / sharing) * kBlockFrames < frames;
         if (waits && !chains_taken(tiles, b, tile)) return;
-        narrow_tile<kTiles, true>(tiles, meta, labels, emit_blank64, emit_label, lat, fused_lds, b, group);
+        if (group == 0) utterance_cost<true>(tiles, meta, emit_blank, b);
+        else narrow_tile<kTiles, true>(tiles, meta, labels, emit_blank, emit_label, lat, fused_lds, b, group - 1);
     }
 }
 
@@ -3495,7 +3617,7 @@ int launch_softmax(const Launch& p, void* stream)
         if (p.A <= kDirectMaxA && p.folded) {
             // the smallest alphabets, host metadata: the launch reads the pinned image itself
             const dim3 grid((p.T + kFlagFrames - 1) / kFlagFrames + sa.parts, p.B);
-            const size_t lds = static_cast<size_t>(kFlagFrames) * p.A * sizeof(float);
+            const size_t lds = static_cast<size_t>(kFlagFrames) * (p.A + 1) * sizeof(float);
             const NarrowImage image{static_cast<const int*>(p.host_image), static_cast<int>(p.lay.labels / 4),
                                     static_cast<int>(p.lay.labels8 / 4), static_cast<int>(p.lay.labels8 / 4), p.lay.labels8,
                                     reinterpret_cast<int*>(p.ws + p.lay.labels)};
@@ -3503,7 +3625,7 @@ int launch_softmax(const Launch& p, void* stream)
             NarrowArgs args;
             NarrowRows& rows_of = args.rows;
             NarrowDevice dv{};
-            if (p.dev_label_lengths) args.plans = plans().table[p.crowded][emission_layout(p.A) == kEmitSymbols];
+            if (p.dev_label_lengths) args.plans = plans().table[p.crowded];
             if (p.dev_label_lengths)
                 dv = NarrowDevice{p.labels, p.dev_label_lengths, p.dev_input_lengths, meta, reinterpret_cast<int*>(p.ws + p.lay.order),
                                   reinterpret_cast<int*>(p.ws + p.lay.status), p.max_label, p.poll_budget,
@@ -3526,7 +3648,7 @@ int launch_softmax(const Launch& p, void* stream)
                                    args, dv, p.T, p.B, p.A, p.blank);
         } else if (p.A <= kDirectMaxA) {
             const dim3 grid((p.T + 63) / 64 + 1, p.B);
-            const size_t lds = static_cast<size_t>(64) * p.A * sizeof(float);
+            const size_t lds = static_cast<size_t>(64) * (p.A + 1) * sizeof(float);
             if (f32)
                 hipLaunchKernelGGL(ctc_softmax_symbols_kernel<float>, grid, block, lds, s, static_cast<const float*>(p.x), meta,
                                    emit_blank, emit_label, sa, p.B, p.A, p.blank);
@@ -3575,7 +3697,7 @@ static TileArgs tile_args(const Launch& p, size_t* lds)
     TileArgs g{};
     g.grads = p.grads;
     g.bf16 = p.dtype != CTC_DTYPE_F32;
-    g.logp = reinterpret_cast<const double*>(p.ws + p.lay.logp);
+    g.mass = reinterpret_cast<const double*>(p.ws + p.lay.mass);
     g.chain_err = reinterpret_cast<const int*>(p.ws + p.lay.chain_err);
     g.costs = p.costs;
     g.domain = reinterpret_cast<const int*>(p.ws + p.lay.domain);
@@ -3598,7 +3720,7 @@ static TileArgs tile_args(const Launch& p, size_t* lds)
         g.rows_per_pass = static_cast<size_t>(kBlockFrames) * (p.max_label + 1) * sizeof(float) <= (size_t(60) << 10) ? kBlockFrames : kBlockFrames / 2;
         *lds = static_cast<size_t>(g.rows_per_pass) * (p.max_label + 1) * sizeof(float);
     }
-    g.groups = (blocks + per_group - 1) / per_group;
+    g.groups = (blocks + per_group - 1) / per_group + (p.A <= kDirectMaxA ? 1 : 0);
     return g;
 }
 
@@ -3613,9 +3735,9 @@ int launch_lattice(const Launch& p, void* stream)
     auto* emit_label = reinterpret_cast<const float*>(p.ws + p.lay.emit_label);
     auto* sink = reinterpret_cast<uint32_t*>(p.ws + p.lay.sink);
     const LatticeOut lat = lattice_blocks(p);
-    auto* logp = reinterpret_cast<double*>(p.ws + p.lay.logp);
+    auto* mass = reinterpret_cast<double*>(p.ws + p.lay.mass);
     auto* chain_err = reinterpret_cast<int*>(p.ws + p.lay.chain_err);
-    const size_t lds_bytes = (p.max_waves > 1 && !p.needs_barrier) ? halo_lds_bytes(p.max_waves) : 0;
+    const size_t lds_bytes = (p.max_waves > 1 && !p.needs_barrier) ? halo_lds_bytes(std::min(p.max_waves + 1, 16)) : 0;
     int n_groups = std::max(p.n_chains, 1);
     LaunchWords wk{};
     wk.row_flags = p.folded ? reinterpret_cast<const int*>(p.ws + p.lay.row_flags) : nullptr;
@@ -3648,7 +3770,7 @@ int launch_lattice(const Launch& p, void* stream)
 #define CTC_LAUNCH_FUSED(SYNC, TILES)                                                              \
     hipLaunchKernelGGL((ctc_lattice_gradient_kernel<SYNC, TILES>), grid, block, lds, s, meta, order, labels, emit_blank,   \
                        reinterpret_cast<const double*>(p.ws + p.lay.emit_blank64), emit_label,                \
-                       lat, logp, p.costs, chain_err, sink, wk, tiles)
+                       lat, mass, p.costs, chain_err, sink, wk, tiles)
 #define CTC_LAUNCH_FUSED_TILES(SYNC)                                                               \
     do {                                                                                           \
         if (p.A <= 32) CTC_LAUNCH_FUSED(SYNC, 2);                                             \
@@ -3661,11 +3783,13 @@ int launch_lattice(const Launch& p, void* stream)
 #undef CTC_LAUNCH_FUSED_TILES
 #undef CTC_LAUNCH_FUSED
     }
-    const dim3 grid(n_groups), block(64 * p.max_waves);
+    // (cost-only calls: one wavefront more than the longest chain needs, for the norms)
+    const int waves = p.mode == Mode::kLoss && !p.needs_barrier ? std::min(p.max_waves + 1, 16) : p.max_waves;
+    const dim3 grid(n_groups), block(64 * waves);
 #define CTC_LAUNCH_LATTICE(KERNEL)                                                                 \
     hipLaunchKernelGGL(KERNEL, grid, block, lds_bytes, s, meta, order, labels, emit_blank,                 \
                        reinterpret_cast<const double*>(p.ws + p.lay.emit_blank64), emit_label,            \
-                       lat, logp, p.costs, chain_err, sink, wk)
+                       lat, mass, p.costs, chain_err, sink, wk)
 #define CTC_LAUNCH_LATTICE_KERNEL(KERNEL)                                                           \
     do {                                                                                           \
         if (p.mode == Mode::kLoss) CTC_LAUNCH_LATTICE((KERNEL<Mode::kLoss>));                      \
@@ -3702,7 +3826,6 @@ int launch_gradient(const Launch& p, void* stream)
 {
     auto* meta = reinterpret_cast<const Utt*>(p.ws + p.lay.meta);
     auto* emit_blank = reinterpret_cast<const float*>(p.ws + p.lay.emit_blank);
-    auto* emit_blank64 = reinterpret_cast<const double*>(p.ws + p.lay.emit_blank64);
     auto* emit_label = reinterpret_cast<const float*>(p.ws + p.lay.emit_label);
     auto s = static_cast<hipStream_t>(stream);
     size_t lds;
@@ -3710,13 +3833,13 @@ int launch_gradient(const Launch& p, void* stream)
     const dim3 grid(args.groups, p.B), block(p.A > kDirectMaxA ? 64 : kRowThreads);
     return checked_launch([&] {
         if (p.A > kDirectMaxA)
-            hipLaunchKernelGGL(ctc_gradient_wide_kernel, grid, block, lds, s, args, meta, p.labels, emit_blank, emit_blank64, emit_label,
+            hipLaunchKernelGGL(ctc_gradient_wide_kernel, grid, block, lds, s, args, meta, p.labels, emit_blank, emit_label,
                                lattice_blocks(p));
         else if (p.A <= 32)
-            hipLaunchKernelGGL(ctc_gradient_narrow_kernel<2>, grid, block, lds, s, args, meta, p.labels, emit_blank64, emit_label,
+            hipLaunchKernelGGL(ctc_gradient_narrow_kernel<2>, grid, block, lds, s, args, meta, p.labels, emit_blank, emit_label,
                                lattice_blocks(p));
         else
-            hipLaunchKernelGGL(ctc_gradient_narrow_kernel<4>, grid, block, lds, s, args, meta, p.labels, emit_blank64, emit_label,
+            hipLaunchKernelGGL(ctc_gradient_narrow_kernel<4>, grid, block, lds, s, args, meta, p.labels, emit_blank, emit_label,
                                lattice_blocks(p));
     });
 }

@@ -2798,7 +2798,8 @@ struct BlockEnds {
 
 // The shares of the label positions base .. base + 127 in block `block` of the utterance: file(row, share0, share1) for
 // the lane's two positions, row = 0 .. 15 in some order, 0 outside [own_first, own_end).  Shares are without the
-// mantissa of 1 / p and times 2^kScaleLog2.  emissions(h, el0, el1): the lane's label emissions in chunk h of the block.
+// mantissa of 1 / p and times 2^kScaleLog2.  emissions(i, el0, el1): the lane's label emissions in the block's chunk 0, 1 and 0
+// again, for i = 0, 1 and 2 in turn.
 // alpha's high dwords wait in LDS, s_alpha0 and s_alpha1 [row][kShareRow], each lane's in a slot of its own that is free
 // again when file is called for the row.  (In registers they cost 32 of them, and the loops over the chunks had to be
 // unrolled: code that runs once per wavefront comes out of memory no faster than data.)
@@ -2829,14 +2830,15 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
         int prev_lo = 0, prev_hi = 0;
         renew_pairs<false>(s, ends.fa0, ends.fa1);
         alpha_frame0 = s.frame;
+        emissions(0, el0, el1);
 #pragma unroll 1
         for (int h = 0; h < 2; ++h) {
             if (h) {
                 renew_pairs<false>(s, s.frame, s.frame);
                 alpha_frame1 = s.frame;
+                emissions(1, el0, el1);
             }
             const double skip0_scale = skip0_one * s.scale;
-            emissions(h, el0, el1);
 #pragma unroll
             for (int q = 0; q < kChunk; ++q) {
 #pragma clang fp contract(off)
@@ -2889,7 +2891,7 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
         const int exponents = (h == 0 ? alpha_frame0 : alpha_frame1) + s.frame + to_share;
         const int x0 = own0 ? exponents : kNoExponent, x1 = own1 ? exponents : kNoExponent;
         const double skip2_scale = skip2_one * s.scale;
-        if (h == 0) emissions(h, el0, el1);              // (chunk 1's are still there)
+        if (h == 0) emissions(2, el0, el1);              // (chunk 1's are still there)
         unsigned alpha0[kChunk], alpha1[kChunk];
 #pragma unroll
         for (int q = 0; q < kChunk; ++q) {
@@ -3082,7 +3084,7 @@ struct TileArgs {
     const int* by_end;            // ... the utterances, those first whose chains end first
     int T, B, A, blank, Lmax;
     int share_blocks;             // narrow
-    int rows_per_pass;            // wide
+    int waves, alpha_at;          // wide
     int groups;                   // workgroups per utterance: one for its cost (narrow), then those with tiles
     int first_group;              // lattice launch: the first one with a tile
 };
@@ -3237,7 +3239,8 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
                 at = LaneLabels(labels + m.lab_off, L, base);
                 ends = BlockEnds::load<kWait>(m, lat, at.p0, block);
             }
-            auto emissions = [&](int h, float (&el0)[kChunk], float (&el1)[kChunk]) {
+            auto emissions = [&](int i, float (&el0)[kChunk], float (&el1)[kChunk]) {
+                const int h = i & 1;
                 auto row = [&](bool has, int symbol, float (&el)[kChunk]) {
                     const float4* v = reinterpret_cast<const float4*>(s_emit + (has ? h * A + symbol : 2 * A) * kEmissionRow);
                     const float4 x = v[0], y = v[1];
@@ -3307,137 +3310,173 @@ void ctc_gradient_narrow_kernel(const TileArgs args, const Utt* __restrict__ met
 }
 
 // Larger alphabets: the softmax launch has written y (and zeros); here the columns of the label's symbols and the
-// blank's are corrected.  A wavefront per block; the shares go to LDS in slot order (the positions of a symbol next to
-// each other, setup_role), and the lane of a symbol's first occurrence adds up its run: one writer per symbol and a
-// fixed order.  `rows_per_pass` frames of a block at a time (16, or 8 where the longest label's shares of 16 frames do not
-// fit).  grid (blocks of T, B); dynamic LDS rows_per_pass * (Lmax + 1) floats.
-__global__ __launch_bounds__(64)
+// blank's are corrected.  A workgroup per block.  Its wavefronts take the label's pieces; the shares go to LDS in slot order
+// (the positions of a symbol next to each other, setup_role), and the lane of a symbol and frame adds up its run: one writer
+// per symbol and a fixed order.  The last wavefront, if it has no piece, lists the symbols meanwhile.  grid (B, blocks of T);
+// LDS: wide_lds_bytes.
+// What bounds it: in launches of up to a block per SIMD (64 utterances of 500 frames: 1140) the time of the slowest block, beyond
+// that the issue of the recomputation.  With a wavefront to a block a block took 7 to 25 us (loads 2, a piece 4.5, sums 1 to 10),
+// and 171 registers left room for three wavefronts on a SIMD.  Two wavefronts share the sums, four the pieces too; a piece's
+// operands have one set of registers, whichever piece it is (101: five wavefronts), and take 2.9 us.  64 x 500 frames, 750
+// symbols: 89.3 -> 82.7 us a call; 512 x 500, 300 symbols: 397 -> 346; 400 x 500, 80 symbols: 303 -> 260; 32 x 1400, labels of up to
+// 500 symbols: 288 -> 248.  Labels of one piece take two wavefronts (64 x 500, 6000 symbols, bf16: 161.0 us; with four 162.7).
+// Neighbouring workgroups are different utterances, one further on from block to block to each: a compute unit gets every n-th
+// workgroup, and with an utterance's blocks side by side some got first blocks only and others the last ones, which many utterances
+// do not have (one wavefront per block, 512 x 500 frames: 397 us, so 364).
+constexpr int kWideWaves = 4;
+// Its LDS: the list of symbols, then the shares [slot][frame] and a slot for those that a wavefront forms for its neighbour's
+// positions, then alpha for each wavefront with a piece.
+constexpr int kSharePitch = kBlockFrames + 1;
+constexpr int wide_alpha_at(int Lmax) { return (2 * Lmax + kSharePitch * (Lmax + 1) + 3) / 4 * 4; }
+constexpr size_t wide_lds_bytes(int Lmax, int waves)
+{
+    return (static_cast<size_t>(wide_alpha_at(Lmax)) + std::min(waves, std::max(label_pieces(Lmax), 1)) * kShareInts) * sizeof(unsigned);
+}
+__global__ __launch_bounds__(64 * kWideWaves)
 void ctc_gradient_wide_kernel(const TileArgs g, const Utt* __restrict__ meta, const int* __restrict__ labels,
                               const float* __restrict__ emit_blank, const float* __restrict__ emit_label, const LatticeOut lat)
 {
-    __shared__ unsigned s_alpha[kShareInts];
-    __shared__ float s_word[kBlockFrames];
-    extern __shared__ float s_share[];                   // [rows_per_pass][L + 1]
-    const int B = g.B, A = g.A, blank = g.blank, rows_per_pass = g.rows_per_pass;
-    const int b = blockIdx.y, lane = threadIdx.x, block = blockIdx.x, t0 = block * kBlockFrames;
+    __shared__ float s_word[kBlockFrames], s_sum[kWideWaves * kBlockFrames];
+    __shared__ int s_symbols;
+    extern __shared__ uint4v wide_lds[];
+    const int B = g.B, A = g.A, blank = g.blank;
+    const int lane = threadIdx.x & 63, block = blockIdx.y, t0 = block * kBlockFrames;
+    const int b = static_cast<int>((blockIdx.x + 3u * block) % static_cast<unsigned>(B));      // (three: neighbours change dies too)
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
     const Utt m = uniform_record(meta[b]);
     if (!(m.flags & kUttRuns) || t0 >= m.Tb) return;
-    // Everything that comes from memory for the first piece is asked for here, before any of it is used: a launch of this
-    // kernel lasts not much longer than one block takes.
-    const int L = m.L, row_pitch = L + 1;
+    unsigned* const s_list = reinterpret_cast<unsigned*>(wide_lds);
+    float* const s_share = reinterpret_cast<float*>(s_list + 2 * g.Lmax);
+    unsigned* const s_alpha = s_list + g.alpha_at + wave * kShareInts;
+    const int L = m.L;
     const int* const lab = L > 0 ? labels + m.lab_off : &meta[b].L;      // (an empty label has no string to look at)
     const int* const link_of = L > 0 ? g.links + m.lab_off : &meta[b].L;
-    const LaneLabels first_labels(lab, max(L, 1), 0);
-    const int first_link0 = link_of[min(first_labels.p0, max(L, 1) - 1)], first_link1 = link_of[min(first_labels.p1, max(L, 1) - 1)];
-    const float norm_word = emit_blank[blank_emission_offset(m, 2 * block) + (lane & (kBlockFrames - 1))];
-    // the emissions of the block for one position: [chunk and half]
-    struct PositionEmissions { float4 v0, v1, v2, v3; };
-    auto emissions_of = [&](bool has, int position) {
-        const float* const p = emit_label + label_emission_offset(m, has, 0, position, 2 * block, kZeroEmission);
-        const float* const q = p + label_emission_step(m, has, false);
-        auto at4 = [](const float* w) { return *reinterpret_cast<const float4*>(w); };
-        return PositionEmissions{at4(p), at4(p + 4), at4(q), at4(q + 4)};
-    };
-    PositionEmissions emit0 = emissions_of(first_labels.has0, first_labels.p0), emit1 = emissions_of(first_labels.has1, first_labels.p1);
-    BlockEnds ends = BlockEnds::load<false>(m, lat, first_labels.p0, block);
-    const bool log_domain = in_log_domain<false>(g.domain, b);
-    const double packed_inverse_p = g.mass[b * kMassWords + kMassInverse];
-    __builtin_amdgcn_sched_barrier(0);
-    if (lane < kBlockFrames) s_word[lane] = norm_word;
-    if (t0 == 0) {
-        const double log2_norms = norms_of_wave(norms_of_lane(m, emit_blank)).log2();
-        if (lane == 0)
-            g.costs[b] = g.chain_err[b] != 0 ? __uint_as_float(0x7FC00000u)
-                                             : cost_of_mass(g.mass[b * kMassWords + kMassValue], g.mass[b * kMassWords + kMassLog2], log2_norms);
-    }
-    const float inverse_p = packed_mantissa(packed_inverse_p);
-    for (int first = 0; first < kBlockFrames; first += rows_per_pass) {
-        for_pieces(L, 0, 1, [&](int base, int own_first, int own_end) {
-            LaneLabels at = first_labels;
-            int link0 = first_link0, link1 = first_link1;
-            if (base + first > 0) {
-                at = LaneLabels(lab, L, base);
-                link0 = link_of[min(at.p0, L - 1)];
-                link1 = link_of[min(at.p1, L - 1)];
-                ends = BlockEnds::load<false>(m, lat, at.p0, block);
-                emit0 = emissions_of(at.has0, at.p0);
-                emit1 = emissions_of(at.has1, at.p1);
-            }
+    if (threadIdx.x < kBlockFrames) s_word[lane] = emit_blank[blank_emission_offset(m, 2 * block) + lane];
+    const int pieces = label_pieces(L);
+    if (wave < pieces) {
+        // Everything that comes from memory for a piece is asked for at once, before any of it is used.
+        LaneLabels at(lab, L, wave * kPieceStep);
+        int link0, link1;
+        struct ChunkEmissions { float4 v0, v1; };
+        ChunkEmissions emit00, emit01, emit10, emit11;   // [position][chunk]
+        BlockEnds ends;
+        auto chunk_emissions = [&](bool has, int position, int h) {
+            const float4* const p = reinterpret_cast<const float4*>(emit_label + label_emission_offset(m, has, 0, position, 2 * block + h, kZeroEmission));
+            return ChunkEmissions{p[0], p[1]};
+        };
+        auto load = [&]() {
+            link0 = link_of[min(at.p0, L - 1)];
+            link1 = link_of[min(at.p1, L - 1)];
+            emit00 = chunk_emissions(at.has0, at.p0, 0);
+            emit10 = chunk_emissions(at.has1, at.p1, 0);
+            emit01 = chunk_emissions(at.has0, at.p0, 1);
+            emit11 = chunk_emissions(at.has1, at.p1, 1);
+            ends = BlockEnds::load<false>(m, lat, at.p0, block);
+        };
+        load();
+        const bool log_domain = in_log_domain<false>(g.domain, b);
+        const double packed_inverse_p = g.mass[b * kMassWords + kMassInverse];
+        __builtin_amdgcn_sched_barrier(0);
+        const float inverse_p = packed_mantissa(packed_inverse_p);
+        for (int i = wave;;) {
+            const int own_first = i == 0 ? 0 : i * kPieceStep + kPieceHalo, own_end = i == pieces - 1 ? L : (i + 1) * kPieceStep + kPieceHalo;
             const bool own0 = at.p0 >= own_first && at.p0 < own_end, own1 = at.p1 >= own_first && at.p1 < own_end;
-            float *const share0 = s_share + (link0 & kLinkSlotMask), *const share1 = s_share + (link1 & kLinkSlotMask);
+            float* const share0 = s_share + (own0 ? link0 & kLinkSlotMask : L) * kSharePitch;
+            float* const share1 = s_share + (own1 ? link1 & kLinkSlotMask : L) * kSharePitch;
             auto file = [&](int row, float x0, float x1) {
-                const int r = row - first;
-                if (r < 0 || r >= rows_per_pass) return;
-                if (own0) share0[r * row_pitch] = x0 * inverse_p;
-                if (own1) share1[r * row_pitch] = x1 * inverse_p;
+                share0[row] = x0 * inverse_p;
+                share1[row] = x1 * inverse_p;
             };
-            if (log_domain) block_shares_log<0, 2>(m, lat, packed_inverse_p, block, base, own_first, own_end, file);
+            if (log_domain) block_shares_log<0, 2>(m, lat, packed_inverse_p, block, i * kPieceStep, own_first, own_end, file);
             else {
-                auto emissions = [&](int h, float (&el0)[kChunk], float (&el1)[kChunk]) {
-                    auto take = [&](const PositionEmissions& e, float (&el)[kChunk]) {
-                        el[0] = h ? e.v2.x : e.v0.x; el[1] = h ? e.v2.y : e.v0.y; el[2] = h ? e.v2.z : e.v0.z; el[3] = h ? e.v2.w : e.v0.w;
-                        el[4] = h ? e.v3.x : e.v1.x; el[5] = h ? e.v3.y : e.v1.y; el[6] = h ? e.v3.z : e.v1.z; el[7] = h ? e.v3.w : e.v1.w;
+                // (the first chunk's are read once more when the second's have been taken: 16 registers)
+                auto emissions = [&](int k, float (&el0)[kChunk], float (&el1)[kChunk]) {
+                    auto get = [](const ChunkEmissions& e, float (&el)[kChunk]) {
+                        el[0] = e.v0.x; el[1] = e.v0.y; el[2] = e.v0.z; el[3] = e.v0.w;
+                        el[4] = e.v1.x; el[5] = e.v1.y; el[6] = e.v1.z; el[7] = e.v1.w;
                     };
-                    take(emit0, el0);
-                    take(emit1, el1);
+                    get(k == 0 ? emit00 : emit01, el0);
+                    get(k == 0 ? emit10 : emit11, el1);
+                    if (k == 1) {
+                        emit01 = chunk_emissions(at.has0, at.p0, 0);
+                        emit11 = chunk_emissions(at.has1, at.p1, 0);
+                    }
                 };
                 block_shares<0>(m, at, ends, packed_inverse_p, block, own_first, own_end, s_alpha,
                                 s_alpha + kBlockFrames * kShareRow, emissions, file);
             }
-        });
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        const int rows = min(rows_per_pass, m.Tb - t0 - first);
-        // The label's symbols one after the other, where alpha was: the word of the first occurrence with the position put into
-        // its unused bits, and the symbol.
-        static_assert(2 * CTC_MAX_LABEL_LENGTH <= kShareInts && CTC_MAX_LABEL_LENGTH < 1024, "the list fits, a position is ten bits");
+            i += waves;
+            if (i >= pieces) break;
+            at = LaneLabels(lab, L, i * kPieceStep);
+            load();
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (wave == waves - 1) {
+        // The label's symbols one after the other: the word of the first occurrence with the position put into its unused bits,
+        // and the symbol.
+        static_assert(CTC_MAX_LABEL_LENGTH < 1024, "a position is ten bits");
         int symbols = 0;
         for (int j0 = 0; j0 < L; j0 += 64) {
             const int j = j0 + lane, link = j < L ? link_of[j] : 0, symbol = j < L ? lab[j] : 0;
             const unsigned long long firsts = __ballot(link < 0);
             if (link < 0) {
                 const int i = symbols + __builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(firsts >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(firsts), 0));
-                s_alpha[2 * i] = static_cast<unsigned>((link & (kLinkSlotMask | kLinkSlotMask << kLinkCountShift)) | (j & 3) << 10 | (j >> 2) << 22);
-                s_alpha[2 * i + 1] = static_cast<unsigned>(symbol);
+                s_list[2 * i] = static_cast<unsigned>((link & (kLinkSlotMask | kLinkSlotMask << kLinkCountShift)) | (j & 3) << 10 | (j >> 2) << 22);
+                s_list[2 * i + 1] = static_cast<unsigned>(symbol);
             }
             symbols += __popcll(firsts);
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        // Four of them at a time, a lane per frame and symbol: the lane adds up the run of its symbol's positions.  (A lane
-        // per symbol took every frame in turn, and the wavefront as long as its most frequent symbol 16 times over.)
-        const int row = lane & (kBlockFrames - 1), t = t0 + first + row;
-        const bool has_row = row < rows;
-        const float* const share = s_share + min(row, rows_per_pass - 1) * row_pitch;
-        const size_t out = (static_cast<size_t>(t) * B + b) * A;
-        const float* const y_row = emit_label + emission_at(m.e_off, L, min(t, m.Tb - 1), 0);
-        auto entry = [&](int i) { return s_alpha[2 * min(i, symbols - 1)]; };
-        auto position = [](unsigned word) { return static_cast<int>(word >> 10 & 3) | static_cast<int>(word >> 22) << 2; };
-        const float word_of_frame = s_word[first + min(row, rows_per_pass - 1)], norm = frame_norm(word_of_frame);
-        float sum = 0.0f;
-        if (symbols > 0) {
-            unsigned word = entry(lane >> 4);
-            float y = y_row[static_cast<size_t>(position(word)) * kChunk];
-            for (int i0 = 0; i0 < symbols; i0 += 4) {
-                const int i = i0 + (lane >> 4);
-                // (the next ones' y on its way)
-                const unsigned next_word = entry(i + 4);
-                const float next_y = y_row[static_cast<size_t>(position(next_word)) * kChunk];
-                const int slot = static_cast<int>(word & kLinkSlotMask), count = static_cast<int>(word >> kLinkCountShift & kLinkSlotMask);
-                float o = share[slot];
-                for (int k = 1; k < count; ++k) o += share[slot + k];
-                if (i < symbols && has_row) {
-                    store_gradient(g, out + s_alpha[2 * i + 1], emission_softmax(y, norm) - o);
-                    sum += o;
-                }
-                word = next_word;
-                y = next_y;
+        if (lane == 0) s_symbols = symbols;
+        if (t0 == 0) {
+            const double log2_norms = norms_of_wave(norms_of_lane(m, emit_blank)).log2();
+            if (lane == 0)
+                g.costs[b] = g.chain_err[b] != 0 ? __uint_as_float(0x7FC00000u)
+                                                 : cost_of_mass(g.mass[b * kMassWords + kMassValue], g.mass[b * kMassWords + kMassLog2], log2_norms);
+        }
+    }
+    __syncthreads();
+    const int symbols = __builtin_amdgcn_readfirstlane(s_symbols);
+    // A lane per frame and symbol adds up the run of its symbol's positions, four symbols to a wavefront side by side and
+    // kAtOnce such rounds in flight.  (A lane per symbol took every frame in turn, and the wavefront as long as its most
+    // frequent symbol 16 times over.)
+    constexpr int kAtOnce = 4;
+    const int rows = min(kBlockFrames, m.Tb - t0);
+    const int row = lane & (kBlockFrames - 1), t = t0 + row;
+    const bool has_row = row < rows;
+    const float* const share = s_share + row;
+    const size_t out = (static_cast<size_t>(t) * B + b) * A;
+    const float* const y_row = emit_label + emission_at(m.e_off, L, min(t, m.Tb - 1), 0);
+    const float word_of_frame = s_word[row], norm = frame_norm(word_of_frame);
+    float sum = 0.0f;
+    for (int i0 = 4 * wave + (lane >> 4); i0 - (lane >> 4) < symbols; i0 += 4 * kAtOnce * waves) {
+        uint2v entry[kAtOnce];
+        float y[kAtOnce];
+#pragma unroll
+        for (int n = 0; n < kAtOnce; ++n) {
+            entry[n] = *reinterpret_cast<const uint2v*>(&s_list[2 * min(i0 + 4 * waves * n, symbols - 1)]);
+            const int position = static_cast<int>(entry[n][0] >> 10 & 3) | static_cast<int>(entry[n][0] >> 22) << 2;
+            y[n] = y_row[static_cast<size_t>(position) * kChunk];
+        }
+#pragma unroll
+        for (int n = 0; n < kAtOnce; ++n) {
+            const int slot = static_cast<int>(entry[n][0] & kLinkSlotMask), count = static_cast<int>(entry[n][0] >> kLinkCountShift & kLinkSlotMask);
+            float o = share[slot * kSharePitch];
+            for (int k = 1; k < count; ++k) o += share[(slot + k) * kSharePitch];
+            if (i0 + 4 * waves * n < symbols && has_row) {
+                store_gradient(g, out + entry[n][1], emission_softmax(y[n], norm) - o);
+                sum += o;
             }
         }
-        // the blank: what the label states leave of 1
-        sum += __shfl_xor(sum, 16);
-        sum += __shfl_xor(sum, 32);
-        if (has_row && lane < kBlockFrames)
-            store_gradient(g, out + blank, blank_softmax(word_of_frame) - (1.0f - sum));
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    // the blank: what the label states leave of 1
+    sum += __shfl_xor(sum, 16);
+    sum += __shfl_xor(sum, 32);
+    if (lane < kBlockFrames) s_sum[wave * kBlockFrames + lane] = sum;
+    __syncthreads();
+    if (wave == 0 && has_row && lane < kBlockFrames) {
+        for (int w = 1; w < waves; ++w) sum += s_sum[w * kBlockFrames + lane];
+        store_gradient(g, out + blank, blank_softmax(word_of_frame) - (1.0f - sum));
     }
 }
 
@@ -3717,8 +3756,9 @@ static TileArgs tile_args(const Launch& p, size_t* lds)
         *lds = static_cast<size_t>(kWaves) * tile_lds_ints(p.max_label, p.A <= 32 ? 2 : 4) * 4;
     } else {
         per_group = 1;
-        g.rows_per_pass = static_cast<size_t>(kBlockFrames) * (p.max_label + 1) * sizeof(float) <= (size_t(60) << 10) ? kBlockFrames : kBlockFrames / 2;
-        *lds = static_cast<size_t>(g.rows_per_pass) * (p.max_label + 1) * sizeof(float);
+        g.waves = label_pieces(p.max_label) > 1 ? kWideWaves : 2;
+        g.alpha_at = wide_alpha_at(p.max_label);
+        *lds = wide_lds_bytes(p.max_label, g.waves);
     }
     g.groups = (blocks + per_group - 1) / per_group + (p.A <= kDirectMaxA ? 1 : 0);
     return g;
@@ -3830,7 +3870,7 @@ int launch_gradient(const Launch& p, void* stream)
     auto s = static_cast<hipStream_t>(stream);
     size_t lds;
     const TileArgs args = tile_args(p, &lds);
-    const dim3 grid(args.groups, p.B), block(p.A > kDirectMaxA ? 64 : kRowThreads);
+    const dim3 grid = p.A > kDirectMaxA ? dim3(p.B, args.groups) : dim3(args.groups, p.B), block(p.A > kDirectMaxA ? 64 * args.waves : kRowThreads);
     return checked_launch([&] {
         if (p.A > kDirectMaxA)
             hipLaunchKernelGGL(ctc_gradient_wide_kernel, grid, block, lds, s, args, meta, p.labels, emit_blank, emit_label,

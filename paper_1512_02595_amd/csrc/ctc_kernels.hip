@@ -515,32 +515,62 @@ __device__ __forceinline__ void raise_rough(Utt* meta, int b, bool rough)
 // before its first whole vector and as many after its last; a lane takes one of them each.  Where the gradient starts at
 // another place within 16 bytes than the activations, the vectors read are written element by element (750 symbols, f32:
 // 87.6 us a call against 86.8 with vectors, 134 with the three passes of ctc_softmax_kernel; 6000 bf16: 119, 107 and 292).
-// Consecutive workgroups take consecutive rows of the tensor.
 // Bound by memory: with the 308 of 768 MB of zero rows that the lattice launch takes over counted in, 64 x 500 rows of
-// 6000 symbols, of which 300 on average are valid, move at 4.8 TB/s (bf16: 128.5 us with a load in each branch, 119 with
-// all loads first and zero rows left over).  27 x 333 rows of 4733 symbols (no multiple of a vector): 108 us with
-// three passes of four-byte loads, 41 so.  64 x 500 rows of 750 symbols: 41.5 us with the rows in LDS, 34.7 so.
-// grid: row_groups workgroups with rows, then sa.parts per utterance for the setup role.
-template <typename T, int kLanes, int kPerLane>
+// 6000 symbols, of which 300 on average are valid, moved at 4.8 TB/s with consecutive rows on consecutive dies (bf16: 128.5 us
+// with a load in each branch, 119 with all loads first and zero rows left over) and take a ninth less in runs (RowPlan).
+// 27 x 333 rows of 4733 symbols (no multiple of a vector): 108 us with three passes of four-byte loads, 41 so.  64 x 500
+// rows of 750 symbols: 41.5 us with the rows in LDS, 34.7 so.
+// kStreaming: the rows are loaded past the caches (see row_plan).
+// grid: plan.groups workgroups with rows, then sa.parts per utterance for the setup role.
+
+// Which rows a workgroup takes.  Workgroup i runs on die i mod 8, and each die has a cache of its own.  With consecutive groups of
+// rows on consecutive dies all eight work in the same few pages of memory, and an utterance's emissions, eight frames to 32 bytes,
+// are written a word here and a word there.  So a die gets tiles of neighbouring groups instead: `frames` frames times
+// `columns` groups, every other round of eight tiles the other way round (utterances end one after the other, so that the tiles
+// of a round have ever less to do).  A tile of 0 frames: consecutive groups, one after the other.
+struct RowPlan {
+    int groups;               // workgroups, some of them without rows
+    int per_frame;            // groups of rows in a frame
+    int frames, columns;      // a tile's
+};
+struct RowPlace { int t, group; };
+__device__ __forceinline__ RowPlace row_place(const RowPlan& plan, int index, bool runs)
+{
+    constexpr int kDies = 8;
+    const int size = plan.frames * plan.columns;
+    if (size == 0) return {index / plan.per_frame, index % plan.per_frame};
+    const int round = index / (kDies * size), in_round = index - round * (kDies * size);
+    const int die = in_round % kDies, within = in_round / kDies, place = round & 1 ? kDies - 1 - die : die;
+    if (runs) {
+        // a run of consecutive groups, across the ends of frames; what is left behind the last whole round lies as it comes
+        if ((round + 1) * (kDies * size) <= plan.groups) index = (round * kDies + place) * size + within;
+        return {index / plan.per_frame, index % plan.per_frame};
+    }
+    const int tile = round * kDies + place, across = (plan.per_frame + plan.columns - 1) / plan.columns;
+    const int band = tile / across, frame = within / plan.columns;
+    return {band * plan.frames + frame, (tile - band * across) * plan.columns + within - frame * plan.columns};
+}
+
+template <typename T, int kLanes, int kPerLane, bool kStreaming>
 __global__ __launch_bounds__(kRowThreads)
 void ctc_softmax_rows_kernel(const T* __restrict__ x, T* __restrict__ grads, Utt* __restrict__ meta,
                              const int* __restrict__ labels, float* __restrict__ emit_blank, float* __restrict__ emit_label,
-                             const SetupArgs sa, int B, int A, int blank, int row_groups, int defer)
+                             const SetupArgs sa, int Tt, int B, int A, int blank, const RowPlan plan, int defer)
 {
     constexpr int N = Vec<T>::N, kVecs = kPerLane / N, kRows = kRowThreads / kLanes;
     static_assert(kLanes == 16 || kLanes == 64 || kLanes == kRowThreads, "row reductions exist for these");
     __shared__ float red[8];
     __shared__ int s_lab[kSetupLabelSlots];
     const int tid = threadIdx.x;
-    if (static_cast<int>(blockIdx.x) >= row_groups) {
-        const int index = static_cast<int>(blockIdx.x) - row_groups, b = index / sa.parts;
+    if (static_cast<int>(blockIdx.x) >= plan.groups) {
+        const int index = static_cast<int>(blockIdx.x) - plan.groups, b = index / sa.parts;
         setup_role(meta[b], b, labels, sa, s_lab, index % sa.parts, sa.parts);
         return;
     }
-    const int per_frame = (B + kRows - 1) / kRows;
-    const int t = static_cast<int>(blockIdx.x) / per_frame, q = tid % kLanes;
-    const int b = (static_cast<int>(blockIdx.x) % per_frame) * kRows + (kRows > 1 ? tid / kLanes : 0);
-    if (b >= B) return;
+    const RowPlace place = row_place(plan, static_cast<int>(blockIdx.x), kLanes == kRowThreads);
+    const int t = place.t, q = tid % kLanes;
+    const int b = place.group * kRows + (kRows > 1 ? tid / kLanes : 0);
+    if (t >= Tt || place.group >= plan.per_frame || b >= B) return;
     const Utt m = meta[b];
     const size_t row_off = (static_cast<size_t>(t) * B + b) * A;
     const T* const row = x + row_off;
@@ -562,7 +592,10 @@ void ctc_softmax_rows_kernel(const T* __restrict__ x, T* __restrict__ grads, Utt
     // between one load and the next (a vector past the end is the last one again, counted by nobody).
     RawVec raw[kVecs];
 #pragma unroll
-    for (int i = 0; i < kVecs; ++i) raw[i] = *reinterpret_cast<const RawVec*>(row + head + static_cast<size_t>(min(q + i * kLanes, nvec - 1)) * N);
+    for (int i = 0; i < kVecs; ++i) {
+        const auto* const from = reinterpret_cast<const RawVec*>(row + head + static_cast<size_t>(min(q + i * kLanes, nvec - 1)) * N);
+        raw[i] = kStreaming ? __builtin_nontemporal_load(from) : *from;
+    }
     float alone = load_elem(row, single >= 0 ? single : 0);
     const int* const lab = labels + m.lab_off;
     const int c_first = q < m.L ? lab[q] : 0;
@@ -3601,6 +3634,40 @@ int row_lanes(const Launch& p)
     const int64_t groups = static_cast<int64_t>(p.T) * ((p.B + rows - 1) / rows) + static_cast<int64_t>(p.B) * (CTC_MAX_LABEL_LENGTH / 64 + 1);
     return groups <= INT32_MAX / kRowThreads ? lanes : 0;
 }
+
+// The tiles of ctc_softmax_rows_kernel.
+// Rows of a workgroup each: runs of 64 rows.  64 x 500 x 6000 288.9 -> 261.6 us a call (runs of 8, 16, 32, 128 and 192 rows: 279 with
+// streaming loads, 269.8, 262.6, 261.6 and 266), in bf16 162.7 -> 145.5; 16 x 1000 x 8000 194.5 -> 181; 200 x 150 x 5000 212 -> 207;
+// 100 x 800 x 4001 bf16 264 -> 251.  From 24 rounds of them on: a die of 27 x 333 x 4733 (17 rounds) has up to a run more to do than
+// another, 68.9 us without tiles and 69.5 with.
+// Several rows to a workgroup: the eight frames of a chunk of emissions, and of a frame all groups up to 32, beyond that about 16 at
+// a time.  64 x 500 x 750 82.0 -> 79.0; 32 x 1500 x 2000 240 -> 226.5; 64 x 1000 x 1000 bf16 147 -> 139; 150 x 500 x 120 87.5 -> 83.2;
+// 512 x 400 x 200 bf16 134.3 -> 132; 256 x 700 x 100 157 -> 156.4, 160 in runs of 64 groups, which write words of a chunk from four
+// dies; of 24 shapes only 200 x 500 x 700 bf16 lost (123.5 -> 125.5).
+constexpr int kRunRows = 64, kRunRounds = 24, kTileGroupsMost = 32, kTileGroups = 16;
+RowPlan row_plan(const Launch& p, int lanes)
+{
+    const int rows = kRowThreads / lanes, per_frame = (p.B + rows - 1) / rows;
+    if (lanes == kRowThreads) return {p.T * per_frame, per_frame, static_cast<int64_t>(p.T) * per_frame >= 8 * kRunRows * kRunRounds ? 1 : 0, kRunRows};
+    const int across = per_frame <= kTileGroupsMost ? 1 : (per_frame + kTileGroups - 1) / kTileGroups;
+    const int columns = (per_frame + across - 1) / across;
+    const int64_t tiles = static_cast<int64_t>((per_frame + columns - 1) / columns) * ((p.T + kChunk - 1) / kChunk);
+    const int64_t groups = (tiles + 7) / 8 * 8 * kChunk * columns;
+    // (fewer tiles than dies, or too many groups of rows for a launch once the ends of tiles are counted in: none)
+    if (tiles < 8 || groups + static_cast<int64_t>(p.B) * (CTC_MAX_LABEL_LENGTH / 64 + 1) > INT32_MAX / kRowThreads)
+        return {p.T * per_frame, per_frame, 0, columns};
+    return {static_cast<int>(groups), per_frame, kChunk, columns};
+}
+// Loads past the caches: fp32 rows of a workgroup each that begin on 16 bytes, in tensors of twice the last-level cache and more.
+// 64 x 500 x 6000 261.6 -> 253.5 us a call, 64 x 500 x 4096 180.8 -> 169, 16 x 1000 x 8000 181 -> 176, 200 x 150 x 5000 206.9 -> 205.5.
+// Smaller tensors lose what the cache still holds of them (20 x 200 x 6000, 96 MB: 41.8 -> 46.6), rows that share lines of memory
+// load those twice (100 x 800 x 4001 bf16 251 -> 258.6), and bf16 gains nothing (64 x 500 x 6000 145.5 -> 146.5).
+constexpr int64_t kStreamedBytes = 512'000'000;
+bool streamed_rows(const Launch& p, int lanes)
+{
+    return lanes == kRowThreads && p.dtype == CTC_DTYPE_F32 && p.A % 4 == 0 && reinterpret_cast<uintptr_t>(p.x) % 16 == 0 &&
+           static_cast<int64_t>(p.T) * p.B * p.A * 4 >= kStreamedBytes;
+}
 }
 
 // Values in the first half of a direction's region, exponents in the second.
@@ -3695,14 +3762,15 @@ int launch_softmax(const Launch& p, void* stream)
                 hipLaunchKernelGGL(ctc_softmax_symbols_kernel<bf16_t>, grid, block, lds, s, static_cast<const bf16_t*>(p.x), meta,
                                    emit_blank, emit_label, sa, p.B, p.A, p.blank);
         } else if (row_lanes(p) > 0) {
-            const int lanes = row_lanes(p), rows = kRowThreads / lanes;
+            const int lanes = row_lanes(p);
             const bool half = p.A <= 16 * lanes;
-            const int row_groups = p.T * ((p.B + rows - 1) / rows);
-            const dim3 grid(row_groups + sa.parts * p.B);
-#define CTC_LAUNCH_ROWS(TYPE, LANES, PER_LANE)                                                     \
-    hipLaunchKernelGGL((ctc_softmax_rows_kernel<TYPE, LANES, PER_LANE>), grid, block, 0, s,        \
+            const RowPlan plan = row_plan(p, lanes);
+            const dim3 grid(plan.groups + sa.parts * p.B);
+#define CTC_LAUNCH_ROWS_FROM(TYPE, LANES, PER_LANE, STREAMING)                                     \
+    hipLaunchKernelGGL((ctc_softmax_rows_kernel<TYPE, LANES, PER_LANE, STREAMING>), grid, block, 0, s, \
                        static_cast<const TYPE*>(p.x), static_cast<TYPE*>(p.grads), meta, labels,   \
-                       emit_blank, emit_label, sa, p.B, p.A, p.blank, row_groups, p.defer)
+                       emit_blank, emit_label, sa, p.T, p.B, p.A, p.blank, plan, p.defer)
+#define CTC_LAUNCH_ROWS(TYPE, LANES, PER_LANE) CTC_LAUNCH_ROWS_FROM(TYPE, LANES, PER_LANE, false)
 #define CTC_LAUNCH_ROWS_OF(TYPE)                                                                   \
     do {                                                                                           \
         if (lanes == 16 && half) CTC_LAUNCH_ROWS(TYPE, 16, 16);                                    \
@@ -3712,10 +3780,14 @@ int launch_softmax(const Launch& p, void* stream)
         else if (half) CTC_LAUNCH_ROWS(TYPE, kRowThreads, 16);                                     \
         else CTC_LAUNCH_ROWS(TYPE, kRowThreads, 32);                                               \
     } while (0)
-            if (f32) CTC_LAUNCH_ROWS_OF(float);
+            if (streamed_rows(p, lanes)) {
+                if (half) CTC_LAUNCH_ROWS_FROM(float, kRowThreads, 16, true);
+                else CTC_LAUNCH_ROWS_FROM(float, kRowThreads, 32, true);
+            } else if (f32) CTC_LAUNCH_ROWS_OF(float);
             else CTC_LAUNCH_ROWS_OF(bf16_t);
 #undef CTC_LAUNCH_ROWS_OF
 #undef CTC_LAUNCH_ROWS
+#undef CTC_LAUNCH_ROWS_FROM
         } else {
             const dim3 grid(p.T + 1, p.B);
             if (f32)

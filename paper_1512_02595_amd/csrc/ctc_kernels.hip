@@ -712,30 +712,34 @@ void ctc_softmax_kernel(const T* __restrict__ x, T* __restrict__ grads,
     raise_log_domain(meta, b, m, small);
 }
 
-// The zero rows that the softmax launch has left (t % 16 < defer), by workgroups of the lattice launch that land on
-// compute units without a chain: workgroup i runs on compute unit i mod n_cu (see order_chains), so those whose place in
+// The zero rows that the softmax launch has left (t % 16 < defer): the last of them by the label columns' launch, the others by
+// workgroups of the lattice launch that land on compute units without a chain.  Workgroup i runs on compute unit i mod n_cu (see order_chains), so those whose place in
 // a round is a chain's leave at once.  (64 x 500 x 6000: 10 us less in the softmax launch, 6.5 more in this one.)
 struct FillArgs {
     void* grads;
     int elem_bytes;
     int T, B, A;
-    int defer;                // 0: nothing to fill
+    int first, defer;         // of every 16 frames, `defer` from `first` on; 0: nothing to fill
     int n_cu, n_chains, rounds;
 };
-__device__ __forceinline__ void fill_rows(const FillArgs& f, const Utt* __restrict__ meta)
+// By a workgroup, a wavefront per row: every workers-th row from the wavefront's own on.
+__device__ __forceinline__ void fill_rows(const FillArgs& f, const Utt* __restrict__ meta, int worker, int workers);
+__device__ __forceinline__ void fill_rows_beside_chains(const FillArgs& f, const Utt* __restrict__ meta)
 {
     const int place = static_cast<int>(blockIdx.x) % f.n_cu, round = static_cast<int>(blockIdx.x) / f.n_cu;
     if (place < f.n_chains) return;
-    // a wavefront per row
-    const int lane = threadIdx.x & 63, waves = blockDim.x >> 6;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int idle = f.n_cu - f.n_chains, workers = idle * f.rounds * waves;
-    const int first = (round * idle + place - f.n_chains) * waves + wave;
-    const int frames = f.T / 16 * f.defer + min(f.T % 16, f.defer);      // deferred ones
+    const int waves = blockDim.x >> 6, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int idle = f.n_cu - f.n_chains;
+    fill_rows(f, meta, (round * idle + place - f.n_chains) * waves + wave, idle * f.rounds * waves);
+}
+__device__ __forceinline__ void fill_rows(const FillArgs& f, const Utt* __restrict__ meta, const int worker, const int workers)
+{
+    const int lane = threadIdx.x & 63;
+    const int frames = f.T / 16 * f.defer + min(max(f.T % 16 - f.first, 0), f.defer);
     const int row_bytes = f.A * f.elem_bytes;
-    for (int64_t i = first; i < static_cast<int64_t>(frames) * f.B; i += workers) {
+    for (int64_t i = worker; i < static_cast<int64_t>(frames) * f.B; i += workers) {
         const int k = static_cast<int>(i / f.B), b = static_cast<int>(i - static_cast<int64_t>(k) * f.B);
-        const int t = k / f.defer * 16 + k % f.defer;
+        const int t = k / f.defer * 16 + f.first + k % f.defer;
         const int frames_of_b = (meta[b].flags & kUttRuns) ? meta[b].Tb : 0;
         if (t < frames_of_b) continue;
         char* const row = static_cast<char*>(f.grads) + (static_cast<size_t>(t) * f.B + b) * row_bytes;
@@ -2487,7 +2491,7 @@ void ctc_lattice_kernel_w1(const Utt* __restrict__ meta, const int* __restrict__
                            int* __restrict__ chain_err, uint32_t* __restrict__ sink, const LaunchWords wk)
 {
     if (kMode == Mode::kGrad && static_cast<int>(blockIdx.x) >= wk.fill.n_chains && wk.fill.defer > 0) {
-        fill_rows(wk.fill, meta);
+        fill_rows_beside_chains(wk.fill, meta);
         return;
     }
     lattice_body<Sync::kNone, kMode>(order[blockIdx.x], meta, labels, emit_blank, emit_blank64, emit_label, lat,
@@ -2507,7 +2511,7 @@ void ctc_lattice_kernel(const Utt* __restrict__ meta, const int* __restrict__ or
 {
     extern __shared__ double2 halo_lds[];                    // halo_lds_bytes(wavefronts of the workgroup)
     if (kMode == Mode::kGrad && static_cast<int>(blockIdx.x) >= wk.fill.n_chains && wk.fill.defer > 0) {
-        fill_rows(wk.fill, meta);
+        fill_rows_beside_chains(wk.fill, meta);
         return;
     }
     lattice_body<Sync::kHalo, kMode>(order[blockIdx.x], meta, labels, emit_blank, emit_blank64, emit_label, lat,
@@ -3345,7 +3349,8 @@ void ctc_gradient_narrow_kernel(const TileArgs args, const Utt* __restrict__ met
 // Larger alphabets: the softmax launch has written y (and zeros); here the columns of the label's symbols and the
 // blank's are corrected.  A workgroup per block.  Its wavefronts take the label's pieces; the shares go to LDS in slot order
 // (the positions of a symbol next to each other, setup_role), and the lane of a symbol and frame adds up its run: one writer
-// per symbol and a fixed order.  The last wavefront, if it has no piece, lists the symbols meanwhile.  grid (B, blocks of T);
+// per symbol and a fixed order.  The last wavefront, if it has no piece, lists the symbols meanwhile.  The launch waits for its
+// slowest block and leaves the memory idle, so its first workgroups write zero rows (columns_frames).  grid (B, fill.rounds + blocks of T);
 // LDS: wide_lds_bytes.
 // What bounds it: in launches of up to a block per SIMD (64 utterances of 500 frames: 1140) the time of the slowest block, beyond
 // that the issue of the recomputation.  With a wavefront to a block a block took 7 to 25 us (loads 2, a piece 4.5, sums 1 to 10),
@@ -3365,15 +3370,24 @@ constexpr size_t wide_lds_bytes(int Lmax, int waves)
 {
     return (static_cast<size_t>(wide_alpha_at(Lmax)) + std::min(waves, std::max(label_pieces(Lmax), 1)) * kShareInts) * sizeof(unsigned);
 }
+// kFill: (without, as a variant of its own: 0.5 % for calls that leave no rows to it)
+template <bool kFill>
 __global__ __launch_bounds__(64 * kWideWaves)
 void ctc_gradient_wide_kernel(const TileArgs g, const Utt* __restrict__ meta, const int* __restrict__ labels,
-                              const float* __restrict__ emit_blank, const float* __restrict__ emit_label, const LatticeOut lat)
+                              const float* __restrict__ emit_blank, const float* __restrict__ emit_label, const LatticeOut lat,
+                              const FillArgs fill)
 {
+    if (kFill && static_cast<int>(blockIdx.y) < fill.rounds) {
+        const int waves = blockDim.x >> 6;
+        fill_rows(fill, meta, static_cast<int>(blockIdx.y * gridDim.x + blockIdx.x) * waves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6),
+                  static_cast<int>(fill.rounds * gridDim.x) * waves);
+        return;
+    }
     __shared__ float s_word[kBlockFrames], s_sum[kWideWaves * kBlockFrames];
     __shared__ int s_symbols;
     extern __shared__ uint4v wide_lds[];
     const int B = g.B, A = g.A, blank = g.blank;
-    const int lane = threadIdx.x & 63, block = blockIdx.y, t0 = block * kBlockFrames;
+    const int lane = threadIdx.x & 63, block = static_cast<int>(blockIdx.y) - (kFill ? fill.rounds : 0), t0 = block * kBlockFrames;
     const int b = static_cast<int>((blockIdx.x + 3u * block) % static_cast<unsigned>(B));      // (three: neighbours change dies too)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
     const Utt m = uniform_record(meta[b]);
@@ -3769,7 +3783,7 @@ int launch_softmax(const Launch& p, void* stream)
 #define CTC_LAUNCH_ROWS_FROM(TYPE, LANES, PER_LANE, STREAMING)                                     \
     hipLaunchKernelGGL((ctc_softmax_rows_kernel<TYPE, LANES, PER_LANE, STREAMING>), grid, block, 0, s, \
                        static_cast<const TYPE*>(p.x), static_cast<TYPE*>(p.grads), meta, labels,   \
-                       emit_blank, emit_label, sa, p.T, p.B, p.A, p.blank, plan, p.defer)
+                       emit_blank, emit_label, sa, p.T, p.B, p.A, p.blank, plan, p.defer + p.defer_columns)
 #define CTC_LAUNCH_ROWS(TYPE, LANES, PER_LANE) CTC_LAUNCH_ROWS_FROM(TYPE, LANES, PER_LANE, false)
 #define CTC_LAUNCH_ROWS_OF(TYPE)                                                                   \
     do {                                                                                           \
@@ -3793,11 +3807,11 @@ int launch_softmax(const Launch& p, void* stream)
             if (f32)
                 hipLaunchKernelGGL(ctc_softmax_kernel<float>, grid, block, 0, s,
                                    static_cast<const float*>(p.x), static_cast<float*>(p.grads), meta, labels, emit_blank,
-                                   emit_label, sa, p.T, p.B, p.A, p.blank, p.defer);
+                                   emit_label, sa, p.T, p.B, p.A, p.blank, p.defer + p.defer_columns);
             else
                 hipLaunchKernelGGL(ctc_softmax_kernel<bf16_t>, grid, block, 0, s,
                                    static_cast<const bf16_t*>(p.x), static_cast<bf16_t*>(p.grads), meta, labels, emit_blank,
-                                   emit_label, sa, p.T, p.B, p.A, p.blank, p.defer);
+                                   emit_label, sa, p.T, p.B, p.A, p.blank, p.defer + p.defer_columns);
         }
     });
 }
@@ -3867,7 +3881,7 @@ int launch_lattice(const Launch& p, void* stream)
     if (p.defer > 0) {
         // as many workgroups per compute unit without a chain as make eight wavefronts
         const int rounds = std::max(1, 8 / p.max_waves);
-        wk.fill = FillArgs{p.grads, p.dtype == CTC_DTYPE_F32 ? 4 : 2, p.T, p.B, p.A, p.defer, p.n_cu, p.n_chains, rounds};
+        wk.fill = FillArgs{p.grads, p.dtype == CTC_DTYPE_F32 ? 4 : 2, p.T, p.B, p.A, 0, p.defer, p.n_cu, p.n_chains, rounds};
         n_groups = p.n_cu * rounds;
     }
     auto s = static_cast<hipStream_t>(stream);
@@ -3942,11 +3956,19 @@ int launch_gradient(const Launch& p, void* stream)
     auto s = static_cast<hipStream_t>(stream);
     size_t lds;
     const TileArgs args = tile_args(p, &lds);
-    const dim3 grid = p.A > kDirectMaxA ? dim3(p.B, args.groups) : dim3(args.groups, p.B), block(p.A > kDirectMaxA ? 64 * args.waves : kRowThreads);
+    FillArgs fill{};
+    if (p.defer_columns > 0) {
+        // (a workgroup to a compute unit; twice and four times as many 0.5 % slower)
+        fill = FillArgs{p.grads, p.dtype == CTC_DTYPE_F32 ? 4 : 2, p.T, p.B, p.A, p.defer, p.defer_columns, p.n_cu, p.n_chains, std::max(1, p.n_cu / p.B)};
+    }
+    const dim3 grid = p.A > kDirectMaxA ? dim3(p.B, args.groups + fill.rounds) : dim3(args.groups, p.B), block(p.A > kDirectMaxA ? 64 * args.waves : kRowThreads);
     return checked_launch([&] {
-        if (p.A > kDirectMaxA)
-            hipLaunchKernelGGL(ctc_gradient_wide_kernel, grid, block, lds, s, args, meta, p.labels, emit_blank, emit_label,
-                               lattice_blocks(p));
+        if (p.A > kDirectMaxA && p.defer_columns > 0)
+            hipLaunchKernelGGL(ctc_gradient_wide_kernel<true>, grid, block, lds, s, args, meta, p.labels, emit_blank, emit_label,
+                               lattice_blocks(p), fill);
+        else if (p.A > kDirectMaxA)
+            hipLaunchKernelGGL(ctc_gradient_wide_kernel<false>, grid, block, lds, s, args, meta, p.labels, emit_blank, emit_label,
+                               lattice_blocks(p), fill);
         else if (p.A <= 32)
             hipLaunchKernelGGL(ctc_gradient_narrow_kernel<2>, grid, block, lds, s, args, meta, p.labels, emit_blank, emit_label,
                                lattice_blocks(p));

@@ -52,3 +52,13 @@ def test_runs_of_whole_rows(T, B):
 @pytest.mark.parametrize("T,B,A", [(160, 100, 8000), (161, 199, 4000), (159, 100, 8000)])
 def test_rows_past_the_caches(T, B, A):
     softmax_of_rows(T, B, A, A)
+
+
+# Zero rows left to the launch of the label columns: few and all of those that the lattice launch does not write, frames that
+# end within the sixteen of a round, more utterances than chains leave compute units for
+@pytest.mark.parametrize("dtype", [ctc.DTYPE_F32, ctc.DTYPE_BF16])
+@pytest.mark.parametrize("T,B", [(17, 1), (41, 300), (31, 140), (160, 7)])
+def test_zero_rows_beside_the_label_columns(T, B, dtype):
+    frames = np.random.default_rng(T).integers(0, max(2, T // 4), B)
+    frames[0] = T
+    pc.check(batch_of(frames, [min(3, f // 3) for f in frames], 2050, T=T, seed=T), dtype)

@@ -755,46 +755,50 @@ __device__ __forceinline__ void fill_rows(const FillArgs& f, const Utt* __restri
 
 // The emissions of 64 frames of a narrow alphabet into lp[64][A], a quad of lanes per frame, and behind them the frames'
 // words (log2 y_blank if plain_logs).  Returns whether a probability of this lane's is below 2^kGentleMinLog2.
-template <typename T>
-__device__ __forceinline__ bool narrow_rows(const T* __restrict__ x, float* lp, int Tb, int b, int t0, int B, int A, int blank, bool plain_logs)
+// kPerLane of a row's symbols to a lane, in registers from their load to the emission: a row costs one memory latency and, with a
+// fixed number of them, no loops around exponentials.  (Kept in LDS between the maximum, the sum and the emission, and stored a
+// word at a time: 4 x 50 frames of 29 symbols 15.0 us a call, so 13.9; one utterance of 750 40.7, 39.4; 64 x 750 51.3, 49.7, of 64
+// symbols 57.2, 52.7; 512 x 750 131.5, 128.9; with the label and the image asked for together, which is 0.3 of it.)
+template <int kPerLane, typename T>
+__device__ __forceinline__ bool narrow_rows_of(const T* __restrict__ x, float* lp, int Tb, int b, int t0, int B, int A, int blank, bool plain_logs)
 {
     constexpr int kPerRow = 4;
     const int tid = threadIdx.x;
     const int r = tid / kPerRow, q = tid % kPerRow, t = t0 + r;
-    float* lrow = lp + r * A;
     bool rough = false;
     if (t < Tb) {
-        const T* row = x + (static_cast<size_t>(t) * B + b) * A;
+        float* const lrow = lp + r * A;
+        const T* const row = x + (static_cast<size_t>(t) * B + b) * A;
+        const float blank_logit = load_elem(row, blank);
+        float v[kPerLane];
+#pragma unroll
+        for (int u = 0; u < kPerLane; ++u) v[u] = load_elem(row, min(q + u * kPerRow, A - 1));
         float mx = -__builtin_inff();
-        // eight reads in flight per thread: a row costs a few memory latencies, not A / kPerRow
-        for (int k0 = q; k0 < A; k0 += 8 * kPerRow) {
-            float v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int k = k0 + u * kPerRow;
-                v[u] = (k < A) ? load_elem(row, k) : -__builtin_inff();
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int k = k0 + u * kPerRow;
-                if (k < A) lrow[k] = v[u];
-                mx = fmaxf(mx, v[u]);
-            }
-        }
+        for (int u = 0; u < kPerLane; ++u) mx = fmaxf(mx, v[u]);         // (the last symbol again where there is none)
         mx = quad_max(mx);
         float sum = 0.0f;
-        for (int k = q; k < A; k += kPerRow) sum += fast_exp2((lrow[k] - mx) * kLog2e);
+#pragma unroll
+        for (int u = 0; u < kPerLane; ++u) sum += q + u * kPerRow < A ? fast_exp2((v[u] - mx) * kLog2e) : 0.0f;
         sum = quad_sum(sum);
         const float ls = fast_log2(sum);
-        const FrameNorm norm(lrow[blank], mx, sum, ls);
+        const FrameNorm norm(blank_logit, mx, sum, ls);
         if (q == 0) lp[kFlagFrames * A + r] = plain_logs ? norm.log_blank : norm.word();
-        for (int k = q; k < A; k += kPerRow) {
-            const float l = log2_softmax(lrow[k], mx, ls);
+#pragma unroll
+        for (int u = 0; u < kPerLane; ++u) {
+            const int k = q + u * kPerRow;
+            const float l = log2_softmax(v[u], mx, ls), e = plain_logs ? l : (k == blank ? encode_blank(norm) : encode_emission(l, norm));
             rough = rough || l < kGentleMinLog2;
-            lrow[k] = plain_logs ? l : (k == blank ? encode_blank(norm) : encode_emission(l, norm));
+            if (k < A) lrow[k] = e;
         }
     }
     return rough;
+}
+template <typename T>
+__device__ __forceinline__ bool narrow_rows(const T* __restrict__ x, float* lp, int Tb, int b, int t0, int B, int A, int blank, bool plain_logs)
+{
+    static_assert(kDirectMaxA <= 64, "sixteen symbols to a lane");
+    return A <= 32 ? narrow_rows_of<8>(x, lp, Tb, b, t0, B, A, blank, plain_logs) : narrow_rows_of<16>(x, lp, Tb, b, t0, B, A, blank, plain_logs);
 }
 
 // A workgroup's share of the emission block: kRows frames from t0 on whose coded rows sit in lp[kRows][A], virtual
@@ -812,11 +816,15 @@ __device__ __forceinline__ bool store_symbol_chunks(const float* lp, int Tb, uns
     // a wavefront per chunk: [symbol][frame], 8 A floats in a row
     float* const out = emit_label + kLabelSlack + e_off + static_cast<size_t>(t0) * A;
     for (int chunk = tid >> 6; chunk * kChunk < padded; chunk += kRowThreads / 64)
-        for (int i = tid & 63; i < kChunk * A; i += 64) {
-            const int a = i / kChunk, r = chunk * kChunk + i % kChunk;
-            const float e = r < rows ? lp[r * A + a] : virtual_emission(a == blank, plain_logs);
-            out[chunk * kChunk * A + i] = e;
-            small = small || (!plain_logs && e < 0.0f);
+        for (int i = tid & 63; i < 2 * A; i += 64) {
+            const int a = i >> 1, r = chunk * kChunk + 4 * (i & 1);
+            float e[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) e[k] = lp[(r + k) * A + a];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) e[k] = r + k < rows ? e[k] : virtual_emission(a == blank, plain_logs);
+            *reinterpret_cast<float4*>(out + chunk * kChunk * A + 4 * i) = make_float4(e[0], e[1], e[2], e[3]);
+            small = small || (!plain_logs && fminf(fminf(e[0], e[1]), fminf(e[2], e[3])) < 0.0f);
         }
     return small;
 }
@@ -1023,14 +1031,20 @@ void ctc_softmax_narrow_kernel(const T* __restrict__ x, const NarrowImage image,
         // this workgroup's share of the image
         const int groups = B * sa.parts, group = b * sa.parts + part;
         const int share = (image.count + groups - 1) / groups;
-        for (int i = group * share + tid; i < min((group + 1) * share, image.count); i += kRowThreads)
-            if (i < image.labels_first || i >= image.labels_end) workspace_words[i] = image.words[i];
-        // its utterance's label, from the bytes
-        const unsigned char* const labels8 = reinterpret_cast<const unsigned char*>(image.words) + image.labels8_offset;
-        if (part == 0) {
-            for (int j = tid; j < m.L; j += kRowThreads) image.labels_out[m.lab_off + j] = labels8[m.lab_off + j];
-            setup_words(m, b, sa);
-        }
+        // its utterance's label, from the bytes; both asked for before either is used: each is a trip to host memory
+        const unsigned char* const labels8 = reinterpret_cast<const unsigned char*>(image.words) + image.labels8_offset + m.lab_off;
+        const int end = min((group + 1) * share, image.count), length = part == 0 ? m.L : 0;
+        int i = group * share + tid, j = tid;
+        do {
+            const int word = i < end ? image.words[i] : 0;
+            const int symbol = j < length ? labels8[j] : 0;
+            __builtin_amdgcn_sched_barrier(0);
+            if (i < end && (i < image.labels_first || i >= image.labels_end)) workspace_words[i] = word;
+            if (j < length) image.labels_out[m.lab_off + j] = symbol;
+            i += kRowThreads;
+            j += kRowThreads;
+        } while (i - tid < end || j - tid < length);
+        if (part == 0) setup_words(m, b, sa);
         return;
     }
     // (the fields of the utterance's record that the rows need)

@@ -3192,13 +3192,14 @@ __device__ __forceinline__ void utterance_cost(const TileArgs& g, const Utt* __r
 
 // Workgroup `group` of utterance b: kRowThreads / 64 wavefronts, ceil(blocks of T / (4 / wavefronts per block)) workgroups;
 // LDS 4 tile_lds_ints(Lmax, kTiles) ints.  kTiles: tiles of 16 symbols.
-template <int kTiles, bool kWait>
+// kLean: the lane's number is made anew where the rows are written (tile_thread), so that 128 registers suffice.
+template <int kTiles, bool kWait, bool kLean = false>
 __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* __restrict__ meta, const int* __restrict__ labels,
                                             const float* __restrict__ emit_blank, const float* __restrict__ emit_label,
                                             const LatticeOut& lat, uint4v* tile_lds, const int b, const int group)
 {
     const int Tt = g_args.T, B = g_args.B, A = g_args.A, blank = g_args.blank, Lmax = g_args.Lmax;
-    const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+    const int lane = kLean ? tile_thread() & 63 : threadIdx.x & 63, c = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const Utt m = uniform_record(meta[b]);
     const int L = m.L, sharing = g_args.share_blocks ? block_waves(L) : 1, part = wave & (sharing - 1);
@@ -3325,16 +3326,17 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
         }
     }
     // Result: lane l holds symbol 16 n + l % 16 of frames 4 (l / 16) .. + 3; y is the emission.
-    const int tr = t0 + 4 * g;
+    const int writer = kLean ? tile_thread() & 63 : 0, column = kLean ? writer & 15 : c, quad = kLean ? writer >> 4 : g;
+    const int tr = t0 + 4 * quad;
     const float scale = packed_mantissa(packed_inverse_p) * (0.5f / (1 << kShareScaleLog2));
     auto write = [&](auto* grads) {
 #pragma unroll
         for (int n = 0; n < kTiles; ++n) {
-            const int k = 16 * n + c;
+            const int k = 16 * n + column;
             if (k >= A) continue;
             auto* out = grads + (static_cast<size_t>(tr) * B + b) * A + k;
-            const float4 y = *reinterpret_cast<const float4*>(s_emit + ((g >> 1) * A + k) * kEmissionRow + (g & 1) * 4);
-            const float4 norm = *reinterpret_cast<const float4*>(s_norm + 4 * g);
+            const float4 y = *reinterpret_cast<const float4*>(s_emit + ((quad >> 1) * A + k) * kEmissionRow + (quad & 1) * 4);
+            const float4 norm = *reinterpret_cast<const float4*>(s_norm + 4 * quad);
             const float yv[4] = {y.x, y.y, y.z, y.w}, norms[4] = {norm.x, norm.y, norm.z, norm.w};
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -3605,8 +3607,11 @@ __device__ __forceinline__ const FusedArgs& fused_args()
     return *(const FusedArgs*)args;
 }
 
-template <Sync kSync, int kTiles>
-__global__ __launch_bounds__(64 * kFusedWaves)
+// kLean: 128 registers, so that a compute unit holds two workgroups of more than four wavefronts and not one, while the blocks wait
+// that the chains have left behind: for up to 32 symbols (more would need a stack) and workgroups of that size (32 x 1500 frames,
+// labels of up to 540 symbols: 135.5 -> 131.0 us a call; up to four wavefronts 0.5 % slower so).
+template <Sync kSync, int kTiles, bool kLean>
+__global__ __launch_bounds__(64 * kFusedWaves, kLean ? 4 : 1)
 void ctc_lattice_gradient_kernel(const Utt* __restrict__ meta, const int* __restrict__ order,
                                  const int* __restrict__ labels, const float* __restrict__ emit_blank,
                                  const double* __restrict__ emit_blank64, const float* __restrict__ emit_label,
@@ -3626,7 +3631,7 @@ void ctc_lattice_gradient_kernel(const Utt* __restrict__ meta, const int* __rest
             const FusedArgs& a = fused_args();
             const int tile = left - 1, rank = tile / a.tiles.groups, b = __builtin_amdgcn_readfirstlane(a.tiles.by_end[rank]), group = tile - rank * a.tiles.groups;
             if (group == 0) utterance_cost<true>(a.tiles, a.meta, a.emit_blank, b);
-            else narrow_tile<kTiles, true>(a.tiles, a.meta, a.labels, a.emit_blank, a.emit_label, a.lat, fused_lds, b, group - 1);
+            else narrow_tile<kTiles, true, kLean>(a.tiles, a.meta, a.labels, a.emit_blank, a.emit_label, a.lat, fused_lds, b, group - 1);
             left = __builtin_amdgcn_readfirstlane(published(&a.tiles.left[tile]));
         } while (left != 0);
     } else {
@@ -3638,7 +3643,7 @@ void ctc_lattice_gradient_kernel(const Utt* __restrict__ meta, const int* __rest
         const bool waits = (flags & kUttRuns) && (group - 1) * (kRowThreads / 64 / sharing) * kBlockFrames < frames;
         if (waits && !chains_taken(tiles, b, tile)) return;
         if (group == 0) utterance_cost<true>(tiles, meta, emit_blank, b);
-        else narrow_tile<kTiles, true>(tiles, meta, labels, emit_blank, emit_label, lat, fused_lds, b, group - 1);
+        else narrow_tile<kTiles, true, kLean>(tiles, meta, labels, emit_blank, emit_label, lat, fused_lds, b, group - 1);
     }
 }
 
@@ -3907,17 +3912,18 @@ int launch_lattice(const Launch& p, void* stream)
         wk.late_percent = p.late_percent;
         tiles.first_group = n_groups;
         const dim3 grid(n_groups + tiles.groups * p.B), block(64 * waves);
-#define CTC_LAUNCH_FUSED(SYNC, TILES)                                                              \
-    hipLaunchKernelGGL((ctc_lattice_gradient_kernel<SYNC, TILES>), grid, block, lds, s, meta, order, labels, emit_blank,   \
+#define CTC_LAUNCH_FUSED(SYNC, TILES, LEAN)                                                        \
+    hipLaunchKernelGGL((ctc_lattice_gradient_kernel<SYNC, TILES, LEAN>), grid, block, lds, s, meta, order, labels, emit_blank,   \
                        reinterpret_cast<const double*>(p.ws + p.lay.emit_blank64), emit_label,                \
                        lat, mass, p.costs, chain_err, sink, wk, tiles)
 #define CTC_LAUNCH_FUSED_TILES(SYNC)                                                               \
     do {                                                                                           \
-        if (p.A <= 32) CTC_LAUNCH_FUSED(SYNC, 2);                                             \
-        else CTC_LAUNCH_FUSED(SYNC, 4);                                                            \
+        if (p.A <= 32) CTC_LAUNCH_FUSED(SYNC, 2, false);                                           \
+        else CTC_LAUNCH_FUSED(SYNC, 4, false);                                                     \
     } while (0)
         return checked_launch([&] {
-            if (p.max_waves == 1) CTC_LAUNCH_FUSED_TILES(Sync::kNone);
+            if (p.max_waves > kRowThreads / 64 && p.A <= 32) CTC_LAUNCH_FUSED(Sync::kHalo, 2, true);
+            else if (p.max_waves == 1) CTC_LAUNCH_FUSED_TILES(Sync::kNone);
             else CTC_LAUNCH_FUSED_TILES(Sync::kHalo);
         });
 #undef CTC_LAUNCH_FUSED_TILES

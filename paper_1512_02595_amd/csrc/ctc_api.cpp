@@ -381,6 +381,7 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
         m.ab_off = ab_off;
         m.e_direct = emission_layout(c.A);
         m.rough = 0;
+        m.steep = 0;
         m.e_cols = m.e_direct == kEmitSymbols ? c.A : L;
         meta[b] = m;
         const int64_t padded = padded_frames(Tb);

@@ -28,7 +28,8 @@ struct Utt {
     int64_t ab_off;    // offset (8-byte words) of its alpha/beta blocks, lattice_words of them
     int32_t e_cols;    // columns of its emission block: a column per symbol, or one per label position
     int16_t e_direct;  // which of the two: kEmitGathered or kEmitSymbols (emission_layout)
-    int16_t rough;     // set by the softmax launch when some probability is below 2^kGentleMinLog2
+    int8_t rough;      // set by the softmax launch when some probability is below 2^kGentleMinLog2
+    int8_t steep;      // ... below 2^kRoughMinLog2
     int32_t waves2;    // the same plan for linear-domain chains of more than 64 pairs, whose lanes own
     int32_t halo2;     // two neighbouring pairs each (plan_waves2)
 };
@@ -277,17 +278,22 @@ constexpr int kUttLogDomain = 4;
 // Linear-domain chains of this utterance give two neighbouring state pairs to every lane
 // (plan_waves2) instead of one (plan_waves): see two_pairs_per_lane.
 constexpr int kUttTwoPairs = 8;
-constexpr float kLinearMinLog2 = -79.0f;
-// Utterances all of whose probabilities are above this look after their lanes' exponents once a block, others once a chunk.
-constexpr float kGentleMinLog2 = -32.0f;
-constexpr int kRowsSmall = 1, kRowsRough = 2;    // bits of Layout::row_flags: one below kLinearMinLog2, one below kGentleMinLog2
+constexpr float kLinearMinLog2 = -100.0f;
+// Chains of the linear domain look after their lanes' exponents once a block of 16 frames where all probabilities of the utterance
+// are above the first of these, once a chunk of 8 where they are above the second, and every kSteepSteps frames otherwise.
+constexpr float kGentleMinLog2 = -32.0f, kRoughMinLog2 = -79.0f;
+constexpr int kSteepSteps = 4;
+constexpr int kRowsSmall = 1, kRowsRough = 2, kRowsSteep = 4;    // bits of Layout::row_flags: one below kLinearMinLog2, kGentleMinLog2, kRoughMinLog2
+// What an utterance's chains publish (Layout::domain): words for every frame, or checkpoints, whose blocks are recomputed with a look at
+// the exponents every kSteepSteps frames or every chunk.
+constexpr int kDomainLog = 1, kDomainSteep = 2;
 // Utterances of more frames than this run the log domain whatever their emissions: the lanes'
-// exponents, which fall by up to 79 per frame, must stay clear of kNoExponent and of int32's end.
+// exponents, which fall or rise by up to 100 per frame, must stay clear of kNoExponent and of int32's end.
 constexpr int kLinearMaxFrames = 1 << 21;
 // Utterances with fewer than this many frames to spare (frames - symbols - repeated neighbours) run the log
 // domain too.  Where hardly a frame is to spare the alignments run along the front of the lattice, and the
 // states behind the front, whose mass can no longer reach the end, may outweigh it by more than the lanes'
-// frames of the linear domain hold (lane_frame in the kernels: 2^760 within nine state pairs); with this
+// frames of the linear domain hold (lane_frame in the kernels: 2^760 within nine state pairs, or five); with this
 // many frames to spare every state that near the front can still reach the end.  Measured before the rule:
 // 138 frames, 91 symbols, 47 repeats, emissions down to 2^-95: the front 2^1900 below its neighbours, the
 // linear domain's cost +inf.

@@ -284,6 +284,7 @@ void ctc_plan_kernel(const int* __restrict__ labels, const int* __restrict__ lab
         m.poll_budget = poll_budget;
         m.e_direct = emission_layout(A);
         m.rough = 0;
+        m.steep = 0;
         m.e_cols = m.e_direct == kEmitSymbols ? A : m.L;
         m.e_off = b * (m.e_direct == kEmitSymbols ? static_cast<int64_t>(padded) * A : gathered_emissions(Tt, longest));
         m.ab_off = b * lattice_words(Tt, longest);
@@ -486,18 +487,17 @@ __device__ __forceinline__ void store_virtual_frames(const Utt& m, float* __rest
             emit_label[emission_at(m.e_off, m.L, t, j)] = virtual_emission(false, plain_logs);
     }
 }
-// `m`: the utterance's record as this launch found it.  A store, and no atomic: nothing else in the word changes during the
-// launch, so that all who raise the flag write the same.  (One atomic per lane that met such an emission, in 64 words for the
+// The smallest log2 probability that a lane has seen decides how the utterance's chains run (lattice_body).
+// `m`: the utterance's record as this launch found it.  Stores, and no atomics: nothing else in the words changes during the
+// launch, so that all who raise a flag write the same.  (One atomic per lane that met such an emission, in 64 words for the
 // whole launch: 64 x 500 rows of 750 symbols with steep logits 650 us; one per row 110; so 23.)
-__device__ __forceinline__ void raise_log_domain(Utt* meta, int b, const Utt& m, bool small)
+__device__ __forceinline__ void raise_flags(Utt* meta, int b, const Utt& m, float lowest)
 {
-    if (small) meta[b].flags = m.flags | kUttLogDomain;
-}
-
-// The same for one with a probability below 2^kGentleMinLog2.
-__device__ __forceinline__ void raise_rough(Utt* meta, int b, bool rough)
-{
-    if (rough) meta[b].rough = 1;
+    if (lowest < kGentleMinLog2) {
+        meta[b].rough = 1;
+        if (lowest < kRoughMinLog2) meta[b].steep = 1;
+        if (lowest < kLinearMinLog2) meta[b].flags = m.flags | kUttLogDomain;
+    }
 }
 
 // ---- softmax statistics + emission gather --------------------------------------------------
@@ -640,22 +640,17 @@ void ctc_softmax_rows_kernel(const T* __restrict__ x, T* __restrict__ grads, Utt
     // 171 x 4186 bf16, cost alone: 90.1 us a call with all of them waiting for the blank's logit, 86.1 so)
     if (q > 0 && q >= m.L && t != m.Tb - 1) return;
     const FrameNorm norm(load_elem(row, blank), mx, sum, ls);
-    bool small = false, rough = norm.log_blank < kGentleMinLog2;
-    if (q == 0) {
-        store_blank(emit_blank, sa.emit_blank64, static_cast<size_t>(m.f_off) + t, sa.plain_logs ? norm.log_blank : norm.word(), sa.plain_logs);
-        small = !sa.plain_logs && norm.small;
-    }
+    float lowest = norm.log_blank;
+    if (q == 0) store_blank(emit_blank, sa.emit_blank64, static_cast<size_t>(m.f_off) + t, sa.plain_logs ? norm.log_blank : norm.word(), sa.plain_logs);
     float* const erow = emit_label + emission_at(m.e_off, m.L, t, 0);
     for (int j = q; j < m.L; j += kLanes) {
         const int c = j == q ? c_first : lab[j];
-        const float lp = log2_softmax(load_elem(row, c), mx, ls), e = sa.plain_logs ? lp : encode_emission(lp, norm);
-        erow[static_cast<size_t>(j) * kChunk] = e;
-        small = small || (!sa.plain_logs && e < 0.0f);
-        rough = rough || lp < kGentleMinLog2;
+        const float lp = log2_softmax(load_elem(row, c), mx, ls);
+        erow[static_cast<size_t>(j) * kChunk] = sa.plain_logs ? lp : encode_emission(lp, norm);
+        lowest = fminf(lowest, lp);
     }
     if (t == m.Tb - 1) store_virtual_frames(m, emit_blank, sa.emit_blank64, emit_label, sa.plain_logs, q, kLanes);
-    raise_rough(meta, b, rough);
-    raise_log_domain(meta, b, m, small);
+    raise_flags(meta, b, m, lowest);
 }
 
 // Alphabets beyond 8192 symbols: one workgroup per row, read three times (the row does not fit the registers).
@@ -696,22 +691,17 @@ void ctc_softmax_kernel(const T* __restrict__ x, T* __restrict__ grads,
         for (int k = threadIdx.x; k < A; k += kRowThreads)
             store_elem(grow, k, fast_exp2(log2_softmax(load_elem(row, k), mx, ls)));
     const FrameNorm norm(load_elem(row, blank), mx, sum, ls);
-    bool small = false, rough = norm.log_blank < kGentleMinLog2;
-    if (threadIdx.x == 0) {
-        store_blank(emit_blank, sa.emit_blank64, static_cast<size_t>(m.f_off) + t, sa.plain_logs ? norm.log_blank : norm.word(), sa.plain_logs);
-        small = !sa.plain_logs && norm.small;
-    }
+    float lowest = norm.log_blank;
+    if (threadIdx.x == 0) store_blank(emit_blank, sa.emit_blank64, static_cast<size_t>(m.f_off) + t, sa.plain_logs ? norm.log_blank : norm.word(), sa.plain_logs);
     if (t == m.Tb - 1) store_virtual_frames(m, emit_blank, sa.emit_blank64, emit_label, sa.plain_logs, threadIdx.x, kRowThreads);
     float* erow = emit_label + emission_at(m.e_off, m.L, t, 0);
     const int* lab = labels + m.lab_off;
     for (int j = threadIdx.x; j < m.L; j += kRowThreads) {
-        const float lp = log2_softmax(load_elem(row, lab[j]), mx, ls), e = sa.plain_logs ? lp : encode_emission(lp, norm);
-        erow[static_cast<size_t>(j) * kChunk] = e;
-        small = small || (!sa.plain_logs && e < 0.0f);
-        rough = rough || lp < kGentleMinLog2;
+        const float lp = log2_softmax(load_elem(row, lab[j]), mx, ls);
+        erow[static_cast<size_t>(j) * kChunk] = sa.plain_logs ? lp : encode_emission(lp, norm);
+        lowest = fminf(lowest, lp);
     }
-    raise_rough(meta, b, rough);
-    raise_log_domain(meta, b, m, small);
+    raise_flags(meta, b, m, lowest);
 }
 
 // The zero rows that the softmax launch has left (t % 16 < defer): the last of them by the label columns' launch, the others by
@@ -756,18 +746,18 @@ __device__ __forceinline__ void fill_rows(const FillArgs& f, const Utt* __restri
 }
 
 // The emissions of 64 frames of a narrow alphabet into lp[64][A], a quad of lanes per frame, and behind them the frames'
-// words (log2 y_blank if plain_logs).  Returns whether a probability of this lane's is below 2^kGentleMinLog2.
+// words (log2 y_blank if plain_logs).  Returns the smallest log2 probability among this lane's.
 // kPerLane of a row's symbols to a lane, in registers from their load to the emission: a row costs one memory latency and, with a
 // fixed number of them, no loops around exponentials.  (Kept in LDS between the maximum, the sum and the emission, and stored a
 // word at a time: 4 x 50 frames of 29 symbols 15.0 us a call, so 13.9; one utterance of 750 40.7, 39.4; 64 x 750 51.3, 49.7, of 64
 // symbols 57.2, 52.7; 512 x 750 131.5, 128.9; with the label and the image asked for together, which is 0.3 of it.)
 template <int kPerLane, typename T>
-__device__ __forceinline__ bool narrow_rows_of(const T* __restrict__ x, float* lp, int Tb, int b, int t0, int B, int A, int blank, bool plain_logs)
+__device__ __forceinline__ float narrow_rows_of(const T* __restrict__ x, float* lp, int Tb, int b, int t0, int B, int A, int blank, bool plain_logs)
 {
     constexpr int kPerRow = 4;
     const int tid = threadIdx.x;
     const int r = tid / kPerRow, q = tid % kPerRow, t = t0 + r;
-    bool rough = false;
+    float lowest = 0.0f;
     if (t < Tb) {
         float* const lrow = lp + r * A;
         const T* const row = x + (static_cast<size_t>(t) * B + b) * A;
@@ -790,29 +780,27 @@ __device__ __forceinline__ bool narrow_rows_of(const T* __restrict__ x, float* l
         for (int u = 0; u < kPerLane; ++u) {
             const int k = q + u * kPerRow;
             const float l = log2_softmax(v[u], mx, ls), e = plain_logs ? l : (k == blank ? encode_blank(norm) : encode_emission(l, norm));
-            rough = rough || l < kGentleMinLog2;
+            lowest = fminf(lowest, l);
             if (k < A) lrow[k] = e;
         }
     }
-    return rough;
+    return lowest;
 }
 template <typename T>
-__device__ __forceinline__ bool narrow_rows(const T* __restrict__ x, float* lp, int Tb, int b, int t0, int B, int A, int blank, bool plain_logs)
+__device__ __forceinline__ float narrow_rows(const T* __restrict__ x, float* lp, int Tb, int b, int t0, int B, int A, int blank, bool plain_logs)
 {
     static_assert(kDirectMaxA <= 64, "sixteen symbols to a lane");
     return A <= 32 ? narrow_rows_of<8>(x, lp, Tb, b, t0, B, A, blank, plain_logs) : narrow_rows_of<16>(x, lp, Tb, b, t0, B, A, blank, plain_logs);
 }
 
 // A workgroup's share of the emission block: kRows frames from t0 on whose coded rows sit in lp[kRows][A], virtual
-// frames past the utterance's end.  kRows is a whole number of chunks.  Returns whether an emission is too
-// small for the linear domain.
+// frames past the utterance's end.  kRows is a whole number of chunks.
 template <int kRows>
-__device__ __forceinline__ bool store_symbol_chunks(const float* lp, int Tb, unsigned f_off, int64_t e_off, int t0, int A, int blank,
+__device__ __forceinline__ void store_symbol_chunks(const float* lp, int Tb, unsigned f_off, int64_t e_off, int t0, int A, int blank,
                                                     float* __restrict__ emit_blank, double* __restrict__ emit_blank64,
                                                     float* __restrict__ emit_label, bool plain_logs)
 {
     const int tid = threadIdx.x, rows = min(kRows, Tb - t0), padded = min(kRows, static_cast<int>(padded_frames(Tb)) - t0);
-    bool small = false;                                  // (the blank has a column among the symbols')
     if (tid < padded)
         store_blank(emit_blank, emit_blank64, static_cast<size_t>(f_off) + t0 + tid, tid < rows ? lp[kRows * A + tid] : virtual_emission(true, plain_logs), plain_logs);
     // a wavefront per chunk: [symbol][frame], 8 A floats in a row
@@ -826,9 +814,7 @@ __device__ __forceinline__ bool store_symbol_chunks(const float* lp, int Tb, uns
 #pragma unroll
             for (int k = 0; k < 4; ++k) e[k] = r + k < rows ? e[k] : virtual_emission(a == blank, plain_logs);
             *reinterpret_cast<float4*>(out + chunk * kChunk * A + 4 * i) = make_float4(e[0], e[1], e[2], e[3]);
-            small = small || (!plain_logs && fminf(fminf(e[0], e[1]), fminf(e[2], e[3])) < 0.0f);
         }
-    return small;
 }
 
 // Alphabets of at most kDirectMaxA symbols, more utterances than the narrow launch below takes: a workgroup takes 64
@@ -850,10 +836,10 @@ void ctc_softmax_symbols_kernel(const T* __restrict__ x, Utt* __restrict__ meta,
     }
     const int t0 = blockIdx.x * kRows;
     if (!(m.flags & kUttRuns) || t0 >= m.Tb) return;
-    raise_rough(meta, b, narrow_rows(x, lp, m.Tb, b, t0, B, A, blank, sa.plain_logs));
+    const float lowest = narrow_rows(x, lp, m.Tb, b, t0, B, A, blank, sa.plain_logs);
+    raise_flags(meta, b, m, lowest);
     __syncthreads();
-    raise_log_domain(meta, b, m, store_symbol_chunks<kRows>(lp, m.Tb, m.f_off, m.e_off, t0, A, blank, emit_blank, sa.emit_blank64,
-                                                            emit_label, sa.plain_logs));
+    store_symbol_chunks<kRows>(lp, m.Tb, m.f_off, m.e_off, t0, A, blank, emit_blank, sa.emit_blank64, emit_label, sa.plain_logs);
 
 }
 
@@ -979,6 +965,7 @@ __device__ __forceinline__ Utt build_record(const NarrowDevice& dv, const PlanTa
     m.poll_budget = dv.poll_budget;
     m.e_direct = emission_layout(A);
     m.rough = 0;
+    m.steep = 0;
     m.e_cols = m.e_direct == kEmitSymbols ? A : m.L;
     m.e_off = b * (m.e_direct == kEmitSymbols ? static_cast<int64_t>(padded) * A : gathered_emissions(Tt, longest));
     m.ab_off = b * lattice_words(Tt, longest);
@@ -1013,7 +1000,7 @@ void ctc_softmax_narrow_kernel(const T* __restrict__ x, const NarrowImage image,
     constexpr int kRows = kFlagFrames;
     static_assert(kRows * 4 == kRowThreads, "a quad per frame (narrow_rows)");
     extern __shared__ float lp[];                          // [kRows][A], [kRows]
-    __shared__ int s_small, s_rough;
+    __shared__ int s_flags;
     const int b = blockIdx.y, tid = threadIdx.x;
     const int row_blocks = static_cast<int>(gridDim.x) - sa.parts;
     if (static_cast<int>(blockIdx.x) >= row_blocks && dv.labels) {
@@ -1066,21 +1053,16 @@ void ctc_softmax_narrow_kernel(const T* __restrict__ x, const NarrowImage image,
     m.e_off = static_cast<int64_t>(m.f_off) * A;
     const int t0 = blockIdx.x * kRows;
     if (t0 >= m.Tb || !(m.flags & kUttRuns)) return;
-    if (tid == 0) {
-        s_small = 0;
-        s_rough = 0;
-    }
-    const bool rough = narrow_rows(x, lp, m.Tb, b, t0, B, A, blank, sa.plain_logs);
+    if (tid == 0) s_flags = 0;
+    const float lowest = narrow_rows(x, lp, m.Tb, b, t0, B, A, blank, sa.plain_logs);
     __syncthreads();
-    const bool small = store_symbol_chunks<kRows>(lp, m.Tb, m.f_off, m.e_off, t0, A, blank, emit_blank, sa.emit_blank64, emit_label,
-                                                  sa.plain_logs);
-    if (small) s_small = kRowsSmall;
-    if (rough) s_rough = kRowsRough;
+    store_symbol_chunks<kRows>(lp, m.Tb, m.f_off, m.e_off, t0, A, blank, emit_blank, sa.emit_blank64, emit_label, sa.plain_logs);
+    if (lowest < kGentleMinLog2) atomicOr(&s_flags, kRowsRough | (lowest < kRoughMinLog2 ? kRowsSteep : 0) | (lowest < kLinearMinLog2 ? kRowsSmall : 0));
     __syncthreads();
-    if (tid == 0) row_flags[static_cast<size_t>(b) * row_blocks + blockIdx.x] = s_small | s_rough;
+    if (tid == 0) row_flags[static_cast<size_t>(b) * row_blocks + blockIdx.x] = s_flags;
 }
 
-// What the narrow softmax launch has met in an utterance's frames: kRowsSmall, kRowsRough.  Asked by a whole wavefront; the same
+// What the narrow softmax launch has met in an utterance's frames: kRowsSmall, kRowsRough, kRowsSteep.  Asked by a whole wavefront; the same
 // answer in every lane.
 __device__ __forceinline__ int rows_flagged(const int* __restrict__ row_flags, int b, int blocks_per_utterance, int Tb)
 {
@@ -1088,7 +1070,9 @@ __device__ __forceinline__ int rows_flagged(const int* __restrict__ row_flags, i
     const int lane = threadIdx.x & 63, n = (Tb + kFlagFrames - 1) / kFlagFrames;
     int any = 0;
     for (int i = lane; i < n; i += 64) any |= row_flags[static_cast<size_t>(b) * blocks_per_utterance + i];
-    return (__ballot(any & kRowsSmall) != 0 ? kRowsSmall : 0) | (__ballot(any & kRowsRough) != 0 ? kRowsRough : 0);
+    if (__builtin_expect(__ballot(any != 0) == 0, 1)) return 0;
+    auto met = [&](int which) { return __ballot(any & which) != 0 ? which : 0; };
+    return met(kRowsSmall) | met(kRowsRough) | met(kRowsSteep);
 }
 
 // ---- lattice storage -------------------------------------------------------------------------
@@ -1691,20 +1675,22 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
 // two fused multiply-adds, an addition and a multiplication per pair, a fifth of the instructions of the
 // log-domain step and no transcendentals.  What makes it safe is an exponent per lane:
 //   true value = (v_blank, v_label) * 2^frame
-// with fp64 values and an int32 `frame` that is looked after at the ends of chunks (ChainFrames).  Probabilities of the linear
-// domain are at least 2^-m (m = -kLinearMinLog2 = 79), ratios to the blank's thus within 2^-m .. 2^m.  A renewal gives a lane
-//   frame = largest binary exponent among its own pairs and the kChunk pairs below it, its window,
+// with fp64 values and an int32 `frame` that is looked after every n = kChunk steps (ChainFrames).  With probabilities of at least
+// 2^-m (m = -kRoughMinLog2 = 79) ratios to the blank's are within 2^-m .. 2^m.  A renewal gives a lane
+//   frame = largest binary exponent among its own pairs and the n pairs below it, its window,
 // but no more than kFrameSlack above its own largest value, down to kFrameDrop below the window's top.  Mass moves up by at most
-// one pair per step, so in the kChunk steps that follow
+// one pair per step, so in the n steps that follow
 //   - what arrives from the window is at most 2^kFrameDrop, and grows by 3 * 2^m a step at most: 2^(370 + 8 * 80.6) = 2^1015,
 //   - a value of at least 2^-kFrameSlack shrinks by 2^-m a step at worst: 2^-(390 + 632) = 2^-1022,
-// both inside fp64.  Two neighbouring frames differ by at most kFrameSlack + kFrameDrop, which the factor between them (scale,
+// both inside fp64.  Utterances with smaller probabilities, down to 2^-100 (-kLinearMinLog2), are *steep*: n = kSteepSteps, 2^776 and
+// 2^-790.  Their chains are a variant of their own, since a branch in the middle of a chunk would be two instructions more for the others
+// (64 x 750 frames, 29 symbols, probabilities down to 2^-90: 55 us a call; in the log domain 123, shares to 2^-19).  Two neighbouring frames differ by at most kFrameSlack + kFrameDrop, which the factor between them (scale,
 // constant between renewals and folded into the multiply-adds) can hold.
 //
 // A pair further than 2^(kFrameSlack + kFrameDrop) below its window's top is rounded away.  Its neighbours have 2^760 times its
 // mass and can still reach the end of the label (utterances with fewer than kTightFrames frames to spare, where they could
-// not, run in the log domain from the start: tight_fit), each of their at most eight extra moves costing 2^-m at worst: what is
-// rounded away is below 2^-128 of the whole.  (With the window's top as the frame of every lane a pair 2^1000 below its
+// not, run in the log domain from the start: tight_fit), each of their at most n extra moves costing 2^-m at worst: what is
+// rounded away is below 2^-128 (steep: 2^-360) of the whole.  (With the window's top as the frame of every lane a pair 2^1000 below its
 // neighbours was lost where it was all there is: an utterance with exactly as many frames as its label needs, logits spread
 // over 40 nats, cost off by 0.03, gradient by 0.03.)
 //
@@ -1723,12 +1709,18 @@ __device__ __forceinline__ int lane_frame(int window_top, int own_top)
 // value within [2^kEasyLow, 2^kEasyHigh] of its frame, and no frame lies more than kSmoothFrames a pair below the frame of the
 // lane below it.  Until the next look, after n steps with ratios within 2^-g .. 2^g, a value is at least 2^(kEasyLow - n g), and
 // at most 2^(kEasyHigh + n (kSmoothFrames + g + 1.6)).  A chunk, g = 79: 2^-982 and 2^936; a block, where all probabilities of the
-// utterance are above 2^kGentleMinLog2 (g = 32): 2^-862 and 2^1021.
+// utterance are above 2^kGentleMinLog2 (g = 32): 2^-862 and 2^1021; kSteepSteps, g = 100, kSteepSmoothFrames: 2^-750 and 2^1005.
 constexpr int kEasyLow = -350, kEasyHigh = 99;
-constexpr int kSmoothFrames = 24;
-static_assert(kFrameSlack - kChunk * kLinearMinLog2 <= 1022 && kEasyLow + kChunk * kLinearMinLog2 >= -1022, "small values");
-static_assert(kFrameDrop + kChunk * (1.6f - kLinearMinLog2) < 1023 && kEasyHigh + kChunk * (kSmoothFrames + 1.6f - kLinearMinLog2) < 1023, "large values");
-static_assert(kEasyLow + kBlockFrames * kGentleMinLog2 >= -1022 && kEasyHigh + kBlockFrames * (kSmoothFrames + 1.6f - kGentleMinLog2) < 1023, "a block");
+constexpr int kSmoothFrames = 24, kSteepSmoothFrames = 125;
+constexpr bool frames_last(int steps, float min_log2, int smooth, bool after_renewal)
+{
+    const float small = steps * min_log2, large = steps * (1.6f - min_log2);
+    return (!after_renewal || (small - kFrameSlack >= -1022 && kFrameDrop + large < 1023)) && kEasyLow + small >= -1022 &&
+           kEasyHigh + large + steps * smooth < 1023;
+}
+static_assert(frames_last(kChunk, kRoughMinLog2, kSmoothFrames, true), "a chunk");
+static_assert(frames_last(kSteepSteps, kLinearMinLog2, kSteepSmoothFrames, true), "a steep one's steps");
+static_assert(frames_last(kBlockFrames, kGentleMinLog2, kSmoothFrames, false), "a block");
 // The test, on the high dword of the largest value of a lane (biased exponent in bits 20..30): one
 // subtraction and one unsigned compare; zero, denormals, infinities and NaN fail it.
 __device__ __forceinline__ bool outside_easy_range(double top)
@@ -1746,9 +1738,10 @@ __device__ __forceinline__ void publish_mass(double* mass, double value, int fra
 }
 
 // A chain's frames; kPairs pairs to a lane.
-template <int kPairs>
+template <int kPairs, bool kSteep>
 struct ChainFrames {
-    static constexpr int kSmooth = kPairs * kSmoothFrames, kSteps = kChunk / kPairs;     // (mass moves up kSteps lanes in a chunk)
+    static constexpr int kSmooth = kPairs * (kSteep ? kSteepSmoothFrames : kSmoothFrames);
+    static constexpr int kSteps = (kSteep ? kSteepSteps : kChunk) / kPairs;     // lanes that mass moves up until the next look at worst
     int frame = 0;
     double scale = 1.0;                                  // 2^(frame of the lane below - frame)
     unsigned long long rough = ~0ull;                    // lanes that may not put a renewal off: see rescale
@@ -1787,7 +1780,7 @@ struct ChainFrames {
     }
 };
 
-template <bool kBackward, Sync kSync, Mode kMode>
+template <bool kBackward, Sync kSync, Mode kMode, bool kSteep>
 __device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const bool gentle, const int* __restrict__ labels,
                                                  const float* __restrict__ emit_label,
                                                  uint32_t* __restrict__ out, int* __restrict__ out_exponents,
@@ -1826,7 +1819,7 @@ __device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const
     int budget = m.poll_budget;
     bool lost = false;
     const bool every_block = halo < 2 * kBlockFrames;    // hand over after every block, or after every second one
-    const unsigned long long steep = gentle ? 0ull : ~0ull;
+    const unsigned long long look = gentle && !kSteep ? 0ull : ~0ull;      // once a chunk, whatever the frames
     int generation = 0;
     int half = 0;
     const int wr_slot = lane >= 64 - halo ? lane - (64 - halo) : 0;
@@ -1845,7 +1838,7 @@ __device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const
     const bool from_below = wave > 0 && lane < halo;
 
     double v_blank = (j == 0) ? 1.0 : 0.0, v_label = 0.0;
-    ChainFrames<1> f;
+    ChainFrames<1, kSteep> f;
     double skip_scale = skip_ok ? 1.0 : 0.0;             // f.scale where the label may be entered from the label of the pair below
 
     auto counter = [&](int* p) {
@@ -1856,7 +1849,7 @@ __device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const
     // Hand-over g: what comes from below is asked for first and used last; passing the own state up fills the time.  A wavefront
     // publishes g when it has taken g itself, so that the one below knows from the same counter which half of the buffer is
     // free.  An entry carries the pair's frame as well.
-    auto hand_over = [&]() {
+    auto hand_over = [&]() __attribute__((always_inline)) {
         ++generation;
         half ^= 32;
         int ready = counter(low_ready);
@@ -1901,26 +1894,27 @@ __device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const
     // Label value of pair j-1 after the last step, in that pair's frame (0 for pair 0: the shift
     // leaves lane 0 what it had).
     int prev_lo = 0, prev_hi = 0;
-    auto from_prev_pair = [&](double mine) { return shift_up(mine, prev_lo, prev_hi); };
-    auto top_value = [&]() { return fmax(v_blank, v_label); };
-    auto renew_frames = [&]() {
+    auto from_prev_pair = [&](double mine) __attribute__((always_inline)) { return shift_up(mine, prev_lo, prev_hi); };
+    auto top_value = [&]() __attribute__((always_inline)) { return fmax(v_blank, v_label); };
+    auto renew_frames = [&]() __attribute__((always_inline)) {
         const int rise = f.renew(top_value(), halo > 0 ? halo - 1 : 0);
         v_blank = __builtin_amdgcn_ldexp(v_blank, rise);
         v_label = __builtin_amdgcn_ldexp(v_label, rise);
         skip_scale = skip_ok ? f.scale : 0.0;
     };
 
-    // After a block's first chunk, and after a block.
-    auto mid_block = [&]() {
-        if (__builtin_expect((f.rough | steep) != 0, 0))
+    // After a block's first chunk (steep: and in the middle of every chunk), and after a block.
+    static_assert(kChunk == 2 * kSteepSteps, "the middle of a chunk");
+    auto mid_block = [&]() __attribute__((always_inline)) {
+        if (__builtin_expect((f.rough | look) != 0, 0))
             if (f.renewal_due(top_value())) renew_frames();
     };
-    auto end_block = [&](bool second) {
+    auto end_block = [&](bool second) __attribute__((always_inline)) {
         if (kSync == Sync::kHalo)
             if (second || every_block) hand_over();
         if (__builtin_expect(f.renewal_due(top_value()), 0)) renew_frames();
     };
-    auto checkpoint = [&]() {
+    auto checkpoint = [&]() __attribute__((always_inline)) {
         *vp = CheckpointState{v_blank, v_label};
         *fp = f.frame;
         vp += row_step;
@@ -1932,7 +1926,7 @@ __device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const
     // Seven instructions, issued one every 4.1 clocks in the order of the statements (pin keeps the compiler from moving them; one
     // that reads the result of the one before it waits another clock).  The shift needs its operand two instructions old.
     auto pin = []() { __builtin_amdgcn_sched_barrier(0); };
-    auto advance = [&](double& el_d, float next_el) {
+    auto advance = [&](double& el_d, float next_el) __attribute__((always_inline)) {
 #pragma clang fp contract(off)                           // (a product stays a product: fused into the next step's sum it would tie the steps together)
         const double prev = from_prev_pair(v_label);
         pin();
@@ -1950,16 +1944,19 @@ __device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const
     };
 
     float el[4][kChunk];
-    auto fetch = [&](auto set, int) {
+    auto fetch = [&](auto set, int) __attribute__((always_inline)) {
         constexpr int k = decltype(set)::value;
         fetch_chunk<kBackward>(ep, estep, el[k]);
         __builtin_amdgcn_sched_barrier(0);
     };
-    auto run = [&](auto set, int) {
+    auto run = [&](auto set, int) __attribute__((always_inline)) {
         constexpr int k = decltype(set)::value;
         double el_d = static_cast<double>(el[k][0]);
 #pragma unroll
-        for (int q = 0; q < kChunk; ++q) advance(el_d, el[k][q + 1 < kChunk ? q + 1 : q]);
+        for (int q = 0; q < kChunk; ++q) {
+            advance(el_d, el[k][q + 1 < kChunk ? q + 1 : q]);
+            if (kSteep && q == kSteepSteps - 1) mid_block();
+        }
         if (!(k & 1)) mid_block();
         else {
             end_block(k == 3);
@@ -1997,7 +1994,7 @@ __device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const
 // The two pairs of a lane are neighbours in the checkpoint's row; where pair B has no label state (the lane of the last
 // pair) its part falls on one of the row's two unused columns.
 
-template <bool kBackward, Mode kMode>
+template <bool kBackward, Mode kMode, bool kSteep>
 __device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, const bool gentle, const int* __restrict__ labels,
                                                   const float* __restrict__ emit_label,
                                                   uint32_t* __restrict__ out, int* __restrict__ out_exponents,
@@ -2039,7 +2036,7 @@ __device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, cons
     int budget = m.poll_budget;
     bool lost = false;
     const bool every_block = halo < kBlockFrames;        // (see run_chain_linear; a halo of h lanes lasts 2h steps)
-    const unsigned long long steep = gentle ? 0ull : ~0ull;
+    const unsigned long long look = gentle && !kSteep ? 0ull : ~0ull;      // once a chunk, whatever the frames
     int generation = 0;
     const int wr_slot = (halo > 0 && lane >= 64 - halo) ? lane - (64 - halo) : 0;
     const int rd_slot = lane < halo ? lane : 0;
@@ -2048,7 +2045,7 @@ __device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, cons
     Halo2Wave* const above_lds = halo_wave<Halo2Wave>(lds, wave < last_wave ? wave + 1 : wave);
 
     double va_blank = (ja == 0) ? 1.0 : 0.0, va_label = 0.0, vb_blank = 0.0, vb_label = 0.0;
-    ChainFrames<2> f;
+    ChainFrames<2, kSteep> f;
     double skip_a_scale = skip_a ? 1.0 : 0.0;
     const double skip_b_one = skip_b ? 1.0 : 0.0;
 
@@ -2075,7 +2072,7 @@ __device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, cons
     // the last word finds the values of hand-over g in the others.  A boundary's buffer holds
     // kRing hand-overs.  Before it overwrites the one that held hand-over g - kRing, a wavefront
     // makes sure that the one above has taken that, which it says by publishing that number itself.
-    auto hand_over = [&]() {
+    auto hand_over = [&]() __attribute__((always_inline)) {
         ++generation;
         const int half = generation & (kRing - 1);
         const int2* const tag = &below_lds->tag[half][rd_slot];
@@ -2121,9 +2118,9 @@ __device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, cons
     };
 
     int prev_lo = 0, prev_hi = 0;
-    auto from_lane_below = [&](double mine) { return shift_up(mine, prev_lo, prev_hi); };
-    auto top_value = [&]() { return fmax(fmax(va_blank, va_label), fmax(vb_blank, vb_label)); };
-    auto renew_frames = [&]() {
+    auto from_lane_below = [&](double mine) __attribute__((always_inline)) { return shift_up(mine, prev_lo, prev_hi); };
+    auto top_value = [&]() __attribute__((always_inline)) { return fmax(fmax(va_blank, va_label), fmax(vb_blank, vb_label)); };
+    auto renew_frames = [&]() __attribute__((always_inline)) {
         const int rise = f.renew(top_value(), halo > 0 ? halo - 1 : 0);
         va_blank = __builtin_amdgcn_ldexp(va_blank, rise);
         va_label = __builtin_amdgcn_ldexp(va_label, rise);
@@ -2132,7 +2129,7 @@ __device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, cons
         skip_a_scale = skip_a ? f.scale : 0.0;
     };
 
-    auto checkpoint = [&]() {
+    auto checkpoint = [&]() __attribute__((always_inline)) {
         const CheckpointState state_a{va_blank, va_label}, state_b{vb_blank, vb_label};
         vp[0] = kBackward ? state_b : state_a;
         vp[1] = kBackward ? state_a : state_b;
@@ -2141,18 +2138,18 @@ __device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, cons
         vp += row_step;
         fp += row_step;
     };
-    auto mid_block = [&]() {
-        if (__builtin_expect((f.rough | steep) != 0, 0))
+    auto mid_block = [&]() __attribute__((always_inline)) {
+        if (__builtin_expect((f.rough | look) != 0, 0))
             if (f.renewal_due(top_value())) renew_frames();
     };
-    auto end_block = [&](bool second) {
+    auto end_block = [&](bool second) __attribute__((always_inline)) {
         if (waves > 1 && (second || every_block)) hand_over();
         if (__builtin_expect(f.renewal_due(top_value()), 0)) renew_frames();
     };
     // One step (see run_chain_linear): the pairs' own sums fill the time that the shift takes.
     //   label' = (label + blank + skip * previous label) * emission, as fma(previous, skip, label + blank)
     auto pin = []() { __builtin_amdgcn_sched_barrier(0); };
-    auto advance = [&](float ela, float elb) {
+    auto advance = [&](float ela, float elb) __attribute__((always_inline)) {
 #pragma clang fp contract(off)                           // (a product stays a product: fusing it into the next step's sum would tie the steps together)
         const double prev = from_lane_below(vb_label);
         pin();
@@ -2179,16 +2176,19 @@ __device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, cons
     };
 
     float ela[4][kChunk], elb[4][kChunk];
-    auto fetch = [&](auto set, int) {
+    auto fetch = [&](auto set, int) __attribute__((always_inline)) {
         constexpr int k = decltype(set)::value;
         fetch_chunk<kBackward>(epa, step_a, ela[k]);
         fetch_chunk<kBackward>(epb, step_b, elb[k]);
         __builtin_amdgcn_sched_barrier(0);
     };
-    auto run = [&](auto set, int) {
+    auto run = [&](auto set, int) __attribute__((always_inline)) {
         constexpr int k = decltype(set)::value;
 #pragma unroll
-        for (int q = 0; q < kChunk; ++q) advance(ela[k][q], elb[k][q]);
+        for (int q = 0; q < kChunk; ++q) {
+            advance(ela[k][q], elb[k][q]);
+            if (kSteep && q == kSteepSteps - 1) mid_block();
+        }
         if (!(k & 1)) mid_block();
         else {
             end_block(k == 3);
@@ -2409,7 +2409,7 @@ __device__ __forceinline__ int lattice_body(const int chain, const Utt* __restri
     // gives one pair or two to a lane as the launcher planned it (two_pairs_per_lane).
     const int met = rows_flagged(wk.row_flags, u, wk.flag_blocks, m.Tb);
     const bool in_log_domain = kSync == Sync::kBarrier || kMode == Mode::kBest || (m.flags & kUttLogDomain) != 0 || (met & kRowsSmall) != 0;
-    const bool gentle = m.rough == 0 && (met & kRowsRough) == 0;
+    const bool gentle = m.rough == 0 && (met & kRowsRough) == 0, steep = m.steep != 0 || (met & kRowsSteep) != 0;
     if (kMode == Mode::kLoss && in_log_domain && !forward) return 0;       // (the forward chain runs all the way)
     const bool two_pairs = kSync == Sync::kHalo && !in_log_domain && (m.flags & kUttTwoPairs) != 0;
     const int waves = two_pairs ? m.waves2 : m.waves;
@@ -2463,22 +2463,27 @@ __device__ __forceinline__ int lattice_body(const int chain, const Utt* __restri
         return 0;
     }
     // (for the gradient, which must know what each chain has left: a word per direction)
-    if (kMode == Mode::kGrad && threadIdx.x == 0) publish(&wk.domain[2 * u + (forward ? 0 : 1)], in_log_domain ? 1 : 0);
+    if (kMode == Mode::kGrad && threadIdx.x == 0) publish(&wk.domain[2 * u + (forward ? 0 : 1)], in_log_domain ? kDomainLog : (steep ? kDomainSteep : 0));
     if constexpr (kSync != Sync::kBarrier && kMode != Mode::kBest) {
         if (!in_log_domain) {
             bool lost = false;
-            if (two_pairs) {
-                if constexpr (kSync == Sync::kHalo) {
-                    if (forward)
-                        lost = run_chain_linear2<false, kMode>(m, u, gentle, labels, emit_label, lat.alpha, lat.alpha_exponents, mass, chain_err, sink, lds);
-                    else
-                        lost = run_chain_linear2<true, kMode>(m, u, gentle, labels, emit_label, lat.beta, lat.beta_exponents, mass, chain_err, sink, lds);
+            auto run = [&](auto steep_ones) __attribute__((always_inline)) {
+                constexpr bool kSteep = decltype(steep_ones)::value;
+                if (two_pairs) {
+                    if constexpr (kSync == Sync::kHalo) {
+                        if (forward)
+                            lost = run_chain_linear2<false, kMode, kSteep>(m, u, gentle, labels, emit_label, lat.alpha, lat.alpha_exponents, mass, chain_err, sink, lds);
+                        else
+                            lost = run_chain_linear2<true, kMode, kSteep>(m, u, gentle, labels, emit_label, lat.beta, lat.beta_exponents, mass, chain_err, sink, lds);
+                    }
+                } else if (forward) {
+                    lost = run_chain_linear<false, kSync, kMode, kSteep>(m, u, gentle, labels, emit_label, lat.alpha, lat.alpha_exponents, mass, chain_err, sink, lds);
+                } else {
+                    lost = run_chain_linear<true, kSync, kMode, kSteep>(m, u, gentle, labels, emit_label, lat.beta, lat.beta_exponents, mass, chain_err, sink, lds);
                 }
-            } else if (forward) {
-                lost = run_chain_linear<false, kSync, kMode>(m, u, gentle, labels, emit_label, lat.alpha, lat.alpha_exponents, mass, chain_err, sink, lds);
-            } else {
-                lost = run_chain_linear<true, kSync, kMode>(m, u, gentle, labels, emit_label, lat.beta, lat.beta_exponents, mass, chain_err, sink, lds);
-            }
+            };
+            if (__builtin_expect(steep, 0)) run(std::true_type{});
+            else run(std::false_type{});
             if (kMode == Mode::kLoss) finish_loss(m, u, labels, lat, emit_blank, mass, wk.done, costs, waves, lost);
             if (kFused) announce_end(&wk.done[u * kDoneStride], waves);
             return left;
@@ -2766,15 +2771,20 @@ struct LanePairs {
     int frame;
     double scale;                                        // 2^(neighbour's frame - frame)
 };
+// steep: the next renewal comes after kSteepSteps frames, otherwise after a chunk.
 template <bool kBackward>
-__device__ __forceinline__ void renew_pairs(LanePairs& s, int frame0, int frame1)
+__device__ __forceinline__ void renew_pairs(LanePairs& s, int frame0, int frame1, bool steep)
 {
     const double top0 = fmax(s.blank0, s.label0), top1 = fmax(s.blank1, s.label1);
     const int mine = max(top0 > 0.0 ? frame0 + __builtin_amdgcn_frexp_exp(top0) : kNoExponent,
                          top1 > 0.0 ? frame1 + __builtin_amdgcn_frexp_exp(top1) : kNoExponent);
     int window = mine;
+    auto lanes = [&](int from, int to) __attribute__((always_inline)) {
 #pragma unroll
-    for (int k = 0; k < kChunk / 2; ++k) window = kBackward ? window_max_step_down(window, mine) : window_max_step(window, mine);
+        for (int k = from; k < to; ++k) window = kBackward ? window_max_step_down(window, mine) : window_max_step(window, mine);
+    };
+    lanes(0, kSteepSteps / 2);
+    if (__builtin_expect(!steep, 1)) lanes(kSteepSteps / 2, kChunk / 2);
     window = lane_frame(window, mine);
     s.blank0 = __builtin_amdgcn_ldexp(s.blank0, frame0 - window);
     s.label0 = __builtin_amdgcn_ldexp(s.label0, frame0 - window);
@@ -2856,9 +2866,11 @@ struct BlockEnds {
 // alpha's high dwords wait in LDS, s_alpha0 and s_alpha1 [row][kShareRow], each lane's in a slot of its own that is free
 // again when file is called for the row.  (In registers they cost 32 of them, and the loops over the chunks had to be
 // unrolled: code that runs once per wavefront comes out of memory no faster than data.)
+// steep: the chains were steep ones, and so frames are renewed every kSteepSteps here too.  (A branch: as a variant of its own the code
+// took 20 to 59 registers more; the branch 2 to 5, and no time that can be measured.)
 template <int kScaleLog2, typename Emissions, typename File>
 __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at, const BlockEnds& ends,
-                                             const double packed_inverse_p, const int block,
+                                             const double packed_inverse_p, const bool steep, const int block,
                                              const int own_first, const int own_end, unsigned* s_alpha0, unsigned* s_alpha1,
                                              Emissions&& emissions, File&& file)
 {
@@ -2874,6 +2886,7 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
 
     // alpha
     int alpha_frame0 = 0, alpha_frame1 = 0;              // of the block's two chunks
+    int alpha_middle0 = 0, alpha_middle1 = 0;            // ... from their middle on
     {
         LanePairs s;
         s.blank0 = block > 0 ? (has0 ? ends.a0.blank : 0.0) : (p0 == 0 ? 1.0 : 0.0);
@@ -2881,20 +2894,25 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
         s.blank1 = block > 0 && has1 ? ends.a1.blank : 0.0;
         s.label1 = block > 0 && has1 ? ends.a1.label : 0.0;
         int prev_lo = 0, prev_hi = 0;
-        renew_pairs<false>(s, ends.fa0, ends.fa1);
-        alpha_frame0 = s.frame;
+        renew_pairs<false>(s, ends.fa0, ends.fa1, steep);
+        alpha_frame0 = alpha_middle0 = s.frame;
         emissions(0, el0, el1);
 #pragma unroll 1
         for (int h = 0; h < 2; ++h) {
             if (h) {
-                renew_pairs<false>(s, s.frame, s.frame);
-                alpha_frame1 = s.frame;
+                renew_pairs<false>(s, s.frame, s.frame, steep);
+                alpha_frame1 = alpha_middle1 = s.frame;
                 emissions(1, el0, el1);
             }
-            const double skip0_scale = skip0_one * s.scale;
+            double skip0_scale = skip0_one * s.scale;
 #pragma unroll
             for (int q = 0; q < kChunk; ++q) {
 #pragma clang fp contract(off)
+                if (q == kSteepSteps && __builtin_expect(steep, 0)) {
+                    renew_pairs<false>(s, s.frame, s.frame, steep);
+                    (h ? alpha_middle1 : alpha_middle0) = s.frame;
+                    skip0_scale = skip0_one * s.scale;
+                }
                 const double prev = shift_up(s.label1, prev_lo, prev_hi);
                 pin();
                 const double u1 = s.blank1 + s.label1;
@@ -2937,13 +2955,18 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
     // A step's shares are formed during the step after it (before the first: of zeros, in a row that is filed again).
     double pending_alpha0 = 0.0, pending_alpha1 = 0.0, pending_beta0 = 0.0, pending_beta1 = 0.0;
     int pending_row = kBlockFrames - 1;
-    renew_pairs<true>(s, ends.fb0, ends.fb1);
+    renew_pairs<true>(s, ends.fb0, ends.fb1, steep);
 #pragma unroll 1
     for (int h = 1; h >= 0; --h) {
-        if (h == 0) renew_pairs<true>(s, s.frame, s.frame);
-        const int exponents = (h == 0 ? alpha_frame0 : alpha_frame1) + s.frame + to_share;
-        const int x0 = own0 ? exponents : kNoExponent, x1 = own1 ? exponents : kNoExponent;
-        const double skip2_scale = skip2_one * s.scale;
+        if (h == 0) renew_pairs<true>(s, s.frame, s.frame, steep);
+        int x0, x1;
+        auto set_exponents = [&](int alpha_frame) __attribute__((always_inline)) {
+            const int exponents = alpha_frame + s.frame + to_share;
+            x0 = own0 ? exponents : kNoExponent;
+            x1 = own1 ? exponents : kNoExponent;
+        };
+        set_exponents(h == 0 ? alpha_middle0 : alpha_middle1);
+        double skip2_scale = skip2_one * s.scale;
         if (h == 0) emissions(2, el0, el1);              // (chunk 1's are still there)
         unsigned alpha0[kChunk], alpha1[kChunk];
 #pragma unroll
@@ -2954,6 +2977,11 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
 #pragma unroll
         for (int q = kChunk - 1; q >= 0; --q) {
 #pragma clang fp contract(off)
+            if (q == kSteepSteps - 1 && __builtin_expect(steep, 0)) {
+                renew_pairs<true>(s, s.frame, s.frame, steep);
+                set_exponents(h == 0 ? alpha_frame0 : alpha_frame1);
+                skip2_scale = skip2_one * s.scale;
+            }
             const double next = shift_down(s.label0, next_lo, next_hi);
             pin();
             const double share0 = pending_alpha0 * pending_beta0;
@@ -3048,12 +3076,12 @@ __device__ __forceinline__ void for_pieces(int L, int first, int step, F&& for_p
 // which last as long as one block takes (English minibatch: 18.8 -> 16.7 us; 512 utterances: 69 -> 83 us).
 constexpr int kShareBlocksMost = 8192;    // blocks times pieces: two rounds of what the chip holds
 __host__ __device__ constexpr int block_waves(int L) { return label_pieces(L) <= 1 ? 1 : (label_pieces(L) == 2 ? 2 : 4); }
-// The domains of an utterance's two chains as its chains published them (a word per direction).
+// The domain of an utterance as its chains published it (a word per direction).
 template <bool kPublished>
-__device__ __forceinline__ bool in_log_domain(const int* domain, int b)
+__device__ __forceinline__ int domain_of(const int* domain, int b)
 {
     const int d = kPublished ? published(&domain[2 * b]) | published(&domain[2 * b + 1]) : domain[2 * b] | domain[2 * b + 1];
-    return __builtin_amdgcn_readfirstlane(d) != 0;
+    return __builtin_amdgcn_readfirstlane(d);
 }
 
 // Alphabets of at most 64 symbols (the English one has 29): a wavefront per block, or two or four that share the label's
@@ -3237,12 +3265,17 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
     const int first_base = part * kPieceStep;
     const LaneLabels first_labels(L > 0 ? labels + m.lab_off : &meta[b].L, max(L, 1), first_base);
     BlockEnds ends;
-    bool log_domain = false;
+    bool log_domain = false, steep = false;
     double packed_inverse_p = 0.0;
     auto load_ends = [&]() {
         ends = BlockEnds::load<kWait>(m, lat, first_labels.p0, block);
-        log_domain = in_log_domain<kWait>(g_args.domain, b);
         packed_inverse_p = kWait ? published(&g_args.mass[b * kMassWords + kMassInverse]) : g_args.mass[b * kMassWords + kMassInverse];
+        const int domain = domain_of<kWait>(g_args.domain, b);
+        if (kLean)                                       // (the same in every lane: two registers)
+            packed_inverse_p = __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(packed_inverse_p)),
+                                                __builtin_amdgcn_readfirstlane(__double2loint(packed_inverse_p)));
+        log_domain = (domain & kDomainLog) != 0;
+        steep = (domain & kDomainSteep) != 0;
     };
     if (!kWait) load_ends();
     __builtin_amdgcn_sched_barrier(0);
@@ -3278,16 +3311,27 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
         mask[n] = k == blank ? static_cast<unsigned>(kNoSymbol) * 0x01010101u : 0x7F7F7F7Fu;
         acc[n] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
     }
-    for_pieces(L, part, sharing, [&](int base, int own_first, int own_end) {
-        auto file = [&](int row, float x0, float x1) {
-            const half2_raw hi = nearest_halves(x0, x1);
-            const half2_raw lo = nearest_halves(minus_low_half(x0, hi), minus_high_half(x1, hi));
-            s_hi[row * kShareRow + lane] = __builtin_bit_cast(unsigned, hi);
-            s_lo[row * kShareRow + lane] = __builtin_bit_cast(unsigned, lo);
-        };
-        if (log_domain) {
+    auto file = [&](int row, float x0, float x1) {
+        const half2_raw hi = nearest_halves(x0, x1);
+        const half2_raw lo = nearest_halves(minus_low_half(x0, hi), minus_high_half(x1, hi));
+        s_hi[row * kShareRow + lane] = __builtin_bit_cast(unsigned, hi);
+        s_lo[row * kShareRow + lane] = __builtin_bit_cast(unsigned, lo);
+    };
+    auto product = [&](int base) __attribute__((always_inline)) {
+        // LDS operations of one wavefront complete in program order; the fences only keep the
+        // compiler from moving them across.
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        share_product<kTiles>(acc, s_hi, s_lo, s_label, base, L, symbol, mask);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    };
+    // (two loops: in one, what either recursion needs is held through the other, 20 registers)
+    if (log_domain)
+        for_pieces(L, part, sharing, [&](int base, int own_first, int own_end) {
             block_shares_log<kShareScaleLog2, 1>(m, lat, packed_inverse_p, block, base, own_first, own_end, file);
-        } else {
+            product(base);
+        });
+    else
+        for_pieces(L, part, sharing, [&](int base, int own_first, int own_end) {
             LaneLabels at = first_labels;
             if (base != first_base) {
                 at = LaneLabels(labels + m.lab_off, L, base);
@@ -3304,14 +3348,9 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
                 row(at.has0, at.symbol0, el0);
                 row(at.has1, at.symbol1, el1);
             };
-            block_shares<kShareScaleLog2>(m, at, ends, packed_inverse_p, block, own_first, own_end, s_hi, s_lo, emissions, file);
-        }
-        // LDS operations of one wavefront complete in program order; the fences only keep the
-        // compiler from moving them across.
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        share_product<kTiles>(acc, s_hi, s_lo, s_label, base, L, symbol, mask);
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    });
+            block_shares<kShareScaleLog2>(m, at, ends, packed_inverse_p, steep, block, own_first, own_end, s_hi, s_lo, emissions, file);
+            product(base);
+        });
     if (sharing > 1) {
         // the first of the wavefronts adds up what the others have, in their order
         float4v* const s_acc = reinterpret_cast<float4v*>(s_hi);
@@ -3439,7 +3478,7 @@ void ctc_gradient_wide_kernel(const TileArgs g, const Utt* __restrict__ meta, co
             ends = BlockEnds::load<false>(m, lat, at.p0, block);
         };
         load();
-        const bool log_domain = in_log_domain<false>(g.domain, b);
+        const int domain = domain_of<false>(g.domain, b);
         const double packed_inverse_p = g.mass[b * kMassWords + kMassInverse];
         __builtin_amdgcn_sched_barrier(0);
         const float inverse_p = packed_mantissa(packed_inverse_p);
@@ -3452,7 +3491,7 @@ void ctc_gradient_wide_kernel(const TileArgs g, const Utt* __restrict__ meta, co
                 share0[row] = x0 * inverse_p;
                 share1[row] = x1 * inverse_p;
             };
-            if (log_domain) block_shares_log<0, 2>(m, lat, packed_inverse_p, block, i * kPieceStep, own_first, own_end, file);
+            if (domain == kDomainLog) block_shares_log<0, 2>(m, lat, packed_inverse_p, block, i * kPieceStep, own_first, own_end, file);
             else {
                 // (the first chunk's are read once more when the second's have been taken: 16 registers)
                 auto emissions = [&](int k, float (&el0)[kChunk], float (&el1)[kChunk]) {
@@ -3467,7 +3506,7 @@ void ctc_gradient_wide_kernel(const TileArgs g, const Utt* __restrict__ meta, co
                         emit11 = chunk_emissions(at.has1, at.p1, 0);
                     }
                 };
-                block_shares<0>(m, at, ends, packed_inverse_p, block, own_first, own_end, s_alpha,
+                block_shares<0>(m, at, ends, packed_inverse_p, domain == kDomainSteep, block, own_first, own_end, s_alpha,
                                 s_alpha + kBlockFrames * kShareRow, emissions, file);
             }
             i += waves;

@@ -57,6 +57,8 @@ __device__ __forceinline__ float log2_softmax(float x, float row_max, float log2
 {
     return fmaf(x - row_max, kLog2e, -log2_sum);
 }
+// ... and its numerator, 2^((x - max) log2 e).
+__device__ __forceinline__ float exp2_from_max(float x, float row_max) { return fast_exp2((x - row_max) * kLog2e); }
 
 // ---- element access for the two activation types -------------------------------------
 
@@ -416,24 +418,29 @@ __device__ __forceinline__ void setup_words(const Utt m, const int b, const Setu
 // A lane that stores a negative word raises the utterance's kUttLogDomain flag, and its chains then take logarithms.
 // (The most probable alignment has no sums to speed up: its launches store plain logarithms.)
 struct FrameNorm {
-    float log_blank, blank, inverse;                     // log2 y_blank, y_blank, about 1 / y_blank
+    float inverse_sum, log_blank, blank, inverse;        // of the row; log2 y_blank, y_blank, about 1 / y_blank
     bool small;                                          // the norm is 1
-    // From the blank's logit, the row's largest one, and the sum of 2^((x - max) log2 e) and its logarithm.  y_blank as a quotient:
-    // where a frame is nearly certain of its blank, the exponential of log2 y_blank would be off by an ulp or two of 1.
+    // From the blank's logit, the row's largest one, and the sum of 2^((x - max) log2 e) and its logarithm.  Probabilities are products
+    // with 1 / sum: where a frame is nearly certain of a symbol, the exponential of log2 y would be off by an ulp or two of 1, and
+    // elsewhere it carries the rounding of a larger logarithm (see encode_emission).
     __device__ __forceinline__ FrameNorm(float x, float row_max, float sum, float log2_sum)
     {
         log_blank = log2_softmax(x, row_max, log2_sum);
-        const float about = __builtin_amdgcn_rcpf(sum), inverse_sum = fmaf(fmaf(-sum, about, 1.0f), about, about);
-        blank = fast_exp2((x - row_max) * kLog2e) * inverse_sum;
+        const float about = __builtin_amdgcn_rcpf(sum);
+        inverse_sum = fmaf(fmaf(-sum, about, 1.0f), about, about);
+        blank = exp2_from_max(x, row_max) * inverse_sum;
         inverse = __builtin_amdgcn_rcpf(blank);
         small = log_blank < kLinearMinLog2;
     }
     __device__ __forceinline__ float word() const { return small ? log_blank - 1.0f : blank; }
 };
-// The emission of a symbol whose log2 y is lp.
-__device__ __forceinline__ float encode_emission(float lp, const FrameNorm& f)
+// The emission of a symbol whose log2 y is lp and whose 2^((x - max) log2 e) is e.  The gradient multiplies the ratio by the norm
+// again, which costs y a rounding or two; as a product y has that much less to begin with.  2-norm of its error, symbols of no label,
+// 29 symbols, logits N(0, 1), N(0, 2) and N(0, 6): 7.0e-8, 6.9e-8, 7.7e-8; from the exponential of lp 1.12e-7, 7.95e-8, 7.8e-8, and
+// without ratio and norm between 1.10e-7, 7.6e-8, 7.3e-8.
+__device__ __forceinline__ float encode_emission(float lp, float e, const FrameNorm& f)
 {
-    const float y = fast_exp2(lp), q = y * f.inverse;
+    const float y = e * f.inverse_sum, q = y * f.inverse;
     const float ratio = fmaf(fmaf(-q, f.blank, y), f.inverse, q);
     return lp < kLinearMinLog2 ? (f.small ? lp : lp - f.log_blank) : (f.small ? y : ratio);
 }
@@ -645,8 +652,8 @@ void ctc_softmax_rows_kernel(const T* __restrict__ x, T* __restrict__ grads, Utt
     float* const erow = emit_label + emission_at(m.e_off, m.L, t, 0);
     for (int j = q; j < m.L; j += kLanes) {
         const int c = j == q ? c_first : lab[j];
-        const float lp = log2_softmax(load_elem(row, c), mx, ls);
-        erow[static_cast<size_t>(j) * kChunk] = sa.plain_logs ? lp : encode_emission(lp, norm);
+        const float logit = load_elem(row, c), lp = log2_softmax(logit, mx, ls);
+        erow[static_cast<size_t>(j) * kChunk] = sa.plain_logs ? lp : encode_emission(lp, exp2_from_max(logit, mx), norm);
         lowest = fminf(lowest, lp);
     }
     if (t == m.Tb - 1) store_virtual_frames(m, emit_blank, sa.emit_blank64, emit_label, sa.plain_logs, q, kLanes);
@@ -697,8 +704,8 @@ void ctc_softmax_kernel(const T* __restrict__ x, T* __restrict__ grads,
     float* erow = emit_label + emission_at(m.e_off, m.L, t, 0);
     const int* lab = labels + m.lab_off;
     for (int j = threadIdx.x; j < m.L; j += kRowThreads) {
-        const float lp = log2_softmax(load_elem(row, lab[j]), mx, ls);
-        erow[static_cast<size_t>(j) * kChunk] = sa.plain_logs ? lp : encode_emission(lp, norm);
+        const float logit = load_elem(row, lab[j]), lp = log2_softmax(logit, mx, ls);
+        erow[static_cast<size_t>(j) * kChunk] = sa.plain_logs ? lp : encode_emission(lp, exp2_from_max(logit, mx), norm);
         lowest = fminf(lowest, lp);
     }
     raise_flags(meta, b, m, lowest);
@@ -769,9 +776,12 @@ __device__ __forceinline__ float narrow_rows_of(const T* __restrict__ x, float* 
 #pragma unroll
         for (int u = 0; u < kPerLane; ++u) mx = fmaxf(mx, v[u]);         // (the last symbol again where there is none)
         mx = quad_max(mx);
-        float sum = 0.0f;
+        float from_max[kPerLane], sum = 0.0f;
 #pragma unroll
-        for (int u = 0; u < kPerLane; ++u) sum += q + u * kPerRow < A ? fast_exp2((v[u] - mx) * kLog2e) : 0.0f;
+        for (int u = 0; u < kPerLane; ++u) {
+            from_max[u] = exp2_from_max(v[u], mx);
+            sum += q + u * kPerRow < A ? from_max[u] : 0.0f;
+        }
         sum = quad_sum(sum);
         const float ls = fast_log2(sum);
         const FrameNorm norm(blank_logit, mx, sum, ls);
@@ -779,7 +789,7 @@ __device__ __forceinline__ float narrow_rows_of(const T* __restrict__ x, float* 
 #pragma unroll
         for (int u = 0; u < kPerLane; ++u) {
             const int k = q + u * kPerRow;
-            const float l = log2_softmax(v[u], mx, ls), e = plain_logs ? l : (k == blank ? encode_blank(norm) : encode_emission(l, norm));
+            const float l = log2_softmax(v[u], mx, ls), e = plain_logs ? l : (k == blank ? encode_blank(norm) : encode_emission(l, from_max[u], norm));
             lowest = fminf(lowest, l);
             if (k < A) lrow[k] = e;
         }

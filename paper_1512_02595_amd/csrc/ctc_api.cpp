@@ -466,7 +466,7 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
         int64_t rows = static_cast<int64_t>(c.T) * c.B;
         for (int i = 0; i < n_run; ++i) rows -= run_frames[i];
         out->defer = deferred_frames(static_cast<double>(rows) * c.A * elem, max_frames, n_run * dirs, out->n_cu);
-        out->defer_columns = columns_frames(static_cast<double>(rows) * c.A * elem, c.A, out->defer, c.T, out->n_cu);
+        out->defer_columns = columns_frames(static_cast<double>(rows) * c.A * elem, c.A, out->defer);
     }
     out->fused = c.mode == Mode::kGrad && !needs_barrier && !sequential_chains && n_run > 0 &&
                  can_fuse_gradient(c.A, max_waves, n_run * dirs, out->n_cu);
@@ -654,7 +654,7 @@ ctc_status_t run_device(const void* x, const int32_t* labels, const int32_t* lab
     // (how much padding there is only the GPU knows: taken for a third of the tensor)
     p.defer = grads && A > kDirectMaxA && !p.needs_barrier
                   ? deferred_frames(static_cast<double>(T) * B * A * elem / 3, T / 2, p.n_chains, p.n_cu) : 0;
-    p.defer_columns = grads && A > kDirectMaxA && !p.needs_barrier ? columns_frames(static_cast<double>(T) * B * A * elem / 3, A, p.defer, T, p.n_cu) : 0;
+    p.defer_columns = grads && A > kDirectMaxA && !p.needs_barrier ? columns_frames(static_cast<double>(T) * B * A * elem / 3, A, p.defer) : 0;
     const int overlap = g_overlap.load(std::memory_order_relaxed);
     p.late_percent = overlap <= 100 ? std::max(overlap, 0) : 0;
     p.fused = grads && !p.needs_barrier && overlap != 0 && can_fuse_gradient(A, p.max_waves, p.n_chains, p.n_cu);

@@ -216,10 +216,20 @@ inline int deferred_frames(double zero_bytes, int longest, int n_chains, int n_c
 constexpr double kFillBesideColumns = 40.0e6, kFillBesideColumnsFrom = 100.0e6;      // (176 x 68 x 2051, 20 MB: 51.8 us without, 56.6 with)
 // Rows of 2048 symbols and less take a wavefront of its own too long for that (512 x 300 x 100: 102.8 us without, 126.6 with).
 constexpr int kFillBesideColumnsMinA = 2048;
-inline int columns_frames(double zero_bytes, int A, int deferred, int T, int n_cu)
+inline int columns_frames(double zero_bytes, int A, int deferred)
 {
-    if (zero_bytes < kFillBesideColumnsFrom || A <= kFillBesideColumnsMinA || frame_blocks(T) + n_cu > 65535) return 0;     // (a grid's second dimension)
+    if (zero_bytes < kFillBesideColumnsFrom || A <= kFillBesideColumnsMinA) return 0;
     return static_cast<int>(std::min(16.0 - deferred, 16.0 * kFillBesideColumns / zero_bytes + 0.5));
+}
+
+// That launch has the utterances in its grid's first dimension and `rows`, as many as an utterance of a million and more frames has
+// blocks, in the other two, which take kMaxGridRows each.
+constexpr int kMaxGridRows = 65535;
+struct WideRows { int y, z; };
+inline WideRows wide_rows(int rows)
+{
+    const int z = (rows + kMaxGridRows - 1) / kMaxGridRows;
+    return {(rows + z - 1) / z, z};
 }
 
 // The gradient's recomputation takes a label in pieces of 128 positions, one to a wavefront, whose inner edges overlap by the

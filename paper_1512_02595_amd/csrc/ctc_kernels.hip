@@ -3417,7 +3417,7 @@ void ctc_gradient_narrow_kernel(const TileArgs args, const Utt* __restrict__ met
 // blank's are corrected.  A workgroup per block.  Its wavefronts take the label's pieces; the shares go to LDS in slot order
 // (the positions of a symbol next to each other, setup_role), and the lane of a symbol and frame adds up its run: one writer
 // per symbol and a fixed order.  The last wavefront, if it has no piece, lists the symbols meanwhile.  The launch waits for its
-// slowest block and leaves the memory idle, so its first workgroups write zero rows (columns_frames).  grid (B, fill.rounds + blocks of T);
+// slowest block and leaves the memory idle, so its first workgroups write zero rows (columns_frames).  grid B, fill.rounds + blocks of T (wide_rows);
 // LDS: wide_lds_bytes.
 // What bounds it: in launches of up to a block per SIMD (64 utterances of 500 frames: 1140) the time of the slowest block, beyond
 // that the issue of the recomputation.  With a wavefront to a block a block took 7 to 25 us (loads 2, a piece 4.5, sums 1 to 10),
@@ -3444,9 +3444,10 @@ void ctc_gradient_wide_kernel(const TileArgs g, const Utt* __restrict__ meta, co
                               const float* __restrict__ emit_blank, const float* __restrict__ emit_label, const LatticeOut lat,
                               const FillArgs fill)
 {
-    if (kFill && static_cast<int>(blockIdx.y) < fill.rounds) {
+    const int grid_row = static_cast<int>(blockIdx.z * gridDim.y + blockIdx.y);
+    if (kFill && grid_row < fill.rounds) {
         const int waves = blockDim.x >> 6;
-        fill_rows(fill, meta, static_cast<int>(blockIdx.y * gridDim.x + blockIdx.x) * waves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6),
+        fill_rows(fill, meta, static_cast<int>(grid_row * gridDim.x + blockIdx.x) * waves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6),
                   static_cast<int>(fill.rounds * gridDim.x) * waves);
         return;
     }
@@ -3454,7 +3455,7 @@ void ctc_gradient_wide_kernel(const TileArgs g, const Utt* __restrict__ meta, co
     __shared__ int s_symbols;
     extern __shared__ uint4v wide_lds[];
     const int B = g.B, A = g.A, blank = g.blank;
-    const int lane = threadIdx.x & 63, block = static_cast<int>(blockIdx.y) - (kFill ? fill.rounds : 0), t0 = block * kBlockFrames;
+    const int lane = threadIdx.x & 63, block = grid_row - (kFill ? fill.rounds : 0), t0 = block * kBlockFrames;
     const int b = static_cast<int>((blockIdx.x + 3u * block) % static_cast<unsigned>(B));      // (three: neighbours change dies too)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
     const Utt m = uniform_record(meta[b]);
@@ -4035,7 +4036,8 @@ int launch_gradient(const Launch& p, void* stream)
         // (a workgroup to a compute unit; twice and four times as many 0.5 % slower)
         fill = FillArgs{p.grads, p.dtype == CTC_DTYPE_F32 ? 4 : 2, p.T, p.B, p.A, p.defer, p.defer_columns, p.n_cu, p.n_chains, std::max(1, p.n_cu / p.B)};
     }
-    const dim3 grid = p.A > kDirectMaxA ? dim3(p.B, args.groups + fill.rounds) : dim3(args.groups, p.B), block(p.A > kDirectMaxA ? 64 * args.waves : kRowThreads);
+    const WideRows rows = wide_rows(args.groups + fill.rounds);
+    const dim3 grid = p.A > kDirectMaxA ? dim3(p.B, rows.y, rows.z) : dim3(args.groups, p.B), block(p.A > kDirectMaxA ? 64 * args.waves : kRowThreads);
     return checked_launch([&] {
         if (p.A > kDirectMaxA && p.defer_columns > 0)
             hipLaunchKernelGGL(ctc_gradient_wide_kernel<true>, grid, block, lds, s, args, meta, p.labels, emit_blank, emit_label,

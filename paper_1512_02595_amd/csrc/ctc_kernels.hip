@@ -1236,7 +1236,7 @@ __device__ __forceinline__ Norms norms_of_lane(const Utt& m, const float* __rest
 }
 // The parts of a wavefront's lanes (all of them active) put together: the same in every lane, and the same each time.
 // (750 frames: 2.5 us for both together, most of it waiting for memory, so whoever has nothing else to do does it: the
-// gradient's workgroups, which write the cost, or a wavefront of a cost-only call that has no part in the chain.)
+// gradient's workgroups, which write the cost, or workgroups of their own in a cost-only call.)
 template <int kCtrl>
 __device__ __forceinline__ Norms norms_permuted(const Norms& n)
 {
@@ -2255,6 +2255,7 @@ struct LaunchWords {
     int status_count;
     int skip_directions;      // bit 0: leave the forward chains out, bit 1: the backward chains (measurements only)
     FillArgs fill;            // zero rows to write beside the chains
+    int norm_groups, utterances;  // cost-only launches: the first workgroup that sees to the utterances' norms, and how many there are
 };
 
 // Cost-only calls: the mass of an utterance from the states that its two chains have left where they meet, alpha after
@@ -2262,18 +2263,18 @@ struct LaunchWords {
 //   p = sum over states s of  (sum of alpha over s and its predecessors) * beta(s).
 // A wavefront that has ended counts itself in, and the utterance's last one does the sum, whichever it is: the order of
 // the additions is that of the pairs.  The count carries, in its upper half, how many wavefronts gave up waiting for a
-// neighbour; then the cost is NaN.  `waves`: wavefronts of a chain.
+// neighbour; then the cost is NaN.  `waves`: wavefronts of a chain.  One more wavefront counts itself in, which has nothing to do with
+// the chains and leaves the norms (norms_of_utterance).
+template <bool kOfChain>
 __device__ __forceinline__ void finish_loss(const Utt& m, const int u, const int* __restrict__ labels, const LatticeOut& lat,
-                                            const float* __restrict__ emit_blank, double* __restrict__ mass, int* __restrict__ done,
-                                            float* __restrict__ costs, const int waves, const bool lost)
+                                            const double* __restrict__ mass, int* __restrict__ done, float* __restrict__ costs,
+                                            const int waves, const bool lost)
 {
-    const int lane = threadIdx.x & 63;
-    // a wavefront of the forward chain's workgroup without a part in the chain sees to the norms meanwhile, where there is one
-    const bool helped = static_cast<int>(blockDim.x) > 64 * waves;
-    const int expected = 2 * waves + (helped ? 1 : 0);
-    // (device scope: the chains may run on different dies)
+    const int lane = threadIdx.x & 63, expected = 2 * waves + 1;
+    // (device scope: the chains may run on different dies; what has been published is past the die's cache once it is out)
     int before = 0;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    if (kOfChain) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if (lane == 0)
         before = __hip_atomic_fetch_add(&done[u * kDoneStride], lost ? 0x10001 : 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     before = __builtin_amdgcn_readfirstlane(before);
@@ -2284,9 +2285,7 @@ __device__ __forceinline__ void finish_loss(const Utt& m, const int u, const int
     const CheckpointState* const beta = reinterpret_cast<const CheckpointState*>(lat.beta + m.ab_off);
     const int *const fa = lat.alpha_exponents + m.ab_off, *const fb = lat.beta_exponents + m.ab_off;
     const int* const lab = labels + m.lab_off;
-    Norms norms{0.5, 1};
-    if (!helped) norms = norms_of_lane(m, emit_blank);
-    const double log2_norms = helped ? published(&mass[u * kMassWords + kMassNorms]) : 0.0;
+    const double log2_norms = published(&mass[u * kMassWords + kMassNorms]);
     // A lane's sum as sum * 2^top.
     double sum = 0.0;
     int top = kNoExponent;
@@ -2321,20 +2320,7 @@ __device__ __forceinline__ void finish_loss(const Utt& m, const int u, const int
         sum = __builtin_amdgcn_ldexp(sum, max(top - higher, -2000)) + __builtin_amdgcn_ldexp(other, max(other_top - higher, -2000));
         top = higher;
     }
-    if (!helped) norms = norms_of_wave(norms);
-    if (lane == 0) {
-        costs[u] = (before >> 16) != 0 || lost ? __uint_as_float(0x7FC00000u) : cost_of_mass(sum, top, helped ? log2_norms : norms.log2());
-    }
-}
-
-// Such a wavefront: leaves the norms and counts itself in.
-__device__ __forceinline__ void help_with_norms(const Utt& m, const int u, const int* __restrict__ labels, const LatticeOut& lat,
-                                                const float* __restrict__ emit_blank, double* __restrict__ mass, int* __restrict__ done,
-                                                float* __restrict__ costs, const int waves)
-{
-    const Norms norms = norms_of_wave(norms_of_lane(m, emit_blank));
-    if ((threadIdx.x & 63) == 0) publish(&mass[u * kMassWords + kMassNorms], norms.log2());
-    finish_loss(m, u, labels, lat, emit_blank, mass, done, costs, waves, false);
+    if (lane == 0) costs[u] = (before >> 16) != 0 || lost ? __uint_as_float(0x7FC00000u) : cost_of_mass(sum, top, log2_norms);
 }
 
 // The word that an utterance's chains and the workgroups that wait for them share: wavefronts that have ended, wavefronts
@@ -2445,10 +2431,6 @@ __device__ __forceinline__ int lattice_body(const int chain, const Utt* __restri
         }
         __syncthreads();
         if (kFused) left = __builtin_amdgcn_readfirstlane(hl->left);
-        if (kMode == Mode::kLoss && !in_log_domain && forward && static_cast<int>(threadIdx.x >> 6) == waves) {
-            help_with_norms(m, u, labels, lat, emit_blank, mass, wk.done, costs, waves);
-            return 0;
-        }
         if (idle) return left;
     } else if (kSync == Sync::kBarrier) {
         if (idle) {
@@ -2467,10 +2449,6 @@ __device__ __forceinline__ int lattice_body(const int chain, const Utt* __restri
         __syncthreads();
         left = __builtin_amdgcn_readfirstlane(hl->left);
         if (threadIdx.x >= 64) return left;
-    }
-    if (kSync == Sync::kNone && kMode == Mode::kLoss && threadIdx.x >= 64) {
-        if (!in_log_domain && forward) help_with_norms(m, u, labels, lat, emit_blank, mass, wk.done, costs, waves);
-        return 0;
     }
     // (for the gradient, which must know what each chain has left: a word per direction)
     if (kMode == Mode::kGrad && threadIdx.x == 0) publish(&wk.domain[2 * u + (forward ? 0 : 1)], in_log_domain ? kDomainLog : (steep ? kDomainSteep : 0));
@@ -2494,7 +2472,7 @@ __device__ __forceinline__ int lattice_body(const int chain, const Utt* __restri
             };
             if (__builtin_expect(steep, 0)) run(std::true_type{});
             else run(std::false_type{});
-            if (kMode == Mode::kLoss) finish_loss(m, u, labels, lat, emit_blank, mass, wk.done, costs, waves, lost);
+            if (kMode == Mode::kLoss) finish_loss<true>(m, u, labels, lat, mass, wk.done, costs, waves, lost);
             if (kFused) announce_end(&wk.done[u * kDoneStride], waves);
             return left;
         }
@@ -2507,12 +2485,30 @@ __device__ __forceinline__ int lattice_body(const int chain, const Utt* __restri
     return left;
 }
 
-// grid = one workgroup per entry of `order` (utterance * 2 + direction: 0 forward, 1 backward).
+// Cost-only launches: a wavefront of the workgroups behind the chains' leaves an utterance's norms and counts itself in.  (As one
+// wavefront more in the forward chain's workgroup it moved the workgroups after it to other SIMDs than order_chains means, and with a
+// write-back of the die's cache of its own: 512 x 750 frames 72 -> 83 us a call, 500 x 60 29.6 -> 35.7; so 69.6 and 28.9.)
+template <Sync kSync>
+__device__ __forceinline__ void norms_of_utterance(const Utt* __restrict__ meta, const int* __restrict__ labels, const float* __restrict__ emit_blank,
+                                                   const LatticeOut& lat, double* __restrict__ mass, float* __restrict__ costs, const LaunchWords& wk)
+{
+    const int u = (static_cast<int>(blockIdx.x) - wk.norm_groups) * static_cast<int>(blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (u >= wk.utterances) return;
+    const Utt m = meta[u];
+    if (!(m.flags & kUttRuns)) return;
+    if ((m.flags & kUttLogDomain) != 0 || (rows_flagged(wk.row_flags, u, wk.flag_blocks, m.Tb) & kRowsSmall) != 0) return;      // (run_chain_log)
+    const Norms norms = norms_of_wave(norms_of_lane(m, emit_blank));
+    if ((threadIdx.x & 63) == 0) publish(&mass[u * kMassWords + kMassNorms], norms.log2());
+    const bool two_pairs = kSync == Sync::kHalo && (m.flags & kUttTwoPairs) != 0;
+    finish_loss<false>(m, u, labels, lat, mass, wk.done, costs, two_pairs ? m.waves2 : m.waves, false);
+}
+
+// grid = one workgroup per entry of `order` (utterance * 2 + direction: 0 forward, 1 backward); cost-only launches: then those of
+// norms_of_utterance, a wavefront per utterance.
 // blockDim.x = 64 * (most wavefronts any utterance of the batch uses).
 // Variant for batches whose labels all fit one wavefront: no exchange at all.
-// (Cost-only calls: and a second wavefront for the norms.)
 template <Mode kMode>
-__global__ __launch_bounds__(kMode == Mode::kLoss ? 128 : 64)
+__global__ __launch_bounds__(64)
 void ctc_lattice_kernel_w1(const Utt* __restrict__ meta, const int* __restrict__ order,
                            const int* __restrict__ labels, const float* __restrict__ emit_blank,
                            const double* __restrict__ emit_blank64,
@@ -2523,6 +2519,10 @@ void ctc_lattice_kernel_w1(const Utt* __restrict__ meta, const int* __restrict__
 {
     if (kMode == Mode::kGrad && static_cast<int>(blockIdx.x) >= wk.fill.n_chains && wk.fill.defer > 0) {
         fill_rows_beside_chains(wk.fill, meta);
+        return;
+    }
+    if (kMode == Mode::kLoss && static_cast<int>(blockIdx.x) >= wk.norm_groups) {
+        norms_of_utterance<Sync::kNone>(meta, labels, emit_blank, lat, mass, costs, wk);
         return;
     }
     lattice_body<Sync::kNone, kMode>(order[blockIdx.x], meta, labels, emit_blank, emit_blank64, emit_label, lat,
@@ -2543,6 +2543,10 @@ void ctc_lattice_kernel(const Utt* __restrict__ meta, const int* __restrict__ or
     extern __shared__ double2 halo_lds[];                    // halo_lds_bytes(wavefronts of the workgroup)
     if (kMode == Mode::kGrad && static_cast<int>(blockIdx.x) >= wk.fill.n_chains && wk.fill.defer > 0) {
         fill_rows_beside_chains(wk.fill, meta);
+        return;
+    }
+    if (kMode == Mode::kLoss && static_cast<int>(blockIdx.x) >= wk.norm_groups) {
+        norms_of_utterance<Sync::kHalo>(meta, labels, emit_blank, lat, mass, costs, wk);
         return;
     }
     lattice_body<Sync::kHalo, kMode>(order[blockIdx.x], meta, labels, emit_blank, emit_blank64, emit_label, lat,
@@ -3937,7 +3941,7 @@ int launch_lattice(const Launch& p, void* stream)
     const LatticeOut lat = lattice_blocks(p);
     auto* mass = reinterpret_cast<double*>(p.ws + p.lay.mass);
     auto* chain_err = reinterpret_cast<int*>(p.ws + p.lay.chain_err);
-    const size_t lds_bytes = (p.max_waves > 1 && !p.needs_barrier) ? halo_lds_bytes(std::min(p.max_waves + 1, 16)) : 0;
+    const size_t lds_bytes = (p.max_waves > 1 && !p.needs_barrier) ? halo_lds_bytes(p.max_waves) : 0;
     int n_groups = std::max(p.n_chains, 1);
     LaunchWords wk{};
     wk.row_flags = p.folded ? reinterpret_cast<const int*>(p.ws + p.lay.row_flags) : nullptr;
@@ -3984,9 +3988,12 @@ int launch_lattice(const Launch& p, void* stream)
 #undef CTC_LAUNCH_FUSED_TILES
 #undef CTC_LAUNCH_FUSED
     }
-    // (cost-only calls: one wavefront more than the longest chain needs, for the norms)
-    const int waves = p.mode == Mode::kLoss && !p.needs_barrier ? std::min(p.max_waves + 1, 16) : p.max_waves;
-    const dim3 grid(n_groups), block(64 * waves);
+    if (p.mode == Mode::kLoss && !p.needs_barrier) {
+        wk.norm_groups = n_groups;
+        wk.utterances = p.B;
+        n_groups += (p.B + p.max_waves - 1) / p.max_waves;
+    }
+    const dim3 grid(n_groups), block(64 * p.max_waves);
 #define CTC_LAUNCH_LATTICE(KERNEL)                                                                 \
     hipLaunchKernelGGL(KERNEL, grid, block, lds_bytes, s, meta, order, labels, emit_blank,                 \
                        reinterpret_cast<const double*>(p.ws + p.lay.emit_blank64), emit_label,            \

@@ -3180,7 +3180,7 @@ struct TileArgs {
     int T, B, A, blank, Lmax;
     int share_blocks;             // narrow
     int waves, alpha_at;          // wide
-    int groups;                   // workgroups per utterance: one for its cost (narrow), then those with tiles
+    int groups;                   // workgroups per utterance
     int first_group;              // lattice launch: the first one with a tile
 };
 __device__ __forceinline__ void store_gradient(const TileArgs& g, size_t i, float v)
@@ -3204,7 +3204,7 @@ __device__ __forceinline__ int chains_awaited(const TileArgs& g, int b, int fram
         word = look();
     }
     if (!chains_ended(word)) {
-        if (tile_thread() == 0) word = __hip_atomic_fetch_or(done, kWaitGivenUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((tile_thread() & 63) == 0) word = __hip_atomic_fetch_or(done, kWaitGivenUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         word = __builtin_amdgcn_readfirstlane(word);
     }
     return !chains_ended(word) ? kNotEnded : ((word & kWaitGivenUp) != 0 ? kSomebodyGaveUp : kEnded);
@@ -3220,21 +3220,22 @@ __device__ __forceinline__ bool wait_for_chains(const TileArgs& g, int b, int fr
     __syncthreads();
     return __builtin_amdgcn_readfirstlane(s_ended) != kNotEnded;
 }
-// The cost of utterance b, by the first wavefront of a workgroup of its own.
+// The cost of utterance b, by a wavefront.
 template <bool kWait>
 __device__ __forceinline__ void utterance_cost(const TileArgs& g, const Utt* __restrict__ meta, const float* __restrict__ emit_blank, int b)
 {
-    if (tile_thread() >= 64) return;
     const Utt m = uniform_record(meta[b]);
     if (!(m.flags & kUttRuns)) return;                   // (written by the setup role)
     const double log2_norms = norms_of_wave(norms_of_lane(m, emit_blank)).log2();
     const int ended = kWait ? chains_awaited(g, b, m.Tb) : kEnded;
     const double* const mass = &g.mass[b * kMassWords];
     const float cost = cost_of_mass(published(&mass[kMassValue]), published(&mass[kMassLog2]), log2_norms);
-    if (tile_thread() == 0) g.costs[b] = ended != kEnded || published(&g.chain_err[b]) != 0 ? __uint_as_float(0x7FC00000u) : cost;
+    if ((tile_thread() & 63) == 0) g.costs[b] = ended != kEnded || published(&g.chain_err[b]) != 0 ? __uint_as_float(0x7FC00000u) : cost;
 }
 
-// Workgroup `group` of utterance b: kRowThreads / 64 wavefronts, ceil(blocks of T / (4 / wavefronts per block)) workgroups;
+// Workgroup `group` of utterance b: kRowThreads / 64 wavefronts, ceil((blocks of T + 1) / (4 / wavefronts per block)) workgroups: the first
+// wavefront behind the utterance's blocks writes its cost.  (With a workgroup of its own for that, 512 x 40 to 130 frames took 43.3 us a
+// call in place of 37.2: places for workgroups are what such launches wait for.)
 // LDS 4 tile_lds_ints(Lmax, kTiles) ints.  kTiles: tiles of 16 symbols.
 // kLean: the lane's number is made anew where the rows are written (tile_thread), so that 128 registers suffice.
 template <int kTiles, bool kWait, bool kLean = false>
@@ -3259,6 +3260,7 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
         if (part == 0) zero_rows();                      // no lattice
         // (the barriers below)
         if (kWait && runs && first_block * kBlockFrames < m.Tb) __syncthreads();
+        if (runs && part == 0 && block == frame_blocks(m.Tb)) utterance_cost<kWait>(g_args, meta, emit_blank, b);
         if (sharing > 1) __syncthreads();
         return;
     }
@@ -3405,6 +3407,12 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
     else write(static_cast<float*>(g_args.grads));
 }
 
+// Which of its utterance's workgroups the within-th one is: one further on from utterance to utterance.  Workgroup i runs on die i mod 8
+// and, as long as places are free, on compute unit i mod 256, and of an utterance's workgroups the last ones often have nothing to do.
+// With 16 workgroups to an utterance they all fell to the same halves of the dies: 122 utterances of up to 454 frames, 34 symbols, 62.0 us
+// a call (before costs had a workgroup 50.9), so 48.5; 32 symbols 50.2 (49.0), 44.4.
+__device__ __forceinline__ int rotated_group(int within, int utterance, int groups) { return (within + utterance) % groups; }
+
 // grid (workgroups per utterance, B)
 template <int kTiles>
 __global__ __launch_bounds__(kRowThreads)
@@ -3413,8 +3421,8 @@ void ctc_gradient_narrow_kernel(const TileArgs args, const Utt* __restrict__ met
                                 const LatticeOut lat)
 {
     extern __shared__ uint4v tile_lds[];
-    if (blockIdx.x == 0) utterance_cost<false>(args, meta, emit_blank, blockIdx.y);
-    else narrow_tile<kTiles, false>(args, meta, labels, emit_blank, emit_label, lat, tile_lds, blockIdx.y, blockIdx.x - 1);
+    const int b = blockIdx.y;
+    narrow_tile<kTiles, false>(args, meta, labels, emit_blank, emit_label, lat, tile_lds, b, rotated_group(blockIdx.x, b, args.groups));
 }
 
 // Larger alphabets: the softmax launch has written y (and zeros); here the columns of the label's symbols and the
@@ -3685,21 +3693,20 @@ void ctc_lattice_gradient_kernel(const Utt* __restrict__ meta, const int* __rest
         do {
             __syncthreads();
             const FusedArgs& a = fused_args();
-            const int tile = left - 1, rank = tile / a.tiles.groups, b = __builtin_amdgcn_readfirstlane(a.tiles.by_end[rank]), group = tile - rank * a.tiles.groups;
-            if (group == 0) utterance_cost<true>(a.tiles, a.meta, a.emit_blank, b);
-            else narrow_tile<kTiles, true, kLean>(a.tiles, a.meta, a.labels, a.emit_blank, a.emit_label, a.lat, fused_lds, b, group - 1);
+            const int tile = left - 1, rank = tile / a.tiles.groups, b = __builtin_amdgcn_readfirstlane(a.tiles.by_end[rank]);
+            narrow_tile<kTiles, true, kLean>(a.tiles, a.meta, a.labels, a.emit_blank, a.emit_label, a.lat, fused_lds, b,
+                                             rotated_group(tile - rank * a.tiles.groups, rank, a.tiles.groups));
             left = __builtin_amdgcn_readfirstlane(published(&a.tiles.left[tile]));
         } while (left != 0);
     } else {
-        const int tile = index - tiles.first_group, rank = tile / tiles.groups, group = tile - rank * tiles.groups;
+        const int tile = index - tiles.first_group, rank = tile / tiles.groups, group = rotated_group(tile - rank * tiles.groups, rank, tiles.groups);
         const int b = __builtin_amdgcn_readfirstlane(tiles.by_end[rank]);
         const int flags = __builtin_amdgcn_readfirstlane(meta[b].flags), frames = __builtin_amdgcn_readfirstlane(meta[b].Tb);
         const int sharing = tiles.share_blocks ? block_waves(__builtin_amdgcn_readfirstlane(meta[b].L)) : 1;
         if (threadIdx.x >= kRowThreads) return;          // (workgroups as large as the longest label's chains)
-        const bool waits = (flags & kUttRuns) && (group - 1) * (kRowThreads / 64 / sharing) * kBlockFrames < frames;
+        const bool waits = (flags & kUttRuns) && group * (kRowThreads / 64 / sharing) <= frame_blocks(frames);     // (narrow_tile: rows, or the cost)
         if (waits && !chains_taken(tiles, b, tile)) return;
-        if (group == 0) utterance_cost<true>(tiles, meta, emit_blank, b);
-        else narrow_tile<kTiles, true, kLean>(tiles, meta, labels, emit_blank, emit_label, lat, fused_lds, b, group - 1);
+        narrow_tile<kTiles, true, kLean>(tiles, meta, labels, emit_blank, emit_label, lat, fused_lds, b, group);
     }
 }
 
@@ -3924,7 +3931,7 @@ static TileArgs tile_args(const Launch& p, size_t* lds)
         g.alpha_at = wide_alpha_at(p.max_label);
         *lds = wide_lds_bytes(p.max_label, g.waves);
     }
-    g.groups = (blocks + per_group - 1) / per_group + (p.A <= kDirectMaxA ? 1 : 0);
+    g.groups = (blocks + (p.A <= kDirectMaxA ? 1 : 0) + per_group - 1) / per_group;
     return g;
 }
 

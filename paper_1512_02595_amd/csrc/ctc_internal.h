@@ -222,6 +222,18 @@ inline int columns_frames(double zero_bytes, int A, int deferred)
     return static_cast<int>(std::min(16.0 - deferred, 16.0 * kFillBesideColumns / zero_bytes + 0.5));
 }
 
+// A number that the GPU divides by, up to 2^31, and what makes its quotients of numbers below 2^31 a product, a sum and a shift: with
+// s = ceil(log2 by) and m = floor(2^32 (2^s - by) / by) + 1, n / by = (floor(n m / 2^32) + n) >> s.
+struct Divisor {
+    unsigned by, magic, shift;
+    explicit Divisor(int divisor) : by(static_cast<unsigned>(divisor)), magic(0), shift(0)
+    {
+        while ((uint64_t(1) << shift) < by) ++shift;
+        magic = static_cast<unsigned>((((uint64_t(1) << shift) - by) << 32) / by + 1);
+    }
+    CTC_HOST_DEVICE unsigned quotient(unsigned n) const { return (static_cast<unsigned>((static_cast<uint64_t>(n) * magic) >> 32) + n) >> shift; }
+};
+
 // That launch has the utterances in its grid's first dimension and `rows`, as many as an utterance of a million and more frames has
 // blocks, in the other two, which take kMaxGridRows each.
 constexpr int kMaxGridRows = 65535;

@@ -535,27 +535,30 @@ __device__ __forceinline__ void raise_flags(Utt* meta, int b, const Utt& m, floa
 // are written a word here and a word there.  So a die gets tiles of neighbouring groups instead: `frames` frames times
 // `columns` groups, every other round of eight tiles the other way round (utterances end one after the other, so that the tiles
 // of a round have ever less to do).  A tile of 0 frames: consecutive groups, one after the other.
+// Everything divides by a number that the launcher knows: with the processor's own divisions, a reciprocal and its corrections each, a row
+// began a microsecond later (214 x 171 x 4186 bf16, cost alone: 62.9 us a call, so 60.4).
 struct RowPlan {
     int groups;               // workgroups, some of them without rows
-    int per_frame;            // groups of rows in a frame
-    int frames, columns;      // a tile's
+    Divisor per_frame;        // groups of rows in a frame
+    int frames;               // a tile's
+    Divisor columns;          // ... groups
+    Divisor round, across;    // workgroups of eight tiles; tiles side by side in a frame
 };
 struct RowPlace { int t, group; };
-__device__ __forceinline__ RowPlace row_place(const RowPlan& plan, int index, bool runs)
+__device__ __forceinline__ RowPlace row_place(const RowPlan& plan, unsigned index, bool runs)
 {
     constexpr int kDies = 8;
-    const int size = plan.frames * plan.columns;
-    if (size == 0) return {index / plan.per_frame, index % plan.per_frame};
-    const int round = index / (kDies * size), in_round = index - round * (kDies * size);
-    const int die = in_round % kDies, within = in_round / kDies, place = round & 1 ? kDies - 1 - die : die;
-    if (runs) {
-        // a run of consecutive groups, across the ends of frames; what is left behind the last whole round lies as it comes
-        if ((round + 1) * (kDies * size) <= plan.groups) index = (round * kDies + place) * size + within;
-        return {index / plan.per_frame, index % plan.per_frame};
-    }
-    const int tile = round * kDies + place, across = (plan.per_frame + plan.columns - 1) / plan.columns;
-    const int band = tile / across, frame = within / plan.columns;
-    return {band * plan.frames + frame, (tile - band * across) * plan.columns + within - frame * plan.columns};
+    auto in_order = [&](unsigned i) {
+        const unsigned t = plan.per_frame.quotient(i);
+        return RowPlace{static_cast<int>(t), static_cast<int>(i - t * plan.per_frame.by)};
+    };
+    if (plan.frames == 0) return in_order(index);
+    const unsigned round = plan.round.quotient(index), in_round = index - round * plan.round.by;
+    const unsigned die = in_round % kDies, within = in_round / kDies, place = round & 1 ? kDies - 1 - die : die;
+    // a run of consecutive groups, across the ends of frames; what is left behind the last whole round lies as it comes
+    if (runs) return in_order((round + 1) * plan.round.by <= static_cast<unsigned>(plan.groups) ? (round * kDies + place) * plan.columns.by + within : index);
+    const unsigned tile = round * kDies + place, band = plan.across.quotient(tile), frame = plan.columns.quotient(within);
+    return {static_cast<int>(band * plan.frames + frame), static_cast<int>((tile - band * plan.across.by) * plan.columns.by + within - frame * plan.columns.by)};
 }
 
 template <typename T, int kLanes, int kPerLane, bool kStreaming>
@@ -574,10 +577,10 @@ void ctc_softmax_rows_kernel(const T* __restrict__ x, T* __restrict__ grads, Utt
         setup_role(meta[b], b, labels, sa, s_lab, index % sa.parts, sa.parts);
         return;
     }
-    const RowPlace place = row_place(plan, static_cast<int>(blockIdx.x), kLanes == kRowThreads);
+    const RowPlace place = row_place(plan, blockIdx.x, kLanes == kRowThreads);
     const int t = place.t, q = tid % kLanes;
     const int b = place.group * kRows + (kRows > 1 ? tid / kLanes : 0);
-    if (t >= Tt || place.group >= plan.per_frame || b >= B) return;
+    if (t >= Tt || place.group >= static_cast<int>(plan.per_frame.by) || b >= B) return;
     const Utt m = meta[b];
     const size_t row_off = (static_cast<size_t>(t) * B + b) * A;
     const T* const row = x + row_off;
@@ -3744,18 +3747,20 @@ constexpr int kRunRows = 64, kRunRounds = 24, kTileGroupsMost = 32, kTileGroups 
 RowPlan row_plan(const Launch& p, int lanes)
 {
     const int rows = kRowThreads / lanes, per_frame = (p.B + rows - 1) / rows;
+    auto plan = [&](int groups, int frames, int columns) {
+        return RowPlan{groups, Divisor(per_frame), frames, Divisor(columns), Divisor(8 * std::max(frames, 1) * columns), Divisor((per_frame + columns - 1) / columns)};
+    };
     // (nothing but emissions is written: consecutive frames of an utterance are better off on one die where that happens to be so;
     // 214 x 171 x 4186 bf16, cost alone: 84.5 us a call without tiles, 93.6 with)
-    if (!p.grads) return {p.T * per_frame, per_frame, 0, kRunRows};
-    if (lanes == kRowThreads) return {p.T * per_frame, per_frame, static_cast<int64_t>(p.T) * per_frame >= 8 * kRunRows * kRunRounds ? 1 : 0, kRunRows};
+    if (!p.grads) return plan(p.T * per_frame, 0, 1);
+    if (lanes == kRowThreads) return plan(p.T * per_frame, static_cast<int64_t>(p.T) * per_frame >= 8 * kRunRows * kRunRounds ? 1 : 0, kRunRows);
     const int across = per_frame <= kTileGroupsMost ? 1 : (per_frame + kTileGroups - 1) / kTileGroups;
     const int columns = (per_frame + across - 1) / across;
     const int64_t tiles = static_cast<int64_t>((per_frame + columns - 1) / columns) * ((p.T + kChunk - 1) / kChunk);
     const int64_t groups = (tiles + 7) / 8 * 8 * kChunk * columns;
     // (fewer tiles than dies, or too many groups of rows for a launch once the ends of tiles are counted in: none)
-    if (tiles < 8 || groups + static_cast<int64_t>(p.B) * (CTC_MAX_LABEL_LENGTH / 64 + 1) > INT32_MAX / kRowThreads)
-        return {p.T * per_frame, per_frame, 0, columns};
-    return {static_cast<int>(groups), per_frame, kChunk, columns};
+    if (tiles < 8 || groups + static_cast<int64_t>(p.B) * (CTC_MAX_LABEL_LENGTH / 64 + 1) > INT32_MAX / kRowThreads) return plan(p.T * per_frame, 0, columns);
+    return plan(static_cast<int>(groups), kChunk, columns);
 }
 // Loads past the caches: fp32 rows of a workgroup each that begin on 16 bytes, in tensors of twice the last-level cache and more.
 // 64 x 500 x 6000 261.6 -> 253.5 us a call, 64 x 500 x 4096 180.8 -> 169, 16 x 1000 x 8000 181 -> 176, 200 x 150 x 5000 206.9 -> 205.5.

@@ -1038,10 +1038,12 @@ void ctc_softmax_narrow_kernel(const T* __restrict__ x, const NarrowImage image,
         const int end = min((group + 1) * share, image.count), length = part == 0 ? m.L : 0;
         int i = group * share + tid, j = tid;
         do {
-            const int word = i < end ? image.words[i] : 0;
+            // (the label strings' own words are not written by the host where there are bytes, and not asked for)
+            const bool copied = i < end && (i < image.labels_first || i >= image.labels_end);
+            const int word = copied ? image.words[i] : 0;
             const int symbol = j < length ? labels8[j] : 0;
             __builtin_amdgcn_sched_barrier(0);
-            if (i < end && (i < image.labels_first || i >= image.labels_end)) workspace_words[i] = word;
+            if (copied) workspace_words[i] = word;
             if (j < length) image.labels_out[m.lab_off + j] = symbol;
             i += kRowThreads;
             j += kRowThreads;

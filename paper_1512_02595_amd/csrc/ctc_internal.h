@@ -213,7 +213,10 @@ inline int deferred_frames(double zero_bytes, int longest, int n_chains, int n_c
 // kFillBesideColumns bytes.  (us a call without, with 1, 2, 3, 4 and 6 sixteenths of the frames: 64 x 500 x 6000, 308 MB of zero rows,
 // 253.4 / 252.4 / 250.2 / 253.0 / 253.2 / 252.9; bf16 145.2 / 145.2 / 144.6 / 143.6 / 143.5 / 146.9; 64 x 500 x 4096
 // 167.9 / 167.6 / 165.1 / 163.2 / 163.6 / 166.8; 200 x 150 x 5000 204.8 / 203.1 / 201.5 / 200.1 / 199.8 / 201.7.)
-constexpr double kFillBesideColumns = 40.0e6, kFillBesideColumnsFrom = 100.0e6;      // (176 x 68 x 2051, 20 MB: 51.8 us without, 56.6 with)
+// Tensors with less than kFillBesideColumnsFrom of them leave none: us a call without / with, 42 MB (176 x 68 x 2051) 44.4 / 50.2, 40 (100 x
+// 100 x 5000 bf16) 44.0 / 47.7, 54 (64 x 160 x 3000) 47.3 / 47.1, 61 (64 x 180 x 3000) 51.1 / 51.6, 69 (64 x 200 x 3000) 56.4 / 53.7, 77 (64 x
+// 250 x 3000) 68.8 / 65.1, 79 (33 x 200 x 7999) 71.4 / 68.7, 80 (100 x 100 x 5000) 68.4 / 66.5.
+constexpr double kFillBesideColumns = 40.0e6, kFillBesideColumnsFrom = 60.0e6;
 // Rows of 2048 symbols and less take a wavefront of its own too long for that (512 x 300 x 100: 102.8 us without, 126.6 with).
 constexpr int kFillBesideColumnsMinA = 2048;
 inline int columns_frames(double zero_bytes, int A, int deferred)

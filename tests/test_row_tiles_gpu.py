@@ -1,16 +1,21 @@
 """GPU tests of the order in which the softmax launch of large alphabets takes its rows: tiles of eight frames that end
 beyond the last frame or the last utterance, fewer tiles than dies, runs of whole rows around the number of rounds from
 which they are used and behind the last whole round, and rows that are loaded past the caches."""
+import os
+import subprocess
+
 import numpy as np
 import pytest
 import torch
 
-from paper_1512_02595_amd import ctc
+from paper_1512_02595_amd import ctc, harness
 
 import parity_checks as pc
 from test_block_edges_gpu import batch_of
 
 pytestmark = pytest.mark.gpu
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 @pytest.mark.parametrize("A,B", [(70, 1), (70, 17), (200, 550), (600, 1), (600, 5), (600, 128), (600, 129), (600, 133), (700, 200)])
@@ -54,11 +59,67 @@ def test_rows_past_the_caches(T, B, A):
     softmax_of_rows(T, B, A, A)
 
 
-# Zero rows left to the launch of the label columns: few and all of those that the lattice launch does not write, frames that
-# end within the sixteen of a round, more utterances than chains leave compute units for
-@pytest.mark.parametrize("dtype", [ctc.DTYPE_F32, ctc.DTYPE_BF16])
-@pytest.mark.parametrize("T,B", [(17, 1), (41, 300), (31, 140), (160, 7)])
-def test_zero_rows_beside_the_label_columns(T, B, dtype):
-    frames = np.random.default_rng(T).integers(0, max(2, T // 4), B)
+# Zero rows left to the launch of the label columns, some of them after those that the lattice launch writes: rows off 16 bytes, frames
+# that end within the sixteen of a round before, among and behind the ones left over, few utterances and so many that the lattice launch
+# leaves none; what is left to whom is asked of the rules themselves (ctc_internal.h).
+RULES = r"""
+#include <cstdio>
+#include "ctc_internal.h"
+int main()
+{
+    double zero_bytes;
+    int longest, chains, A;
+    while (std::scanf("%lf %d %d %d", &zero_bytes, &longest, &chains, &A) == 4) {
+        const int defer = ctc::deferred_frames(zero_bytes, longest, chains, 256);
+        std::printf("%d %d\n", defer, ctc::columns_frames(zero_bytes, A, defer));
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    (d / "rules.cpp").write_text(RULES)
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_1512_02595_amd", "csrc"),
+                    str(d / "rules.cpp"), "-o", str(d / "rules")], check=True)
+
+    def ask(*args):
+        out = subprocess.run([str(d / "rules")], input=" ".join(map(str, args)), capture_output=True, text=True, check=True).stdout
+        return tuple(map(int, out.split()))
+    return ask
+
+
+def padded_batch(T, B, A):
+    frames = np.random.default_rng(T).integers(1, max(2, T // 4), B)
     frames[0] = T
-    pc.check(batch_of(frames, [min(3, f // 3) for f in frames], 2050, T=T, seed=T), dtype)
+    return batch_of(frames, [min(3, f // 3) for f in frames], A, T=T, seed=T)
+
+
+@pytest.mark.parametrize("T,B,A,dtype", [
+    (113, 90, 2051, ctc.DTYPE_F32), (127, 90, 2053, ctc.DTYPE_F32), (121, 80, 2052, ctc.DTYPE_F32), (401, 20, 4097, ctc.DTYPE_F32),
+    (118, 170, 2050, ctc.DTYPE_F32), (113, 170, 2051, ctc.DTYPE_BF16), (127, 90, 4099, ctc.DTYPE_BF16), (124, 90, 4098, ctc.DTYPE_BF16),
+    (399, 40, 5001, ctc.DTYPE_BF16)])
+def test_zero_rows_beside_the_label_columns(T, B, A, dtype, rules):
+    batch = padded_batch(T, B, A)
+    zero_bytes = (T * B - int(batch.input_lengths.sum())) * A * (4 if dtype == ctc.DTYPE_F32 else 2)
+    defer, columns = rules(zero_bytes, T, 2 * B, A)
+    assert columns > 0 and (defer > 0 or B > 96)
+    pc.check(batch, dtype)
+
+
+@pytest.mark.parametrize("T,B,A", [(303, 40, 4099), (305, 40, 4099)])
+def test_zero_rows_beside_the_label_columns_with_metadata_on_the_gpu(T, B, A, rules):
+    batch = padded_batch(T, B, A)
+    defer, columns = rules(T * B * A * 4 / 3, T // 2, 2 * B, A)
+    assert columns > 0 and defer > 0
+    dm = harness.DeviceMetaBatch(T, B, A, 3, batch.blank)
+    dm.load(batch)
+    dm.poison()
+    dm.run()
+    status, costs, grads = dm.results()
+    want_costs, want = pc.orc.ctc_loss_and_grad(batch.logits, batch.flat_labels, batch.label_lengths, batch.input_lengths, batch.blank)
+    assert status == ctc.STATUS_SUCCESS and np.abs(grads - want).max() <= pc.GRAD_ATOL
+    assert (np.abs(costs - want_costs) <= pc.COST_RTOL * np.maximum(np.abs(want_costs), 1e-2)).all()
+    for b in range(B):
+        assert not grads[batch.input_lengths[b]:, b].any()

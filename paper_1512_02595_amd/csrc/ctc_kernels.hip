@@ -649,13 +649,13 @@ void ctc_softmax_rows_kernel(const T* __restrict__ x, T* __restrict__ grads, Utt
     // the emissions, out of the row that the caches still hold; wavefronts without a label position make room for other rows (214 x
     // 171 x 4186 bf16, cost alone: 90.1 us a call with all of them waiting for the blank's logit, 86.1 so)
     if (q > 0 && q >= m.L && t != m.Tb - 1) return;
-    const FrameNorm norm(load_elem(row, blank), mx, sum, ls);
+    const float blank_logit = load_elem(row, blank), first_logit = load_elem(row, c_first);        // (both asked for before either is used)
+    const FrameNorm norm(blank_logit, mx, sum, ls);
     float lowest = norm.log_blank;
     if (q == 0) store_blank(emit_blank, sa.emit_blank64, static_cast<size_t>(m.f_off) + t, sa.plain_logs ? norm.log_blank : norm.word(), sa.plain_logs);
     float* const erow = emit_label + emission_at(m.e_off, m.L, t, 0);
     for (int j = q; j < m.L; j += kLanes) {
-        const int c = j == q ? c_first : lab[j];
-        const float logit = load_elem(row, c), lp = log2_softmax(logit, mx, ls);
+        const float logit = j == q ? first_logit : load_elem(row, lab[j]), lp = log2_softmax(logit, mx, ls);
         erow[static_cast<size_t>(j) * kChunk] = sa.plain_logs ? lp : encode_emission(lp, exp2_from_max(logit, mx), norm);
         lowest = fminf(lowest, lp);
     }

@@ -58,10 +58,11 @@ struct WavePlan {
     bool barrier;      // too long for a halo: 64 pairs per wavefront, one barrier per step
 };
 
-// Wavefronts and halo width for a label of this length.  Measured on gfx950: with one
+// Wavefronts and halo width for a label of this length.  Fitted to log-domain chains on gfx950: with one
 // wavefront per SIMD (up to 4) a step costs about 210 clocks and a hand-over about 500; with
 // several per SIMD the vector ALU is the limit (about 170 clocks per wavefront-step) and part
-// of a hand-over's latency hides behind the other wavefronts (about 350).
+// of a hand-over's latency hides behind the other wavefronts (about 350).  (The linear domain's steps, which share the plans, take 38 to 51
+// clocks, 18 to 24 ns: its plans have not been fitted to that.)
 // (Host and device: the launcher plans on the host, the device-metadata entry point on the GPU.)
 // `crowded`: the launch has more wavefronts than the chip runs side by side at one per SIMD, so
 // what counts is the total work (wavefront-steps plus hand-overs), not one chain's latency.
@@ -96,7 +97,7 @@ CTC_HOST_DEVICE inline WavePlan plan_waves(int label_length, bool crowded = fals
 // 64 pairs).  A wavefront then covers 128 pairs, an error at lane 0 needs two steps per lane to
 // move up, so a halo of h lanes lasts 2h steps: h is a multiple of 4 (hand-overs on chunk
 // boundaries), at most 16 (the exchange buffer).  Sixteen wavefronts hold any supported label.
-// Measured on gfx950: about 150 clocks per step with one wavefront per SIMD, 600 per hand-over.
+// Fitted when a step took about 150 clocks with one wavefront per SIMD and a hand-over 600 (they take about 75, 35 ns, now).
 CTC_HOST_DEVICE inline WavePlan plan_waves2(int label_length, bool crowded = false)
 {
     const int lanes = (label_length + 2) / 2;          // ceil((L + 1) / 2)
@@ -124,8 +125,8 @@ CTC_HOST_DEVICE inline WavePlan plan_waves2(int label_length, bool crowded = fal
     return best;
 }
 
-// Which of the two plans a linear-domain chain uses.  Measured on gfx950: a step of a two-pair
-// lane takes about 180 clocks against 120 for a one-pair lane, and a hand-over 560, so while a
+// Which of the two plans a linear-domain chain uses.  A step of a two-pair lane takes half as long again as one of a one-pair lane (180
+// clocks against 120 when this was fitted, 12 instructions against 7 now), so while a
 // label's one-pair plan keeps to one wavefront per SIMD (at most 4) it is the faster one; beyond
 // that, and in crowded launches, where wavefront-steps count and not one chain's latency, the
 // two-pair plan with half the wavefronts wins.  Where the emission block holds the symbols' rows
@@ -192,7 +193,7 @@ const Plans& plans();
 constexpr int kEmitGathered = 0, kEmitSymbols = 1;
 CTC_HOST_DEVICE inline int emission_layout(int A) { return A <= kDirectMaxA ? kEmitSymbols : kEmitGathered; }
 
-// Frames between two states that a chain stores for the gradient (checkpoints): see gradient_tile.
+// Frames between two states that a chain stores for the gradient (checkpoints): see block_shares.
 constexpr int kBlockFrames = 2 * kChunkSteps;
 CTC_HOST_DEVICE inline int frame_blocks(int frames) { return (frames + kBlockFrames - 1) / kBlockFrames; }
 CTC_HOST_DEVICE inline int64_t padded_frames(int frames) { return static_cast<int64_t>(frame_blocks(frames)) * kBlockFrames; }
@@ -201,7 +202,7 @@ CTC_HOST_DEVICE inline int64_t padded_frames(int frames) { return static_cast<in
 // alignment) to the lattice launch, whose compute units without a chain would idle: as many as fit in the time of
 // its longest chain.  `zero_bytes`: of all zero rows.
 constexpr double kFillBytesPerUs = 3.0e6;      // what the idle half of the chip writes beside the chains
-constexpr double kChainUsPerFrame = 0.045;     // the quickest chains (one wavefront)
+constexpr double kChainUsPerFrame = 0.045;     // the quickest chains when this was fitted (one wavefront; 0.018 now)
 inline int deferred_frames(double zero_bytes, int longest, int n_chains, int n_cu)
 {
     if (n_chains + n_cu / 4 > n_cu || zero_bytes <= 0) return 0;
@@ -282,7 +283,10 @@ inline bool gradient_beside_chains(double early, double late, double chain_us, i
     return max_waves > 8 ? 1.5 * late + 18.0 * busy <= saved + 0.4 * early * (1.0 - busy)
                          : late + 3.0 * busy <= saved + 0.7 * early * (1.0 - 0.4 * busy);
 }
-// About what a chain of this many wavefronts takes for a frame, in microseconds (up to four run on a SIMD each).
+// What a chain of this many wavefronts took for a frame, in microseconds, when the rule above was fitted (up to four run on a SIMD each).
+// The steps of a linear-domain chain take about half of that now, 0.018, 0.024 to 0.035 and 0.043; the rule, which divides these numbers
+// by its own constants, has not been fitted again.  (Measured since: 122 x 454 frames, 29 symbols, apart 42.1 us a call, beside 44.0; 128
+// x 454 x 34 46.8 and 50.3; 100 x 454 x 34 44.2 and 43.1; 64 x 454 x 29 35.3 and 34.6: beside in all four.)
 inline double chain_us_per_frame(int waves) { return waves == 1 ? 0.045 : (waves <= 4 ? 0.06 : 0.088); }
 
 constexpr int kDoneStride = 16;      // words between two utterances' words: a line each for those who poll
@@ -430,8 +434,8 @@ CTC_HOST_DEVICE inline int64_t label_emission_step(const Utt& m, bool has_label,
 {
     return has_label ? (backward ? -1 : 1) * static_cast<int64_t>(m.e_cols) * kChunk : 0;
 }
-// The blank's emissions of a chunk: one value per frame, in frame order, for all lanes.  (Twice: as floats, coded
-// like the labels', and as fp64 probabilities, which the linear-domain chains take as scalars, a chunk in one load.)
+// What a chunk's frames have in common, one value per frame, in frame order: the frames' words as floats (FrameNorm), or, in launches for
+// the most probable alignment, the blank's logarithms as doubles, which its chains take as scalars, a chunk in one load.
 CTC_HOST_DEVICE inline int64_t blank_emission_offset(const Utt& m, int chunk)
 {
     return kBlankSlack + m.f_off + static_cast<int64_t>(chunk) * kChunk;

@@ -7,9 +7,9 @@
 //             alphabets of at most 64 symbols and few utterances: done by the softmax launch itself
 //   setup     per utterance: label positions grouped by symbol (the appendix's one-off
 //             key-value sort, done by counting), degenerate costs; rides in the softmax launch
-//   softmax   per frame row: log2-sum-exp2 of the scaled logits, and the emissions (softmax
-//             outputs) of blank and of every label position, gathered once so that the
-//             recursions read them coalesced (small alphabets: the normalised rows themselves),
+//   softmax   per frame row: log2-sum-exp2 of the scaled logits, the blank's probability and the
+//             emissions (softmax outputs divided by it) of every label position, gathered once so that
+//             the recursions read them coalesced (small alphabets: of every symbol),
 //             in chunks of eight frames a column; larger alphabets: also the gradient but for the
 //             label columns
 //   lattice   alpha and beta recursions, both in one launch, a workgroup per utterance and direction
@@ -341,7 +341,7 @@ struct SetupArgs {
                           // share (finish_loss, announce_end, take_chain)
     float* log0;          // kEmissionConstants floats that lattice lanes without a label state read as their
                           // emission: probability 0 (linear-domain chains) and log 0 (log-domain chains)
-    double* emit_blank64; // the blank's probability per frame as fp64 (Layout::emit_blank64)
+    double* emit_blank64; // alignments: log2 of the blank's probability per frame (Layout::emit_blank64)
     int* host_flag;       // pinned host word: receives flag_value once the upload has been consumed
     int flag_value;
     bool plain_logs;      // emissions are stored as log2 probabilities throughout (most probable alignment)
@@ -1605,7 +1605,7 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
     // (every lane starts from the exact state of its pair, halo lanes included)
     float el[4][kChunk], eb[2];                          // eb: the frames' words
     double blank_logs[2][kChunk] = {};                   // (Mode::kBest: as scalars, see run_chain_linear)
-    const double* next_blanks = emit_blank64 + blank_emission_offset(m, chain_chunk(0, chunks, kBackward));
+    const double* next_blanks = kMode == Mode::kBest ? emit_blank64 + blank_emission_offset(m, chain_chunk(0, chunks, kBackward)) : nullptr;
     auto fetch = [&](auto set, int i) {
         constexpr int k = decltype(set)::value;
         if (i >= kBlankAhead && kMode == Mode::kBest) {
@@ -3657,7 +3657,6 @@ struct FusedArgs {
     const int* order;
     const int* labels;
     const float* emit_blank;
-    const double* emit_blank64;
     const float* emit_label;
     LatticeOut lat;
     double* mass;
@@ -3682,8 +3681,7 @@ __device__ __forceinline__ const FusedArgs& fused_args()
 template <Sync kSync, int kTiles, bool kLean>
 __global__ __launch_bounds__(64 * kFusedWaves, kLean ? 4 : 1)
 void ctc_lattice_gradient_kernel(const Utt* __restrict__ meta, const int* __restrict__ order,
-                                 const int* __restrict__ labels, const float* __restrict__ emit_blank,
-                                 const double* __restrict__ emit_blank64, const float* __restrict__ emit_label,
+                                 const int* __restrict__ labels, const float* __restrict__ emit_blank, const float* __restrict__ emit_label,
                                  const LatticeOut lat, double* __restrict__ mass, float* __restrict__ costs,
                                  int* __restrict__ chain_err, uint32_t* __restrict__ sink, const LaunchWords wk, const TileArgs tiles)
 {
@@ -3691,7 +3689,7 @@ void ctc_lattice_gradient_kernel(const Utt* __restrict__ meta, const int* __rest
     const int index = static_cast<int>(blockIdx.x);
     if (index < tiles.first_group) {
         __builtin_amdgcn_s_setprio(3);
-        int left = lattice_body<kSync, Mode::kGrad, true>(order[index], meta, labels, emit_blank, emit_blank64, emit_label, lat, mass,
+        int left = lattice_body<kSync, Mode::kGrad, true>(order[index], meta, labels, emit_blank, nullptr, emit_label, lat, mass,
                                                           costs, chain_err, sink, fused_lds, wk);
         if (__builtin_expect(left == 0, 1) || threadIdx.x >= kRowThreads) return;
         __builtin_amdgcn_s_setprio(0);
@@ -3987,8 +3985,7 @@ int launch_lattice(const Launch& p, void* stream)
         const dim3 grid(n_groups + tiles.groups * p.B), block(64 * waves);
 #define CTC_LAUNCH_FUSED(SYNC, TILES, LEAN)                                                        \
     hipLaunchKernelGGL((ctc_lattice_gradient_kernel<SYNC, TILES, LEAN>), grid, block, lds, s, meta, order, labels, emit_blank,   \
-                       reinterpret_cast<const double*>(p.ws + p.lay.emit_blank64), emit_label,                \
-                       lat, mass, p.costs, chain_err, sink, wk, tiles)
+                       emit_label, lat, mass, p.costs, chain_err, sink, wk, tiles)
 #define CTC_LAUNCH_FUSED_TILES(SYNC)                                                               \
     do {                                                                                           \
         if (p.A <= 32) CTC_LAUNCH_FUSED(SYNC, 2, false);                                           \

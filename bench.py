@@ -31,13 +31,13 @@ ALU_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12
 # Algorithmic lane-operations of one step of one (blank, label) state pair in one direction, priced
 # for the log-space recursion that defines the path: two two-term log-sum-exps = 4 transcendentals
 # (two exp2, two log2) at quarter rate (= 16) + 25 plain operations.  The kernel itself recurs on
-# probabilities with a per-lane exponent and issues about a third of that (see LANE_OPS_EXECUTED),
+# probabilities with a per-lane exponent and issues about a fifth of that (see LANE_OPS_EXECUTED),
 # so `achieved` is the rate at which the defined work gets done, not the ALU's busy rate.
 LANE_OPS_PER_PAIR_STEP = 41
-# What the linear-domain kernel executes per pair-step: 2 fused multiply-adds, 1 addition,
-# 2 multiplications, 1 conversion of the label's emission, 2 DPP moves, and about 3 for the
-# renewal of the exponents every 8 steps and the states stored every 16.
-LANE_OPS_EXECUTED = 11
+# What the linear-domain kernel executes per pair-step: 2 fused multiply-adds, 1 addition, 1 multiplication,
+# 1 conversion of the label's emission, 2 DPP moves, and about 1 for the looks at the exponents and the states
+# stored every 16 steps.
+LANE_OPS_EXECUTED = 8
 # The max recursion of the alignment has no transcendentals: compares, selects, two fp64 adds.
 LANE_OPS_PER_PAIR_STEP_ALIGN = 22
 
@@ -99,14 +99,21 @@ def deferred_share(zero_bytes, longest, chains, n_cu=256):
     return min(16, int(16 * fits / zero_bytes)) / 16
 
 
+def columns_share(zero_bytes, A, deferred):
+    """Share of them that the label columns' launch writes: columns_frames in csrc/ctc_internal.h."""
+    if zero_bytes < 60e6 or A <= 2048:
+        return 0.0
+    return int(min(16 - 16 * deferred, 16 * 40e6 / zero_bytes + 0.5)) / 16
+
+
 def kernel_bytes(batch, elem, mode="grad"):
     """Algorithmic HBM bytes of each kernel for one launch on `batch`: what the kernel must read and write once, as the
     comments below state.  (Where the lattice launch writes the gradient too, it has the bytes of both: main.)"""
     frames, A = batch.frames, batch.A
     T, L = batch.input_lengths.astype(np.int64), batch.label_lengths.astype(np.int64)
     pairs = int((T * (L + 1)).sum())
-    # emissions: a float per frame and symbol, or label position; the blank's again as a float and a double
-    emissions = (frames * A if A <= NARROW else int((T * L).sum())) * 4 + frames * 12
+    # emissions: a float per frame and symbol, or label position; per frame its norm, or (align) the blank's logarithm as a double
+    emissions = (frames * A if A <= NARROW else int((T * L).sum())) * 4 + frames * (8 if mode == "align" else 4)
     # states at the ends of blocks of frames: two doubles and an exponent per label position and direction
     states = int(((T + BLOCK - 1) // BLOCK * L).sum()) * 20 * 2
     full = batch.T * batch.B * A * elem
@@ -122,12 +129,13 @@ def kernel_bytes(batch, elem, mode="grad"):
         out["ctc_gradient"] = states + emissions + full
     else:
         # the softmax launch also writes the dense gradient: y, or zeros for padding, a share of which the lattice launch
-        # takes over; the gradient launch rewrites the label's columns and the blank
+        # and the gradient launch take over; the latter rewrites the label's columns and the blank
         zeros = full - frames * A * elem
-        beside = zeros * deferred_share(zeros, int(T.max()), 2 * batch.B)
-        out["ctc_softmax"] += full - beside
+        share = deferred_share(zeros, int(T.max()), 2 * batch.B)
+        beside, columns = zeros * share, zeros * columns_share(zeros, A, share)
+        out["ctc_softmax"] += full - beside - columns
         out["ctc_lattice"] += states + beside
-        out["ctc_gradient"] = states + emissions + int((T * (L + 1)).sum()) * elem
+        out["ctc_gradient"] = states + emissions + int((T * (L + 1)).sum()) * elem + columns
     return out, pairs
 
 

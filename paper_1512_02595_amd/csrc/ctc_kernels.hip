@@ -1698,9 +1698,14 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
 //   - what arrives from the window is at most 2^kFrameDrop, and grows by 3 * 2^m a step at most: 2^(370 + 8 * 80.6) = 2^1015,
 //   - a value of at least 2^-kFrameSlack shrinks by 2^-m a step at worst: 2^-(390 + 632) = 2^-1022,
 // both inside fp64.  Utterances with smaller probabilities, down to 2^-100 (-kLinearMinLog2), are *steep*: n = kSteepSteps, 2^776 and
-// 2^-790.  Their chains are a variant of their own, since a branch in the middle of a chunk would be two instructions more for the others
-// (64 x 750 frames, 29 symbols, probabilities down to 2^-90: 55 us a call; in the log domain 123, shares to 2^-19).  Two neighbouring frames differ by at most kFrameSlack + kFrameDrop, which the factor between them (scale,
-// constant between renewals and folded into the multiply-adds) can hold.
+// 2^-790.  Their chains are a variant of their own, since a branch in the middle of a chunk would be two instructions more for the
+// others (64 x 750 frames, 29 symbols, probabilities down to 2^-90: 55 us a call; in the log domain 123, and shares to 2^-19 only).
+// Two neighbouring frames differ by at most kFrameSlack + kFrameDrop, which the factor between them (scale, constant between renewals
+// and folded into the multiply-adds) can hold.
+//
+// The states of a lane share its frame.  A label state's own blank that lies 2^1022 below it is lost; it takes a label that is more
+// probable than its blank for so long (no favoured blank and hundreds of thousands of frames), and it matters where the label must be
+// left again and the only way there is from that blank.
 //
 // A pair further than 2^(kFrameSlack + kFrameDrop) below its window's top is rounded away.  Its neighbours have 2^760 times its
 // mass and can still reach the end of the label (utterances with fewer than kTightFrames frames to spare, where they could
@@ -1727,15 +1732,14 @@ __device__ __forceinline__ int lane_frame(int window_top, int own_top)
 // utterance are above 2^kGentleMinLog2 (g = 32): 2^-862 and 2^1021; kSteepSteps, g = 100, kSteepSmoothFrames: 2^-750 and 2^1005.
 constexpr int kEasyLow = -350, kEasyHigh = 99;
 constexpr int kSmoothFrames = 24, kSteepSmoothFrames = 125;
-constexpr bool frames_last(int steps, float min_log2, int smooth, bool after_renewal)
+constexpr bool frames_last(int steps, float min_log2, int smooth)
 {
     const float small = steps * min_log2, large = steps * (1.6f - min_log2);
-    return (!after_renewal || (small - kFrameSlack >= -1022 && kFrameDrop + large < 1023)) && kEasyLow + small >= -1022 &&
-           kEasyHigh + large + steps * smooth < 1023;
+    return small - kFrameSlack >= -1022 && kFrameDrop + large < 1023 && kEasyLow + small >= -1022 && kEasyHigh + large + steps * smooth < 1023;
 }
-static_assert(frames_last(kChunk, kRoughMinLog2, kSmoothFrames, true), "a chunk");
-static_assert(frames_last(kSteepSteps, kLinearMinLog2, kSteepSmoothFrames, true), "a steep one's steps");
-static_assert(frames_last(kBlockFrames, kGentleMinLog2, kSmoothFrames, false), "a block");
+static_assert(frames_last(kBlockFrames, kGentleMinLog2, kSmoothFrames), "a block");
+static_assert(frames_last(kChunk, kRoughMinLog2, kSmoothFrames), "a chunk");
+static_assert(frames_last(kSteepSteps, kLinearMinLog2, kSteepSmoothFrames), "a steep one's steps");
 // The test, on the high dword of the largest value of a lane (biased exponent in bits 20..30): one
 // subtraction and one unsigned compare; zero, denormals, infinities and NaN fail it.
 __device__ __forceinline__ bool outside_easy_range(double top)

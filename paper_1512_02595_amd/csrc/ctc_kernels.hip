@@ -1072,7 +1072,11 @@ void ctc_softmax_narrow_kernel(const T* __restrict__ x, const NarrowImage image,
     const float lowest = narrow_rows(x, lp, m.Tb, b, t0, B, A, blank, sa.plain_logs);
     __syncthreads();
     store_symbol_chunks<kRows>(lp, m.Tb, m.f_off, m.e_off, t0, A, blank, emit_blank, sa.emit_blank64, emit_label, sa.plain_logs);
-    if (lowest < kGentleMinLog2) atomicOr(&s_flags, kRowsRough | (lowest < kRoughMinLog2 ? kRowsSteep : 0) | (lowest < kLinearMinLog2 ? kRowsSmall : 0));
+    if (__ballot(lowest < kGentleMinLog2) != 0) {
+        // (once a wavefront: one lane after the other on one word takes longer than the rows where many have something to say)
+        const int met = kRowsRough | (__ballot(lowest < kRoughMinLog2) != 0 ? kRowsSteep : 0) | (__ballot(lowest < kLinearMinLog2) != 0 ? kRowsSmall : 0);
+        if ((tid & 63) == 0) atomicOr(&s_flags, met);
+    }
     __syncthreads();
     if (tid == 0) row_flags[static_cast<size_t>(b) * row_blocks + blockIdx.x] = s_flags;
 }

@@ -1105,8 +1105,9 @@ __device__ __forceinline__ int rows_flagged(const int* __restrict__ row_flags, i
 // the gradient by the bytes it read; a checkpoint is 20 bytes per state and block, 1.25 per frame.
 //   alpha, after frame 16 k + 15:  per label position j  (blank j, label j) as doubles, and their frame (int32)
 //   beta, after frame 16 k:        per label position j  (blank j + 1, label j)
-// (inclusive quantities, see the recursions), position j in column 1 + j of row k.  Values in the first half of the
-// direction's region, frames in the second.
+// (inclusive quantities, see the recursions), position j in column 1 + j.  Rows lie in the order in which the chain stores them, the
+// last one, which nobody asks for, left out; a row's 16-byte states come first, then its frames (CheckpointRow).  All of it in the
+// first half of the direction's region.
 //
 // Log-domain chains (rare) store every frame, per label state a number m * 2^e, as
 //   a value word (uint32): the high dword of the fp64 m (sign, exponent, top 20 mantissa bits),
@@ -1117,6 +1118,19 @@ __device__ __forceinline__ int rows_flagged(const int* __restrict__ row_flags, i
 //
 // The mass p of an utterance (its reciprocal) keeps both parts in one 8-byte word (pack_state).
 struct alignas(16) CheckpointState { double blank, label; };
+struct CheckpointRow {
+    int64_t pitch;                                       // columns
+    __device__ __forceinline__ int64_t bytes() const { return (pitch * static_cast<int64_t>(sizeof(CheckpointState) + sizeof(int)) + 15) / 16 * 16; }
+    __device__ __forceinline__ int64_t frames_at() const { return pitch * static_cast<int64_t>(sizeof(CheckpointState)); }
+    __device__ __forceinline__ const CheckpointState* states(const uint32_t* block, int64_t row) const
+    {
+        return reinterpret_cast<const CheckpointState*>(reinterpret_cast<const char*>(block) + row * bytes());
+    }
+    __device__ __forceinline__ const int* frames(const uint32_t* block, int64_t row) const
+    {
+        return reinterpret_cast<const int*>(reinterpret_cast<const char*>(block) + row * bytes() + frames_at());
+    }
+};
 constexpr int kNoExponent = -(1 << 28);   // exponent of zero: below every real one, far from int32's ends
 
 __device__ __forceinline__ double pack_state(double in_frame, int frame)
@@ -1160,6 +1174,43 @@ __device__ __forceinline__ double published(const double* p)
     return __longlong_as_double(__hip_atomic_load(reinterpret_cast<const long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 __device__ __forceinline__ CheckpointState published(const CheckpointState* p) { return {published(&p->blank), published(&p->label)}; }
+
+// Where a linear-domain chain's lane stores its states and frames, row after row.  Through a buffer resource, for three reasons.
+// Stores with kPast go past the die's cache as publish() does, but sixteen bytes at a time, and the compiler goes on counting them among
+// the memory operations in flight.  With plain stores a chain had to have its die's cache written back at its end, during which every
+// chain on the die waited a microsecond for its emissions: 64 x 750 frames, 29 symbols, blocks of 16 frames that take 0.44 us took up to
+// 1.5 us once the short utterances ended.  A lane that has nothing to store gets an offset beyond the buffer's end, where the
+// hardware drops stores.  And so is the row after the last one dropped, for which the chain's end would have to wait.
+constexpr int kPast = 16;                                // (cache policy: sc1)
+struct CheckpointRows {
+    static constexpr unsigned kNowhere = 0x80000000u;    // (a block has fewer bytes: make_layout)
+    __amdgpu_buffer_rsrc_t block;
+    unsigned state_at, frame_at;                         // in the row, of this lane
+    int at, step;                                        // of the row
+    __device__ __forceinline__ CheckpointRows(uint32_t* out, CheckpointRow row, int rows, bool stores, int column)
+        : block(__builtin_amdgcn_make_buffer_rsrc(out, 0, static_cast<int>(rows * row.bytes()), 0x00020000)),
+          state_at(stores ? static_cast<unsigned>(column * sizeof(CheckpointState)) : kNowhere),
+          frame_at(stores ? static_cast<unsigned>(row.frames_at() + column * sizeof(int)) : kNowhere),
+          at(0), step(static_cast<int>(row.bytes()))
+    {
+    }
+    typedef unsigned Words4 __attribute__((ext_vector_type(4)));
+    typedef unsigned Words2 __attribute__((ext_vector_type(2)));
+    template <int kPolicy>
+    __device__ __forceinline__ void state(int column, const CheckpointState& s) const
+    {
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(Words4, s), block, static_cast<int>(state_at) + column * static_cast<int>(sizeof(CheckpointState)), at, kPolicy);
+    }
+    template <int kPolicy>
+    __device__ __forceinline__ void frame(int f) const { __builtin_amdgcn_raw_buffer_store_b32(static_cast<unsigned>(f), block, static_cast<int>(frame_at), at, kPolicy); }
+    // (the same in two neighbouring columns)
+    template <int kPolicy>
+    __device__ __forceinline__ void frames(int f) const
+    {
+        __builtin_amdgcn_raw_buffer_store_b64(Words2{static_cast<unsigned>(f), static_cast<unsigned>(f)}, block, static_cast<int>(frame_at), at, kPolicy);
+    }
+    __device__ __forceinline__ void next() { at += step; }
+};
 
 // log2(2^a + 2^b) for fp64 a, b with the exponentials taken on the fp32 difference.
 __device__ __forceinline__ double lse2(double a, double b)
@@ -1363,7 +1414,7 @@ __device__ __forceinline__ Wave* halo_wave(void* lds, int wave)
 //
 // A lone wavefront on its SIMD issues an instruction about every five clocks whatever its kind
 // (a vector memory instruction counts for three), so the step is written for instruction count:
-// pointers advance by adds, lanes without a pair write to a sink, whole chunks run without a look
+// pointers advance by adds, lanes without a pair write to a sink or nowhere, whole chunks run without a look
 // at the step number.
 //
 // Labels of more than 63 symbols span several wavefronts.  Exchanging a value at every step
@@ -1803,12 +1854,11 @@ struct ChainFrames {
     }
 };
 
-template <bool kBackward, Sync kSync, Mode kMode, bool kSteep>
+// kPolicy: of the checkpoints' stores, kPast where another workgroup of the launch reads them.
+template <bool kBackward, Sync kSync, Mode kMode, bool kSteep, int kPolicy>
 __device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const bool gentle, const int* __restrict__ labels,
-                                                 const float* __restrict__ emit_label,
-                                                 uint32_t* __restrict__ out, int* __restrict__ out_exponents,
-                                                 double* __restrict__ mass, int* __restrict__ chain_err,
-                                                 uint32_t* __restrict__ sink, void* lds)
+                                                 const float* __restrict__ emit_label, uint32_t* __restrict__ out,
+                                                 double* __restrict__ mass, int* __restrict__ chain_err, void* lds)
 {
     static_assert(kSync != Sync::kBarrier, "the barrier kernel runs the log-domain chain");
     static_assert(kMode != Mode::kBest, "the maximum recursion runs in the log domain");
@@ -1827,13 +1877,9 @@ __device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const
     const float* ep = emit_label + label_emission_offset(m, has_label, has_label ? lab[li] : 0, li,
                                                          chain_chunk(0, chunks, kBackward), kZeroEmission);
     const int64_t estep = label_emission_step(m, has_label, kBackward);
-    // Checkpoints: row k after block k of the utterance.
-    const bool stores = kMode == Mode::kGrad && active && has_label;
-    const int64_t pitch = lattice_pitch(L), first_row = kBackward ? frame_blocks(m.Tb) - 1 : 0;
-    CheckpointState* vp = stores ? reinterpret_cast<CheckpointState*>(out + m.ab_off) + first_row * pitch + li + 1
-                                 : reinterpret_cast<CheckpointState*>(sink);
-    int* fp = stores ? out_exponents + m.ab_off + first_row * pitch + li + 1 : reinterpret_cast<int*>(sink);
-    const int64_t row_step = stores ? (kBackward ? -pitch : pitch) : 0;
+    // Checkpoints.  (Cost only: one row, by pair, in the chain's own order.)
+    CheckpointRows rows(out + m.ab_off, CheckpointRow{lattice_pitch(L)}, kMode == Mode::kGrad ? frame_blocks(m.Tb) - 1 : 1,
+                        kMode == Mode::kGrad ? active && has_label : active, kMode == Mode::kGrad ? li + 1 : j);
 
     const int last_wave = m.waves - 1;
     HaloWave* const mine_lds = halo_wave<HaloWave>(lds, wave);
@@ -1938,10 +1984,9 @@ __device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const
         if (__builtin_expect(f.renewal_due(top_value()), 0)) renew_frames();
     };
     auto checkpoint = [&]() __attribute__((always_inline)) {
-        *vp = CheckpointState{v_blank, v_label};
-        *fp = f.frame;
-        vp += row_step;
-        fp += row_step;
+        rows.template state<kPolicy>(0, CheckpointState{v_blank, v_label});
+        rows.template frame<kPolicy>(f.frame);
+        rows.next();
     };
     // One step.  The blank state sums its own value and the label of the pair before; the label state
     // its own value, the old blank and, where the skip is allowed, that label too:
@@ -1990,10 +2035,8 @@ __device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const
 
     if (kMode == Mode::kLoss) {
         // the state of every pair, for finish_loss
-        if (active) {
-            reinterpret_cast<CheckpointState*>(out + m.ab_off)[j] = CheckpointState{v_blank, v_label};
-            out_exponents[m.ab_off + j] = f.frame;
-        }
+        rows.template state<kPolicy>(0, CheckpointState{v_blank, v_label});
+        rows.template frame<kPolicy>(f.frame);
         return lost;
     }
     if (!kBackward) {
@@ -2017,12 +2060,10 @@ __device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const
 // The two pairs of a lane are neighbours in the checkpoint's row; where pair B has no label state (the lane of the last
 // pair) its part falls on one of the row's two unused columns.
 
-template <bool kBackward, Mode kMode, bool kSteep>
+template <bool kBackward, Mode kMode, bool kSteep, int kPolicy>
 __device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, const bool gentle, const int* __restrict__ labels,
-                                                  const float* __restrict__ emit_label,
-                                                  uint32_t* __restrict__ out, int* __restrict__ out_exponents,
-                                                  double* __restrict__ mass, int* __restrict__ chain_err,
-                                                  uint32_t* __restrict__ sink, void* lds)
+                                                  const float* __restrict__ emit_label, uint32_t* __restrict__ out,
+                                                  double* __restrict__ mass, int* __restrict__ chain_err, void* lds)
 {
     static_assert(kMode != Mode::kBest, "the maximum recursion runs in the log domain");
     const int L = m.L, chunks = 2 * frame_blocks(m.Tb);
@@ -2046,14 +2087,10 @@ __device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, cons
     const float* epb = emit_label + label_emission_offset(m, has_b, has_b ? lab[lib] : 0, lib, first_chunk, kZeroEmission);
     const int64_t step_a = label_emission_step(m, has_a, kBackward), step_b = label_emission_step(m, has_b, kBackward);
     // Checkpoints: position i in column 1 + i, this lane's two are columns 1 + min(lia, lib) and the next one.  (has_a
-    // false: nothing of this lane is kept.)
-    const bool stores = kMode == Mode::kGrad && active && has_a;
-    const int64_t pitch = lattice_pitch(L), first_row = kBackward ? frame_blocks(m.Tb) - 1 : 0;
-    const int first_column = 1 + (kBackward ? lib : lia);
-    CheckpointState* vp = stores ? reinterpret_cast<CheckpointState*>(out + m.ab_off) + first_row * pitch + first_column
-                                 : reinterpret_cast<CheckpointState*>(sink);
-    int* fp = stores ? out_exponents + m.ab_off + first_row * pitch + first_column : reinterpret_cast<int*>(sink);
-    const int64_t row_step = stores ? (kBackward ? -pitch : pitch) : 0;
+    // false: nothing of this lane is kept.)  Cost only: one row, by pair, in the chain's own order; a lane without a pair B stores
+    // what nobody reads in the row's last column.
+    CheckpointRows rows(out + m.ab_off, CheckpointRow{lattice_pitch(L)}, kMode == Mode::kGrad ? frame_blocks(m.Tb) - 1 : 1,
+                        kMode == Mode::kGrad ? active && has_a : active, kMode == Mode::kGrad ? 1 + (kBackward ? lib : lia) : ja);
 
     const int last_wave = waves - 1;
     int budget = m.poll_budget;
@@ -2154,12 +2191,10 @@ __device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, cons
 
     auto checkpoint = [&]() __attribute__((always_inline)) {
         const CheckpointState state_a{va_blank, va_label}, state_b{vb_blank, vb_label};
-        vp[0] = kBackward ? state_b : state_a;
-        vp[1] = kBackward ? state_a : state_b;
-        typedef int Frames __attribute__((ext_vector_type(2), aligned(4)));
-        *reinterpret_cast<Frames*>(fp) = Frames{f.frame, f.frame};       // both pairs of the lane share its frame
-        vp += row_step;
-        fp += row_step;
+        rows.template state<kPolicy>(0, kBackward ? state_b : state_a);
+        rows.template state<kPolicy>(1, kBackward ? state_a : state_b);
+        rows.template frames<kPolicy>(f.frame);          // both pairs of the lane share its frame
+        rows.next();
     };
     auto mid_block = [&]() __attribute__((always_inline)) {
         if (__builtin_expect((f.rough | look) != 0, 0))
@@ -2222,15 +2257,9 @@ __device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, cons
 
     if (kMode == Mode::kLoss) {
         // the state of every pair, for finish_loss
-        CheckpointState* const states = reinterpret_cast<CheckpointState*>(out + m.ab_off);
-        if (active) {
-            states[ja] = CheckpointState{va_blank, va_label};
-            out_exponents[m.ab_off + ja] = f.frame;
-        }
-        if (active && jb <= L) {
-            states[jb] = CheckpointState{vb_blank, vb_label};
-            out_exponents[m.ab_off + jb] = f.frame;
-        }
+        rows.template state<kPolicy>(0, CheckpointState{va_blank, va_label});
+        rows.template state<kPolicy>(1, CheckpointState{vb_blank, vb_label});
+        rows.template frames<kPolicy>(f.frame);
         return lost;
     }
     if (!kBackward) {
@@ -2245,7 +2274,7 @@ __device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, cons
 
 // Where the chains of a launch leave their states: value and exponent blocks of both directions
 // (see "lattice storage").  In the modes without a gradient: the state of every pair after a chain's last frame (cost
-// only: doubles in the value block, frames in the exponent block), or the predecessor choices in the value block and
+// only: one row of checkpoints in the value block), or the predecessor choices in the value block and
 // the last states, base-2 logarithms, in the exponent block (Mode::kBest).
 struct LatticeOut {
     uint32_t* alpha;
@@ -2278,25 +2307,22 @@ struct LaunchWords {
 // the additions is that of the pairs.  The count carries, in its upper half, how many wavefronts gave up waiting for a
 // neighbour; then the cost is NaN.  `waves`: wavefronts of a chain.  One more wavefront counts itself in, which has nothing to do with
 // the chains and leaves the norms (norms_of_utterance).
-template <bool kOfChain>
 __device__ __forceinline__ void finish_loss(const Utt& m, const int u, const int* __restrict__ labels, const LatticeOut& lat,
                                             const double* __restrict__ mass, int* __restrict__ done, float* __restrict__ costs,
                                             const int waves, const bool lost)
 {
     const int lane = threadIdx.x & 63, expected = 2 * waves + 1;
-    // (device scope: the chains may run on different dies; what has been published is past the die's cache once it is out)
+    // (the chains may run on different dies; what has been published is past the die's cache once it is out)
     int before = 0;
-    if (kOfChain) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if (lane == 0)
         before = __hip_atomic_fetch_add(&done[u * kDoneStride], lost ? 0x10001 : 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     before = __builtin_amdgcn_readfirstlane(before);
     if ((before & 0xFFFF) != expected - 1) return;
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     const int L = m.L;
-    const CheckpointState* const alpha = reinterpret_cast<const CheckpointState*>(lat.alpha + m.ab_off);
-    const CheckpointState* const beta = reinterpret_cast<const CheckpointState*>(lat.beta + m.ab_off);
-    const int *const fa = lat.alpha_exponents + m.ab_off, *const fb = lat.beta_exponents + m.ab_off;
+    const CheckpointRow row{lattice_pitch(L)};
+    const CheckpointState *const alpha = row.states(lat.alpha + m.ab_off, 0), *const beta = row.states(lat.beta + m.ab_off, 0);
+    const int *const fa = row.frames(lat.alpha + m.ab_off, 0), *const fb = row.frames(lat.beta + m.ab_off, 0);
     const int* const lab = labels + m.lab_off;
     const double log2_norms = published(&mass[u * kMassWords + kMassNorms]);
     // A lane's sum as sum * 2^top.
@@ -2310,21 +2336,38 @@ __device__ __forceinline__ void finish_loss(const Utt& m, const int u, const int
         sum = __builtin_amdgcn_ldexp(sum, max(top - higher, -2000)) + __builtin_amdgcn_ldexp(v, max(e - higher, -2000));
         top = higher;
     };
-    for (int j = lane; j <= L; j += 64) {
-        // pair j going forward: blank j and label j; the backward chain's pair i: blank L - i and label L - 1 - i
-        const CheckpointState a = alpha[j];
-        const CheckpointState before_a = j > 0 ? alpha[j - 1] : CheckpointState{0.0, 0.0};
-        const int a_frame = fa[j], before_frame = j > 0 ? fa[j - 1] : 0;
-        const double blank_b = beta[L - j].blank;
-        const int blank_frame = fb[L - j];
-        add(a.blank, a_frame, blank_b, blank_frame);
-        add(before_a.label, before_frame, blank_b, blank_frame);
-        if (j < L) {
-            const double label_b = beta[L - 1 - j].label;
-            const int label_frame = fb[L - 1 - j];
-            add(a.label, a_frame, label_b, label_frame);
-            add(a.blank, a_frame, label_b, label_frame);
-            if (j > 0 && lab[j] != lab[j - 1]) add(before_a.label, before_frame, label_b, label_frame);
+    // pair j going forward: blank j and label j; the backward chain's pair i: blank L - i and label L - 1 - i.  (Past the cache each look
+    // is a trip to memory: kAtOnce pairs' words travel together.)
+    constexpr int kAtOnce = 2;
+    for (int j0 = lane; j0 - lane <= L; j0 += 64 * kAtOnce) {
+        CheckpointState a[kAtOnce];
+        double before_label[kAtOnce], blank_b[kAtOnce], label_b[kAtOnce];
+        int a_frame[kAtOnce], before_frame[kAtOnce], blank_frame[kAtOnce], label_frame[kAtOnce];
+        bool skips[kAtOnce];
+#pragma unroll
+        for (int n = 0; n < kAtOnce; ++n) {
+            const int j = min(j0 + 64 * n, L), before = max(j - 1, 0), after = max(L - 1 - j, 0);
+            a[n] = published(&alpha[j]);
+            a_frame[n] = published(&fa[j]);
+            before_label[n] = published(&alpha[before].label);
+            before_frame[n] = published(&fa[before]);
+            blank_b[n] = published(&beta[L - j].blank);
+            blank_frame[n] = published(&fb[L - j]);
+            label_b[n] = published(&beta[after].label);
+            label_frame[n] = published(&fb[after]);
+            skips[n] = j > 0 && j < L && lab[j] != lab[j - 1];
+        }
+#pragma unroll
+        for (int n = 0; n < kAtOnce; ++n) {
+            const int j = j0 + 64 * n;
+            if (j > L) continue;
+            add(a[n].blank, a_frame[n], blank_b[n], blank_frame[n]);
+            if (j > 0) add(before_label[n], before_frame[n], blank_b[n], blank_frame[n]);
+            if (j < L) {
+                add(a[n].label, a_frame[n], label_b[n], label_frame[n]);
+                add(a[n].blank, a_frame[n], label_b[n], label_frame[n]);
+                if (skips[n]) add(before_label[n], before_frame[n], label_b[n], label_frame[n]);
+            }
         }
     }
     for (int d = 1; d < 64; d <<= 1) {
@@ -2345,11 +2388,9 @@ __device__ __forceinline__ bool chains_ended(int done)
     return ((done >> kChainsShift) & 3) == 2 && (done & kField) == ((done >> kWavesShift) & kField);
 }
 // A wavefront of a chain has ended, and everything it has published is out; `waves` of them make the chain, the first says
-// so.
+// so.  (What log-domain chains have stored the ordinary way must leave the die's cache before.)
 __device__ __forceinline__ void announce_end(int* done, int waves)
 {
-    // (what was stored the ordinary way must leave the die's cache)
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     const int count = threadIdx.x < 64 ? 1 + (waves << kWavesShift) + (1 << kChainsShift) : 1;
     if ((threadIdx.x & 63) == 0) __hip_atomic_fetch_add(done, count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -2394,7 +2435,7 @@ __device__ __forceinline__ int lattice_body(const int chain, const Utt* __restri
     if (chain < 0) return 0;      // device-planned batches launch a workgroup per utterance and direction, running or not
     // (measurements of the recursions one after the other: a launch that leaves one direction out)
     if (kMode == Mode::kGrad && ((wk.skip_directions >> (chain & 1)) & 1)) return 0;
-    // Lanes with nothing to store write to a sink: 64 bytes of it per wavefront of the launch.  (One
+    // Lanes of log-domain chains with nothing to store write to a sink: 64 bytes of it per wavefront of the launch.  (One
     // address for the whole launch was what a crowded launch waited for: every store instruction of
     // every chain carried a write to it, and they all met in one channel of each die's L2.  512
     // utterances of 20 symbols and 740 frames: 59 -> 40 us.  Writing to an unused column of the
@@ -2470,22 +2511,23 @@ __device__ __forceinline__ int lattice_body(const int chain, const Utt* __restri
             bool lost = false;
             auto run = [&](auto steep_ones) __attribute__((always_inline)) {
                 constexpr bool kSteep = decltype(steep_ones)::value;
+                constexpr int kPolicy = kFused || kMode == Mode::kLoss ? kPast : 0;
                 if (two_pairs) {
                     if constexpr (kSync == Sync::kHalo) {
                         if (forward)
-                            lost = run_chain_linear2<false, kMode, kSteep>(m, u, gentle, labels, emit_label, lat.alpha, lat.alpha_exponents, mass, chain_err, sink, lds);
+                            lost = run_chain_linear2<false, kMode, kSteep, kPolicy>(m, u, gentle, labels, emit_label, lat.alpha, mass, chain_err, lds);
                         else
-                            lost = run_chain_linear2<true, kMode, kSteep>(m, u, gentle, labels, emit_label, lat.beta, lat.beta_exponents, mass, chain_err, sink, lds);
+                            lost = run_chain_linear2<true, kMode, kSteep, kPolicy>(m, u, gentle, labels, emit_label, lat.beta, mass, chain_err, lds);
                     }
                 } else if (forward) {
-                    lost = run_chain_linear<false, kSync, kMode, kSteep>(m, u, gentle, labels, emit_label, lat.alpha, lat.alpha_exponents, mass, chain_err, sink, lds);
+                    lost = run_chain_linear<false, kSync, kMode, kSteep, kPolicy>(m, u, gentle, labels, emit_label, lat.alpha, mass, chain_err, lds);
                 } else {
-                    lost = run_chain_linear<true, kSync, kMode, kSteep>(m, u, gentle, labels, emit_label, lat.beta, lat.beta_exponents, mass, chain_err, sink, lds);
+                    lost = run_chain_linear<true, kSync, kMode, kSteep, kPolicy>(m, u, gentle, labels, emit_label, lat.beta, mass, chain_err, lds);
                 }
             };
             if (__builtin_expect(steep, 0)) run(std::true_type{});
             else run(std::false_type{});
-            if (kMode == Mode::kLoss) finish_loss<true>(m, u, labels, lat, mass, wk.done, costs, waves, lost);
+            if (kMode == Mode::kLoss) finish_loss(m, u, labels, lat, mass, wk.done, costs, waves, lost);
             if (kFused) announce_end(&wk.done[u * kDoneStride], waves);
             return left;
         }
@@ -2494,7 +2536,10 @@ __device__ __forceinline__ int lattice_body(const int chain, const Utt* __restri
         run_chain_log<false, kSync, kMode>(m, u, labels, emit_blank, emit_blank64, emit_label, lat.alpha, lat.alpha_exponents, mass, costs, chain_err, sink, lds);
     else if constexpr (kMode != Mode::kLoss)
         run_chain_log<true, kSync, kMode>(m, u, labels, emit_blank, emit_blank64, emit_label, lat.beta, lat.beta_exponents, mass, costs, chain_err, sink, lds);
-    if (kFused) announce_end(&wk.done[u * kDoneStride], waves);
+    if (kFused) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        announce_end(&wk.done[u * kDoneStride], waves);
+    }
     return left;
 }
 
@@ -2513,7 +2558,7 @@ __device__ __forceinline__ void norms_of_utterance(const Utt* __restrict__ meta,
     const Norms norms = norms_of_wave(norms_of_lane(m, emit_blank));
     if ((threadIdx.x & 63) == 0) publish(&mass[u * kMassWords + kMassNorms], norms.log2());
     const bool two_pairs = kSync == Sync::kHalo && (m.flags & kUttTwoPairs) != 0;
-    finish_loss<false>(m, u, labels, lat, mass, wk.done, costs, two_pairs ? m.waves2 : m.waves, false);
+    finish_loss(m, u, labels, lat, mass, wk.done, costs, two_pairs ? m.waves2 : m.waves, false);
 }
 
 // grid = one workgroup per entry of `order` (utterance * 2 + direction: 0 forward, 1 backward); cost-only launches: then those of
@@ -2864,21 +2909,19 @@ struct BlockEnds {
     static __device__ __forceinline__ BlockEnds load(const Utt& m, const LatticeOut& lat, int p0, int block)
     {
         BlockEnds e;
-        const int64_t pitch = lattice_pitch(m.L);
-        const int column = 1 + min(p0, max(m.L, 1) - 1);
+        const CheckpointRow row{lattice_pitch(m.L)};
+        const int blocks = frame_blocks(m.Tb), column = 1 + min(p0, max(m.L, 1) - 1);
         auto state = [](const CheckpointState* p) { return kPublished ? published(p) : *p; };
         auto word = [](const int* p) { return kPublished ? published(p) : *p; };
         if (block > 0) {
-            const int64_t where = (block - 1) * pitch + column;
-            const CheckpointState* v = reinterpret_cast<const CheckpointState*>(lat.alpha + m.ab_off) + where;
-            const int* f = lat.alpha_exponents + m.ab_off + where;
+            const CheckpointState* const v = row.states(lat.alpha + m.ab_off, block - 1) + column;
+            const int* const f = row.frames(lat.alpha + m.ab_off, block - 1) + column;
             e.a0 = state(&v[0]); e.a1 = state(&v[1]);
             e.fa0 = word(&f[0]); e.fa1 = word(&f[1]);
         }
-        if (block + 1 < frame_blocks(m.Tb)) {
-            const int64_t where = (block + 1) * pitch + column;
-            const CheckpointState* v = reinterpret_cast<const CheckpointState*>(lat.beta + m.ab_off) + where;
-            const int* f = lat.beta_exponents + m.ab_off + where;
+        if (block + 1 < blocks) {
+            const CheckpointState* const v = row.states(lat.beta + m.ab_off, blocks - 2 - block) + column;
+            const int* const f = row.frames(lat.beta + m.ab_off, blocks - 2 - block) + column;
             e.b0 = state(&v[0]); e.b1 = state(&v[1]);
             e.fb0 = word(&f[0]); e.fb1 = word(&f[1]);
         }

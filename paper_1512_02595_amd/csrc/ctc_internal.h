@@ -262,9 +262,10 @@ CTC_HOST_DEVICE constexpr int label_pieces(int L)
 // (64 utterances of 2000 frames); with eight, labels of 470 symbols and more could not use what it saves for 32 utterances of
 // 1500 frames (540 symbols: 169.4 us apart, 157.6 beside).
 constexpr int kFusedWaves = 12;
+constexpr int kCrowdedFusedWaves = 8;    // ... where there are more chains than compute units
 constexpr bool can_fuse_gradient(int A, int max_waves, int n_chains, int n_cu)
 {
-    return A <= kDirectMaxA && max_waves <= kFusedWaves && n_chains <= n_cu;
+    return A <= kDirectMaxA && max_waves <= (n_chains <= n_cu ? kFusedWaves : kCrowdedFusedWaves);
 }
 // Whether that pays.  Beside the chains, the compute units without one write the gradient of the utterances that end before the
 // longest (`early`; `late`: whose chains end in the last 15 % of the time) and a launch boundary is saved.  But what is left at
@@ -284,10 +285,25 @@ inline bool gradient_beside_chains(double early, double late, double chain_us, i
                          : late + 3.0 * busy <= saved + 0.7 * early * (1.0 - 0.4 * busy);
 }
 // What a chain of this many wavefronts took for a frame, in microseconds, when the rule above was fitted (up to four run on a SIMD each).
-// The steps of a linear-domain chain take about half of that now, 0.018, 0.024 to 0.035 and 0.043; the rule, which divides these numbers
-// by its own constants, has not been fitted again.  (Measured since: 122 x 454 frames, 29 symbols, apart 42.1 us a call, beside 44.0; 128
-// x 454 x 34 46.8 and 50.3; 100 x 454 x 34 44.2 and 43.1; 64 x 454 x 29 35.3 and 34.6: beside in all four.)
+// The steps of a linear-domain chain take about half of that now, 0.018, 0.024 to 0.035 and 0.043; the rule divides by these.
 inline double chain_us_per_frame(int waves) { return waves == 1 ? 0.045 : (waves <= 4 ? 0.06 : 0.088); }
+
+// The rule that launches follow.  The one above was fitted before the chains' checkpoints went past the caches, when a chain's end held up
+// the others on its die; of it, launches of more than eight wavefronts are left.  Random batches, three of a kind in turn:
+// Up to a chain per compute unit, up to eight wavefronts: beside (87 batches: 0.79 to 0.97 of the time apart; 128 x 454 x 29 36.3 us a
+// call apart, 32.3 beside; 64 x 750 x 60, lengths from 600 on, 72.0 and 65.4).
+// More chains than compute units, up to four wavefronts: beside while all of them start together, four workgroups to a compute unit (51 batches: 0.83 to
+// 1.01 of the time apart, in the mean 0.93; 512 x 750 x 29 127.3 apart, 115.5 beside).  Beyond it 51 batches took 0.85 to 1.18, in the mean 1.02.
+// More wavefronts, two workgroups to a compute unit: up to 2.75 chains to one, and at least half of the work early (11 batches: 0.88 to 1.00,
+// in the mean 0.95; seven others 0.87 to 1.08, 1.01).
+// Chains of up to 100 frames keep to the launch apart: blocks that wait for them are most of such a launch (22 batches: 0.91 to 1.11, in the
+// mean 0.98).
+constexpr double kCrowdedBesideUs = 4.5;
+inline bool gradient_in_lattice_launch(double early, double late, double chain_us, int max_waves, int n_chains, int n_cu)
+{
+    if (n_chains > n_cu) return chain_us >= kCrowdedBesideUs && (max_waves <= 4 ? n_chains <= 4 * n_cu : 4 * n_chains <= 11 * n_cu && late <= early);
+    return max_waves <= 8 || gradient_beside_chains(early, late, chain_us, max_waves, n_chains, n_cu);
+}
 
 constexpr int kDoneStride = 16;      // words between two utterances' words: a line each for those who poll
 constexpr int kTakenWord = 1;        // which of them says that the chains have a workgroup (take_chain; the first is the counter)

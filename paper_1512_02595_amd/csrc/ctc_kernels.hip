@@ -1106,8 +1106,10 @@ __device__ __forceinline__ int rows_flagged(const int* __restrict__ row_flags, i
 //   alpha, after frame 16 k + 15:  per label position j  (blank j, label j) as doubles, and their frame (int32)
 //   beta, after frame 16 k:        per label position j  (blank j + 1, label j)
 // (inclusive quantities, see the recursions), position j in column 1 + j.  Rows lie in the order in which the chain stores them, the
-// last one, which nobody asks for, left out; a row's 16-byte states come first, then its frames (CheckpointRow).  All of it in the
-// first half of the direction's region.
+// last one, which nobody asks for, left out; a row's 16-byte states come first, those of even columns before those of odd ones, then its
+// frames (CheckpointRow).  All of it in the first half of the direction's region.
+// (Where a lane stores two columns next to each other, either store otherwise writes half of every 32 bytes, and past the die's cache nobody
+// puts them together: 512 x 750 frames, 29 symbols, three minibatches in turn, gradient beside the chains, 134.2 us a call.)
 //
 // Log-domain chains (rare) store every frame, per label state a number m * 2^e, as
 //   a value word (uint32): the high dword of the fp64 m (sign, exponent, top 20 mantissa bits),
@@ -1120,8 +1122,11 @@ __device__ __forceinline__ int rows_flagged(const int* __restrict__ row_flags, i
 struct alignas(16) CheckpointState { double blank, label; };
 struct CheckpointRow {
     int64_t pitch;                                       // columns
-    __device__ __forceinline__ int64_t bytes() const { return (pitch * static_cast<int64_t>(sizeof(CheckpointState) + sizeof(int)) + 15) / 16 * 16; }
-    __device__ __forceinline__ int64_t frames_at() const { return pitch * static_cast<int64_t>(sizeof(CheckpointState)); }
+    __device__ __forceinline__ int64_t half() const { return (pitch + 1) / 2; }
+    __device__ __forceinline__ int slot(int column) const { return (column >> 1) + ((column & 1) ? static_cast<int>(half()) : 0); }
+    // (whole pieces of 64 bytes, as the region begins: 64 * pitch of them are there for a row)
+    __device__ __forceinline__ int64_t bytes() const { return (frames_at() + pitch * static_cast<int64_t>(sizeof(int)) + 63) / 64 * 64; }
+    __device__ __forceinline__ int64_t frames_at() const { return 2 * half() * static_cast<int64_t>(sizeof(CheckpointState)); }
     __device__ __forceinline__ const CheckpointState* states(const uint32_t* block, int64_t row) const
     {
         return reinterpret_cast<const CheckpointState*>(reinterpret_cast<const char*>(block) + row * bytes());
@@ -1185,11 +1190,12 @@ constexpr int kPast = 16;                                // (cache policy: sc1)
 struct CheckpointRows {
     static constexpr unsigned kNowhere = 0x80000000u;    // (a block has fewer bytes: make_layout)
     __amdgpu_buffer_rsrc_t block;
-    unsigned state_at, frame_at;                         // in the row, of this lane
+    unsigned state_at, next_state_at, frame_at;          // in the row, of this lane's column and the one after it
     int at, step;                                        // of the row
     __device__ __forceinline__ CheckpointRows(uint32_t* out, CheckpointRow row, int rows, bool stores, int column)
         : block(__builtin_amdgcn_make_buffer_rsrc(out, 0, static_cast<int>(rows * row.bytes()), 0x00020000)),
-          state_at(stores ? static_cast<unsigned>(column * sizeof(CheckpointState)) : kNowhere),
+          state_at(stores ? static_cast<unsigned>(row.slot(column) * sizeof(CheckpointState)) : kNowhere),
+          next_state_at(stores ? static_cast<unsigned>(row.slot(column + 1) * sizeof(CheckpointState)) : kNowhere),
           frame_at(stores ? static_cast<unsigned>(row.frames_at() + column * sizeof(int)) : kNowhere),
           at(0), step(static_cast<int>(row.bytes()))
     {
@@ -1199,7 +1205,7 @@ struct CheckpointRows {
     template <int kPolicy>
     __device__ __forceinline__ void state(int column, const CheckpointState& s) const
     {
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(Words4, s), block, static_cast<int>(state_at) + column * static_cast<int>(sizeof(CheckpointState)), at, kPolicy);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(Words4, s), block, static_cast<int>(column == 0 ? state_at : next_state_at), at, kPolicy);
     }
     template <int kPolicy>
     __device__ __forceinline__ void frame(int f) const { __builtin_amdgcn_raw_buffer_store_b32(static_cast<unsigned>(f), block, static_cast<int>(frame_at), at, kPolicy); }
@@ -1244,12 +1250,13 @@ __device__ __forceinline__ int window_max_step_down(int window, int mine)
     asm("s_nop 1\n\tv_max_i32_dpp %0, %0, %1 wave_shl:1 row_mask:0xf bank_mask:0xf" : "+v"(window) : "v"(mine));
     return window;
 }
-// Lane i receives the value of lane i+1 (DPP wave_shl:1); lane 63 keeps what `into` held.
-__device__ __forceinline__ double shift_down(double v, int& into_lo, int& into_hi)
+// Lane i receives the value of lane i - 1 (kDown: i + 1), and a lane without such a neighbour zero.
+template <bool kDown>
+__device__ __forceinline__ double lane_shift(double v)
 {
-    into_lo = __builtin_amdgcn_update_dpp(into_lo, __double2loint(v), 0x130, 0xf, 0xf, false);
-    into_hi = __builtin_amdgcn_update_dpp(into_hi, __double2hiint(v), 0x130, 0xf, 0xf, false);
-    return __hiloint2double(into_hi, into_lo);
+    constexpr int kCtrl = kDown ? 0x130 : 0x138;
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), kCtrl, 0xf, 0xf, true),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(v), kCtrl, 0xf, 0xf, true));
 }
 
 // What is kept of an utterance's mass p (of its frames divided by their norms), kMassWords doubles:
@@ -2347,13 +2354,13 @@ __device__ __forceinline__ void finish_loss(const Utt& m, const int u, const int
 #pragma unroll
         for (int n = 0; n < kAtOnce; ++n) {
             const int j = min(j0 + 64 * n, L), before = max(j - 1, 0), after = max(L - 1 - j, 0);
-            a[n] = published(&alpha[j]);
+            a[n] = published(&alpha[row.slot(j)]);
             a_frame[n] = published(&fa[j]);
-            before_label[n] = published(&alpha[before].label);
+            before_label[n] = published(&alpha[row.slot(before)].label);
             before_frame[n] = published(&fa[before]);
-            blank_b[n] = published(&beta[L - j].blank);
+            blank_b[n] = published(&beta[row.slot(L - j)].blank);
             blank_frame[n] = published(&fb[L - j]);
-            label_b[n] = published(&beta[after].label);
+            label_b[n] = published(&beta[row.slot(after)].label);
             label_frame[n] = published(&fb[after]);
             skips[n] = j > 0 && j < L && lab[j] != lab[j - 1];
         }
@@ -2768,8 +2775,9 @@ void ctc_backtrace_kernel(const Utt* __restrict__ meta, const int* __restrict__ 
 //   alpha: (blank j, label j) as in the forward chain;  beta: (label j, blank j + 1), the backward chain's pair.
 // 128 positions make a piece; longer labels take several, each recomputing the 16 positions at its inner edges that
 // its neighbour owns (an error at the edge moves up one position per frame).
-// A row of one value per lane in LDS, padded so that 16-byte reads of 16 rows meet in no bank; two blocks of a row per frame.
-constexpr int kShareRow = kPiecePositions / 2 + 4, kShareInts = 2 * kBlockFrames * kShareRow;
+// A row of one value per lane in LDS; two blocks of a row per frame.  (Not padded: 16 rows' 16-byte reads meet in the same banks, 12 of
+// them a piece, but both words of a frame are one instruction's offsets apart: 32 address additions a piece less.)
+constexpr int kShareRow = kPiecePositions / 2, kShareInts = 2 * kBlockFrames * kShareRow;
 constexpr int kNormInts = kBlockFrames;
 static_assert(kPieceStep % 32 == 0, "pieces start at multiples of 32 positions (share_product)");
 
@@ -2911,20 +2919,19 @@ struct BlockEnds {
         BlockEnds e;
         const CheckpointRow row{lattice_pitch(m.L)};
         const int blocks = frame_blocks(m.Tb), column = 1 + min(p0, max(m.L, 1) - 1);
-        auto state = [](const CheckpointState* p) { return kPublished ? published(p) : *p; };
-        auto word = [](const int* p) { return kPublished ? published(p) : *p; };
-        if (block > 0) {
-            const CheckpointState* const v = row.states(lat.alpha + m.ab_off, block - 1) + column;
-            const int* const f = row.frames(lat.alpha + m.ab_off, block - 1) + column;
-            e.a0 = state(&v[0]); e.a1 = state(&v[1]);
-            e.fa0 = word(&f[0]); e.fa1 = word(&f[1]);
-        }
-        if (block + 1 < blocks) {
-            const CheckpointState* const v = row.states(lat.beta + m.ab_off, blocks - 2 - block) + column;
-            const int* const f = row.frames(lat.beta + m.ab_off, blocks - 2 - block) + column;
-            e.b0 = state(&v[0]); e.b1 = state(&v[1]);
-            e.fb0 = word(&f[0]); e.fb1 = word(&f[1]);
-        }
+        const int slot0 = row.slot(column) * static_cast<int>(sizeof(CheckpointState)), slot1 = row.slot(column + 1) * static_cast<int>(sizeof(CheckpointState));
+        const int frame_at = static_cast<int>(row.frames_at()) + column * static_cast<int>(sizeof(int));
+        constexpr int kPolicy = kPublished ? kPast : 0;
+        auto load_row = [&](const uint32_t* states, int r, CheckpointState& s0, CheckpointState& s1, int& f0, int& f1) __attribute__((always_inline)) {
+            const auto block_row = __builtin_amdgcn_make_buffer_rsrc(const_cast<CheckpointState*>(row.states(states + m.ab_off, r)), 0, static_cast<int>(row.bytes()), 0x00020000);
+            s0 = __builtin_bit_cast(CheckpointState, __builtin_amdgcn_raw_buffer_load_b128(block_row, slot0, 0, kPolicy));
+            s1 = __builtin_bit_cast(CheckpointState, __builtin_amdgcn_raw_buffer_load_b128(block_row, slot1, 0, kPolicy));
+            const auto f = __builtin_amdgcn_raw_buffer_load_b64(block_row, frame_at, 0, kPolicy);
+            f0 = static_cast<int>(f[0]);
+            f1 = static_cast<int>(f[1]);
+        };
+        if (block > 0) load_row(lat.alpha, block - 1, e.a0, e.a1, e.fa0, e.fa1);
+        if (block + 1 < blocks) load_row(lat.beta, blocks - 2 - block, e.b0, e.b1, e.fb0, e.fb1);
         return e;
     }
 };
@@ -2963,7 +2970,6 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
         s.label0 = block > 0 && has0 ? ends.a0.label : 0.0;
         s.blank1 = block > 0 && has1 ? ends.a1.blank : 0.0;
         s.label1 = block > 0 && has1 ? ends.a1.label : 0.0;
-        int prev_lo = 0, prev_hi = 0;
         renew_pairs<false>(s, ends.fa0, ends.fa1, steep);
         alpha_frame0 = alpha_middle0 = s.frame;
         emissions(0, el0, el1);
@@ -2983,7 +2989,7 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
                     (h ? alpha_middle1 : alpha_middle0) = s.frame;
                     skip0_scale = skip0_one * s.scale;
                 }
-                const double prev = shift_up(s.label1, prev_lo, prev_hi);
+                const double prev = lane_shift<false>(s.label1);
                 pin();
                 const double u1 = s.blank1 + s.label1;
                 pin();
@@ -3021,7 +3027,6 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
     s.label1 = !last && has1 ? ends.b1.label : 0.0;
     const bool own0 = p0 >= own_first && p0 < own_end, own1 = p1 >= own_first && p1 < own_end;
     const int to_share = __double2loint(packed_inverse_p) + kScaleLog2;
-    int next_lo = 0, next_hi = 0;
     // A step's shares are formed during the step after it (before the first: of zeros, in a row that is filed again).
     double pending_alpha0 = 0.0, pending_alpha1 = 0.0, pending_beta0 = 0.0, pending_beta1 = 0.0;
     int pending_row = kBlockFrames - 1;
@@ -3052,7 +3057,7 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
                 set_exponents(h == 0 ? alpha_frame0 : alpha_frame1);
                 skip2_scale = skip2_one * s.scale;
             }
-            const double next = shift_down(s.label0, next_lo, next_hi);
+            const double next = lane_shift<true>(s.label0);
             pin();
             const double share0 = pending_alpha0 * pending_beta0;
             pin();
@@ -3166,7 +3171,7 @@ __device__ __forceinline__ int domain_of(const int* domain, int b)
 //     2-norm of the gradient's error: within 1 % of what three bf16 parts (the whole fp32 share) give, which cost the 512
 //     utterances' gradient 1.6 % of the call; with both halves rounded toward zero it was 7 to 11 % more;
 //   - A operand, per 32 positions: lane l holds frame l % 16, positions 8 (l / 16) .. + 7, one 16-byte
-//     read out of LDS (rows 272 bytes apart: no bank is asked twice);
+//     read out of LDS;
 //   - B operand: lane l holds the same positions for symbol l % 16 (+ 16 per tile of symbols), made from the
 //     label's bytes in LDS; the blank's column is 1 everywhere, so that it receives the sum of all shares, and
 //     the blank's occupancy is what is left of 1.
@@ -3178,8 +3183,11 @@ __host__ __device__ constexpr int tile_label_ints(int L) { return (L + 31) / 32 
 // lanes that read different symbols meet in few banks), one more row of zeros for lanes without a position.
 constexpr int kEmissionRow = 12;
 __host__ __device__ constexpr int tile_emission_ints(int tiles) { return (2 * 16 * tiles + 1) * kEmissionRow; }
-// LDS of one wavefront.
-__host__ __device__ constexpr int tile_lds_ints(int Lmax, int tiles) { return kNormInts + kShareInts + tile_emission_ints(tiles) + tile_label_ints(Lmax); }
+// LDS of one wavefront.  staged: with the block's emissions.
+__host__ __device__ constexpr int tile_lds_ints(int Lmax, int tiles, bool staged)
+{
+    return kNormInts + kShareInts + (staged ? tile_emission_ints(tiles) : 0) + tile_label_ints(Lmax);
+}
 __device__ __forceinline__ void stage_label_bytes(unsigned* s_label, const int* __restrict__ labels, int L)
 {
     for (int w = threadIdx.x & 63; w < tile_label_ints(L); w += 64) {
@@ -3195,10 +3203,17 @@ __device__ __forceinline__ void stage_label_bytes(unsigned* s_label, const int* 
 
 template <int kTiles>
 __device__ __forceinline__ void share_product(float4v (&acc)[kTiles], const unsigned* s_hi, const unsigned* s_lo,
-                                              const unsigned* s_label, int base, int L, const unsigned (&symbol)[kTiles],
-                                              const unsigned (&mask)[kTiles])
+                                              const unsigned* s_label, int base, int L, int blank)
 {
     const int lane = tile_thread() & 63, c = lane & 15, g = lane >> 4;
+    // the symbol of this lane's column, per tile of symbols: label bytes are compared as (byte & mask) ^ symbol == 0
+    unsigned symbol[kTiles], mask[kTiles];
+#pragma unroll
+    for (int n = 0; n < kTiles; ++n) {
+        const int k = 16 * n + c;
+        symbol[n] = k == blank ? 0u : static_cast<unsigned>(k) * 0x01010101u;
+        mask[n] = k == blank ? static_cast<unsigned>(kNoSymbol) * 0x01010101u : 0x7F7F7F7Fu;
+    }
     for (int k0 = base; k0 < min(L, base + kPiecePositions); k0 += 32) {
         const int at = c * kShareRow + (k0 - base) / 2 + 4 * g;
         const half8 hi = __builtin_bit_cast(half8, *reinterpret_cast<const uint4v*>(s_hi + at));
@@ -3292,9 +3307,13 @@ __device__ __forceinline__ void utterance_cost(const TileArgs& g, const Utt* __r
 // Workgroup `group` of utterance b: kRowThreads / 64 wavefronts, ceil((blocks of T + 1) / (4 / wavefronts per block)) workgroups: the first
 // wavefront behind the utterance's blocks writes its cost.  (With a workgroup of its own for that, 512 x 40 to 130 frames took 43.3 us a
 // call in place of 37.2: places for workgroups are what such launches wait for.)
-// LDS 4 tile_lds_ints(Lmax, kTiles) ints.  kTiles: tiles of 16 symbols.
+// LDS 4 tile_lds_ints(Lmax, kTiles, kStaged) ints.  kTiles: tiles of 16 symbols.
+// kStaged: the block's emissions wait in LDS, where they are at once when the chains have ended.  Otherwise a lane takes its own from the
+// die's cache when it needs them: without them (3 and 6 KB a wavefront, 32 and 64 symbols) four workgroups fit a compute unit in place of
+// three and two, as many as 128 registers allow.  (What the launch lasts then: 512 x 300 frames, 50 symbols, 67.1 us a call staged, 61.4 not;
+// 300 x 400, 40 symbols bf16, 62.2 and 58.4; 512 x 750, 29 symbols, no difference: it is bound by issue.)
 // kLean: the lane's number is made anew where the rows are written (tile_thread), so that 128 registers suffice.
-template <int kTiles, bool kWait, bool kLean = false>
+template <int kTiles, bool kWait, bool kStaged, bool kLean = false>
 __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* __restrict__ meta, const int* __restrict__ labels,
                                             const float* __restrict__ emit_blank, const float* __restrict__ emit_label,
                                             const LatticeOut& lat, uint4v* tile_lds, const int b, const int group)
@@ -3320,22 +3339,35 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
         if (sharing > 1) __syncthreads();
         return;
     }
-    unsigned* const s_hi = reinterpret_cast<unsigned*>(tile_lds) + wave * tile_lds_ints(Lmax, kTiles);
+    unsigned* const s_hi = reinterpret_cast<unsigned*>(tile_lds) + wave * tile_lds_ints(Lmax, kTiles, kStaged);
     unsigned* const s_lo = s_hi + kBlockFrames * kShareRow;
     float* const s_emit = reinterpret_cast<float*>(s_hi + kShareInts);
-    float* const s_norm = s_emit + tile_emission_ints(kTiles);
+    float* const s_norm = s_emit + (kStaged ? tile_emission_ints(kTiles) : 0);
     unsigned* const s_label = reinterpret_cast<unsigned*>(s_norm + kBlockFrames);
-    static_assert((kShareInts + tile_emission_ints(kTiles)) % 4 == 0 && kNormInts % 4 == 0, "16-byte reads");
+    static_assert((kShareInts + (kStaged ? tile_emission_ints(kTiles) : 0)) % 4 == 0 && kNormInts % 4 == 0, "16-byte reads");
     // Everything that comes from memory is asked for here, before any of it is used.
     const float4* const emit_in = reinterpret_cast<const float4*>(emit_label + emission_at(m.e_off, A, t0, 0));
     // (the block's 16 A emissions: up to 4 A vectors, 64 lanes; variables of their own, as the array went to scratch memory)
     auto emission_vector = [&](int i) { return emit_in[min(64 * i + lane, 4 * A - 1)]; };
-    const float4 emit0 = emission_vector(0), emit1 = emission_vector(1);
-    const float4 emit2 = kTiles > 2 ? emission_vector(2) : emit0, emit3 = kTiles > 2 ? emission_vector(3) : emit0;
+    float4 emit0, emit1, emit2, emit3;
+    if constexpr (kStaged) {
+        emit0 = emission_vector(0);
+        emit1 = emission_vector(1);
+    }
+    if constexpr (kStaged && kTiles > 2) {
+        emit2 = emission_vector(2);
+        emit3 = emission_vector(3);
+    }
     const float norm_word = emit_blank[blank_emission_offset(m, 2 * block) + (lane & (kBlockFrames - 1))];
     // (an empty label has no string to look at, and the caller's array may be empty)
     const int first_base = part * kPieceStep;
     const LaneLabels first_labels(L > 0 ? labels + m.lab_off : &meta[b].L, max(L, 1), first_base);
+    // Not staged: a lane's emissions of either chunk and position.
+    struct ChunkEmissions { float4 v0, v1; };
+    auto chunk_emissions = [&](bool has, int symbol, int h) __attribute__((always_inline)) {
+        const float4* const p = reinterpret_cast<const float4*>(emit_label + label_emission_offset(m, has, symbol, 0, 2 * block + h, kZeroEmission));
+        return ChunkEmissions{p[0], p[1]};
+    };
     BlockEnds ends;
     bool log_domain = false, steep = false;
     double packed_inverse_p = 0.0;
@@ -3356,13 +3388,15 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
         const int v = 64 * i + lane;                     // vector v: half v % 2 of row v / 2
         if (v < 4 * A) *reinterpret_cast<float4*>(s_emit + (v >> 1) * kEmissionRow + (v & 1) * 4) = e;
     };
-    stage(0, emit0);
-    stage(1, emit1);
-    if constexpr (kTiles > 2) {
-        stage(2, emit2);
-        stage(3, emit3);
+    if constexpr (kStaged) {
+        stage(0, emit0);
+        stage(1, emit1);
+        if constexpr (kTiles > 2) {
+            stage(2, emit2);
+            stage(3, emit3);
+        }
+        if (lane < 8) s_emit[2 * A * kEmissionRow + lane] = 0.0f;
     }
-    if (lane < 8) s_emit[2 * A * kEmissionRow + lane] = 0.0f;
     if (lane < kBlockFrames) s_norm[lane] = frame_norm(norm_word);
     if (kWait) {
         if (!wait_for_chains(g_args, b, m.Tb)) {
@@ -3373,16 +3407,9 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
         load_ends();
     }
     if (kWait && log_domain) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    // the symbol of this lane's column, per tile of symbols: label bytes are compared as (byte & mask) ^ symbol == 0
-    unsigned symbol[kTiles], mask[kTiles];
     float4v acc[kTiles];
 #pragma unroll
-    for (int n = 0; n < kTiles; ++n) {
-        const int k = 16 * n + c;
-        symbol[n] = k == blank ? 0u : static_cast<unsigned>(k) * 0x01010101u;
-        mask[n] = k == blank ? static_cast<unsigned>(kNoSymbol) * 0x01010101u : 0x7F7F7F7Fu;
-        acc[n] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
-    }
+    for (int n = 0; n < kTiles; ++n) acc[n] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
     auto file = [&](int row, float x0, float x1) {
         const half2_raw hi = nearest_halves(x0, x1);
         const half2_raw lo = nearest_halves(minus_low_half(x0, hi), minus_high_half(x1, hi));
@@ -3393,7 +3420,7 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
         // LDS operations of one wavefront complete in program order; the fences only keep the
         // compiler from moving them across.
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        share_product<kTiles>(acc, s_hi, s_lo, s_label, base, L, symbol, mask);
+        share_product<kTiles>(acc, s_hi, s_lo, s_label, base, L, blank);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     };
     // (two loops: in one, what either recursion needs is held through the other, 20 registers)
@@ -3409,8 +3436,17 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
                 at = LaneLabels(labels + m.lab_off, L, base);
                 ends = BlockEnds::load<kWait>(m, lat, at.p0, block);
             }
-            auto emissions = [&](int i, float (&el0)[kChunk], float (&el1)[kChunk]) {
+            auto emissions = [&](int i, float (&el0)[kChunk], float (&el1)[kChunk]) __attribute__((always_inline)) {
                 const int h = i & 1;
+                if constexpr (!kStaged) {
+                    auto get = [](const ChunkEmissions& e, float (&el)[kChunk]) {
+                        el[0] = e.v0.x; el[1] = e.v0.y; el[2] = e.v0.z; el[3] = e.v0.w;
+                        el[4] = e.v1.x; el[5] = e.v1.y; el[6] = e.v1.z; el[7] = e.v1.w;
+                    };
+                    get(chunk_emissions(at.has0, at.symbol0, h), el0);
+                    get(chunk_emissions(at.has1, at.symbol1, h), el1);
+                    return;
+                }
                 auto row = [&](bool has, int symbol, float (&el)[kChunk]) {
                     const float4* v = reinterpret_cast<const float4*>(s_emit + (has ? h * A + symbol : 2 * A) * kEmissionRow);
                     const float4 x = v[0], y = v[1];
@@ -3433,7 +3469,7 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
         __syncthreads();
         if (part > 0) return;
         for (int i = 1; i < sharing; ++i) {
-            const float4v* const theirs = reinterpret_cast<const float4v*>(s_hi + i * tile_lds_ints(Lmax, kTiles));
+            const float4v* const theirs = reinterpret_cast<const float4v*>(s_hi + i * tile_lds_ints(Lmax, kTiles, kStaged));
 #pragma unroll
             for (int n = 0; n < kTiles; ++n) acc[n] += theirs[n * 64 + lane];
         }
@@ -3448,7 +3484,8 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
             const int k = 16 * n + column;
             if (k >= A) continue;
             auto* out = grads + (static_cast<size_t>(tr) * B + b) * A + k;
-            const float4 y = *reinterpret_cast<const float4*>(s_emit + ((quad >> 1) * A + k) * kEmissionRow + (quad & 1) * 4);
+            const float4 y = kStaged ? *reinterpret_cast<const float4*>(s_emit + ((quad >> 1) * A + k) * kEmissionRow + (quad & 1) * 4)
+                                     : emit_in[2 * ((quad >> 1) * A + k) + (quad & 1)];
             const float4 norm = *reinterpret_cast<const float4*>(s_norm + 4 * quad);
             const float yv[4] = {y.x, y.y, y.z, y.w}, norms[4] = {norm.x, norm.y, norm.z, norm.w};
 #pragma unroll
@@ -3471,14 +3508,14 @@ __device__ __forceinline__ int rotated_group(int within, int utterance, int grou
 
 // grid (workgroups per utterance, B)
 template <int kTiles>
-__global__ __launch_bounds__(kRowThreads)
+__global__ __launch_bounds__(kRowThreads, 4)
 void ctc_gradient_narrow_kernel(const TileArgs args, const Utt* __restrict__ meta, const int* __restrict__ labels,
                                 const float* __restrict__ emit_blank, const float* __restrict__ emit_label,
                                 const LatticeOut lat)
 {
     extern __shared__ uint4v tile_lds[];
     const int b = blockIdx.y;
-    narrow_tile<kTiles, false>(args, meta, labels, emit_blank, emit_label, lat, tile_lds, b, rotated_group(blockIdx.x, b, args.groups));
+    narrow_tile<kTiles, false, false, true>(args, meta, labels, emit_blank, emit_label, lat, tile_lds, b, rotated_group(blockIdx.x, b, args.groups));
 }
 
 // Larger alphabets: the softmax launch has written y (and zeros); here the columns of the label's symbols and the
@@ -3728,9 +3765,11 @@ __device__ __forceinline__ const FusedArgs& fused_args()
 
 // kLean: 128 registers, so that a compute unit holds two workgroups of more than four wavefronts and not one, while the blocks wait
 // that the chains have left behind: for up to 32 symbols (more would need a stack) and workgroups of that size (32 x 1500 frames,
-// labels of up to 540 symbols: 135.5 -> 131.0 us a call; up to four wavefronts 0.5 % slower so).
-template <Sync kSync, int kTiles, bool kLean>
-__global__ __launch_bounds__(64 * kFusedWaves, kLean ? 4 : 1)
+// labels of up to 540 symbols: 135.5 -> 131.0 us a call; up to four wavefronts 0.5 % slower so).  Launches of more chains than compute
+// units have it too, and no emissions in LDS (kStaged), so that four workgroups of up to four wavefronts share a compute unit: up to four
+// times as many chains as compute units start together.
+template <Sync kSync, int kTiles, bool kLean, bool kStaged>
+__global__ __launch_bounds__(64 * (kStaged ? kFusedWaves : kCrowdedFusedWaves), kLean ? 4 : 1)
 void ctc_lattice_gradient_kernel(const Utt* __restrict__ meta, const int* __restrict__ order,
                                  const int* __restrict__ labels, const float* __restrict__ emit_blank, const float* __restrict__ emit_label,
                                  const LatticeOut lat, double* __restrict__ mass, float* __restrict__ costs,
@@ -3748,7 +3787,7 @@ void ctc_lattice_gradient_kernel(const Utt* __restrict__ meta, const int* __rest
             __syncthreads();
             const FusedArgs& a = fused_args();
             const int tile = left - 1, rank = tile / a.tiles.groups, b = __builtin_amdgcn_readfirstlane(a.tiles.by_end[rank]);
-            narrow_tile<kTiles, true, kLean>(a.tiles, a.meta, a.labels, a.emit_blank, a.emit_label, a.lat, fused_lds, b,
+            narrow_tile<kTiles, true, kStaged, kLean>(a.tiles, a.meta, a.labels, a.emit_blank, a.emit_label, a.lat, fused_lds, b,
                                              rotated_group(tile - rank * a.tiles.groups, rank, a.tiles.groups));
             left = __builtin_amdgcn_readfirstlane(published(&a.tiles.left[tile]));
         } while (left != 0);
@@ -3760,7 +3799,7 @@ void ctc_lattice_gradient_kernel(const Utt* __restrict__ meta, const int* __rest
         if (threadIdx.x >= kRowThreads) return;          // (workgroups as large as the longest label's chains)
         const bool waits = (flags & kUttRuns) && group * (kRowThreads / 64 / sharing) <= frame_blocks(frames);     // (narrow_tile: rows, or the cost)
         if (waits && !chains_taken(tiles, b, tile)) return;
-        narrow_tile<kTiles, true, kLean>(tiles, meta, labels, emit_blank, emit_label, lat, fused_lds, b, group);
+        narrow_tile<kTiles, true, kStaged, kLean>(tiles, meta, labels, emit_blank, emit_label, lat, fused_lds, b, group);
     }
 }
 
@@ -3957,6 +3996,9 @@ int launch_softmax(const Launch& p, void* stream)
     });
 }
 
+// Narrow alphabets: do the gradient's workgroups hold their emissions in LDS (narrow_tile)?  Those that wait for their chains while
+// compute units are free do: it is time that they have.
+static bool staged_emissions(const Launch& p) { return p.fused && p.n_chains <= p.n_cu; }
 // The gradient's workgroups: what they get, how many there are (in args.groups per utterance) and their LDS.
 static TileArgs tile_args(const Launch& p, size_t* lds)
 {
@@ -3980,7 +4022,7 @@ static TileArgs tile_args(const Launch& p, size_t* lds)
     if (p.A <= kDirectMaxA) {
         g.share_blocks = static_cast<int64_t>(p.B) * blocks * label_pieces(p.max_label) <= kShareBlocksMost;
         if (g.share_blocks) per_group = kWaves / block_waves(p.max_label);
-        *lds = static_cast<size_t>(kWaves) * tile_lds_ints(p.max_label, p.A <= 32 ? 2 : 4) * 4;
+        *lds = static_cast<size_t>(kWaves) * tile_lds_ints(p.max_label, p.A <= 32 ? 2 : 4, staged_emissions(p)) * 4;
     } else {
         per_group = 1;
         g.waves = label_pieces(p.max_label) > 1 ? kWideWaves : 2;
@@ -4034,18 +4076,20 @@ int launch_lattice(const Launch& p, void* stream)
         wk.late_percent = p.late_percent;
         tiles.first_group = n_groups;
         const dim3 grid(n_groups + tiles.groups * p.B), block(64 * waves);
-#define CTC_LAUNCH_FUSED(SYNC, TILES, LEAN)                                                        \
-    hipLaunchKernelGGL((ctc_lattice_gradient_kernel<SYNC, TILES, LEAN>), grid, block, lds, s, meta, order, labels, emit_blank,   \
+#define CTC_LAUNCH_FUSED(SYNC, TILES, LEAN, STAGED)                                                \
+    hipLaunchKernelGGL((ctc_lattice_gradient_kernel<SYNC, TILES, LEAN, STAGED>), grid, block, lds, s, meta, order, labels, emit_blank,   \
                        emit_label, lat, mass, p.costs, chain_err, sink, wk, tiles)
-#define CTC_LAUNCH_FUSED_TILES(SYNC)                                                               \
+#define CTC_LAUNCH_FUSED_TILES(SYNC, LEAN, STAGED)                                                 \
     do {                                                                                           \
-        if (p.A <= 32) CTC_LAUNCH_FUSED(SYNC, 2, false);                                           \
-        else CTC_LAUNCH_FUSED(SYNC, 4, false);                                                     \
+        if (p.A <= 32) CTC_LAUNCH_FUSED(SYNC, 2, LEAN, STAGED);                                    \
+        else CTC_LAUNCH_FUSED(SYNC, 4, LEAN, STAGED);                                              \
     } while (0)
         return checked_launch([&] {
-            if (p.max_waves > kRowThreads / 64 && p.A <= 32) CTC_LAUNCH_FUSED(Sync::kHalo, 2, true);
-            else if (p.max_waves == 1) CTC_LAUNCH_FUSED_TILES(Sync::kNone);
-            else CTC_LAUNCH_FUSED_TILES(Sync::kHalo);
+            if (!staged_emissions(p) && p.max_waves == 1) CTC_LAUNCH_FUSED_TILES(Sync::kNone, true, false);
+            else if (!staged_emissions(p)) CTC_LAUNCH_FUSED_TILES(Sync::kHalo, true, false);
+            else if (p.max_waves > kRowThreads / 64 && p.A <= 32) CTC_LAUNCH_FUSED(Sync::kHalo, 2, true, true);
+            else if (p.max_waves == 1) CTC_LAUNCH_FUSED_TILES(Sync::kNone, false, true);
+            else CTC_LAUNCH_FUSED_TILES(Sync::kHalo, false, true);
         });
 #undef CTC_LAUNCH_FUSED_TILES
 #undef CTC_LAUNCH_FUSED

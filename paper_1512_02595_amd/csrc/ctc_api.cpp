@@ -475,10 +475,11 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
     if (out->fused && overlap < 0) {
         double last = 0, early = 0, late = 0;
         auto end_of = [&](int i) { return run_frames[i] * chain_us_per_frame(run_waves[i]); };
-        for (int i = 0; i < n_run; ++i) last = std::max(last, end_of(i));
-        for (int i = 0; i < n_run; ++i)
+        const int counted = beside_by_work(max_waves, n_run * dirs, out->n_cu) ? n_run : 0;
+        for (int i = 0; i < counted; ++i) last = std::max(last, end_of(i));
+        for (int i = 0; i < counted; ++i)
             (end_of(i) < 0.85 * last ? early : late) += static_cast<double>(frame_blocks(run_frames[i])) * std::max(1, label_pieces(meta[running[i]].L));
-        out->fused = gradient_in_lattice_launch(early, late, last, max_waves, n_run * dirs, out->n_cu);
+        out->fused = gradient_in_lattice_launch(early, late, last, max_frames, max_waves, n_run * dirs, out->n_cu);
     }
     out->fused = out->fused && overlap != 0;
     out->folded = c.A <= kDirectMaxA && c.B <= kNarrowMaxB && c.T < (1 << 29);
@@ -663,7 +664,7 @@ ctc_status_t run_device(const void* x, const int32_t* labels, const int32_t* lab
         const double blocks = static_cast<double>(B) * frame_blocks(T);
         const double late = 0.14 * blocks * std::max(1, label_pieces(max_label * 3 / 4)), all = 0.5 * blocks * std::max(1, label_pieces(max_label / 2));
         p.fused = gradient_in_lattice_launch(std::max(all - late, 0.0), late, T * chain_us_per_frame(all_plans.latency_waves[max_label]),
-                                             p.max_waves, p.n_chains, p.n_cu);
+                                             T, p.max_waves, p.n_chains, p.n_cu);
     }
     // Narrow alphabets: the softmax launch builds the records itself (no planning launch before it); every
     // utterance's setup workgroup weighs all B utterances for the run order, which is worth it up to here.

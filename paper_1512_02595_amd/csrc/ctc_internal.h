@@ -298,11 +298,14 @@ inline double chain_us_per_frame(int waves) { return waves == 1 ? 0.045 : (waves
 // in the mean 0.95; seven others 0.87 to 1.08, 1.01).
 // Chains of up to 100 frames keep to the launch apart: blocks that wait for them are most of such a launch (22 batches: 0.91 to 1.11, in the
 // mean 0.98).
-constexpr double kCrowdedBesideUs = 4.5;
-inline bool gradient_in_lattice_launch(double early, double late, double chain_us, int max_waves, int n_chains, int n_cu)
+constexpr int kCrowdedBesideFrames = 100;
+// Does the answer depend on `early`, `late` and `chain_us`?  (Adding them up takes the host a microsecond for 512 utterances.)
+inline bool beside_by_work(int max_waves, int n_chains, int n_cu) { return max_waves > (n_chains > n_cu ? 4 : 8); }
+inline bool gradient_in_lattice_launch(double early, double late, double chain_us, int max_frames, int max_waves, int n_chains, int n_cu)
 {
-    if (n_chains > n_cu) return chain_us >= kCrowdedBesideUs && (max_waves <= 4 ? n_chains <= 4 * n_cu : 4 * n_chains <= 11 * n_cu && late <= early);
-    return max_waves <= 8 || gradient_beside_chains(early, late, chain_us, max_waves, n_chains, n_cu);
+    if (n_chains > n_cu)
+        return max_frames > kCrowdedBesideFrames && (beside_by_work(max_waves, n_chains, n_cu) ? 4 * n_chains <= 11 * n_cu && late <= early : n_chains <= 4 * n_cu);
+    return !beside_by_work(max_waves, n_chains, n_cu) || gradient_beside_chains(early, late, chain_us, max_waves, n_chains, n_cu);
 }
 
 constexpr int kDoneStride = 16;      // words between two utterances' words: a line each for those who poll

@@ -3507,15 +3507,15 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
 __device__ __forceinline__ int rotated_group(int within, int utterance, int groups) { return (within + utterance) % groups; }
 
 // grid (workgroups per utterance, B)
-template <int kTiles>
-__global__ __launch_bounds__(kRowThreads, 4)
+template <int kTiles, bool kStaged>
+__global__ __launch_bounds__(kRowThreads, kStaged ? 1 : 4)
 void ctc_gradient_narrow_kernel(const TileArgs args, const Utt* __restrict__ meta, const int* __restrict__ labels,
                                 const float* __restrict__ emit_blank, const float* __restrict__ emit_label,
                                 const LatticeOut lat)
 {
     extern __shared__ uint4v tile_lds[];
     const int b = blockIdx.y;
-    narrow_tile<kTiles, false, false, true>(args, meta, labels, emit_blank, emit_label, lat, tile_lds, b, rotated_group(blockIdx.x, b, args.groups));
+    narrow_tile<kTiles, false, kStaged, !kStaged>(args, meta, labels, emit_blank, emit_label, lat, tile_lds, b, rotated_group(blockIdx.x, b, args.groups));
 }
 
 // Larger alphabets: the softmax launch has written y (and zeros); here the columns of the label's symbols and the
@@ -3996,9 +3996,15 @@ int launch_softmax(const Launch& p, void* stream)
     });
 }
 
+// Narrow alphabets: do several wavefronts share a block?
+static bool shares_blocks(const Launch& p)
+{
+    return static_cast<int64_t>(p.B) * frame_blocks(p.T) * label_pieces(p.max_label) <= kShareBlocksMost;
+}
 // Narrow alphabets: do the gradient's workgroups hold their emissions in LDS (narrow_tile)?  Those that wait for their chains while
-// compute units are free do: it is time that they have.
-static bool staged_emissions(const Launch& p) { return p.fused && p.n_chains <= p.n_cu; }
+// compute units are free do: it is time that they have.  And in launches of their own those of few blocks, which last as long as a block
+// takes (300 x 60 x 29 24.9 us a call, from the cache 25.7; 512 x 45 x 29 27.8 and 29.1).
+static bool staged_emissions(const Launch& p) { return p.fused ? p.n_chains <= p.n_cu : shares_blocks(p); }
 // The gradient's workgroups: what they get, how many there are (in args.groups per utterance) and their LDS.
 static TileArgs tile_args(const Launch& p, size_t* lds)
 {
@@ -4020,7 +4026,7 @@ static TileArgs tile_args(const Launch& p, size_t* lds)
     const int blocks = frame_blocks(p.T);
     int per_group = kWaves;
     if (p.A <= kDirectMaxA) {
-        g.share_blocks = static_cast<int64_t>(p.B) * blocks * label_pieces(p.max_label) <= kShareBlocksMost;
+        g.share_blocks = shares_blocks(p);
         if (g.share_blocks) per_group = kWaves / block_waves(p.max_label);
         *lds = static_cast<size_t>(kWaves) * tile_lds_ints(p.max_label, p.A <= 32 ? 2 : 4, staged_emissions(p)) * 4;
     } else {
@@ -4149,6 +4155,13 @@ int launch_gradient(const Launch& p, void* stream)
         // (a workgroup to a compute unit; twice and four times as many 0.5 % slower)
         fill = FillArgs{p.grads, p.dtype == CTC_DTYPE_F32 ? 4 : 2, p.T, p.B, p.A, p.defer, p.defer_columns, p.n_cu, p.n_chains, std::max(1, p.n_cu / p.B)};
     }
+#define CTC_LAUNCH_NARROW(STAGED)                                                                  \
+    do {                                                                                           \
+        if (p.A <= 32)                                                                             \
+            hipLaunchKernelGGL((ctc_gradient_narrow_kernel<2, STAGED>), grid, block, lds, s, args, meta, p.labels, emit_blank, emit_label, lattice_blocks(p)); \
+        else                                                                                       \
+            hipLaunchKernelGGL((ctc_gradient_narrow_kernel<4, STAGED>), grid, block, lds, s, args, meta, p.labels, emit_blank, emit_label, lattice_blocks(p)); \
+    } while (0)
     const WideRows rows = wide_rows(args.groups + fill.rounds);
     const dim3 grid = p.A > kDirectMaxA ? dim3(p.B, rows.y, rows.z) : dim3(args.groups, p.B), block(p.A > kDirectMaxA ? 64 * args.waves : kRowThreads);
     return checked_launch([&] {
@@ -4158,13 +4171,10 @@ int launch_gradient(const Launch& p, void* stream)
         else if (p.A > kDirectMaxA)
             hipLaunchKernelGGL(ctc_gradient_wide_kernel<false>, grid, block, lds, s, args, meta, p.labels, emit_blank, emit_label,
                                lattice_blocks(p), fill);
-        else if (p.A <= 32)
-            hipLaunchKernelGGL(ctc_gradient_narrow_kernel<2>, grid, block, lds, s, args, meta, p.labels, emit_blank, emit_label,
-                               lattice_blocks(p));
-        else
-            hipLaunchKernelGGL(ctc_gradient_narrow_kernel<4>, grid, block, lds, s, args, meta, p.labels, emit_blank, emit_label,
-                               lattice_blocks(p));
+        else if (staged_emissions(p)) CTC_LAUNCH_NARROW(true);
+        else CTC_LAUNCH_NARROW(false);
     });
+#undef CTC_LAUNCH_NARROW
 }
 
 }  // namespace ctc

@@ -3527,9 +3527,11 @@ void ctc_gradient_narrow_kernel(const TileArgs args, const Utt* __restrict__ met
 // What bounds it: in launches of up to a block per SIMD (64 utterances of 500 frames: 1140) the time of the slowest block, beyond
 // that the issue of the recomputation.  With a wavefront to a block a block took 7 to 25 us (loads 2, a piece 4.5, sums 1 to 10),
 // and 171 registers left room for three wavefronts on a SIMD.  Two wavefronts share the sums, four the pieces too; a piece's
-// operands have one set of registers, whichever piece it is (101: five wavefronts), and take 2.9 us.  64 x 500 frames, 750
+// operands have one set of registers, whichever piece it is, and take 2.9 us.  64 x 500 frames, 750
 // symbols: 89.3 -> 82.7 us a call; 512 x 500, 300 symbols: 397 -> 346; 400 x 500, 80 symbols: 303 -> 260; 32 x 1400, labels of up to
-// 500 symbols: 288 -> 248.  Labels of one piece take two wavefronts (64 x 500, 6000 symbols, bf16: 161.0 us; with four 162.7).
+// 500 symbols: 288 -> 248.  Registers are for five wavefronts on a SIMD (91; at 101, four, labels of up to 175 symbols needed a second round of
+// workgroups): 64 x 500, 750 symbols 76.1 -> 74.3; 400 x 500, 80 symbols 158.0 -> 149.7; 128 x 400, 3000 symbols bf16 152.6 -> 150.9.
+// Labels of one piece take two wavefronts (64 x 500, 6000 symbols, bf16: 161.0 us; with four 162.7).
 // Neighbouring workgroups are different utterances, one further on from block to block to each: a compute unit gets every n-th
 // workgroup, and with an utterance's blocks side by side some got first blocks only and others the last ones, which many utterances
 // do not have (one wavefront per block, 512 x 500 frames: 397 us, so 364).
@@ -3609,18 +3611,14 @@ void ctc_gradient_wide_kernel(const TileArgs g, const Utt* __restrict__ meta, co
             };
             if (domain == kDomainLog) block_shares_log<0, 2>(m, lat, packed_inverse_p, block, i * kPieceStep, own_first, own_end, file);
             else {
-                // (the first chunk's are read once more when the second's have been taken: 16 registers)
-                auto emissions = [&](int k, float (&el0)[kChunk], float (&el1)[kChunk]) {
+                // (the first chunk's are read once more when they are needed again: a trip to the cache, and 16 registers)
+                auto emissions = [&](int k, float (&el0)[kChunk], float (&el1)[kChunk]) __attribute__((always_inline)) {
                     auto get = [](const ChunkEmissions& e, float (&el)[kChunk]) {
                         el[0] = e.v0.x; el[1] = e.v0.y; el[2] = e.v0.z; el[3] = e.v0.w;
                         el[4] = e.v1.x; el[5] = e.v1.y; el[6] = e.v1.z; el[7] = e.v1.w;
                     };
-                    get(k == 0 ? emit00 : emit01, el0);
-                    get(k == 0 ? emit10 : emit11, el1);
-                    if (k == 1) {
-                        emit01 = chunk_emissions(at.has0, at.p0, 0);
-                        emit11 = chunk_emissions(at.has1, at.p1, 0);
-                    }
+                    get(k == 0 ? emit00 : k == 1 ? emit01 : chunk_emissions(at.has0, at.p0, 0), el0);
+                    get(k == 0 ? emit10 : k == 1 ? emit11 : chunk_emissions(at.has1, at.p1, 0), el1);
                 };
                 block_shares<0>(m, at, ends, packed_inverse_p, domain == kDomainSteep, block, own_first, own_end, s_alpha,
                                 s_alpha + kBlockFrames * kShareRow, emissions, file);

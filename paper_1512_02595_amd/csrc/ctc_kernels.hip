@@ -517,7 +517,7 @@ __device__ __forceinline__ void raise_flags(Utt* meta, int b, const Utt& m, floa
 // launch, whose compute units without a chain have nothing else to do (fill_rows).
 
 // kLanes lanes (16, a wavefront or the workgroup) hold a row of up to kPerLane kLanes symbols in registers between the
-// maximum and the sum (kPerLane: 16, or 32 where that is not enough): it is read once, with 16-byte loads, and written with 16-byte stores.  A row that starts off a 16-byte
+// maximum and the sum (kPerLane: the fewest that suffice, see row_lanes): it is read once, with 16-byte loads, and written with 16-byte stores.  A row that starts off a 16-byte
 // boundary (an alphabet size that is no multiple of the vector, or a tensor that starts off one) has up to N - 1 symbols
 // before its first whole vector and as many after its last; a lane takes one of them each.  Where the gradient starts at
 // another place within 16 bytes than the activations, the vectors read are written element by element (750 symbols, f32:
@@ -3811,6 +3811,11 @@ int checked_launch(F&& f)
 }  // namespace
 
 namespace {
+// Symbols to a lane of ctc_softmax_rows_kernel: 16, 24 or 32, and 12 where a wavefront has fp32 rows of up to 768 symbols.  Vectors
+// behind a row's end are asked for all the same and cost their instructions (with 16 and 32 alone 27 x 333 x 4733 bf16 44.3 us a call, so
+// 43.4, fp32 67.3 and 67.0; 64 x 500 x 6000 247.8 and 246.5, bf16 138.2 and 137.6; 64 x 500 x 750 74.3 and 73.9).
+template <typename T, int kLanes>
+constexpr int kFewest = kLanes == 64 && sizeof(T) == 4 ? 12 : 16;
 // Lanes per row of ctc_softmax_rows_kernel; 0 where it does not apply: rows of more than 8192 symbols, more workgroups than a
 // grid holds.
 int row_lanes(const Launch& p)
@@ -3955,30 +3960,31 @@ int launch_softmax(const Launch& p, void* stream)
                                    emit_blank, emit_label, sa, p.B, p.A, p.blank);
         } else if (row_lanes(p) > 0) {
             const int lanes = row_lanes(p);
-            const bool half = p.A <= 16 * lanes;
             const RowPlan plan = row_plan(p, lanes);
             const dim3 grid(plan.groups + sa.parts * p.B);
 #define CTC_LAUNCH_ROWS_FROM(TYPE, LANES, PER_LANE, STREAMING)                                     \
     hipLaunchKernelGGL((ctc_softmax_rows_kernel<TYPE, LANES, PER_LANE, STREAMING>), grid, block, 0, s, \
                        static_cast<const TYPE*>(p.x), static_cast<TYPE*>(p.grads), meta, labels,   \
                        emit_blank, emit_label, sa, p.T, p.B, p.A, p.blank, plan, p.defer + p.defer_columns)
-#define CTC_LAUNCH_ROWS(TYPE, LANES, PER_LANE) CTC_LAUNCH_ROWS_FROM(TYPE, LANES, PER_LANE, false)
+#define CTC_LAUNCH_ROWS_OF_LANES(TYPE, LANES, STREAMING)                                           \
+    do {                                                                                           \
+        if (p.A <= LANES * (kFewest<TYPE, LANES>)) CTC_LAUNCH_ROWS_FROM(TYPE, LANES, (kFewest<TYPE, LANES>), STREAMING); \
+        else if (p.A <= LANES * 16) CTC_LAUNCH_ROWS_FROM(TYPE, LANES, 16, STREAMING);              \
+        else if (p.A <= LANES * 24) CTC_LAUNCH_ROWS_FROM(TYPE, LANES, 24, STREAMING);              \
+        else CTC_LAUNCH_ROWS_FROM(TYPE, LANES, 32, STREAMING);                                     \
+    } while (0)
 #define CTC_LAUNCH_ROWS_OF(TYPE)                                                                   \
     do {                                                                                           \
-        if (lanes == 16 && half) CTC_LAUNCH_ROWS(TYPE, 16, 16);                                    \
-        else if (lanes == 16) CTC_LAUNCH_ROWS(TYPE, 16, 32);                                       \
-        else if (lanes == 64 && half) CTC_LAUNCH_ROWS(TYPE, 64, 16);                               \
-        else if (lanes == 64) CTC_LAUNCH_ROWS(TYPE, 64, 32);                                       \
-        else if (half) CTC_LAUNCH_ROWS(TYPE, kRowThreads, 16);                                     \
-        else CTC_LAUNCH_ROWS(TYPE, kRowThreads, 32);                                               \
+        if (lanes == 16) CTC_LAUNCH_ROWS_OF_LANES(TYPE, 16, false);                                \
+        else if (lanes == 64) CTC_LAUNCH_ROWS_OF_LANES(TYPE, 64, false);                           \
+        else CTC_LAUNCH_ROWS_OF_LANES(TYPE, kRowThreads, false);                                   \
     } while (0)
             if (streamed_rows(p, lanes)) {
-                if (half) CTC_LAUNCH_ROWS_FROM(float, kRowThreads, 16, true);
-                else CTC_LAUNCH_ROWS_FROM(float, kRowThreads, 32, true);
+                CTC_LAUNCH_ROWS_OF_LANES(float, kRowThreads, true);
             } else if (f32) CTC_LAUNCH_ROWS_OF(float);
             else CTC_LAUNCH_ROWS_OF(bf16_t);
 #undef CTC_LAUNCH_ROWS_OF
-#undef CTC_LAUNCH_ROWS
+#undef CTC_LAUNCH_ROWS_OF_LANES
 #undef CTC_LAUNCH_ROWS_FROM
         } else {
             const dim3 grid(p.T + 1, p.B);

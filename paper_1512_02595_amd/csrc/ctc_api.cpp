@@ -469,7 +469,7 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
         out->defer_columns = columns_frames(static_cast<double>(rows) * c.A * elem, c.A, out->defer);
     }
     out->fused = c.mode == Mode::kGrad && !needs_barrier && !sequential_chains && n_run > 0 &&
-                 can_fuse_gradient(c.A, max_waves, n_run * dirs, out->n_cu);
+                 can_fuse_gradient(c.A, max_waves, n_run * dirs, out->n_cu, c.T, c.B);
     const int overlap = g_overlap.load(std::memory_order_relaxed);
     out->late_percent = overlap <= 100 ? std::max(overlap, 0) : 0;
     if (out->fused && overlap < 0) {
@@ -658,7 +658,7 @@ ctc_status_t run_device(const void* x, const int32_t* labels, const int32_t* lab
     p.defer_columns = grads && A > kDirectMaxA && !p.needs_barrier ? columns_frames(static_cast<double>(T) * B * A * elem / 3, A, p.defer) : 0;
     const int overlap = g_overlap.load(std::memory_order_relaxed);
     p.late_percent = overlap <= 100 ? std::max(overlap, 0) : 0;
-    p.fused = grads && !p.needs_barrier && overlap != 0 && can_fuse_gradient(A, p.max_waves, p.n_chains, p.n_cu);
+    p.fused = grads && !p.needs_barrier && overlap != 0 && can_fuse_gradient(A, p.max_waves, p.n_chains, p.n_cu, T, B);
     if (p.fused && overlap < 0) {
         // (lengths spread evenly up to the bounds, as above: one utterance in seven ends late, half the frames are frames)
         const double blocks = static_cast<double>(B) * frame_blocks(T);

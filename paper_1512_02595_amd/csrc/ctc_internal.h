@@ -263,9 +263,17 @@ CTC_HOST_DEVICE constexpr int label_pieces(int L)
 // 1500 frames (540 symbols: 169.4 us apart, 157.6 beside).
 constexpr int kFusedWaves = 12;
 constexpr int kCrowdedFusedWaves = 8;    // ... where there are more chains than compute units
-constexpr bool can_fuse_gradient(int A, int max_waves, int n_chains, int n_cu)
+// The workgroups of that launch, all in the grid's first dimension, have fewer than 2^32 threads together; a gradient launch of its own has
+// the utterances in the second.  (At worst a workgroup to a block of frames and one more to an utterance: from 512 utterances of 524 000 frames on,
+// with labels of up to four wavefronts, the launches are apart.)
+constexpr bool fused_grid_fits(int T, int B, int max_waves, int n_chains)
 {
-    return A <= kDirectMaxA && max_waves <= (n_chains <= n_cu ? kFusedWaves : kCrowdedFusedWaves);
+    const int64_t workgroups = n_chains + (static_cast<int64_t>(T) / kBlockFrames + 2) * B;
+    return workgroups * 64 * std::max(max_waves, 4) < int64_t(1) << 32;
+}
+constexpr bool can_fuse_gradient(int A, int max_waves, int n_chains, int n_cu, int T, int B)
+{
+    return A <= kDirectMaxA && max_waves <= (n_chains <= n_cu ? kFusedWaves : kCrowdedFusedWaves) && fused_grid_fits(T, B, max_waves, n_chains);
 }
 // Whether that pays.  Beside the chains, the compute units without one write the gradient of the utterances that end before the
 // longest (`early`; `late`: whose chains end in the last 15 % of the time) and a launch boundary is saved.  But what is left at

@@ -50,3 +50,33 @@ def test_more_late_work_never_favours_the_chains_launch(rule):
         for chains in (2, 100, 256):
             forms = [rule(1000, late, 40, waves, chains) for late in range(0, 20000, 500)]
             assert forms == sorted(forms, reverse=True)
+
+
+GRID_PROGRAM = r"""
+#include "ctc_internal.h"
+#include <cstdio>
+int main()
+{
+    int T, B, waves, chains;
+    while (std::scanf("%d %d %d %d", &T, &B, &waves, &chains) == 4)
+        std::printf("%d\n", ctc::can_fuse_gradient(2, waves, chains, 256, T, B));
+}
+"""
+
+
+# Forms by the size of the grid alone: at worst a workgroup of 64 max(waves, 4) threads to a block of 16 frames, and one more.
+@pytest.mark.parametrize("T,B,waves,chains,beside", [
+    (750, 512, 1, 1024, True),
+    (2_100_000, 512, 1, 1024, False),           # (67 million workgroups of 256 threads)
+    (1_500_000, 352, 5, 704, False),            # (33 million of 320)
+    (500_000, 512, 4, 1024, True),
+    (2**31 - 1, 1, 4, 2, False),
+])
+def test_launches_beside_the_chains_fit_a_grid(tmp_path, T, B, waves, chains, beside):
+    (tmp_path / "grid.cpp").write_text(GRID_PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_1512_02595_amd", "csrc"),
+                    str(tmp_path / "grid.cpp"), "-o", str(tmp_path / "grid")], check=True)
+    out = subprocess.run([str(tmp_path / "grid")], input=f"{T} {B} {waves} {chains}", capture_output=True, text=True, check=True).stdout
+    assert (out == "1\n") == beside
+    if beside:
+        assert (T // 16 + 2) * B * 64 * max(waves, 4) < 2**32

@@ -275,29 +275,24 @@ constexpr bool can_fuse_gradient(int A, int max_waves, int n_chains, int n_cu, i
 {
     return A <= kDirectMaxA && max_waves <= (n_chains <= n_cu ? kFusedWaves : kCrowdedFusedWaves) && fused_grid_fits(T, B, max_waves, n_chains);
 }
-// Whether that pays.  Beside the chains, the compute units without one write the gradient of the utterances that end before the
-// longest (`early`; `late`: whose chains end in the last 15 % of the time) and a launch boundary is saved.  But what is left at
-// the end is written by fewer workgroups at a time than in a launch of its own, since they are as large as the chains' ones:
-// three to a compute unit with four wavefronts, two with up to eight, one with more.  `early` and `late` are blocks of frames
+// Whether that pays where a chain has more than eight wavefronts and a compute unit of its own.  Beside the chains, the compute units without one write
+// the gradient of the utterances that end before the longest (`early`; `late`: whose chains end in the last 15 % of the time) and a launch boundary is
+// saved.  But what is left at the end is written by fewer workgroups at a time than in a launch of its own, since they are as large as the chains' ones:
+// one or two to a compute unit.  `early` and `late` are blocks of frames
 // times pieces of the label, a third of a microsecond on the whole chip for every compute unit; `chain_us`: the longest chain.
-// Fitted to 692 batches (1 to 128 utterances of 50 to 1500 frames, labels of 12 to 660 symbols, frames spread from 10 to 100 %
-// of the longest up to it).  Against the better of the two forms: always beside takes 3.3 % more on average and 59 % at worst
-// (128 utterances of 1275 to 1500 frames, labels of 400 to 660 symbols: 468 us, apart 294), always apart 2.9 and 17.5 %, this
-// rule 0.6 and 17.5 % (64 utterances of 300 to 1500 frames, labels of 360 to 600: 182 us apart, 155 beside).
-inline bool gradient_beside_chains(double early, double late, double chain_us, int max_waves, int n_chains, int n_cu)
+// Fitted, before the chains' checkpoints went past the caches, to batches of 32 to 128 utterances with labels of up to 660 symbols: 128
+// utterances of 1275 to 1500 frames, labels of 400 to 660, 294 us a call apart and 468 beside; 64 of 300 to 1500, labels of 360 to 600, 182 and 155; 32 of
+// 1500 frames, labels of up to 540, 169.6 and 157.6.
+inline bool gradient_beside_long_chains(double early, double late, double chain_us, int n_chains, int n_cu)
 {
     const double busy = static_cast<double>(n_chains) / n_cu, saved = std::min(std::max(chain_us / 8, 2.0), 10.0);
-    early /= n_cu;
-    late /= n_cu;
-    return max_waves > 8 ? 1.5 * late + 18.0 * busy <= saved + 0.4 * early * (1.0 - busy)
-                         : late + 3.0 * busy <= saved + 0.7 * early * (1.0 - 0.4 * busy);
+    return 1.5 * late / n_cu + 18.0 * busy <= saved + 0.4 * early / n_cu * (1.0 - busy);
 }
 // What a chain of this many wavefronts took for a frame, in microseconds, when the rule above was fitted (up to four run on a SIMD each).
 // The steps of a linear-domain chain take about half of that now, 0.018, 0.024 to 0.035 and 0.043; the rule divides by these.
 inline double chain_us_per_frame(int waves) { return waves == 1 ? 0.045 : (waves <= 4 ? 0.06 : 0.088); }
 
-// The rule that launches follow.  The one above was fitted before the chains' checkpoints went past the caches, when a chain's end held up
-// the others on its die; of it, launches of more than eight wavefronts are left.  Random batches, three of a kind in turn:
+// The rule that launches follow.  Random batches, three of a kind in turn:
 // Up to a chain per compute unit, up to eight wavefronts: beside (87 batches: 0.79 to 0.97 of the time apart; 128 x 454 x 29 36.3 us a
 // call apart, 32.3 beside; 64 x 750 x 60, lengths from 600 on, 72.0 and 65.4).
 // More chains than compute units, up to four wavefronts: beside while all of them start together, four workgroups to a compute unit (51 batches: 0.83 to
@@ -313,7 +308,7 @@ inline bool gradient_in_lattice_launch(double early, double late, double chain_u
 {
     if (n_chains > n_cu)
         return max_frames > kCrowdedBesideFrames && (beside_by_work(max_waves, n_chains, n_cu) ? 4 * n_chains <= 11 * n_cu && late <= early : n_chains <= 4 * n_cu);
-    return !beside_by_work(max_waves, n_chains, n_cu) || gradient_beside_chains(early, late, chain_us, max_waves, n_chains, n_cu);
+    return !beside_by_work(max_waves, n_chains, n_cu) || gradient_beside_long_chains(early, late, chain_us, n_chains, n_cu);
 }
 
 constexpr int kDoneStride = 16;      // words between two utterances' words: a line each for those who poll

@@ -357,10 +357,10 @@ void ctc_debug_set_poll_budget(int polls);
 void ctc_debug_set_end_polls(int polls);
 
 /*
- * Diagnostics.  Where a call's recursions leave compute units idle (no more chains, two per utterance,
- * than compute units; alphabets of at most 64 symbols; labels of no more than twelve wavefronts), the
+ * Diagnostics.  For alphabets of at most 64 symbols the
  * gradient may be written inside the recursions' launch, by workgroups that each wait for the two chains of
- * their utterance; it is where the batch's lengths make that the quicker form.  `percent`: 0 gives the gradient
+ * their utterance (labels of no more than twelve wavefronts where there is a compute unit for every chain, two per utterance, of
+ * no more than eight beyond that; fewer than 2^32 threads in all); it is where the batch's shape makes that the quicker form.  `percent`: 0 gives the gradient
  * a launch of its own after the recursions' for calls made afterwards, process-wide; 1..100 writes it beside the
  * recursions wherever that can be done, and makes about that share of the recursions' workgroups come late, so that
  * workgroups that wait for them leave their work to them, as they do when another launch keeps those from a compute

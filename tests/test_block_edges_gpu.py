@@ -36,10 +36,23 @@ def test_labels_around_pieces(A):
     pc.check(batch_of([2 * n + 40 for n in labels], labels, A))
 
 
+@pytest.fixture(params=[0, 101], ids=["apart", "beside"])
+def form(request):
+    """The gradient in a launch of its own, and beside the chains."""
+    ctc.debug_set_overlap(request.param)
+    yield request.param
+    ctc.debug_set_overlap(-1)
+
+
 @pytest.mark.parametrize("A", [29, 40])
-def test_blocks_of_many_utterances_are_not_shared(A):
+def test_blocks_of_many_utterances_are_not_shared(A, form):
     """Enough blocks times pieces for every wavefront to take a whole block of its own."""
     pc.check(batch_of([560, 530], [230, 129], A, copies=64, sigma=1.0))
+
+
+@pytest.mark.parametrize("A", [29, 40])
+def test_log_domain_blocks_of_many_utterances_are_not_shared(A, form):
+    pc.check(batch_of([560, 530], [230, 129], A, copies=64, sigma=60.0))
 
 
 @pytest.mark.parametrize("A", [29, 90])
@@ -47,8 +60,8 @@ def test_longest_labels_and_bf16(A):
     pc.check(batch_of([1500, 1130], [600, 1023 if A > 64 else 900], A, sigma=1.0), ctc.DTYPE_BF16)
 
 
-@pytest.mark.parametrize("A,copies", [(29, 1), (64, 1), (90, 1), (40, 12)])     # beside the chains, in launches of their own
-def test_log_domain_around_blocks_and_pieces(A, copies):
+@pytest.mark.parametrize("A,copies", [(29, 1), (64, 1), (90, 1), (40, 12)])     # (12: more chains than compute units)
+def test_log_domain_around_blocks_and_pieces(A, copies, form):
     """Logits so steep that every utterance has emissions below the linear domain's range."""
     frames = [1, 15, 16, 17, 33, 150, 300, 290, 480, 470, 700]
     labels = [1, 2, 0, 5, 9, 63, 127, 128, 223, 225, 321]

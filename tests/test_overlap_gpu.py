@@ -1,5 +1,5 @@
-"""GPU tests of the gradient rows written inside the lattice launch (launches that leave compute
-units idle: few utterances, alphabets of at most 64 symbols).  Whatever share of the utterances the
+"""GPU tests of the gradient rows written inside the lattice launch (alphabets of at most 64 symbols; here launches that leave
+compute units idle, test_crowded_beside_gpu has the others).  Whatever share of the utterances the
 launch's workers take (none, some, all), costs and gradients are bitwise the same, and they match
 the CPU oracle to the usual tolerances."""
 import numpy as np
@@ -31,7 +31,7 @@ def run_with(batch, dtype, percent):
     (lambda: wl.make_random(4, T=300, B=7, A=5, max_label=290, min_input=250, feasible_only=True), ctc.DTYPE_F32),
     (lambda: wl.make_random(81, T=120, B=6, A=7, max_label=40, min_input=90, sigma=60.0, feasible_only=True), ctc.DTYPE_F32),  # log domain
     (lambda: wl.make_random(17, T=50, B=4, A=29, max_label=0), ctc.DTYPE_F32),                  # empty labels
-    (lambda: wl.make_random(33, T=90, B=100, A=20, max_label=30, min_input=10), ctc.DTYPE_F32), # 200 chains: just under the limit
+    (lambda: wl.make_random(33, T=90, B=100, A=20, max_label=30, min_input=10), ctc.DTYPE_F32), # up to 200 chains
 ])
 def test_same_results_whatever_the_workers_share(maker, dtype):
     batch = maker()

@@ -3811,11 +3811,12 @@ int checked_launch(F&& f)
 }  // namespace
 
 namespace {
-// Symbols to a lane of ctc_softmax_rows_kernel: 16, 24 or 32, and 12 where a wavefront has fp32 rows of up to 768 symbols.  Vectors
-// behind a row's end are asked for all the same and cost their instructions (with 16 and 32 alone 27 x 333 x 4733 bf16 44.3 us a call, so
-// 43.4, fp32 67.3 and 67.0; 64 x 500 x 6000 247.8 and 246.5, bf16 138.2 and 137.6; 64 x 500 x 750 74.3 and 73.9).
-template <typename T, int kLanes>
-constexpr int kFewest = kLanes == 64 && sizeof(T) == 4 ? 12 : 16;
+// Symbols to a lane of ctc_softmax_rows_kernel: 12 (fp32: three vectors; bf16 vectors have eight symbols), 16, 24 or 32.  Vectors
+// behind a row's end are asked for all the same and cost their instructions.  With 16 and 32 alone 27 x 333 x 4733 bf16 44.3 us a call, so
+// 43.4, fp32 67.3 and 67.0; 64 x 500 x 6000 247.8 and 246.5, bf16 138.2 and 137.6.  With 16 in place of 12, fp32, 64 x 500 frames: 100 symbols 52.0, so 51.9; 600
+// 65.5 and 65.2; 750 72.6 and 72.1; 2100 125.1 and 123.4; 2500 134.4 and 132.8; 3000 148.4 and 148.0.
+template <typename T>
+constexpr int kFewest = sizeof(T) == 4 ? 12 : 16;
 // Lanes per row of ctc_softmax_rows_kernel; 0 where it does not apply: rows of more than 8192 symbols, more workgroups than a
 // grid holds.
 int row_lanes(const Launch& p)
@@ -3968,7 +3969,7 @@ int launch_softmax(const Launch& p, void* stream)
                        emit_blank, emit_label, sa, p.T, p.B, p.A, p.blank, plan, p.defer + p.defer_columns)
 #define CTC_LAUNCH_ROWS_OF_LANES(TYPE, LANES, STREAMING)                                           \
     do {                                                                                           \
-        if (p.A <= LANES * (kFewest<TYPE, LANES>)) CTC_LAUNCH_ROWS_FROM(TYPE, LANES, (kFewest<TYPE, LANES>), STREAMING); \
+        if (p.A <= LANES * kFewest<TYPE>) CTC_LAUNCH_ROWS_FROM(TYPE, LANES, kFewest<TYPE>, STREAMING);     \
         else if (p.A <= LANES * 16) CTC_LAUNCH_ROWS_FROM(TYPE, LANES, 16, STREAMING);              \
         else if (p.A <= LANES * 24) CTC_LAUNCH_ROWS_FROM(TYPE, LANES, 24, STREAMING);              \
         else CTC_LAUNCH_ROWS_FROM(TYPE, LANES, 32, STREAMING);                                     \

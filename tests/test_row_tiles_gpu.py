@@ -54,7 +54,7 @@ def test_runs_of_whole_rows(T, B):
 
 
 # 512 million bytes: 160 frames of 100 utterances of 8000 symbols
-@pytest.mark.parametrize("T,B,A", [(160, 100, 8000), (161, 199, 4000), (159, 100, 8000)])
+@pytest.mark.parametrize("T,B,A", [(160, 100, 8000), (161, 199, 4000), (159, 100, 8000), (210, 200, 3072)])
 def test_rows_past_the_caches(T, B, A):
     softmax_of_rows(T, B, A, A)
 

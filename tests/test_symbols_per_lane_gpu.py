@@ -11,7 +11,7 @@ from test_row_vectors_gpu import check_off_boundary
 
 pytestmark = pytest.mark.gpu
 
-SIZES = [383, 384, 385, 767, 768, 769, 1535, 1536, 1537, 6143, 6144, 6145]
+SIZES = [191, 192, 193, 383, 384, 385, 767, 768, 769, 1535, 1536, 1537, 3071, 3072, 3073, 6143, 6144, 6145]
 
 
 @pytest.mark.parametrize("dtype", [ctc.DTYPE_F32, ctc.DTYPE_BF16])
@@ -21,7 +21,7 @@ def test_rows_around_symbols_per_lane(A, dtype):
 
 
 @pytest.mark.parametrize("dtype,torch_dtype", [(ctc.DTYPE_F32, torch.float32), (ctc.DTYPE_BF16, torch.bfloat16)])
-@pytest.mark.parametrize("A", [384, 768, 1536, 6144])
+@pytest.mark.parametrize("A", [192, 384, 768, 1536, 3072, 6144])
 @pytest.mark.parametrize("x_at,g_at", [(0, 0), (1, 0), (3, 6)])
 def test_full_rows_off_a_boundary(A, dtype, torch_dtype, x_at, g_at):
     check_off_boundary(A, dtype, torch_dtype, x_at, g_at)

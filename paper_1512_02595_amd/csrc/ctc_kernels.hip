@@ -2775,8 +2775,10 @@ void ctc_backtrace_kernel(const Utt* __restrict__ meta, const int* __restrict__ 
 //   alpha: (blank j, label j) as in the forward chain;  beta: (label j, blank j + 1), the backward chain's pair.
 // 128 positions make a piece; longer labels take several, each recomputing the 16 positions at its inner edges that
 // its neighbour owns (an error at the edge moves up one position per frame).
-// A row of one value per lane in LDS; two blocks of a row per frame.  (Not padded: 16 rows' 16-byte reads meet in the same banks, 12 of
-// them a piece, but both words of a frame are one instruction's offsets apart: 32 address additions a piece less.)
+// A row of one value per lane in LDS; two blocks of a row per frame.  (Not padded: 16 rows' 16-byte reads meet in the same banks, up to eight of
+// them a piece (share_product), and the counters show twice the conflicts, but both words of a frame are one instruction's offsets apart: 32 address additions a
+// piece less.  With four words of padding, so: 64 x 750 frames, 29 symbols 45.4 us a call, 45.5; 512 x 750 118.4, 118.6; 256 x 500, 60
+// symbols 61.2, 60.9; 400 x 400, 90 symbols 114.2, 113.6: within half a per cent either way, and 512 bytes of LDS a wavefront less.)
 constexpr int kShareRow = kPiecePositions / 2, kShareInts = 2 * kBlockFrames * kShareRow;
 constexpr int kNormInts = kBlockFrames;
 static_assert(kPieceStep % 32 == 0, "pieces start at multiples of 32 positions (share_product)");

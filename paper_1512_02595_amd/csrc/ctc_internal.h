@@ -481,8 +481,9 @@ CTC_HOST_DEVICE inline int chain_chunks(int frames, bool backward)
 // There is no branch inside a round: the compiler's count of the memory operations in flight stays exact, and a
 // wavefront waits for the emissions it is about to use only, not for stores.
 constexpr int kBlankAhead = 2;
+// run may make `chunks` less than 0: the round is then the last one.
 template <typename Fetch, typename Run>
-CTC_HOST_DEVICE inline void chain_schedule(int chunks, Fetch&& fetch, Run&& run)
+CTC_HOST_DEVICE inline void chain_schedule(const int& chunks, Fetch&& fetch, Run&& run)
 {
     const std::integral_constant<int, 0> a{};
     const std::integral_constant<int, 1> b{};

@@ -1118,6 +1118,9 @@ __device__ __forceinline__ int rows_flagged(const int* __restrict__ row_flags, i
 // Twenty mantissa bits bound the relative error of a state's share alpha * beta / p by 2^-19, which is 2e-6 of a gradient
 // entry at most.  Exponents stay above -2^30 so that the sum of two cannot wrap.
 //
+// Wavefronts of linear-domain chains that have gone on with an exponent to every state (finish_with_exponents) store checkpoints, and hand states up, with
+// kLogs as their frame and logarithms in the values' places (coded_logs).
+//
 // The mass p of an utterance (its reciprocal) keeps both parts in one 8-byte word (pack_state).
 struct alignas(16) CheckpointState { double blank, label; };
 struct CheckpointRow {
@@ -1127,16 +1130,22 @@ struct CheckpointRow {
     // (whole pieces of 64 bytes, as the region begins: 64 * pitch of them are there for a row)
     __device__ __forceinline__ int64_t bytes() const { return (frames_at() + pitch * static_cast<int64_t>(sizeof(int)) + 63) / 64 * 64; }
     __device__ __forceinline__ int64_t frames_at() const { return 2 * half() * static_cast<int64_t>(sizeof(CheckpointState)); }
-    __device__ __forceinline__ const CheckpointState* states(const uint32_t* block, int64_t row) const
+    // (a block has fewer than 2^31 bytes: make_layout)
+    __device__ __forceinline__ unsigned at(int row) const { return static_cast<unsigned>(row) * static_cast<unsigned>(bytes()); }
+    __device__ __forceinline__ const CheckpointState* states(const uint32_t* block, int row) const
     {
-        return reinterpret_cast<const CheckpointState*>(reinterpret_cast<const char*>(block) + row * bytes());
+        return reinterpret_cast<const CheckpointState*>(reinterpret_cast<const char*>(block) + at(row));
     }
-    __device__ __forceinline__ const int* frames(const uint32_t* block, int64_t row) const
+    __device__ __forceinline__ const int* frames(const uint32_t* block, int row) const
     {
-        return reinterpret_cast<const int*>(reinterpret_cast<const char*>(block) + row * bytes() + frames_at());
+        return reinterpret_cast<const int*>(reinterpret_cast<const char*>(block) + at(row) + frames_at());
     }
 };
 constexpr int kNoExponent = -(1 << 28);   // exponent of zero: below every real one, far from int32's ends
+// No frame: the values are logarithms.  They are coded such that nobody who renews frames has to ask for it: a renewal that meets the frame, in its own lane
+// or below it, finds the lane's first blank 2^1000 below its label, or below 2^kLogs, and so strained (kStrained).
+constexpr int kLogs = 1 << 30;
+constexpr double kLogOffset = 0x1p29, kLogZeroCode = 0x1p20, kBlankLogScale = 0x1p-1000;      // (fp64 keeps 23 bits behind the point)
 
 __device__ __forceinline__ double pack_state(double in_frame, int frame)
 {
@@ -1200,6 +1209,7 @@ struct CheckpointRows {
           at(0), step(static_cast<int>(row.bytes()))
     {
     }
+    __device__ __forceinline__ void drop() { state_at = next_state_at = frame_at = kNowhere; }
     typedef unsigned Words4 __attribute__((ext_vector_type(4)));
     typedef unsigned Words2 __attribute__((ext_vector_type(2)));
     template <int kPolicy>
@@ -1218,6 +1228,21 @@ struct CheckpointRows {
     __device__ __forceinline__ void next() { at += step; }
 };
 
+__device__ __forceinline__ CheckpointState coded_logs(double blank, double label)
+{
+    auto code = [](double w) { return w > -1.0e9 ? w + kLogOffset : kLogZeroCode; };
+    return {code(blank) * kBlankLogScale, code(label)};
+}
+// log2 of a pair's states, from their values and frame.
+__device__ __forceinline__ CheckpointState state_logs(const CheckpointState& s, int frame, double log0 = kNeg)
+{
+    auto decoded = [&](double v) { return v > 0x1p27 ? v - kLogOffset : log0; };
+    auto log2_of = [&](double v) {
+        const double log2 = static_cast<double>(frame + __builtin_amdgcn_frexp_exp(v)) + static_cast<double>(fast_log2(static_cast<float>(__builtin_amdgcn_frexp_mant(v))));
+        return v > 0.0 ? log2 : log0;
+    };
+    return {frame == kLogs ? decoded(s.blank * 0x1p1000) : log2_of(s.blank), frame == kLogs ? decoded(s.label) : log2_of(s.label)};
+}
 // log2(2^a + 2^b) for fp64 a, b with the exponentials taken on the fp32 difference.
 __device__ __forceinline__ double lse2(double a, double b)
 {
@@ -1333,9 +1358,9 @@ template <bool kBackward>
 __device__ __forceinline__ void fetch_chunk(const float*& p, int64_t step, float (&el)[kChunk])
 {
     const float4 lo = *reinterpret_cast<const float4*>(p), hi = *reinterpret_cast<const float4*>(p + 4);
-    const float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-#pragma unroll
-    for (int i = 0; i < kChunk; ++i) el[i] = v[kBackward ? kChunk - 1 - i : i];
+    constexpr int kFlip = kBackward ? kChunk - 1 : 0;
+    el[0 ^ kFlip] = lo.x; el[1 ^ kFlip] = lo.y; el[2 ^ kFlip] = lo.z; el[3 ^ kFlip] = lo.w;
+    el[4 ^ kFlip] = hi.x; el[5 ^ kFlip] = hi.y; el[6 ^ kFlip] = hi.z; el[7 ^ kFlip] = hi.w;
     p += step;
 }
 // Predecessor choices of a pair at one frame, as stored for the backtrace: three bits, the steps of a chunk in one word
@@ -1386,14 +1411,26 @@ struct Halo2Wave {
     double2 data[kRing][kHalo2Lanes][2];      // [hand-over mod kRing][halo lane][pair]: (blank, label)
     int2 tag[kRing][kHalo2Lanes];             // (the lane's frame, number of the hand-over)
 };
-constexpr size_t kHaloWaveBytes = sizeof(HaloWave) > sizeof(Halo2Wave) ? sizeof(HaloWave) : sizeof(Halo2Wave);
-static_assert(sizeof(HaloHeader) % 16 == 0 && kHaloWaveBytes % 16 == 0, "the blocks hold 16-byte entries");
+// What a wavefront had when it left the recursion on probabilities (finish_with_exponents): a lane's states and frame (kLogs: they are logarithms).
+// (In LDS, from where they are read again: as values that leave the loop from a dozen places they took more registers than there are.  So the wavefront goes
+// on to the end of the loop's round, its stores going nowhere.)
+struct StrainedWave {
+    double2 states[2][64];
+    int frame[64];
+};
+constexpr size_t kExchangeBytes = sizeof(HaloWave) > sizeof(Halo2Wave) ? sizeof(HaloWave) : sizeof(Halo2Wave);
+constexpr size_t kHaloWaveBytes = kExchangeBytes + sizeof(StrainedWave);
+static_assert(sizeof(HaloHeader) % 16 == 0 && kExchangeBytes % 16 == 0 && kHaloWaveBytes % 16 == 0, "the blocks hold 16-byte entries");
 // Bytes of dynamic LDS of a lattice launch whose workgroups have `waves` wavefronts.
 constexpr size_t halo_lds_bytes(int waves) { return sizeof(HaloHeader) + static_cast<size_t>(waves) * kHaloWaveBytes; }
 template <typename Wave>
 __device__ __forceinline__ Wave* halo_wave(void* lds, int wave)
 {
     return reinterpret_cast<Wave*>(static_cast<char*>(lds) + sizeof(HaloHeader) + static_cast<size_t>(wave) * kHaloWaveBytes);
+}
+__device__ __forceinline__ StrainedWave* strained_wave(void* lds, int wave)
+{
+    return reinterpret_cast<StrainedWave*>(static_cast<char*>(lds) + sizeof(HaloHeader) + static_cast<size_t>(wave) * kHaloWaveBytes + kExchangeBytes);
 }
 
 
@@ -1748,6 +1785,74 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
     }
 }
 
+// Where the chains of a launch leave their states: value and exponent blocks of both directions
+// (see "lattice storage").  In the modes without a gradient: the state of every pair after a chain's last frame (cost
+// only: one row of checkpoints in the value block), or the predecessor choices in the value block and
+// the last states, base-2 logarithms, in the exponent block (Mode::kBest).
+struct LatticeOut {
+    uint32_t* alpha;
+    int* alpha_exponents;
+    uint32_t* beta;
+    int* beta_exponents;
+};
+
+// What the chains' workgroups get besides.
+struct LaunchWords {
+    const int* row_flags;     // narrow softmax launch's words (rows_flagged), or nullptr: the records' flags say it all
+    int flag_blocks;          // ... per utterance
+    int* domain;              // per utterance and direction: did the chain run in the log domain
+    int* done;                // per utterance, kDoneStride apart: see finish_loss, announce_end
+    int late_percent;         // launch that writes the gradient too: this share of the chains' workgroups come late (tests)
+    int* host_flag;           // pinned host word that receives host_flag_value: the image may be reused (or nullptr)
+    int host_flag_value;
+    const int* status_words;  // device-resident metadata built by the narrow softmax launch: per utterance, nonzero if
+    int* status_out;          // invalid; gathered into the caller's status word by this launch (or nullptr)
+    int status_count;
+    int skip_directions;      // bit 0: leave the forward chains out, bit 1: the backward chains (measurements only)
+    FillArgs fill;            // zero rows to write beside the chains
+    int norm_groups, utterances;  // cost-only launches: the first workgroup that sees to the utterances' norms, and how many there are
+};
+
+// The arguments of a launch with chains as they lie in memory, in the kernels' order.
+template <bool kFused>
+struct ChainArgs {
+    const Utt* meta;
+    const int* order;
+    const int* labels;
+    const float* emit_blank;
+    const double* emit_blank64;
+    const float* emit_label;
+    LatticeOut lat;
+    double* mass;
+    float* costs;
+    int* chain_err;
+    uint32_t* sink;
+    LaunchWords wk;
+};
+template <>
+struct ChainArgs<true> {
+    const Utt* meta;
+    const int* order;
+    const int* labels;
+    const float* emit_blank;
+    const float* emit_label;
+    LatticeOut lat;
+    double* mass;
+    float* costs;
+    int* chain_err;
+    uint32_t* sink;
+    LaunchWords wk;
+};
+// Read again from there: nothing of it is kept in registers from before.
+template <typename Args>
+__device__ __forceinline__ const Args& args_again()
+{
+    typedef __attribute__((address_space(4))) const Args* ArgsPointer;
+    ArgsPointer args = (ArgsPointer)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    return *(const Args*)args;
+}
+
 // The same chain on probabilities, each frame's divided by its blank's (FrameNorm), instead of their logarithms: a step is then
 // two fused multiply-adds, an addition and a multiplication per pair, a fifth of the instructions of the
 // log-domain step and no transcendentals.  What makes it safe is an exponent per lane:
@@ -1765,9 +1870,11 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
 // Two neighbouring frames differ by at most kFrameSlack + kFrameDrop, which the factor between them (scale, constant between renewals
 // and folded into the multiply-adds) can hold.
 //
-// The states of a lane share its frame, and that is a fault: a state that lies 2^1022 below one further on in the label is lost, and what
-// would have gone on from it later with it.  Symbols held against the blank do it: seen
-// from 15 frames at 20 nats and from 60 at 6, rarely there and often beyond.
+// The states of a lane share its frame.  One that lies 2^1022 below another further on in the label would be rounded to zero, and what
+// would have gone on from it later be lost; symbols held against the blank for dozens of frames do that.  A wavefront that meets it (strains) leaves this
+// recursion there and goes on with an exponent to every state (finish_with_exponents); so do those above it, once they are handed its logarithms.
+// It suffices to look at a lane's first blank, when frames are renewed: a blank state loses nothing from step to step and gets at
+// least what its pair's label gets, so but for the last steps' factors it is the least of the lane's states, and only a renewal makes values smaller.
 //
 // A pair further than 2^(kFrameSlack + kFrameDrop) below its window's top is rounded away.  Its neighbours have 2^760 times its
 // mass and can still reach the end of the label (utterances with fewer than kTightFrames frames to spare, where they could
@@ -1802,6 +1909,11 @@ constexpr bool frames_last(int steps, float min_log2, int smooth)
 static_assert(frames_last(kBlockFrames, kGentleMinLog2, kSmoothFrames), "a block");
 static_assert(frames_last(kChunk, kRoughMinLog2, kSmoothFrames), "a chunk");
 static_assert(frames_last(kSteepSteps, kLinearMinLog2, kSteepSmoothFrames), "a steep one's steps");
+// Does a renewal leave a lane's first blank below 2^kStrained of its new frame?  (`rise`: from the frame it had.  A lane without mass has a blank of 0, whose
+// exponent reads 0.)  What is above keeps all its bits until the next renewal: 2^(kStrained + kLinearMinLog2) is above fp64's smallest normal number.
+constexpr int kStrained = -900;
+static_assert(kStrained + kLinearMinLog2 >= -1022, "what a first blank of 2^kStrained gives its label");
+__device__ __forceinline__ bool strains(double first, int rise) { return __ballot(__builtin_amdgcn_frexp_exp(first) + rise < kStrained) != 0; }
 // The test, on the high dword of the largest value of a lane (biased exponent in bits 20..30): one
 // subtraction and one unsigned compare; zero, denormals, infinities and NaN fail it.
 __device__ __forceinline__ bool outside_easy_range(double top)
@@ -1817,6 +1929,12 @@ __device__ __forceinline__ void publish_mass(double* mass, double value, int fra
     publish(&mass[kMassValue], value);
     publish(&mass[kMassLog2], static_cast<double>(frame));
 }
+
+// How a wavefront of a linear-domain chain ends.
+struct ChainEnd {
+    int unit;                                            // nonzero: after so many half chunks it has left the recursion (finish_with_exponents)
+    bool lost;                                           // it gave up a wait
+};
 
 // A chain's frames; kPairs pairs to a lane.
 template <int kPairs, bool kSteep>
@@ -1863,16 +1981,16 @@ struct ChainFrames {
 
 // kPolicy: of the checkpoints' stores, kPast where another workgroup of the launch reads them.
 template <bool kBackward, Sync kSync, Mode kMode, bool kSteep, int kPolicy>
-__device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const bool gentle, const int* __restrict__ labels,
+__device__ __forceinline__ ChainEnd run_chain_linear(const Utt m, const int u, const bool gentle, const int* __restrict__ labels,
                                                  const float* __restrict__ emit_label, uint32_t* __restrict__ out,
                                                  double* __restrict__ mass, int* __restrict__ chain_err, void* lds)
 {
     static_assert(kSync != Sync::kBarrier, "the barrier kernel runs the log-domain chain");
     static_assert(kMode != Mode::kBest, "the maximum recursion runs in the log domain");
     const int L = m.L, chunks = 2 * frame_blocks(m.Tb);
-    const int count = kMode == Mode::kLoss ? chain_chunks(m.Tb, kBackward) : chunks;     // chunks of this chain
+    int count = kMode == Mode::kLoss ? chain_chunks(m.Tb, kBackward) : chunks;     // chunks of this chain; -unit once it has been left
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (uniform: in a scalar register)
-    const int halo = (kSync == Sync::kHalo) ? m.halo : 0;
+    int halo = (kSync == Sync::kHalo) ? m.halo : 0;      // (0 once the chain has been left: nothing is handed up)
     const int j = wave * (64 - halo) + lane;             // pair of this lane (see run_chain_log)
     const int* lab = labels + m.lab_off;
     const bool has_label = j >= 0 && j < L;
@@ -1908,7 +2026,7 @@ __device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const
     int nil = 0;
     asm volatile("" : "+v"(nil));
     int* const always = &static_cast<HaloHeader*>(lds)->always + nil;
-    int* const my_ready = &mine_lds->ready + nil;
+    int* my_ready = &mine_lds->ready + nil;
     int* const up_ready = wave < last_wave ? &above_lds->ready + nil : always;
     int* const low_ready = wave > 0 ? &below_lds->ready + nil : always;
     const bool from_below = wave > 0 && lane < halo;
@@ -1972,8 +2090,20 @@ __device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const
     int prev_lo = 0, prev_hi = 0;
     auto from_prev_pair = [&](double mine) __attribute__((always_inline)) { return shift_up(mine, prev_lo, prev_hi); };
     auto top_value = [&]() __attribute__((always_inline)) { return fmax(v_blank, v_label); };
-    auto renew_frames = [&]() __attribute__((always_inline)) {
+    // Leaves the recursion after `unit` half chunks, with the states in `frame` (StrainedWave).
+    auto leave = [&](int unit, int frame) __attribute__((always_inline)) {
+        if (count < 0) return;
+        count = -unit;
+        StrainedWave* const w = strained_wave(lds, wave);
+        w->states[0][lane] = make_double2(v_blank, v_label);
+        w->frame[lane] = frame;
+        rows.drop();
+        halo = 0;
+        if (kSync == Sync::kHalo) my_ready = &mine_lds->done + nil;
+    };
+    auto renew_frames = [&](int unit) __attribute__((always_inline)) {
         const int rise = f.renew(top_value(), halo > 0 ? halo - 1 : 0);
+        if (__builtin_expect(strains(v_blank, rise), 0)) leave(unit, f.frame + rise);
         v_blank = __builtin_amdgcn_ldexp(v_blank, rise);
         v_label = __builtin_amdgcn_ldexp(v_label, rise);
         skip_scale = skip_ok ? f.scale : 0.0;
@@ -1981,14 +2111,14 @@ __device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const
 
     // After a block's first chunk (steep: and in the middle of every chunk), and after a block.
     static_assert(kChunk == 2 * kSteepSteps, "the middle of a chunk");
-    auto mid_block = [&]() __attribute__((always_inline)) {
+    auto mid_block = [&](int unit) __attribute__((always_inline)) {
         if (__builtin_expect((f.rough | look) != 0, 0))
-            if (f.renewal_due(top_value())) renew_frames();
+            if (f.renewal_due(top_value())) renew_frames(unit);
     };
-    auto end_block = [&](bool second) __attribute__((always_inline)) {
+    auto end_block = [&](bool second, int unit) __attribute__((always_inline)) {
         if (kSync == Sync::kHalo)
             if (second || every_block) hand_over();
-        if (__builtin_expect(f.renewal_due(top_value()), 0)) renew_frames();
+        if (__builtin_expect(f.renewal_due(top_value()), 0)) renew_frames(unit);
     };
     auto checkpoint = [&]() __attribute__((always_inline)) {
         rows.template state<kPolicy>(0, CheckpointState{v_blank, v_label});
@@ -2024,27 +2154,28 @@ __device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const
         fetch_chunk<kBackward>(ep, estep, el[k]);
         __builtin_amdgcn_sched_barrier(0);
     };
-    auto run = [&](auto set, int) __attribute__((always_inline)) {
+    auto run = [&](auto set, int i) __attribute__((always_inline)) {
         constexpr int k = decltype(set)::value;
         double el_d = static_cast<double>(el[k][0]);
 #pragma unroll
         for (int q = 0; q < kChunk; ++q) {
             advance(el_d, el[k][q + 1 < kChunk ? q + 1 : q]);
-            if (kSteep && q == kSteepSteps - 1) mid_block();
+            if (kSteep && q == kSteepSteps - 1) mid_block(2 * i + 1);
         }
-        if (!(k & 1)) mid_block();
+        if (!(k & 1)) mid_block(2 * i + 2);
         else {
-            end_block(k == 3);
+            end_block(k == 3, 2 * i + 2);
             if (kMode == Mode::kGrad) checkpoint();
         }
     };
     chain_schedule(count, fetch, run);
+    if (__builtin_expect(count < 0, 0)) return {-count, lost};
 
     if (kMode == Mode::kLoss) {
         // the state of every pair, for finish_loss
         rows.template state<kPolicy>(0, CheckpointState{v_blank, v_label});
         rows.template frame<kPolicy>(f.frame);
-        return lost;
+        return {0, lost};
     }
     if (!kBackward) {
         // p = alpha_{T-1}(2L) + alpha_{T-1}(2L-1), from the lane of pair L (exact, as is the
@@ -2053,7 +2184,7 @@ __device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const
         if (active && j == L) publish_mass(&mass[u * kMassWords], v_blank + from_below, f.frame);
     }
     if (kSync == Sync::kHalo && lost && lane == 0) publish(&chain_err[u], 1);
-    return lost;
+    return {0, lost};
 }
 
 // Linear-domain chains of more than 64 pairs: a lane owns two neighbouring pairs, A = 2q and
@@ -2068,15 +2199,16 @@ __device__ __forceinline__ bool run_chain_linear(const Utt m, const int u, const
 // pair) its part falls on one of the row's two unused columns.
 
 template <bool kBackward, Mode kMode, bool kSteep, int kPolicy>
-__device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, const bool gentle, const int* __restrict__ labels,
+__device__ __forceinline__ ChainEnd run_chain_linear2(const Utt m, const int u, const bool gentle, const int* __restrict__ labels,
                                                   const float* __restrict__ emit_label, uint32_t* __restrict__ out,
                                                   double* __restrict__ mass, int* __restrict__ chain_err, void* lds)
 {
     static_assert(kMode != Mode::kBest, "the maximum recursion runs in the log domain");
     const int L = m.L, chunks = 2 * frame_blocks(m.Tb);
-    const int count = kMode == Mode::kLoss ? chain_chunks(m.Tb, kBackward) : chunks;     // chunks of this chain
+    int count = kMode == Mode::kLoss ? chain_chunks(m.Tb, kBackward) : chunks;     // (see run_chain_linear)
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (uniform: in a scalar register)
-    const int halo = m.halo2, waves = m.waves2;
+    int halo = m.halo2;
+    const int waves = m.waves2;
     const int q = wave * (64 - halo) + lane;
     const int ja = 2 * q, jb = 2 * q + 1;                // the lane's pairs, in the chain's own order
     const int* lab = labels + m.lab_off;
@@ -2187,8 +2319,19 @@ __device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, cons
     int prev_lo = 0, prev_hi = 0;
     auto from_lane_below = [&](double mine) __attribute__((always_inline)) { return shift_up(mine, prev_lo, prev_hi); };
     auto top_value = [&]() __attribute__((always_inline)) { return fmax(fmax(va_blank, va_label), fmax(vb_blank, vb_label)); };
-    auto renew_frames = [&]() __attribute__((always_inline)) {
+    auto leave = [&](int unit, int frame) __attribute__((always_inline)) {
+        if (count < 0) return;
+        count = -unit;
+        StrainedWave* const w = strained_wave(lds, wave);
+        w->states[0][lane] = make_double2(va_blank, va_label);
+        w->states[1][lane] = make_double2(vb_blank, vb_label);
+        w->frame[lane] = frame;
+        rows.drop();
+        halo = 0;
+    };
+    auto renew_frames = [&](int unit) __attribute__((always_inline)) {
         const int rise = f.renew(top_value(), halo > 0 ? halo - 1 : 0);
+        if (__builtin_expect(strains(va_blank, rise), 0)) leave(unit, f.frame + rise);
         va_blank = __builtin_amdgcn_ldexp(va_blank, rise);
         va_label = __builtin_amdgcn_ldexp(va_label, rise);
         vb_blank = __builtin_amdgcn_ldexp(vb_blank, rise);
@@ -2203,13 +2346,13 @@ __device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, cons
         rows.template frames<kPolicy>(f.frame);          // both pairs of the lane share its frame
         rows.next();
     };
-    auto mid_block = [&]() __attribute__((always_inline)) {
+    auto mid_block = [&](int unit) __attribute__((always_inline)) {
         if (__builtin_expect((f.rough | look) != 0, 0))
-            if (f.renewal_due(top_value())) renew_frames();
+            if (f.renewal_due(top_value())) renew_frames(unit);
     };
-    auto end_block = [&](bool second) __attribute__((always_inline)) {
+    auto end_block = [&](bool second, int unit) __attribute__((always_inline)) {
         if (waves > 1 && (second || every_block)) hand_over();
-        if (__builtin_expect(f.renewal_due(top_value()), 0)) renew_frames();
+        if (__builtin_expect(f.renewal_due(top_value()), 0)) renew_frames(unit);
     };
     // One step (see run_chain_linear): the pairs' own sums fill the time that the shift takes.
     //   label' = (label + blank + skip * previous label) * emission, as fma(previous, skip, label + blank)
@@ -2247,27 +2390,28 @@ __device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, cons
         fetch_chunk<kBackward>(epb, step_b, elb[k]);
         __builtin_amdgcn_sched_barrier(0);
     };
-    auto run = [&](auto set, int) __attribute__((always_inline)) {
+    auto run = [&](auto set, int i) __attribute__((always_inline)) {
         constexpr int k = decltype(set)::value;
 #pragma unroll
         for (int q = 0; q < kChunk; ++q) {
             advance(ela[k][q], elb[k][q]);
-            if (kSteep && q == kSteepSteps - 1) mid_block();
+            if (kSteep && q == kSteepSteps - 1) mid_block(2 * i + 1);
         }
-        if (!(k & 1)) mid_block();
+        if (!(k & 1)) mid_block(2 * i + 2);
         else {
-            end_block(k == 3);
+            end_block(k == 3, 2 * i + 2);
             if (kMode == Mode::kGrad) checkpoint();
         }
     };
     chain_schedule(count, fetch, run);
+    if (__builtin_expect(count < 0, 0)) return {-count, lost};
 
     if (kMode == Mode::kLoss) {
         // the state of every pair, for finish_loss
         rows.template state<kPolicy>(0, CheckpointState{va_blank, va_label});
         rows.template state<kPolicy>(1, CheckpointState{vb_blank, vb_label});
         rows.template frames<kPolicy>(f.frame);
-        return lost;
+        return {0, lost};
     }
     if (!kBackward) {
         // p = alpha_{T-1}(2L) + alpha_{T-1}(2L-1): the blank of pair L and the label of pair L - 1.
@@ -2276,56 +2420,237 @@ __device__ __forceinline__ bool run_chain_linear2(const Utt m, const int u, cons
         if (active && (ja == L || jb == L)) publish_mass(&mass[u * kMassWords], ja == L ? va_blank + from_below : vb_blank + va_label, f.frame);
     }
     if (lost && lane == 0) publish(&chain_err[u], 1);
-    return lost;
+    return {0, lost};
 }
 
-// Where the chains of a launch leave their states: value and exponent blocks of both directions
-// (see "lattice storage").  In the modes without a gradient: the state of every pair after a chain's last frame (cost
-// only: one row of checkpoints in the value block), or the predecessor choices in the value block and
-// the last states, base-2 logarithms, in the exponent block (Mode::kBest).
-struct LatticeOut {
-    uint32_t* alpha;
-    int* alpha_exponents;
-    uint32_t* beta;
-    int* beta_exponents;
+// A record whose fields the compiler knows to be the same in every lane, wherever it was read from.
+__device__ __forceinline__ Utt uniform_record(const Utt& m)
+{
+    Utt u = m;
+    auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+    auto uniform64 = [&](int64_t v) {
+        return static_cast<int64_t>(static_cast<uint64_t>(static_cast<unsigned>(uniform(static_cast<int>(v)))) |
+                                    (static_cast<uint64_t>(static_cast<unsigned>(uniform(static_cast<int>(v >> 32)))) << 32));
+    };
+    u.Tb = uniform(m.Tb);
+    u.L = uniform(m.L);
+    u.lab_off = uniform(m.lab_off);
+    u.flags = uniform(m.flags);
+    u.f_off = static_cast<unsigned>(uniform(static_cast<int>(m.f_off)));
+    u.e_cols = uniform(m.e_cols);
+    u.e_direct = static_cast<int16_t>(uniform(m.e_direct));
+    u.waves = uniform(m.waves);
+    u.halo = uniform(m.halo);
+    u.waves2 = uniform(m.waves2);
+    u.halo2 = uniform(m.halo2);
+    u.poll_budget = uniform(m.poll_budget);
+    u.e_off = uniform64(m.e_off);
+    u.ab_off = uniform64(m.ab_off);
+    return u;
+}
+
+// A state with an exponent of its own, mantissa * 2^exponent; zero: 0 and kNoExponent.
+struct OwnExponent {
+    double mantissa;
+    int exponent;
+    __device__ __forceinline__ OwnExponent plus(const OwnExponent& other) const
+    {
+        const int higher = max(exponent, other.exponent);
+        const double v = __builtin_amdgcn_ldexp(mantissa, exponent - higher) + __builtin_amdgcn_ldexp(other.mantissa, other.exponent - higher);
+        return {__builtin_amdgcn_frexp_mant(v), higher + __builtin_amdgcn_frexp_exp(v)};
+    }
+    __device__ __forceinline__ OwnExponent times(double factor) const
+    {
+        const double v = mantissa * factor;
+        return {v, v > 0.0 ? exponent : kNoExponent};
+    }
+    __device__ __forceinline__ double log2() const
+    {
+        const double v = static_cast<double>(exponent + __builtin_amdgcn_frexp_exp(mantissa)) +
+                         static_cast<double>(fast_log2(static_cast<float>(__builtin_amdgcn_frexp_mant(mantissa))));
+        return mantissa > 0.0 ? v : kNeg;
+    }
+    static __device__ __forceinline__ OwnExponent of(double v, int frame) { return {__builtin_amdgcn_frexp_mant(v), v > 0.0 ? frame + __builtin_amdgcn_frexp_exp(v) : kNoExponent}; }
+    static __device__ __forceinline__ OwnExponent of_log2(double w)
+    {
+        const double whole = floor(w);
+        return w > -1.0e9 ? OwnExponent{static_cast<double>(fast_exp2(static_cast<float>(w - whole))), static_cast<int>(whole)} : OwnExponent{0.0, kNoExponent};
+    }
 };
 
-// What the chains' workgroups get besides.
-struct LaunchWords {
-    const int* row_flags;     // narrow softmax launch's words (rows_flagged), or nullptr: the records' flags say it all
-    int flag_blocks;          // ... per utterance
-    int* domain;              // per utterance and direction: did the chain run in the log domain
-    int* done;                // per utterance, kDoneStride apart: see finish_loss, announce_end
-    int late_percent;         // launch that writes the gradient too: this share of the chains' workgroups come late (tests)
-    int* host_flag;           // pinned host word that receives host_flag_value: the image may be reused (or nullptr)
-    int host_flag_value;
-    const int* status_words;  // device-resident metadata built by the narrow softmax launch: per utterance, nonzero if
-    int* status_out;          // invalid; gathered into the caller's status word by this launch (or nullptr)
-    int status_count;
-    int skip_directions;      // bit 0: leave the forward chains out, bit 1: the backward chains (measurements only)
-    FillArgs fill;            // zero rows to write beside the chains
-    int norm_groups, utterances;  // cost-only launches: the first workgroup that sees to the utterances' norms, and how many there are
-};
+// The rest of a chain whose wavefront has left the recursion after `unit` half chunks: the same with an exponent to every state, and with the
+// checkpoints and the hand-overs of the chain it goes on from, in logarithms (coded_logs).  Returns whether it gave up a wait.
+// (Rare, and written to cost the chains it stands behind nothing: every argument is read again.  In logarithms throughout, as in the log domain, rounding added
+// up differently in the two directions of an utterance: 2^21 frames, gradient off by 6e-4.)
+template <Sync kSync, Mode kMode, bool kFused>
+__device__ __forceinline__ bool finish_with_exponents(int unit, bool lost, void* lds)
+{
+    // (one at a time: eight words of them loaded at once had to be kept in memory)
+    auto args = []() -> const ChainArgs<kFused>& { return args_again<ChainArgs<kFused>>(); };
+    const int chain = __builtin_amdgcn_readfirstlane(args().order[blockIdx.x]), u = chain >> 1;
+    const bool backward = (chain & 1) != 0;
+    const Utt m = uniform_record(args().meta[u]);
+    const bool two = kSync == Sync::kHalo && (m.flags & kUttTwoPairs) != 0;
+    const int L = m.L, chunks = 2 * frame_blocks(m.Tb), units = 2 * (kMode == Mode::kLoss ? chain_chunks(m.Tb, backward) : chunks);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+    const int halo = two ? m.halo2 : (kSync == Sync::kHalo ? m.halo : 0), last_wave = (two ? m.waves2 : m.waves) - 1;
+    const int first_pair = (two ? 2 : 1) * (wave * (64 - halo) + lane);
+    const bool active = (wave == 0 || lane >= halo) && first_pair <= L;
+    const int* const lab = args().labels + m.lab_off;
+    // Pair 0 or 1 of the lane: its label's index (back: to the pair before), whether it has one, whether that may be entered from the pair before's.
+    const int back = backward ? 1 : -1;
+    auto position = [&](int k) { return backward ? L - 1 - (first_pair + k) : first_pair + k; };
+    const bool has0 = first_pair < L, has1 = two && first_pair + 1 < L;
+    const int symbol0 = has0 ? lab[position(0)] : 0, symbol1 = has1 ? lab[position(1)] : 0;
+    const bool skip0 = has0 && first_pair >= 1 && symbol0 != lab[position(0) + back], skip1 = has1 && symbol1 != symbol0;
+    const int first_chunk = chain_chunk(0, chunks, backward);
+    const float* const emit_label = args().emit_label;
+    const float* const at0 = emit_label + label_emission_offset(m, has0, symbol0, position(0), first_chunk, kZeroEmission);
+    const float* const at1 = emit_label + label_emission_offset(m, has1, symbol1, position(1), first_chunk, kZeroEmission);
+    const int64_t step0 = label_emission_step(m, has0, backward), step1 = label_emission_step(m, has1, backward);
+
+    struct Pair { OwnExponent blank, label; };
+    const OwnExponent zero{0.0, kNoExponent};
+    Pair s0{zero, zero}, s1{zero, zero};
+    auto pair_of = [](const double2& v, int frame) {
+        const CheckpointState logs = state_logs(CheckpointState{v.x, v.y}, frame);
+        return frame == kLogs ? Pair{OwnExponent::of_log2(logs.blank), OwnExponent::of_log2(logs.label)} : Pair{OwnExponent::of(v.x, frame), OwnExponent::of(v.y, frame)};
+    };
+    auto take = [&](const double2& v0, const double2& v1, int frame) {
+        s0 = pair_of(v0, frame);
+        if (two) s1 = pair_of(v1, frame);
+    };
+    auto coded = [](const Pair& s) {
+        const CheckpointState c = coded_logs(s.blank.log2(), s.label.log2());
+        return make_double2(c.blank, c.label);
+    };
+    const StrainedWave* const from = strained_wave(lds, wave);
+    take(from->states[0][lane], from->states[1][lane], from->frame[lane]);
+
+    constexpr bool kGrad = kMode == Mode::kGrad;
+    CheckpointRows rows((backward ? args().lat.beta : args().lat.alpha) + m.ab_off, CheckpointRow{lattice_pitch(L)}, kGrad ? frame_blocks(m.Tb) - 1 : 1,
+                        active && (has0 || !kGrad), !kGrad ? first_pair : 1 + position(two && backward ? 1 : 0));
+    if (kGrad) rows.at = ((unit - 1) >> 2) * rows.step;  // (four units make a block)
+    constexpr int kPolicy = kFused || !kGrad ? kPast : 0;
+    auto store = [&]() {
+        const double2 c0 = coded(s0), c1 = coded(s1);
+        const CheckpointState a{c0.x, c0.y}, b{c1.x, c1.y};
+        const bool swapped = kGrad && two && backward;
+        rows.template state<kPolicy>(0, swapped ? b : a);
+        rows.template frame<kPolicy>(kLogs);
+        if (two) {
+            rows.template state<kPolicy>(1, swapped ? a : b);
+            rows.template frames<kPolicy>(kLogs);
+        }
+        rows.next();
+    };
+
+    // Hand-overs: as in the chain, one thing after the other.
+    const bool exchanges = kSync == Sync::kHalo && last_wave > 0, every_block = (two ? 2 : 1) * halo < 2 * kBlockFrames;
+    int generation = every_block ? unit >> 2 : unit >> 3, budget = m.poll_budget;
+    const int wr_slot = lane >= 64 - halo ? lane - (64 - halo) : 0, rd_slot = lane < halo ? lane : 0;
+    auto hand_over = [&]() {
+        ++generation;
+        const int half = (generation & 1) * 32, slot = generation & (kRing - 1);
+        // Waits until wavefront w has published the number `until`.  (LDS operations of a wavefront complete in order.)
+        auto wait = [&](int w, int until) {
+            const int* const number = two ? &halo_wave<Halo2Wave>(lds, w)->tag[slot][0].y : &halo_wave<HaloWave>(lds, w)->ready;
+            auto look = [&]() { return uniform(__hip_atomic_load(number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)); };
+            int seen = look();
+            for (; seen < until && budget > 0; --budget) seen = look();
+            lost = lost || seen < until;
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        };
+        auto data = [&](int w, int lane_slot, int k) { return two ? &halo_wave<Halo2Wave>(lds, w)->data[slot][lane_slot][k] : &halo_wave<HaloWave>(lds, w)->data[half + lane_slot]; };
+        auto frame = [&](int w, int lane_slot) { return two ? &halo_wave<Halo2Wave>(lds, w)->tag[slot][lane_slot].x : &halo_wave<HaloWave>(lds, w)->frame[half + lane_slot]; };
+        const bool hands_up = lane >= 64 - halo;
+        if (wave < last_wave) wait(wave + 1, generation - (two ? kRing : 2));
+        if (hands_up) {
+            *data(wave, wr_slot, 0) = coded(s0);
+            if (two) *data(wave, wr_slot, 1) = coded(s1);
+            else *frame(wave, wr_slot) = kLogs;
+        }
+        if (wave > 0) {
+            wait(wave - 1, generation);
+            const double2 v0 = *data(wave - 1, rd_slot, 0), v1 = *data(wave - 1, rd_slot, 1);
+            const int f = *frame(wave - 1, rd_slot);
+            if (lane < halo) take(v0, v1, f);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        if (two && hands_up)
+            __hip_atomic_store(reinterpret_cast<unsigned long long*>(&halo_wave<Halo2Wave>(lds, wave)->tag[slot][wr_slot]),
+                               (static_cast<unsigned long long>(static_cast<unsigned>(generation)) << 32) | static_cast<unsigned>(kLogs),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (!two && lane == 63) __hip_atomic_store(&halo_wave<HaloWave>(lds, wave)->ready, generation, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+
+    auto from_lane_below = [&]() {
+        const OwnExponent last = two ? s1.label : s0.label;
+        return OwnExponent{lane_shift<false>(last.mantissa), __builtin_amdgcn_update_dpp(kNoExponent, last.exponent, 0x138, 0xf, 0xf, false)};
+    };
+    static_assert(kSteepSteps == 4 && kBlockFrames == 4 * kSteepSteps, "units of four steps");
+    // (a block that has just ended has handed over, but its checkpoint is to come)
+    if (kGrad && (unit & 3) == 0) store();
+#pragma unroll 1
+    for (; unit < units; ++unit) {
+        const int64_t in_chunk = (unit & 1) != (backward ? 1 : 0) ? kSteepSteps : 0;
+        const float4 el0 = *reinterpret_cast<const float4*>(at0 + (unit >> 1) * step0 + in_chunk), el1 = *reinterpret_cast<const float4*>(at1 + (unit >> 1) * step1 + in_chunk);
+#pragma unroll 1
+        for (int q = 0; q < kSteepSteps; ++q) {
+            const int frame = backward ? kSteepSteps - 1 - q : q;
+            auto component = [&](const float4& v) { return frame == 0 ? v.x : frame == 1 ? v.y : frame == 2 ? v.z : v.w; };
+            auto step = [&](Pair& s, const OwnExponent& before, bool skip, float emission) {
+                const OwnExponent blank = s.blank.plus(before), label = s.label.plus(skip ? blank : s.blank);
+                s = Pair{blank, label.times(static_cast<double>(emission))};
+            };
+            const OwnExponent prev = from_lane_below();
+            if (two) step(s1, s0.label, skip1, component(el1));
+            step(s0, prev, skip0, component(el0));
+        }
+        if ((unit & 3) == 3) {
+            if (exchanges && (every_block || (unit & 4) != 0)) hand_over();
+            if (kGrad) store();
+        }
+    }
+    if (!kGrad) {
+        store();
+        return lost;
+    }
+    if (!backward) {
+        // (see run_chain_linear2)
+        const OwnExponent below = from_lane_below();
+        if (active && (first_pair == L || (two && first_pair + 1 == L))) {
+            const OwnExponent p = first_pair == L ? s0.blank.plus(below) : s1.blank.plus(s0.label);
+            publish_mass(&args().mass[u * kMassWords], p.mantissa, p.exponent);
+        }
+    }
+    if (kSync == Sync::kHalo && lost && lane == 0) publish(&args().chain_err[u], 1);
+    return lost;
+}
 
 // Cost-only calls: the mass of an utterance from the states that its two chains have left where they meet, alpha after
 // the last of the forward chain's frames and beta (its frame included) at the first of the backward chain's:
 //   p = sum over states s of  (sum of alpha over s and its predecessors) * beta(s).
 // A wavefront that has ended counts itself in, and the utterance's last one does the sum, whichever it is: the order of
-// the additions is that of the pairs.  The count carries, in its upper half, how many wavefronts gave up waiting for a
-// neighbour; then the cost is NaN.  `waves`: wavefronts of a chain.  One more wavefront counts itself in, which has nothing to do with
+// the additions is that of the pairs.  The count carries how many wavefronts gave up waiting for a
+// neighbour, from bit 16 on (then the cost is NaN), and, from bit 24 on, how many
+// have left logarithms (finish_with_exponents).  `waves`: wavefronts of a chain.  One more wavefront counts itself in, which has nothing to do with
 // the chains and leaves the norms (norms_of_utterance).
 __device__ __forceinline__ void finish_loss(const Utt& m, const int u, const int* __restrict__ labels, const LatticeOut& lat,
                                             const double* __restrict__ mass, int* __restrict__ done, float* __restrict__ costs,
-                                            const int waves, const bool lost)
+                                            const int waves, const bool lost, const bool in_logs)
 {
+    constexpr int kLost = 1 << 16, kInLogs = 1 << 24;    // (up to 33 wavefronts)
     const int lane = threadIdx.x & 63, expected = 2 * waves + 1;
     // (the chains may run on different dies; what has been published is past the die's cache once it is out)
     int before = 0;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if (lane == 0)
-        before = __hip_atomic_fetch_add(&done[u * kDoneStride], lost ? 0x10001 : 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        before = __hip_atomic_fetch_add(&done[u * kDoneStride], 1 + (lost ? kLost : 0) + (in_logs ? kInLogs : 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     before = __builtin_amdgcn_readfirstlane(before);
-    if ((before & 0xFFFF) != expected - 1) return;
+    if ((before & (kLost - 1)) != expected - 1) return;
+    const bool given_up = (before & (kInLogs - kLost)) != 0 || lost, some_logs = before >= kInLogs || in_logs;
     const int L = m.L;
     const CheckpointRow row{lattice_pitch(L)};
     const CheckpointState *const alpha = row.states(lat.alpha + m.ab_off, 0), *const beta = row.states(lat.beta + m.ab_off, 0);
@@ -2344,46 +2669,64 @@ __device__ __forceinline__ void finish_loss(const Utt& m, const int u, const int
         top = higher;
     };
     // pair j going forward: blank j and label j; the backward chain's pair i: blank L - i and label L - 1 - i.  (Past the cache each look
-    // is a trip to memory: kAtOnce pairs' words travel together.)
-    constexpr int kAtOnce = 2;
-    for (int j0 = lane; j0 - lane <= L; j0 += 64 * kAtOnce) {
-        CheckpointState a[kAtOnce];
-        double before_label[kAtOnce], blank_b[kAtOnce], label_b[kAtOnce];
-        int a_frame[kAtOnce], before_frame[kAtOnce], blank_frame[kAtOnce], label_frame[kAtOnce];
-        bool skips[kAtOnce];
+    // is a trip to memory: kAtOnce pairs' words travel together.)  logs: some are logarithms.
+    auto add_pairs = [&](auto logs) __attribute__((always_inline)) {
+        constexpr bool kSomeLogs = decltype(logs)::value;
+        constexpr int kAtOnce = kSomeLogs ? 1 : 2;
+        // (to a value and a frame of its own again)
+        auto plain = [](double& v, int& frame, bool is_blank) {
+            const double code = is_blank ? v * 0x1p1000 : v, w = code - kLogOffset, whole = floor(w);
+            if (!kSomeLogs || frame != kLogs) return;
+            frame = code > 0x1p27 ? static_cast<int>(whole) : 0;
+            v = code > 0x1p27 ? static_cast<double>(fast_exp2(static_cast<float>(w - whole))) : 0.0;
+        };
+        for (int j0 = lane; j0 - lane <= L; j0 += 64 * kAtOnce) {
+            CheckpointState a[kAtOnce];
+            double before_label[kAtOnce], blank_b[kAtOnce], label_b[kAtOnce];
+            int a_frame[kAtOnce], before_frame[kAtOnce], blank_frame[kAtOnce], label_frame[kAtOnce];
+            bool skips[kAtOnce];
 #pragma unroll
-        for (int n = 0; n < kAtOnce; ++n) {
-            const int j = min(j0 + 64 * n, L), before = max(j - 1, 0), after = max(L - 1 - j, 0);
-            a[n] = published(&alpha[row.slot(j)]);
-            a_frame[n] = published(&fa[j]);
-            before_label[n] = published(&alpha[row.slot(before)].label);
-            before_frame[n] = published(&fa[before]);
-            blank_b[n] = published(&beta[row.slot(L - j)].blank);
-            blank_frame[n] = published(&fb[L - j]);
-            label_b[n] = published(&beta[row.slot(after)].label);
-            label_frame[n] = published(&fb[after]);
-            skips[n] = j > 0 && j < L && lab[j] != lab[j - 1];
-        }
+            for (int n = 0; n < kAtOnce; ++n) {
+                const int j = min(j0 + 64 * n, L), before = max(j - 1, 0), after = max(L - 1 - j, 0);
+                a[n] = published(&alpha[row.slot(j)]);
+                a_frame[n] = published(&fa[j]);
+                before_label[n] = published(&alpha[row.slot(before)].label);
+                before_frame[n] = published(&fa[before]);
+                blank_b[n] = published(&beta[row.slot(L - j)].blank);
+                blank_frame[n] = published(&fb[L - j]);
+                label_b[n] = published(&beta[row.slot(after)].label);
+                label_frame[n] = published(&fb[after]);
+                skips[n] = j > 0 && j < L && lab[j] != lab[j - 1];
+            }
 #pragma unroll
-        for (int n = 0; n < kAtOnce; ++n) {
-            const int j = j0 + 64 * n;
-            if (j > L) continue;
-            add(a[n].blank, a_frame[n], blank_b[n], blank_frame[n]);
-            if (j > 0) add(before_label[n], before_frame[n], blank_b[n], blank_frame[n]);
-            if (j < L) {
-                add(a[n].label, a_frame[n], label_b[n], label_frame[n]);
-                add(a[n].blank, a_frame[n], label_b[n], label_frame[n]);
-                if (skips[n]) add(before_label[n], before_frame[n], label_b[n], label_frame[n]);
+            for (int n = 0; n < kAtOnce; ++n) {
+                const int j = j0 + 64 * n;
+                if (j > L) continue;
+                int a_blank_frame = a_frame[n];
+                plain(a[n].blank, a_blank_frame, true);
+                plain(a[n].label, a_frame[n], false);
+                plain(before_label[n], before_frame[n], false);
+                plain(blank_b[n], blank_frame[n], true);
+                plain(label_b[n], label_frame[n], false);
+                add(a[n].blank, a_blank_frame, blank_b[n], blank_frame[n]);
+                if (j > 0) add(before_label[n], before_frame[n], blank_b[n], blank_frame[n]);
+                if (j < L) {
+                    add(a[n].label, a_frame[n], label_b[n], label_frame[n]);
+                    add(a[n].blank, a_blank_frame, label_b[n], label_frame[n]);
+                    if (skips[n]) add(before_label[n], before_frame[n], label_b[n], label_frame[n]);
+                }
             }
         }
-    }
+    };
+    if (__builtin_expect(some_logs, 0)) add_pairs(std::true_type{});
+    else add_pairs(std::false_type{});
     for (int d = 1; d < 64; d <<= 1) {
         const double other = __shfl_xor(sum, d);
         const int other_top = __shfl_xor(top, d), higher = max(top, other_top);
         sum = __builtin_amdgcn_ldexp(sum, max(top - higher, -2000)) + __builtin_amdgcn_ldexp(other, max(other_top - higher, -2000));
         top = higher;
     }
-    if (lane == 0) costs[u] = (before >> 16) != 0 || lost ? __uint_as_float(0x7FC00000u) : cost_of_mass(sum, top, log2_norms);
+    if (lane == 0) costs[u] = given_up ? __uint_as_float(0x7FC00000u) : cost_of_mass(sum, top, log2_norms);
 }
 
 // The word that an utterance's chains and the workgroups that wait for them share: wavefronts that have ended, wavefronts
@@ -2515,26 +2858,27 @@ __device__ __forceinline__ int lattice_body(const int chain, const Utt* __restri
     if (kMode == Mode::kGrad && threadIdx.x == 0) publish(&wk.domain[2 * u + (forward ? 0 : 1)], in_log_domain ? kDomainLog : (steep ? kDomainSteep : 0));
     if constexpr (kSync != Sync::kBarrier && kMode != Mode::kBest) {
         if (!in_log_domain) {
-            bool lost = false;
+            ChainEnd end{0, false};
             auto run = [&](auto steep_ones) __attribute__((always_inline)) {
                 constexpr bool kSteep = decltype(steep_ones)::value;
                 constexpr int kPolicy = kFused || kMode == Mode::kLoss ? kPast : 0;
                 if (two_pairs) {
                     if constexpr (kSync == Sync::kHalo) {
                         if (forward)
-                            lost = run_chain_linear2<false, kMode, kSteep, kPolicy>(m, u, gentle, labels, emit_label, lat.alpha, mass, chain_err, lds);
+                            end = run_chain_linear2<false, kMode, kSteep, kPolicy>(m, u, gentle, labels, emit_label, lat.alpha, mass, chain_err, lds);
                         else
-                            lost = run_chain_linear2<true, kMode, kSteep, kPolicy>(m, u, gentle, labels, emit_label, lat.beta, mass, chain_err, lds);
+                            end = run_chain_linear2<true, kMode, kSteep, kPolicy>(m, u, gentle, labels, emit_label, lat.beta, mass, chain_err, lds);
                     }
                 } else if (forward) {
-                    lost = run_chain_linear<false, kSync, kMode, kSteep, kPolicy>(m, u, gentle, labels, emit_label, lat.alpha, mass, chain_err, lds);
+                    end = run_chain_linear<false, kSync, kMode, kSteep, kPolicy>(m, u, gentle, labels, emit_label, lat.alpha, mass, chain_err, lds);
                 } else {
-                    lost = run_chain_linear<true, kSync, kMode, kSteep, kPolicy>(m, u, gentle, labels, emit_label, lat.beta, mass, chain_err, lds);
+                    end = run_chain_linear<true, kSync, kMode, kSteep, kPolicy>(m, u, gentle, labels, emit_label, lat.beta, mass, chain_err, lds);
                 }
             };
             if (__builtin_expect(steep, 0)) run(std::true_type{});
             else run(std::false_type{});
-            if (kMode == Mode::kLoss) finish_loss(m, u, labels, lat, mass, wk.done, costs, waves, lost);
+            if (__builtin_expect(end.unit != 0, 0)) end.lost = finish_with_exponents<kSync, kMode, kFused>(end.unit, end.lost, lds);
+            if (kMode == Mode::kLoss) finish_loss(m, u, labels, lat, mass, wk.done, costs, waves, end.lost, end.unit != 0);
             if (kFused) announce_end(&wk.done[u * kDoneStride], waves);
             return left;
         }
@@ -2565,7 +2909,7 @@ __device__ __forceinline__ void norms_of_utterance(const Utt* __restrict__ meta,
     const Norms norms = norms_of_wave(norms_of_lane(m, emit_blank));
     if ((threadIdx.x & 63) == 0) publish(&mass[u * kMassWords + kMassNorms], norms.log2());
     const bool two_pairs = kSync == Sync::kHalo && (m.flags & kUttTwoPairs) != 0;
-    finish_loss(m, u, labels, lat, mass, wk.done, costs, two_pairs ? m.waves2 : m.waves, false);
+    finish_loss(m, u, labels, lat, mass, wk.done, costs, two_pairs ? m.waves2 : m.waves, false, false);
 }
 
 // grid = one workgroup per entry of `order` (utterance * 2 + direction: 0 forward, 1 backward); cost-only launches: then those of
@@ -2590,8 +2934,9 @@ void ctc_lattice_kernel_w1(const Utt* __restrict__ meta, const int* __restrict__
         norms_of_utterance<Sync::kNone>(meta, labels, emit_blank, lat, mass, costs, wk);
         return;
     }
+    __shared__ double2 lds[kMode == Mode::kBest ? 1 : halo_lds_bytes(1) / sizeof(double2)];
     lattice_body<Sync::kNone, kMode>(order[blockIdx.x], meta, labels, emit_blank, emit_blank64, emit_label, lat,
-                                                                   mass, costs, chain_err, sink, nullptr, wk);
+                                                                   mass, costs, chain_err, sink, lds, wk);
 }
 
 // Multi-wavefront chains with the halo exchange.
@@ -2789,27 +3134,6 @@ typedef float float4v __attribute__((ext_vector_type(4)));
 typedef unsigned uint2v __attribute__((ext_vector_type(2)));
 typedef unsigned uint4v __attribute__((ext_vector_type(4)));
 
-// A record whose fields the compiler knows to be the same in every lane, wherever it was read from.
-__device__ __forceinline__ Utt uniform_record(const Utt& m)
-{
-    Utt u = m;
-    auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
-    auto uniform64 = [&](int64_t v) {
-        return static_cast<int64_t>(static_cast<uint64_t>(static_cast<unsigned>(uniform(static_cast<int>(v)))) |
-                                    (static_cast<uint64_t>(static_cast<unsigned>(uniform(static_cast<int>(v >> 32)))) << 32));
-    };
-    u.Tb = uniform(m.Tb);
-    u.L = uniform(m.L);
-    u.lab_off = uniform(m.lab_off);
-    u.flags = uniform(m.flags);
-    u.f_off = static_cast<unsigned>(uniform(static_cast<int>(m.f_off)));
-    u.e_cols = uniform(m.e_cols);
-    u.e_direct = static_cast<int16_t>(uniform(m.e_direct));
-    u.e_off = uniform64(m.e_off);
-    u.ab_off = uniform64(m.ab_off);
-    return u;
-}
-
 // alpha * beta / p of one state (without the mantissa of 1 / p) from alpha's high dword and beta, `exponents` the sum of
 // all exponents.  Either value may lie a thousand binary orders below or above the unit of its own frame (lane_frame)
 // while the product is a share of order one: alpha takes all the exponents first.  A state of any mass has beta above
@@ -2853,9 +3177,13 @@ struct LanePairs {
     int frame;
     double scale;                                        // 2^(neighbour's frame - frame)
 };
-// steep: the next renewal comes after kSteepSteps frames, otherwise after a chunk.
+// steep: the next renewal comes after kSteepSteps frames, otherwise after a chunk.  Returns whether there is a lane whose first blank, position p0's
+// going forward, p1's going backward, the new frame does not hold: it lies 2^kHeldGap below the lane's largest value, which is 2^-kFrameSlack of the frame at
+// least.  (Asked with the lane's largest exponent, which says that there is no mass, and not with the frame, since there frames without mass go anywhere.)
+constexpr int kHeldGap = 600;
+static_assert(-kFrameSlack - kHeldGap >= -1022, "normal numbers");
 template <bool kBackward>
-__device__ __forceinline__ void renew_pairs(LanePairs& s, int frame0, int frame1, bool steep)
+__device__ __forceinline__ bool renew_pairs(LanePairs& s, int frame0, int frame1, bool steep)
 {
     const double top0 = fmax(s.blank0, s.label0), top1 = fmax(s.blank1, s.label1);
     const int mine = max(top0 > 0.0 ? frame0 + __builtin_amdgcn_frexp_exp(top0) : kNoExponent,
@@ -2868,6 +3196,7 @@ __device__ __forceinline__ void renew_pairs(LanePairs& s, int frame0, int frame1
     lanes(0, kSteepSteps / 2);
     if (__builtin_expect(!steep, 1)) lanes(kSteepSteps / 2, kChunk / 2);
     window = lane_frame(window, mine);
+    const bool strained = __ballot(__builtin_amdgcn_frexp_exp(kBackward ? s.blank1 : s.blank0) + (kBackward ? frame1 : frame0) + kHeldGap < mine) != 0;
     s.blank0 = __builtin_amdgcn_ldexp(s.blank0, frame0 - window);
     s.label0 = __builtin_amdgcn_ldexp(s.label0, frame0 - window);
     s.blank1 = __builtin_amdgcn_ldexp(s.blank1, frame1 - window);
@@ -2875,6 +3204,7 @@ __device__ __forceinline__ void renew_pairs(LanePairs& s, int frame0, int frame1
     s.frame = window;
     const int neighbour = __builtin_amdgcn_update_dpp(kNoExponent, window, kBackward ? 0x130 : 0x138, 0xf, 0xf, false);
     s.scale = __builtin_amdgcn_ldexp(1.0, min(max(neighbour - window, -1100), 1023));
+    return strained;
 }
 
 // The thread's index, for parts of a tile's code that a loop goes through again (places that have been left): not known to be
@@ -2947,8 +3277,9 @@ struct BlockEnds {
 // unrolled: code that runs once per wavefront comes out of memory no faster than data.)
 // steep: the chains were steep ones, and so frames are renewed every kSteepSteps here too.  (A branch: as a variant of its own the code
 // took 20 to 59 registers more; the branch 2 to 5, and no time that can be measured.)
+// Returns false where a lane's frame does not hold its states, or a chain has left logarithms: block_shares_of_logs does such a block.
 template <int kScaleLog2, typename Emissions, typename File>
-__device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at, const BlockEnds& ends,
+__device__ __forceinline__ bool block_shares(const Utt& m, const LaneLabels& at, const BlockEnds& ends,
                                              const double packed_inverse_p, const bool steep, const int block,
                                              const int own_first, const int own_end, unsigned* s_alpha0, unsigned* s_alpha1,
                                              Emissions&& emissions, File&& file)
@@ -2957,11 +3288,12 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
     const int L = m.L, blocks = frame_blocks(m.Tb);
     const int p0 = at.p0, p1 = at.p1;
     const bool has0 = at.has0, has1 = at.has1;
-    const double skip0_one = at.skip0 ? 1.0 : 0.0, skip1_one = at.skip1 ? 1.0 : 0.0, skip2_one = at.skip2 ? 1.0 : 0.0;
+    const double skip1_one = at.skip1 ? 1.0 : 0.0;       // (skip0 and skip2 stay masks: registers)
     float el0[kChunk], el1[kChunk];
     // The order of the statements is the order of issue (run_chain_linear2): left to itself the compiler put results and
     // their uses next to each other, and a block's recomputation took 3.0 us in place of 2.0.
     auto pin = []() { __builtin_amdgcn_sched_barrier(0); };
+
 
     // alpha
     int alpha_frame0 = 0, alpha_frame1 = 0;              // of the block's two chunks
@@ -2972,24 +3304,24 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
         s.label0 = block > 0 && has0 ? ends.a0.label : 0.0;
         s.blank1 = block > 0 && has1 ? ends.a1.blank : 0.0;
         s.label1 = block > 0 && has1 ? ends.a1.label : 0.0;
-        renew_pairs<false>(s, ends.fa0, ends.fa1, steep);
+        if (__builtin_expect(renew_pairs<false>(s, ends.fa0, ends.fa1, steep), 0)) return false;
         alpha_frame0 = alpha_middle0 = s.frame;
         emissions(0, el0, el1);
 #pragma unroll 1
         for (int h = 0; h < 2; ++h) {
             if (h) {
-                renew_pairs<false>(s, s.frame, s.frame, steep);
+                if (__builtin_expect(renew_pairs<false>(s, s.frame, s.frame, steep), 0)) return false;
                 alpha_frame1 = alpha_middle1 = s.frame;
                 emissions(1, el0, el1);
             }
-            double skip0_scale = skip0_one * s.scale;
+            double skip0_scale = at.skip0 ? s.scale : 0.0;
 #pragma unroll
             for (int q = 0; q < kChunk; ++q) {
 #pragma clang fp contract(off)
                 if (q == kSteepSteps && __builtin_expect(steep, 0)) {
-                    renew_pairs<false>(s, s.frame, s.frame, steep);
+                    if (__builtin_expect(renew_pairs<false>(s, s.frame, s.frame, steep), 0)) return false;
                     (h ? alpha_middle1 : alpha_middle0) = s.frame;
-                    skip0_scale = skip0_one * s.scale;
+                    skip0_scale = at.skip0 ? s.scale : 0.0;
                 }
                 const double prev = lane_shift<false>(s.label1);
                 pin();
@@ -3025,17 +3357,18 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
     const bool last = block + 1 == blocks;
     s.blank0 = last ? (p0 == L - 1 ? 1.0 : 0.0) : (has0 ? ends.b0.blank : 0.0);
     s.label0 = !last && has0 ? ends.b0.label : 0.0;
-    s.blank1 = last ? (p1 == L - 1 ? 1.0 : 0.0) : (has1 ? ends.b1.blank : 0.0);
+    // (without a position p1 the blank of p0 once more, for renew_pairs: nothing comes of it)
+    s.blank1 = last && has1 ? (p1 == L - 1 ? 1.0 : 0.0) : (has1 ? ends.b1.blank : s.blank0);
     s.label1 = !last && has1 ? ends.b1.label : 0.0;
     const bool own0 = p0 >= own_first && p0 < own_end, own1 = p1 >= own_first && p1 < own_end;
     const int to_share = __double2loint(packed_inverse_p) + kScaleLog2;
     // A step's shares are formed during the step after it (before the first: of zeros, in a row that is filed again).
     double pending_alpha0 = 0.0, pending_alpha1 = 0.0, pending_beta0 = 0.0, pending_beta1 = 0.0;
     int pending_row = kBlockFrames - 1;
-    renew_pairs<true>(s, ends.fb0, ends.fb1, steep);
+    if (__builtin_expect(renew_pairs<true>(s, ends.fb0, has1 ? ends.fb1 : ends.fb0, steep), 0)) return false;
 #pragma unroll 1
     for (int h = 1; h >= 0; --h) {
-        if (h == 0) renew_pairs<true>(s, s.frame, s.frame, steep);
+        if (h == 0 && __builtin_expect(renew_pairs<true>(s, s.frame, s.frame, steep), 0)) return false;
         int x0, x1;
         auto set_exponents = [&](int alpha_frame) __attribute__((always_inline)) {
             const int exponents = alpha_frame + s.frame + to_share;
@@ -3043,7 +3376,7 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
             x1 = own1 ? exponents : kNoExponent;
         };
         set_exponents(h == 0 ? alpha_middle0 : alpha_middle1);
-        double skip2_scale = skip2_one * s.scale;
+        double skip2_scale = at.skip2 ? s.scale : 0.0;
         if (h == 0) emissions(2, el0, el1);              // (chunk 1's are still there)
         unsigned alpha0[kChunk], alpha1[kChunk];
 #pragma unroll
@@ -3055,9 +3388,9 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
         for (int q = kChunk - 1; q >= 0; --q) {
 #pragma clang fp contract(off)
             if (q == kSteepSteps - 1 && __builtin_expect(steep, 0)) {
-                renew_pairs<true>(s, s.frame, s.frame, steep);
+                if (__builtin_expect(renew_pairs<true>(s, s.frame, s.frame, steep), 0)) return false;
                 set_exponents(h == 0 ? alpha_frame0 : alpha_frame1);
-                skip2_scale = skip2_one * s.scale;
+                skip2_scale = at.skip2 ? s.scale : 0.0;
             }
             const double next = lane_shift<true>(s.label0);
             pin();
@@ -3107,6 +3440,97 @@ __device__ __forceinline__ void block_shares(const Utt& m, const LaneLabels& at,
         }
     }
     file(pending_row, static_cast<float>(pending_alpha0 * pending_beta0), static_cast<float>(pending_alpha1 * pending_beta1));
+    return true;
+}
+// The same in logarithms, from checkpoints of either kind.  Rare, and written to need few registers beside those of the tile: two frames at a time from
+// the last ones on, alpha from the block's start each time.  (Utterances of the linear domain: a blank's emission is its norm, and its logarithm 0.)
+template <int kScaleLog2, bool kPublished, typename File>
+__device__ __forceinline__ void block_shares_of_logs(const Utt* __restrict__ meta, const int* __restrict__ labels, const float* __restrict__ emit_label,
+                                                     const LatticeOut& lat, const double* __restrict__ mass, const int b, int block, int base,
+                                                     const int own_first, const int own_end, File&& file)
+{
+    const Utt m = uniform_record(meta[b]);
+    const int* const lab = labels + m.lab_off;
+    const double packed_inverse_p = published(&mass[b * kMassWords + kMassInverse]);
+    // (everything is read again: nothing is kept for it through block_shares, no constant either)
+    int low, high;
+    asm volatile("" : "+s"(block));
+    asm volatile("" : "+s"(base));
+    asm volatile("v_mov_b32 %0, 0\n\tv_mov_b32 %1, 0xc6300000" : "=v"(low), "=v"(high));
+    const double log0 = __hiloint2double(high, low);     // -2^100, as good as kNeg
+    const int L = m.L, p0 = base + 2 * static_cast<int>(tile_thread() & 63), p1 = p0 + 1;
+    int symbol0, symbol1, flags;                         // (in one register, not as masks in scalar ones)
+    constexpr int kHas0 = 1, kHas1 = 2, kSkip0 = 4, kSkip1 = 8, kSkip2 = 16, kOwn0 = 32, kOwn1 = 64;
+    {
+        const LaneLabels at(lab, L, base);
+        symbol0 = at.symbol0;
+        symbol1 = at.symbol1;
+        flags = (at.has0 ? kHas0 : 0) | (at.has1 ? kHas1 : 0) | (at.skip0 ? kSkip0 : 0) | (at.skip1 ? kSkip1 : 0) | (at.skip2 ? kSkip2 : 0) |
+                (p0 >= own_first && p0 < own_end ? kOwn0 : 0) | (p1 >= own_first && p1 < own_end ? kOwn1 : 0);
+    }
+    auto is = [&](int which) {
+        asm volatile("" : "+v"(flags));
+        return (flags & which) != 0;
+    };
+    constexpr int kFrames = 2, kGroups = kBlockFrames / kFrames, kChunkGroups = kChunk / kFrames;
+    auto emissions = [&](int has, int symbol, int p, int group) {
+        return *reinterpret_cast<const float2*>(emit_label + label_emission_offset(m, is(has), symbol, p, 2 * block + group / kChunkGroups, kLogZeroEmission) +
+                                                group % kChunkGroups * kFrames);
+    };
+    // the neighbour's label, log 0 at the end
+    auto from_below = [&](double v) {
+        int lo = __double2loint(log0), hi = __double2hiint(log0);
+        return shift_up(v, lo, hi);
+    };
+    auto from_above = [&](double v) {
+        const double w = lane_shift<true>(v);
+        return (tile_thread() & 63) == 63 ? log0 : w;
+    };
+    struct Logs { double b0, l0, b1, l1; };
+    auto ends_of = [&](bool backward) {
+        const BlockEnds ends = BlockEnds::load<kPublished>(m, lat, p0, block);
+        const bool none = backward ? block + 1 == frame_blocks(m.Tb) : block == 0;
+        const int first = backward ? L - 1 : 0;          // position that has the blank a recursion starts from
+        const CheckpointState s0 = backward ? ends.b0 : ends.a0, s1 = backward ? ends.b1 : ends.a1;
+        const int f0 = backward ? ends.fb0 : ends.fa0, f1 = backward ? ends.fb1 : ends.fa1;
+        const CheckpointState w0 = state_logs(s0, f0, log0), w1 = state_logs(s1, f1, log0);
+        return Logs{none ? (p0 == first ? 0.0 : log0) : (is(kHas0) ? w0.blank : log0), !none && is(kHas0) ? w0.label : log0,
+                    none ? (p1 == first ? 0.0 : log0) : (is(kHas1) ? w1.blank : log0), !none && is(kHas1) ? w1.label : log0};
+    };
+    Logs beta = ends_of(true);
+    const double to_share = static_cast<double>(__double2loint(packed_inverse_p) + kScaleLog2);
+    auto share = [&](int own, double alpha_label, double beta_label) {
+        return is(own) ? fast_exp2(static_cast<float>(fmax(alpha_label + beta_label + to_share, -1.0e4))) : 0.0f;
+    };
+#pragma unroll 1
+    for (int group = kGroups - 1; group >= 0; --group) {
+        double alpha0[kFrames], alpha1[kFrames];
+        Logs alpha = ends_of(false);
+#pragma unroll 1
+        for (int g = 0; g <= group; ++g) {
+            const float2 x0 = emissions(kHas0, symbol0, p0, g), x1 = emissions(kHas1, symbol1, p1, g);
+#pragma unroll
+            for (int q = 0; q < kFrames; ++q) {          // (unrolled: registers for alpha0 and alpha1)
+                const double prev = from_below(alpha.l1);
+                const double nb1 = lse2(alpha.b1, alpha.l0), nl1 = lse2(alpha.l1, is(kSkip1) ? nb1 : alpha.b1);
+                const double nb0 = lse2(alpha.b0, prev), nl0 = lse2(alpha.l0, is(kSkip0) ? nb0 : alpha.b0);
+                alpha = Logs{nb0, nl0 + emission_log2(q ? x0.y : x0.x), nb1, nl1 + emission_log2(q ? x1.y : x1.x)};
+                alpha0[q] = alpha.l0;
+                alpha1[q] = alpha.l1;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        const float2 x0 = emissions(kHas0, symbol0, p0, group), x1 = emissions(kHas1, symbol1, p1, group);
+#pragma unroll
+        for (int q = kFrames - 1; q >= 0; --q) {
+            const double next = from_above(beta.l0);
+            const double nb0 = lse2(beta.b0, beta.l1), nl0 = lse2(beta.l0, is(kSkip1) ? nb0 : beta.b0);
+            const double nb1 = lse2(beta.b1, next), nl1 = lse2(beta.l1, is(kSkip2) ? nb1 : beta.b1);
+            file(group * kFrames + q, share(kOwn0, alpha0[q], nl0), share(kOwn1, alpha1[q], nl1));
+            beta = Logs{nb0, nl0 + emission_log2(q ? x0.y : x0.x), nb1, nl1 + emission_log2(q ? x1.y : x1.x)};
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
 }
 // The same from the words that log-domain chains have stored for every frame, kFrames of them at a time: two, or one
 // where a second frame's registers would cost the linear domain (512 utterances 0.4 %).  512 utterances in the log domain:
@@ -3306,6 +3730,20 @@ __device__ __forceinline__ void utterance_cost(const TileArgs& g, const Utt* __r
     if ((tile_thread() & 63) == 0) g.costs[b] = ended != kEnded || published(&g.chain_err[b]) != 0 ? __uint_as_float(0x7FC00000u) : cost;
 }
 
+// The arguments of the launches with tiles (args_again): of the chains' launch, and of launches of their own.
+struct FusedArgs {
+    ChainArgs<true> chains;
+    TileArgs tiles;
+};
+struct GradientArgs {
+    TileArgs tiles;
+    const Utt* meta;
+    const int* labels;
+    const float* emit_blank;
+    const float* emit_label;
+    LatticeOut lat;
+};
+
 // Workgroup `group` of utterance b: kRowThreads / 64 wavefronts, ceil((blocks of T + 1) / (4 / wavefronts per block)) workgroups: the first
 // wavefront behind the utterance's blocks writes its cost.  (With a workgroup of its own for that, 512 x 40 to 130 frames took 43.3 us a
 // call in place of 37.2: places for workgroups are what such launches wait for.)
@@ -3431,8 +3869,10 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
             block_shares_log<kShareScaleLog2, 1>(m, lat, packed_inverse_p, block, base, own_first, own_end, file);
             product(base);
         });
-    else
+    bool strained = false;
+    if (!log_domain)
         for_pieces(L, part, sharing, [&](int base, int own_first, int own_end) {
+            if (strained) return;
             LaneLabels at = first_labels;
             if (base != first_base) {
                 at = LaneLabels(labels + m.lab_off, L, base);
@@ -3440,27 +3880,41 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
             }
             auto emissions = [&](int i, float (&el0)[kChunk], float (&el1)[kChunk]) __attribute__((always_inline)) {
                 const int h = i & 1;
-                if constexpr (!kStaged) {
-                    auto get = [](const ChunkEmissions& e, float (&el)[kChunk]) {
-                        el[0] = e.v0.x; el[1] = e.v0.y; el[2] = e.v0.z; el[3] = e.v0.w;
-                        el[4] = e.v1.x; el[5] = e.v1.y; el[6] = e.v1.z; el[7] = e.v1.w;
-                    };
-                    get(chunk_emissions(at.has0, at.symbol0, h), el0);
-                    get(chunk_emissions(at.has1, at.symbol1, h), el1);
-                    return;
-                }
-                auto row = [&](bool has, int symbol, float (&el)[kChunk]) {
-                    const float4* v = reinterpret_cast<const float4*>(s_emit + (has ? h * A + symbol : 2 * A) * kEmissionRow);
-                    const float4 x = v[0], y = v[1];
+                auto row = [&](bool has, int symbol, float (&el)[kChunk]) __attribute__((always_inline)) {
+                    float4 x, y;
+                    if constexpr (kStaged) {
+                        const float4* v = reinterpret_cast<const float4*>(s_emit + (has ? h * A + symbol : 2 * A) * kEmissionRow);
+                        x = v[0];
+                        y = v[1];
+                    } else {
+                        const ChunkEmissions e = chunk_emissions(has, symbol, h);
+                        x = e.v0;
+                        y = e.v1;
+                    }
                     el[0] = x.x; el[1] = x.y; el[2] = x.z; el[3] = x.w;
                     el[4] = y.x; el[5] = y.y; el[6] = y.z; el[7] = y.w;
                 };
                 row(at.has0, at.symbol0, el0);
                 row(at.has1, at.symbol1, el1);
             };
-            block_shares<kShareScaleLog2>(m, at, ends, packed_inverse_p, steep, block, own_first, own_end, s_hi, s_lo, emissions, file);
+            strained = !block_shares<kShareScaleLog2>(m, at, ends, packed_inverse_p, steep, block, own_first, own_end, s_hi, s_lo, emissions, file);
+            if (__builtin_expect(!strained, 1)) product(base);
+        });
+    if (__builtin_expect(strained, 0)) {
+#pragma unroll
+        for (int n = 0; n < kTiles; ++n) acc[n] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
+        for_pieces(L, part, sharing, [&](int base, int own_first, int own_end) {
+            // (read again as well)
+            if constexpr (kWait) {
+                const FusedArgs& a = args_again<FusedArgs>();
+                block_shares_of_logs<kShareScaleLog2, kWait>(a.chains.meta, a.chains.labels, a.chains.emit_label, a.chains.lat, a.tiles.mass, b, block, base, own_first, own_end, file);
+            } else {
+                const GradientArgs& a = args_again<GradientArgs>();
+                block_shares_of_logs<kShareScaleLog2, kWait>(a.meta, a.labels, a.emit_label, a.lat, a.tiles.mass, b, block, base, own_first, own_end, file);
+            }
             product(base);
         });
+    }
     if (sharing > 1) {
         // the first of the wavefronts adds up what the others have, in their order
         float4v* const s_acc = reinterpret_cast<float4v*>(s_hi);
@@ -3622,8 +4076,12 @@ void ctc_gradient_wide_kernel(const TileArgs g, const Utt* __restrict__ meta, co
                     get(k == 0 ? emit00 : k == 1 ? emit01 : chunk_emissions(at.has0, at.p0, 0), el0);
                     get(k == 0 ? emit10 : k == 1 ? emit11 : chunk_emissions(at.has1, at.p1, 0), el1);
                 };
-                block_shares<0>(m, at, ends, packed_inverse_p, domain == kDomainSteep, block, own_first, own_end, s_alpha,
-                                s_alpha + kBlockFrames * kShareRow, emissions, file);
+                if (__builtin_expect(!block_shares<0>(m, at, ends, packed_inverse_p, domain == kDomainSteep, block, own_first, own_end, s_alpha,
+                                                      s_alpha + kBlockFrames * kShareRow, emissions, file), 0))
+                {
+                    const GradientArgs& a = args_again<GradientArgs>();
+                    block_shares_of_logs<0, false>(a.meta, a.labels, a.emit_label, a.lat, a.tiles.mass, b, block, i * kPieceStep, own_first, own_end, file);
+                }
             }
             i += waves;
             if (i >= pieces) break;
@@ -3739,29 +4197,6 @@ __device__ __forceinline__ bool chains_taken(const TileArgs& g, int b, int tile)
     }
 }
 
-// The launch's arguments as they lie in memory, in the kernel's order.
-struct FusedArgs {
-    const Utt* meta;
-    const int* order;
-    const int* labels;
-    const float* emit_blank;
-    const float* emit_label;
-    LatticeOut lat;
-    double* mass;
-    float* costs;
-    int* chain_err;
-    uint32_t* sink;
-    LaunchWords wk;
-    TileArgs tiles;
-};
-// Read again from there: nothing of it is kept in registers from before.
-__device__ __forceinline__ const FusedArgs& fused_args()
-{
-    typedef __attribute__((address_space(4))) const FusedArgs* ArgsPointer;
-    ArgsPointer args = (ArgsPointer)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(args));
-    return *(const FusedArgs*)args;
-}
 
 // kLean: 128 registers, so that a compute unit holds two workgroups of more than four wavefronts and not one, while the blocks wait
 // that the chains have left behind: for up to 32 symbols (more would need a stack) and workgroups of that size (32 x 1500 frames,
@@ -3785,11 +4220,12 @@ void ctc_lattice_gradient_kernel(const Utt* __restrict__ meta, const int* __rest
         __builtin_amdgcn_s_setprio(0);
         do {
             __syncthreads();
-            const FusedArgs& a = fused_args();
-            const int tile = left - 1, rank = tile / a.tiles.groups, b = __builtin_amdgcn_readfirstlane(a.tiles.by_end[rank]);
-            narrow_tile<kTiles, true, kStaged, kLean>(a.tiles, a.meta, a.labels, a.emit_blank, a.emit_label, a.lat, fused_lds, b,
-                                             rotated_group(tile - rank * a.tiles.groups, rank, a.tiles.groups));
-            left = __builtin_amdgcn_readfirstlane(published(&a.tiles.left[tile]));
+            const FusedArgs& args = args_again<FusedArgs>();
+            const ChainArgs<true>& a = args.chains;
+            const int tile = left - 1, rank = tile / args.tiles.groups, b = __builtin_amdgcn_readfirstlane(args.tiles.by_end[rank]);
+            narrow_tile<kTiles, true, kStaged, kLean>(args.tiles, a.meta, a.labels, a.emit_blank, a.emit_label, a.lat, fused_lds, b,
+                                             rotated_group(tile - rank * args.tiles.groups, rank, args.tiles.groups));
+            left = __builtin_amdgcn_readfirstlane(published(&args.tiles.left[tile]));
         } while (left != 0);
     } else {
         const int tile = index - tiles.first_group, rank = tile / tiles.groups, group = rotated_group(tile - rank * tiles.groups, rank, tiles.groups);

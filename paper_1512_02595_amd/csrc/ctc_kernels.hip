@@ -1911,6 +1911,9 @@ static_assert(frames_last(kChunk, kRoughMinLog2, kSmoothFrames), "a chunk");
 static_assert(frames_last(kSteepSteps, kLinearMinLog2, kSteepSmoothFrames), "a steep one's steps");
 // Does a renewal leave a lane's first blank below 2^kStrained of its new frame?  (`rise`: from the frame it had.  A lane without mass has a blank of 0, whose
 // exponent reads 0.)  What is above keeps all its bits until the next renewal: 2^(kStrained + kLinearMinLog2) is above fp64's smallest normal number.
+// (The look costs, with the gradient's, renew_pairs: 64 x 750 frames, 29 symbols 45.3 -> 45.9 us a call, cost only 27.7 -> 28.6, 512 x 750 119.7 -> 122.3.
+// 24 x 750 frames of symbols held for 60 frames at 14 nats take 184 us.  Redoing the whole utterance in the log domain took 663 us where this takes 52, random
+// logits of deviation 4, which seldom strain a lane.)
 constexpr int kStrained = -900;
 static_assert(kStrained + kLinearMinLog2 >= -1022, "what a first blank of 2^kStrained gives its label");
 __device__ __forceinline__ bool strains(double first, int rise) { return __ballot(__builtin_amdgcn_frexp_exp(first) + rise < kStrained) != 0; }

@@ -1911,7 +1911,9 @@ static_assert(frames_last(kChunk, kRoughMinLog2, kSmoothFrames), "a chunk");
 static_assert(frames_last(kSteepSteps, kLinearMinLog2, kSteepSmoothFrames), "a steep one's steps");
 // Does a renewal leave a lane's first blank below 2^kStrained of its new frame?  (`rise`: from the frame it had.  A lane without mass has a blank of 0, whose
 // exponent reads 0.)  What is above keeps all its bits until the next renewal: 2^(kStrained + kLinearMinLog2) is above fp64's smallest normal number.
-// (The look costs, with the gradient's, renew_pairs: 64 x 750 frames, 29 symbols 45.3 -> 45.9 us a call, cost only 27.7 -> 28.6, 512 x 750 119.7 -> 122.3.
+// (The look costs, with the gradient's, renew_pairs: 64 x 750 frames, 29 symbols 45.9 -> 46.3 us a call, cost only 28.2 -> 28.8, 512 x 750 114.2 -> 116.0, one
+// utterance 38.8 -> 39.4: three to nine instructions more in a round of 290 to 390.  Ways out of the round itself, in place of a `count` that ends it, made the
+// compiler keep what the chains hold in memory.
 // 24 x 750 frames of symbols held for 60 frames at 14 nats take 184 us.  Redoing the whole utterance in the log domain took 663 us where this takes 52, random
 // logits of deviation 4, which seldom strain a lane.)
 constexpr int kStrained = -900;
@@ -3180,13 +3182,13 @@ struct LanePairs {
     int frame;
     double scale;                                        // 2^(neighbour's frame - frame)
 };
-// steep: the next renewal comes after kSteepSteps frames, otherwise after a chunk.  Returns whether there is a lane whose first blank, position p0's
-// going forward, p1's going backward, the new frame does not hold: it lies 2^kHeldGap below the lane's largest value, which is 2^-kFrameSlack of the frame at
-// least.  (Asked with the lane's largest exponent, which says that there is no mass, and not with the frame, since there frames without mass go anywhere.)
+// steep: the next renewal comes after kSteepSteps frames, otherwise after a chunk.  Returns by how many binary orders the lane's first blank, position p0's
+// going forward, p1's going backward, lies above the lane's largest value (negative: below).  Under -kHeldGap the new frame, which that value is 2^-kFrameSlack of
+// at least, does not hold it.  (Of the lane's largest exponent, which says that there is no mass, and not of the frame, since there frames without mass go anywhere.)
 constexpr int kHeldGap = 600;
 static_assert(-kFrameSlack - kHeldGap >= -1022, "normal numbers");
 template <bool kBackward>
-__device__ __forceinline__ bool renew_pairs(LanePairs& s, int frame0, int frame1, bool steep)
+__device__ __forceinline__ int renew_pairs(LanePairs& s, int frame0, int frame1, bool steep)
 {
     const double top0 = fmax(s.blank0, s.label0), top1 = fmax(s.blank1, s.label1);
     const int mine = max(top0 > 0.0 ? frame0 + __builtin_amdgcn_frexp_exp(top0) : kNoExponent,
@@ -3199,7 +3201,7 @@ __device__ __forceinline__ bool renew_pairs(LanePairs& s, int frame0, int frame1
     lanes(0, kSteepSteps / 2);
     if (__builtin_expect(!steep, 1)) lanes(kSteepSteps / 2, kChunk / 2);
     window = lane_frame(window, mine);
-    const bool strained = __ballot(__builtin_amdgcn_frexp_exp(kBackward ? s.blank1 : s.blank0) + (kBackward ? frame1 : frame0) + kHeldGap < mine) != 0;
+    const int held = __builtin_amdgcn_frexp_exp(kBackward ? s.blank1 : s.blank0) + (kBackward ? frame1 : frame0) - mine;
     s.blank0 = __builtin_amdgcn_ldexp(s.blank0, frame0 - window);
     s.label0 = __builtin_amdgcn_ldexp(s.label0, frame0 - window);
     s.blank1 = __builtin_amdgcn_ldexp(s.blank1, frame1 - window);
@@ -3207,7 +3209,7 @@ __device__ __forceinline__ bool renew_pairs(LanePairs& s, int frame0, int frame1
     s.frame = window;
     const int neighbour = __builtin_amdgcn_update_dpp(kNoExponent, window, kBackward ? 0x130 : 0x138, 0xf, 0xf, false);
     s.scale = __builtin_amdgcn_ldexp(1.0, min(max(neighbour - window, -1100), 1023));
-    return strained;
+    return held;
 }
 
 // The thread's index, for parts of a tile's code that a loop goes through again (places that have been left): not known to be
@@ -3280,7 +3282,9 @@ struct BlockEnds {
 // unrolled: code that runs once per wavefront comes out of memory no faster than data.)
 // steep: the chains were steep ones, and so frames are renewed every kSteepSteps here too.  (A branch: as a variant of its own the code
 // took 20 to 59 registers more; the branch 2 to 5, and no time that can be measured.)
-// Returns false where a lane's frame does not hold its states, or a chain has left logarithms: block_shares_of_logs does such a block.
+// Returns false where a lane's frame does not hold its states, or a chain has left logarithms: block_shares_of_logs does such a block.  (Asked once, at the end, with
+// the least of what the renewals have found: what such a block files before is filed again.  With a way out behind every renewal a piece's loops had 990
+// instructions in place of 880 and 840 without the question: 4 x 50 frames, 29 symbols 13.9 us a call in place of 13.7, 512 x 750 117.5 and 116.0.)
 template <int kScaleLog2, typename Emissions, typename File>
 __device__ __forceinline__ bool block_shares(const Utt& m, const LaneLabels& at, const BlockEnds& ends,
                                              const double packed_inverse_p, const bool steep, const int block,
@@ -3297,7 +3301,7 @@ __device__ __forceinline__ bool block_shares(const Utt& m, const LaneLabels& at,
     // their uses next to each other, and a block's recomputation took 3.0 us in place of 2.0.
     auto pin = []() { __builtin_amdgcn_sched_barrier(0); };
 
-
+    int held;
     // alpha
     int alpha_frame0 = 0, alpha_frame1 = 0;              // of the block's two chunks
     int alpha_middle0 = 0, alpha_middle1 = 0;            // ... from their middle on
@@ -3307,13 +3311,13 @@ __device__ __forceinline__ bool block_shares(const Utt& m, const LaneLabels& at,
         s.label0 = block > 0 && has0 ? ends.a0.label : 0.0;
         s.blank1 = block > 0 && has1 ? ends.a1.blank : 0.0;
         s.label1 = block > 0 && has1 ? ends.a1.label : 0.0;
-        if (__builtin_expect(renew_pairs<false>(s, ends.fa0, ends.fa1, steep), 0)) return false;
+        held = renew_pairs<false>(s, ends.fa0, ends.fa1, steep);
         alpha_frame0 = alpha_middle0 = s.frame;
         emissions(0, el0, el1);
 #pragma unroll 1
         for (int h = 0; h < 2; ++h) {
             if (h) {
-                if (__builtin_expect(renew_pairs<false>(s, s.frame, s.frame, steep), 0)) return false;
+                held = min(held, renew_pairs<false>(s, s.frame, s.frame, steep));
                 alpha_frame1 = alpha_middle1 = s.frame;
                 emissions(1, el0, el1);
             }
@@ -3322,7 +3326,7 @@ __device__ __forceinline__ bool block_shares(const Utt& m, const LaneLabels& at,
             for (int q = 0; q < kChunk; ++q) {
 #pragma clang fp contract(off)
                 if (q == kSteepSteps && __builtin_expect(steep, 0)) {
-                    if (__builtin_expect(renew_pairs<false>(s, s.frame, s.frame, steep), 0)) return false;
+                    held = min(held, renew_pairs<false>(s, s.frame, s.frame, steep));
                     (h ? alpha_middle1 : alpha_middle0) = s.frame;
                     skip0_scale = at.skip0 ? s.scale : 0.0;
                 }
@@ -3368,10 +3372,10 @@ __device__ __forceinline__ bool block_shares(const Utt& m, const LaneLabels& at,
     // A step's shares are formed during the step after it (before the first: of zeros, in a row that is filed again).
     double pending_alpha0 = 0.0, pending_alpha1 = 0.0, pending_beta0 = 0.0, pending_beta1 = 0.0;
     int pending_row = kBlockFrames - 1;
-    if (__builtin_expect(renew_pairs<true>(s, ends.fb0, has1 ? ends.fb1 : ends.fb0, steep), 0)) return false;
+    held = min(held, renew_pairs<true>(s, ends.fb0, has1 ? ends.fb1 : ends.fb0, steep));
 #pragma unroll 1
     for (int h = 1; h >= 0; --h) {
-        if (h == 0 && __builtin_expect(renew_pairs<true>(s, s.frame, s.frame, steep), 0)) return false;
+        if (h == 0) held = min(held, renew_pairs<true>(s, s.frame, s.frame, steep));
         int x0, x1;
         auto set_exponents = [&](int alpha_frame) __attribute__((always_inline)) {
             const int exponents = alpha_frame + s.frame + to_share;
@@ -3391,7 +3395,7 @@ __device__ __forceinline__ bool block_shares(const Utt& m, const LaneLabels& at,
         for (int q = kChunk - 1; q >= 0; --q) {
 #pragma clang fp contract(off)
             if (q == kSteepSteps - 1 && __builtin_expect(steep, 0)) {
-                if (__builtin_expect(renew_pairs<true>(s, s.frame, s.frame, steep), 0)) return false;
+                held = min(held, renew_pairs<true>(s, s.frame, s.frame, steep));
                 set_exponents(h == 0 ? alpha_frame0 : alpha_frame1);
                 skip2_scale = at.skip2 ? s.scale : 0.0;
             }
@@ -3443,7 +3447,7 @@ __device__ __forceinline__ bool block_shares(const Utt& m, const LaneLabels& at,
         }
     }
     file(pending_row, static_cast<float>(pending_alpha0 * pending_beta0), static_cast<float>(pending_alpha1 * pending_beta1));
-    return true;
+    return __ballot(held < -kHeldGap) == 0;
 }
 // The same in logarithms, from checkpoints of either kind.  Rare, and written to need few registers beside those of the tile: two frames at a time from
 // the last ones on, alpha from the block's start each time.  (Utterances of the linear domain: a blank's emission is its norm, and its logarithm 0.)

@@ -1200,13 +1200,13 @@ struct CheckpointRows {
     static constexpr unsigned kNowhere = 0x80000000u;    // (a block has fewer bytes: make_layout)
     __amdgpu_buffer_rsrc_t block;
     unsigned state_at, next_state_at, frame_at;          // in the row, of this lane's column and the one after it
-    int at, step;                                        // of the row
+    int at, next_by, step;                               // of the row
     __device__ __forceinline__ CheckpointRows(uint32_t* out, CheckpointRow row, int rows, bool stores, int column)
         : block(__builtin_amdgcn_make_buffer_rsrc(out, 0, static_cast<int>(rows * row.bytes()), 0x00020000)),
           state_at(stores ? static_cast<unsigned>(row.slot(column) * sizeof(CheckpointState)) : kNowhere),
           next_state_at(stores ? static_cast<unsigned>(row.slot(column + 1) * sizeof(CheckpointState)) : kNowhere),
           frame_at(stores ? static_cast<unsigned>(row.frames_at() + column * sizeof(int)) : kNowhere),
-          at(0), step(static_cast<int>(row.bytes()))
+          at(0), next_by(0), step(static_cast<int>(row.bytes()))
     {
     }
     __device__ __forceinline__ void drop() { state_at = next_state_at = frame_at = kNowhere; }
@@ -1225,7 +1225,12 @@ struct CheckpointRows {
     {
         __builtin_amdgcn_raw_buffer_store_b64(Words2{static_cast<unsigned>(f), static_cast<unsigned>(f)}, block, static_cast<int>(frame_at), at, kPolicy);
     }
-    __device__ __forceinline__ void next() { at += step; }
+    // (a chain stores when it begins a block; what the first one stores in the first row, the second one stores over)
+    __device__ __forceinline__ void next()
+    {
+        at += next_by;
+        next_by = step;
+    }
 };
 
 __device__ __forceinline__ CheckpointState coded_logs(double blank, double label)
@@ -1355,12 +1360,17 @@ enum class Sync { kNone, kHalo, kBarrier };
 
 static_assert(kChunk == 8, "fetch_chunk loads two float4");
 template <bool kBackward>
-__device__ __forceinline__ void fetch_chunk(const float*& p, int64_t step, float (&el)[kChunk])
+__device__ __forceinline__ void read_chunk(const float* p, float (&el)[kChunk])
 {
     const float4 lo = *reinterpret_cast<const float4*>(p), hi = *reinterpret_cast<const float4*>(p + 4);
     constexpr int kFlip = kBackward ? kChunk - 1 : 0;
     el[0 ^ kFlip] = lo.x; el[1 ^ kFlip] = lo.y; el[2 ^ kFlip] = lo.z; el[3 ^ kFlip] = lo.w;
     el[4 ^ kFlip] = hi.x; el[5 ^ kFlip] = hi.y; el[6 ^ kFlip] = hi.z; el[7 ^ kFlip] = hi.w;
+}
+template <bool kBackward>
+__device__ __forceinline__ void fetch_chunk(const float*& p, int64_t step, float (&el)[kChunk])
+{
+    read_chunk<kBackward>(p, el);
     p += step;
 }
 // Predecessor choices of a pair at one frame, as stored for the backtrace: three bits, the steps of a chunk in one word
@@ -1390,27 +1400,32 @@ struct HaloHeader {
     int gave_up;
     float cost;
     int left;                         // chains of a launch that writes the gradient too: see lattice_body
-    int always;                       // a counter that is as far as anybody asks
-    int unused;
-    int always_tag[2];                // ... and such a tag (frame, number)
 };
-// Chains with one pair per lane.
+// Log-domain chains.
 struct HaloWave {
     double2 data[kHaloEntries];
-    int frame[kHaloEntries];          // linear-domain chains: the frame exponent that goes with each entry
-                                      // (Mode::kBest: the origins, blank state's in the low half)
+    int origins[kHaloEntries];        // Mode::kBest: blank state's in the low half
     int ready;                        // last generation this wavefront has published
     int done;                         // last generation this wavefront has taken from the one below
     int unused[2];
 };
 
-// Chains with two pairs per lane (run_chain_linear2).
-constexpr int kRing = 4;                  // hand-overs a boundary's buffer holds
-constexpr int kHalo2Lanes = 16;           // most halo lanes plan_waves2 asks for
-struct Halo2Wave {
-    double2 data[kRing][kHalo2Lanes][2];      // [hand-over mod kRing][halo lane][pair]: (blank, label)
-    int2 tag[kRing][kHalo2Lanes];             // (the lane's frame, number of the hand-over)
+// Linear-domain chains: what a wavefront hands to the one above it at the end of a block, the states, frames and number of the hand-over of its upper lanes.
+// kRing blocks: now and then a wavefront has a renewal to do that takes as long as a block, each at another time, and where one could only be two
+// hand-overs ahead of the next, all of them waited for whoever was at it.
+constexpr int kRing = 4;
+template <int kPairs>
+struct LinearWave {
+    static constexpr int kLanes = 32 / kPairs;           // the widest halos (plan_waves, plan_waves2)
+    struct alignas(16) Tag { int2 word; };               // (the lane's frame, number of the hand-over; as far apart as the states, so that one address serves)
+    struct Slot {
+        double2 states[kPairs][kLanes];
+        Tag tag[kLanes];
+    } slot[kRing];                                       // of a block's end, by the block's number
 };
+// How often the wavefronts of a chain hand over: never (there is one), at every block's end, at every second one's.
+enum class Exchange { kNone, kBlock, kTwoBlocks };
+
 // What a wavefront had when it left the recursion on probabilities (finish_with_exponents): a lane's states and frame (kLogs: they are logarithms).
 // (In LDS, from where they are read again: as values that leave the loop from a dozen places they took more registers than there are.  So the wavefront goes
 // on to the end of the loop's round, its stores going nowhere.)
@@ -1418,7 +1433,7 @@ struct StrainedWave {
     double2 states[2][64];
     int frame[64];
 };
-constexpr size_t kExchangeBytes = sizeof(HaloWave) > sizeof(Halo2Wave) ? sizeof(HaloWave) : sizeof(Halo2Wave);
+constexpr size_t kExchangeBytes = std::max({sizeof(HaloWave), sizeof(LinearWave<1>), sizeof(LinearWave<2>)});
 constexpr size_t kHaloWaveBytes = kExchangeBytes + sizeof(StrainedWave);
 static_assert(sizeof(HaloHeader) % 16 == 0 && kExchangeBytes % 16 == 0 && kHaloWaveBytes % 16 == 0, "the blocks hold 16-byte entries");
 // Bytes of dynamic LDS of a lattice launch whose workgroups have `waves` wavefronts.
@@ -1469,11 +1484,10 @@ __device__ __forceinline__ StrainedWave* strained_wave(void* lds, int wave)
 // An error at lane 0 (whose neighbour is missing) moves up one lane per step, so the lanes
 // from `halo` on stay exact for `halo` steps.  Every `halo` steps (a whole number of chunks)
 // the lower wavefront hands
-// over the exact state of those pairs through LDS (a small ring per boundary, guarded by two
-// counters: `ready` written by the producer after the data, `done` by the consumer after its
-// read).  No barrier; the wavefronts run skewed.  A wavefront waits for data only on lower
+// over the exact state of those pairs through LDS.  No barrier; the wavefronts run skewed.  A wavefront waits for data only on lower
 // ones and for space only on higher ones, wavefront 0 needs no data and the last one no space,
 // so every wait ends; a poll budget bounds them regardless and raises chain_err when spent.
+// (Here two counters guard a boundary's buffer: `ready` written by the producer after the data, `done` by the consumer after its read.  Linear-domain chains: HandOvers.)
 template <bool kBackward, Sync kSync, Mode kMode>
 __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const int* __restrict__ labels,
                                           const float* __restrict__ emit_blank, const double* __restrict__ emit_blank64,
@@ -1579,7 +1593,7 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
             }
             if (lane >= 64 - halo) {
                 wr_base[half] = make_double2(v_blank, v_label);
-                if (kMode == Mode::kBest) mine_lds->frame[half + lane - (64 - halo)] = blank_origin | label_origin << 16;
+                if (kMode == Mode::kBest) mine_lds->origins[half + lane - (64 - halo)] = blank_origin | label_origin << 16;
             }
             // LDS operations of a wavefront complete in order: the counter follows the data.
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1589,7 +1603,7 @@ __device__ __forceinline__ void run_chain_log(const Utt m, const int u, const in
         if (wave > 0) {
             // Counter and data are read back to back; the data count only if the counter,
             // read first, already showed this generation.
-            const int* const rd_origin = &below_lds->frame[half + (lane < halo ? lane : 0)];
+            const int* const rd_origin = &below_lds->origins[half + (lane < halo ? lane : 0)];
             int ready = counter(low_ready);
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             double2 v = rd_base[half];
@@ -1885,28 +1899,39 @@ __device__ __forceinline__ const Args& args_again()
 //
 // Storage (Mode::kGrad): the whole state after every block (see "lattice storage").
 //
-// What a step costs (a lone wavefront of a chain issues an instruction every 4.1 clocks): 7 instructions, 12 where a lane owns
-// two pairs.  With the blank's emissions as scalars it was 9 and 14, and they had to be fetched and waited for; with a renewal
-// at every chunk and hand-overs of 570 clocks the steps of a 750-frame utterance took, in ns, labels of 40 / 150 / 190 / 240 /
-// 420 symbols: 32.8 / 40.6 / 45.5 / 49.5 / 52.3; now 17.9 / 24.3 / 30.3 / 35.3 / 43.2.
+// What a step costs (a lone wavefront of a chain issues an instruction every five clocks, whatever it is): 7 instructions and 35 clocks, 12 and 60
+// where a lane owns two pairs; the rest is what a block's end adds.  Clocks a step (2.4 GHz) of the last wavefront, 750 frames, alone on the chip, labels of 40 / 127 /
+// 190 / 240 / 420 symbols: 48 / 69 / 85 / 98 / 134 when a hand-over took 550 clocks, a look at the frames 100 and a checkpoint 110; so 44 / 59 / 71 / 93 / 111.
 constexpr int kFrameSlack = 390, kFrameDrop = 370;
 __device__ __forceinline__ int lane_frame(int window_top, int own_top)
 {
     return window_top - min(max(window_top - own_top - kFrameSlack, 0), kFrameDrop);
 }
-// A renewal (about 250 clocks, a chunk's eight steps 240) is put off while it is not needed: every lane with mass has its largest
-// value within [2^kEasyLow, 2^kEasyHigh] of its frame, and no frame lies more than kSmoothFrames a pair below the frame of the
+// A renewal (about 300 clocks, with what else is unusual at a block's end up to 900; a chunk's eight steps 300) is put off while it is not needed: every lane with
+// mass has its largest value within [2^kEasyLow, 2^kEasyHigh] of its frame, and no frame lies more than kSmoothFrames a pair below the frame of the
 // lane below it.  Until the next look, after n steps with ratios within 2^-g .. 2^g, a value is at least 2^(kEasyLow - n g), and
-// at most 2^(kEasyHigh + n (kSmoothFrames + g + 1.6)).  A chunk, g = 79: 2^-982 and 2^936; a block, where all probabilities of the
-// utterance are above 2^kGentleMinLog2 (g = 32): 2^-862 and 2^1021; kSteepSteps, g = 100, kSteepSmoothFrames: 2^-750 and 2^1005.
+// at most 2^(kEasyHigh + n (kSmoothFrames + g + 1.6)).  A chunk, g = 79: 2^-982 and 2^936; kSteepSteps, g = 100, kSteepSmoothFrames: 2^-750 and 2^1005.
+// Where all probabilities of the utterance are above 2^kGentleMinLog2 (g = 32) the look is taken kLookAhead steps before the chunk ends, and the range is wider.  (Looked at
+// after blocks of 16 frames, what is admissible is so narrow that the lanes above the front of the lattice renewed at every second block.)
+// Where the renewal puts the largest value of a window: 2^kHeadroom below its frame, as values grow more often than they shrink.
+constexpr int kHeadroom = 100;
+__device__ __forceinline__ int chain_frame(int window_top, int own_top)
+{
+    return window_top + kHeadroom - min(max(window_top - own_top - (kFrameSlack - kHeadroom), 0), kFrameDrop + kHeadroom);
+}
+constexpr int kLookAhead = 1;
 constexpr int kEasyLow = -350, kEasyHigh = 99;
 constexpr int kSmoothFrames = 24, kSteepSmoothFrames = 125;
-constexpr bool frames_last(int steps, float min_log2, int smooth)
+// Gentle utterances.  States handed up are taken into the frames of the lanes that take them where those are no more than kShiftUp below and kShiftDown above the frames that they
+// come in: a chunk later 2^-1018 and 2^966 at worst.  (In the frames that they come in, all factors between frames had to be made anew whenever a wavefront below had renewed its own.)
+constexpr int kGentleLow = -450, kGentleHigh = 120, kGentleSmooth = 36;
+constexpr int kShiftUp = 220, kShiftDown = 280;
+constexpr bool frames_last(int steps, float min_log2, int smooth, int low = kEasyLow, int high = kEasyHigh)
 {
     const float small = steps * min_log2, large = steps * (1.6f - min_log2);
-    return small - kFrameSlack >= -1022 && kFrameDrop + large < 1023 && kEasyLow + small >= -1022 && kEasyHigh + large + steps * smooth < 1023;
+    return small - kFrameSlack >= -1022 && kFrameDrop + large < 1023 && low + small >= -1022 && high + large + steps * smooth < 1023;
 }
-static_assert(frames_last(kBlockFrames, kGentleMinLog2, kSmoothFrames), "a block");
+static_assert(frames_last(kChunk + kLookAhead, kGentleMinLog2, kGentleSmooth, kGentleLow - kShiftDown, kGentleHigh + kShiftUp), "a gentle one's chunk");
 static_assert(frames_last(kChunk, kRoughMinLog2, kSmoothFrames), "a chunk");
 static_assert(frames_last(kSteepSteps, kLinearMinLog2, kSteepSmoothFrames), "a steep one's steps");
 // Does a renewal leave a lane's first blank below 2^kStrained of its new frame?  (`rise`: from the frame it had.  A lane without mass has a blank of 0, whose
@@ -1919,13 +1944,20 @@ static_assert(frames_last(kSteepSteps, kLinearMinLog2, kSteepSmoothFrames), "a s
 constexpr int kStrained = -900;
 static_assert(kStrained + kLinearMinLog2 >= -1022, "what a first blank of 2^kStrained gives its label");
 __device__ __forceinline__ bool strains(double first, int rise) { return __ballot(__builtin_amdgcn_frexp_exp(first) + rise < kStrained) != 0; }
-// The test, on the high dword of the largest value of a lane (biased exponent in bits 20..30): one
-// subtraction and one unsigned compare; zero, denormals, infinities and NaN fail it.
-__device__ __forceinline__ bool outside_easy_range(double top)
-{
-    const unsigned hi = static_cast<unsigned>(__double2hiint(top));
-    return hi - (static_cast<unsigned>(1023 + kEasyLow) << 20) >= (static_cast<unsigned>(kEasyHigh - kEasyLow + 1) << 20);
-}
+// The test, on the exponent of the largest value of a lane: one subtraction and one unsigned compare.  Lanes without mass pass it.
+struct EasyRange {
+    int low, width, smooth;                              // smooth: for a pair
+    __device__ __forceinline__ EasyRange(bool gentle, bool steep)
+        : low(gentle ? kGentleLow : kEasyLow), width(gentle ? kGentleHigh - kGentleLow : kEasyHigh - kEasyLow),
+          smooth(gentle ? kGentleSmooth : (steep ? kSteepSmoothFrames : kSmoothFrames))
+    {
+    }
+    __device__ __forceinline__ bool outside(double top) const
+    {
+        static_assert(kEasyLow < -1 && kEasyHigh > 0 && kGentleLow < -1 && kGentleHigh > 0, "zero, whose exponent reads 0, is in it");
+        return static_cast<unsigned>(__builtin_amdgcn_frexp_exp(top) - 1 - low) > static_cast<unsigned>(width);
+    }
+};
 
 // A forward chain's end: p = value * 2^frame.
 __device__ __forceinline__ void publish_mass(double* mass, double value, int frame)
@@ -1944,8 +1976,9 @@ struct ChainEnd {
 // A chain's frames; kPairs pairs to a lane.
 template <int kPairs, bool kSteep>
 struct ChainFrames {
-    static constexpr int kSmooth = kPairs * (kSteep ? kSteepSmoothFrames : kSmoothFrames);
-    static constexpr int kSteps = (kSteep ? kSteepSteps : kChunk) / kPairs;     // lanes that mass moves up until the next look at worst
+    static constexpr int kSteps = (kSteep ? kSteepSteps : kChunk) / kPairs;     // lanes that mass moves up in a chunk at worst
+    const EasyRange easy;
+    __device__ __forceinline__ explicit ChainFrames(bool gentle) : easy(gentle, kSteep) {}
     int frame = 0;
     double scale = 1.0;                                  // 2^(frame of the lane below - frame)
     unsigned long long rough = ~0ull;                    // lanes that may not put a renewal off: see rescale
@@ -1956,7 +1989,8 @@ struct ChainFrames {
         const int down = __builtin_amdgcn_update_dpp(kNoExponent, frame, 0x138, 0xf, 0xf, false) - frame;
         // 2^1023 is the largest factor there is; a pair that far below its neighbour has been rounded away already.
         scale = __builtin_amdgcn_ldexp(1.0, min(max(down, -1100), 1023));
-        rough = __ballot(down > kSmooth) | (__ballot(down < -kSmooth) & massless & ~1ull);       // (lane 0 has nothing below)
+        const int smooth = kPairs * easy.smooth;
+        rough = __ballot(down > smooth) | (__ballot(down < -smooth) & massless & ~1ull);       // (lane 0 has nothing below)
     }
     // The frames after a renewal; returns what the lane's values are to be scaled by.  `top`: the largest of them.  Lanes above the highest one with mass take that one's frame, so that the front of the lattice
     // passes through a wavefront like anything else; where no lane has mass, `reference`'s.
@@ -1968,7 +2002,7 @@ struct ChainFrames {
         int window = mine;
 #pragma unroll
         for (int k = 0; k < kSteps; ++k) window = window_max_step(window, mine);
-        int next = massive != 0 ? lane_frame(window, mine) : frame;
+        int next = massive != 0 ? chain_frame(window, mine) : frame;
         const int front = massive != 0 ? 63 - __builtin_clzll(massive) : reference;
         const int beyond = __builtin_amdgcn_readlane(next, front);
         next = static_cast<int>(threadIdx.x & 63) > front ? beyond : next;
@@ -1978,24 +2012,158 @@ struct ChainFrames {
         return rise;
     }
     // Is a renewal due?  (A lane without mass is where it should be unless it is rough.)
-    __device__ __forceinline__ bool renewal_due(double top) const
+    __device__ __forceinline__ bool renewal_due(double top) const { return (__ballot(easy.outside(top)) | rough) != 0; }
+};
+
+// The hand-overs of a linear-domain chain of several wavefronts (what they are for: see above run_chain_log), at the ends of blocks.  What decides their cost is how
+// many instructions they take, as anywhere in a chain, and that nothing is waited for.  A wavefront asks for what the one below it has left some steps before its block
+// ends, and compares before the last step: the halo's lanes whether they have read the number of this hand-over beside their states and whether the
+// frame is near enough to theirs to take these by a shift, lane 63, in the tag of the wavefront above, whether what is about to be overwritten has been taken
+// (a number is published when that hand-over has been taken from below as well).  Where any lane says no, or one is due for a renewal, the block's end is
+// unusual: whoever has asked too early asks again until it is there, and then waits a little more, so as not to be early at every block from then on;
+// frames are taken over from below; frames are renewed.  LDS operations of a wavefront complete in order: a tag is read before the states, and written after
+// them.  (A hand-over took 550 clocks when it was asked for at the block's end, two counters one after the other, and made all factors between frames anew; now 180.
+// Unusual ends: 2 of 47 in the lowest wavefront of a label of 190 symbols, 10 in the highest.)
+constexpr int kSlack = 2;                                // (s_sleep: 64 clocks each)
+constexpr int kAskAhead = 5, kAskAhead2 = 4;             // steps before the block's end, with one pair to a lane and with two
+template <int kPairs, Exchange kExchange>
+struct HandOvers {
+    static constexpr int kNever = 0x7FFFFFFF, kLeft = 1 << 30;
+    typedef LinearWave<kPairs> Wave;
+    typedef typename Wave::Slot Slot;
+    const char *in, *out;                                // in the first slot: what this lane takes (its tag: looks at), what it hands up
+    bool takes, hands;                                   // this lane is one of the halo's; of the ones above's
+    int behind;                                          // by how much the tag that it reads may be behind the hand-over
+    unsigned shift;                                      // ... and its frame differ
+    int number = 2;                                      // of the coming hand-over, times two, and one more where states are due for a renewal (kLeft: the chain has been left)
+    unsigned round = 0;                                  // the first slot of this round of blocks, in bytes
+    int2 tag{};
+    double2 states[kPairs] = {};
+    unsigned long long late = 0, shifted = 0;
+    __device__ __forceinline__ HandOvers(void* lds, int wave, int last_wave, int halo)
     {
-        return ((__ballot(outside_easy_range(top)) & __ballot(top > 0.0)) | rough) != 0;
+        const int lane = threadIdx.x & 63, first = 64 - halo;
+        takes = wave > 0 && lane < halo;
+        hands = lane >= first;
+        const bool looks_up = wave < last_wave && lane == 63;
+        in = reinterpret_cast<const char*>(&halo_wave<Wave>(lds, looks_up ? wave + 1 : (wave > 0 ? wave - 1 : 0))->slot[0].states[0][takes ? lane : (looks_up ? halo - 1 : 0)]);
+        out = reinterpret_cast<const char*>(&halo_wave<Wave>(lds, wave)->slot[0].states[0][hands ? lane - first : 0]);
+        behind = takes ? 0 : (looks_up ? 2 * (kExchange == Exchange::kBlock ? kRing : kRing / 2) : kNever);
+        shift = takes ? kShiftDown + kShiftUp : ~0u;
+        asm volatile("" : "+v"(number));                 // (in a vector register, from where it is stored)
+    }
+    // A lane's states and tag in the slot of this round's block `block`.
+    __device__ __forceinline__ double2* states_at(const char* lane, int block, int pair) const
+    {
+        return const_cast<double2*>(reinterpret_cast<const double2*>(lane + round + block * sizeof(Slot) + pair * Wave::kLanes * sizeof(double2)));
+    }
+    __device__ __forceinline__ unsigned long long* tag_at(const char* lane, int block) const
+    {
+        return const_cast<unsigned long long*>(reinterpret_cast<const unsigned long long*>(lane + round + block * sizeof(Slot) + offsetof(Slot, tag)));
+    }
+    // (from then on nobody hears of this wavefront through here)
+    __device__ __forceinline__ void leave()
+    {
+        number = kLeft;
+        hands = false;
+    }
+    __device__ __forceinline__ void ask(int block)
+    {
+        const unsigned long long w = __hip_atomic_load(tag_at(in, block), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        tag = make_int2(static_cast<int>(w), static_cast<int>(w >> 32));
+#pragma unroll
+        for (int k = 0; k < kPairs; ++k) states[k] = *states_at(in, block, k);
+    }
+    // What has been asked for is there now.  (Else it would be waited for where it is used, and what has been stored since with it.)
+    __device__ __forceinline__ void arrive()
+    {
+#pragma unroll
+        for (int k = 0; k < kPairs; ++k) asm volatile("" : "+v"(states[k].x), "+v"(states[k].y));
+    }
+    // Lanes that have not read what the next hand-over needs, or take states that are due for a renewal (a tag further than this
+    // hand-over's); lanes that take states in a frame far from their own.
+    __device__ __forceinline__ void look(int frame)
+    {
+        late = __ballot(static_cast<unsigned>(number - tag.y) > static_cast<unsigned>(behind));
+        shifted = __ballot(static_cast<unsigned>(tag.x - frame + kShiftDown) > shift);
+        arrive();
+    }
+    // Where any are: waits for what is late, and gives the lanes that take states the frames of those.  due: so are the states handed up (whoever takes them
+    // renews as well).
+    __device__ __forceinline__ void prepare(int block, bool due, int& frame, int& budget, bool& lost)
+    {
+        if (__builtin_amdgcn_readfirstlane(number) >= kLeft) return;
+        auto waits = [&]() { return __ballot(number - tag.y > behind) != 0; };
+        if (waits()) {
+            bool still = true;
+            for (; still && budget > 0; --budget) {
+                ask(block);
+                still = waits();
+            }
+            arrive();
+            lost = lost || still;
+            __builtin_amdgcn_s_sleep(kSlack);
+        }
+        frame = takes ? tag.x : frame;
+        number += due ? 1 : 0;
+    }
+    __device__ __forceinline__ void publish(int block, const double2 (&mine)[kPairs], int frame)
+    {
+        if (hands) {
+#pragma unroll
+            for (int k = 0; k < kPairs; ++k) *states_at(out, block, k) = mine[k];
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __hip_atomic_store(tag_at(out, block), (static_cast<unsigned long long>(static_cast<unsigned>(number)) << 32) | static_cast<unsigned>(frame),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        number += 2;
+    }
+    __device__ __forceinline__ void next_round() { round ^= 2 * sizeof(Slot); }
+};
+static_assert(kRing == 4, "two rounds of two blocks");
+
+// Where a linear-domain chain is in its emissions: what moves is the same for all lanes, and so in scalar registers.  Pairs from L on, which have no label state,
+// read what pair L - 1 reads: what they then hold moves up only, past the end of the label.  (Reading a constant 0 took them a pointer and a step of their own,
+// in vector registers, and a 64-bit addition of all lanes a chunk and pair.)  An empty label's read constants.
+template <bool kBackward>
+struct ChainEmissions {
+    const float* emit_label;
+    int64_t chunk, step;
+    __device__ __forceinline__ ChainEmissions(const Utt& m, const float* __restrict__ emit_label)
+        : emit_label(emit_label), chunk(label_emission_offset(m, m.L > 0, 0, 0, chain_chunk(0, 2 * frame_blocks(m.Tb), kBackward), kZeroEmission)),
+          step(label_emission_step(m, m.L > 0, kBackward))
+    {
+    }
+    // The column of pair j, in bytes.
+    __device__ __forceinline__ unsigned column(const Utt& m, const int* __restrict__ lab, int j) const
+    {
+        const int in_order = min(j, m.L - 1), position = kBackward ? m.L - 1 - in_order : in_order;
+        return m.L > 0 ? static_cast<unsigned>((m.e_direct == kEmitSymbols ? lab[position] : position) * kChunk * static_cast<int>(sizeof(float))) : 0u;
+    }
+    __device__ __forceinline__ void read(unsigned column, float (&el)[kChunk]) const
+    {
+        read_chunk<kBackward>(reinterpret_cast<const float*>(reinterpret_cast<const char*>(emit_label + chunk) + column), el);
+    }
+    __device__ __forceinline__ void next()
+    {
+        chunk += step;
+        asm volatile("" : "+s"(chunk));                  // (or a round's chunks are counted from its first)
     }
 };
 
 // kPolicy: of the checkpoints' stores, kPast where another workgroup of the launch reads them.
-template <bool kBackward, Sync kSync, Mode kMode, bool kSteep, int kPolicy>
+template <bool kBackward, Exchange kHandsOver, Mode kMode, bool kSteep, int kPolicy>
 __device__ __forceinline__ ChainEnd run_chain_linear(const Utt m, const int u, const bool gentle, const int* __restrict__ labels,
                                                  const float* __restrict__ emit_label, uint32_t* __restrict__ out,
                                                  double* __restrict__ mass, int* __restrict__ chain_err, void* lds)
 {
-    static_assert(kSync != Sync::kBarrier, "the barrier kernel runs the log-domain chain");
     static_assert(kMode != Mode::kBest, "the maximum recursion runs in the log domain");
+    constexpr bool kExchange = kHandsOver != Exchange::kNone;
     const int L = m.L, chunks = 2 * frame_blocks(m.Tb);
     int count = kMode == Mode::kLoss ? chain_chunks(m.Tb, kBackward) : chunks;     // chunks of this chain; -unit once it has been left
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (uniform: in a scalar register)
-    int halo = (kSync == Sync::kHalo) ? m.halo : 0;      // (0 once the chain has been left: nothing is handed up)
+    const int halo = kExchange ? m.halo : 0;
     const int j = wave * (64 - halo) + lane;             // pair of this lane (see run_chain_log)
     const int* lab = labels + m.lab_off;
     const bool has_label = j >= 0 && j < L;
@@ -2003,92 +2171,21 @@ __device__ __forceinline__ ChainEnd run_chain_linear(const Utt m, const int u, c
     const int li = kBackward ? (L - 1 - j) : j;
     const bool skip_ok = has_label && j >= 1 && lab[li] != lab[kBackward ? (li + 1) : (li - 1)];
 
-    // A lane without a label state reads a constant probability 0 and stays there.
-    const float* ep = emit_label + label_emission_offset(m, has_label, has_label ? lab[li] : 0, li,
-                                                         chain_chunk(0, chunks, kBackward), kZeroEmission);
-    const int64_t estep = label_emission_step(m, has_label, kBackward);
+    ChainEmissions<kBackward> emissions(m, emit_label);
+    const unsigned column = emissions.column(m, lab, j);
     // Checkpoints.  (Cost only: one row, by pair, in the chain's own order.)
     CheckpointRows rows(out + m.ab_off, CheckpointRow{lattice_pitch(L)}, kMode == Mode::kGrad ? frame_blocks(m.Tb) - 1 : 1,
                         kMode == Mode::kGrad ? active && has_label : active, kMode == Mode::kGrad ? li + 1 : j);
 
     const int last_wave = m.waves - 1;
-    HaloWave* const mine_lds = halo_wave<HaloWave>(lds, wave);
-    HaloWave* const below_lds = halo_wave<HaloWave>(lds, wave > 0 ? wave - 1 : 0);
-    HaloWave* const above_lds = halo_wave<HaloWave>(lds, wave < last_wave ? wave + 1 : wave);
     int budget = m.poll_budget;
     bool lost = false;
-    const bool every_block = halo < 2 * kBlockFrames;    // hand over after every block, or after every second one
+    HandOvers<1, kHandsOver> with(kExchange ? lds : nullptr, wave, last_wave, halo);
     const unsigned long long look = gentle && !kSteep ? 0ull : ~0ull;      // once a chunk, whatever the frames
-    int generation = 0;
-    int half = 0;
-    const int wr_slot = lane >= 64 - halo ? lane - (64 - halo) : 0;
-    const int rd_slot = lane < halo ? lane : 0;
-    double2* const wr_base = (kSync == Sync::kHalo) ? &mine_lds->data[wr_slot] : nullptr;
-    const double2* const rd_base = (kSync == Sync::kHalo) ? &below_lds->data[rd_slot] : nullptr;
-    int* const wr_frame = (kSync == Sync::kHalo) ? &mine_lds->frame[wr_slot] : nullptr;
-    const int* const rd_frame = (kSync == Sync::kHalo) ? &below_lds->frame[rd_slot] : nullptr;
-    // (at the ends: nobody to wait for.  `nil`: addresses in vector registers, where they are needed)
-    int nil = 0;
-    asm volatile("" : "+v"(nil));
-    int* const always = &static_cast<HaloHeader*>(lds)->always + nil;
-    int* my_ready = &mine_lds->ready + nil;
-    int* const up_ready = wave < last_wave ? &above_lds->ready + nil : always;
-    int* const low_ready = wave > 0 ? &below_lds->ready + nil : always;
-    const bool from_below = wave > 0 && lane < halo;
 
     double v_blank = (j == 0) ? 1.0 : 0.0, v_label = 0.0;
-    ChainFrames<1, kSteep> f;
+    ChainFrames<1, kSteep> f(gentle && !kSteep);
     double skip_scale = skip_ok ? 1.0 : 0.0;             // f.scale where the label may be entered from the label of the pair below
-
-    auto counter = [&](int* p) {
-        return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    };
-    auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
-    int up_seen = 0;
-    // Hand-over g: what comes from below is asked for first and used last; passing the own state up fills the time.  A wavefront
-    // publishes g when it has taken g itself, so that the one below knows from the same counter which half of the buffer is
-    // free.  An entry carries the pair's frame as well.
-    auto hand_over = [&]() __attribute__((always_inline)) {
-        ++generation;
-        half ^= 32;
-        int ready = counter(low_ready);
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        double2 v = rd_base[half];
-        int vf = rd_frame[half];
-        int seen = uniform(up_seen);
-        if (__builtin_expect(seen < generation - 2, 0)) {
-            while (seen < generation - 2 && budget > 0) {
-                --budget;
-                seen = uniform(counter(up_ready));
-            }
-            lost = lost || seen < generation - 2;
-        }
-        if (lane >= 64 - halo) {
-            wr_base[half] = make_double2(v_blank, v_label);
-            wr_frame[half] = f.frame;
-        }
-        ready = uniform(ready);
-        if (__builtin_expect(ready < generation, 0)) {
-            while (ready < generation && budget > 0) {
-                --budget;
-                ready = counter(low_ready);
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                v = rd_base[half];
-                vf = rd_frame[half];
-                ready = uniform(ready);
-            }
-            lost = lost || ready < generation;
-        }
-        // (LDS operations of a wavefront complete in order: the counter follows the data, and the reads)
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        if (lane == 63) __hip_atomic_store(my_ready, generation, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        up_seen = counter(up_ready);
-        v_blank = from_below ? v.x : v_blank;
-        v_label = from_below ? v.y : v_label;
-        f.frame = from_below ? vf : f.frame;
-        f.rescale(__ballot(!(fmax(v_blank, v_label) > 0.0)));    // (the halo lanes come back with other frames)
-        skip_scale = skip_ok ? f.scale : 0.0;
-    };
 
     // Label value of pair j-1 after the last step, in that pair's frame (0 for pair 0: the shift
     // leaves lane 0 what it had).
@@ -2103,8 +2200,7 @@ __device__ __forceinline__ ChainEnd run_chain_linear(const Utt m, const int u, c
         w->states[0][lane] = make_double2(v_blank, v_label);
         w->frame[lane] = frame;
         rows.drop();
-        halo = 0;
-        if (kSync == Sync::kHalo) my_ready = &mine_lds->done + nil;
+        with.leave();
     };
     auto renew_frames = [&](int unit) __attribute__((always_inline)) {
         const int rise = f.renew(top_value(), halo > 0 ? halo - 1 : 0);
@@ -2116,14 +2212,37 @@ __device__ __forceinline__ ChainEnd run_chain_linear(const Utt m, const int u, c
 
     // After a block's first chunk (steep: and in the middle of every chunk), and after a block.
     static_assert(kChunk == 2 * kSteepSteps, "the middle of a chunk");
-    auto mid_block = [&](int unit) __attribute__((always_inline)) {
-        if (__builtin_expect((f.rough | look) != 0, 0))
-            if (f.renewal_due(top_value())) renew_frames(unit);
+    auto renew_if_due = [&](int unit) __attribute__((always_inline)) {
+        if (f.renewal_due(top_value())) renew_frames(unit);
     };
-    auto end_block = [&](bool second, int unit) __attribute__((always_inline)) {
-        if (kSync == Sync::kHalo)
-            if (second || every_block) hand_over();
-        if (__builtin_expect(f.renewal_due(top_value()), 0)) renew_frames(unit);
+    // Before a block's last kLookAhead steps: may its end be the ordinary one?  (A comparison's result is on its way to a branch for some 20 clocks.)
+    unsigned long long outside = 0;
+    auto look_ahead = [&](bool exchange) __attribute__((always_inline)) {
+        outside = __ballot(f.easy.outside(top_value()));
+        if (exchange) with.look(f.frame);
+    };
+    auto end_block = [&](int block, bool exchange, int unit) __attribute__((always_inline)) {
+        const bool unusual = (outside | f.rough | look | (exchange ? with.late | with.shifted : 0ull)) != 0;
+        if (exchange && __builtin_expect(unusual, 0)) with.prepare(block, f.renewal_due(top_value()), f.frame, budget, lost);
+        if (exchange) {
+            const double2 mine[1] = {make_double2(v_blank, v_label)};
+            with.publish(block, mine, f.frame);
+            if (with.takes) {
+                const int shift = with.tag.x - f.frame;
+                v_blank = __builtin_amdgcn_ldexp(with.states[0].x, shift);
+                v_label = __builtin_amdgcn_ldexp(with.states[0].y, shift);
+                asm volatile("" : "+v"(v_blank), "+v"(v_label));      // (a mask, and not a choice for each)
+            }
+        }
+        if (__builtin_expect(unusual, 0)) {
+            const double top = top_value();
+            if (exchange) {
+                with.number &= ~1;
+                f.rescale(__ballot(!(top > 0.0)));
+                skip_scale = skip_ok ? f.scale : 0.0;
+            }
+            if (f.renewal_due(top)) renew_frames(unit);
+        }
     };
     auto checkpoint = [&]() __attribute__((always_inline)) {
         rows.template state<kPolicy>(0, CheckpointState{v_blank, v_label});
@@ -2156,22 +2275,26 @@ __device__ __forceinline__ ChainEnd run_chain_linear(const Utt m, const int u, c
     float el[4][kChunk];
     auto fetch = [&](auto set, int) __attribute__((always_inline)) {
         constexpr int k = decltype(set)::value;
-        fetch_chunk<kBackward>(ep, estep, el[k]);
+        emissions.read(column, el[k]);
+        emissions.next();
         __builtin_amdgcn_sched_barrier(0);
     };
     auto run = [&](auto set, int i) __attribute__((always_inline)) {
         constexpr int k = decltype(set)::value;
+        constexpr bool kEnds = (k & 1) != 0;             // the chunk ends a block
+        constexpr bool kHere = kEnds && kExchange && (k == 3 || kHandsOver == Exchange::kBlock);
+        if (kMode == Mode::kGrad && !kEnds) checkpoint();
         double el_d = static_cast<double>(el[k][0]);
 #pragma unroll
         for (int q = 0; q < kChunk; ++q) {
             advance(el_d, el[k][q + 1 < kChunk ? q + 1 : q]);
-            if (kSteep && q == kSteepSteps - 1) mid_block(2 * i + 1);
+            if (kSteep && q == kSteepSteps - 1) renew_if_due(2 * i + 1);
+            if (kHere && q == kChunk - 1 - kAskAhead) with.ask(k >> 1);
+            if (q == kChunk - 1 - kLookAhead) look_ahead(kHere);
         }
-        if (!(k & 1)) mid_block(2 * i + 2);
-        else {
-            end_block(k == 3, 2 * i + 2);
-            if (kMode == Mode::kGrad) checkpoint();
-        }
+        if (kEnds) end_block(k >> 1, kHere, 2 * i + 2);
+        else if (__builtin_expect((outside | f.rough | look) != 0, 0)) renew_if_due(2 * i + 2);
+        if (kExchange && k == 3) with.next_round();
     };
     chain_schedule(count, fetch, run);
     if (__builtin_expect(count < 0, 0)) return {-count, lost};
@@ -2188,7 +2311,7 @@ __device__ __forceinline__ ChainEnd run_chain_linear(const Utt m, const int u, c
         const double from_below = from_prev_pair(v_label) * f.scale;
         if (active && j == L) publish_mass(&mass[u * kMassWords], v_blank + from_below, f.frame);
     }
-    if (kSync == Sync::kHalo && lost && lane == 0) publish(&chain_err[u], 1);
+    if (kExchange && lost && lane == 0) publish(&chain_err[u], 1);
     return {0, lost};
 }
 
@@ -2203,16 +2326,17 @@ __device__ __forceinline__ ChainEnd run_chain_linear(const Utt m, const int u, c
 // The two pairs of a lane are neighbours in the checkpoint's row; where pair B has no label state (the lane of the last
 // pair) its part falls on one of the row's two unused columns.
 
-template <bool kBackward, Mode kMode, bool kSteep, int kPolicy>
+template <bool kBackward, Exchange kHandsOver, Mode kMode, bool kSteep, int kPolicy>
 __device__ __forceinline__ ChainEnd run_chain_linear2(const Utt m, const int u, const bool gentle, const int* __restrict__ labels,
                                                   const float* __restrict__ emit_label, uint32_t* __restrict__ out,
                                                   double* __restrict__ mass, int* __restrict__ chain_err, void* lds)
 {
     static_assert(kMode != Mode::kBest, "the maximum recursion runs in the log domain");
+    constexpr bool kExchange = kHandsOver != Exchange::kNone;
     const int L = m.L, chunks = 2 * frame_blocks(m.Tb);
     int count = kMode == Mode::kLoss ? chain_chunks(m.Tb, kBackward) : chunks;     // (see run_chain_linear)
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (uniform: in a scalar register)
-    int halo = m.halo2;
+    const int halo = kExchange ? m.halo2 : 0;
     const int waves = m.waves2;
     const int q = wave * (64 - halo) + lane;
     const int ja = 2 * q, jb = 2 * q + 1;                // the lane's pairs, in the chain's own order
@@ -2225,11 +2349,8 @@ __device__ __forceinline__ ChainEnd run_chain_linear2(const Utt m, const int u, 
     const bool skip_a = has_a && ja >= 1 && lab[lia] != lab[lia + back];
     const bool skip_b = has_b && lab[lib] != lab[lib + back];
 
-    // A pair without a label state reads a constant probability 0 and stays there.
-    const int first_chunk = chain_chunk(0, chunks, kBackward);
-    const float* epa = emit_label + label_emission_offset(m, has_a, has_a ? lab[lia] : 0, lia, first_chunk, kZeroEmission);
-    const float* epb = emit_label + label_emission_offset(m, has_b, has_b ? lab[lib] : 0, lib, first_chunk, kZeroEmission);
-    const int64_t step_a = label_emission_step(m, has_a, kBackward), step_b = label_emission_step(m, has_b, kBackward);
+    ChainEmissions<kBackward> emissions(m, emit_label);
+    const unsigned column_a = emissions.column(m, lab, ja), column_b = emissions.column(m, lab, jb);
     // Checkpoints: position i in column 1 + i, this lane's two are columns 1 + min(lia, lib) and the next one.  (has_a
     // false: nothing of this lane is kept.)  Cost only: one row, by pair, in the chain's own order; a lane without a pair B stores
     // what nobody reads in the row's last column.
@@ -2239,87 +2360,13 @@ __device__ __forceinline__ ChainEnd run_chain_linear2(const Utt m, const int u, 
     const int last_wave = waves - 1;
     int budget = m.poll_budget;
     bool lost = false;
-    const bool every_block = halo < kBlockFrames;        // (see run_chain_linear; a halo of h lanes lasts 2h steps)
+    HandOvers<2, kHandsOver> with(kExchange ? lds : nullptr, wave, last_wave, halo);
     const unsigned long long look = gentle && !kSteep ? 0ull : ~0ull;      // once a chunk, whatever the frames
-    int generation = 0;
-    const int wr_slot = (halo > 0 && lane >= 64 - halo) ? lane - (64 - halo) : 0;
-    const int rd_slot = lane < halo ? lane : 0;
-    Halo2Wave* const mine_lds = halo_wave<Halo2Wave>(lds, wave);
-    Halo2Wave* const below_lds = halo_wave<Halo2Wave>(lds, wave > 0 ? wave - 1 : 0);
-    Halo2Wave* const above_lds = halo_wave<Halo2Wave>(lds, wave < last_wave ? wave + 1 : wave);
 
     double va_blank = (ja == 0) ? 1.0 : 0.0, va_label = 0.0, vb_blank = 0.0, vb_label = 0.0;
-    ChainFrames<2, kSteep> f;
+    ChainFrames<2, kSteep> f(gentle && !kSteep);
     double skip_a_scale = skip_a ? 1.0 : 0.0;
     const double skip_b_one = skip_b ? 1.0 : 0.0;
-
-    auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
-    auto generation_of = [&](const int2* tag) {
-        return __hip_atomic_load(&tag->y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    };
-    auto read_tag = [&](const int2* tag) {
-        const unsigned long long w = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(tag),
-                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        return make_int2(static_cast<int>(w), static_cast<int>(w >> 32));
-    };
-    auto write_tag = [&](int2* tag, int frame_of_lane, int number) {
-        __hip_atomic_store(reinterpret_cast<unsigned long long*>(tag),
-                           (static_cast<unsigned long long>(static_cast<unsigned>(number)) << 32) |
-                               static_cast<unsigned>(frame_of_lane),
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    };
-    int above_seen = 0;
-    const int2* const always = reinterpret_cast<const int2*>(&static_cast<HaloHeader*>(lds)->always_tag);
-    const bool from_below = wave > 0 && lane < halo;
-    // Hand-over g, as in run_chain_linear.  An entry is a lane's four values and, in a last word, its frame and
-    // the number g; LDS operations of a wavefront complete in order, so a reader that finds g in
-    // the last word finds the values of hand-over g in the others.  A boundary's buffer holds
-    // kRing hand-overs.  Before it overwrites the one that held hand-over g - kRing, a wavefront
-    // makes sure that the one above has taken that, which it says by publishing that number itself.
-    auto hand_over = [&]() __attribute__((always_inline)) {
-        ++generation;
-        const int half = generation & (kRing - 1);
-        const int2* const tag = &below_lds->tag[half][rd_slot];
-        const double2* const data = &below_lds->data[half][rd_slot][0];
-        int2 taken = read_tag(wave > 0 ? tag : always);
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        double2 a = data[0], b = data[1];
-        int seen = uniform(above_seen);
-        if (__builtin_expect(seen < generation - kRing, 0)) {
-            while (seen < generation - kRing && budget > 0) {
-                --budget;
-                seen = uniform(generation_of(&above_lds->tag[half][0]));
-            }
-            lost = lost || seen < generation - kRing;
-        }
-        if (lane >= 64 - halo) {
-            mine_lds->data[half][wr_slot][0] = make_double2(va_blank, va_label);
-            mine_lds->data[half][wr_slot][1] = make_double2(vb_blank, vb_label);
-        }
-        const int frame_up = f.frame;
-        int ready = uniform(taken.y);
-        if (__builtin_expect(ready < generation, 0)) {
-            while (ready < generation && budget > 0) {
-                --budget;
-                taken = read_tag(tag);
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                a = data[0];
-                b = data[1];
-                ready = uniform(taken.y);
-            }
-            lost = lost || ready < generation;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        if (lane >= 64 - halo) write_tag(&mine_lds->tag[half][wr_slot], frame_up, generation);
-        above_seen = generation_of(wave < last_wave ? &above_lds->tag[(half + 1) & (kRing - 1)][0] : always);
-        va_blank = from_below ? a.x : va_blank;
-        va_label = from_below ? a.y : va_label;
-        vb_blank = from_below ? b.x : vb_blank;
-        vb_label = from_below ? b.y : vb_label;
-        f.frame = from_below ? taken.x : f.frame;
-        f.rescale(__ballot(!(fmax(fmax(va_blank, va_label), fmax(vb_blank, vb_label)) > 0.0)));
-        skip_a_scale = skip_a ? f.scale : 0.0;
-    };
 
     int prev_lo = 0, prev_hi = 0;
     auto from_lane_below = [&](double mine) __attribute__((always_inline)) { return shift_up(mine, prev_lo, prev_hi); };
@@ -2332,7 +2379,7 @@ __device__ __forceinline__ ChainEnd run_chain_linear2(const Utt m, const int u, 
         w->states[1][lane] = make_double2(vb_blank, vb_label);
         w->frame[lane] = frame;
         rows.drop();
-        halo = 0;
+        with.leave();
     };
     auto renew_frames = [&](int unit) __attribute__((always_inline)) {
         const int rise = f.renew(top_value(), halo > 0 ? halo - 1 : 0);
@@ -2351,13 +2398,39 @@ __device__ __forceinline__ ChainEnd run_chain_linear2(const Utt m, const int u, 
         rows.template frames<kPolicy>(f.frame);          // both pairs of the lane share its frame
         rows.next();
     };
-    auto mid_block = [&](int unit) __attribute__((always_inline)) {
-        if (__builtin_expect((f.rough | look) != 0, 0))
-            if (f.renewal_due(top_value())) renew_frames(unit);
+    auto renew_if_due = [&](int unit) __attribute__((always_inline)) {
+        if (f.renewal_due(top_value())) renew_frames(unit);
     };
-    auto end_block = [&](bool second, int unit) __attribute__((always_inline)) {
-        if (waves > 1 && (second || every_block)) hand_over();
-        if (__builtin_expect(f.renewal_due(top_value()), 0)) renew_frames(unit);
+    // Before a block's last kLookAhead steps: may its end be the ordinary one?  (A comparison's result is on its way to a branch for some 20 clocks.)
+    unsigned long long outside = 0;
+    auto look_ahead = [&](bool exchange) __attribute__((always_inline)) {
+        outside = __ballot(f.easy.outside(top_value()));
+        if (exchange) with.look(f.frame);
+    };
+    auto end_block = [&](int block, bool exchange, int unit) __attribute__((always_inline)) {
+        const bool unusual = (outside | f.rough | look | (exchange ? with.late | with.shifted : 0ull)) != 0;
+        if (exchange && __builtin_expect(unusual, 0)) with.prepare(block, f.renewal_due(top_value()), f.frame, budget, lost);
+        if (exchange) {
+            const double2 mine[2] = {make_double2(va_blank, va_label), make_double2(vb_blank, vb_label)};
+            with.publish(block, mine, f.frame);
+            if (with.takes) {
+                const int shift = with.tag.x - f.frame;
+                va_blank = __builtin_amdgcn_ldexp(with.states[0].x, shift);
+                va_label = __builtin_amdgcn_ldexp(with.states[0].y, shift);
+                vb_blank = __builtin_amdgcn_ldexp(with.states[1].x, shift);
+                vb_label = __builtin_amdgcn_ldexp(with.states[1].y, shift);
+                asm volatile("" : "+v"(va_blank), "+v"(va_label), "+v"(vb_blank), "+v"(vb_label));      // (a mask, and not a choice for each)
+            }
+        }
+        if (__builtin_expect(unusual, 0)) {
+            const double top = top_value();
+            if (exchange) {
+                with.number &= ~1;
+                f.rescale(__ballot(!(top > 0.0)));
+                skip_a_scale = skip_a ? f.scale : 0.0;
+            }
+            if (f.renewal_due(top)) renew_frames(unit);
+        }
     };
     // One step (see run_chain_linear): the pairs' own sums fill the time that the shift takes.
     //   label' = (label + blank + skip * previous label) * emission, as fma(previous, skip, label + blank)
@@ -2391,22 +2464,26 @@ __device__ __forceinline__ ChainEnd run_chain_linear2(const Utt m, const int u, 
     float ela[4][kChunk], elb[4][kChunk];
     auto fetch = [&](auto set, int) __attribute__((always_inline)) {
         constexpr int k = decltype(set)::value;
-        fetch_chunk<kBackward>(epa, step_a, ela[k]);
-        fetch_chunk<kBackward>(epb, step_b, elb[k]);
+        emissions.read(column_a, ela[k]);
+        emissions.read(column_b, elb[k]);
+        emissions.next();
         __builtin_amdgcn_sched_barrier(0);
     };
     auto run = [&](auto set, int i) __attribute__((always_inline)) {
         constexpr int k = decltype(set)::value;
+        constexpr bool kEnds = (k & 1) != 0;             // the chunk ends a block
+        constexpr bool kHere = kEnds && kExchange && (k == 3 || kHandsOver == Exchange::kBlock);
+        if (kMode == Mode::kGrad && !kEnds) checkpoint();
 #pragma unroll
         for (int q = 0; q < kChunk; ++q) {
             advance(ela[k][q], elb[k][q]);
-            if (kSteep && q == kSteepSteps - 1) mid_block(2 * i + 1);
+            if (kSteep && q == kSteepSteps - 1) renew_if_due(2 * i + 1);
+            if (kHere && q == kChunk - 1 - kAskAhead2) with.ask(k >> 1);
+            if (q == kChunk - 1 - kLookAhead) look_ahead(kHere);
         }
-        if (!(k & 1)) mid_block(2 * i + 2);
-        else {
-            end_block(k == 3, 2 * i + 2);
-            if (kMode == Mode::kGrad) checkpoint();
-        }
+        if (kEnds) end_block(k >> 1, kHere, 2 * i + 2);
+        else if (__builtin_expect((outside | f.rough | look) != 0, 0)) renew_if_due(2 * i + 2);
+        if (kExchange && k == 3) with.next_round();
     };
     chain_schedule(count, fetch, run);
     if (__builtin_expect(count < 0, 0)) return {-count, lost};
@@ -2424,7 +2501,7 @@ __device__ __forceinline__ ChainEnd run_chain_linear2(const Utt m, const int u, 
         const double from_below = from_lane_below(vb_label) * f.scale;
         if (active && (ja == L || jb == L)) publish_mass(&mass[u * kMassWords], ja == L ? va_blank + from_below : vb_blank + va_label, f.frame);
     }
-    if (lost && lane == 0) publish(&chain_err[u], 1);
+    if (kExchange && lost && lane == 0) publish(&chain_err[u], 1);
     return {0, lost};
 }
 
@@ -2498,7 +2575,6 @@ __device__ __forceinline__ bool finish_with_exponents(int unit, bool lost, void*
     const bool two = kSync == Sync::kHalo && (m.flags & kUttTwoPairs) != 0;
     const int L = m.L, chunks = 2 * frame_blocks(m.Tb), units = 2 * (kMode == Mode::kLoss ? chain_chunks(m.Tb, backward) : chunks);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
     const int halo = two ? m.halo2 : (kSync == Sync::kHalo ? m.halo : 0), last_wave = (two ? m.waves2 : m.waves) - 1;
     const int first_pair = (two ? 2 : 1) * (wave * (64 - halo) + lane);
     const bool active = (wave == 0 || lane >= halo) && first_pair <= L;
@@ -2536,6 +2612,7 @@ __device__ __forceinline__ bool finish_with_exponents(int unit, bool lost, void*
     constexpr bool kGrad = kMode == Mode::kGrad;
     CheckpointRows rows((backward ? args().lat.beta : args().lat.alpha) + m.ab_off, CheckpointRow{lattice_pitch(L)}, kGrad ? frame_blocks(m.Tb) - 1 : 1,
                         active && (has0 || !kGrad), !kGrad ? first_pair : 1 + position(two && backward ? 1 : 0));
+    rows.next_by = rows.step;
     if (kGrad) rows.at = ((unit - 1) >> 2) * rows.step;  // (four units make a block)
     constexpr int kPolicy = kFused || !kGrad ? kPast : 0;
     auto store = [&]() {
@@ -2552,42 +2629,46 @@ __device__ __forceinline__ bool finish_with_exponents(int unit, bool lost, void*
     };
 
     // Hand-overs: as in the chain, one thing after the other.
-    const bool exchanges = kSync == Sync::kHalo && last_wave > 0, every_block = (two ? 2 : 1) * halo < 2 * kBlockFrames;
+    const bool exchanges = kSync == Sync::kHalo && last_wave > 0;
+    const bool every_block = (two ? 2 : 1) * halo < 2 * kBlockFrames;
     int generation = every_block ? unit >> 2 : unit >> 3, budget = m.poll_budget;
-    const int wr_slot = lane >= 64 - halo ? lane - (64 - halo) : 0, rd_slot = lane < halo ? lane : 0;
-    auto hand_over = [&]() {
+    // At the end of `block`.
+    auto hand_over = [&](int block) {
         ++generation;
-        const int half = (generation & 1) * 32, slot = generation & (kRing - 1);
-        // Waits until wavefront w has published the number `until`.  (LDS operations of a wavefront complete in order.)
-        auto wait = [&](int w, int until) {
-            const int* const number = two ? &halo_wave<Halo2Wave>(lds, w)->tag[slot][0].y : &halo_wave<HaloWave>(lds, w)->ready;
-            auto look = [&]() { return uniform(__hip_atomic_load(number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)); };
-            int seen = look();
-            for (; seen < until && budget > 0; --budget) seen = look();
-            lost = lost || seen < until;
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const int slot = block & (kRing - 1), first = 64 - halo, wr_slot = max(lane - first, 0), rd_slot = min(lane, halo - 1);
+        auto data = [&](int w, int l, int k) {
+            return two ? &halo_wave<LinearWave<2>>(lds, w)->slot[slot].states[k][l] : &halo_wave<LinearWave<1>>(lds, w)->slot[slot].states[0][l];
         };
-        auto data = [&](int w, int lane_slot, int k) { return two ? &halo_wave<Halo2Wave>(lds, w)->data[slot][lane_slot][k] : &halo_wave<HaloWave>(lds, w)->data[half + lane_slot]; };
-        auto frame = [&](int w, int lane_slot) { return two ? &halo_wave<Halo2Wave>(lds, w)->tag[slot][lane_slot].x : &halo_wave<HaloWave>(lds, w)->frame[half + lane_slot]; };
-        const bool hands_up = lane >= 64 - halo;
-        if (wave < last_wave) wait(wave + 1, generation - (two ? kRing : 2));
-        if (hands_up) {
+        auto tag = [&](int w, int l) {
+            return reinterpret_cast<unsigned long long*>(two ? &halo_wave<LinearWave<2>>(lds, w)->slot[slot].tag[l].word : &halo_wave<LinearWave<1>>(lds, w)->slot[slot].tag[l].word);
+        };
+        // Waits until wavefront w has published the number `until`, in this lane's tag.  (LDS operations of a wavefront complete in order.)
+        auto wait = [&](int w, int until) {
+            unsigned long long seen;
+            auto early = [&]() {
+                seen = __hip_atomic_load(tag(w, rd_slot), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                return __ballot(static_cast<int>(seen >> 32) < 2 * until) != 0;
+            };
+            bool waits = early();
+            for (; waits && budget > 0; --budget) waits = early();
+            lost = lost || waits;
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            return static_cast<int>(seen);
+        };
+        if (wave < last_wave) wait(wave + 1, generation - (every_block ? kRing : kRing / 2));
+        if (lane >= first) {
             *data(wave, wr_slot, 0) = coded(s0);
             if (two) *data(wave, wr_slot, 1) = coded(s1);
-            else *frame(wave, wr_slot) = kLogs;
         }
         if (wave > 0) {
-            wait(wave - 1, generation);
-            const double2 v0 = *data(wave - 1, rd_slot, 0), v1 = *data(wave - 1, rd_slot, 1);
-            const int f = *frame(wave - 1, rd_slot);
+            const int f = wait(wave - 1, generation);
+            const double2 v0 = *data(wave - 1, rd_slot, 0), v1 = *data(wave - 1, rd_slot, two ? 1 : 0);
             if (lane < halo) take(v0, v1, f);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        if (two && hands_up)
-            __hip_atomic_store(reinterpret_cast<unsigned long long*>(&halo_wave<Halo2Wave>(lds, wave)->tag[slot][wr_slot]),
-                               (static_cast<unsigned long long>(static_cast<unsigned>(generation)) << 32) | static_cast<unsigned>(kLogs),
+        if (lane >= first)
+            __hip_atomic_store(tag(wave, wr_slot), (static_cast<unsigned long long>(static_cast<unsigned>(2 * generation)) << 32) | static_cast<unsigned>(kLogs),
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (!two && lane == 63) __hip_atomic_store(&halo_wave<HaloWave>(lds, wave)->ready, generation, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     };
 
     auto from_lane_below = [&]() {
@@ -2614,7 +2695,7 @@ __device__ __forceinline__ bool finish_with_exponents(int unit, bool lost, void*
             step(s0, prev, skip0, component(el0));
         }
         if ((unit & 3) == 3) {
-            if (exchanges && (every_block || (unit & 4) != 0)) hand_over();
+            if (exchanges && (every_block || (unit & 4) != 0)) hand_over(unit >> 2);
             if (kGrad) store();
         }
     }
@@ -2823,20 +2904,22 @@ __device__ __forceinline__ int lattice_body(const int chain, const Utt* __restri
         // the exchange buffer in use starts with every counter and hand-over number at zero
         // (every wavefront of the workgroup clears its own block, whether it takes part or not)
         HaloHeader* hl = static_cast<HaloHeader*>(lds);
-        if (two_pairs) {
-            int* tags = reinterpret_cast<int*>(&halo_wave<Halo2Wave>(lds, threadIdx.x >> 6)->tag[0][0]);
-            for (int i = threadIdx.x & 63; i < kRing * kHalo2Lanes * 2; i += 64) tags[i] = 0;
-        } else if ((threadIdx.x & 63) == 0) {
+        if (in_log_domain) {
             HaloWave* w = halo_wave<HaloWave>(lds, threadIdx.x >> 6);
             w->ready = 0;
             w->done = 0;
+        } else {
+            auto clear = [&](auto* w) {
+                constexpr int kLanes = std::remove_pointer_t<decltype(w)>::kLanes;
+                for (int i = threadIdx.x & 63; i < kRing * kLanes; i += 64) w->slot[i / kLanes].tag[i % kLanes].word = make_int2(0, 0);
+            };
+            if (two_pairs) clear(halo_wave<LinearWave<2>>(lds, threadIdx.x >> 6));
+            else clear(halo_wave<LinearWave<1>>(lds, threadIdx.x >> 6));
         }
         if (threadIdx.x == 0) {
             hl->finished = 0;
             hl->gave_up = 0;
             hl->left = left;
-            hl->always = 0x7FFFFFFF;
-            hl->always_tag[1] = 0x7FFFFFFF;
         }
         __syncthreads();
         if (kFused) left = __builtin_amdgcn_readfirstlane(hl->left);
@@ -2867,18 +2950,25 @@ __device__ __forceinline__ int lattice_body(const int chain, const Utt* __restri
             auto run = [&](auto steep_ones) __attribute__((always_inline)) {
                 constexpr bool kSteep = decltype(steep_ones)::value;
                 constexpr int kPolicy = kFused || kMode == Mode::kLoss ? kPast : 0;
-                if (two_pairs) {
-                    if constexpr (kSync == Sync::kHalo) {
-                        if (forward)
-                            end = run_chain_linear2<false, kMode, kSteep, kPolicy>(m, u, gentle, labels, emit_label, lat.alpha, mass, chain_err, lds);
-                        else
-                            end = run_chain_linear2<true, kMode, kSteep, kPolicy>(m, u, gentle, labels, emit_label, lat.beta, mass, chain_err, lds);
-                    }
-                } else if (forward) {
-                    end = run_chain_linear<false, kSync, kMode, kSteep, kPolicy>(m, u, gentle, labels, emit_label, lat.alpha, mass, chain_err, lds);
-                } else {
-                    end = run_chain_linear<true, kSync, kMode, kSteep, kPolicy>(m, u, gentle, labels, emit_label, lat.beta, mass, chain_err, lds);
-                }
+                auto of_direction = [&](auto backward, auto exchange) __attribute__((always_inline)) {
+                    constexpr bool kBackward = decltype(backward)::value;
+                    constexpr Exchange kExchange = decltype(exchange)::value;
+                    // (read again: with the pointers of both directions held through either the kernel came out with room for them in memory)
+                    const auto& again = args_again<ChainArgs<kFused>>();
+                    uint32_t* const out = kBackward ? again.lat.beta : again.lat.alpha;
+                    if (kSync == Sync::kHalo && two_pairs)
+                        end = run_chain_linear2<kBackward, kExchange, kMode, kSteep, kPolicy>(m, u, gentle, again.labels, again.emit_label, out, again.mass, again.chain_err, lds);
+                    else
+                        end = run_chain_linear<kBackward, kExchange, kMode, kSteep, kPolicy>(m, u, gentle, again.labels, again.emit_label, out, again.mass, again.chain_err, lds);
+                };
+                auto handing_over = [&](auto exchange) __attribute__((always_inline)) {
+                    if (forward) of_direction(std::false_type{}, exchange);
+                    else of_direction(std::true_type{}, exchange);
+                };
+                // (a halo lasts as many frames as it has pairs)
+                if (kSync == Sync::kNone || waves == 1) handing_over(std::integral_constant<Exchange, Exchange::kNone>{});
+                else if ((two_pairs ? 2 * m.halo2 : m.halo) < 2 * kBlockFrames) handing_over(std::integral_constant<Exchange, kSync == Sync::kHalo ? Exchange::kBlock : Exchange::kNone>{});
+                else handing_over(std::integral_constant<Exchange, kSync == Sync::kHalo ? Exchange::kTwoBlocks : Exchange::kNone>{});
             };
             if (__builtin_expect(steep, 0)) run(std::true_type{});
             else run(std::false_type{});

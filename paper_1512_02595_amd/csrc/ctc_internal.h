@@ -356,6 +356,15 @@ CTC_HOST_DEVICE inline bool tight_fit(int frames, int label_length, int repeats)
 // Lattice wavefronts of one launch beyond which chains are planned for total work: two per SIMD
 // of the 256 compute units.
 constexpr int kCrowdedWaves = 2 * 4 * 256;
+// What an utterance weighs in the orders of chains and of ends: how long its chains take, a frame's time in ns (750 frames, alone on the chip), where a chain has SIMDs of
+// its own; in crowded launches, where what counts is how much they keep SIMDs busy, frames times wavefronts.  (By frames times wavefronts throughout, an utterance of
+// two wavefronts with two pairs to a lane, which lasts longest, was taken to end early.)
+CTC_HOST_DEVICE inline int64_t chain_weight(int frames, int waves, bool two_pairs, bool log_domain, bool crowded)
+{
+    if (crowded) return static_cast<int64_t>(frames) * waves;
+    const int per_frame = log_domain ? 60 + 25 * waves : (two_pairs ? (waves <= 1 ? 30 : (waves <= 4 ? 32 + 4 * waves : 65)) : (waves <= 1 ? 19 : 19 + 3 * waves));
+    return static_cast<int64_t>(frames) * per_frame;
+}
 // The order in which the lattice launch takes its chains (entry = utterance * 2 + direction).
 // `utt`: the utterances whose lattice runs, heaviest (frames x wavefronts) first; `dirs`: 2 when
 // the backward chains run too.  Up to `n_cu` chains (one per compute unit) keep that order.

@@ -911,18 +911,12 @@ struct NarrowDevice {
     int n_cu;                     // compute units of the device (a multiple of kChainBlock, or 0: keep the plain order)
 };
 
-// Wavefronts of an utterance's chains (0: its lengths are out of range).
-__device__ __forceinline__ int chain_waves(const PlanTable& plans, int L, int Tb, int Tt, int max_label, bool log_domain)
+// Weight of an utterance in the run order (chain_weight; 0: its lengths are out of range).
+__device__ __forceinline__ long long weight_of(const PlanTable& plans, int L, int Tb, int Tt, int max_label, bool log_domain, bool crowded)
 {
     if (L < 0 || L > max_label || Tb < 0 || Tb > Tt) return 0;
     const bool two = !log_domain && Tb <= kLinearMaxFrames && plans.two_pairs(L);
-    return two ? plans.waves2(L) : plans.waves1(L);
-}
-// Weight of an utterance in the run order: its frames times the wavefronts of its chains.
-__device__ __forceinline__ long long chain_weight(const PlanTable& plans, int L, int Tb, int Tt, int max_label,
-                                                  bool log_domain)
-{
-    return static_cast<long long>(Tb) * chain_waves(plans, L, Tb, Tt, max_label, log_domain);
+    return chain_weight(Tb, two ? plans.waves2(L) : plans.waves1(L), two, log_domain, crowded);
 }
 // By the whole workgroup.  Returns the record (the same in every thread).
 __device__ __forceinline__ Utt build_record(const NarrowDevice& dv, const PlanTable& plans, int b, int Tt, int B, int A,
@@ -949,11 +943,11 @@ __device__ __forceinline__ Utt build_record(const NarrowDevice& dv, const PlanTa
     if (repeats) atomicAdd(&s_repeats, repeats);
     if (bad) s_bad = 1;
     // the utterances that come before this one in the run order: heavier, or as heavy and earlier
-    const long long mine = chain_weight(plans, L_in, Tb_in, Tt, dv.max_label, dv.log_domain);
+    const long long mine = weight_of(plans, L_in, Tb_in, Tt, dv.max_label, dv.log_domain, dv.crowded);
     int before = 0;
     for (int j = tid; j < B; j += kRowThreads) {
         const int Lj = dv.label_lengths[j], Tj = dv.input_lengths[j];
-        const long long w = chain_weight(plans, Lj, Tj, Tt, dv.max_label, dv.log_domain);
+        const long long w = weight_of(plans, Lj, Tj, Tt, dv.max_label, dv.log_domain, dv.crowded);
         before += (w > mine || (w == mine && j < b)) ? 1 : 0;
     }
     if (before) atomicAdd(&s_rank, before);
@@ -3673,6 +3667,15 @@ __device__ __forceinline__ void for_pieces(int L, int first, int step, F&& for_p
 // Wavefronts that share a block in the narrow gradient kernel, one piece each up to four -- in launches of few blocks,
 // which last as long as one block takes (English minibatch: 18.8 -> 16.7 us; 512 utterances: 69 -> 83 us).
 constexpr int kShareBlocksMost = 8192;    // blocks times pieces: two rounds of what the chip holds
+// In a lattice launch that has more, those of the utterances that end last (about): by then compute units are free, and a label of five pieces keeps one wavefront to a
+// block for 18 us after its chains have ended.  As many blocks times pieces as this, fewer where there are more chains than compute units, whose blocks are
+// still under way.  us a call with none / 2048 / 4096 / 8192: 32 x 1500 x 29 128.1 / 121.3 / 119.8 / 119.9; the same, lengths from 400 on, 111.9 / 103.2 / 101.1 / 100.7; 128 x
+// 750 x 29 49.4 / 49.4 / 49.4 / 46.6; 512 x 750 x 29 116.9 / 115.4 / 116.4 / 117.7; 300 x 400 x 40 50.1 / 50.0 / 50.0 / 50.0.
+constexpr int kShareLast = 8192, kShareLastCrowded = 2048;
+inline int shared_utterances(const Launch& p, int blocks)
+{
+    return std::min(p.B, (p.n_chains > p.n_cu ? kShareLastCrowded : kShareLast) / (blocks * std::max(1, label_pieces(p.max_label))));
+}
 __host__ __device__ constexpr int block_waves(int L) { return label_pieces(L) <= 1 ? 1 : (label_pieces(L) == 2 ? 2 : 4); }
 // The domain of an utterance as its chains published it (a word per direction).
 template <bool kPublished>
@@ -3772,10 +3775,27 @@ struct TileArgs {
     int end_polls;                // ... and how often to look before giving up
     const int* by_end;            // ... the utterances, those first whose chains end first
     int T, B, A, blank, Lmax;
-    int share_blocks;             // narrow
+    int shared_from;              // narrow: of by_end's utterances, those from this one on have several wavefronts to a block
+    int shared_groups;            // ... and so many workgroups
     int waves, alpha_at;          // wide
-    int groups;                   // workgroups per utterance
+    int groups;                   // workgroups per utterance (narrow: of the others)
     int first_group;              // lattice launch: the first one with a tile
+    __host__ __device__ int64_t tiles() const { return static_cast<int64_t>(shared_from) * groups + static_cast<int64_t>(B - shared_from) * shared_groups; }
+};
+// Which utterance (of by_end's) a workgroup works for, and which of its workgroups it is.
+struct TilePlace {
+    int rank, within, groups;
+    bool shares;
+    __device__ __forceinline__ TilePlace(const TileArgs& g, int64_t tile)
+    {
+        const int64_t plain = static_cast<int64_t>(g.shared_from) * g.groups;
+        shares = tile >= plain;
+        groups = shares ? g.shared_groups : g.groups;
+        // (a launch has fewer workgroups than 2^32)
+        const unsigned i = static_cast<unsigned>(shares ? tile - plain : tile), utterance = i / static_cast<unsigned>(groups);
+        rank = static_cast<int>(utterance) + (shares ? g.shared_from : 0);
+        within = static_cast<int>(i - utterance * groups);
+    }
 };
 __device__ __forceinline__ void store_gradient(const TileArgs& g, size_t i, float v)
 {
@@ -3853,13 +3873,13 @@ struct GradientArgs {
 template <int kTiles, bool kWait, bool kStaged, bool kLean = false>
 __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* __restrict__ meta, const int* __restrict__ labels,
                                             const float* __restrict__ emit_blank, const float* __restrict__ emit_label,
-                                            const LatticeOut& lat, uint4v* tile_lds, const int b, const int group)
+                                            const LatticeOut& lat, uint4v* tile_lds, const int b, const int group, const bool shares)
 {
     const int Tt = g_args.T, B = g_args.B, A = g_args.A, blank = g_args.blank, Lmax = g_args.Lmax;
     const int lane = kLean ? tile_thread() & 63 : threadIdx.x & 63, c = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const Utt m = uniform_record(meta[b]);
-    const int L = m.L, sharing = g_args.share_blocks ? block_waves(L) : 1, part = wave & (sharing - 1);
+    const int L = m.L, sharing = shares ? block_waves(L) : 1, part = wave & (sharing - 1);
     const int first_block = group * (kRowThreads / 64 / sharing);
     const int block = first_block + wave / sharing, t0 = block * kBlockFrames;
     const bool runs = (m.flags & kUttRuns) != 0, has_rows = runs && t0 < m.Tb;
@@ -4059,7 +4079,8 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
 // a call (before costs had a workgroup 50.9), so 48.5; 32 symbols 50.2 (49.0), 44.4.
 __device__ __forceinline__ int rotated_group(int within, int utterance, int groups) { return (within + utterance) % groups; }
 
-// grid (workgroups per utterance, B)
+// A workgroup per tile, in as many rows of the grid as they take; those of the utterances that took longest come first.  (Which utterances have several wavefronts to a block is as it
+// is beside the chains: the sums are in another order with them.)
 template <int kTiles, bool kStaged>
 __global__ __launch_bounds__(kRowThreads, kStaged ? 1 : 4)
 void ctc_gradient_narrow_kernel(const TileArgs args, const Utt* __restrict__ meta, const int* __restrict__ labels,
@@ -4067,8 +4088,14 @@ void ctc_gradient_narrow_kernel(const TileArgs args, const Utt* __restrict__ met
                                 const LatticeOut lat)
 {
     extern __shared__ uint4v tile_lds[];
-    const int b = blockIdx.y;
-    narrow_tile<kTiles, false, kStaged, !kStaged>(args, meta, labels, emit_blank, emit_label, lat, tile_lds, b, rotated_group(blockIdx.x, b, args.groups));
+    const int64_t tile = args.tiles() - 1 - (static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x);
+    if (tile < 0) return;
+    const TilePlace place(args, tile);
+    // (where all utterances are treated alike, their order is nothing to wait for)
+    const bool alike = args.shared_from == 0 || args.shared_from == args.B;
+    const int b = alike ? place.rank : __builtin_amdgcn_readfirstlane(args.by_end[place.rank]);
+    narrow_tile<kTiles, false, kStaged, !kStaged>(args, meta, labels, emit_blank, emit_label, lat, tile_lds, b,
+                                                  rotated_group(place.within, place.rank, place.groups), place.shares);
 }
 
 // Larger alphabets: the softmax launch has written y (and zeros); here the columns of the label's symbols and the
@@ -4319,20 +4346,23 @@ void ctc_lattice_gradient_kernel(const Utt* __restrict__ meta, const int* __rest
             __syncthreads();
             const FusedArgs& args = args_again<FusedArgs>();
             const ChainArgs<true>& a = args.chains;
-            const int tile = left - 1, rank = tile / args.tiles.groups, b = __builtin_amdgcn_readfirstlane(args.tiles.by_end[rank]);
+            const int tile = left - 1;
+            const TilePlace place(args.tiles, tile);
+            const int b = __builtin_amdgcn_readfirstlane(args.tiles.by_end[place.rank]);
             narrow_tile<kTiles, true, kStaged, kLean>(args.tiles, a.meta, a.labels, a.emit_blank, a.emit_label, a.lat, fused_lds, b,
-                                             rotated_group(tile - rank * args.tiles.groups, rank, args.tiles.groups));
+                                             rotated_group(place.within, place.rank, place.groups), place.shares);
             left = __builtin_amdgcn_readfirstlane(published(&args.tiles.left[tile]));
         } while (left != 0);
     } else {
-        const int tile = index - tiles.first_group, rank = tile / tiles.groups, group = rotated_group(tile - rank * tiles.groups, rank, tiles.groups);
-        const int b = __builtin_amdgcn_readfirstlane(tiles.by_end[rank]);
+        const int tile = index - tiles.first_group;
+        const TilePlace place(tiles, tile);
+        const int group = rotated_group(place.within, place.rank, place.groups), b = __builtin_amdgcn_readfirstlane(tiles.by_end[place.rank]);
         const int flags = __builtin_amdgcn_readfirstlane(meta[b].flags), frames = __builtin_amdgcn_readfirstlane(meta[b].Tb);
-        const int sharing = tiles.share_blocks ? block_waves(__builtin_amdgcn_readfirstlane(meta[b].L)) : 1;
+        const int sharing = place.shares ? block_waves(__builtin_amdgcn_readfirstlane(meta[b].L)) : 1;
         if (threadIdx.x >= kRowThreads) return;          // (workgroups as large as the longest label's chains)
         const bool waits = (flags & kUttRuns) && group * (kRowThreads / 64 / sharing) <= frame_blocks(frames);     // (narrow_tile: rows, or the cost)
         if (waits && !chains_taken(tiles, b, tile)) return;
-        narrow_tile<kTiles, true, kStaged, kLean>(tiles, meta, labels, emit_blank, emit_label, lat, fused_lds, b, group);
+        narrow_tile<kTiles, true, kStaged, kLean>(tiles, meta, labels, emit_blank, emit_label, lat, fused_lds, b, group, place.shares);
     }
 }
 
@@ -4564,18 +4594,20 @@ static TileArgs tile_args(const Launch& p, size_t* lds)
     g.Lmax = p.max_label;
     constexpr int kWaves = kRowThreads / 64;
     const int blocks = frame_blocks(p.T);
-    int per_group = kWaves;
     if (p.A <= kDirectMaxA) {
-        g.share_blocks = shares_blocks(p);
-        if (g.share_blocks) per_group = kWaves / block_waves(p.max_label);
+        // (an utterance's blocks, and a wavefront for its cost)
+        auto groups = [&](int waves_per_block) { return (blocks + 1 + kWaves / waves_per_block - 1) / (kWaves / waves_per_block); };
+        const int shared = shares_blocks(p) ? p.B : shared_utterances(p, blocks);
+        g.shared_groups = groups(block_waves(p.max_label));
+        g.shared_from = p.B - shared;
+        g.groups = shared == p.B ? g.shared_groups : groups(1);
         *lds = static_cast<size_t>(kWaves) * tile_lds_ints(p.max_label, p.A <= 32 ? 2 : 4, staged_emissions(p)) * 4;
     } else {
-        per_group = 1;
+        g.groups = blocks;
         g.waves = label_pieces(p.max_label) > 1 ? kWideWaves : 2;
         g.alpha_at = wide_alpha_at(p.max_label);
         *lds = wide_lds_bytes(p.max_label, g.waves);
     }
-    g.groups = (blocks + (p.A <= kDirectMaxA ? 1 : 0) + per_group - 1) / per_group;
     return g;
 }
 
@@ -4621,7 +4653,7 @@ int launch_lattice(const Launch& p, void* stream)
         lds = std::max(lds, halo_lds_bytes(waves));
         wk.late_percent = p.late_percent;
         tiles.first_group = n_groups;
-        const dim3 grid(n_groups + tiles.groups * p.B), block(64 * waves);
+        const dim3 grid(n_groups + static_cast<unsigned>(tiles.tiles())), block(64 * waves);
 #define CTC_LAUNCH_FUSED(SYNC, TILES, LEAN, STAGED)                                                \
     hipLaunchKernelGGL((ctc_lattice_gradient_kernel<SYNC, TILES, LEAN, STAGED>), grid, block, lds, s, meta, order, labels, emit_blank,   \
                        emit_label, lat, mass, p.costs, chain_err, sink, wk, tiles)
@@ -4703,7 +4735,8 @@ int launch_gradient(const Launch& p, void* stream)
             hipLaunchKernelGGL((ctc_gradient_narrow_kernel<4, STAGED>), grid, block, lds, s, args, meta, p.labels, emit_blank, emit_label, lattice_blocks(p)); \
     } while (0)
     const WideRows rows = wide_rows(args.groups + fill.rounds);
-    const dim3 grid = p.A > kDirectMaxA ? dim3(p.B, rows.y, rows.z) : dim3(args.groups, p.B), block(p.A > kDirectMaxA ? 64 * args.waves : kRowThreads);
+    const int64_t tiles = p.A > kDirectMaxA ? 0 : args.tiles(), across = std::min<int64_t>(tiles, 1 << 20);
+    const dim3 grid = p.A > kDirectMaxA ? dim3(p.B, rows.y, rows.z) : dim3(static_cast<unsigned>(across), static_cast<unsigned>((tiles + across - 1) / across)), block(p.A > kDirectMaxA ? 64 * args.waves : kRowThreads);
     return checked_launch([&] {
         if (p.A > kDirectMaxA && p.defer_columns > 0)
             hipLaunchKernelGGL(ctc_gradient_wide_kernel<true>, grid, block, lds, s, args, meta, p.labels, emit_blank, emit_label,

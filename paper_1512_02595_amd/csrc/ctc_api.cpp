@@ -432,12 +432,16 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
         for (int b = 0; b < c.B; ++b)
             if (!(meta[b].flags & kUttRuns)) *by_end++ = b;
     for (int i = n_run - 1; i >= 0; --i) *by_end++ = running[i];
+    thread_local std::vector<int32_t> frames_by_end;
+    frames_by_end.assign(static_cast<size_t>(c.B), 0);
+    for (int i = 0; i < n_run; ++i) frames_by_end[c.B - 1 - i] = run_frames[i];
 
     const bool sequential_chains = c.mode == Mode::kGrad && g_sequential_chains.load(std::memory_order_relaxed) != 0;
 
     if (c.ws_bytes < lay.total) return CTC_STATUS_WORKSPACE_TOO_SMALL;
 
     out->mode = c.mode;
+    out->frames_by_end = frames_by_end.data();
     out->T = c.T; out->B = c.B; out->A = c.A; out->blank = c.blank;
     out->dtype = c.dtype;
     out->n_run = n_run;

@@ -594,6 +594,7 @@ struct Launch {
     int max_waves;      // wavefronts per lattice block
     int max_frames;     // longest utterance among those whose lattice runs
     int max_label;      // longest label of the batch
+    const int32_t* frames_by_end = nullptr;   // host metadata: frames of the utterances (0: there is no lattice), those first whose chains end first; for this call only
     bool needs_barrier; // some utterance's label leaves no room for a halo
     const void* x;
     void* grads;        // nullptr unless mode == kGrad

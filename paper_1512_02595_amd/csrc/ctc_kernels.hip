@@ -3773,28 +3773,37 @@ struct TileArgs {
     int* done;                    // lattice launch: what to wait for
     int* left;                    // ... and, per workgroup, who has left before it (chains_taken)
     int end_polls;                // ... and how often to look before giving up
-    const int* by_end;            // ... the utterances, those first whose chains end first
+    const int* by_end;            // ... the utterances, those first whose chains end first (nullptr, a launch of its own: as they come)
     int T, B, A, blank, Lmax;
-    int shared_from;              // narrow: of by_end's utterances, those from this one on have several wavefronts to a block
-    int shared_groups;            // ... and so many workgroups
+    // narrow: by_end's utterances in segments, those of one with as many workgroups each as its longest needs.  (With as many as the tensor's frames need, two in five had nothing
+    // but zero rows to write, a microsecond or two in the place of another, and workgroups go out one after the other: 75 in a microsecond.  us a call: 512 x 60 x 29 29.7,
+    // so 27.2; 512 x 750 x 29 115.6 and 115.1; 400 x 1500 x 29 300.0 and 298.5.)
+    static constexpr int kSegments = 8;
+    unsigned segment_tile[kSegments + 1];      // its first workgroup; the last entry: how many there are
+    int segment_rank[kSegments], segment_groups[kSegments];
+    int shared_from;              // from this utterance on, a segment's first one, several wavefronts share a block
     int waves, alpha_at;          // wide
-    int groups;                   // workgroups per utterance (narrow: of the others)
+    int groups;                   // wide: workgroups per utterance
     int first_group;              // lattice launch: the first one with a tile
-    __host__ __device__ int64_t tiles() const { return static_cast<int64_t>(shared_from) * groups + static_cast<int64_t>(B - shared_from) * shared_groups; }
 };
 // Which utterance (of by_end's) a workgroup works for, and which of its workgroups it is.
 struct TilePlace {
     int rank, within, groups;
     bool shares;
-    __device__ __forceinline__ TilePlace(const TileArgs& g, int64_t tile)
+    static __device__ __forceinline__ TilePlace of(const TileArgs& g, unsigned tile)
     {
-        const int64_t plain = static_cast<int64_t>(g.shared_from) * g.groups;
-        shares = tile >= plain;
-        groups = shares ? g.shared_groups : g.groups;
-        // (a launch has fewer workgroups than 2^32)
-        const unsigned i = static_cast<unsigned>(shares ? tile - plain : tile), utterance = i / static_cast<unsigned>(groups);
-        rank = static_cast<int>(utterance) + (shares ? g.shared_from : 0);
-        within = static_cast<int>(i - utterance * groups);
+        unsigned first = 0;
+        int first_rank = 0, groups = g.segment_groups[0];
+#pragma unroll
+        for (int i = 1; i < TileArgs::kSegments; ++i) {
+            const bool here = tile >= g.segment_tile[i];
+            first = here ? g.segment_tile[i] : first;
+            first_rank = here ? g.segment_rank[i] : first_rank;
+            groups = here ? g.segment_groups[i] : groups;
+        }
+        const unsigned i = tile - first, utterance = i / static_cast<unsigned>(groups);
+        const int rank = first_rank + static_cast<int>(utterance);
+        return {rank, static_cast<int>(i - utterance * groups), groups, rank >= g.shared_from};
     }
 };
 __device__ __forceinline__ void store_gradient(const TileArgs& g, size_t i, float v)
@@ -3873,7 +3882,7 @@ struct GradientArgs {
 template <int kTiles, bool kWait, bool kStaged, bool kLean = false>
 __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* __restrict__ meta, const int* __restrict__ labels,
                                             const float* __restrict__ emit_blank, const float* __restrict__ emit_label,
-                                            const LatticeOut& lat, uint4v* tile_lds, const int b, const int group, const bool shares)
+                                            const LatticeOut& lat, uint4v* tile_lds, const int b, const int group, const int groups, const bool shares)
 {
     const int Tt = g_args.T, B = g_args.B, A = g_args.A, blank = g_args.blank, Lmax = g_args.Lmax;
     const int lane = kLean ? tile_thread() & 63 : threadIdx.x & 63, c = lane & 15, g = lane >> 4;
@@ -3888,6 +3897,12 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
         for (int r = 0; r < kBlockFrames; ++r)
             if (t0 + r < Tt && lane < A) store_gradient(g_args, (static_cast<size_t>(t0 + r) * B + b) * A + lane, 0.0f);
     };
+    // The rows behind the utterance's last workgroup are divided among all of them.
+    const int covered = min(groups * (kRowThreads / 64 / sharing) * kBlockFrames, Tt), each = (Tt - covered + groups - 1) / groups;
+    const int from = covered + group * each, until = min(from + each, Tt);
+#pragma unroll 4
+    for (int t = from + wave; t < until; t += kRowThreads / 64)
+        if (lane < A) store_gradient(g_args, (static_cast<size_t>(t) * B + b) * A + lane, 0.0f);
     if (!has_rows) {
         if (part == 0) zero_rows();                      // no lattice
         // (the barriers below)
@@ -4079,8 +4094,8 @@ __device__ __forceinline__ void narrow_tile(const TileArgs& g_args, const Utt* _
 // a call (before costs had a workgroup 50.9), so 48.5; 32 symbols 50.2 (49.0), 44.4.
 __device__ __forceinline__ int rotated_group(int within, int utterance, int groups) { return (within + utterance) % groups; }
 
-// A workgroup per tile, in as many rows of the grid as they take; those of the utterances that took longest come first.  (Which utterances have several wavefronts to a block is as it
-// is beside the chains: the sums are in another order with them.)
+// Without by_end: grid (workgroups per utterance, B).  With it: a workgroup per tile, in as many rows of the grid as they take, those of the utterances that took longest first.
+// (Which utterances have several wavefronts to a block is as it is beside the chains: the sums are in another order with them.)
 template <int kTiles, bool kStaged>
 __global__ __launch_bounds__(kRowThreads, kStaged ? 1 : 4)
 void ctc_gradient_narrow_kernel(const TileArgs args, const Utt* __restrict__ meta, const int* __restrict__ labels,
@@ -4088,14 +4103,16 @@ void ctc_gradient_narrow_kernel(const TileArgs args, const Utt* __restrict__ met
                                 const LatticeOut lat)
 {
     extern __shared__ uint4v tile_lds[];
-    const int64_t tile = args.tiles() - 1 - (static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x);
-    if (tile < 0) return;
-    const TilePlace place(args, tile);
-    // (where all utterances are treated alike, their order is nothing to wait for)
-    const bool alike = args.shared_from == 0 || args.shared_from == args.B;
-    const int b = alike ? place.rank : __builtin_amdgcn_readfirstlane(args.by_end[place.rank]);
+    TilePlace place{static_cast<int>(blockIdx.y), static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x), args.shared_from == 0};
+    int b = place.rank;
+    if (args.by_end) {
+        const unsigned back = blockIdx.y * gridDim.x + blockIdx.x, tiles = args.segment_tile[TileArgs::kSegments];
+        if (back >= tiles) return;
+        place = TilePlace::of(args, tiles - 1 - back);
+        b = __builtin_amdgcn_readfirstlane(args.by_end[place.rank]);
+    }
     narrow_tile<kTiles, false, kStaged, !kStaged>(args, meta, labels, emit_blank, emit_label, lat, tile_lds, b,
-                                                  rotated_group(place.within, place.rank, place.groups), place.shares);
+                                                  rotated_group(place.within, place.rank, place.groups), place.groups, place.shares);
 }
 
 // Larger alphabets: the softmax launch has written y (and zeros); here the columns of the label's symbols and the
@@ -4347,22 +4364,22 @@ void ctc_lattice_gradient_kernel(const Utt* __restrict__ meta, const int* __rest
             const FusedArgs& args = args_again<FusedArgs>();
             const ChainArgs<true>& a = args.chains;
             const int tile = left - 1;
-            const TilePlace place(args.tiles, tile);
+            const TilePlace place = TilePlace::of(args.tiles, tile);
             const int b = __builtin_amdgcn_readfirstlane(args.tiles.by_end[place.rank]);
             narrow_tile<kTiles, true, kStaged, kLean>(args.tiles, a.meta, a.labels, a.emit_blank, a.emit_label, a.lat, fused_lds, b,
-                                             rotated_group(place.within, place.rank, place.groups), place.shares);
+                                             rotated_group(place.within, place.rank, place.groups), place.groups, place.shares);
             left = __builtin_amdgcn_readfirstlane(published(&args.tiles.left[tile]));
         } while (left != 0);
     } else {
         const int tile = index - tiles.first_group;
-        const TilePlace place(tiles, tile);
+        const TilePlace place = TilePlace::of(tiles, tile);
         const int group = rotated_group(place.within, place.rank, place.groups), b = __builtin_amdgcn_readfirstlane(tiles.by_end[place.rank]);
         const int flags = __builtin_amdgcn_readfirstlane(meta[b].flags), frames = __builtin_amdgcn_readfirstlane(meta[b].Tb);
         const int sharing = place.shares ? block_waves(__builtin_amdgcn_readfirstlane(meta[b].L)) : 1;
         if (threadIdx.x >= kRowThreads) return;          // (workgroups as large as the longest label's chains)
         const bool waits = (flags & kUttRuns) && group * (kRowThreads / 64 / sharing) <= frame_blocks(frames);     // (narrow_tile: rows, or the cost)
         if (waits && !chains_taken(tiles, b, tile)) return;
-        narrow_tile<kTiles, true, kStaged, kLean>(tiles, meta, labels, emit_blank, emit_label, lat, fused_lds, b, group, place.shares);
+        narrow_tile<kTiles, true, kStaged, kLean>(tiles, meta, labels, emit_blank, emit_label, lat, fused_lds, b, group, place.groups, place.shares);
     }
 }
 
@@ -4595,12 +4612,35 @@ static TileArgs tile_args(const Launch& p, size_t* lds)
     constexpr int kWaves = kRowThreads / 64;
     const int blocks = frame_blocks(p.T);
     if (p.A <= kDirectMaxA) {
-        // (an utterance's blocks, and a wavefront for its cost)
-        auto groups = [&](int waves_per_block) { return (blocks + 1 + kWaves / waves_per_block - 1) / (kWaves / waves_per_block); };
-        const int shared = shares_blocks(p) ? p.B : shared_utterances(p, blocks);
-        g.shared_groups = groups(block_waves(p.max_label));
+        const int shared = shares_blocks(p) ? p.B : shared_utterances(p, blocks), segments = TileArgs::kSegments;
         g.shared_from = p.B - shared;
-        g.groups = shared == p.B ? g.shared_groups : groups(1);
+        // (those whose blocks are shared, where others' are not, are the last segment)
+        const bool apart = shared > 0 && shared < p.B;
+        const int even = apart ? segments - 1 : segments, ranks = apart ? g.shared_from : p.B;
+        auto lay_out = [&](const int32_t* frames_by_end) {
+            uint64_t tiles = 0;
+            for (int i = 0; i < segments; ++i) {
+                const int first = i < even ? static_cast<int>(static_cast<int64_t>(ranks) * i / even) : ranks;
+                const int end = i < even ? static_cast<int>(static_cast<int64_t>(ranks) * (i + 1) / even) : p.B;
+                int frames = frames_by_end ? 0 : p.T;
+                for (int r = first; frames_by_end && r < end; ++r) frames = std::max(frames, frames_by_end[r]);
+                // (an utterance's blocks, and a wavefront for its cost)
+                const int per_group = kWaves / (first >= g.shared_from ? block_waves(p.max_label) : 1);
+                g.segment_tile[i] = static_cast<unsigned>(tiles);
+                g.segment_rank[i] = first;
+                g.segment_groups[i] = (frame_blocks(frames) + 1 + per_group - 1) / per_group;
+                tiles += static_cast<uint64_t>(end - first) * g.segment_groups[i];
+            }
+            g.segment_tile[segments] = static_cast<unsigned>(tiles);
+            return tiles;
+        };
+        const uint64_t fewer = lay_out(p.frames_by_end);
+        // (a launch of its own whose workgroups are nearly as many anyway does not wait for the order first: 512 x 100 x 29 31.4 us a call with it, 30.5 without)
+        if (!p.fused && !apart) {
+            TileArgs by_segment = g;
+            if (4 * fewer <= 3 * lay_out(nullptr)) g = by_segment;
+            else g.by_end = nullptr;
+        }
         *lds = static_cast<size_t>(kWaves) * tile_lds_ints(p.max_label, p.A <= 32 ? 2 : 4, staged_emissions(p)) * 4;
     } else {
         g.groups = blocks;
@@ -4653,7 +4693,7 @@ int launch_lattice(const Launch& p, void* stream)
         lds = std::max(lds, halo_lds_bytes(waves));
         wk.late_percent = p.late_percent;
         tiles.first_group = n_groups;
-        const dim3 grid(n_groups + static_cast<unsigned>(tiles.tiles())), block(64 * waves);
+        const dim3 grid(n_groups + tiles.segment_tile[TileArgs::kSegments]), block(64 * waves);
 #define CTC_LAUNCH_FUSED(SYNC, TILES, LEAN, STAGED)                                                \
     hipLaunchKernelGGL((ctc_lattice_gradient_kernel<SYNC, TILES, LEAN, STAGED>), grid, block, lds, s, meta, order, labels, emit_blank,   \
                        emit_label, lat, mass, p.costs, chain_err, sink, wk, tiles)
@@ -4734,9 +4774,10 @@ int launch_gradient(const Launch& p, void* stream)
         else                                                                                       \
             hipLaunchKernelGGL((ctc_gradient_narrow_kernel<4, STAGED>), grid, block, lds, s, args, meta, p.labels, emit_blank, emit_label, lattice_blocks(p)); \
     } while (0)
-    const WideRows rows = wide_rows(args.groups + fill.rounds);
-    const int64_t tiles = p.A > kDirectMaxA ? 0 : args.tiles(), across = std::min<int64_t>(tiles, 1 << 20);
-    const dim3 grid = p.A > kDirectMaxA ? dim3(p.B, rows.y, rows.z) : dim3(static_cast<unsigned>(across), static_cast<unsigned>((tiles + across - 1) / across)), block(p.A > kDirectMaxA ? 64 * args.waves : kRowThreads);
+    const WideRows rows = p.A > kDirectMaxA ? wide_rows(args.groups + fill.rounds) : WideRows{1, 1};
+    const unsigned tiles = args.segment_tile[TileArgs::kSegments], across = std::min(std::max(tiles, 1u), 1u << 20);
+    const dim3 narrow = args.by_end ? dim3(across, (tiles + across - 1) / across) : dim3(args.segment_groups[0], p.B);
+    const dim3 grid = p.A > kDirectMaxA ? dim3(p.B, rows.y, rows.z) : narrow, block(p.A > kDirectMaxA ? 64 * args.waves : kRowThreads);
     return checked_launch([&] {
         if (p.A > kDirectMaxA && p.defer_columns > 0)
             hipLaunchKernelGGL(ctc_gradient_wide_kernel<true>, grid, block, lds, s, args, meta, p.labels, emit_blank, emit_label,

@@ -1907,11 +1907,13 @@ __device__ __forceinline__ int lane_frame(int window_top, int own_top)
 // at most 2^(kEasyHigh + n (kSmoothFrames + g + 1.6)).  A chunk, g = 79: 2^-982 and 2^936; kSteepSteps, g = 100, kSteepSmoothFrames: 2^-750 and 2^1005.
 // Where all probabilities of the utterance are above 2^kGentleMinLog2 (g = 32) the look is taken kLookAhead steps before the chunk ends, and the range is wider.  (Looked at
 // after blocks of 16 frames, what is admissible is so narrow that the lanes above the front of the lattice renewed at every second block.)
-// Where the renewal puts the largest value of a window: 2^kHeadroom below its frame, as values grow more often than they shrink.
+// Rough utterances are looked at then too, in a range that is narrower for it; steep ones when the steps are done.
+// Where a gentle one's renewal puts the largest value of a window: 2^kHeadroom below its frame, as values grow more often than they shrink.  (For rough ones, whose
+// lanes hold states further apart, it made more of them strained: 64 x 750 frames, logits of deviation 6, 52 us a call, 81 with it.)
 constexpr int kHeadroom = 100;
-__device__ __forceinline__ int chain_frame(int window_top, int own_top)
+__device__ __forceinline__ int chain_frame(int window_top, int own_top, int headroom)
 {
-    return window_top + kHeadroom - min(max(window_top - own_top - (kFrameSlack - kHeadroom), 0), kFrameDrop + kHeadroom);
+    return window_top + headroom - min(max(window_top - own_top - (kFrameSlack - headroom), 0), kFrameDrop + headroom);
 }
 constexpr int kLookAhead = 1;
 constexpr int kEasyLow = -350, kEasyHigh = 99;
@@ -1919,6 +1921,7 @@ constexpr int kSmoothFrames = 24, kSteepSmoothFrames = 125;
 // Gentle utterances.  States handed up are taken into the frames of the lanes that take them where those are no more than kShiftUp below and kShiftDown above the frames that they
 // come in: a chunk later 2^-1018 and 2^966 at worst.  (In the frames that they come in, all factors between frames had to be made anew whenever a wavefront below had renewed its own.)
 constexpr int kGentleLow = -450, kGentleHigh = 120, kGentleSmooth = 36;
+constexpr int kRoughLow = -310, kRoughHigh = 80;
 constexpr int kShiftUp = 220, kShiftDown = 280;
 constexpr bool frames_last(int steps, float min_log2, int smooth, int low = kEasyLow, int high = kEasyHigh)
 {
@@ -1927,6 +1930,8 @@ constexpr bool frames_last(int steps, float min_log2, int smooth, int low = kEas
 }
 static_assert(frames_last(kChunk + kLookAhead, kGentleMinLog2, kGentleSmooth, kGentleLow - kShiftDown, kGentleHigh + kShiftUp), "a gentle one's chunk");
 static_assert(frames_last(kChunk, kRoughMinLog2, kSmoothFrames), "a chunk");
+static_assert(kRoughLow + (kChunk + kLookAhead) * kRoughMinLog2 >= -1022 && kRoughHigh + (kChunk + kLookAhead) * (1.6f - kRoughMinLog2 + kSmoothFrames) < 1023,
+              "a rough one's chunk, from look to renewal");
 static_assert(frames_last(kSteepSteps, kLinearMinLog2, kSteepSmoothFrames), "a steep one's steps");
 // Does a renewal leave a lane's first blank below 2^kStrained of its new frame?  (`rise`: from the frame it had.  A lane without mass has a blank of 0, whose
 // exponent reads 0.)  What is above keeps all its bits until the next renewal: 2^(kStrained + kLinearMinLog2) is above fp64's smallest normal number.
@@ -1937,18 +1942,19 @@ static_assert(frames_last(kSteepSteps, kLinearMinLog2, kSteepSmoothFrames), "a s
 // logits of deviation 4, which seldom strain a lane.)
 constexpr int kStrained = -900;
 static_assert(kStrained + kLinearMinLog2 >= -1022, "what a first blank of 2^kStrained gives its label");
-__device__ __forceinline__ bool strains(double first, int rise) { return __ballot(__builtin_amdgcn_frexp_exp(first) + rise < kStrained) != 0; }
+// (Lanes behind the label's end hold nothing that anybody needs.)
+__device__ __forceinline__ bool strains(double first, int rise, bool of_label) { return __ballot(of_label && __builtin_amdgcn_frexp_exp(first) + rise < kStrained) != 0; }
 // The test, on the exponent of the largest value of a lane: one subtraction and one unsigned compare.  Lanes without mass pass it.
 struct EasyRange {
-    int low, width, smooth;                              // smooth: for a pair
+    int low, width, smooth, headroom;                    // smooth: for a pair
     __device__ __forceinline__ EasyRange(bool gentle, bool steep)
-        : low(gentle ? kGentleLow : kEasyLow), width(gentle ? kGentleHigh - kGentleLow : kEasyHigh - kEasyLow),
-          smooth(gentle ? kGentleSmooth : (steep ? kSteepSmoothFrames : kSmoothFrames))
+        : low(gentle ? kGentleLow : (steep ? kEasyLow : kRoughLow)), width(gentle ? kGentleHigh - kGentleLow : (steep ? kEasyHigh - kEasyLow : kRoughHigh - kRoughLow)),
+          smooth(gentle ? kGentleSmooth : (steep ? kSteepSmoothFrames : kSmoothFrames)), headroom(gentle ? kHeadroom : 0)
     {
     }
     __device__ __forceinline__ bool outside(double top) const
     {
-        static_assert(kEasyLow < -1 && kEasyHigh > 0 && kGentleLow < -1 && kGentleHigh > 0, "zero, whose exponent reads 0, is in it");
+        static_assert(kEasyLow < -1 && kEasyHigh > 0 && kRoughLow < -1 && kRoughHigh > 0 && kGentleLow < -1 && kGentleHigh > 0, "zero, whose exponent reads 0, is in it");
         return static_cast<unsigned>(__builtin_amdgcn_frexp_exp(top) - 1 - low) > static_cast<unsigned>(width);
     }
 };
@@ -1996,7 +2002,7 @@ struct ChainFrames {
         int window = mine;
 #pragma unroll
         for (int k = 0; k < kSteps; ++k) window = window_max_step(window, mine);
-        int next = massive != 0 ? chain_frame(window, mine) : frame;
+        int next = massive != 0 ? chain_frame(window, mine, easy.headroom) : frame;
         const int front = massive != 0 ? 63 - __builtin_clzll(massive) : reference;
         const int beyond = __builtin_amdgcn_readlane(next, front);
         next = static_cast<int>(threadIdx.x & 63) > front ? beyond : next;
@@ -2028,13 +2034,14 @@ struct HandOvers {
     const char *in, *out;                                // in the first slot: what this lane takes (its tag: looks at), what it hands up
     bool takes, hands;                                   // this lane is one of the halo's; of the ones above's
     int behind;                                          // by how much the tag that it reads may be behind the hand-over
-    unsigned shift;                                      // ... and its frame differ
+    unsigned shift;                                      // ... and its frame differ, from shift_down below this lane's on
+    int shift_down;
     int number = 2;                                      // of the coming hand-over, times two, and one more where states are due for a renewal (kLeft: the chain has been left)
     unsigned round = 0;                                  // the first slot of this round of blocks, in bytes
     int2 tag{};
     double2 states[kPairs] = {};
     unsigned long long late = 0, shifted = 0;
-    __device__ __forceinline__ HandOvers(void* lds, int wave, int last_wave, int halo)
+    __device__ __forceinline__ HandOvers(void* lds, int wave, int last_wave, int halo, bool gentle)
     {
         const int lane = threadIdx.x & 63, first = 64 - halo;
         takes = wave > 0 && lane < halo;
@@ -2043,7 +2050,8 @@ struct HandOvers {
         in = reinterpret_cast<const char*>(&halo_wave<Wave>(lds, looks_up ? wave + 1 : (wave > 0 ? wave - 1 : 0))->slot[0].states[0][takes ? lane : (looks_up ? halo - 1 : 0)]);
         out = reinterpret_cast<const char*>(&halo_wave<Wave>(lds, wave)->slot[0].states[0][hands ? lane - first : 0]);
         behind = takes ? 0 : (looks_up ? 2 * (kExchange == Exchange::kBlock ? kRing : kRing / 2) : kNever);
-        shift = takes ? kShiftDown + kShiftUp : ~0u;
+        shift_down = gentle ? kShiftDown : 0;
+        shift = takes ? (gentle ? kShiftDown + kShiftUp : 0) : ~0u;
         asm volatile("" : "+v"(number));                 // (in a vector register, from where it is stored)
     }
     // A lane's states and tag in the slot of this round's block `block`.
@@ -2080,7 +2088,7 @@ struct HandOvers {
     __device__ __forceinline__ void look(int frame)
     {
         late = __ballot(static_cast<unsigned>(number - tag.y) > static_cast<unsigned>(behind));
-        shifted = __ballot(static_cast<unsigned>(tag.x - frame + kShiftDown) > shift);
+        shifted = __ballot(static_cast<unsigned>(tag.x - frame + shift_down) > shift);
         arrive();
     }
     // Where any are: waits for what is late, and gives the lanes that take states the frames of those.  due: so are the states handed up (whoever takes them
@@ -2174,8 +2182,8 @@ __device__ __forceinline__ ChainEnd run_chain_linear(const Utt m, const int u, c
     const int last_wave = m.waves - 1;
     int budget = m.poll_budget;
     bool lost = false;
-    HandOvers<1, kHandsOver> with(kExchange ? lds : nullptr, wave, last_wave, halo);
-    const unsigned long long look = gentle && !kSteep ? 0ull : ~0ull;      // once a chunk, whatever the frames
+    HandOvers<1, kHandsOver> with(kExchange ? lds : nullptr, wave, last_wave, halo, gentle && !kSteep);
+    const unsigned long long look = kSteep ? ~0ull : 0ull;      // after every chunk, whatever the frames
 
     double v_blank = (j == 0) ? 1.0 : 0.0, v_label = 0.0;
     ChainFrames<1, kSteep> f(gentle && !kSteep);
@@ -2198,7 +2206,7 @@ __device__ __forceinline__ ChainEnd run_chain_linear(const Utt m, const int u, c
     };
     auto renew_frames = [&](int unit) __attribute__((always_inline)) {
         const int rise = f.renew(top_value(), halo > 0 ? halo - 1 : 0);
-        if (__builtin_expect(strains(v_blank, rise), 0)) leave(unit, f.frame + rise);
+        if (__builtin_expect(strains(v_blank, rise, j <= L), 0)) leave(unit, f.frame + rise);
         v_blank = __builtin_amdgcn_ldexp(v_blank, rise);
         v_label = __builtin_amdgcn_ldexp(v_label, rise);
         skip_scale = skip_ok ? f.scale : 0.0;
@@ -2217,7 +2225,7 @@ __device__ __forceinline__ ChainEnd run_chain_linear(const Utt m, const int u, c
     };
     auto end_block = [&](int block, bool exchange, int unit) __attribute__((always_inline)) {
         const bool unusual = (outside | f.rough | look | (exchange ? with.late | with.shifted : 0ull)) != 0;
-        if (exchange && __builtin_expect(unusual, 0)) with.prepare(block, f.renewal_due(top_value()), f.frame, budget, lost);
+        if (exchange && __builtin_expect(unusual, 0)) with.prepare(block, (outside | f.rough) != 0, f.frame, budget, lost);
         if (exchange) {
             const double2 mine[1] = {make_double2(v_blank, v_label)};
             with.publish(block, mine, f.frame);
@@ -2230,12 +2238,16 @@ __device__ __forceinline__ ChainEnd run_chain_linear(const Utt m, const int u, c
         }
         if (__builtin_expect(unusual, 0)) {
             const double top = top_value();
-            if (exchange) {
-                with.number &= ~1;
-                f.rescale(__ballot(!(top > 0.0)));
-                skip_scale = skip_ok ? f.scale : 0.0;
+            if (exchange) with.number &= ~1;
+            bool renews = __ballot(f.easy.outside(top)) != 0;      // (then the factors between the frames are made there)
+            if (!renews) {
+                if (exchange) {
+                    f.rescale(__ballot(!(top > 0.0)));
+                    skip_scale = skip_ok ? f.scale : 0.0;
+                }
+                renews = f.rough != 0;
             }
-            if (f.renewal_due(top)) renew_frames(unit);
+            if (renews) renew_frames(unit);
         }
     };
     auto checkpoint = [&]() __attribute__((always_inline)) {
@@ -2287,7 +2299,10 @@ __device__ __forceinline__ ChainEnd run_chain_linear(const Utt m, const int u, c
             if (q == kChunk - 1 - kLookAhead) look_ahead(kHere);
         }
         if (kEnds) end_block(k >> 1, kHere, 2 * i + 2);
-        else if (__builtin_expect((outside | f.rough | look) != 0, 0)) renew_if_due(2 * i + 2);
+        else if (__builtin_expect((outside | f.rough | look) != 0, 0)) {
+            if (kSteep) renew_if_due(2 * i + 2);
+            else renew_frames(2 * i + 2);
+        }
         if (kExchange && k == 3) with.next_round();
     };
     chain_schedule(count, fetch, run);
@@ -2354,8 +2369,8 @@ __device__ __forceinline__ ChainEnd run_chain_linear2(const Utt m, const int u, 
     const int last_wave = waves - 1;
     int budget = m.poll_budget;
     bool lost = false;
-    HandOvers<2, kHandsOver> with(kExchange ? lds : nullptr, wave, last_wave, halo);
-    const unsigned long long look = gentle && !kSteep ? 0ull : ~0ull;      // once a chunk, whatever the frames
+    HandOvers<2, kHandsOver> with(kExchange ? lds : nullptr, wave, last_wave, halo, gentle && !kSteep);
+    const unsigned long long look = kSteep ? ~0ull : 0ull;      // after every chunk, whatever the frames
 
     double va_blank = (ja == 0) ? 1.0 : 0.0, va_label = 0.0, vb_blank = 0.0, vb_label = 0.0;
     ChainFrames<2, kSteep> f(gentle && !kSteep);
@@ -2377,7 +2392,7 @@ __device__ __forceinline__ ChainEnd run_chain_linear2(const Utt m, const int u, 
     };
     auto renew_frames = [&](int unit) __attribute__((always_inline)) {
         const int rise = f.renew(top_value(), halo > 0 ? halo - 1 : 0);
-        if (__builtin_expect(strains(va_blank, rise), 0)) leave(unit, f.frame + rise);
+        if (__builtin_expect(strains(va_blank, rise, ja <= L), 0)) leave(unit, f.frame + rise);
         va_blank = __builtin_amdgcn_ldexp(va_blank, rise);
         va_label = __builtin_amdgcn_ldexp(va_label, rise);
         vb_blank = __builtin_amdgcn_ldexp(vb_blank, rise);
@@ -2403,7 +2418,7 @@ __device__ __forceinline__ ChainEnd run_chain_linear2(const Utt m, const int u, 
     };
     auto end_block = [&](int block, bool exchange, int unit) __attribute__((always_inline)) {
         const bool unusual = (outside | f.rough | look | (exchange ? with.late | with.shifted : 0ull)) != 0;
-        if (exchange && __builtin_expect(unusual, 0)) with.prepare(block, f.renewal_due(top_value()), f.frame, budget, lost);
+        if (exchange && __builtin_expect(unusual, 0)) with.prepare(block, (outside | f.rough) != 0, f.frame, budget, lost);
         if (exchange) {
             const double2 mine[2] = {make_double2(va_blank, va_label), make_double2(vb_blank, vb_label)};
             with.publish(block, mine, f.frame);
@@ -2418,12 +2433,16 @@ __device__ __forceinline__ ChainEnd run_chain_linear2(const Utt m, const int u, 
         }
         if (__builtin_expect(unusual, 0)) {
             const double top = top_value();
-            if (exchange) {
-                with.number &= ~1;
-                f.rescale(__ballot(!(top > 0.0)));
-                skip_a_scale = skip_a ? f.scale : 0.0;
+            if (exchange) with.number &= ~1;
+            bool renews = __ballot(f.easy.outside(top)) != 0;      // (then the factors between the frames are made there)
+            if (!renews) {
+                if (exchange) {
+                    f.rescale(__ballot(!(top > 0.0)));
+                    skip_a_scale = skip_a ? f.scale : 0.0;
+                }
+                renews = f.rough != 0;
             }
-            if (f.renewal_due(top)) renew_frames(unit);
+            if (renews) renew_frames(unit);
         }
     };
     // One step (see run_chain_linear): the pairs' own sums fill the time that the shift takes.
@@ -2476,7 +2495,10 @@ __device__ __forceinline__ ChainEnd run_chain_linear2(const Utt m, const int u, 
             if (q == kChunk - 1 - kLookAhead) look_ahead(kHere);
         }
         if (kEnds) end_block(k >> 1, kHere, 2 * i + 2);
-        else if (__builtin_expect((outside | f.rough | look) != 0, 0)) renew_if_due(2 * i + 2);
+        else if (__builtin_expect((outside | f.rough | look) != 0, 0)) {
+            if (kSteep) renew_if_due(2 * i + 2);
+            else renew_frames(2 * i + 2);
+        }
         if (kExchange && k == 3) with.next_round();
     };
     chain_schedule(count, fetch, run);

@@ -353,6 +353,14 @@ CTC_HOST_DEVICE inline bool tight_fit(int frames, int label_length, int repeats)
 {
     return frames - label_length - repeats < kTightFrames;
 }
+// Where pair j of a linear-domain chain finds its label state's emissions, in bytes from the chunk's first (`column`: the symbol, or the position where they are gathered).  Pairs
+// from L on have none: past the end of the buffer, whose loads give 0 there.
+constexpr unsigned kNoColumn = 0x80000000u;
+CTC_HOST_DEVICE inline unsigned emission_column(int j, int L, int column)
+{
+    return j < L ? static_cast<unsigned>(column) * static_cast<unsigned>(kChunkSteps * sizeof(float)) : kNoColumn;
+}
+
 // Lattice wavefronts of one launch beyond which chains are planned for total work: two per SIMD
 // of the 256 compute units.
 constexpr int kCrowdedWaves = 2 * 4 * 256;

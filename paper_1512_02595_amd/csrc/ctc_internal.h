@@ -311,6 +311,21 @@ inline bool gradient_in_lattice_launch(double early, double late, double chain_u
     return !beside_by_work(max_waves, n_chains, n_cu) || gradient_beside_long_chains(early, late, chain_us, n_chains, n_cu);
 }
 
+// Narrow alphabets, gradients whose blocks are not all shared by several wavefronts: of how many blocks times pieces, at most, those are which are, in the utterances that end last.
+// By then compute units are free, and a label of five pieces keeps one wavefront to a block for 18 us after its chains have ended: us a call with none / 2048 / 4096 / 8192,
+// 32 x 1500 x 29 122.9 / 111.6 / 111.6 / 111.2; the same, lengths from 400 on, 120.3 / 109.0 / 108.8 / 108.5; 128 x 750 x 29 49.2 / 45.3 / 45.1 / 45.0.  But not where those that
+// end in the last 15 % of the time have as many as the chip has places for wavefronts (`late`, in blocks times pieces; the batches above have up to 3000): then a shared block
+// only costs more places.  64 utterances of 750 frames and 225 symbols 61.8 / 64.3 / 67.3 / 72.3, 128 of them 82.1 / 84.3 / 86.6 / 92.6, 32 of 1500 frames and 540 symbols 152.7 /
+// 157.3 / 166.8 / 166.1 (48 of 1500 and 400 116.5 / 116.4 / 118.0 / 119.9; 64 of 900 and 400 94.5 / 88.8 / 90.5 / 91.0).
+// With more chains than compute units, whose blocks are still under way, or where the lengths are not known here (late < 0), in between: 512 x 750 x 29 105.7 / 104.6 / 106.0 / 107.0;
+// lengths on the GPU, 100 x 1000 x 29 67.7 / 61.2 / 61.9 / 66.5, 64 x 750 with labels of up to 270 symbols 68.0 / 66.9 / 70.5 / 70.5.
+constexpr int kShareLast = 8192, kShareSome = 2048, kLateFillsChip = 4096;
+inline int blocks_to_share(int64_t late, int n_chains, int n_cu)
+{
+    if (n_chains > n_cu || late < 0) return kShareSome;
+    return late <= kLateFillsChip ? kShareLast : 0;
+}
+
 constexpr int kDoneStride = 16;      // words between two utterances' words: a line each for those who poll
 constexpr int kTakenWord = 1;        // which of them says that the chains have a workgroup (take_chain; the first is the counter)
 constexpr int kDoneWords = 2;
@@ -602,6 +617,7 @@ struct Launch {
     int max_waves;      // wavefronts per lattice block
     int max_frames;     // longest utterance among those whose lattice runs
     int max_label;      // longest label of the batch
+    int share_last;     // narrow alphabets: blocks_to_share
     const int32_t* frames_by_end = nullptr;   // host metadata: frames of the utterances (0: there is no lattice), those first whose chains end first; for this call only
     bool needs_barrier; // some utterance's label leaves no room for a halo
     const void* x;

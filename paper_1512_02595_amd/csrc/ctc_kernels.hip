@@ -3698,14 +3698,10 @@ __device__ __forceinline__ void for_pieces(int L, int first, int step, F&& for_p
 // Wavefronts that share a block in the narrow gradient kernel, one piece each up to four -- in launches of few blocks,
 // which last as long as one block takes (English minibatch: 18.8 -> 16.7 us; 512 utterances: 69 -> 83 us).
 constexpr int kShareBlocksMost = 8192;    // blocks times pieces: two rounds of what the chip holds
-// In a lattice launch that has more, those of the utterances that end last (about): by then compute units are free, and a label of five pieces keeps one wavefront to a
-// block for 18 us after its chains have ended.  As many blocks times pieces as this, fewer where there are more chains than compute units, whose blocks are
-// still under way.  us a call with none / 2048 / 4096 / 8192: 32 x 1500 x 29 128.1 / 121.3 / 119.8 / 119.9; the same, lengths from 400 on, 111.9 / 103.2 / 101.1 / 100.7; 128 x
-// 750 x 29 49.4 / 49.4 / 49.4 / 46.6; 512 x 750 x 29 116.9 / 115.4 / 116.4 / 117.7; 300 x 400 x 40 50.1 / 50.0 / 50.0 / 50.0.
-constexpr int kShareLast = 8192, kShareLastCrowded = 2048;
+// In a lattice launch that has more, those of the utterances that end last (about; blocks_to_share).
 inline int shared_utterances(const Launch& p, int blocks)
 {
-    return std::min(p.B, (p.n_chains > p.n_cu ? kShareLastCrowded : kShareLast) / (blocks * std::max(1, label_pieces(p.max_label))));
+    return std::min(p.B, p.share_last / (blocks * std::max(1, label_pieces(p.max_label))));
 }
 __host__ __device__ constexpr int block_waves(int L) { return label_pieces(L) <= 1 ? 1 : (label_pieces(L) == 2 ? 2 : 4); }
 // The domain of an utterance as its chains published it (a word per direction).

@@ -1418,8 +1418,8 @@ struct LinearWave {
         Tag tag[kLanes];
     } slot[kRing];                                       // of a block's end, by the block's number
 };
-// How often the wavefronts of a chain hand over: never (there is one), at every block's end, at every second one's.
-enum class Exchange { kNone, kBlock, kTwoBlocks };
+// How often the wavefronts of a chain hand over: never (there is one), at every block's end, at every second one's; or whichever of these it is (steep chains).
+enum class Exchange { kNone, kBlock, kTwoBlocks, kAny };
 
 // What a wavefront had when it left the recursion on probabilities (finish_with_exponents): a lane's states and frame (kLogs: they are logarithms).
 // (In LDS, from where they are read again: as values that leave the loop from a dozen places they took more registers than there are.  So the wavefront goes
@@ -2027,7 +2027,7 @@ struct ChainFrames {
 // Unusual ends: 2 of 47 in the lowest wavefront of a label of 190 symbols, 10 in the highest.)
 constexpr int kSlack = 2;                                // (s_sleep: 64 clocks each)
 constexpr int kAskAhead = 5, kAskAhead2 = 4;             // steps before the block's end, with one pair to a lane and with two
-template <int kPairs, Exchange kExchange>
+template <int kPairs>
 struct HandOvers {
     static constexpr int kNever = 0x7FFFFFFF, kLeft = 1 << 30;
     typedef LinearWave<kPairs> Wave;
@@ -2042,7 +2042,7 @@ struct HandOvers {
     int2 tag{};
     double2 states[kPairs] = {};
     unsigned long long late = 0, shifted = 0;
-    __device__ __forceinline__ HandOvers(void* lds, int wave, int last_wave, int halo, bool gentle)
+    __device__ __forceinline__ HandOvers(void* lds, int wave, int last_wave, int halo, bool every_block, bool gentle)
     {
         const int lane = threadIdx.x & 63, first = 64 - halo;
         takes = wave > 0 && lane < halo;
@@ -2050,7 +2050,7 @@ struct HandOvers {
         const bool looks_up = wave < last_wave && lane == 63;
         in = reinterpret_cast<const char*>(&halo_wave<Wave>(lds, looks_up ? wave + 1 : (wave > 0 ? wave - 1 : 0))->slot[0].states[0][takes ? lane : (looks_up ? halo - 1 : 0)]);
         out = reinterpret_cast<const char*>(&halo_wave<Wave>(lds, wave)->slot[0].states[0][hands ? lane - first : 0]);
-        behind = takes ? 0 : (looks_up ? 2 * (kExchange == Exchange::kBlock ? kRing : kRing / 2) : kNever);
+        behind = takes ? 0 : (looks_up ? 2 * (every_block ? kRing : kRing / 2) : kNever);
         shift_down = gentle ? kShiftDown : 0;
         shift = takes ? (gentle ? kShiftDown + kShiftUp : 0) : ~0u;
         asm volatile("" : "+v"(number));                 // (in a vector register, from where it is stored)
@@ -2191,7 +2191,8 @@ __device__ __forceinline__ ChainEnd run_chain_linear(const Utt m, const int u, c
     const int last_wave = m.waves - 1;
     int budget = m.poll_budget;
     bool lost = false;
-    HandOvers<1, kHandsOver> with(kExchange ? lds : nullptr, wave, last_wave, halo, gentle && !kSteep);
+    const bool every_block = kHandsOver == Exchange::kBlock || (kHandsOver == Exchange::kAny && halo < 2 * kBlockFrames);
+    HandOvers<1> with(kExchange ? lds : nullptr, wave, last_wave, halo, every_block, gentle && !kSteep);
     const unsigned long long look = kSteep ? ~0ull : 0ull;      // after every chunk, whatever the frames
 
     double v_blank = (j == 0) ? 1.0 : 0.0, v_label = 0.0;
@@ -2297,17 +2298,17 @@ __device__ __forceinline__ ChainEnd run_chain_linear(const Utt m, const int u, c
     auto run = [&](auto set, int i) __attribute__((always_inline)) {
         constexpr int k = decltype(set)::value;
         constexpr bool kEnds = (k & 1) != 0;             // the chunk ends a block
-        constexpr bool kHere = kEnds && kExchange && (k == 3 || kHandsOver == Exchange::kBlock);
+        const bool here = kEnds && kExchange && (kHandsOver != Exchange::kAny || last_wave > 0) && (k == 3 || every_block);
         if (kMode == Mode::kGrad && !kEnds) checkpoint();
         double el_d = static_cast<double>(el[k][0]);
 #pragma unroll
         for (int q = 0; q < kChunk; ++q) {
             advance(el_d, el[k][q + 1 < kChunk ? q + 1 : q]);
             if (kSteep && q == kSteepSteps - 1) renew_if_due(2 * i + 1);
-            if (kHere && q == kChunk - 1 - kAskAhead) with.ask(k >> 1);
-            if (q == kChunk - 1 - kLookAhead) look_ahead(kHere);
+            if (here && q == kChunk - 1 - kAskAhead) with.ask(k >> 1);
+            if (q == kChunk - 1 - kLookAhead) look_ahead(here);
         }
-        if (kEnds) end_block(k >> 1, kHere, 2 * i + 2);
+        if (kEnds) end_block(k >> 1, here, 2 * i + 2);
         else if (__builtin_expect((outside | f.rough | look) != 0, 0)) {
             if (kSteep) renew_if_due(2 * i + 2);
             else renew_frames(2 * i + 2);
@@ -2378,7 +2379,8 @@ __device__ __forceinline__ ChainEnd run_chain_linear2(const Utt m, const int u, 
     const int last_wave = waves - 1;
     int budget = m.poll_budget;
     bool lost = false;
-    HandOvers<2, kHandsOver> with(kExchange ? lds : nullptr, wave, last_wave, halo, gentle && !kSteep);
+    const bool every_block = kHandsOver == Exchange::kBlock || (kHandsOver == Exchange::kAny && 2 * halo < 2 * kBlockFrames);
+    HandOvers<2> with(kExchange ? lds : nullptr, wave, last_wave, halo, every_block, gentle && !kSteep);
     const unsigned long long look = kSteep ? ~0ull : 0ull;      // after every chunk, whatever the frames
 
     double va_blank = (ja == 0) ? 1.0 : 0.0, va_label = 0.0, vb_blank = 0.0, vb_label = 0.0;
@@ -2494,16 +2496,16 @@ __device__ __forceinline__ ChainEnd run_chain_linear2(const Utt m, const int u, 
     auto run = [&](auto set, int i) __attribute__((always_inline)) {
         constexpr int k = decltype(set)::value;
         constexpr bool kEnds = (k & 1) != 0;             // the chunk ends a block
-        constexpr bool kHere = kEnds && kExchange && (k == 3 || kHandsOver == Exchange::kBlock);
+        const bool here = kEnds && kExchange && (kHandsOver != Exchange::kAny || last_wave > 0) && (k == 3 || every_block);
         if (kMode == Mode::kGrad && !kEnds) checkpoint();
 #pragma unroll
         for (int q = 0; q < kChunk; ++q) {
             advance(ela[k][q], elb[k][q]);
             if (kSteep && q == kSteepSteps - 1) renew_if_due(2 * i + 1);
-            if (kHere && q == kChunk - 1 - kAskAhead2) with.ask(k >> 1);
-            if (q == kChunk - 1 - kLookAhead) look_ahead(kHere);
+            if (here && q == kChunk - 1 - kAskAhead2) with.ask(k >> 1);
+            if (q == kChunk - 1 - kLookAhead) look_ahead(here);
         }
-        if (kEnds) end_block(k >> 1, kHere, 2 * i + 2);
+        if (kEnds) end_block(k >> 1, here, 2 * i + 2);
         else if (__builtin_expect((outside | f.rough | look) != 0, 0)) {
             if (kSteep) renew_if_due(2 * i + 2);
             else renew_frames(2 * i + 2);
@@ -2990,10 +2992,14 @@ __device__ __forceinline__ int lattice_body(const int chain, const Utt* __restri
                     if (forward) of_direction(std::false_type{}, exchange);
                     else of_direction(std::true_type{}, exchange);
                 };
-                // (a halo lasts as many frames as it has pairs)
-                if (kSync == Sync::kNone || waves == 1) handing_over(std::integral_constant<Exchange, Exchange::kNone>{});
-                else if ((two_pairs ? 2 * m.halo2 : m.halo) < 2 * kBlockFrames) handing_over(std::integral_constant<Exchange, kSync == Sync::kHalo ? Exchange::kBlock : Exchange::kNone>{});
-                else handing_over(std::integral_constant<Exchange, kSync == Sync::kHalo ? Exchange::kTwoBlocks : Exchange::kNone>{});
+                // (a halo lasts as many frames as it has pairs.  Steep chains, which are rare, ask as they go: with a loop for each kind of theirs as well the largest of these kernels had
+                // 324 KB, so 249, and the build took 2.6 minutes, so 1.7.  us a call: 64 x 750 x 29, logits of deviation 6, 55.7 and 55.0, cost only, of deviation 4, 32.9 and 32.3.)
+                if (kSync == Sync::kNone || (waves == 1 && !kSteep)) handing_over(std::integral_constant<Exchange, Exchange::kNone>{});
+                else if constexpr (kSync == Sync::kHalo) {
+                    if constexpr (kSteep) handing_over(std::integral_constant<Exchange, Exchange::kAny>{});
+                    else if ((two_pairs ? 2 * m.halo2 : m.halo) < 2 * kBlockFrames) handing_over(std::integral_constant<Exchange, Exchange::kBlock>{});
+                    else handing_over(std::integral_constant<Exchange, Exchange::kTwoBlocks>{});
+                }
             };
             if (__builtin_expect(steep, 0)) run(std::true_type{});
             else run(std::false_type{});

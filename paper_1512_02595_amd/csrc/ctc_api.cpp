@@ -410,8 +410,7 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
     by_weight.resize(static_cast<size_t>(n_run));
     for (int i = 0; i < n_run; ++i) {
         const int b = order[i];
-        const bool logs = c.mode == Mode::kBest || (meta[b].flags & kUttLogDomain) != 0, two = !logs && (meta[b].flags & kUttTwoPairs) != 0;
-        by_weight[i] = (~static_cast<uint64_t>(chain_weight(meta[b].Tb, chain_waves(b), two, logs, crowded)) << 16) | static_cast<uint64_t>(b);
+        by_weight[i] = (~static_cast<uint64_t>(chain_weight(meta[b], c.mode == Mode::kBest, crowded)) << 16) | static_cast<uint64_t>(b);
     }
     std::sort(by_weight.begin(), by_weight.end());
     thread_local std::vector<int32_t> running, run_frames, run_waves;

@@ -379,17 +379,34 @@ CTC_HOST_DEVICE inline unsigned emission_column(int j, int L, int column)
 // Lattice wavefronts of one launch beyond which chains are planned for total work: two per SIMD
 // of the 256 compute units.
 constexpr int kCrowdedWaves = 2 * 4 * 256;
-// What an utterance weighs in the orders of chains and of ends: how long its chains take, a frame's time in ns (750 frames, alone on the chip), where a chain has SIMDs of
-// its own; in crowded launches, where what counts is how much they keep SIMDs busy, frames times wavefronts.  (By frames times wavefronts throughout, an utterance of
-// two wavefronts with two pairs to a lane, which lasts longest, was taken to end early.)
-CTC_HOST_DEVICE inline int64_t chain_weight(int frames, int waves, bool two_pairs, bool log_domain, bool crowded)
+// How an utterance's chains run, for its weight: on probabilities with a pair to a lane or two, on logarithms, or as the best alignment's.
+enum class ChainForm { kOnePair, kTwoPairs, kLogs, kBest };
+CTC_HOST_DEVICE inline ChainForm chain_form(int flags, bool best)
+{
+    if (best) return ChainForm::kBest;
+    return (flags & kUttLogDomain) ? ChainForm::kLogs : ((flags & kUttTwoPairs) ? ChainForm::kTwoPairs : ChainForm::kOnePair);
+}
+// What an utterance weighs in the orders of chains and of ends: how long its chains take, a frame's time in ns (the difference between 1500 frames and 750, alone on the chip),
+// where a chain has SIMDs of its own; in crowded launches, where what counts is how much they keep SIMDs busy, frames times wavefronts.  (By frames times wavefronts throughout,
+// an utterance of two wavefronts with two pairs to a lane, which lasts longest, was taken to end early.)  Measured with 1 / 2 / 3 / 4 / 5 and 6 / 7 and 8 / 10 to 12 wavefronts:
+// one pair 20 / 23 / 22 / 23; two pairs - / 31 / 31 / 31 / 55; logarithms 101 / 109 / 111 / 115 / 197 / 196 / 287; alignments 51 / 59 / 60 / 65 / 87 / 89 / 120.
+CTC_HOST_DEVICE inline int64_t chain_weight(int frames, int waves, ChainForm form, bool crowded)
 {
     if (crowded) return static_cast<int64_t>(frames) * waves;
-    const int per_frame = log_domain ? 60 + 25 * waves : (two_pairs ? (waves <= 1 ? 30 : (waves <= 4 ? 32 + 4 * waves : 65)) : (waves <= 1 ? 19 : 19 + 3 * waves));
+    const int per_simd = (waves + 3) / 4;
+    int per_frame = waves <= 1 ? 20 : 23;
+    if (form == ChainForm::kTwoPairs) per_frame = waves <= 4 ? 31 : 55;
+    if (form == ChainForm::kLogs) per_frame = waves <= 4 ? 97 + 4 * waves : 97 * per_simd;
+    if (form == ChainForm::kBest) per_frame = waves <= 4 ? 47 + 5 * waves : 20 + 34 * per_simd;
     return static_cast<int64_t>(frames) * per_frame;
 }
+CTC_HOST_DEVICE inline int64_t chain_weight(const Utt& m, bool best, bool crowded)
+{
+    const ChainForm form = chain_form(m.flags, best);
+    return chain_weight(m.Tb, form == ChainForm::kTwoPairs ? m.waves2 : m.waves, form, crowded);
+}
 // The order in which the lattice launch takes its chains (entry = utterance * 2 + direction).
-// `utt`: the utterances whose lattice runs, heaviest (frames x wavefronts) first; `dirs`: 2 when
+// `utt`: the utterances whose lattice runs, heaviest (chain_weight) first; `dirs`: 2 when
 // the backward chains run too.  Up to `n_cu` chains (one per compute unit) keep that order.
 // Beyond that, chains share compute units, and the launch lasts as long as the busiest SIMD:
 // a chain's wavefront nearly fills the SIMD it runs on, so two on one SIMD take the sum of

@@ -218,7 +218,7 @@ void ctc_upload_kernel(const int* __restrict__ host_image, int* __restrict__ ws,
 // iff T_b >= L + repeats), the wavefront plan, and the offsets of its blocks, which are laid
 // out with the strides of the largest utterance the caller allows (labels [B][max_label]; emissions, lattice and frames what
 // gathered_emissions, lattice_words and padded_frames give for T and longest_aligned).  Then the run
-// order: heaviest chains first (rank by T_b x wavefronts, ties by index), -1 for the rest.
+// order: heaviest chains first (rank by chain_weight, ties by index), -1 for the rest.
 constexpr int kPlanThreads = 1024;
 
 __global__ __launch_bounds__(kPlanThreads)
@@ -228,7 +228,7 @@ void ctc_plan_kernel(const int* __restrict__ labels, const int* __restrict__ lab
                      int Tt, int B, int A, int blank, int max_label, int poll_budget, bool crowded,
                      bool log_domain)
 {
-    __shared__ long long weight[kMaxDeviceMetaB];     // T_b x wavefronts; -1: does not run
+    __shared__ long long weight[kMaxDeviceMetaB];     // chain_weight; -1: does not run
     __shared__ int repeats[kMaxDeviceMetaB];          // adjacent equal symbols; kBadLabel added for a bad symbol
     __shared__ int s_bad, s_running;
     constexpr int kBadLabel = 1 << 20;
@@ -297,7 +297,7 @@ void ctc_plan_kernel(const int* __restrict__ labels, const int* __restrict__ lab
         m.e_off = b * (m.e_direct == kEmitSymbols ? static_cast<int64_t>(padded) * A : gathered_emissions(Tt, longest));
         m.ab_off = b * lattice_words(Tt, longest);
         meta[b] = m;
-        weight[b] = runs ? static_cast<long long>(Tb) * ((m.flags & kUttTwoPairs) ? wp2.waves : wp.waves) : -1;
+        weight[b] = runs ? chain_weight(m, false, crowded) : -1;
         if (bad) s_bad = 1;
         if (runs) atomicAdd(&s_running, 1);
     }
@@ -917,12 +917,14 @@ struct NarrowDevice {
     int n_cu;                     // compute units of the device (a multiple of kChainBlock, or 0: keep the plain order)
 };
 
-// Weight of an utterance in the run order (chain_weight; 0: its lengths are out of range).
+// Weight of an utterance in the run order (chain_weight; 0: its lengths are out of range).  Every utterance's setup weighs all of them, by their lengths alone: tight fits that
+// only repeated neighbours make weigh as if they ran on probabilities.
 __device__ __forceinline__ long long weight_of(const PlanTable& plans, int L, int Tb, int Tt, int max_label, bool log_domain, bool crowded)
 {
     if (L < 0 || L > max_label || Tb < 0 || Tb > Tt) return 0;
-    const bool two = !log_domain && Tb <= kLinearMaxFrames && plans.two_pairs(L);
-    return chain_weight(Tb, two ? plans.waves2(L) : plans.waves1(L), two, log_domain, crowded);
+    const bool logs = log_domain || Tb > kLinearMaxFrames || tight_fit(Tb, L, 0);
+    const ChainForm form = chain_form((logs ? kUttLogDomain : 0) | (plans.two_pairs(L) ? kUttTwoPairs : 0), false);
+    return chain_weight(Tb, form == ChainForm::kTwoPairs ? plans.waves2(L) : plans.waves1(L), form, crowded);
 }
 // By the whole workgroup.  Returns the record (the same in every thread).
 __device__ __forceinline__ Utt build_record(const NarrowDevice& dv, const PlanTable& plans, int b, int Tt, int B, int A,

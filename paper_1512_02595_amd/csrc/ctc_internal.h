@@ -345,8 +345,8 @@ constexpr int kUttLogDomain = 4;
 // (plan_waves2) instead of one (plan_waves): see two_pairs_per_lane.
 constexpr int kUttTwoPairs = 8;
 constexpr float kLinearMinLog2 = -100.0f;
-// Chains of the linear domain look after their lanes' exponents once a block of 16 frames where all probabilities of the utterance
-// are above the first of these, once a chunk of 8 where they are above the second, and every kSteepSteps frames otherwise.
+// Chains of the linear domain look after their lanes' exponents once a chunk of 8 frames where all probabilities of the utterance
+// are above the second of these, in a wider range where they are above the first, and every kSteepSteps frames otherwise.
 constexpr float kGentleMinLog2 = -32.0f, kRoughMinLog2 = -79.0f;
 constexpr int kSteepSteps = 4;
 constexpr int kRowsSmall = 1, kRowsRough = 2, kRowsSteep = 4;    // bits of Layout::row_flags: one below kLinearMinLog2, kGentleMinLog2, kRoughMinLog2

@@ -1905,12 +1905,15 @@ __device__ __forceinline__ int lane_frame(int window_top, int own_top)
     return window_top - min(max(window_top - own_top - kFrameSlack, 0), kFrameDrop);
 }
 // A renewal (about 300 clocks, with what else is unusual at a block's end up to 900; a chunk's eight steps 300) is put off while it is not needed: every lane with
-// mass has its largest value within [2^kEasyLow, 2^kEasyHigh] of its frame, and no frame lies more than kSmoothFrames a pair below the frame of the
-// lane below it.  Until the next look, after n steps with ratios within 2^-g .. 2^g, a value is at least 2^(kEasyLow - n g), and
-// at most 2^(kEasyHigh + n (kSmoothFrames + g + 1.6)).  A chunk, g = 79: 2^-982 and 2^936; kSteepSteps, g = 100, kSteepSmoothFrames: 2^-750 and 2^1005.
-// Where all probabilities of the utterance are above 2^kGentleMinLog2 (g = 32) the look is taken kLookAhead steps before the chunk ends, and the range is wider.  (Looked at
-// after blocks of 16 frames, what is admissible is so narrow that the lanes above the front of the lattice renewed at every second block.)
-// Rough utterances are looked at then too, in a range that is narrower for it; steep ones when the steps are done.
+// mass has its largest value within [2^low, 2^high] of its frame, and no frame lies more than `smooth` a pair below the frame of the lane below it.  Until the next renewal can be
+// had, n steps later with ratios within 2^-g .. 2^g, a value is at least 2^(low - n g), and at most 2^(high + n (smooth + g + 1.6)).  Each class of utterances has its own range:
+//   gentle (all probabilities above 2^kGentleMinLog2, g = 32): kGentleLow, kGentleHigh, kGentleSmooth, looked at kLookAhead steps before a chunk ends, n = 9; a lane that takes
+//     states handed up may have scaled them by 2^-kShiftDown to 2^kShiftUp since: 2^-1018 and 2^966.  (Looked at after blocks of 16 frames, what is admissible is so narrow that the
+//     lanes above the front of the lattice renewed at every second block.)
+//   rough (above 2^kRoughMinLog2, g = 79): kRoughLow, kRoughHigh, kSmoothFrames, looked at as early, n = 9: 2^-1021 and 2^1021
+//   steep (g = 100): kEasyLow, kEasyHigh, kSteepSmoothFrames, looked at when kSteepSteps steps are done, n = 4: 2^-750 and 2^1005
+// And after a renewal, n = 8 (steep: 4) steps: see above.
+// (Rough ones, smooth / high: 28 / 44, 20 / 116 and 16 / 152 are as far as 24 / 80 goes; 64 x 750 x 29 of deviation 4 52.0, 51.6 and 52.8 us a call where this took 51.1.)
 // Where a gentle one's renewal puts the largest value of a window: 2^kHeadroom below its frame, as values grow more often than they shrink.  (For rough ones, whose
 // lanes hold states further apart, it made more of them strained: 64 x 750 frames, logits of deviation 6, 52 us a call, 81 with it.)
 constexpr int kHeadroom = 100;
@@ -1926,16 +1929,11 @@ constexpr int kSmoothFrames = 24, kSteepSmoothFrames = 125;
 constexpr int kGentleLow = -450, kGentleHigh = 120, kGentleSmooth = 36;
 constexpr int kRoughLow = -310, kRoughHigh = 80;
 constexpr int kShiftUp = 220, kShiftDown = 280;
-constexpr bool frames_last(int steps, float min_log2, int smooth, int low = kEasyLow, int high = kEasyHigh)
-{
-    const float small = steps * min_log2, large = steps * (1.6f - min_log2);
-    return small - kFrameSlack >= -1022 && kFrameDrop + large < 1023 && low + small >= -1022 && high + large + steps * smooth < 1023;
-}
-static_assert(frames_last(kChunk + kLookAhead, kGentleMinLog2, kGentleSmooth, kGentleLow - kShiftDown, kGentleHigh + kShiftUp), "a gentle one's chunk");
-static_assert(frames_last(kChunk, kRoughMinLog2, kSmoothFrames), "a chunk");
-static_assert(kRoughLow + (kChunk + kLookAhead) * kRoughMinLog2 >= -1022 && kRoughHigh + (kChunk + kLookAhead) * (1.6f - kRoughMinLog2 + kSmoothFrames) < 1023,
-              "a rough one's chunk, from look to renewal");
-static_assert(frames_last(kSteepSteps, kLinearMinLog2, kSteepSmoothFrames), "a steep one's steps");
+constexpr bool renewal_lasts(int steps, float min_log2) { return steps * min_log2 - kFrameSlack >= -1022 && kFrameDrop + steps * (1.6f - min_log2) < 1023; }
+constexpr bool look_lasts(int steps, float min_log2, int smooth, int low, int high) { return low + steps * min_log2 >= -1022 && high + steps * (1.6f - min_log2 + smooth) < 1023; }
+static_assert(renewal_lasts(kChunk, kGentleMinLog2) && look_lasts(kChunk + kLookAhead, kGentleMinLog2, kGentleSmooth, kGentleLow - kShiftDown, kGentleHigh + kShiftUp), "gentle");
+static_assert(renewal_lasts(kChunk, kRoughMinLog2) && look_lasts(kChunk + kLookAhead, kRoughMinLog2, kSmoothFrames, kRoughLow, kRoughHigh), "rough");
+static_assert(renewal_lasts(kSteepSteps, kLinearMinLog2) && look_lasts(kSteepSteps, kLinearMinLog2, kSteepSmoothFrames, kEasyLow, kEasyHigh), "steep");
 // Does a renewal leave a lane's first blank below 2^kStrained of its new frame?  (`rise`: from the frame it had.  A lane without mass has a blank of 0, whose
 // exponent reads 0.)  What is above keeps all its bits until the next renewal: 2^(kStrained + kLinearMinLog2) is above fp64's smallest normal number.
 // (The look costs, with the gradient's, renew_pairs: 64 x 750 frames, 29 symbols 45.9 -> 46.3 us a call, cost only 28.2 -> 28.8, 512 x 750 114.2 -> 116.0, one
@@ -2273,7 +2271,7 @@ __device__ __forceinline__ ChainEnd run_chain_linear(const Utt m, const int u, c
     // One step.  The blank state sums its own value and the label of the pair before; the label state
     // its own value, the old blank and, where the skip is allowed, that label too:
     //   label' = fma(previous label, skip, label + blank) * emission.
-    // Seven instructions, issued one every 4.1 clocks in the order of the statements (pin keeps the compiler from moving them; one
+    // Seven instructions, issued one every five clocks in the order of the statements (pin keeps the compiler from moving them; one
     // that reads the result of the one before it waits another clock).  The shift needs its operand two instructions old.
     auto pin = []() { __builtin_amdgcn_sched_barrier(0); };
     auto advance = [&](double& el_d, float next_el) __attribute__((always_inline)) {
@@ -4630,7 +4628,7 @@ static bool shares_blocks(const Launch& p)
 // compute units are free do: it is time that they have.  And in launches of their own those of few blocks, which last as long as a block
 // takes (300 x 60 x 29 24.9 us a call, from the cache 25.7; 512 x 45 x 29 27.8 and 29.1).
 static bool staged_emissions(const Launch& p) { return p.fused ? p.n_chains <= p.n_cu : shares_blocks(p); }
-// The gradient's workgroups: what they get, how many there are (in args.groups per utterance) and their LDS.
+// The gradient's workgroups: what they get, how many there are (narrow: by segment, args.segment_groups; wide: args.groups per utterance) and their LDS.
 static TileArgs tile_args(const Launch& p, size_t* lds)
 {
     TileArgs g{};

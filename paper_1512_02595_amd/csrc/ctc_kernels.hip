@@ -1926,6 +1926,13 @@ constexpr int kEasyLow = -350, kEasyHigh = 99;
 constexpr int kSmoothFrames = 24, kSteepSmoothFrames = 125;
 // Gentle utterances.  States handed up are taken into the frames of the lanes that take them where those are no more than kShiftUp below and kShiftDown above the frames that they
 // come in: a chunk later 2^-1018 and 2^966 at worst.  (In the frames that they come in, all factors between frames had to be made anew whenever a wavefront below had renewed its own.)
+// That is for a lane's largest value.  A first blank, of which a renewal allows 2^kStrained, would be rounded by more than 2^-90.  It is not where the lane had mass when its frame was set:
+// a blank never falls, so what that renewal found above 2^kStrained of the frame still is.  A lane without mass takes what has come up within the 32 frames since the last
+// hand-over.  At the first look after it has, eight steps at most, its blank is 2^-714 of a frame that needs no renewal.  For less the largest of its window must have gained 2^600 on it
+// since, and then hands that on to the next blank, which does not fall either; a path by the blank that is lost here can gain on those no more than 2^32 a frame, for half of the
+// frames until the next hand-over puts it right, 2^512.  (kShiftDown of 90: half as many unusual block ends again to twice as many; 32 x 1500 x 29 111.1 us a call, 107.4 with 280.  Lanes
+// left at 2^-710 instead: utterances that hold symbols for 60 frames at 6 nats 187, 177.  Replayed on the CPU, symbols held and dropped at 2^31 to their blank for 4 to 40 frames, none
+// came below 2^-651.)
 constexpr int kGentleLow = -450, kGentleHigh = 120, kGentleSmooth = 36;
 constexpr int kRoughLow = -310, kRoughHigh = 80;
 constexpr int kShiftUp = 220, kShiftDown = 280;
@@ -1943,6 +1950,7 @@ static_assert(renewal_lasts(kSteepSteps, kLinearMinLog2) && look_lasts(kSteepSte
 // logits of deviation 4, which seldom strain a lane.)
 constexpr int kStrained = -900;
 static_assert(kStrained + kLinearMinLog2 >= -1022, "what a first blank of 2^kStrained gives its label");
+static_assert(kGentleLow + kChunk * (kGentleMinLog2 - 1) - kShiftDown >= -1022, "what a shift leaves of a blank whose label has come up since the last look");
 // (of_label: lanes behind the label's end hold nothing that anybody needs.)
 __device__ __forceinline__ bool strains(double first, int rise, bool of_label) { return __ballot(of_label && __builtin_amdgcn_frexp_exp(first) + rise < kStrained) != 0; }
 // The test, on the exponent of the largest value of a lane: one subtraction and one unsigned compare.  Lanes without mass pass it.

@@ -64,7 +64,8 @@ class Chain:
         self.shift_down, self.shift_up = (k["kShiftDown"], k["kShiftUp"]) if gentle else (0, 0)
         self.strained_below = k["kGentleStrained"] if gentle and "kGentleStrained" in k else k["kStrained"]
         self.exchange = 0 if waves == 1 else (1 if pairs * halo < 32 else 2)     # blocks between hand-overs
-        self.renewals = self.unusual = self.flushed = 0
+        self.renewals = self.unusual = 0
+        self.lowest = 0                                  # exponent of the least first blank that a shift down has left, before any wavefront would have left the recursion
         self.strained = self.overflowed = False
         with np.errstate(over="ignore", under="ignore", invalid="ignore"):
             self.run(blocks)
@@ -137,9 +138,9 @@ class Chain:
             handed = (self.blank[w, up].copy(), self.label[w, up].copy(), self.frame[w, up].copy(), due and unusual)
             if w > 0:
                 shift = (frame - self.frame[w, :halo])[:, None]
-                # (a state of the label's that the shift rounds; what a lane without mass at all holds is 0 before and after)
-                for v, counts in ((blank, self.pair[w, :halo] <= self.L), (label, self.pair[w, :halo] < self.L)):
-                    self.flushed += int((counts & (v > 0) & (np.ldexp(np.ldexp(v, shift), -shift) != v)).sum())
+                lower = (self.first[w, :halo] <= self.L) & (blank[:, 0] > 0) & (shift[:, 0] < 0)
+                if lower.any() and not self.strained:
+                    self.lowest = min(self.lowest, int((np.frexp(blank[:, 0])[1] + shift[:, 0])[lower].min()))
                 self.blank[w, :halo], self.label[w, :halo] = np.ldexp(blank, shift), np.ldexp(label, shift)
         self.handed[w] = handed
         self.unusual += unusual

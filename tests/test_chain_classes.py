@@ -62,3 +62,32 @@ def test_each_class_notices_states_that_its_frames_do_not_hold(hold, depth, blan
     kind = "gentle" if depth / np.log(2) < 25 else "rough"
     for chain, want in chains(batch, kind):
         assert chain.strained or abs(chain.cost - want) <= 1e-6 * abs(want) + 1e-9, (chain.L, chain.cost, want)
+
+
+def held_and_dropped(seed, L, symbols, T=420, B=4):
+    """For 4 to 40 frames at a time some symbols at 2^31 to the blank, or at 2^-31, and the others as probable as it."""
+    rng = np.random.default_rng([seed, L, symbols])
+    batch = batch_of([T] * B, [L] * B, symbols + 1, seed=seed)
+    batch.logits[:] = rng.normal(0, 0.05, batch.logits.shape)
+    for b in range(B):
+        t = 0
+        while t < T:
+            frames, up = int(rng.integers(4, 41)), rng.random() < 0.5
+            some = np.nonzero(rng.random(symbols) < rng.choice([0.2, 0.5, 0.9]))[0] + 1
+            batch.logits[t:t + frames, b, some] += (31 if up else -31) * np.log(2)
+            t += frames
+    return batch
+
+
+def test_a_shift_rounds_no_blank():
+    """Of the states that are taken by a shift a lane's first blank is the least; what it gives its label in the next step is 2^-32 of it at worst."""
+    lowest = []
+    for seed in range(6):
+        for x, label, blank, _ in utterances_of(held_and_dropped(seed, 60 + 30 * (seed % 3), 2 + seed % 4)):
+            for pairs, halo in ((1, 16), (1, 32), (2, 8), (2, 16)):
+                lanes = (len(label) + pairs) // pairs
+                waves = max(2, -(-(lanes - halo) // (64 - halo)))
+                lowest += [Chain(x, label, blank, "gentle", pairs, waves, halo, backward).lowest for backward in (False, True)]
+    print(f"  lowest first blanks after a shift: 2^{sorted(lowest)[:5]}")
+    assert min(lowest) >= -1022 + 32
+    assert min(lowest) < -500                            # (these inputs ask for it)

@@ -61,8 +61,8 @@ struct WavePlan {
 // Wavefronts and halo width for a label of this length.  Fitted to log-domain chains on gfx950: with one
 // wavefront per SIMD (up to 4) a step costs about 210 clocks and a hand-over about 500; with
 // several per SIMD the vector ALU is the limit (about 170 clocks per wavefront-step) and part
-// of a hand-over's latency hides behind the other wavefronts (about 350).  (The linear domain's steps, which share the plans, take 38 to 51
-// clocks at most a wavefront to a SIMD, 44 to 110 with all that comes at the ends of blocks: its plans have not been fitted to that.)
+// of a hand-over's latency hides behind the other wavefronts (about 350).  (The linear domain's steps, which share the plans, take 35 to 60
+// clocks at most a wavefront to a SIMD, 45 to 85 with all that comes at the ends of blocks: its plans have not been fitted to that.)
 // (Host and device: the launcher plans on the host, the device-metadata entry point on the GPU.)
 // `crowded`: the launch has more wavefronts than the chip runs side by side at one per SIMD, so
 // what counts is the total work (wavefront-steps plus hand-overs), not one chain's latency.
@@ -289,7 +289,7 @@ inline bool gradient_beside_long_chains(double early, double late, double chain_
     return 1.5 * late / n_cu + 18.0 * busy <= saved + 0.4 * early / n_cu * (1.0 - busy);
 }
 // What a chain of this many wavefronts took for a frame, in microseconds, when the rule above was fitted (up to four run on a SIMD each).
-// The steps of a linear-domain chain take about half of that now, 0.018, 0.024 to 0.038 and 0.043; the rule divides by these.
+// The steps of a linear-domain chain take about half of that now, 0.019, 0.023 to 0.035 and 0.055; the rule divides by these.
 inline double chain_us_per_frame(int waves) { return waves == 1 ? 0.045 : (waves <= 4 ? 0.06 : 0.088); }
 
 // The rule that launches follow.  Random batches, three of a kind in turn:

@@ -1897,8 +1897,9 @@ __device__ __forceinline__ const Args& args_again()
 // Storage (Mode::kGrad): the whole state after every block (see "lattice storage").
 //
 // What a step costs (a lone wavefront of a chain issues an instruction every five clocks, whatever it is): 7 instructions and 35 clocks, 12 and 60
-// where a lane owns two pairs; the rest is what a block's end adds.  Clocks a step (2.4 GHz) of the last wavefront, 750 frames, alone on the chip, labels of 40 / 127 /
-// 190 / 240 / 420 symbols: 48 / 69 / 85 / 98 / 134 when a hand-over took 550 clocks, a look at the frames 100 and a checkpoint 110; so 44 / 59 / 71 / 93 / 111.
+// where a lane owns two pairs; the rest is what a block's end adds.  Clocks a step (2.4 GHz; 1500 frames less 750, alone on the chip), labels of 40 / 127 / 190 / 240 /
+// 420 symbols: 48 / 65 / 74 / 87 / 100 when a hand-over took 550 clocks, a look at the frames 100 and a checkpoint 110; so 45 / 56 / 62 / 78 / 85.  Logits doubled (rough
+// utterances): 52 / 73 / 83 / 96 / 113, so 46 / 64 / 71 / 88 / 104.
 constexpr int kFrameSlack = 390, kFrameDrop = 370;
 __device__ __forceinline__ int lane_frame(int window_top, int own_top)
 {
@@ -2032,7 +2033,7 @@ struct ChainFrames {
 // unusual: whoever has asked too early asks again until it is there, and then waits a little more, so as not to be early at every block from then on;
 // frames are taken over from below; frames are renewed.  LDS operations of a wavefront complete in order: a tag is read before the states, and written after
 // them.  (A hand-over took 550 clocks when it was asked for at the block's end, two counters one after the other, and made all factors between frames anew; now 180.
-// Unusual ends: 2 of 47 in the lowest wavefront of a label of 190 symbols, 10 in the highest.)
+// Unusual ends, replayed on the CPU: 1 of 47 in the lowest wavefront of a label of 190 symbols, 5 in the others; of a rough utterance 11, and 37.)
 constexpr int kSlack = 2;                                // (s_sleep: 64 clocks each)
 constexpr int kAskAhead = 5, kAskAhead2 = 4;             // steps before the block's end, with one pair to a lane and with two
 template <int kPairs>

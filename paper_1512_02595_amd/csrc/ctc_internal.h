@@ -389,12 +389,12 @@ CTC_HOST_DEVICE inline ChainForm chain_form(int flags, bool best)
 // What an utterance weighs in the orders of chains and of ends: how long its chains take, a frame's time in ns (the difference between 1500 frames and 750, alone on the chip),
 // where a chain has SIMDs of its own; in crowded launches, where what counts is how much they keep SIMDs busy, frames times wavefronts.  (By frames times wavefronts throughout,
 // an utterance of two wavefronts with two pairs to a lane, which lasts longest, was taken to end early.)  Measured with 1 / 2 / 3 / 4 / 5 and 6 / 7 and 8 / 10 to 12 wavefronts:
-// one pair 20 / 23 / 22 / 23; two pairs - / 31 / 31 / 31 / 55; logarithms 101 / 109 / 111 / 115 / 197 / 196 / 287; alignments 51 / 59 / 60 / 65 / 87 / 89 / 120.
+// one pair 20 / 23 / 22 / 22 to 26 (rough utterances 20 / 25 / 25 / 28 to 30); two pairs - / 31 / 31 / 31 / 55; logarithms 101 / 109 / 111 / 115 / 197 / 196 / 287; alignments 51 / 59 / 60 / 65 / 87 / 89 / 120.
 CTC_HOST_DEVICE inline int64_t chain_weight(int frames, int waves, ChainForm form, bool crowded)
 {
     if (crowded) return static_cast<int64_t>(frames) * waves;
     const int per_simd = (waves + 3) / 4;
-    int per_frame = waves <= 1 ? 20 : 23;
+    int per_frame = waves <= 1 ? 20 : (waves <= 3 ? 23 : 26);
     if (form == ChainForm::kTwoPairs) per_frame = waves <= 4 ? 31 : 55;
     if (form == ChainForm::kLogs) per_frame = waves <= 4 ? 97 + 4 * waves : 97 * per_simd;
     if (form == ChainForm::kBest) per_frame = waves <= 4 ? 47 + 5 * waves : 20 + 34 * per_simd;

@@ -491,7 +491,7 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
     auto weight = [&](int i) { return ~by_weight[i] >> 16; };
     for (int i = 0; i < n_run && n_run * dirs <= out->n_cu && 100 * weight(i) >= 85 * weight(0); ++i)
         late_blocks += static_cast<int64_t>(frame_blocks(run_frames[i])) * std::max(1, label_pieces(meta[running[i]].L));
-    out->share_last = blocks_to_share(late_blocks, n_run * dirs, out->n_cu);
+    out->share_last = blocks_to_share(late_blocks, c.A, n_run * dirs, out->n_cu);
     out->folded = c.A <= kDirectMaxA && c.B <= kNarrowMaxB && c.T < (1 << 29);
     out->lay = lay;
     return CTC_STATUS_SUCCESS;
@@ -662,7 +662,7 @@ ctc_status_t run_device(const void* x, const int32_t* labels, const int32_t* lab
     p.poll_budget = g_poll_budget.load(std::memory_order_relaxed);
     p.end_polls = g_end_polls.load(std::memory_order_relaxed);
     p.n_cu = compute_units();
-    p.share_last = blocks_to_share(-1, p.n_chains, p.n_cu);
+    p.share_last = blocks_to_share(-1, A, p.n_chains, p.n_cu);
     // (how much padding there is only the GPU knows: taken for a third of the tensor)
     p.defer = grads && A > kDirectMaxA && !p.needs_barrier
                   ? deferred_frames(static_cast<double>(T) * B * A * elem / 3, T / 2, p.n_chains, p.n_cu) : 0;

@@ -312,18 +312,20 @@ inline bool gradient_in_lattice_launch(double early, double late, double chain_u
 }
 
 // Narrow alphabets, gradients whose blocks are not all shared by several wavefronts: of how many blocks times pieces, at most, those are which are, in the utterances that end last.
-// By then compute units are free, and a label of five pieces keeps one wavefront to a block for 18 us after its chains have ended: us a call with none / 2048 / 4096 / 8192,
-// 32 x 1500 x 29 122.9 / 111.6 / 111.6 / 111.2; the same, lengths from 400 on, 120.3 / 109.0 / 108.8 / 108.5; 128 x 750 x 29 49.2 / 45.3 / 45.1 / 45.0.  But not where those that
-// end in the last 15 % of the time have as many as the chip has places for wavefronts (`late`, in blocks times pieces; the batches above have up to 3000): then a shared block
-// only costs more places.  64 utterances of 750 frames and 225 symbols 61.8 / 64.3 / 67.3 / 72.3, 128 of them 82.1 / 84.3 / 86.6 / 92.6, 32 of 1500 frames and 540 symbols 152.7 /
-// 157.3 / 166.8 / 166.1 (48 of 1500 and 400 116.5 / 116.4 / 118.0 / 119.9; 64 of 900 and 400 94.5 / 88.8 / 90.5 / 91.0).
-// With more chains than compute units, whose blocks are still under way, or where the lengths are not known here (late < 0), in between: 512 x 750 x 29 105.7 / 104.6 / 106.0 / 107.0;
-// lengths on the GPU, 100 x 1000 x 29 67.7 / 61.2 / 61.9 / 66.5, 64 x 750 with labels of up to 270 symbols 68.0 / 66.9 / 70.5 / 70.5.
-constexpr int kShareLast = 8192, kShareSome = 2048, kLateFillsChip = 4096;
-inline int blocks_to_share(int64_t late, int n_chains, int n_cu)
+// By then compute units are free, and a label of five pieces keeps one wavefront to a block for 18 us after its chains have ended: us a call with none / 1024 / 2048 / 4096 / 8192,
+// 32 x 1500 x 29 122.1 / 118.7 / 109.9 / 109.8 / 109.5 (logits tripled: 2048 563, 8192 526); the same, lengths from 400 on, 119.3 / 107.5 / 108.2 / 107.7 / 108.0; 128 x 750 x 29 48.5 / 45.7 /
+// 45.1 / 44.7 / 44.8; 128 x 768 x 29 with 0.3 symbols a frame 56.2 / 50.2 / 49.5 / 51.5 / 53.9.  With four tiles of symbols in place of two a shared block has twice as much to add up:
+// 32 x 1500 x 60 134.6 / 134.1 / 129.4 / 137.1 / 148.7; 128 x 750 x 40 52.1 / 50.9 / 52.4 / 53.1 / 55.1; 128 x 768 x 37 with 0.3 symbols a frame 59.3 / 56.0 / 58.3 / 61.9 / 69.1.
+// None where those that end in the last 15 % of the time have more than the chip has places for wavefronts (`late`, in blocks times pieces; the batches above have up to 3000): then a shared block
+// only costs more places.  64 utterances of 750 frames and 225 symbols 61.8 / 62.5 / 64.3 / 67.3 / 72.3, 128 of them 82.1 / 81.9 / 84.3 / 86.6 / 92.6, 32 of 1500 frames and 540 symbols 152.7 /
+// 157.1 / 157.3 / 166.8 / 166.1 (48 of 1500 and 400 116.5 / 116.6 / 116.4 / 118.0 / 119.9; 64 of 900 and 400 94.5 / 88.6 / 88.8 / 90.5 / 91.0).
+// With more chains than compute units, whose blocks are still under way: 512 x 750 x 29 105.7 / 104.8 / 104.6 / 106.0 / 107.0; where lengths are not known here (late < 0):
+// 100 x 1000 x 29 67.7 / 64.8 / 61.2 / 61.9 / 66.5, 64 x 750 with labels of up to 270 symbols 68.0 / 66.9 / 66.9 / 70.5 / 70.5.
+constexpr int kShareLast = 4096, kShareSome = 2048, kLateFillsChip = 4096;
+inline int blocks_to_share(int64_t late, int A, int n_chains, int n_cu)
 {
     if (n_chains > n_cu || late < 0) return kShareSome;
-    return late <= kLateFillsChip ? kShareLast : 0;
+    return late > kLateFillsChip ? 0 : (A <= 32 ? kShareLast : kShareSome);
 }
 
 constexpr int kDoneStride = 16;      // words between two utterances' words: a line each for those who poll

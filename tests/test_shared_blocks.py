@@ -12,8 +12,8 @@ PROGRAM = r"""
 int main()
 {
     long late;
-    int chains;
-    while (std::scanf("%ld %d", &late, &chains) == 2) std::printf("%d\n", ctc::blocks_to_share(late, chains, 256));
+    int A, chains;
+    while (std::scanf("%ld %d %d", &late, &A, &chains) == 3) std::printf("%d\n", ctc::blocks_to_share(late, A, chains, 256));
 }
 """
 
@@ -24,16 +24,18 @@ def rule(tmp_path_factory):
     (d / "rule.cpp").write_text(PROGRAM)
     subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_1512_02595_amd", "csrc"),
                     str(d / "rule.cpp"), "-o", str(d / "rule")], check=True)
-    return lambda late, chains: int(subprocess.run([str(d / "rule")], input=f"{late} {chains}", capture_output=True, text=True, check=True).stdout)
+    return lambda late, A, chains: int(subprocess.run([str(d / "rule")], input=f"{late} {A} {chains}", capture_output=True, text=True, check=True).stdout)
 
 
 @pytest.mark.parametrize("utterances,frames,symbols,pieces", [(64, 750, 225, 3), (128, 750, 225, 3), (128, 750, 300, 3), (32, 1500, 540, 6), (48, 1500, 400, 4), (128, 750, 130, 2)])
 def test_utterances_that_end_together_share_nothing(rule, utterances, frames, symbols, pieces):
     """us a call, none shared and 8192 blocks times pieces: 61.8 and 72.3, 82.1 and 92.6, 92.5 and 101.8, 152.7 and 166.1, 116.5 and 119.9, 62.5 and 66.9."""
-    assert rule(utterances * ((frames + 15) // 16) * pieces, 2 * utterances) == 0
+    assert rule(utterances * ((frames + 15) // 16) * pieces, 29, 2 * utterances) == 0
 
 
-@pytest.mark.parametrize("late,chains,share", [(2847, 64, 8192), (2770, 64, 8192), (1305, 256, 8192), (4096, 256, 8192), (4097, 256, 0), (2000, 258, 2048), (-1, 64, 2048), (-1, 1024, 2048)])
-def test_mixed_batches(rule, late, chains, share):
-    """32 x 1500, lengths from 1200 and from 400 on, and 128 x 750: 122.9 and 111.2, 120.3 and 108.5, 49.2 and 45.0; crowded launches and unknown lengths in between."""
-    assert rule(late, chains) == share
+@pytest.mark.parametrize("late,A,chains,share", [(2847, 29, 64, 4096), (1305, 32, 256, 4096), (4096, 29, 256, 4096), (4097, 29, 256, 0), (1162, 37, 256, 2048), (1104, 60, 64, 2048), (4097, 60, 64, 0),
+                                                 (2000, 29, 258, 2048), (-1, 29, 64, 2048), (-1, 40, 1024, 2048)])
+def test_mixed_batches(rule, late, A, chains, share):
+    """us a call with none, this many and 8192: 32 x 1500 x 29 122.1, 109.8, 109.5; 128 x 750 x 29 48.5, 44.7, 44.8; 128 x 768 x 37 59.3, 58.3, 69.1; 32 x 1500 x 60 134.6, 129.4, 148.7.
+    Crowded launches and unknown lengths: 2048."""
+    assert rule(late, A, chains) == share

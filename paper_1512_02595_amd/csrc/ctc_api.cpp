@@ -431,16 +431,19 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
         for (int b = 0; b < c.B; ++b)
             if (!(meta[b].flags & kUttRuns)) *by_end++ = b;
     for (int i = n_run - 1; i >= 0; --i) *by_end++ = running[i];
+    const bool narrow_gradient = c.mode == Mode::kGrad && c.A <= kDirectMaxA;
     thread_local std::vector<int32_t> frames_by_end;
-    frames_by_end.assign(static_cast<size_t>(c.B), 0);
-    for (int i = 0; i < n_run; ++i) frames_by_end[c.B - 1 - i] = run_frames[i];
+    if (narrow_gradient) {
+        frames_by_end.assign(static_cast<size_t>(c.B), 0);
+        for (int i = 0; i < n_run; ++i) frames_by_end[c.B - 1 - i] = run_frames[i];
+    }
 
     const bool sequential_chains = c.mode == Mode::kGrad && g_sequential_chains.load(std::memory_order_relaxed) != 0;
 
     if (c.ws_bytes < lay.total) return CTC_STATUS_WORKSPACE_TOO_SMALL;
 
     out->mode = c.mode;
-    out->frames_by_end = frames_by_end.data();
+    out->frames_by_end = narrow_gradient ? frames_by_end.data() : nullptr;
     out->T = c.T; out->B = c.B; out->A = c.A; out->blank = c.blank;
     out->dtype = c.dtype;
     out->n_run = n_run;
@@ -489,7 +492,7 @@ ctc_status_t prepare(const Call& c, const Layout& lay, Launch* out, char* image)
     // Blocks times pieces of the utterances whose chains end in the last 15 % of the time (a question of up to a chain per compute unit: blocks_to_share).
     int64_t late_blocks = 0;
     auto weight = [&](int i) { return ~by_weight[i] >> 16; };
-    for (int i = 0; i < n_run && n_run * dirs <= out->n_cu && 100 * weight(i) >= 85 * weight(0); ++i)
+    for (int i = 0; i < n_run && narrow_gradient && n_run * dirs <= out->n_cu && 100 * weight(i) >= 85 * weight(0); ++i)
         late_blocks += static_cast<int64_t>(frame_blocks(run_frames[i])) * std::max(1, label_pieces(meta[running[i]].L));
     out->share_last = blocks_to_share(late_blocks, c.A, n_run * dirs, out->n_cu);
     out->folded = c.A <= kDirectMaxA && c.B <= kNarrowMaxB && c.T < (1 << 29);

@@ -394,13 +394,12 @@ CTC_HOST_DEVICE inline ChainForm chain_form(int flags, bool best)
 // one pair 20 / 23 / 22 / 22 to 26 (rough utterances 20 / 25 / 25 / 28 to 30); two pairs - / 31 / 31 / 31 / 55; logarithms 101 / 109 / 111 / 115 / 197 / 196 / 287; alignments 51 / 59 / 60 / 65 / 87 / 89 / 120.
 CTC_HOST_DEVICE inline int64_t chain_weight(int frames, int waves, ChainForm form, bool crowded)
 {
-    if (crowded) return static_cast<int64_t>(frames) * waves;
-    const int per_simd = (waves + 3) / 4;
-    int per_frame = waves <= 1 ? 20 : (waves <= 3 ? 23 : 26);
+    const int up_to_four = waves < 4 ? waves : 4, per_simd = (waves + 3) / 4;
+    int per_frame = (0x1A171714 >> (8 * up_to_four - 8)) & 255;        // 20, 23, 23, 26
     if (form == ChainForm::kTwoPairs) per_frame = waves <= 4 ? 31 : 55;
-    if (form == ChainForm::kLogs) per_frame = waves <= 4 ? 97 + 4 * waves : 97 * per_simd;
+    if (form == ChainForm::kLogs) per_frame = 97 * per_simd + (waves <= 4 ? 4 * waves : 0);
     if (form == ChainForm::kBest) per_frame = waves <= 4 ? 47 + 5 * waves : 20 + 34 * per_simd;
-    return static_cast<int64_t>(frames) * per_frame;
+    return static_cast<int64_t>(frames) * (crowded ? waves : per_frame);
 }
 CTC_HOST_DEVICE inline int64_t chain_weight(const Utt& m, bool best, bool crowded)
 {

@@ -919,12 +919,15 @@ struct NarrowDevice {
 
 // Weight of an utterance in the run order (chain_weight; 0: its lengths are out of range).  Every utterance's setup weighs all of them, by their lengths alone: tight fits that
 // only repeated neighbours make weigh as if they ran on probabilities.
+// (Few instructions: of a batch of short utterances the setup is the softmax launch's longest, and takes 5 clocks for each.  64 x 93 x 30, lengths from 11 on, that launch 5.05 us with frames times
+// wavefronts, 5.4 with each form's time in branches, so 5.2.)
 __device__ __forceinline__ long long weight_of(const PlanTable& plans, int L, int Tb, int Tt, int max_label, bool log_domain, bool crowded)
 {
-    if (L < 0 || L > max_label || Tb < 0 || Tb > Tt) return 0;
+    const bool in_range = L >= 0 && L <= max_label && Tb >= 0 && Tb <= Tt;
+    const int one = plans.one[in_range ? L : 0], two = plans.two[in_range ? L : 0];      // (both at once: one after the other took a trip to memory more)
     const bool logs = log_domain || Tb > kLinearMaxFrames || tight_fit(Tb, L, 0);
-    const ChainForm form = chain_form((logs ? kUttLogDomain : 0) | (plans.two_pairs(L) ? kUttTwoPairs : 0), false);
-    return chain_weight(Tb, form == ChainForm::kTwoPairs ? plans.waves2(L) : plans.waves1(L), form, crowded);
+    const ChainForm form = chain_form((logs ? kUttLogDomain : 0) | ((one & 128) ? kUttTwoPairs : 0), false);
+    return in_range ? chain_weight(Tb, ((form == ChainForm::kTwoPairs ? two : one) & 15) + 1, form, crowded) : 0;
 }
 // By the whole workgroup.  Returns the record (the same in every thread).
 __device__ __forceinline__ Utt build_record(const NarrowDevice& dv, const PlanTable& plans, int b, int Tt, int B, int A,

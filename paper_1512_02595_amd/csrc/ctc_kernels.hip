@@ -2245,9 +2245,11 @@ __device__ __forceinline__ ChainEnd run_chain_linear(const Utt m, const int u, c
         outside = __ballot(f.easy.outside(top_value()));
         if (exchange) with.look(f.frame);
     };
-    // (Nothing here is said to be unlikely: what is goes to the kernel's end, further away than a branch reaches, and rough utterances take it at every other block.  us a call with
-    // it there, and so: 64 x 750 x 29 41.1 and 41.3, logits of deviation 4 51.3 and 49.3, of 6 55.0 and 52.7, cost only 25.7 and 25.6, 32.3 and 31.5, 33.4 and 32.8; 32 x 1500 x 29 107.5 and
-    // 108.2, 122.4 and 120.8; one utterance of 750 frames 32.4 and 32.3, 40.6 and 38.6.)
+    // (With hand-overs nothing here is said to be unlikely: what is goes to the kernel's end, further away than a branch reaches, and rough utterances take it at every other block.  us a call
+    // with it there, and so: 64 x 750 x 29 41.1 and 41.3, logits of deviation 4 51.3 and 49.3, of 6 55.0 and 52.7, cost only 25.7 and 25.6, 32.3 and 31.5, 33.4 and 32.8; 32 x 1500 x 29
+    // 107.5 and 108.2, 122.4 and 120.8; one utterance of 750 frames 32.4 and 32.3, 40.6 and 38.6.  A wavefront by itself renews seldom, and it is unlikely there: cost only 25.6 and
+    // 25.2 with it at the end.)
+    auto seldom = [](bool unusual) __attribute__((always_inline)) { return kExchange ? unusual : static_cast<bool>(__builtin_expect(unusual, 0)); };
     auto end_block = [&](int block, bool exchange, int unit) __attribute__((always_inline)) {
         const bool unusual = (outside | f.rough | look | (exchange ? with.late | with.shifted : 0ull)) != 0;
         if (exchange && unusual) with.prepare(block, (outside | f.rough) != 0, f.frame, budget, lost);
@@ -2261,7 +2263,7 @@ __device__ __forceinline__ ChainEnd run_chain_linear(const Utt m, const int u, c
                 asm volatile("" : "+v"(v_blank), "+v"(v_label));      // (a mask, and not a choice for each)
             }
         }
-        if (unusual) {
+        if (seldom(unusual)) {
             const double top = top_value();
             if (exchange) with.number &= ~1;
             bool renews = __ballot(f.easy.outside(top)) != 0;      // (then the factors between the frames are made there)
@@ -2324,7 +2326,7 @@ __device__ __forceinline__ ChainEnd run_chain_linear(const Utt m, const int u, c
             if (q == kChunk - 1 - kLookAhead) look_ahead(here);
         }
         if (kEnds) end_block(k >> 1, here, 2 * i + 2);
-        else if ((outside | f.rough | look) != 0) {
+        else if (seldom((outside | f.rough | look) != 0)) {
             if (kSteep) renew_if_due(2 * i + 2);
             else renew_frames(2 * i + 2);
         }
@@ -2442,6 +2444,7 @@ __device__ __forceinline__ ChainEnd run_chain_linear2(const Utt m, const int u, 
         outside = __ballot(f.easy.outside(top_value()));
         if (exchange) with.look(f.frame);
     };
+    auto seldom = [](bool unusual) __attribute__((always_inline)) { return kExchange ? unusual : static_cast<bool>(__builtin_expect(unusual, 0)); };      // (see run_chain_linear)
     auto end_block = [&](int block, bool exchange, int unit) __attribute__((always_inline)) {
         const bool unusual = (outside | f.rough | look | (exchange ? with.late | with.shifted : 0ull)) != 0;
         if (exchange && unusual) with.prepare(block, (outside | f.rough) != 0, f.frame, budget, lost);
@@ -2457,7 +2460,7 @@ __device__ __forceinline__ ChainEnd run_chain_linear2(const Utt m, const int u, 
                 asm volatile("" : "+v"(va_blank), "+v"(va_label), "+v"(vb_blank), "+v"(vb_label));      // (a mask, and not a choice for each)
             }
         }
-        if (unusual) {
+        if (seldom(unusual)) {
             const double top = top_value();
             if (exchange) with.number &= ~1;
             bool renews = __ballot(f.easy.outside(top)) != 0;      // (then the factors between the frames are made there)
@@ -2521,7 +2524,7 @@ __device__ __forceinline__ ChainEnd run_chain_linear2(const Utt m, const int u, 
             if (q == kChunk - 1 - kLookAhead) look_ahead(here);
         }
         if (kEnds) end_block(k >> 1, here, 2 * i + 2);
-        else if ((outside | f.rough | look) != 0) {
+        else if (seldom((outside | f.rough | look) != 0)) {
             if (kSteep) renew_if_due(2 * i + 2);
             else renew_frames(2 * i + 2);
         }
